@@ -149,7 +149,7 @@ ETV_API int32_t etv_tensorize_tree(const int32_t *parent, const int32_t *n_nodes
  *  lse           float [B, Hq, T_max]   natural-log sum of exp of the scaled scores, nullable
  *  workspace     etv_tree_verify_attention_workspace_bytes(h_desc) bytes, 256-byte aligned
  * Supported: dtype F32 or BF16 (fp32 accumulation), d in {64, 128}, Hq % Hkv == 0,
- * 1 <= T_max <= ETV_ATTN_MAX_TREE.  bf16 with d = 128 runs on the MFMA kernel.
+ * 1 <= T_max <= ETV_ATTN_MAX_TREE.  bf16 runs on the MFMA kernel.
  * ------------------------------------------------------------------------- */
 typedef struct etv_attn_desc {
     int32_t B, T_max, Hq, Hkv, d;
@@ -181,7 +181,7 @@ ETV_API size_t etv_tree_verify_attention_workspace_bytes(const etv_attn_desc *h_
  * model fitted on one machine; kv_split and the ETV_ATTN_FLAG_* tuning flags of h_desc override every part of it,
  * and this call shows the outcome, so that a poor pick on another shape or machine can be seen and corrected. */
 typedef struct etv_attn_plan {
-    int32_t mfma;        /* 1: attn_mfma_kernel (bf16, d = 128); 0: the fp32-VALU kernel */
+    int32_t mfma;        /* 1: attn_mfma_kernel (bf16); 0: the fp32-VALU kernel */
     int32_t wavefronts;  /* per workgroup: 4 or 8 (1 for the VALU kernel) */
     int32_t key_halves;  /* 1: two wavefronts per 32-row chunk, each with 32 of a tile's 64 keys */
     int32_t ring_stages; /* K/V tiles of LDS ring */

@@ -2,7 +2,7 @@
 // prefix cache plus the tree's own K/V (Section 3.3, "Execution view" and "Tree attention mask").
 //
 // Two kernels compute the per-split partial (m, l, O):
-//   * attn_mfma_kernel   bf16, d = 128: K/V tiles staged through LDS, QK^T and PV on
+//   * attn_mfma_kernel   bf16: K/V tiles staged through LDS, QK^T and PV on
 //                        v_mfma_f32_32x32x16_bf16, online softmax in registers, the ancestor mask applied
 //                        as a per-row bitmask only on the tree tile.
 //   * attn_generic_kernel  any supported dtype / head dim, fp32 VALU arithmetic, one wavefront per query
@@ -346,7 +346,7 @@ __global__ void __launch_bounds__(256) attn_combine_kernel(AttnParams p) {
 }
 
 // ----------------------------------------------------------------------------------------------
-// MFMA kernel (bf16, d = 128).
+// MFMA kernel (bf16, d = 128 or 64; sizes below for d = 128).
 //
 // Work unit: (split, KV head x row group, sequence).  A workgroup has NW wavefronts (8, or 4 for small
 // trees); wavefront w owns one 32-row chunk of the KV head's packed query rows and all of them share the K/V tiles of
@@ -376,6 +376,11 @@ __global__ void __launch_bounds__(256) attn_combine_kernel(AttnParams p) {
 //                                          B = P^T taken straight from the S^T accumulator registers
 // Both products keep the query index on the accumulator column, so the softmax statistics and the
 // rescale of O never cross lanes.
+//
+// d = 64 runs the same loop on tiles of half the bytes, with two bf16 parts per probability (Geo::NP): half the
+// products per score but the same softmax, so the vector ALU bounds it from T = 32 up.  B = 4 sequences of 900 ... 1500
+// keys, T = 48, 32/8 heads: 20 us (1040 us on the one-row-per-wavefront VALU kernel, which re-read every key row from
+// L2 for each of the G * T query rows); B = 32, P = 4096: T = 8 52 us, T = 32 81 us, T = 128 242 us.
 // ----------------------------------------------------------------------------------------------
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
@@ -386,15 +391,35 @@ typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 typedef __attribute__((address_space(4))) const int32_t *const_i32_ptr;
 
-constexpr int KT = 64;                      // keys per tile
-constexpr int ROW_BYTES = 256;              // one K or V row of a KV head (d = 128, bf16)
-constexpr int TILE_BYTES = KT * ROW_BYTES;  // 16 KiB
-constexpr int STAGE_BYTES = 2 * TILE_BYTES; // K tile then V tile
+constexpr int KT = 64;  // keys per tile
+
+// Sizes that follow from the head dimension (128 or 64).
+template <int D>
+struct Geo {
+    static constexpr int ROW_BYTES = 2 * D;               // one K or V row of a KV head, bf16
+    static constexpr int TILE_BYTES = KT * ROW_BYTES;     // 16 KiB at d = 128
+    static constexpr int STAGE_BYTES = 2 * TILE_BYTES;    // K tile then V tile
+    static constexpr int RPU = 1024 / ROW_BYTES;          // key rows of a 1 KiB load unit (64 lanes x 16 B): 4 or 8
+    static constexpr int CPR = ROW_BYTES / 16;            // 16-byte chunks of a row: 16 or 8
+    static constexpr int KK = D / 16;                     // 16-wide contraction steps of Q . K
+    static constexpr int DB = D / 32;                     // 32-wide output column blocks
+    // bf16 parts of a probability in the PV product.  At d = 64 the products are half as many per score, and a second
+    // part (the remainder of the first) keeps the error of the result that of its own rounding to bf16.
+    static constexpr int NP = D == 64 ? 2 : 1;
+};
 
 __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
     f32x2 v = {a, b};
     bf16x2 r = __builtin_convertvector(v, bf16x2);
     return __builtin_bit_cast(uint32_t, r);
+}
+
+// Two fp32 values as bf16 pairs hi + lo: hi their upper halves, lo the remainders (exact) rounded to bf16, so that
+// hi + lo carries 16 significant bits.
+__device__ __forceinline__ void split_bf16x2(float a, float b, uint32_t &hi, uint32_t &lo) {
+    const uint32_t ua = __float_as_uint(a), ub = __float_as_uint(b);
+    hi = __builtin_amdgcn_perm(ub, ua, 0x07060302u);
+    lo = pack_bf16x2(a - __uint_as_float(ua & 0xffff0000u), b - __uint_as_float(ub & 0xffff0000u));
 }
 
 // acc + the two bf16 values of a packed pair, in fp32: one instruction for two probabilities.  The row sum is
@@ -434,24 +459,29 @@ __device__ __forceinline__ float half_swap_sum(float v) {
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 // chunk-position swizzles (measured on gfx950: 16-byte reads reach the full 256 B/clk only with a 4-bit
-// row term; the 8-byte transpose reads are fastest with the 3-bit term below)
-__device__ __forceinline__ int kswz_of_row(int r) { return r & 15; }
-__device__ __forceinline__ int vswz_of_row(int r) { return ((r & 3) << 1) | ((r >> 2) & 1); }
+// row term; the 8-byte transpose reads are fastest with the 3-bit term below).  Rows of 128 B (d = 64) lie two to a
+// 256-byte line of the banks: the K term uses the row pair, and the V term moves rows 2, 3 of four to the other half.
+template <int D>
+__device__ __forceinline__ int kswz_of_row(int r) { return D == 128 ? (r & 15) : ((r >> 1) & 7); }
+template <int D>
+__device__ __forceinline__ int vswz_of_row(int r) { return D == 128 ? (((r & 3) << 1) | ((r >> 2) & 1)) : ((r & 2) << 1); }
 
 extern __shared__ __attribute__((aligned(1024))) uint8_t attn_smem[];
 
-// Asynchronous loads of one 64-key K/V tile into ring stage (ti % NS).  A tile is 16 chunk pairs of
-// 1 KiB (4 key rows of K, the same 4 rows of V).  Issuing wavefront w takes pairs w, w+4, w+8, w+12; in a chunk
-// lane i fetches key row 4j + i/16 and the 16-byte piece that belongs at chunk position i%16 of that row.
-// Pair w + 4u holds rows 16u + 4w .. +3: the lane's place within those 16 rows (and with it both swizzles)
-// does not depend on u, so a load is a scalar base per u plus one per-lane 32-bit offset, and the address
-// arithmetic of a tile is scalar (a wavefront's instruction issue rate is what bounds a tile step).
-template <int NW>
+// Asynchronous loads of one 64-key K/V tile into ring stage (ti % NS).  A tile is 16 (d = 64: 8) chunk pairs of
+// 1 KiB (4 (8) key rows of K, the same rows of V).  Issuing wavefront w takes pairs w, w+4, ...; in a chunk
+// lane i fetches key row 4j + i/16 (8j + i/8) and the 16-byte piece that belongs at chunk position i%16 (i%8) of
+// that row.  Pair w + 4u holds rows 16u + 4w .. +3 (32u + 8w .. +7): the lane's place within those 16 rows (and with
+// it both swizzles) does not depend on u, so a load is a scalar base per u plus one per-lane 32-bit offset, and the
+// address arithmetic of a tile is scalar (a wavefront's instruction issue rate is what bounds a tile step).
+template <int D, int NW>
 struct TileLoader {
     // wavefronts that issue loads: all 4 of a small workgroup; of 8, only wavefronts 0..3, which otherwise
     // idle at the tile barrier while wavefronts 4..7 (one phase behind) finish their longer chain
     static constexpr int NI = 4;
-    static constexpr int U = 16 / NI;  // chunk pairs per issuing wavefront and tile
+    static constexpr int U = Geo<D>::TILE_BYTES / 1024 / NI;  // chunk pairs per issuing wavefront and tile: 4 or 2
+    // 16-key block of the tile in which pair w + 4u lies
+    static __device__ __forceinline__ int block_of(int w, int u) { return (Geo<D>::RPU * (w + NI * u)) >> 4; }
     const uint8_t *kc, *vc, *kt, *vt;
     const uint8_t *kf, *vf;  // full tiles: kc / vc advanced by head_off (paged) or seq_off (contiguous)
     const int32_t *bt;
@@ -478,64 +508,65 @@ __device__ __forceinline__ void async_load16_s(const void *sbase, uint32_t voff,
 // full prefix tile (all 64 keys exist): straight-line address arithmetic.  For a paged cache the physical
 // block ids are fetched with scalar loads by fetch_blocks() ahead of the wait and barrier of the ring step,
 // so their latency is hidden; the block table is read-only for the kernel (constant address space).
-template <int NW>
-__device__ __forceinline__ void fetch_blocks(const TileLoader<NW> &ld, int ti, int (&blk)[TileLoader<NW>::U]) {
+template <int D, int NW>
+__device__ __forceinline__ void fetch_blocks(const TileLoader<D, NW> &ld, int ti, int (&blk)[TileLoader<D, NW>::U]) {
     const int lb0 = (ld.k0 + ti * KT) >> 4;
 #pragma unroll
-    for (int u = 0; u < TileLoader<NW>::U; u++)
-        blk[u] = ((const_i32_ptr)(uintptr_t)ld.bt)[lb0 + ((ld.wave + TileLoader<NW>::NI * u) >> 2)];
+    for (int u = 0; u < TileLoader<D, NW>::U; u++)
+        blk[u] = ((const_i32_ptr)(uintptr_t)ld.bt)[lb0 + TileLoader<D, NW>::block_of(ld.wave, u)];
 }
 
-template <int NW, int NS, bool PAGED, bool NT>
-__device__ __forceinline__ void issue_full_tile(const TileLoader<NW> &ld, int ti, const int (&blk)[TileLoader<NW>::U]) {
-    constexpr int U = TileLoader<NW>::U, NI = TileLoader<NW>::NI;
-    static_assert(NI == 4 && U == 4, "pair w + 4u lies in 16-key block u of the tile");
-    const uint32_t dst = ld.smem_addr + (uint32_t)(ti % NS) * STAGE_BYTES + (uint32_t)ld.wave * 1024;
+template <int D, int NW, int NS, bool PAGED, bool NT>
+__device__ __forceinline__ void issue_full_tile(const TileLoader<D, NW> &ld, int ti, const int (&blk)[TileLoader<D, NW>::U]) {
+    constexpr int U = TileLoader<D, NW>::U, NI = TileLoader<D, NW>::NI;
+    constexpr int TILE_BYTES = Geo<D>::TILE_BYTES;
+    const uint32_t dst = ld.smem_addr + (uint32_t)(ti % NS) * Geo<D>::STAGE_BYTES + (uint32_t)ld.wave * 1024;
 #pragma unroll
     for (int u = 0; u < U; u++) {
         // kf / vf: the cache pointers advanced to this KV head's part of block 0 (paged) or of row 0 of the sequence
         const size_t off = PAGED ? (size_t)(uint32_t)blk[u] * (size_t)(uint32_t)ld.blk_stride
-                                 : (size_t)(uint32_t)(ld.k0 + ti * KT + 16 * u) * (size_t)(uint32_t)ld.row_stride;
+                                 : (size_t)(uint32_t)(ld.k0 + ti * KT + Geo<D>::RPU * NI * u) * (size_t)(uint32_t)ld.row_stride;
         async_load16_s<NT>(ld.kf + off, ld.koff, dst + u * (NI * 1024));
         async_load16_s<NT>(ld.vf + off, ld.voff, dst + TILE_BYTES + u * (NI * 1024));
     }
 }
 
 // ragged last prefix tile or tree tile: rows past the end re-read the last valid row (masked later)
-template <int NW, int NS>
-__device__ __forceinline__ void issue_edge_tile(const TileLoader<NW> &ld, int ti) {
-    constexpr int U = TileLoader<NW>::U, NI = TileLoader<NW>::NI;
+template <int D, int NW, int NS>
+__device__ __forceinline__ void issue_edge_tile(const TileLoader<D, NW> &ld, int ti) {
+    constexpr int U = TileLoader<D, NW>::U, NI = TileLoader<D, NW>::NI;
+    constexpr int ROW_BYTES = Geo<D>::ROW_BYTES, RPU = Geo<D>::RPU;
     const bool tree = ti >= ld.npt;
     const int base = tree ? (ti - ld.npt) * KT : ld.k0 + ti * KT;
     const int last = (tree ? ld.n : ld.k1) - 1;
-    const uint32_t stage = ld.smem_addr + (uint32_t)(ti % NS) * STAGE_BYTES;
+    const uint32_t stage = ld.smem_addr + (uint32_t)(ti % NS) * Geo<D>::STAGE_BYTES;
     const bool own = tree && !ld.tail;  // rows of the step's own tree buffer
     const uint8_t *ksrc = own ? ld.kt : ld.kc;
     const uint8_t *vsrc = own ? ld.vt : ld.vc;
 #pragma unroll
     for (int u = 0; u < U; u++) {
         const int j = ld.wave + NI * u;
-        const int r_in = 4 * j + ld.l_row;
+        const int r_in = RPU * j + ld.l_row;
         const int key = min(base + r_in, last);
         size_t off;
         if (own) {
             off = (size_t)key * ld.row_stride;
         } else if (tree) {
-            // in-place branch cache: node `key` sits at cache position P + key.  P is arbitrary, so the four rows
+            // in-place branch cache: node `key` sits at cache position P + key.  P is arbitrary, so the rows
             // of a chunk may lie in two blocks: the block id is looked up per lane.
             const int pos = ld.P + key;
             if (ld.bt) off = (size_t)ld.bt[pos >> 4] * ld.blk_stride + ld.head_off + (size_t)(pos & 15) * ROW_BYTES;
             else off = ld.seq_off + (size_t)pos * ld.row_stride;
         } else if (ld.bt) {
             // the logical block is the same for the whole chunk (its rows are clamped into one block)
-            const int lb = __builtin_amdgcn_readfirstlane(min(base + 4 * j, last) >> 4);
+            const int lb = __builtin_amdgcn_readfirstlane(min(base + RPU * j, last) >> 4);
             const int blk = ((const_i32_ptr)(uintptr_t)ld.bt)[lb];
             off = (size_t)blk * ld.blk_stride + ld.head_off + (size_t)(key & 15) * ROW_BYTES;
         } else {
             off = ld.seq_off + (size_t)key * ld.row_stride;
         }
         async_load16(ksrc + off + ld.kcol, stage + j * 1024);
-        async_load16(vsrc + off + ld.vcol, stage + TILE_BYTES + j * 1024);
+        async_load16(vsrc + off + ld.vcol, stage + Geo<D>::TILE_BYTES + j * 1024);
     }
 }
 
@@ -554,12 +585,14 @@ struct TileView {
 constexpr float kLazy = 8.0f;
 
 // V^T fragments of 32 keys (key block kb) of the V tile at lv.
-__device__ __forceinline__ void load_v_frags(const TileView &tv, const uint8_t *lv, int kb, bf16x8 (&vf)[2][4]) {
+template <int D>
+__device__ __forceinline__ void load_v_frags(const TileView &tv, const uint8_t *lv, int kb, bf16x8 (&vf)[2][Geo<D>::DB]) {
+    constexpr int ROW_BYTES = Geo<D>::ROW_BYTES;
 #pragma unroll
     for (int st = 0; st < 2; st++) {
         const uint8_t *vr = lv + (32 * kb + 16 * st + tv.vrow) * ROW_BYTES + tv.vsub;
 #pragma unroll
-        for (int db = 0; db < 4; db++) {
+        for (int db = 0; db < Geo<D>::DB; db++) {
             const int cpos = ((4 * db + tv.vchunk) ^ tv.vsw) << 4;
             const s16x4 v0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(vr + cpos));
             const s16x4 v1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(vr + 8 * ROW_BYTES + cpos));
@@ -569,27 +602,35 @@ __device__ __forceinline__ void load_v_frags(const TileView &tv, const uint8_t *
     }
 }
 
+// The B operands of a PV product over 32 keys from the packed probabilities of a lane.
+__device__ __forceinline__ void pack_frags(const uint32_t (&pk)[8], bf16x8 (&pf)[2]) {
+    const uint4 l = {pk[0], pk[1], pk[2], pk[3]}, h = {pk[4], pk[5], pk[6], pk[7]};
+    pf[0] = __builtin_bit_cast(bf16x8, l);
+    pf[1] = __builtin_bit_cast(bf16x8, h);
+}
+
 // First half of a 64-key tile for one wavefront (32 query rows): S^T = K Q^T, mask, running reference,
 // P^T = exp2(S^T * scale - m) packed to bf16 in pf[key block][16-key step].  MASKED: key kin of the tile is
 // visible to the lane's row iff bit kin of `vis`.
-template <bool MASKED>
-__device__ __forceinline__ void qk_softmax(const TileView &tv, const uint8_t *lk, const bf16x8 (&qreg)[8],
-                                           f32x16 (&oacc)[4], float &m_run, float &l_run, float scale_log2,
-                                           uint64_t vis, bf16x8 (&pf)[2][2]) {
+template <int D, bool MASKED>
+__device__ __forceinline__ void qk_softmax(const TileView &tv, const uint8_t *lk, const bf16x8 (&qreg)[Geo<D>::KK],
+                                           f32x16 (&oacc)[Geo<D>::DB], float &m_run, float &l_run, float scale_log2,
+                                           uint64_t vis, bf16x8 (&pf)[Geo<D>::NP][2][2]) {
+    constexpr int ROW_BYTES = Geo<D>::ROW_BYTES, KK = Geo<D>::KK;
     // two independent accumulator chains (keys 0..31 and 32..63)
     f32x16 s0, s1;
 #pragma unroll
     for (int i = 0; i < 16; i++) { s0[i] = 0.f; s1[i] = 0.f; }
     {
-        bf16x8 ka[8], kb[8];
+        bf16x8 ka[KK], kb[KK];
 #pragma unroll
-        for (int kk = 0; kk < 8; kk++) {
+        for (int kk = 0; kk < KK; kk++) {
             const int col = (((2 * kk + tv.hh) ^ tv.ksw) << 4);
             ka[kk] = *reinterpret_cast<const bf16x8 *>(lk + tv.krow + col);
             kb[kk] = *reinterpret_cast<const bf16x8 *>(lk + tv.krow + 32 * ROW_BYTES + col);
         }
 #pragma unroll
-        for (int kk = 0; kk < 8; kk++) {
+        for (int kk = 0; kk < KK; kk++) {
             s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[kk], qreg[kk], s0, 0, 0, 0);
             s1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kb[kk], qreg[kk], s1, 0, 0, 0);
         }
@@ -621,49 +662,60 @@ __device__ __forceinline__ void qk_softmax(const TileView &tv, const uint8_t *lk
         m_run = m_new;
         l_run *= alpha;
 #pragma unroll
-        for (int db = 0; db < 4; db++)
+        for (int db = 0; db < Geo<D>::DB; db++)
 #pragma unroll
             for (int i = 0; i < 16; i++) oacc[db][i] *= alpha;
     }
     const float neg_m = (MASKED && m_run == -INFINITY) ? 0.f : -m_run;
     float psum = 0.f, psum2 = 0.f;  // two chains
-    uint32_t pk0[8], pk1[8];
+    uint32_t pk[Geo<D>::NP][2][8];
 #pragma unroll
     for (int i = 0; i < 16; i += 2) {
         const float a0 = __builtin_amdgcn_exp2f(fmaf(s0[i], scale_log2, neg_m));
         const float a1 = __builtin_amdgcn_exp2f(fmaf(s0[i + 1], scale_log2, neg_m));
         const float b0 = __builtin_amdgcn_exp2f(fmaf(s1[i], scale_log2, neg_m));
         const float b1 = __builtin_amdgcn_exp2f(fmaf(s1[i + 1], scale_log2, neg_m));
-        pk0[i >> 1] = pack_bf16x2(a0, a1);
-        pk1[i >> 1] = pack_bf16x2(b0, b1);
-        psum = pair_sum(pk0[i >> 1], psum);
-        psum2 = pair_sum(pk1[i >> 1], psum2);
+        if constexpr (Geo<D>::NP == 2) {
+            split_bf16x2(a0, a1, pk[0][0][i >> 1], pk[1][0][i >> 1]);
+            split_bf16x2(b0, b1, pk[0][1][i >> 1], pk[1][1][i >> 1]);
+            psum += a0 + a1;
+            psum2 += b0 + b1;
+        } else {
+            pk[0][0][i >> 1] = pack_bf16x2(a0, a1);
+            pk[0][1][i >> 1] = pack_bf16x2(b0, b1);
+            psum = pair_sum(pk[0][0][i >> 1], psum);
+            psum2 = pair_sum(pk[0][1][i >> 1], psum2);
+        }
     }
-    const uint4 l0 = {pk0[0], pk0[1], pk0[2], pk0[3]}, h0 = {pk0[4], pk0[5], pk0[6], pk0[7]};
-    const uint4 l1 = {pk1[0], pk1[1], pk1[2], pk1[3]}, h1 = {pk1[4], pk1[5], pk1[6], pk1[7]};
-    pf[0][0] = __builtin_bit_cast(bf16x8, l0); pf[0][1] = __builtin_bit_cast(bf16x8, h0);
-    pf[1][0] = __builtin_bit_cast(bf16x8, l1); pf[1][1] = __builtin_bit_cast(bf16x8, h1);
+#pragma unroll
+    for (int x = 0; x < Geo<D>::NP; x++)
+#pragma unroll
+        for (int kb = 0; kb < 2; kb++) pack_frags(pk[x][kb], pf[x][kb]);
     l_run += psum + psum2;
 }
 
-// Second half: O^T += V^T P^T over the 64 keys of the V tile at lv; four independent accumulator chains.
-// The first 32 keys' fragments may have been read ahead (vf0_ready).
-__device__ __forceinline__ void pv_accumulate(const TileView &tv, const uint8_t *lv, const bf16x8 (&pf)[2][2],
-                                              f32x16 (&oacc)[4], bf16x8 (&vf)[2][4], bool vf0_ready) {
-    if (!vf0_ready) load_v_frags(tv, lv, 0, vf);
+// Second half: O^T += V^T P^T over the 64 keys of the V tile at lv; D / 32 independent accumulator chains.
+template <int D>
+__device__ __forceinline__ void pv_accumulate(const TileView &tv, const uint8_t *lv, const bf16x8 (&pf)[Geo<D>::NP][2][2],
+                                              f32x16 (&oacc)[Geo<D>::DB]) {
+    constexpr int DB = Geo<D>::DB;
+    bf16x8 vf[2][DB];
+    load_v_frags<D>(tv, lv, 0, vf);
 #pragma unroll
     for (int kb = 0; kb < 2; kb++) {
-        bf16x8 va[2][4];
+        bf16x8 va[2][DB];
 #pragma unroll
         for (int st = 0; st < 2; st++)
 #pragma unroll
-            for (int db = 0; db < 4; db++) va[st][db] = vf[st][db];
-        if (kb == 0) load_v_frags(tv, lv, 1, vf);  // the second half's fragments fly during the first half's products
+            for (int db = 0; db < DB; db++) va[st][db] = vf[st][db];
+        if (kb == 0) load_v_frags<D>(tv, lv, 1, vf);  // the second half's fragments fly during the first half's products
 #pragma unroll
         for (int st = 0; st < 2; st++)
 #pragma unroll
-            for (int db = 0; db < 4; db++)
-                oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[st][db], pf[kb][st], oacc[db], 0, 0, 0);
+            for (int db = 0; db < DB; db++)
+#pragma unroll
+                for (int x = 0; x < Geo<D>::NP; x++)
+                    oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[st][db], pf[x][kb][st], oacc[db], 0, 0, 0);
     }
 }
 
@@ -671,22 +723,23 @@ __device__ __forceinline__ void pv_accumulate(const TileView &tv, const uint8_t 
 // 32-row chunk and keep independent running (m, l, O), merged once after the last tile.  Halves the
 // per-tile dependency chain of a wavefront, which is what bounds the rate when a workgroup has fewer chunks
 // than wavefronts.  vis32: visibility bits of the wavefront's 32 keys.
-template <bool MASKED>
-__device__ __forceinline__ void qk_softmax_half(const TileView &tv, const uint8_t *lk, int kb, const bf16x8 (&qreg)[8],
-                                                f32x16 (&oacc)[4], float &m_run, float &l_run, float scale_log2,
-                                                uint32_t vis32, bf16x8 (&pf)[2]) {
+template <int D, bool MASKED>
+__device__ __forceinline__ void qk_softmax_half(const TileView &tv, const uint8_t *lk, int kb, const bf16x8 (&qreg)[Geo<D>::KK],
+                                                f32x16 (&oacc)[Geo<D>::DB], float &m_run, float &l_run, float scale_log2,
+                                                uint32_t vis32, bf16x8 (&pf)[Geo<D>::NP][2]) {
+    constexpr int ROW_BYTES = Geo<D>::ROW_BYTES, KK = Geo<D>::KK;
     // two accumulator chains over the even / odd 16-wide d steps, summed afterwards
     f32x16 s0, s1;
 #pragma unroll
     for (int i = 0; i < 16; i++) { s0[i] = 0.f; s1[i] = 0.f; }
     {
-        bf16x8 ka[8];
+        bf16x8 ka[KK];
         const uint8_t *kr = lk + tv.krow + kb * (32 * ROW_BYTES);
 #pragma unroll
-        for (int kk = 0; kk < 8; kk++)
+        for (int kk = 0; kk < KK; kk++)
             ka[kk] = *reinterpret_cast<const bf16x8 *>(kr + (((2 * kk + tv.hh) ^ tv.ksw) << 4));
 #pragma unroll
-        for (int kk = 0; kk < 8; kk += 2) {
+        for (int kk = 0; kk < KK; kk += 2) {
             s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[kk], qreg[kk], s0, 0, 0, 0);
             s1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[kk + 1], qreg[kk + 1], s1, 0, 0, 0);
         }
@@ -714,41 +767,50 @@ __device__ __forceinline__ void qk_softmax_half(const TileView &tv, const uint8_
         m_run = m_new;
         l_run *= alpha;
 #pragma unroll
-        for (int db = 0; db < 4; db++)
+        for (int db = 0; db < Geo<D>::DB; db++)
 #pragma unroll
             for (int i = 0; i < 16; i++) oacc[db][i] *= alpha;
     }
     const float neg_m = (MASKED && m_run == -INFINITY) ? 0.f : -m_run;
     float psum = 0.f;
-    uint32_t pk[8];
+    uint32_t pk[Geo<D>::NP][8];
 #pragma unroll
     for (int i = 0; i < 16; i += 2) {
         const float a0 = __builtin_amdgcn_exp2f(fmaf(s0[i], scale_log2, neg_m));
         const float a1 = __builtin_amdgcn_exp2f(fmaf(s0[i + 1], scale_log2, neg_m));
-        pk[i >> 1] = pack_bf16x2(a0, a1);
-        psum = pair_sum(pk[i >> 1], psum);
+        if constexpr (Geo<D>::NP == 2) {
+            split_bf16x2(a0, a1, pk[0][i >> 1], pk[1][i >> 1]);
+            psum += a0 + a1;
+        } else {
+            pk[0][i >> 1] = pack_bf16x2(a0, a1);
+            psum = pair_sum(pk[0][i >> 1], psum);
+        }
     }
-    const uint4 l0 = {pk[0], pk[1], pk[2], pk[3]}, h0 = {pk[4], pk[5], pk[6], pk[7]};
-    pf[0] = __builtin_bit_cast(bf16x8, l0);
-    pf[1] = __builtin_bit_cast(bf16x8, h0);
+#pragma unroll
+    for (int x = 0; x < Geo<D>::NP; x++) pack_frags(pk[x], pf[x]);
     l_run += psum;
 }
 
-__device__ __forceinline__ void pv_accumulate_half(const TileView &tv, const uint8_t *lv, int kb, const bf16x8 (&pf)[2],
-                                                   f32x16 (&oacc)[4]) {
-    bf16x8 vf[2][4];
-    load_v_frags(tv, lv, kb, vf);
+template <int D>
+__device__ __forceinline__ void pv_accumulate_half(const TileView &tv, const uint8_t *lv, int kb, const bf16x8 (&pf)[Geo<D>::NP][2],
+                                                   f32x16 (&oacc)[Geo<D>::DB]) {
+    bf16x8 vf[2][Geo<D>::DB];
+    load_v_frags<D>(tv, lv, kb, vf);
 #pragma unroll
     for (int st = 0; st < 2; st++)
 #pragma unroll
-        for (int db = 0; db < 4; db++)
-            oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[st][db], pf[st], oacc[db], 0, 0, 0);
+        for (int db = 0; db < Geo<D>::DB; db++)
+#pragma unroll
+            for (int x = 0; x < Geo<D>::NP; x++)
+                oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[st][db], pf[x][st], oacc[db], 0, 0, 0);
 }
 
-template <int NW, int NS, bool PAGED, bool KH>
+template <int D, int NW, int NS, bool PAGED, bool KH>
 __global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(AttnParams p) {
-    constexpr int D = 128;
-    constexpr int LPW = 2 * TileLoader<NW>::U;  // direct-to-LDS loads an issuing wavefront issues per tile
+    using Loader = TileLoader<D, NW>;
+    constexpr int ROW_BYTES = Geo<D>::ROW_BYTES, TILE_BYTES = Geo<D>::TILE_BYTES, STAGE_BYTES = Geo<D>::STAGE_BYTES;
+    constexpr int KK = Geo<D>::KK, DB = Geo<D>::DB;
+    constexpr int LPW = 2 * Loader::U;  // direct-to-LDS loads an issuing wavefront issues per tile
     uint8_t *const smem = attn_smem;
     const uint32_t smem_addr = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)attn_smem;
 
@@ -792,9 +854,8 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(AttnParams p) {
     } else {
         n_raw = ((const_i32_ptr)(uintptr_t)p.n_nodes)[b]; P_raw = ((const_i32_ptr)(uintptr_t)p.prefix_len)[b];
     }
-    // (an issuing wavefront needs ids lb, lb+1, lb+2, lb+3 of each tile: 4 * PD consecutive table entries)
-    static_assert(TileLoader<NW>::U == 4 && TileLoader<NW>::NI == 4, "block ids of a tile: four consecutive entries");
-    int blk_pro[PD][4];
+    // (the four blocks of a tile are consecutive table entries; an issuing wavefront needs U of them)
+    int blk_pro[PD][Loader::U];
     const int lb_first = (s * p.chunk) >> 4;
     const bool spec = PAGED && !p.balanced && lb_first + 4 * PD <= p.max_blocks;  // the whole range lies inside the table row
     if (spec) {
@@ -802,23 +863,38 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(AttnParams p) {
 #pragma unroll
         for (int t = 0; t < PD; t++)
 #pragma unroll
-            for (int u = 0; u < 4; u++) blk_pro[t][u] = bt_row[4 * t + u];
+            for (int u = 0; u < Loader::U; u++) blk_pro[t][u] = bt_row[4 * t + Loader::block_of(wave & 3, u)];
     } else {
 #pragma unroll
         for (int t = 0; t < PD; t++)
 #pragma unroll
-            for (int u = 0; u < 4; u++) blk_pro[t][u] = 0;
+            for (int u = 0; u < Loader::U; u++) blk_pro[t][u] = 0;
     }
     // one wait for all of them
-    if constexpr (PD == 3)
-        asm volatile("" ::"s"(n_raw), "s"(P_raw), "s"(blk_pro[0][0]), "s"(blk_pro[0][1]), "s"(blk_pro[0][2]), "s"(blk_pro[0][3]),
+    if constexpr (PD == 3 && Loader::U == 4)
+        asm volatile("" ::"s"(n_raw), "s"(P_raw),
+                     "s"(blk_pro[0][0]), "s"(blk_pro[0][1]), "s"(blk_pro[0][2]), "s"(blk_pro[0][3]),
                      "s"(blk_pro[1][0]), "s"(blk_pro[1][1]), "s"(blk_pro[1][2]), "s"(blk_pro[1][3]),
                      "s"(blk_pro[2][0]), "s"(blk_pro[2][1]), "s"(blk_pro[2][2]), "s"(blk_pro[2][3]));
-    else if constexpr (PD == 2)
-        asm volatile("" ::"s"(n_raw), "s"(P_raw), "s"(blk_pro[0][0]), "s"(blk_pro[0][1]), "s"(blk_pro[0][2]), "s"(blk_pro[0][3]),
+    else if constexpr (PD == 2 && Loader::U == 4)
+        asm volatile("" ::"s"(n_raw), "s"(P_raw),
+                     "s"(blk_pro[0][0]), "s"(blk_pro[0][1]), "s"(blk_pro[0][2]), "s"(blk_pro[0][3]),
                      "s"(blk_pro[1][0]), "s"(blk_pro[1][1]), "s"(blk_pro[1][2]), "s"(blk_pro[1][3]));
+    else if constexpr (PD == 1 && Loader::U == 4)
+        asm volatile("" ::"s"(n_raw), "s"(P_raw),
+                     "s"(blk_pro[0][0]), "s"(blk_pro[0][1]), "s"(blk_pro[0][2]), "s"(blk_pro[0][3]));
+    else if constexpr (PD == 3 && Loader::U == 2)
+        asm volatile("" ::"s"(n_raw), "s"(P_raw),
+                     "s"(blk_pro[0][0]), "s"(blk_pro[0][1]),
+                     "s"(blk_pro[1][0]), "s"(blk_pro[1][1]),
+                     "s"(blk_pro[2][0]), "s"(blk_pro[2][1]));
+    else if constexpr (PD == 2 && Loader::U == 2)
+        asm volatile("" ::"s"(n_raw), "s"(P_raw),
+                     "s"(blk_pro[0][0]), "s"(blk_pro[0][1]),
+                     "s"(blk_pro[1][0]), "s"(blk_pro[1][1]));
     else
-        asm volatile("" ::"s"(n_raw), "s"(P_raw), "s"(blk_pro[0][0]), "s"(blk_pro[0][1]), "s"(blk_pro[0][2]), "s"(blk_pro[0][3]));
+        asm volatile("" ::"s"(n_raw), "s"(P_raw),
+                     "s"(blk_pro[0][0]), "s"(blk_pro[0][1]));
 
     const int n = clampi(n_raw, 0, p.T_max);
     const int P = clampi(P_raw, 0, p.P_max);
@@ -846,7 +922,7 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(AttnParams p) {
     const int ntt = (s == nvalid - 1) ? (n + KT - 1) / KT : 0;      // tree tiles
     const int nt = npt + ntt;
 
-    TileLoader<NW> ld;
+    Loader ld;
     ld.kc = static_cast<const uint8_t *>(p.k_cache); ld.vc = static_cast<const uint8_t *>(p.v_cache);
     ld.kt = static_cast<const uint8_t *>(p.kt) + ((size_t)b * p.T_max * p.Hkv + kvh) * ROW_BYTES;
     ld.vt = static_cast<const uint8_t *>(p.vt) + ((size_t)b * p.T_max * p.Hkv + kvh) * ROW_BYTES;
@@ -856,18 +932,18 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(AttnParams p) {
     ld.blk_stride = (size_t)p.Hkv * 16 * ROW_BYTES;                  // paged cache: one block, all heads
     ld.head_off = (size_t)kvh * 16 * ROW_BYTES;
     ld.kf = ld.kc + (PAGED ? ld.head_off : ld.seq_off); ld.vf = ld.vc + (PAGED ? ld.head_off : ld.seq_off);
-    ld.smem_addr = smem_addr; ld.wave = wave; ld.l_row = lane >> 4; ld.l_pos = lane & 15;
+    ld.smem_addr = smem_addr; ld.wave = wave; ld.l_row = lane / Geo<D>::CPR; ld.l_pos = lane % Geo<D>::CPR;
     ld.k0 = k0; ld.k1 = k1; ld.npt = npt; ld.n = n; ld.P = P; ld.tail = (p.kt == nullptr);
     {
         // the lane's row within the 16 rows that pair `wave` + 4u covers, the same for every u
-        const int r_in = 4 * wave + ld.l_row;
-        ld.kcol = (uint32_t)((ld.l_pos ^ kswz_of_row(r_in)) * 16);
-        ld.vcol = (uint32_t)((ld.l_pos ^ vswz_of_row(r_in)) * 16);
+        const int r_in = Geo<D>::RPU * wave + ld.l_row;
+        ld.kcol = (uint32_t)((ld.l_pos ^ kswz_of_row<D>(r_in)) * 16);
+        ld.vcol = (uint32_t)((ld.l_pos ^ vswz_of_row<D>(r_in)) * 16);
         const uint32_t rowpart = PAGED ? (uint32_t)((r_in & 15) * ROW_BYTES) : (uint32_t)r_in * (uint32_t)ld.row_stride;
         ld.koff = rowpart + ld.kcol;
         ld.voff = rowpart + ld.vcol;
     }
-    const bool issuer = wave < TileLoader<NW>::NI;
+    const bool issuer = wave < Loader::NI;
     // one workgroup per (split, KV head): nobody else reads these K/V bytes, so they are streamed past L2
     const bool stream_kv = p.wgp == 1;
     // prologue: fill the ring, then fetch Q and the mask row while those loads fly
@@ -875,17 +951,17 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(AttnParams p) {
     for (int t = 0; t < PD; t++) {
         if (t >= nt || !issuer) continue;
         if (t < nfull) {
-            if (PAGED && !spec) fetch_blocks<NW>(ld, t, blk_pro[t]);
-            if (stream_kv) issue_full_tile<NW, NS, PAGED, true>(ld, t, blk_pro[t]);
-            else issue_full_tile<NW, NS, PAGED, false>(ld, t, blk_pro[t]);
+            if (PAGED && !spec) fetch_blocks<D, NW>(ld, t, blk_pro[t]);
+            if (stream_kv) issue_full_tile<D, NW, NS, PAGED, true>(ld, t, blk_pro[t]);
+            else issue_full_tile<D, NW, NS, PAGED, false>(ld, t, blk_pro[t]);
         } else {
-            issue_edge_tile<NW, NS>(ld, t);
+            issue_edge_tile<D, NW, NS>(ld, t);
         }
     }
 
     const uint16_t *qp = static_cast<const uint16_t *>(p.q);
     // Q as B operand: lane holds query row kq, d values 16*kk + 8*hh .. +7
-    bf16x8 qreg[8];
+    bf16x8 qreg[KK];
     uint64_t mbits0 = 0, mbits1 = 0, mbits2 = 0, mbits3 = 0;  // the row's ancestor bits, one word per tree tile
     const bool rv = active && kq < n;
     if (rv) {
@@ -896,16 +972,16 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(AttnParams p) {
         if (p.words > 3) mbits3 = mrow[3];
     }
 #pragma unroll
-    for (int kk = 0; kk < 8; kk++) {
+    for (int kk = 0; kk < KK; kk++) {
         uint4 v = {0, 0, 0, 0};
         if (rv) v = *reinterpret_cast<const uint4 *>(qp + (((size_t)b * p.T_max + kq) * p.Hq + h) * D + 16 * kk + 8 * hh);
         qreg[kk] = __builtin_bit_cast(bf16x8, v);
     }
 
-    f32x16 oacc[4];
+    f32x16 oacc[DB];
     float m_run = -INFINITY, l_run = 0.f;
 #pragma unroll
-    for (int db = 0; db < 4; db++)
+    for (int db = 0; db < DB; db++)
 #pragma unroll
         for (int i = 0; i < 16; i++) oacc[db][i] = 0.f;
 
@@ -916,7 +992,7 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(AttnParams p) {
     // per-lane LDS offsets (bytes within a tile) that do not depend on the tile
     const int g16 = lane >> 4, i16 = lane & 15;
     const int vrow = 4 * hh + (i16 >> 2);  // V row within a 16-key step (second read: +8)
-    TileView tv{c32 * ROW_BYTES, kswz_of_row(c32), vrow, vswz_of_row(vrow),
+    TileView tv{c32 * ROW_BYTES, kswz_of_row<D>(c32), vrow, vswz_of_row<D>(vrow),
                 2 * (g16 & 1) + ((i16 & 3) >> 1), 8 * (i16 & 1), hh};
 
     // Ring step: wait for tile ti, barrier, refill.  PD = tiles in flight behind the one being consumed.
@@ -924,9 +1000,9 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(AttnParams p) {
     // the stage that is refilled is the one of tile ti-2.
     auto ring_step = [&](int ti) {
         const int tn = ti + PD;  // tile to issue in this step
-        int blk[TileLoader<NW>::U];
+        int blk[Loader::U];
         const bool full_next = issuer && tn < nfull;
-        if (PAGED && full_next) fetch_blocks<NW>(ld, tn, blk);  // scalar loads fly during the wait below
+        if (PAGED && full_next) fetch_blocks<D, NW>(ld, tn, blk);  // scalar loads fly during the wait below
         const int ahead = min(PD - 1, nt - 1 - ti);  // younger tiles whose loads may still be outstanding
         if (PD >= 3 && ahead >= 2) wait_vmcnt<2 * LPW>();
         else if (PD >= 2 && ahead == 1) wait_vmcnt<LPW>();
@@ -934,10 +1010,10 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(AttnParams p) {
         __builtin_amdgcn_s_barrier();  // everyone's part of tile ti is in LDS; the refilled stage is no longer read
         asm volatile("" ::: "memory");
         if (full_next) {
-            if (stream_kv) issue_full_tile<NW, NS, PAGED, true>(ld, tn, blk);
-            else issue_full_tile<NW, NS, PAGED, false>(ld, tn, blk);
+            if (stream_kv) issue_full_tile<D, NW, NS, PAGED, true>(ld, tn, blk);
+            else issue_full_tile<D, NW, NS, PAGED, false>(ld, tn, blk);
         }
-        else if (issuer && tn < nt) issue_edge_tile<NW, NS>(ld, tn);
+        else if (issuer && tn < nt) issue_edge_tile<D, NW, NS>(ld, tn);
     };
     auto tile_vis = [&](int ti) -> uint64_t {
         if (ti < npt) return (1ull << (k1 - k0 - nfull * KT)) - 1ull;  // ragged last prefix tile: 1..63 keys
@@ -945,23 +1021,24 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(AttnParams p) {
         const uint64_t lo = (w & 1) ? mbits1 : mbits0, hi = (w & 1) ? mbits3 : mbits2;
         return (w & 2) ? hi : lo;
     };
-    bf16x8 pf[2][2], vf[2][4];
+    bf16x8 pf[Geo<D>::NP][2][2];        // whole tiles: [part][key block][16-key step]
+    bf16x8 pfh[Geo<D>::NP][2];          // key halves: [part][16-key step]
     // one tile for one wavefront, in two parts (the parts run in different ring steps for late wavefronts)
     auto part_qk = [&](int t, bool masked) {
         const uint8_t *lk = smem + (t % NS) * STAGE_BYTES;
         if (KH) {
             const uint32_t v32 = masked ? (uint32_t)(tile_vis(t) >> (32 * kb)) : ~0u;
-            if (masked) qk_softmax_half<true>(tv, lk, kb, qreg, oacc, m_run, l_run, p.scale_log2, v32, pf[0]);
-            else qk_softmax_half<false>(tv, lk, kb, qreg, oacc, m_run, l_run, p.scale_log2, v32, pf[0]);
+            if (masked) qk_softmax_half<D, true>(tv, lk, kb, qreg, oacc, m_run, l_run, p.scale_log2, v32, pfh);
+            else qk_softmax_half<D, false>(tv, lk, kb, qreg, oacc, m_run, l_run, p.scale_log2, v32, pfh);
         } else {
-            if (masked) qk_softmax<true>(tv, lk, qreg, oacc, m_run, l_run, p.scale_log2, tile_vis(t), pf);
-            else qk_softmax<false>(tv, lk, qreg, oacc, m_run, l_run, p.scale_log2, ~0ull, pf);
+            if (masked) qk_softmax<D, true>(tv, lk, qreg, oacc, m_run, l_run, p.scale_log2, tile_vis(t), pf);
+            else qk_softmax<D, false>(tv, lk, qreg, oacc, m_run, l_run, p.scale_log2, ~0ull, pf);
         }
     };
     auto part_pv = [&](int t) {
         const uint8_t *lv = smem + (t % NS) * STAGE_BYTES + TILE_BYTES;
-        if (KH) pv_accumulate_half(tv, lv, kb, pf[0], oacc);
-        else pv_accumulate(tv, lv, pf, oacc, vf, false);
+        if (KH) pv_accumulate_half<D>(tv, lv, kb, pfh, oacc);
+        else pv_accumulate<D>(tv, lv, pf, oacc);
     };
     int ti = 0;
     if (!kShifted || wave < 4) {
@@ -1000,26 +1077,26 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(AttnParams p) {
         // wavefront hands its (m, l, O) to its kb = 0 partner, which rescales both to the larger reference.
         __builtin_amdgcn_s_barrier();  // every wavefront has finished reading tiles; no tile load is outstanding
         asm volatile("" ::: "memory");
-        float4 *mx = reinterpret_cast<float4 *>(smem) + (size_t)(wave % CW) * (17 * 64);
+        float4 *mx = reinterpret_cast<float4 *>(smem) + (size_t)(wave % CW) * ((4 * DB + 1) * 64);
         if (kb == 1 && wactive) {
 #pragma unroll
-            for (int db = 0; db < 4; db++)
+            for (int db = 0; db < DB; db++)
 #pragma unroll
                 for (int ig = 0; ig < 4; ig++)
                     mx[(4 * db + ig) * 64 + lane] = float4{oacc[db][4 * ig], oacc[db][4 * ig + 1], oacc[db][4 * ig + 2], oacc[db][4 * ig + 3]};
-            mx[16 * 64 + lane] = float4{m_run, l_run, 0.f, 0.f};
+            mx[4 * DB * 64 + lane] = float4{m_run, l_run, 0.f, 0.f};
         }
         __syncthreads();
         if (kb == 1) return;
         if (wactive) {
-            const float4 ml = mx[16 * 64 + lane];
+            const float4 ml = mx[4 * DB * 64 + lane];
             const float m_new = fmaxf(m_run, ml.x);
             const float fa = (m_run == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m_run - m_new);
             const float fb = (ml.x == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(ml.x - m_new);
             m_run = m_new;
             l_run = l_run * fa + ml.y * fb;
 #pragma unroll
-            for (int db = 0; db < 4; db++)
+            for (int db = 0; db < DB; db++)
 #pragma unroll
                 for (int ig = 0; ig < 4; ig++) {
                     const float4 o = mx[(4 * db + ig) * 64 + lane];
@@ -1040,7 +1117,7 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(AttnParams p) {
         const size_t orow = (((size_t)b * p.T_max + kq) * p.Hq + h) * D;
         const float inv = rv ? 1.f / l_tot : 0.f;
 #pragma unroll
-        for (int db = 0; db < 4; db++)
+        for (int db = 0; db < DB; db++)
 #pragma unroll
             for (int ig = 0; ig < 4; ig++) {
                 const int dcol = 32 * db + 8 * ig + 4 * hh;
@@ -1053,7 +1130,7 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(AttnParams p) {
     } else if (rv) {
         const size_t pr = part_row(p, p.balanced ? (int)blockIdx.x : b * p.nsplit + s, h, kq);
 #pragma unroll
-        for (int db = 0; db < 4; db++)
+        for (int db = 0; db < DB; db++)
 #pragma unroll
             for (int ig = 0; ig < 4; ig++) {
                 const int dcol = 32 * db + 8 * ig + 4 * hh;
@@ -1092,11 +1169,13 @@ constexpr double kTileKhAlone = 1.1, kTileKhShared = 2.2, kTileKh8 = 1.65;
 // whole tiles: one 8-wavefront workgroup per compute unit (its two wavefronts per SIMD run one phase apart and it
 // fetches each tile once) is 4-7 % faster in sustained runs than two 4-wavefront workgroups, which cost 2.8 together
 constexpr double kTileWhole8 = 2.65;
+// At d = 64 a tile costs about 0.6 of that in every shape (the softmax does not shrink), and what the constants pick is
+// the best forced shape or within 5 % of it (seven workloads, B = 1 ... 32, T = 8 ... 128), so they serve both.
 static Plan make_plan(const etv_attn_desc *h) {
     Plan pl{};
     const int tiles = max(1, (h->P_max + KT - 1) / KT);
     const int B = max(1, h->B);
-    pl.mfma = (h->dtype == ETV_BF16 && h->d == 128 && !(h->flags & ETV_ATTN_FLAG_GENERIC));
+    pl.mfma = (h->dtype == ETV_BF16 && !(h->flags & ETV_ATTN_FLAG_GENERIC));  // d is 64 or 128
     if (!pl.mfma) {
         const long units = ((long)B * h->Hq * h->T_max + 7) / 8;  // 8 resident wavefronts ~ one workgroup slot
         int tps;
@@ -1156,16 +1235,37 @@ static Plan make_plan(const etv_attn_desc *h) {
     return pl;
 }
 
-template <int NW, int NS, bool PAGED, bool KH>
+template <int D, int NW, int NS, bool PAGED, bool KH>
 static int32_t launch_mfma(const AttnParams &p, dim3 grid, hipStream_t st) {
-    constexpr size_t lds = (size_t)NS * STAGE_BYTES;
+    constexpr size_t lds = (size_t)NS * Geo<D>::STAGE_BYTES;
     static const bool lds_ok = [] {  // opt in to more than 64 KiB of dynamic LDS, once per process
-        return hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_mfma_kernel<NW, NS, PAGED, KH>),
+        return hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_mfma_kernel<D, NW, NS, PAGED, KH>),
                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) == hipSuccess;
     }();
     if (!lds_ok) return ETV_ERR_HIP;
-    hipLaunchKernelGGL((attn_mfma_kernel<NW, NS, PAGED, KH>), grid, dim3(NW * 64), lds, st, p);
+    hipLaunchKernelGGL((attn_mfma_kernel<D, NW, NS, PAGED, KH>), grid, dim3(NW * 64), lds, st, p);
     return check_launch();
+}
+
+// 8 wavefronts: one workgroup per compute unit with a 4-stage ring (128 KiB of LDS at d = 128);
+// 4 wavefronts: two workgroups per compute unit with 2 stages each, or 4 stages when the grid is small
+template <int D>
+static int32_t launch_mfma_shape(const Plan &pl, bool paged, const AttnParams &p, dim3 grid, hipStream_t st) {
+    const int shape = (pl.nw == 8 ? 0 : (pl.ns == 4 ? 1 : 2)) * 4 + (paged ? 2 : 0) + (pl.kh ? 1 : 0);
+    switch (shape) {
+    case 0: return launch_mfma<D, 8, 4, false, false>(p, grid, st);
+    case 1: return launch_mfma<D, 8, 4, false, true>(p, grid, st);
+    case 2: return launch_mfma<D, 8, 4, true, false>(p, grid, st);
+    case 3: return launch_mfma<D, 8, 4, true, true>(p, grid, st);
+    case 4: return launch_mfma<D, 4, 4, false, false>(p, grid, st);
+    case 5: return launch_mfma<D, 4, 4, false, true>(p, grid, st);
+    case 6: return launch_mfma<D, 4, 4, true, false>(p, grid, st);
+    case 7: return launch_mfma<D, 4, 4, true, true>(p, grid, st);
+    case 8: return launch_mfma<D, 4, 2, false, false>(p, grid, st);
+    case 9: return launch_mfma<D, 4, 2, false, true>(p, grid, st);
+    case 10: return launch_mfma<D, 4, 2, true, false>(p, grid, st);
+    default: return launch_mfma<D, 4, 2, true, true>(p, grid, st);
+    }
 }
 
 }  // namespace etv
@@ -1250,24 +1350,8 @@ static int32_t attention_run(const etv_attn_desc *h, const void *q, const void *
     int32_t rc;
     if (pl.mfma) {
         const dim3 grid = pl.balanced ? dim3(pl.nsplit * h->B, h->Hkv * pl.wgp, 1) : dim3(pl.nsplit, h->Hkv * pl.wgp, h->B);
-        const bool paged = h->block_size > 0;
-        // 8 wavefronts: one workgroup per compute unit with a 4-stage ring (128 KiB of LDS);
-        // 4 wavefronts: two workgroups per compute unit with 2 stages each, or 4 stages when the grid is small
-        const int shape = (pl.nw == 8 ? 0 : (pl.ns == 4 ? 1 : 2)) * 4 + (paged ? 2 : 0) + (pl.kh ? 1 : 0);
-        switch (shape) {
-        case 0: rc = launch_mfma<8, 4, false, false>(p, grid, st); break;
-        case 1: rc = launch_mfma<8, 4, false, true>(p, grid, st); break;
-        case 2: rc = launch_mfma<8, 4, true, false>(p, grid, st); break;
-        case 3: rc = launch_mfma<8, 4, true, true>(p, grid, st); break;
-        case 4: rc = launch_mfma<4, 4, false, false>(p, grid, st); break;
-        case 5: rc = launch_mfma<4, 4, false, true>(p, grid, st); break;
-        case 6: rc = launch_mfma<4, 4, true, false>(p, grid, st); break;
-        case 7: rc = launch_mfma<4, 4, true, true>(p, grid, st); break;
-        case 8: rc = launch_mfma<4, 2, false, false>(p, grid, st); break;
-        case 9: rc = launch_mfma<4, 2, false, true>(p, grid, st); break;
-        case 10: rc = launch_mfma<4, 2, true, false>(p, grid, st); break;
-        default: rc = launch_mfma<4, 2, true, true>(p, grid, st); break;
-        }
+        rc = h->d == 128 ? launch_mfma_shape<128>(pl, h->block_size > 0, p, grid, st)
+                         : launch_mfma_shape<64>(pl, h->block_size > 0, p, grid, st);
     } else {
         dim3 grid(h->T_max, h->Hq, h->B * pl.nsplit);
         if (h->dtype == ETV_F32 && h->d == 64)

@@ -144,6 +144,23 @@ def test_mfma_kernel_key_halves_and_whole_tiles_agree_with_the_oracle(flags, pag
     _check(wl, kv_split=1024, flags=flags)
 
 
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("flags", [0, api.ATTN_FLAG_KEY_HALVES | api.ATTN_FLAG_SMALL_WG, api.ATTN_FLAG_WHOLE_TILE | api.ATTN_FLAG_SMALL_WG,
+                                   api.ATTN_FLAG_KEY_HALVES | api.ATTN_FLAG_LARGE_WG, api.ATTN_FLAG_WHOLE_TILE | api.ATTN_FLAG_LARGE_WG])
+def test_mfma_kernel_heads_of_64(flags, paged):
+    """Every launch shape at head dimension 64: prefixes and trees around the 32- and 64-key boundaries.  Probabilities
+    enter the second product as two bf16 parts (16 bits), so the scaled error is that of rounding the output to bf16,
+    2^-9, plus terms of 2^-16: 2^-8 bounds it with a factor of two."""
+    rng = np.random.default_rng(6400 + flags + 100 * paged)
+    P = [0, 1, 31, 32, 33, 63, 64, 65, 95, 97, 128, 500]
+    n = [24, 1, 7, 24, 9, 24, 2, 24, 24, 5, 24, 11]
+    for T, Hq, Hkv, P, n in ((24, 8, 2, P, n), (70, 8, 2, [200, 33], [70, 65]), (128, 6, 3, [130, 64], [128, 127]), (1, 4, 4, [77, 0], [1, 1])):
+        wl = _small(rng, len(P), T, Hq, Hkv, 64, P, "bf16", paged, n_nodes=n, q_scale=2.0)
+        for kv_split in (0, 64, 4096):
+            err, rel = _check(wl, flags=flags, kv_split=kv_split)
+            assert rel <= 2.0 ** -8, (T, kv_split, rel)
+
+
 def test_key_halves_merge_is_deterministic():
     """The merge of the two key halves has a fixed order: two launches on the same inputs give the same bits."""
     rng = np.random.default_rng(1800)
