@@ -1,12 +1,13 @@
 // tree_verify_attention: tree-masked attention of the draft-tree query rows against the committed
 // prefix cache plus the tree's own K/V (Section 3.3, "Execution view" and "Tree attention mask").
 //
-// Two kernels compute the per-split partial (m, l, O):
+// Three kernels compute the per-split partial (m, l, O):
 //   * attn_mfma_kernel   bf16: K/V tiles staged through LDS, QK^T and PV on
 //                        v_mfma_f32_32x32x16_bf16, online softmax in registers, the ancestor mask applied
 //                        as a per-row bitmask only on the tree tile.
+//   * attn_f32_kernel    fp32: both products on v_mfma_f32_16x16x4_f32, no barrier in the tile loop.
 //   * attn_generic_kernel  any supported dtype / head dim, fp32 VALU arithmetic, one wavefront per query
-//                        row.  It is the fp32 path (bit-for-bit fp32 inputs need fp32 products).
+//                        row; runs only where ETV_ATTN_FLAG_GENERIC asks for it, as an independent check.
 // and attn_combine_kernel merges the splits by log-sum-exp.  With a single split the partial kernels write
 // the final output themselves.
 //
@@ -1145,10 +1146,290 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(AttnParams p) {
 }
 
 // ----------------------------------------------------------------------------------------------
+// fp32 kernel (d = 128 or 64): both products on v_mfma_f32_16x16x4_f32, which multiplies and adds in fp32.
+//
+// Work unit: (split, KV head, sequence) x 16-row chunk of the KV head's packed query rows, one workgroup of four
+// wavefronts that take the 16-key tiles of the split in turn and merge their (m, l, O) through LDS at the end.  No tile
+// is shared inside a workgroup, so the loop has no barrier.  V goes from memory straight into the registers that the
+// matrix instructions read (16 lanes fetch 256 consecutive bytes of a row).  The K operand wants a different row in each
+// of 16 neighbouring lanes, which the vector memory path serves at a quarter of its rate: K tiles take the way through LDS, two buffers per
+// wavefront, filled by direct-to-LDS loads one tile ahead (a lone wavefront's tile 1.35 us, against 1.55 with K in registers,
+// of which the matrix instructions are 0.86).
+// The chunks of one (split, KV head, sequence) re-read its K/V; they get ids that differ by 8, so they run side by side
+// on one XCD and find it in that XCD's L2.
+//
+// 64-lane layouts of the 16x16x4 instruction: A / B operand lane = (row | col l % 16, contraction index l / 16),
+// accumulator lane = (col l % 16, rows 4 * (l / 16) + i).  With c = l % 16, g = l / 16:
+//   S^T[key, q]: A = K[c][16 j + 4 g + e], B = Q[c][16 j + 4 g + e], e = 0..3 from one 16-byte load
+//   O^T[d, q]:   B = p[i] of key 4 g + i straight from the S^T accumulator, A = V[4 g + i][64 v + 4 c + e], e = 0..3 from
+//                one 16-byte load: accumulator (v, e) holds columns d = 64 v + 4 * row + e
+// so a query row is a lane column in both, and only the row maximum crosses lanes (c, g) -> (c, g').
+//
+// B = 2, T = 33, 16/4 heads of 128, P = 771 / 1003: 18 us (262 us with one wavefront per query row on the vector ALU,
+// which re-read every key row for each of the G * T rows); B = 1, T = 15, 4/4 heads of 64, P = 128: 6.6 us against
+// 19.7 and a combine launch of 4.0; B = 16, T = 128, P = 2048, 32/8 heads of 128: 646 us, 109 TFLOP/s (the library's fp32
+// matrix product reaches 144 ... 154 on this machine).
+// ----------------------------------------------------------------------------------------------
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+
+__device__ __forceinline__ float quad_max(float v) {  // over the lanes c, c + 16, c + 32, c + 48
+    auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return fmaxf(__uint_as_float(q[0]), __uint_as_float(q[1]));
+}
+
+constexpr int F32_NW = 4;    // wavefronts of a workgroup
+constexpr int F32_ROWS = 16; // query rows of a chunk = keys of a tile
+
+template <int D>
+__global__ void __launch_bounds__(F32_NW * 64, 2) attn_f32_kernel(AttnParams p) {
+    constexpr int KJ = D / 16, VB = D / 64, ROWB = 4 * D;
+    const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // 1-D grid: id = ((unit / 8) * chunks + chunk) * 8 + unit % 8, unit = slot * Hkv + KV head, slot = (sequence, split)
+    const int rest = blockIdx.x >> 3, rg = rest % p.pairs;
+    const long unit = (long)(rest / p.pairs) * 8 + (blockIdx.x & 7);
+    const int slot = (int)(unit / p.Hkv), kvh = (int)(unit % p.Hkv);
+    if (slot >= p.B * p.nsplit) return;  // uniform over the workgroup
+    SplitShare share{};
+    if (p.balanced) {
+        share = balanced_share(p, slot, lane);
+        if (!share.live) return;  // uniform over the workgroup
+        if (share.j == 0 && kvh == 0 && rg == 0 && threadIdx.x == 0) p.split_tab[share.b] = make_int2(share.start, share.nvalid);
+    }
+    const int b = p.balanced ? share.b : slot / p.nsplit;
+    const int s = p.balanced ? share.j : slot % p.nsplit;
+    const int chunk = p.balanced ? share.tps * KT : p.chunk;
+    const int n = clampi(p.balanced ? share.n_raw : p.n_nodes[b], 0, p.T_max);
+    const int P = clampi(p.balanced ? share.P_raw : p.prefix_len[b], 0, p.P_max);
+    const int nvalid = p.balanced ? share.nvalid : seq_nsplit(p, P);
+    if (s >= nvalid) return;  // uniform over the workgroup
+    const bool direct = (p.nsplit == 1);
+
+    const int r = rg * F32_ROWS + c;  // the lane's packed query row: node kq, head h
+    const int kq = r / p.G, h = kvh * p.G + (r - kq * p.G);
+    const bool rv = kq < n;
+    const int k0 = s * chunk, k1 = min(P, k0 + chunk);
+    const bool active = rg * F32_ROWS < n * p.G;  // does the chunk hold a valid row?
+    const int nfull = (active && k1 > k0) ? (k1 - k0) >> 4 : 0;     // full prefix tiles
+    const int npt = (active && k1 > k0) ? (k1 - k0 + 15) >> 4 : 0;  // prefix tiles incl. a ragged last one
+    const int nt = npt + ((active && s == nvalid - 1) ? (n + 15) >> 4 : 0);
+
+    const uint8_t *kc = static_cast<const uint8_t *>(p.k_cache), *vc = static_cast<const uint8_t *>(p.v_cache);
+    const uint8_t *kt = static_cast<const uint8_t *>(p.kt), *vt = static_cast<const uint8_t *>(p.vt);
+    const const_i32_ptr bt = (const_i32_ptr)(uintptr_t)(p.block_size ? p.block_table + (size_t)b * p.max_blocks : nullptr);
+    const size_t hstride = (size_t)p.Hkv * ROWB;  // between the rows of a head (contiguous cache, tree buffer)
+
+    // K tiles go into LDS buffer `buf` of the wavefront.  A 1 KiB load covers RPL rows; chunk x (16 bytes) of row r is kept
+    // at position x ^ r, which spreads the reads of 16 rows at one chunk over all banks.
+    constexpr int CPR = ROWB / 16, RPL = 64 / CPR, LOADS = 16 / RPL, TILE = 16 * ROWB;
+    __shared__ __attribute__((aligned(1024))) uint8_t smem[F32_NW * 2 * TILE];
+    uint8_t *const kbuf = smem + wave * (2 * TILE);
+    const uint32_t kbuf_addr = (uint32_t)__builtin_amdgcn_readfirstlane(
+        (int)(uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)kbuf);
+    const int lr = lane / CPR, lp = lane % CPR;
+
+    // Full prefix tiles: a scalar base (block or row) plus per-lane offsets that are the same for every tile.
+    const uint32_t rstride = (uint32_t)(bt ? (size_t)ROWB : hstride);
+    uint32_t koff[LOADS], voff[4];
+#pragma unroll
+    for (int u = 0; u < LOADS; u++) koff[u] = (RPL * u + lr) * rstride + ((lp ^ (RPL * u + lr)) * 16);
+#pragma unroll
+    for (int i = 0; i < 4; i++) voff[i] = (4 * g + i) * rstride + 16 * c;
+    auto full_off = [&](int t) -> size_t {
+        const int base = k0 + t * 16;
+        return bt ? ((size_t)bt[base >> 4] * p.Hkv + kvh) * (size_t)(16 * ROWB)
+                  : (((size_t)b * p.P_cap + base) * p.Hkv + kvh) * (size_t)ROWB;
+    };
+    auto full_k = [&](size_t off, int buf) {
+#pragma unroll
+        for (int u = 0; u < LOADS; u++) async_load16_s<false>(kc + off, koff[u], kbuf_addr + buf * TILE + u * 1024);
+    };
+    // Ragged last prefix tile and tree tiles: rows past the end repeat the last valid one (masked later).
+    auto edge_row = [&](int t, int j, const uint8_t *cache, const uint8_t *own) -> const uint8_t * {
+        const bool tree = t >= npt;
+        const int base = tree ? (t - npt) * 16 : k0 + t * 16;
+        const int key = min(base + j, (tree ? n : k1) - 1);
+        if (tree && own) return own + (((size_t)b * p.T_max + key) * p.Hkv + kvh) * (size_t)ROWB;
+        const int pos = tree ? P + key : key;  // in-place branch cache: node j at position P + j
+        if (bt) return cache + (((size_t)bt[pos >> 4] * p.Hkv + kvh) * 16 + (pos & 15)) * (size_t)ROWB;
+        return cache + (((size_t)b * p.P_cap + pos) * p.Hkv + kvh) * (size_t)ROWB;
+    };
+    auto edge_k = [&](int t, int buf) {
+#pragma unroll
+        for (int u = 0; u < LOADS; u++)
+            async_load16(edge_row(t, RPL * u + lr, kc, kt) + ((lp ^ (RPL * u + lr)) * 16), kbuf_addr + buf * TILE + u * 1024);
+    };
+
+    f32x4 qf[KJ], o[VB][4];
+    float m_run = -INFINITY, l_run = 0.f;
+    size_t cur = 0;
+    if (wave < nfull) {
+        cur = full_off(wave);
+        full_k(cur, 0);
+    } else if (wave < nt) {
+        edge_k(wave, 0);
+    }
+    const float *qrow = static_cast<const float *>(p.q) + (((size_t)b * p.T_max + kq) * p.Hq + h) * D + 4 * g;
+#pragma unroll
+    for (int j = 0; j < KJ; j++) qf[j] = rv ? *reinterpret_cast<const f32x4 *>(qrow + 16 * j) : f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int v = 0; v < VB; v++)
+#pragma unroll
+        for (int e = 0; e < 4; e++) o[v][e] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const uint64_t *mrow = p.bitmask + ((size_t)b * p.T_max + (rv ? kq : 0)) * p.words;
+
+    // Q . K of the tile in buffer `buf`, online softmax, P . V with the V rows already requested.  vis: keys that the
+    // lane's row sees.
+    auto tile = [&](int buf, const f32x4 (&vf)[4][VB], uint32_t vis, bool masked) {
+        const uint8_t *krow = kbuf + buf * TILE + c * ROWB;
+        f32x4 kf[KJ], s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;  // two chains
+#pragma unroll
+        for (int j = 0; j < KJ; j++) kf[j] = *reinterpret_cast<const f32x4 *>(krow + (((4 * j + g) ^ c) * 16));
+#pragma unroll
+        for (int j = 0; j < KJ; j += 2)
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[j][e], qf[j][e], s0, 0, 0, 0);
+                s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[j + 1][e], qf[j + 1][e], s1, 0, 0, 0);
+            }
+        float sc[4];
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            sc[i] = (s0[i] + s1[i]) * p.scale_log2;
+            if (masked) sc[i] = ((vis >> (4 * g + i)) & 1u) ? sc[i] : -INFINITY;
+        }
+        const float tmax = quad_max(fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3])));
+        const bool lift = tmax > m_run + kLazy;
+        if (__any(lift)) {
+            const float m_new = lift ? tmax : m_run;
+            const float alpha = lift ? __builtin_amdgcn_exp2f(m_run - m_new) : 1.f;
+            m_run = m_new;
+            l_run *= alpha;
+#pragma unroll
+            for (int v = 0; v < VB; v++)
+#pragma unroll
+                for (int e = 0; e < 4; e++) o[v][e] *= alpha;
+        }
+        const float ref = (masked && m_run == -INFINITY) ? 0.f : m_run;
+        float pr[4];
+#pragma unroll
+        for (int i = 0; i < 4; i++) pr[i] = __builtin_amdgcn_exp2f(sc[i] - ref);
+        l_run += (pr[0] + pr[1]) + (pr[2] + pr[3]);
+#pragma unroll
+        for (int i = 0; i < 4; i++)
+#pragma unroll
+            for (int v = 0; v < VB; v++)
+#pragma unroll
+                for (int e = 0; e < 4; e++)
+                    o[v][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[i][v][e], pr[i], o[v][e], 0, 0, 0);
+    };
+    // A K tile is in LDS when its turn comes: the first one is waited for at the top, a later one is older than the V rows
+    // that the previous products have used.  The next K tile is requested before this tile's V rows for that reason.
+    int t = wave, buf = 0;
+    for (; t < nfull; t += F32_NW, buf ^= 1) {
+        wait_vmcnt<0>();
+        asm volatile("" ::: "memory");
+        const uint8_t *vb = vc + cur;
+        const int tn = t + F32_NW;
+        if (tn < nfull) {
+            cur = full_off(tn);
+            full_k(cur, buf ^ 1);
+        } else if (tn < nt) {
+            edge_k(tn, buf ^ 1);
+        }
+        f32x4 vf[4][VB];
+#pragma unroll
+        for (int i = 0; i < 4; i++)
+#pragma unroll
+            for (int v = 0; v < VB; v++) vf[i][v] = *reinterpret_cast<const f32x4 *>(vb + voff[i] + 256 * v);
+        tile(buf, vf, 0xffffu, false);
+    }
+    for (; t < nt; t += F32_NW, buf ^= 1) {
+        wait_vmcnt<0>();
+        asm volatile("" ::: "memory");
+        if (t + F32_NW < nt) edge_k(t + F32_NW, buf ^ 1);
+        f32x4 vf[4][VB];
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            const uint8_t *row = edge_row(t, 4 * g + i, vc, vt) + 16 * c;
+#pragma unroll
+            for (int v = 0; v < VB; v++) vf[i][v] = *reinterpret_cast<const f32x4 *>(row + 256 * v);
+        }
+        uint32_t vis;
+        if (t >= npt) {
+            const int j0 = (t - npt) * 16;
+            vis = rv ? (uint32_t)(mrow[j0 >> 6] >> (j0 & 63)) & 0xffffu : 0u;
+        } else {
+            vis = (1u << (k1 - k0 - t * 16)) - 1u;  // ragged last prefix tile: 1..15 keys
+        }
+        tile(buf, vf, vis, true);
+    }
+
+    // ---- merge the four wavefronts
+    static_assert(F32_NW * F32_ROWS * (D + 6) * 4 <= F32_NW * 2 * TILE, "the merge fits the K buffers");
+    __syncthreads();  // every wavefront has read its last K tile
+    float (*s_o)[F32_ROWS][D + 4] = reinterpret_cast<float (*)[F32_ROWS][D + 4]>(smem);
+    float (*s_m)[F32_ROWS] = reinterpret_cast<float (*)[F32_ROWS]>(smem + sizeof(float) * F32_NW * F32_ROWS * (D + 4));
+    float (*s_l)[F32_ROWS] = s_m + F32_NW;
+    l_run += __shfl_xor(l_run, 16);
+    l_run += __shfl_xor(l_run, 32);
+#pragma unroll
+    for (int v = 0; v < VB; v++)
+#pragma unroll
+        for (int i = 0; i < 4; i++)
+            *reinterpret_cast<f32x4 *>(&s_o[wave][c][64 * v + 16 * g + 4 * i]) = f32x4{o[v][0][i], o[v][1][i], o[v][2][i], o[v][3][i]};
+    if (g == 0) {
+        s_m[wave][c] = m_run;
+        s_l[wave][c] = l_run;
+    }
+    __syncthreads();
+    const int row = threadIdx.x >> 4, piece = threadIdx.x & 15;  // a row's 16 threads own columns 64 v + 4 * piece .. + 3
+    const int r2 = rg * F32_ROWS + row, kq2 = r2 / p.G, h2 = kvh * p.G + (r2 - kq2 * p.G);
+    if (kq2 >= p.T_max) return;
+    const bool rv2 = kq2 < n;
+    if (!rv2 && !direct) return;
+    float M = -INFINITY, L = 0.f, w[F32_NW];
+#pragma unroll
+    for (int x = 0; x < F32_NW; x++) M = fmaxf(M, s_m[x][row]);
+#pragma unroll
+    for (int x = 0; x < F32_NW; x++) {
+        w[x] = s_m[x][row] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(s_m[x][row] - M);
+        L = fmaf(w[x], s_l[x][row], L);
+    }
+    const size_t pr = part_row(p, slot, h2, kq2);
+    float *dst = direct ? static_cast<float *>(p.out) + (((size_t)b * p.T_max + kq2) * p.Hq + h2) * D : p.part_o + pr * D;
+    const float inv = direct ? (rv2 ? 1.f / L : 0.f) : 1.f;
+#pragma unroll
+    for (int v = 0; v < VB; v++) {
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int x = 0; x < F32_NW; x++) {
+            const f32x4 ox = *reinterpret_cast<const f32x4 *>(&s_o[x][row][64 * v + 4 * piece]);
+#pragma unroll
+            for (int e = 0; e < 4; e++) acc[e] = fmaf(w[x], ox[e], acc[e]);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; e++) acc[e] = rv2 ? acc[e] * inv : 0.f;
+        *reinterpret_cast<f32x4 *>(dst + 64 * v + 4 * piece) = acc;
+    }
+    if (piece == 0) {
+        if (direct) {
+            if (p.lse) p.lse[((size_t)b * p.Hq + h2) * p.T_max + kq2] = rv2 ? (M + log2f(L)) * kLn2 : -INFINITY;
+        } else {
+            p.part_m[pr] = M;
+            p.part_l[pr] = L;
+        }
+    }
+}
+
+// ----------------------------------------------------------------------------------------------
 // host side
 // ----------------------------------------------------------------------------------------------
 struct Plan {
-    bool mfma, kh;
+    bool mfma, kh;  // mfma: attn_mfma_kernel
+    bool f32;       // attn_f32_kernel
     int nw, ns, pairs, wgp, chunk, nsplit;
     bool balanced;  // split slots shared out among the sequences by their lengths, on the device
 };
@@ -1171,11 +1452,46 @@ constexpr double kTileKhAlone = 1.1, kTileKhShared = 2.2, kTileKh8 = 1.65;
 constexpr double kTileWhole8 = 2.65;
 // At d = 64 a tile costs about 0.6 of that in every shape (the softmax does not shrink), and what the constants pick is
 // the best forced shape or within 5 % of it (seven workloads, B = 1 ... 32, T = 8 ... 128), so they serve both.
+static long f32_blocks(const etv_attn_desc *h, const Plan &pl) {
+    return ((long)h->B * pl.nsplit * h->Hkv + 7) / 8 * 8 * pl.pairs;
+}
+
 static Plan make_plan(const etv_attn_desc *h) {
     Plan pl{};
     const int tiles = max(1, (h->P_max + KT - 1) / KT);
     const int B = max(1, h->B);
-    pl.mfma = (h->dtype == ETV_BF16 && !(h->flags & ETV_ATTN_FLAG_GENERIC));  // d is 64 or 128
+    // d is 64 or 128.  The row groups of all KV heads share a grid dimension of at most 65535; thousands of heads with the
+    // largest trees that go beyond it stay on the kernel with a workgroup per row.
+    const long rows = (long)(h->Hq / h->Hkv) * h->T_max;
+    const bool generic = (h->flags & ETV_ATTN_FLAG_GENERIC) != 0;
+    pl.mfma = h->dtype == ETV_BF16 && !generic && (h->d == 128 || h->Hkv * ((rows + 63) / 64) <= 65535);
+    pl.f32 = h->dtype == ETV_F32 && !generic;
+    if (pl.f32) {
+        // A workgroup puts one wavefront on each SIMD of a compute unit and the matrix cores bound the launch: its time is
+        // the tiles of a wavefront times the workgroups of the fullest compute unit, and not less than a tile's latency
+        // chain allows; every split adds partials and a combine step, the first one the combine launch.  Measured per tile:
+        // 1.1 us at d = 128 (0.6 at d = 64) times the wavefronts of a SIMD, 1.35 us (0.8) for a lone one, of which
+        // 0.86 (0.43) are matrix instructions; 16384 keys, T = 1: 24 us with 43 splits, 36 with 128.
+        pl.pairs = (int)((rows + F32_ROWS - 1) / F32_ROWS);
+        const double busy = h->d == 128 ? 1.1 : 0.6, chain = h->d == 128 ? 1.35 : 0.8;
+        const double part_us = 2.0 * B * h->Hq * h->T_max * (h->d + 2.0) * 4.0 / 3.0e6;
+        const long units = (long)B * h->Hkv * pl.pairs;
+        const int forced_tps = h->kv_split > 0 ? min(tiles, (h->kv_split + KT - 1) / KT) : 0;
+        double best = 1e30;
+        for (int ns = 1; ns <= tiles; ns++) {
+            const int tps = forced_tps ? forced_tps : (tiles + ns - 1) / ns;
+            if ((tiles + tps - 1) / tps != ns) continue;
+            const double per_wave = ceil((tps * 4.0 + (h->T_max + 15) / 16) / F32_NW);
+            const double full = ceil((double)(units * ns) / 256.0);
+            const double est = per_wave * (full * busy > chain ? full * busy : chain) + (ns > 1 ? 4.0 + ns * (part_us + 0.1) : 0.0);
+            if (est < best) {
+                best = est;
+                pl.chunk = tps * KT; pl.nsplit = ns;
+            }
+        }
+        pl.balanced = pl.nsplit > 1 && B >= 2 && B <= 64 && !(h->flags & ETV_ATTN_FLAG_UNIFORM_SPLITS);
+        return pl;
+    }
     if (!pl.mfma) {
         const long units = ((long)B * h->Hq * h->T_max + 7) / 8;  // 8 resident wavefronts ~ one workgroup slot
         int tps;
@@ -1274,15 +1590,15 @@ extern "C" int32_t etv_tree_verify_attention_plan(const etv_attn_desc *h, etv_at
     if (!h || !out || !etv::supported(h) || h->Hq % h->Hkv != 0) return ETV_ERR_INVALID_ARG;
     const etv::Plan pl = etv::make_plan(h);
     out->mfma = pl.mfma ? 1 : 0;
-    out->wavefronts = pl.mfma ? pl.nw : 1;
+    out->wavefronts = pl.mfma ? pl.nw : (pl.f32 ? etv::F32_NW : 1);
     out->key_halves = pl.mfma && pl.kh ? 1 : 0;
     out->ring_stages = pl.mfma ? pl.ns : 0;
-    out->row_groups = pl.mfma ? pl.wgp : 0;
+    out->row_groups = pl.mfma ? pl.wgp : (pl.f32 ? pl.pairs : 0);
     out->kv_split = pl.chunk;
     out->n_splits = pl.nsplit;
-    out->balanced_splits = pl.mfma && pl.balanced ? 1 : 0;
-    out->workgroups = pl.mfma ? (int64_t)pl.nsplit * h->Hkv * pl.wgp * (h->B > 0 ? h->B : 0)
-                              : (int64_t)h->T_max * h->Hq * (h->B > 0 ? h->B : 0) * pl.nsplit;
+    out->balanced_splits = pl.balanced ? 1 : 0;
+    out->workgroups = pl.mfma || pl.f32 ? (int64_t)pl.nsplit * h->Hkv * out->row_groups * (h->B > 0 ? h->B : 0)
+                                        : (int64_t)h->T_max * h->Hq * (h->B > 0 ? h->B : 0) * pl.nsplit;
     return ETV_OK;
 }
 
@@ -1323,7 +1639,8 @@ static int32_t attention_run(const etv_attn_desc *h, const void *q, const void *
     if (h->B > 65535) return ETV_ERR_UNSUPPORTED;
 
     Plan pl = make_plan(h);
-    if ((long)h->B * pl.nsplit > 65535 && !pl.mfma) return ETV_ERR_UNSUPPORTED;
+    if ((long)h->B * pl.nsplit > 65535 && !pl.mfma && !pl.f32) return ETV_ERR_UNSUPPORTED;
+    if (pl.f32 && f32_blocks(h, pl) > 0x7fffffffL) return ETV_ERR_UNSUPPORTED;
     if (pl.nsplit > 1) {
         if (!workspace || workspace_bytes < etv_tree_verify_attention_workspace_bytes(h))
             return ETV_ERR_WORKSPACE_TOO_SMALL;
@@ -1344,7 +1661,7 @@ static int32_t attention_run(const etv_attn_desc *h, const void *q, const void *
         p.part_m = p.part_o + rows * h->d;
         p.part_l = p.part_m + rows;
         p.split_tab = reinterpret_cast<int2 *>(p.part_l + rows);  // 8-byte aligned: rows * (d + 2) floats in
-        p.balanced = pl.mfma && pl.balanced;
+        p.balanced = pl.balanced;
     }
     hipStream_t st = as_stream(stream);
     int32_t rc;
@@ -1352,6 +1669,11 @@ static int32_t attention_run(const etv_attn_desc *h, const void *q, const void *
         const dim3 grid = pl.balanced ? dim3(pl.nsplit * h->B, h->Hkv * pl.wgp, 1) : dim3(pl.nsplit, h->Hkv * pl.wgp, h->B);
         rc = h->d == 128 ? launch_mfma_shape<128>(pl, h->block_size > 0, p, grid, st)
                          : launch_mfma_shape<64>(pl, h->block_size > 0, p, grid, st);
+    } else if (pl.f32) {
+        const dim3 grid((unsigned)f32_blocks(h, pl));
+        if (h->d == 64) hipLaunchKernelGGL((attn_f32_kernel<64>), grid, dim3(F32_NW * 64), 0, st, p);
+        else hipLaunchKernelGGL((attn_f32_kernel<128>), grid, dim3(F32_NW * 64), 0, st, p);
+        rc = check_launch();
     } else {
         dim3 grid(h->T_max, h->Hq, h->B * pl.nsplit);
         if (h->dtype == ETV_F32 && h->d == 64)

@@ -161,6 +161,24 @@ def test_mfma_kernel_heads_of_64(flags, paged):
             assert rel <= 2.0 ** -8, (T, kv_split, rel)
 
 
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("d", [64, 128])
+def test_fp32_kernel_tile_and_chunk_edges(d, paged):
+    """The fp32 matrix-core kernel at the edges of its 16-key tiles, of its 16-row chunks (T * G around multiples of 16) and
+    of the four wavefronts that share a split's tiles; splits, and the vector kernel on the same inputs.  fp32 products
+    and sums on both sides: 1e-5 as for every fp32 case."""
+    rng = np.random.default_rng(3200 + d + paged)
+    P = [0, 1, 15, 16, 17, 31, 33, 47, 63, 64, 65, 300]
+    n = [17, 1, 16, 15, 17, 2, 17, 9, 17, 16, 1, 17]
+    for T, Hq, Hkv, P, n in ((17, 4, 2, P, n), (1, 4, 4, [130, 0], [1, 1]), (33, 3, 1, [80, 79], [33, 31]), (256, 2, 2, [70], [255])):
+        for q_scale in (1.0, 4.0):
+            wl = _small(rng, len(P), T, Hq, Hkv, d, P, "f32", paged, n_nodes=n, q_scale=q_scale)
+            for kv_split in (0, 64, 4096):
+                _check(wl, kv_split=kv_split)
+            _check(wl, kv_split=64, flags=api.ATTN_FLAG_UNIFORM_SPLITS)
+            _check(wl, flags=api.ATTN_FLAG_GENERIC)
+
+
 def test_key_halves_merge_is_deterministic():
     """The merge of the two key halves has a fixed order: two launches on the same inputs give the same bits."""
     rng = np.random.default_rng(1800)
