@@ -64,8 +64,8 @@ __device__ __forceinline__ void posterior_for_sequence(
     __shared__ int32_t s_len[256];
     __shared__ int32_t s_path[256];
     if (pval && chunks > 16) {
-        // many partials per node (the per-tile maxima of the fused head): one wavefront per node, lanes stride
-        // over the partials, shuffle reduce
+        // many partials per node (the per-tile maxima of the fused head) and few nodes: one wavefront per node, lanes
+        // stride over the partials, shuffle reduce
         const int lane = t & 63;
         for (int node = t >> 6; node < T_max; node += 4) {
             MaxIdx m = {-INFINITY, 0x7fffffff};
@@ -338,6 +338,10 @@ __device__ __forceinline__ void commit_compact_layer(const etv_commit_desc &dsc,
     }
 }
 
+// host side, defined next to the head kernels: argmax[row] (and maxval, nullable) from the partials [rows_total][partials],
+// one wavefront per row
+int32_t launch_finish_argmax(const float *pval, const int32_t *pidx, int partials, const int32_t *n_nodes, long rows_total,
+                             int T_max, int32_t *argmax, float *maxval, hipStream_t s);
 // host side, defined next to the commit kernels
 int32_t check_commit_args(const etv_commit_desc *h, const void *kt, const void *vt, const void *k_cache,
                           const void *v_cache, const int32_t *block_table);

@@ -27,7 +27,7 @@
 // and the stream reaches 4.6-4.8 TB/s; with the weights packed once into tiles ([V/128][D/128][128 rows][128],
 // etv_pack_lm_head) a step's tile is 32 KiB of consecutive memory and the same kernel reaches 5.5-5.8 TB/s.
 // Both layouts are accepted.
-#include "etv_common.h"
+#include "epilogue_parts.h"
 
 namespace etv {
 
@@ -634,6 +634,13 @@ __global__ void __launch_bounds__(256) lm_head_finish_kernel(const float *__rest
     }
 }
 
+int32_t launch_finish_argmax(const float *pval, const int32_t *pidx, int partials, const int32_t *n_nodes, long rows_total,
+                             int T_max, int32_t *argmax, float *maxval, hipStream_t s) {
+    hipLaunchKernelGGL(lm_head_finish_kernel, dim3((unsigned)((rows_total + 3) / 4)), dim3(256), 0, s, pval, pidx, partials,
+                       n_nodes, (int)rows_total, T_max, argmax, maxval);
+    return check_launch();
+}
+
 // Packing: out[tile][step][r][c] = weight[tile * 128 + r][step * 128 + c], zeros for rows past V.
 // One thread per 16-byte piece.
 __global__ void __launch_bounds__(256) lm_head_pack_kernel(const uint4 *__restrict__ weight, uint4 *__restrict__ out,
@@ -725,7 +732,5 @@ extern "C" int32_t etv_lm_head_argmax(const void *hidden, const void *weight, in
     else hipLaunchKernelGGL(lm_head_argmax_kernel, dim3((unsigned)nblocks), dim3(512), lds, s, p);
     int32_t rc = check_launch();
     if (rc != ETV_OK || !argmax) return rc;  // without argmax the per-tile maxima stay in the workspace for the epilogue
-    hipLaunchKernelGGL(lm_head_finish_kernel, dim3((unsigned)((rows_total + 3) / 4)), dim3(256), 0, s, p.pval, p.pidx,
-                       (int)tiles, n_nodes, (int)rows_total, (int)T_max, argmax, maxval);
-    return check_launch();
+    return launch_finish_argmax(p.pval, p.pidx, (int)tiles, n_nodes, rows_total, T_max, argmax, maxval, s);
 }

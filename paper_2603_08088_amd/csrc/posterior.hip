@@ -149,6 +149,20 @@ __global__ void __launch_bounds__(256) verify_epilogue_kernel(
     }
 }
 
+// Many partials per node (the per-tile maxima of the fused head: 250 at V = 32000): the acceptance kernels run one
+// workgroup per sequence -- the epilogue one per sequence and layer group, each of which would repeat the reduction -- and
+// a wavefront reduces one node per trip to memory, so beyond a few nodes a launch of one wavefront per node comes first
+// and hands on the choice per node.  Epilogue over 32 layers, V = 32000, inline / with the extra launch: T = 8 8.2 / 9.4 us,
+// T = 16 9.7 / 8.9, T = 60 21.6 / 9.5; B = 32: T = 8 15.5 / 15.8, T = 128 71.3 / 18.6.
+constexpr int kInlineNodes = 12, kInlinePartials = 16;
+static int32_t finish_partials_first(float *&pval, const int32_t *pidx, int chunks, const int32_t *n_nodes, int B, int T_max,
+                                     int32_t *argmax, hipStream_t s) {
+    if (!pval || chunks <= kInlinePartials || T_max <= kInlineNodes) return ETV_OK;
+    const int32_t rc = launch_finish_argmax(pval, pidx, chunks, n_nodes, (long)B * T_max, T_max, argmax, nullptr, s);
+    pval = nullptr;
+    return rc;
+}
+
 }  // namespace etv
 
 extern "C" int32_t etv_safe_gather_paths(const int32_t *retrieve, const int32_t *n_nodes, int32_t B, int32_t L_max,
@@ -208,6 +222,8 @@ extern "C" int32_t etv_evaluate_posterior(const float *logits, const int32_t *to
         pval = static_cast<float *>(workspace);
         pidx = reinterpret_cast<int32_t *>(pval + (size_t)B * T_max * chunks);
     }
+    rc = etv::finish_partials_first(pval, pidx, chunks, n_nodes, B, T_max, argmax, s);
+    if (rc != ETV_OK) return rc;
     hipLaunchKernelGGL(etv::posterior_paths_kernel, dim3(B), dim3(256), 0, s, pval, pidx, chunks, tokens, retrieve,
                        n_nodes, (int)T_max, (int)L_max, (int)W, (int)dummy, argmax, len, best, accept_len, acc_nodes,
                        bonus);
@@ -259,6 +275,8 @@ extern "C" int32_t etv_verify_epilogue(const etv_commit_desc *h, const float *lo
         pval = static_cast<float *>(workspace);
         pidx = reinterpret_cast<int32_t *>(pval + (size_t)B * T_max * chunks);
     }
+    rc = etv::finish_partials_first(pval, pidx, chunks, n_nodes, B, T_max, argmax, s);
+    if (rc != ETV_OK) return rc;
     const long gather_blocks = (safe || pvalid || gathered) ? ((long)B * L_max * h->W + 3) / 4 : 0;
     // layer groups per sequence: enough workgroups to spread the row copies over the chip, at most one per layer
     const int G = std::max(1, std::min((int)h->n_layers, 512 / B));

@@ -221,3 +221,31 @@ def test_head_to_commit_without_logits():
     for key in rc:
         assert np.array_equal(bits_of(c[key]), rc[key]), key
     assert np.array_equal(bits_of(dkc), kc) and np.array_equal(bits_of(dvc), vc)
+
+
+@pytest.mark.parametrize("T", [12, 13, 70])
+@pytest.mark.parametrize("V", [2048, 2049, 8200])
+def test_partials_of_the_head_are_finished_inline_or_by_a_launch(T, V):
+    """The choice per node out of the head's per-tile maxima, on both sides of the rule that picks where they are reduced
+    (nodes per tree, partials per node): hand-made partials with ties, against numpy and the oracle's acceptance."""
+    from helpers import logits_from_argmax, random_tree
+    rng = np.random.default_rng(100 * T + V)
+    B, tiles = 3, (V + 127) // 128
+    n = [T, 1, max(1, T - 5)]
+    parents = [random_tree(rng, x) for x in n]
+    wl = synth.assemble("partials", rng, parents, [40] * B, Hq=2, Hkv=2, d=64, dtype="bf16", V=V, W=T, paged=False, T_max=T,
+                        with_logits=False)
+    pval = rng.integers(0, 9, size=(B, T, tiles)).astype(np.float32)            # few distinct values: ties across tiles
+    pidx = np.minimum(np.arange(tiles) * 128 + rng.integers(0, 128, size=(B, T, tiles)), V - 1).astype(np.int32)
+    want = np.take_along_axis(pidx, pval.argmax(axis=2)[..., None], axis=2)[..., 0]   # first maximum = lowest index
+    lg = np.stack([logits_from_argmax(rng, want[b], V) for b in range(B)])
+    rp = oracle.evaluate_posterior(lg, wl.tokens, wl.retrieve, wl.n_nodes)
+    ws = torch.cat([to_dev(pval).reshape(-1).view(torch.uint8), to_dev(pidx).reshape(-1).view(torch.uint8)])
+    tok, ret, dn = to_dev(wl.tokens), to_dev(wl.retrieve), to_dev(wl.n_nodes)
+    p = api.evaluate_posterior(None, tok, ret, dn, workspace=ws, head_V=V)
+    kt, vt, kc, vc = (to_dev(x)[None].clone() for x in (wl.kt, wl.vt, wl.k_cache, wl.v_cache))
+    _, q, _ = api.verify_epilogue(None, tok, ret, dn, kt, vt, kc, vc, to_dev(wl.prefix_len), to_dev(wl.capacity),
+                                  workspace=ws, head_V=V)
+    torch.cuda.synchronize()
+    for key in rp:
+        assert np.array_equal(bits_of(p[key]), rp[key]) and np.array_equal(bits_of(q[key]), rp[key]), key
