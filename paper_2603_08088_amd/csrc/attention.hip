@@ -448,12 +448,11 @@ __device__ __forceinline__ float half_swap_max(float v) {
     auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
     return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
-// three-input max as one instruction.  (fmaxf would first canonicalise each MFMA result with an extra v_max,
-// doubling the instruction count of the row-max reduction; scores are never NaN here.)
+// Three-input max as one instruction (v_maximum3_f32).  fmaxf would first canonicalise each MFMA result with an extra
+// v_max; an asm statement hides from the compiler that the instruction reads a matrix result, and it then issues before
+// that result is written (the maximum of a row came out stale now and then).
 __device__ __forceinline__ float max3(float a, float b, float c) {
-    float r;
-    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-    return r;
+    return __builtin_elementwise_maximum(__builtin_elementwise_maximum(a, b), c);
 }
 __device__ __forceinline__ float half_swap_sum(float v) {
     auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);

@@ -179,6 +179,26 @@ def test_fp32_kernel_tile_and_chunk_edges(d, paged):
             _check(wl, flags=api.ATTN_FLAG_GENERIC)
 
 
+@pytest.mark.parametrize("flags", [api.ATTN_FLAG_WHOLE_TILE | api.ATTN_FLAG_LARGE_WG, api.ATTN_FLAG_WHOLE_TILE | api.ATTN_FLAG_SMALL_WG,
+                                   api.ATTN_FLAG_KEY_HALVES | api.ATTN_FLAG_LARGE_WG])
+@pytest.mark.parametrize("d", [64, 128])
+def test_row_maximum_uses_the_finished_scores(d, flags):
+    """The reference of a row's softmax must come from the scores after the last matrix instruction.  Keys 0 and 32 of the
+    first tile (read first by the maximum) get scores of hundreds of log2 units that sit entirely in the last 16
+    dimensions, i.e. in the last instruction: a reference without them overflows the exponentials."""
+    rng = np.random.default_rng(77 + d + flags)
+    for key in (0, 4, 32, 36, 1, 33):
+        wl = _small(rng, 1, 64, 8, 2, d, [320], "bf16", False)
+        q, k = np.zeros(wl.q.shape, np.float32), rng.standard_normal(wl.k_cache.shape).astype(np.float32)
+        q[..., d - 16:] = 16.0
+        k[..., d - 16:] = 0.0
+        k[:, key, :, d - 16:] = 16.0     # score 16 * 256 / sqrt(d) = 362 / 512 in natural units, every other prefix score 0
+        kt = rng.standard_normal(wl.kt.shape).astype(np.float32)
+        kt[..., d - 16:] = 0.0
+        wl.q, wl.k_cache, wl.kt = (synth.f32_to_bf16_bits(x) for x in (q, k, kt))
+        _check(wl, flags=flags, kv_split=4096)
+
+
 def test_key_halves_merge_is_deterministic():
     """The merge of the two key halves has a fixed order: two launches on the same inputs give the same bits."""
     rng = np.random.default_rng(1800)
