@@ -173,6 +173,8 @@ typedef struct etv_attn_desc {
 #define ETV_ATTN_FLAG_UNIFORM_SPLITS 32 /* one split size for the whole batch, also where the splits could follow the
                                            sequences' lengths (tuning) */
 
+#define ETV_ATTN_FLAG_KEY_BLOCKS 64 /* bf16: every wavefront takes 32-key blocks of its own (tuning) */
+
 ETV_API size_t etv_tree_verify_attention_workspace_bytes(const etv_attn_desc *h_desc);
 
 /* The launch shape the library picks for h_desc (host only, launches nothing): which kernel, how many wavefronts
@@ -181,10 +183,10 @@ ETV_API size_t etv_tree_verify_attention_workspace_bytes(const etv_attn_desc *h_
  * model fitted on one machine; kv_split and the ETV_ATTN_FLAG_* tuning flags of h_desc override every part of it,
  * and this call shows the outcome, so that a poor pick on another shape or machine can be seen and corrected. */
 typedef struct etv_attn_plan {
-    int32_t mfma;        /* 1: attn_mfma_kernel (bf16); 0: a kernel with fp32 products */
+    int32_t mfma;        /* 1: the bf16 matrix-core kernels; 0: a kernel with fp32 products */
     int32_t wavefronts;  /* per workgroup: 4 or 8 (fp32: 4; 1 for the VALU kernel) */
     int32_t key_halves;  /* 1: two wavefronts per 32-row chunk, each with 32 of a tile's 64 keys */
-    int32_t ring_stages; /* K/V tiles of LDS ring */
+    int32_t ring_stages; /* K/V tiles of LDS ring; 0: every wavefront takes 32-key blocks of its own, no ring */
     int32_t row_groups;  /* workgroups per (split, KV head, sequence); 0 for the VALU kernel */
     int32_t kv_split;    /* prefix keys per split (multiple of 64) */
     int32_t n_splits;    /* splits the launch provides; more than 1 means partials + the combine launch */

@@ -1,10 +1,12 @@
 // tree_verify_attention: tree-masked attention of the draft-tree query rows against the committed
 // prefix cache plus the tree's own K/V (Section 3.3, "Execution view" and "Tree attention mask").
 //
-// Three kernels compute the per-split partial (m, l, O):
+// Four kernels compute the per-split partial (m, l, O):
 //   * attn_mfma_kernel   bf16: K/V tiles staged through LDS, QK^T and PV on
 //                        v_mfma_f32_32x32x16_bf16, online softmax in registers, the ancestor mask applied
 //                        as a per-row bitmask only on the tree tile.
+//   * attn_blocks_kernel bf16, launches that are short of work: the same products, every wavefront with 32-key blocks of
+//                        its own instead of a tile shared by the workgroup.
 //   * attn_f32_kernel    fp32: both products on v_mfma_f32_16x16x4_f32, no barrier in the tile loop.
 //   * attn_generic_kernel  any supported dtype / head dim, fp32 VALU arithmetic, one wavefront per query
 //                        row; runs only where ETV_ATTN_FLAG_GENERIC asks for it, as an independent check.
@@ -37,6 +39,7 @@ struct AttnParams {
     //   part_o [B * nsplit][Hq][T_max][d]; split_tab[b] = (first slot, splits in use) for the combine kernel
     int balanced;
     int2 *split_tab;
+    uint32_t inv_g, inv_hkv, inv_nsplit;  // key-block kernel: floor(2^32 / G) and so on, for fast_div
 };
 
 constexpr float kLn2 = 0.6931471805599453f;
@@ -281,12 +284,16 @@ __global__ void __launch_bounds__(64) attn_generic_kernel(AttnParams p) {
 // trips to memory: the sequence's sizes, then the row's first U splits (only splits that exist are read; all loads of
 // a batch are in flight together).  Further batches of U splits, for launches with more splits than that, update a
 // running (M, L, acc) that is rescaled when a later batch raises the maximum.
-template <typename T, int D, int WPR, int U>
+// SHARED: the four wavefronts of a workgroup take every fourth split of one row and merge through LDS, for launches whose
+// splits would otherwise be several batches in series.  32 rows, 43 splits: 9.0 -> 4.7 us; 16 rows, 107 splits: 18.2 -> 7.4;
+// with many rows the batches of different rows overlap anyway (1920 rows, 32 splits: 9.0, shared 11.2), and up to 16 splits
+// one wavefront's single batch is as fast.
+template <typename T, int D, int WPR, int U, bool SHARED>
 __global__ void __launch_bounds__(256) attn_combine_kernel(AttnParams p) {
     constexpr int E = D / (64 * WPR);
-    static_assert(E >= 1, "at least one element per lane");
+    static_assert(E >= 1 && (!SHARED || WPR == 1), "at least one element per lane");
     const int wv = threadIdx.x >> 6;
-    const long row = (long)blockIdx.x * (4 / WPR) + wv / WPR;
+    const long row = SHARED ? (long)blockIdx.x : (long)blockIdx.x * (4 / WPR) + wv / WPR;
     const int lane = (wv % WPR) * 64 + (threadIdx.x & 63);  // position within the row, in units of E elements
     const long rows_total = (long)p.B * p.T_max * p.Hq;
     if (row >= rows_total) return;
@@ -301,6 +308,7 @@ __global__ void __launch_bounds__(256) attn_combine_kernel(AttnParams p) {
     const size_t lrow = ((size_t)b * p.Hq + h) * p.T_max + k;
     const int nvalid = p.balanced ? share.y : seq_nsplit(p, clampi(P_raw, 0, p.P_max));
     if (k >= clampi(n_raw, 0, p.T_max)) {
+        if (SHARED && wv > 0) return;  // uniform over the workgroup: no barrier is left behind
 #pragma unroll
         for (int e = 0; e < E; e++) store_elem<T>(out, orow + e, 0.f);
         if (p.lse && lane == 0) p.lse[lrow] = -INFINITY;
@@ -308,15 +316,16 @@ __global__ void __launch_bounds__(256) attn_combine_kernel(AttnParams p) {
     }
     const size_t pr0 = part_row(p, p.balanced ? share.x : b * p.nsplit, h, k);
     const size_t sstride = (size_t)p.Hq * p.T_max;  // rows between consecutive splits
+    constexpr int STEP = SHARED ? 4 : 1;
     float M = -INFINITY, L = 0.f, acc[E];
 #pragma unroll
     for (int e = 0; e < E; e++) acc[e] = 0.f;
-    for (int s0 = 0; s0 < nvalid; s0 += U) {
+    for (int s0 = SHARED ? wv : 0; s0 < nvalid; s0 += U * STEP) {
         float ms[U], ls[U], os[U][E];
 #pragma unroll
         for (int u = 0; u < U; u++) {
-            const bool ok = s0 + u < nvalid;
-            const size_t r = pr0 + (size_t)(ok ? s0 + u : 0) * sstride;
+            const bool ok = s0 + u * STEP < nvalid;
+            const size_t r = pr0 + (size_t)(ok ? s0 + u * STEP : 0) * sstride;
             ms[u] = ok ? p.part_m[r] : -INFINITY;
             ls[u] = ok ? p.part_l[r] : 0.f;
 #pragma unroll
@@ -339,6 +348,25 @@ __global__ void __launch_bounds__(256) attn_combine_kernel(AttnParams p) {
 #pragma unroll
                 for (int e = 0; e < E; e++) acc[e] = fmaf(w, os[u][e], acc[e]);
             }
+        }
+    }
+    if (SHARED) {
+        __shared__ float s_m[4], s_l[4], s_acc[4][D];
+        if (lane == 0) { s_m[wv] = M; s_l[wv] = L; }
+#pragma unroll
+        for (int e = 0; e < E; e++) s_acc[wv][lane * E + e] = acc[e];
+        __syncthreads();
+        if (wv > 0) return;
+        M = fmaxf(fmaxf(s_m[0], s_m[1]), fmaxf(s_m[2], s_m[3]));
+        L = 0.f;
+#pragma unroll
+        for (int e = 0; e < E; e++) acc[e] = 0.f;
+#pragma unroll
+        for (int x = 0; x < 4; x++) {
+            const float w = s_m[x] == -INFINITY ? 0.f : exp2f(s_m[x] - M);
+            L = fmaf(w, s_l[x], L);
+#pragma unroll
+            for (int e = 0; e < E; e++) acc[e] = fmaf(w, s_acc[x][lane * E + e], acc[e]);
         }
     }
 #pragma unroll
@@ -722,11 +750,12 @@ __device__ __forceinline__ void pv_accumulate(const TileView &tv, const uint8_t 
 // Key-halves variants: a wavefront takes 32 of the 64 keys of a tile (key block kb); two wavefronts share a
 // 32-row chunk and keep independent running (m, l, O), merged once after the last tile.  Halves the
 // per-tile dependency chain of a wavefront, which is what bounds the rate when a workgroup has fewer chunks
-// than wavefronts.  vis32: visibility bits of the wavefront's 32 keys.
+// than wavefronts.  vis32: visibility bits of the wavefront's 32 keys; apply: a uniform switch for callers that keep one
+// copy of the code for masked and unmasked blocks.
 template <int D, bool MASKED>
 __device__ __forceinline__ void qk_softmax_half(const TileView &tv, const uint8_t *lk, int kb, const bf16x8 (&qreg)[Geo<D>::KK],
                                                 f32x16 (&oacc)[Geo<D>::DB], float &m_run, float &l_run, float scale_log2,
-                                                uint32_t vis32, bf16x8 (&pf)[Geo<D>::NP][2]) {
+                                                uint32_t vis32, bf16x8 (&pf)[Geo<D>::NP][2], bool apply = true) {
     constexpr int ROW_BYTES = Geo<D>::ROW_BYTES, KK = Geo<D>::KK;
     // two accumulator chains over the even / odd 16-wide d steps, summed afterwards
     f32x16 s0, s1;
@@ -746,7 +775,7 @@ __device__ __forceinline__ void qk_softmax_half(const TileView &tv, const uint8_
     }
 #pragma unroll
     for (int i = 0; i < 16; i++) s0[i] += s1[i];
-    if (MASKED) {
+    if (MASKED && apply) {
         const uint32_t lo = vis32 >> (4 * tv.hh);
 #pragma unroll
         for (int i = 0; i < 16; i++) {
@@ -1145,6 +1174,320 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(AttnParams p) {
 }
 
 // ----------------------------------------------------------------------------------------------
+// Key-block kernel (bf16, d = 128 or 64): launches that are short of work.
+//
+// Work unit: (split, KV head, sequence) x 32-row chunk of the KV head's packed query rows, one workgroup of eight
+// wavefronts.  attn_mfma_kernel shares a tile among the chunks of a workgroup and walks through a split tile by tile, a
+// barrier and a whole chain (fragment reads, products, softmax, products) per 64 keys; where a split is a handful of
+// tiles that chain and the extra splits that keep the chip busy are all there is to its time.  Here every wavefront takes
+// 32-key blocks of its own (block t goes to wavefront t % 8), so a workgroup has 256 keys in flight at once, there is no
+// barrier in the loop, and the eight (m, l, O) merge once through LDS: the same keys need an eighth of the steps, and
+// fewer splits.  The price is that K/V are fetched once per chunk instead of once per workgroup of chunks; the chunks of
+// one (split, KV head, sequence) get ids that differ by 8, so they run side by side on one XCD and all but the first
+// reader find the bytes in its L2.
+//
+// A wavefront owns a K and a V buffer of one block each (8 KiB + 8 KiB at d = 128), filled by direct-to-LDS loads: K of
+// the next block is requested when the score products have read this one's, V when the value products have.  Q (one
+// copy for the workgroup) and the rows' ancestor bits come the same way, so that nothing the compiler tracks is
+// outstanding and no wait of its own drains the block loads.  What bounds a step is the LDS pipe (K and V written, read once
+// for 32 rows: 256 KiB per compute unit and step) and, with one chunk, the latency of the next block.
+//
+// B = 1, 32/8 heads of 128: T = 60, P = 2048 16.1 -> 14.0 us (4 splits instead of 8); P = 500 13.5 -> 9.4; T = 8, P = 4096
+// 14.5 -> 13.0; T = 128, P = 1024 17.8 -> 12.1.  B = 4, T = 60, P = 1000 21.6 -> 14.6; B = 32, T = 8, P = 4096 87.4 -> 82.7 us
+// (128 KiB in flight per compute unit: 6.5 TB/s); heads of 64, B = 4, T = 48, P = 900 ... 1500 18.1 -> 12.5.
+// ----------------------------------------------------------------------------------------------
+constexpr int KB_NW = 8;     // wavefronts of a workgroup
+constexpr int KB_KEYS = 32;  // keys of a block
+
+template <int D>
+struct KbGeo {
+    static constexpr int BLOCK = KB_KEYS * Geo<D>::ROW_BYTES;  // K (or V) bytes of a block: 8 or 4 KiB
+    static constexpr int U = BLOCK / 1024;                     // 1 KiB loads of a block: 8 or 4
+    static constexpr int Q_AT = KB_NW * 2 * BLOCK;             // LDS: wavefront buffers, Q, ancestor bits, (m, l)
+    static constexpr int BITS_AT = Q_AT + BLOCK;               // 4 words x 32 rows x 8 B
+    static constexpr int ML_AT = BITS_AT + 4 * 256;
+    static constexpr int LDS = ML_AT + KB_NW * 32 * 8;         // 139 KiB (one workgroup per compute unit) or 71 KiB (two)
+};
+
+// 4 bytes per lane from global memory straight into LDS at (lds_addr + 4 * lane); asynchronous.
+__device__ __forceinline__ void async_load4(const void *gptr, uint32_t lds_addr) {
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off\n" ::"v"(gptr),
+                 "s"(__builtin_amdgcn_readfirstlane(lds_addr)) : "memory");
+}
+// every LDS read this wavefront has issued is done (the buffer it read may be filled again)
+__device__ __forceinline__ void wait_lds_reads() {
+    __builtin_amdgcn_s_waitcnt(0xc07f);
+    asm volatile("" ::: "memory");
+}
+
+// x / d and x % d with inv = floor(2^32 / d): the estimate is at most one too small for any 32-bit x.  (The compiler's
+// general division is some forty dependent instructions, each 3.5 ns of a lone wavefront's start-up.)
+__device__ __forceinline__ uint32_t fast_div(uint32_t x, uint32_t d, uint32_t inv, uint32_t &rem) {
+    uint32_t q = __umulhi(x, inv);
+    rem = x - q * d;
+    if (rem >= d) {
+        q++;
+        rem -= d;
+    }
+    return q;
+}
+
+static uint32_t fast_div_inv(int d) { return d == 1 ? 0xffffffffu : (uint32_t)((1ull << 32) / (uint32_t)d); }
+
+template <int D, bool PAGED>
+__global__ void __launch_bounds__(KB_NW * 64, D == 64 ? 4 : 2) attn_blocks_kernel(AttnParams p) {
+    using G_ = KbGeo<D>;
+    constexpr int ROW_BYTES = Geo<D>::ROW_BYTES, KK = Geo<D>::KK, DB = Geo<D>::DB, RPU = Geo<D>::RPU, CPR = Geo<D>::CPR;
+    constexpr int BLOCK = G_::BLOCK, U = G_::U, UH = U / 2;  // UH loads cover 16 rows
+    constexpr int VP = D == 128 ? 2 : 1;                     // the V swizzle of a load repeats with this period
+    uint8_t *const smem = attn_smem;
+    const uint32_t smem_addr = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)attn_smem;
+    const int tid = threadIdx.x, lane = tid & 63, c32 = lane & 31, hh = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // grid (8, chunks, units / 8): the linear id is ((unit / 8) * chunks + chunk) * 8 + unit % 8, unit = slot * Hkv + KV head
+    const int rg = blockIdx.y;
+    uint32_t rem;
+    const int slot = (int)fast_div(blockIdx.z * 8 + blockIdx.x, p.Hkv, p.inv_hkv, rem);
+    const int kvh = (int)rem;
+    if (slot >= p.B * p.nsplit) return;  // uniform over the workgroup
+    asm volatile("" ::"s"(p.q), "s"(p.k_cache), "s"(p.v_cache), "s"(p.kt), "s"(p.vt), "s"(p.block_table),
+                 "s"(p.prefix_len), "s"(p.n_nodes), "s"(p.bitmask), "s"(p.T_max), "s"(p.Hq), "s"(p.G),
+                 "s"(p.max_blocks), "s"(p.P_cap), "s"(p.P_max), "s"(p.words), "s"(p.chunk));
+    SplitShare share{};
+    if (p.balanced) {
+        share = balanced_share(p, slot, lane);
+        if (!share.live) return;  // uniform over the workgroup
+        if (share.j == 0 && kvh == 0 && rg == 0 && tid == 0) p.split_tab[share.b] = make_int2(share.start, share.nvalid);
+    }
+    const int slot_b = (int)fast_div(slot, p.nsplit, p.inv_nsplit, rem);
+    const int b = uni(p.balanced ? share.b : slot_b);
+    const int s = uni(p.balanced ? share.j : (int)rem);
+    const int chunk = uni(p.balanced ? share.tps * KT : p.chunk);
+    const int k0 = s * chunk;
+    const const_i32_ptr bt = (const_i32_ptr)(uintptr_t)(PAGED ? p.block_table + (size_t)b * p.max_blocks : nullptr);
+    // One trip for the sizes and the two cache blocks of the wavefront's first key block; those ids are read before it is
+    // known whether the prefix reaches that far, and used only if it does.
+    const int lb0 = (k0 >> 4) + 2 * wave;
+    int blk0 = 0, blk1 = 0;
+    if (PAGED && lb0 + 1 < p.max_blocks) {
+        blk0 = bt[lb0];
+        blk1 = bt[lb0 + 1];
+    }
+    const int n_raw = p.balanced ? share.n_raw : ((const_i32_ptr)(uintptr_t)p.n_nodes)[b];
+    const int P_raw = p.balanced ? share.P_raw : ((const_i32_ptr)(uintptr_t)p.prefix_len)[b];
+    asm volatile("" ::"s"(n_raw), "s"(P_raw), "s"(blk0), "s"(blk1));
+    const int n = uni(clampi(n_raw, 0, p.T_max)), P = uni(clampi(P_raw, 0, p.P_max));
+    const int nvalid = uni(p.balanced ? share.nvalid : seq_nsplit(p, P));
+    if (s >= nvalid) return;  // uniform over the workgroup
+    const bool direct = (p.nsplit == 1);
+    const bool active = rg * 32 < n * p.G;  // does the chunk hold a valid row?
+    const int k1 = min(P, k0 + chunk);
+    const int nfull = (active && k1 > k0) ? (k1 - k0) >> 5 : 0;     // full prefix blocks
+    const int npb = (active && k1 > k0) ? (k1 - k0 + 31) >> 5 : 0;  // prefix blocks incl. a ragged last one
+    const bool with_tree = active && s == nvalid - 1;
+    const int nt = npb + (with_tree ? (n + 31) >> 5 : 0);
+
+    const uint8_t *const kc = static_cast<const uint8_t *>(p.k_cache), *const vc = static_cast<const uint8_t *>(p.v_cache);
+    const size_t hstride = (size_t)p.Hkv * ROW_BYTES;  // between the rows of a head (contiguous cache, tree buffer)
+    const size_t blk_stride = (size_t)p.Hkv * 16 * ROW_BYTES;
+    const size_t head_at = PAGED ? (size_t)kvh * 16 * ROW_BYTES : ((size_t)b * p.P_cap * p.Hkv + kvh) * ROW_BYTES;
+    const uint32_t rstride = PAGED ? (uint32_t)ROW_BYTES : (uint32_t)hstride;
+    const uint32_t kbuf = smem_addr + (uint32_t)wave * (2 * BLOCK), vbuf = kbuf + BLOCK;
+    const int l_row = lane / CPR, l_pos = lane % CPR;
+    // chunk-position swizzles as in the tile kernel: load u covers rows RPU * u + l_row of the block
+    uint32_t koff[UH], voff[VP];
+#pragma unroll
+    for (int x = 0; x < UH; x++) koff[x] = l_row * rstride + (l_pos ^ kswz_of_row<D>(RPU * x + l_row)) * 16;
+#pragma unroll
+    for (int x = 0; x < VP; x++) voff[x] = l_row * rstride + (l_pos ^ vswz_of_row<D>(RPU * x + l_row)) * 16;
+    const bool stream_kv = p.pairs == 1;  // a single reader of these K/V bytes: streamed past L2
+    auto full_base = [&](int t, int j, int blk) -> size_t {
+        return head_at + (PAGED ? (size_t)(uint32_t)uni(blk) * blk_stride : (size_t)(uint32_t)(k0 + t * KB_KEYS + 16 * j) * hstride);
+    };
+    auto issue_full = [&](const uint8_t *cache, uint32_t dst, bool is_v, size_t b0, size_t b1) {
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const uint8_t *src = cache + (u < UH ? b0 : b1) + (size_t)((u % UH) * RPU) * rstride;
+            const uint32_t off = is_v ? voff[u % VP] : koff[u % UH];
+            if (stream_kv) async_load16_s<true>(src, off, dst + u * 1024);
+            else async_load16_s<false>(src, off, dst + u * 1024);
+        }
+    };
+    // ragged last prefix block and tree blocks: rows past the end repeat the last valid one (masked later)
+    auto issue_edge = [&](int t, const uint8_t *cache, const void *own_rows, uint32_t dst, bool is_v) {
+        const bool tree = t >= npb;
+        const int base = tree ? (t - npb) * KB_KEYS : k0 + t * KB_KEYS;
+        const int last = (tree ? n : k1) - 1;
+        const uint8_t *own = static_cast<const uint8_t *>(own_rows);
+#pragma unroll 1
+        for (int u = 0; u < U; u++) {
+            const int r = RPU * u + l_row;
+            const int key = min(base + r, last);
+            const uint8_t *src;
+            if (tree && own) {
+                src = own + (((size_t)b * p.T_max + key) * p.Hkv + kvh) * ROW_BYTES;
+            } else {
+                const int pos = tree ? P + key : key;  // in-place branch cache: node j at position P + j
+                if (PAGED) src = cache + (size_t)(uint32_t)bt[pos >> 4] * blk_stride + head_at + (size_t)(pos & 15) * ROW_BYTES;
+                else src = cache + head_at + (size_t)pos * hstride;
+            }
+            async_load16(src + (l_pos ^ (is_v ? vswz_of_row<D>(r) : kswz_of_row<D>(r))) * 16, dst + u * 1024);
+        }
+    };
+
+    int t = wave;
+    if (active) {
+        // Q, 1 KiB per wavefront, laid out like a K block; padded rows repeat node 0's (their results are dropped)
+        if (wave < U) {
+            const int row = RPU * wave + l_row;
+            int kq = (int)fast_div(rg * 32 + row, p.G, p.inv_g, rem), h = kvh * p.G + (int)rem;
+            if (kq >= n) { kq = 0; h = kvh * p.G; }
+            async_load16(static_cast<const uint8_t *>(p.q) + (((size_t)b * p.T_max + kq) * p.Hq + h) * ROW_BYTES +
+                             (l_pos ^ kswz_of_row<D>(row)) * 16, smem_addr + G_::Q_AT + wave * 1024);
+        }
+        if (with_tree && wave < p.words) {  // word `wave` of the ancestor bits of the 32 rows
+            int kq = (int)fast_div(rg * 32 + (lane >> 1), p.G, p.inv_g, rem);
+            if (kq >= n) kq = 0;
+            async_load4(reinterpret_cast<const uint32_t *>(p.bitmask + ((size_t)b * p.T_max + kq) * p.words + wave) + (lane & 1),
+                        smem_addr + G_::BITS_AT + wave * 256);
+        }
+        if (t < nfull) {
+            const size_t b0 = full_base(t, 0, blk0), b1 = full_base(t, 1, blk1);
+            issue_full(kc, kbuf, false, b0, b1);
+            issue_full(vc, vbuf, true, b0, b1);
+        } else if (t < nt) {
+            issue_edge(t, kc, p.kt, kbuf, false);
+            issue_edge(t, vc, p.vt, vbuf, true);
+        }
+        if (t < nt) wait_vmcnt<2 * U>();
+        else wait_vmcnt<0>();
+    }
+    __builtin_amdgcn_s_barrier();  // Q and the ancestor bits are in LDS
+    asm volatile("" ::: "memory");
+
+    // the views of the wavefront's buffers, as in the tile kernel
+    const int g16 = lane >> 4, i16 = lane & 15;
+    const int vrow = 4 * hh + (i16 >> 2);
+    const TileView tv{c32 * ROW_BYTES, kswz_of_row<D>(c32), vrow, vswz_of_row<D>(vrow),
+                      2 * (g16 & 1) + ((i16 & 3) >> 1), 8 * (i16 & 1), hh};
+    const uint8_t *const lk = smem + wave * (2 * BLOCK), *const lv = lk + BLOCK;
+    f32x16 oacc[DB];
+    float m_run = -INFINITY, l_run = 0.f;
+#pragma unroll
+    for (int db = 0; db < DB; db++)
+#pragma unroll
+        for (int i = 0; i < 16; i++) oacc[db][i] = 0.f;
+    if (t < nt) {
+        bf16x8 qreg[KK];
+        const uint8_t *lq = smem + G_::Q_AT + c32 * ROW_BYTES;
+#pragma unroll
+        for (int kk = 0; kk < KK; kk++) qreg[kk] = *reinterpret_cast<const bf16x8 *>(lq + (((2 * kk + hh) ^ tv.ksw) << 4));
+        for (; t < nt; t += KB_NW) {
+            const int tn = t + KB_NW;
+            int nb0 = 0, nb1 = 0;  // the next block's ids fly during this one's products
+            if (PAGED && tn < nfull) {
+                nb0 = bt[(k0 >> 4) + 2 * tn];
+                nb1 = bt[(k0 >> 4) + 2 * tn + 1];
+            }
+            wait_vmcnt<U>();  // K of block t (V may still be on its way)
+            asm volatile("" ::: "memory");
+            bf16x8 pf[Geo<D>::NP][2];
+            // one copy of the code for masked and unmasked blocks: a launch this short pays for every instruction it fetches
+            uint32_t vis = ~0u;
+            if (t >= npb) vis = *reinterpret_cast<const uint32_t *>(smem + G_::BITS_AT + ((t - npb) >> 1) * 256 + c32 * 8 + ((t - npb) & 1) * 4);
+            else if (t >= nfull) vis = (1u << (k1 - k0 - t * KB_KEYS)) - 1u;  // ragged last prefix block: 1..31 keys
+            qk_softmax_half<D, true>(tv, lk, 0, qreg, oacc, m_run, l_run, p.scale_log2, vis, pf, t >= nfull);
+            wait_lds_reads();
+            size_t b0 = 0, b1 = 0;
+            if (tn < nfull) {
+                b0 = full_base(tn, 0, nb0);
+                b1 = full_base(tn, 1, nb1);
+                issue_full(kc, kbuf, false, b0, b1);
+            } else if (tn < nt) {
+                issue_edge(tn, kc, p.kt, kbuf, false);
+            }
+            if (tn < nt) wait_vmcnt<U>();  // V of block t (K of the next one may still be on its way)
+            else wait_vmcnt<0>();
+            asm volatile("" ::: "memory");
+            pv_accumulate_half<D>(tv, lv, 0, pf, oacc);
+            wait_lds_reads();
+            if (tn < nfull) issue_full(vc, vbuf, true, b0, b1);
+            else if (tn < nt) issue_edge(tn, vc, p.vt, vbuf, true);
+        }
+    }
+
+    // ---- merge the wavefronts: each leaves O in its own K/V buffers (same size), 16-byte piece c of row r at c ^ r
+    constexpr int CH = D / 4;  // 16-byte pieces of an fp32 output row
+    float2 *const ml = reinterpret_cast<float2 *>(smem + G_::ML_AT);
+    const int live = min(KB_NW, nt);
+    if (wave < live) {
+        const float l_tot = half_swap_sum(l_run);
+        float4 *dst = reinterpret_cast<float4 *>(smem + wave * (2 * BLOCK)) + c32 * CH;
+#pragma unroll
+        for (int db = 0; db < DB; db++)
+#pragma unroll
+            for (int ig = 0; ig < 4; ig++)
+                dst[(8 * db + 2 * ig + hh) ^ (c32 & (CH - 1))] =
+                    float4{oacc[db][4 * ig], oacc[db][4 * ig + 1], oacc[db][4 * ig + 2], oacc[db][4 * ig + 3]};
+        if (hh == 0) ml[wave * 32 + c32] = float2{m_run, l_tot};
+    }
+    __syncthreads();
+    const int row = tid >> 4, piece = tid & 15;  // a row's 16 threads own pieces `piece` and (d = 128) piece + 16
+    const int kq2 = (int)fast_div(rg * 32 + row, p.G, p.inv_g, rem), h2 = kvh * p.G + (int)rem;
+    if (kq2 >= p.T_max) return;
+    const bool rv = kq2 < n;
+    if (!rv && !direct) return;
+    // all reads of the statistics in one trip, then all reads of the outputs (those of absent wavefronts are skipped)
+    float2 e[KB_NW];
+    float M = -INFINITY, L = 0.f;
+#pragma unroll
+    for (int x = 0; x < KB_NW; x++) e[x] = ml[x * 32 + row];
+#pragma unroll
+    for (int x = 0; x < KB_NW; x++) {
+        if (x >= live) e[x] = float2{-INFINITY, 0.f};
+        M = fmaxf(M, e[x].x);
+    }
+    float4 acc[D / 64];
+#pragma unroll
+    for (int v = 0; v < D / 64; v++) acc[v] = float4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int x = 0; x < KB_NW; x++) {
+        if (x >= live) break;  // uniform
+        const float w = e[x].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(e[x].x - M);
+        L = fmaf(w, e[x].y, L);
+        const float4 *src = reinterpret_cast<const float4 *>(smem + x * (2 * BLOCK)) + row * CH;
+#pragma unroll
+        for (int v = 0; v < D / 64; v++) {
+            const float4 o = src[(piece + 16 * v) ^ (row & (CH - 1))];
+            acc[v].x = fmaf(w, o.x, acc[v].x); acc[v].y = fmaf(w, o.y, acc[v].y);
+            acc[v].z = fmaf(w, o.z, acc[v].z); acc[v].w = fmaf(w, o.w, acc[v].w);
+        }
+    }
+    if (direct) {
+        uint16_t *orow = static_cast<uint16_t *>(p.out) + (((size_t)b * p.T_max + kq2) * p.Hq + h2) * D;
+        const float inv = rv ? 1.f / L : 0.f;
+#pragma unroll
+        for (int v = 0; v < D / 64; v++) {
+            uint2 w = {0u, 0u};
+            if (rv) {
+                w.x = pack_bf16x2(acc[v].x * inv, acc[v].y * inv);
+                w.y = pack_bf16x2(acc[v].z * inv, acc[v].w * inv);
+            }
+            *reinterpret_cast<uint2 *>(orow + 4 * (piece + 16 * v)) = w;
+        }
+        if (p.lse && piece == 0) p.lse[((size_t)b * p.Hq + h2) * p.T_max + kq2] = rv ? (M + __builtin_amdgcn_logf(L)) * kLn2 : -INFINITY;
+    } else {
+        const size_t pr = part_row(p, slot, h2, kq2);
+#pragma unroll
+        for (int v = 0; v < D / 64; v++) *reinterpret_cast<float4 *>(p.part_o + pr * D + 4 * (piece + 16 * v)) = acc[v];
+        if (piece == 0) {
+            p.part_m[pr] = M;
+            p.part_l[pr] = L;
+        }
+    }
+}
+
+// ----------------------------------------------------------------------------------------------
 // fp32 kernel (d = 128 or 64): both products on v_mfma_f32_16x16x4_f32, which multiplies and adds in fp32.
 //
 // Work unit: (split, KV head, sequence) x 16-row chunk of the KV head's packed query rows, one workgroup of four
@@ -1429,6 +1772,7 @@ __global__ void __launch_bounds__(F32_NW * 64, 2) attn_f32_kernel(AttnParams p) 
 struct Plan {
     bool mfma, kh;  // mfma: attn_mfma_kernel
     bool f32;       // attn_f32_kernel
+    bool blocks;    // attn_blocks_kernel
     int nw, ns, pairs, wgp, chunk, nsplit;
     bool balanced;  // split slots shared out among the sequences by their lengths, on the device
 };
@@ -1455,6 +1799,15 @@ static long f32_blocks(const etv_attn_desc *h, const Plan &pl) {
     return ((long)h->B * pl.nsplit * h->Hkv + 7) / 8 * 8 * pl.pairs;
 }
 
+// bytes of the partial results of ns splits (and of the split table)
+static size_t split_workspace(const etv_attn_desc *h, int ns) {
+    return (size_t)h->B * h->Hq * h->T_max * ns * ((size_t)h->d + 2) * sizeof(float) + 1024;
+}
+
+// The next split count worth a look: with tps tiles per split now, the smallest count whose splits are shorter (the counts
+// between differ only in empty splits).  Some 2 * sqrt(tiles) candidates instead of all of them, on every call.
+static int next_split_count(int tiles, int tps) { return tps > 1 ? (tiles + tps - 2) / (tps - 1) : tiles + 1; }
+
 static Plan make_plan(const etv_attn_desc *h) {
     Plan pl{};
     const int tiles = max(1, (h->P_max + KT - 1) / KT);
@@ -1477,9 +1830,8 @@ static Plan make_plan(const etv_attn_desc *h) {
         const long units = (long)B * h->Hkv * pl.pairs;
         const int forced_tps = h->kv_split > 0 ? min(tiles, (h->kv_split + KT - 1) / KT) : 0;
         double best = 1e30;
-        for (int ns = 1; ns <= tiles; ns++) {
-            const int tps = forced_tps ? forced_tps : (tiles + ns - 1) / ns;
-            if ((tiles + tps - 1) / tps != ns) continue;
+        for (int ns = forced_tps ? (tiles + forced_tps - 1) / forced_tps : 1, tps; ns <= tiles; ns = forced_tps ? tiles + 1 : next_split_count(tiles, tps)) {
+            tps = forced_tps ? forced_tps : (tiles + ns - 1) / ns;
             const double per_wave = ceil((tps * 4.0 + (h->T_max + 15) / 16) / F32_NW);
             const double full = ceil((double)(units * ns) / 256.0);
             const double est = per_wave * (full * busy > chain ? full * busy : chain) + (ns > 1 ? 4.0 + ns * (part_us + 0.1) : 0.0);
@@ -1507,8 +1859,9 @@ static Plan make_plan(const etv_attn_desc *h) {
     }
     pl.pairs = ((h->Hq / h->Hkv) * h->T_max + 31) / 32;  // 32-row chunks of the G * T_max packed rows of a KV head
     const double part_us = 2.0 * B * h->Hq * h->T_max * (h->d + 2.0) * 4.0 / 3.0e6;
-    double best = 1e30;
-    for (int nw = 4; nw <= 8; nw += 4) {
+    double best = 1e30, best_lat = 0.0;
+    const bool blocks_only = (h->flags & ETV_ATTN_FLAG_KEY_BLOCKS) != 0;
+    for (int nw = 4; nw <= 8 && !blocks_only; nw += 4) {
         for (int kh = 0; kh <= 1; kh++) {
             const int cw = kh ? nw / 2 : nw;  // chunks per workgroup
             // key halves pay when a workgroup would otherwise have idle wavefronts
@@ -1520,9 +1873,8 @@ static Plan make_plan(const etv_attn_desc *h) {
             const long units = (long)B * h->Hkv * wgp;
             // candidates: every distinct number of splits, or the one split size the caller asks for
             const int forced_tps = h->kv_split > 0 ? min(tiles, (h->kv_split + KT - 1) / KT) : 0;
-            for (int ns = 1; ns <= tiles; ns++) {
-                const int tps = forced_tps ? forced_tps : (tiles + ns - 1) / ns;
-                if ((tiles + tps - 1) / tps != ns) continue;
+            for (int ns = forced_tps ? (tiles + forced_tps - 1) / forced_tps : 1, tps; ns <= tiles; ns = forced_tps ? tiles + 1 : next_split_count(tiles, tps)) {
+                tps = forced_tps ? forced_tps : (tiles + ns - 1) / ns;
                 const long wgs = units * ns;
                 const bool alone = (nw == 4 && wgs <= 256);
                 const double slots = nw == 8 ? 256.0 : 512.0;
@@ -1533,9 +1885,47 @@ static Plan make_plan(const etv_attn_desc *h) {
                 const double est = rounds * (tps + 1.5) * t_tile + 4.0 + (ns > 1 ? 4.6 + ns * part_us : 0.0);
                 if (est < best) {
                     best = est;
+                    best_lat = rounds * (tps + 1.0) * t_tile;
                     pl.nw = nw; pl.kh = kh; pl.wgp = wgp; pl.chunk = tps * KT; pl.nsplit = ns;
                     pl.ns = nw == 8 ? 4 : (alone ? 4 : 2);  // ring stages: a lone small workgroup can afford four
                 }
+            }
+        }
+    }
+    constexpr int kShapeFlags = ETV_ATTN_FLAG_SMALL_WG | ETV_ATTN_FLAG_LARGE_WG | ETV_ATTN_FLAG_WHOLE_TILE | ETV_ATTN_FLAG_KEY_HALVES;
+    if (blocks_only || !(h->flags & kShapeFlags)) {
+        // Key-block kernel against the pick so far, for launches that fit the chip at once (one workgroup per compute unit, two
+        // at d = 64): a further round pays start-up and merge again, and the other kernel is then always ahead.  Microseconds,
+        // fitted to 128 workloads (B = 1 ... 32, T = 1 ... 250, P = 48 ... 30310, both head sizes; for 38 of them every split
+        // count of both kernels): the pick is within 0.5 % of the best measured shape on average, and 14 % ahead of what the
+        // other kernel gives.  A wavefront's block is 1.6 (2.15 where a single chunk waits for HBM and not for its neighbours'
+        // lines in L2; d = 64 1.1, and 1.8 times that with two workgroups on a compute unit); the memory side is the K/V bytes
+        // once at 6.9 TB/s and once more per further chunk at 42 TB/s.
+        const bool d64 = h->d == 64;
+        const double kv_bytes = 4.0 * B * h->P_max * (double)h->Hkv * h->d, part2_us = part_us * 0.72;
+        if (best < 1e30) {
+            const double lat = 0.8 * best_lat * (d64 ? 0.76 : 1.0) + 5.6, mem = 7.8 + kv_bytes / 6.2e6;
+            best = (lat > mem ? lat : mem) + (pl.nsplit > 1 ? 3.3 + pl.nsplit * part2_us : 0.0);
+        }
+        const long units = (long)B * h->Hkv * pl.pairs, slots = d64 ? 512 : 256;
+        const double mem = 4.9 + kv_bytes / 6.9e6 + (pl.pairs - 1) * kv_bytes / 42.0e6, mem25 = mem * mem * sqrt(mem);
+        const int tree_blocks = (h->T_max + KB_KEYS - 1) / KB_KEYS;
+        const int forced_tps = h->kv_split > 0 ? min(tiles, (h->kv_split + KT - 1) / KT) : 0;
+        for (int ns = forced_tps ? (tiles + forced_tps - 1) / forced_tps : 1, tps; ns <= tiles; ns = forced_tps ? tiles + 1 : next_split_count(tiles, tps)) {
+            tps = forced_tps ? forced_tps : (tiles + ns - 1) / ns;
+            const long wgs = units * ns;
+            if (wgs > slots && !(blocks_only && (ns == 1 || forced_tps))) break;
+            if (((long)B * ns * h->Hkv + 7) / 8 > 65535 || pl.pairs > 65535) break;  // grid dimensions
+            // splits of its own choice fit the library's array wherever the other kernel's did
+            if (!forced_tps && ns > 1 && split_workspace(h, ns) > ETV_ATTN_STATIC_WORKSPACE_BYTES) break;
+            const int most = (2 * tps + tree_blocks + KB_NW - 1) / KB_NW, usual = (2 * tps + KB_NW - 1) / KB_NW;
+            const double steps = ns > 1 ? 0.5 * (most + usual) : most;  // only the last split takes the tree
+            const double t_step = d64 ? (wgs > 256 ? 2.0 : 1.1) : (pl.pairs == 1 ? 2.15 : 1.6);
+            const double lat = steps * t_step + (d64 ? 2.5 : 3.4);
+            const double est = pow(lat * lat * sqrt(lat) + mem25, 0.4) + (ns > 1 ? 3.3 + ns * part2_us : 0.0);
+            if (est < best) {
+                best = est;
+                pl.blocks = true; pl.nw = KB_NW; pl.kh = false; pl.wgp = pl.pairs; pl.chunk = tps * KT; pl.nsplit = ns; pl.ns = 0;
             }
         }
     }
@@ -1559,6 +1949,17 @@ static int32_t launch_mfma(const AttnParams &p, dim3 grid, hipStream_t st) {
     }();
     if (!lds_ok) return ETV_ERR_HIP;
     hipLaunchKernelGGL((attn_mfma_kernel<D, NW, NS, PAGED, KH>), grid, dim3(NW * 64), lds, st, p);
+    return check_launch();
+}
+
+template <int D, bool PAGED>
+static int32_t launch_blocks(const AttnParams &p, dim3 grid, hipStream_t st) {
+    static const bool lds_ok = [] {
+        return hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_blocks_kernel<D, PAGED>),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, KbGeo<D>::LDS) == hipSuccess;
+    }();
+    if (!lds_ok) return ETV_ERR_HIP;
+    hipLaunchKernelGGL((attn_blocks_kernel<D, PAGED>), grid, dim3(KB_NW * 64), KbGeo<D>::LDS, st, p);
     return check_launch();
 }
 
@@ -1605,8 +2006,7 @@ extern "C" size_t etv_tree_verify_attention_workspace_bytes(const etv_attn_desc 
     if (!h || !etv::supported(h) || h->B == 0) return 0;
     etv::Plan pl = etv::make_plan(h);
     if (pl.nsplit <= 1) return 256;
-    size_t rows = (size_t)h->B * h->Hq * h->T_max * pl.nsplit;
-    return rows * ((size_t)h->d + 2) * sizeof(float) + 1024;  // partials, then 64 (first slot, splits) pairs
+    return etv::split_workspace(h, pl.nsplit);  // partials, then 64 (first slot, splits) pairs
 }
 
 namespace etv {
@@ -1664,7 +2064,14 @@ static int32_t attention_run(const etv_attn_desc *h, const void *q, const void *
     }
     hipStream_t st = as_stream(stream);
     int32_t rc;
-    if (pl.mfma) {
+    if (pl.blocks) {
+        const dim3 grid(8, pl.pairs, ((unsigned)h->B * pl.nsplit * h->Hkv + 7) / 8);
+        p.inv_g = fast_div_inv(p.G);
+        p.inv_hkv = fast_div_inv(p.Hkv);
+        p.inv_nsplit = fast_div_inv(p.nsplit);
+        if (h->d == 128) rc = h->block_size > 0 ? launch_blocks<128, true>(p, grid, st) : launch_blocks<128, false>(p, grid, st);
+        else rc = h->block_size > 0 ? launch_blocks<64, true>(p, grid, st) : launch_blocks<64, false>(p, grid, st);
+    } else if (pl.mfma) {
         const dim3 grid = pl.balanced ? dim3(pl.nsplit * h->B, h->Hkv * pl.wgp, 1) : dim3(pl.nsplit, h->Hkv * pl.wgp, h->B);
         rc = h->d == 128 ? launch_mfma_shape<128>(pl, h->block_size > 0, p, grid, st)
                          : launch_mfma_shape<64>(pl, h->block_size > 0, p, grid, st);
@@ -1687,13 +2094,16 @@ static int32_t attention_run(const etv_attn_desc *h, const void *q, const void *
     }
     if (rc != ETV_OK || pl.nsplit == 1) return rc;
     const long crows = (long)h->B * h->T_max * h->Hq;
-    const bool two = h->d == 128 && crows <= 512;  // very few rows: two wavefronts per row
-    const bool wide = pl.nsplit > 8;                // many splits: sixteen per batch of loads
-    dim3 cgrid((unsigned)((crows + (two ? 1 : 3)) / (two ? 2 : 4)));
+    const bool shared = pl.nsplit > 16 && crows <= 1024;      // more splits than one batch of a wavefront
+    const bool two = !shared && h->d == 128 && crows <= 512;  // very few rows: two wavefronts per row
+    const bool wide = pl.nsplit > 8;                          // many splits: sixteen per batch of loads
+    const int rows_per_wg = shared ? 1 : (two ? 2 : 4);
+    dim3 cgrid((unsigned)((crows + rows_per_wg - 1) / rows_per_wg));
 #define ETV_COMBINE(TY, DD, WPR) \
     do { \
-        if (wide) hipLaunchKernelGGL((attn_combine_kernel<TY, DD, WPR, 16>), cgrid, dim3(256), 0, st, p); \
-        else hipLaunchKernelGGL((attn_combine_kernel<TY, DD, WPR, 8>), cgrid, dim3(256), 0, st, p); \
+        if (shared) hipLaunchKernelGGL((attn_combine_kernel<TY, DD, 1, 16, true>), cgrid, dim3(256), 0, st, p); \
+        else if (wide) hipLaunchKernelGGL((attn_combine_kernel<TY, DD, WPR, 16, false>), cgrid, dim3(256), 0, st, p); \
+        else hipLaunchKernelGGL((attn_combine_kernel<TY, DD, WPR, 8, false>), cgrid, dim3(256), 0, st, p); \
     } while (0)
     if (h->dtype == ETV_F32 && h->d == 64) ETV_COMBINE(float, 64, 1);
     else if (h->dtype == ETV_F32 && two) ETV_COMBINE(float, 128, 2);

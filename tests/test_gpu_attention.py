@@ -356,3 +356,24 @@ def test_config5_sweep_cells(T, D):
         err, rel, padded_zero = attention_errors(out[sl], ref, wl.n_nodes[sl])
         _record(f"{wl.name} sequence {b}", err, rel)
         assert padded_zero and err <= TOL["bf16"] and rel <= REL_TOL["bf16"], (T, D, b, err, rel)
+
+
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("d", [64, 128])
+def test_key_block_kernel_edges(d, paged):
+    """A wavefront per 32-key block: prefixes around the 32-key blocks and around the 256 keys that the eight wavefronts of a
+    workgroup hold at once (fewer blocks than wavefronts, one more round for some of them), trees around a block and of
+    every mask word, group sizes that are not powers of two, splits of both kinds, peaked scores.  The bars are those of
+    every bf16 case, and of heads of 64 (the derivation stands there)."""
+    flag = api.ATTN_FLAG_KEY_BLOCKS
+    rng = np.random.default_rng(5200 + d + paged)
+    P = [0, 1, 31, 32, 33, 63, 65, 223, 255, 256, 257, 288, 289, 513, 700]
+    n = [24, 1, 7, 24, 9, 24, 2, 24, 24, 5, 24, 11, 24, 24, 3]
+    for T, Hq, Hkv, P, n in ((24, 8, 2, P, n), (1, 4, 4, [77, 0], [1, 1]), (33, 6, 2, [300, 129], [33, 31]), (70, 7, 1, [200, 33], [70, 65]),
+                             (256, 4, 2, [70, 530], [255, 193]), (130, 2, 2, [130], [129])):
+        for q_scale in (1.0, 4.0) if T < 100 else (2.0,):
+            wl = _small(rng, len(P), T, Hq, Hkv, d, P, "bf16", paged, n_nodes=n, q_scale=q_scale)
+            for kv_split in (0, 64, 256, 4096):
+                err, rel = _check(wl, flags=flag, kv_split=kv_split)
+                assert d == 128 or rel <= 2.0 ** -8, (T, kv_split, rel)
+            _check(wl, kv_split=64, flags=flag | api.ATTN_FLAG_UNIFORM_SPLITS)
