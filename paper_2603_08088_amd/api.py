@@ -1,4 +1,4 @@
-"""Thin Python binding of libeagletv.so: argument marshalling only.
+"""Thin Python binding of libeagletv.so: shapes, outputs and descriptors; csrc/binding.cpp makes the calls.
 
 Each function has the name of the C entry point it calls (``include/eagletv.h``)
 and takes torch tensors that already live on the GPU; outputs are allocated
@@ -18,6 +18,7 @@ import torch
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libeagletv.so")
 _lib = None
+_calls = None
 
 F32, BF16 = 0, 1
 TREE_RANGE, TREE_CYCLE, TREE_CLOSURE = 1, 2, 4
@@ -122,15 +123,17 @@ def lib():
     return _lib
 
 
-def _ptr(t: Optional[torch.Tensor]):
-    if t is None:
-        return None
-    assert t.is_cuda and t.is_contiguous(), "device-resident contiguous tensors only"
-    return t.data_ptr()
-
-
-def _stream():
-    return torch.cuda.current_stream().cuda_stream
+def _native():
+    """The library's calls as a Python module: tensors (or None) where the C prototype has pointers, current stream."""
+    global _calls
+    if _calls is None:
+        lib()
+        try:
+            from . import _binding
+        except ImportError as e:
+            raise RuntimeError(f"{_HERE}/_binding.so does not load ({e}): build it with `python -m paper_2603_08088_amd.build`")
+        _calls = _binding
+    return _calls
 
 
 def _check(fn: str, rc: int):
@@ -163,8 +166,7 @@ def build_tree_mask(parent: torch.Tensor, n_nodes: torch.Tensor, *, want_dense: 
     status = o.get("status") if out else None
     if status is None:
         status = torch.empty((B,), dtype=torch.int32, device=dev)
-    rc = lib().etv_build_tree_mask(_ptr(parent), _ptr(n_nodes), B, T, _ptr(bitmask), _ptr(dense), _ptr(depth),
-                                   _ptr(status), _stream())
+    rc = _native().build_tree_mask(parent, n_nodes, B, T, bitmask, dense, depth, status)
     _check("etv_build_tree_mask", rc)
     return dict(bitmask=bitmask, dense=dense, depth=depth, status=status)
 
@@ -186,9 +188,8 @@ def tensorize_tree(parent: torch.Tensor, n_nodes: torch.Tensor, prefix_len: torc
     dense = o.get("dense") if out else (torch.empty((B, 1, T, T), dtype=torch.uint8, device=dev) if want_dense else None)
     depth, pos = get("depth", (B, T)), get("position_ids", (B, T))
     retrieve, n_paths, status = get("retrieve", (B, L_max, W)), get("n_paths", (B,)), get("status", (B,))
-    rc = lib().etv_tensorize_tree(_ptr(parent), _ptr(n_nodes), _ptr(prefix_len), B, T, L_max, W, _ptr(bitmask),
-                                  _ptr(dense), _ptr(depth), _ptr(pos), _ptr(retrieve), _ptr(n_paths), _ptr(status),
-                                  _stream())
+    rc = _native().tensorize_tree(parent, n_nodes, prefix_len, B, T, L_max, W, bitmask, dense, depth, pos, retrieve, n_paths,
+                                   status)
     _check("etv_tensorize_tree", rc)
     return dict(bitmask=bitmask, dense=dense, depth=depth, position_ids=pos, retrieve=retrieve, n_paths=n_paths,
                 status=status)
@@ -211,6 +212,13 @@ def attn_desc(q: torch.Tensor, kt: torch.Tensor, k_cache: Optional[torch.Tensor]
     return dsc
 
 
+def _attn_desc_only(dsc):
+    """The binding takes any object with the memory of a descriptor: a caller's own is checked here."""
+    if not isinstance(dsc, AttnDesc):
+        raise C.ArgumentError("expected AttnDesc instead of " + type(dsc).__name__)
+    return dsc
+
+
 def tree_verify_attention_workspace_bytes(dsc: AttnDesc) -> int:
     return int(lib().etv_tree_verify_attention_workspace_bytes(C.byref(dsc)))
 
@@ -228,17 +236,16 @@ def tree_verify_attention(q, k_cache, v_cache, prefix_len, kt, vt, bitmask, n_no
     """q [B,T,Hq,d]; kt/vt [B,T,Hkv,d]; cache contiguous [B,P_cap,Hkv,d] or paged [nb,Hkv,16,d] + block_table.
     Returns (out [B,T,Hq,d] in q's dtype, lse float32 [B,Hq,T] or None)."""
     dsc = desc or attn_desc(q, kt, k_cache, block_table, P_max, scale, kv_split, flags)
-    B, T, Hq, d = q.shape
     if out is None:
         out = torch.empty_like(q)
     if lse is None and want_lse:
+        B, T, Hq, _ = q.shape
         lse = torch.empty((B, Hq, T), dtype=torch.float32, device=q.device)
     if workspace is None:
         workspace = torch.empty((max(256, tree_verify_attention_workspace_bytes(dsc)),), dtype=torch.uint8,
                                 device=q.device)
-    rc = lib().etv_tree_verify_attention(C.byref(dsc), _ptr(q), _ptr(k_cache), _ptr(v_cache), _ptr(block_table),
-                                         _ptr(prefix_len), _ptr(kt), _ptr(vt), _ptr(bitmask), _ptr(n_nodes),
-                                         _ptr(out), _ptr(lse), _ptr(workspace), workspace.numel(), _stream())
+    rc = _native().tree_verify_attention(_attn_desc_only(dsc), q, k_cache, v_cache, block_table, prefix_len, kt, vt, bitmask,
+                                         n_nodes, out, lse, workspace, workspace.numel())
     _check("etv_tree_verify_attention", rc)
     return out, lse
 
@@ -249,9 +256,8 @@ def tree_verify_attention_static(q, k_cache, v_cache, prefix_len, kt, vt, bitmas
     """tree_verify_attention with the split partials in the library's own fixed device array: the caller passes
     every input and output (`out`, optionally `lse`) and nothing is allocated, here or in the library."""
     dsc = desc or attn_desc(q, kt, k_cache, block_table, P_max, scale, kv_split, flags)
-    rc = lib().etv_tree_verify_attention_static(C.byref(dsc), _ptr(q), _ptr(k_cache), _ptr(v_cache),
-                                                _ptr(block_table), _ptr(prefix_len), _ptr(kt), _ptr(vt),
-                                                _ptr(bitmask), _ptr(n_nodes), _ptr(out), _ptr(lse), _stream())
+    rc = _native().tree_verify_attention_static(_attn_desc_only(dsc), q, k_cache, v_cache, block_table, prefix_len, kt, vt,
+                                                bitmask, n_nodes, out, lse)
     _check("etv_tree_verify_attention_static", rc)
     return out, lse
 
@@ -271,8 +277,7 @@ def safe_gather_paths(retrieve, n_nodes, T_max: int, dummy: int = 0, src: Option
         gathered = o.get("gathered") if out else None
         if gathered is None:
             gathered = torch.empty((B, L, W) + tuple(src.shape[2:]), dtype=src.dtype, device=dev)
-    rc = lib().etv_safe_gather_paths(_ptr(retrieve), _ptr(n_nodes), B, L, W, T_max, dummy, _ptr(src), row_bytes,
-                                     _ptr(safe), _ptr(pvalid), _ptr(gathered), _stream())
+    rc = _native().safe_gather_paths(retrieve, n_nodes, B, L, W, T_max, dummy, src, row_bytes, safe, pvalid, gathered)
     _check("etv_safe_gather_paths", rc)
     return dict(safe=safe, pvalid=pvalid, gathered=gathered)
 
@@ -302,9 +307,8 @@ def evaluate_posterior(logits, tokens, retrieve, n_nodes, dummy: int = 0, worksp
     A, acc, bonus = get("accept_len", (B,)), get("acc_nodes", (B, W)), get("bonus", (B,))
     if workspace is None and logits is not None:
         workspace = torch.empty((max(256, evaluate_posterior_workspace_bytes(B, T, V)),), dtype=torch.uint8, device=dev)
-    rc = lib().etv_evaluate_posterior(_ptr(logits), _ptr(tokens), _ptr(retrieve), _ptr(n_nodes), B, T, V, L, W,
-                                      dummy, _ptr(g), _ptr(ln), _ptr(best), _ptr(A), _ptr(acc), _ptr(bonus),
-                                      _ptr(workspace), workspace.numel() if workspace is not None else 0, _stream())
+    rc = _native().evaluate_posterior(logits, tokens, retrieve, n_nodes, B, T, V, L, W, dummy, g, ln, best, A, acc, bonus,
+                                      workspace, workspace.numel() if workspace is not None else 0)
     _check("etv_evaluate_posterior", rc)
     return dict(argmax=g, len=ln, best=best, accept_len=A, acc_nodes=acc, bonus=bonus)
 
@@ -316,7 +320,7 @@ def pack_lm_head(weight: torch.Tensor) -> torch.Tensor:
     if n == 0:
         raise EtvError("etv_lm_head_packed_bytes", -2)
     packed = torch.empty((n // 2,), dtype=weight.dtype, device=weight.device)
-    _check("etv_pack_lm_head", lib().etv_pack_lm_head(_ptr(weight), V, D, _ptr(packed), _stream()))
+    _check("etv_pack_lm_head", _native().pack_lm_head(weight, V, D, packed))
     return packed
 
 
@@ -339,9 +343,8 @@ def lm_head_argmax(hidden, weight, n_nodes, *, V: Optional[int] = None, want_max
     if workspace is None:
         workspace = torch.empty((max(256, int(lib().etv_lm_head_argmax_workspace_bytes(B, T, V))),), dtype=torch.uint8,
                                 device=dev)
-    rc = lib().etv_lm_head_argmax(_ptr(hidden), _ptr(weight), int(packed), _ptr(n_nodes), B, T, D, V,
-                                  _ptr(g) if finish else None, _ptr(mx) if finish else None,
-                                  _ptr(workspace), workspace.numel(), _stream())
+    rc = _native().lm_head_argmax(hidden, weight, int(packed), n_nodes, B, T, D, V, g if finish else None,
+                                  mx if finish else None, workspace, workspace.numel())
     _check("etv_lm_head_argmax", rc)
     return dict(argmax=g, maxval=mx) if finish else dict(workspace=workspace)
 
@@ -353,14 +356,12 @@ def _commit_desc(kt, k_cache, block_table, W: int, B: Optional[int] = None, T_ma
         Lyr, T = k_cache.shape[0], int(T_max)
         Hkv, d = (k_cache.shape[2], k_cache.shape[4]) if block_table is not None else (k_cache.shape[3], k_cache.shape[4])
     assert k_cache.shape[0] == Lyr
-    dsc = CommitDesc(B=B, T_max=T, Hkv=Hkv, d=d, elem_bytes=k_cache.element_size(), n_layers=Lyr, W=W, block_size=0,
-                     max_blocks=0, num_blocks=0, P_cap=0, reserved=0,
-                     cache_layer_stride=k_cache.stride(0) if Lyr > 1 else k_cache[0].numel())
+    stride = k_cache.stride(0) if Lyr > 1 else k_cache.numel()
+    elem = k_cache.element_size()
+    # positional, in the order of CommitDesc: B ... W, block_size, max_blocks, num_blocks, P_cap, reserved, cache_layer_stride
     if block_table is not None:
-        dsc.block_size, dsc.max_blocks, dsc.num_blocks = k_cache.shape[3], block_table.shape[1], k_cache.shape[1]
-    else:
-        dsc.P_cap = k_cache.shape[2]
-    return dsc
+        return CommitDesc(B, T, Hkv, d, elem, Lyr, W, k_cache.shape[3], block_table.shape[1], k_cache.shape[1], 0, 0, stride)
+    return CommitDesc(B, T, Hkv, d, elem, Lyr, W, 0, 0, 0, k_cache.shape[2], 0, stride)
 
 
 def verify_epilogue(logits, tokens, retrieve, n_nodes, kt, vt, k_cache, v_cache, prefix_len, capacity, *,
@@ -387,7 +388,7 @@ def verify_epilogue(logits, tokens, retrieve, n_nodes, kt, vt, k_cache, v_cache,
     safe, pvalid = get(go, "safe", (B, L, W)), get(go, "pvalid", (B, L, W), torch.uint8)
     gathered, row_bytes = None, 0
     if src is not None:
-        row_bytes = src[0, 0].numel() * src.element_size()
+        row_bytes = src.element_size() * (src.numel() // max(1, src.shape[0] * src.shape[1]))
         gathered = get(go, "gathered", (B, L, W) + tuple(src.shape[2:]), src.dtype)
     g, ln, best = get(po, "argmax", (B, T)), get(po, "len", (B, L)), get(po, "best", (B,))
     A, acc, bonus = get(po, "accept_len", (B,)), get(po, "acc_nodes", (B, W)), get(po, "bonus", (B,))
@@ -395,12 +396,9 @@ def verify_epilogue(logits, tokens, retrieve, n_nodes, kt, vt, k_cache, v_cache,
     if workspace is None and logits is not None:
         workspace = torch.empty((max(256, evaluate_posterior_workspace_bytes(B, T, V)),), dtype=torch.uint8, device=dev)
     dsc = _commit_desc(kt, k_cache, block_table, W, B, T)
-    rc = lib().etv_verify_epilogue(C.byref(dsc), _ptr(logits), V, _ptr(tokens), _ptr(retrieve), L, dummy, _ptr(src),
-                                   row_bytes, _ptr(safe), _ptr(pvalid), _ptr(gathered), _ptr(g), _ptr(ln), _ptr(best),
-                                   _ptr(A), _ptr(acc), _ptr(bonus), _ptr(kt), _ptr(vt), _ptr(k_cache), _ptr(v_cache),
-                                   _ptr(block_table), _ptr(prefix_len), _ptr(capacity), _ptr(n_nodes), _ptr(plo),
-                                   _ptr(slot), _ptr(status), _ptr(workspace),
-                                   workspace.numel() if workspace is not None else 0, _stream())
+    rc = _native().verify_epilogue(dsc, logits, V, tokens, retrieve, L, dummy, src, row_bytes, safe, pvalid, gathered, g, ln,
+                                   best, A, acc, bonus, kt, vt, k_cache, v_cache, block_table, prefix_len, capacity, n_nodes,
+                                   plo, slot, status, workspace, workspace.numel() if workspace is not None else 0)
     _check("etv_verify_epilogue", rc)
     return (dict(safe=safe, pvalid=pvalid, gathered=gathered),
             dict(argmax=g, len=ln, best=best, accept_len=A, acc_nodes=acc, bonus=bonus),
@@ -423,38 +421,31 @@ def commit_accepted_kv(kt, vt, k_cache, v_cache, prefix_len, capacity, n_nodes, 
         prefix_len_out = torch.empty((B,), dtype=torch.int32, device=dev)
     slot = o.get("slot_map") if out else torch.empty((B, W), dtype=torch.int32, device=dev)
     status = o.get("status") if out else torch.empty((B,), dtype=torch.int32, device=dev)
-    rc = lib().etv_commit_accepted_kv(C.byref(dsc), _ptr(kt), _ptr(vt), _ptr(k_cache), _ptr(v_cache),
-                                      _ptr(block_table), _ptr(prefix_len), _ptr(capacity), _ptr(n_nodes),
-                                      _ptr(acc_nodes), _ptr(accept_len), _ptr(prefix_len_out), _ptr(slot),
-                                      _ptr(status), _stream())
+    rc = _native().commit_accepted_kv(dsc, kt, vt, k_cache, v_cache, block_table, prefix_len, capacity, n_nodes,
+                                      acc_nodes, accept_len, prefix_len_out, slot, status)
     _check("etv_commit_accepted_kv", rc)
     return dict(prefix_len_out=prefix_len_out, slot_map=slot, status=status)
 
 
 def _cache_desc(cache: torch.Tensor, B: int, table: Optional[torch.Tensor]) -> CacheDesc:
-    Lyr = cache.shape[0]
-    dsc = CacheDesc(B=B, Hkv=0, d=cache.shape[4], elem_bytes=cache.element_size(), n_layers=Lyr, block_size=0,
-                    max_blocks=0, num_blocks=0, P_cap=0, reserved=0,
-                    cache_layer_stride=cache.stride(0) if Lyr > 1 else cache[0].numel())
-    if table is not None:
-        dsc.Hkv, dsc.block_size, dsc.max_blocks, dsc.num_blocks = cache.shape[2], cache.shape[3], table.shape[-1], cache.shape[1]
-    else:
-        dsc.Hkv, dsc.P_cap = cache.shape[3], cache.shape[2]
-    return dsc
+    Lyr, n1, n2, n3, d = cache.shape
+    stride = cache.stride(0) if Lyr > 1 else cache.numel()
+    # positional, in the order of CacheDesc: B, Hkv, d, elem_bytes, n_layers, block_size, max_blocks, num_blocks, P_cap, reserved
+    if table is not None:   # [Lyr, num_blocks, Hkv, block_size, d]
+        return CacheDesc(B, n2, d, cache.element_size(), Lyr, n3, table.shape[-1], n1, 0, 0, stride)
+    return CacheDesc(B, n3, d, cache.element_size(), Lyr, 0, 0, 0, n2, 0, stride)
 
 
 def replicate_branches(k_cache, v_cache, block_table, prefix_len, tail_len, N: int, free_blocks):
     """Paged caches [Lyr, nb, Hkv, bs, d]; block_table [B, max_blocks]; free_blocks int32 [n_free].
     Returns branch_table [B, N, max_blocks], block_base [B], n_taken [1], status [B] (device tensors)."""
-    B, dev = block_table.shape[0], k_cache.device
+    B = block_table.shape[0]
     dsc = _cache_desc(k_cache, B, block_table)
-    bt = torch.empty((B, N, block_table.shape[1]), dtype=torch.int32, device=dev)
-    base = torch.empty((B,), dtype=torch.int32, device=dev)
-    taken = torch.empty((1,), dtype=torch.int32, device=dev)
-    status = torch.empty((B,), dtype=torch.int32, device=dev)
-    rc = lib().etv_replicate_branches(C.byref(dsc), _ptr(k_cache), _ptr(v_cache), _ptr(block_table), _ptr(prefix_len),
-                                      _ptr(tail_len), N, _ptr(free_blocks), free_blocks.numel(), _ptr(bt), _ptr(base),
-                                      _ptr(taken), _ptr(status), _stream())
+    empty = _native().empty_i32
+    bt, base = empty(k_cache, B, N, block_table.shape[1]), empty(k_cache, B)
+    taken, status = empty(k_cache, 1), empty(k_cache, B)
+    rc = _native().replicate_branches(dsc, k_cache, v_cache, block_table, prefix_len, tail_len, N, free_blocks,
+                                      free_blocks.numel(), bt, base, taken, status)
     _check("etv_replicate_branches", rc)
     return dict(branch_table=bt, block_base=base, n_taken=taken, status=status)
 
@@ -464,12 +455,9 @@ def commit_path_indices(src_k, src_v, dst_k, dst_v, path_indices, src_len, new_l
     """Caches [Lyr, B, P_cap, Hkv, d] (two buffers) or [Lyr, nb, Hkv, bs, d] with two block tables (dst_table is
     updated in place with the shared blocks).  Returns kept_len, status."""
     B, L_cap = path_indices.shape
-    dev = src_k.device
     dsc = _cache_desc(src_k, B, src_table)
-    kept = torch.empty((B,), dtype=torch.int32, device=dev)
-    status = torch.empty((B,), dtype=torch.int32, device=dev)
-    rc = lib().etv_commit_path_indices(C.byref(dsc), _ptr(src_k), _ptr(src_v), _ptr(dst_k), _ptr(dst_v), _ptr(src_table),
-                                       _ptr(dst_table), _ptr(path_indices), L_cap, _ptr(src_len), _ptr(new_len),
-                                       int(fast), _ptr(kept), _ptr(status), _stream())
+    kept, status = _native().empty_i32(src_k, B), _native().empty_i32(src_k, B)
+    rc = _native().commit_path_indices(dsc, src_k, src_v, dst_k, dst_v, src_table, dst_table, path_indices, L_cap,
+                                       src_len, new_len, int(fast), kept, status)
     _check("etv_commit_path_indices", rc)
     return dict(kept_len=kept, status=status)

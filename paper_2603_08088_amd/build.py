@@ -1,15 +1,17 @@
-"""Build libeagletv.so (hipcc, gfx950) in-tree.  Run as ``python -m paper_2603_08088_amd.build``."""
+"""Build libeagletv.so (hipcc, gfx950) and its Python binding in-tree.  Run as ``python -m paper_2603_08088_amd.build``."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libeagletv.so")
 PROBE_LIB = os.path.join(HERE, "libeagletv_probe.so")   # measurement aids (include/eagletv_probe.h), separate on purpose
+BINDING = os.path.join(HERE, "_binding.so")   # the calls of the library as a Python module (csrc/binding.cpp), host code only
 SOURCES = ["api.hip", "mask.hip", "attention.hip", "posterior.hip", "commit.hip", "lmhead.hip", "branch.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
@@ -19,13 +21,28 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-fvi
 
 def _hipcc(sources, target, verbose, extra=()):
     # extern "C" entry points are exported explicitly; everything else stays hidden
-    cmd = [HIPCC] + FLAGS + ["-DETV_BUILDING"] + list(extra) + [os.path.join(CSRC, s) for s in sources] + ["-o", target]
+    _run([HIPCC] + FLAGS + ["-DETV_BUILDING"] + list(extra) + [os.path.join(CSRC, s) for s in sources] + ["-o", target], verbose)
+
+
+def _host_binding(verbose):
+    import torch
+    from torch.utils import cpp_extension
+    torch_lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    rocm = os.path.dirname(os.path.dirname(HIPCC))
+    includes = [os.path.join(ROOT, "include"), sysconfig.get_paths()["include"], os.path.join(rocm, "include")] + cpp_extension.include_paths()
+    _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+          f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"] + [f"-I{d}" for d in includes] +
+         [os.path.join(CSRC, "binding.cpp"), "-o", BINDING, f"-L{HERE}", f"-L{torch_lib}", "-l:libeagletv.so", "-lc10", "-lc10_hip", "-ltorch_cpu",
+          "-ltorch_python", "-Wl,-rpath,$ORIGIN"], verbose)
+
+
+def _run(cmd, verbose):
     if verbose:
         print(" ".join(cmd), flush=True)
     res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     out = "\n".join(l for l in res.stdout.splitlines() if "packed-fp32-ops" not in l)
     if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + out)
+        raise RuntimeError(os.path.basename(cmd[0]) + " failed:\n" + out)
     if verbose and out.strip():
         print(out)
 
@@ -33,6 +50,7 @@ def _hipcc(sources, target, verbose, extra=()):
 def build(verbose: bool = False, extra=()) -> str:
     _hipcc(SOURCES, LIB, verbose, extra)
     _hipcc(["probe.hip"], PROBE_LIB, verbose)
+    _host_binding(verbose)
     return LIB
 
 

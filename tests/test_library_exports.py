@@ -89,3 +89,24 @@ def test_struct_layouts_match_the_header():
     assert ctypes.sizeof(api.AttnDesc) == 14 * 4
     assert ctypes.sizeof(api.AttnPlan) == 8 * 4 + 8
     assert ctypes.sizeof(api.CommitDesc) == 12 * 4 + 8
+
+
+def test_binding_refuses_what_is_not_a_device_tensor_or_a_descriptor():
+    """The native call path checks its arguments before anything is launched; it needs no GPU to do so."""
+    import pytest
+    import torch
+    x = torch.zeros(8, dtype=torch.int32)
+    call = api._native()
+    with pytest.raises(AssertionError):          # host memory
+        call.pack_lm_head(x, 1, 128, x)
+    with pytest.raises(TypeError):               # neither a tensor nor None
+        call.pack_lm_head([1, 2], 1, 128, None)
+    with pytest.raises(TypeError):               # a size that is not an int
+        call.pack_lm_head(None, 1.0, 128, None)
+    with pytest.raises(TypeError):               # the C prototype's number of arguments, less the stream
+        call.pack_lm_head(None, 1, 128)
+    with pytest.raises(ValueError):              # shorter than the struct
+        call.commit_accepted_kv(b"\0" * 8, *[None] * 13)
+    with pytest.raises(ctypes.ArgumentError):    # another struct
+        api.tree_verify_attention(x, x, x, x, x, x, x, x, P_max=1, desc=api.CommitDesc(), out=x, lse=x, workspace=x)
+    assert call.empty_i32(x, 3, 4).shape == (3, 4) and call.empty_i32(x, 2).dtype == torch.int32
