@@ -462,14 +462,17 @@ __global__ void __launch_bounds__(512, 1) lm_head_argmax_wide_kernel(LhParams p)
 // node rows; wavefront w of 8 owns 128 vocabulary rows (w % 2) x 64 node rows (w / 2) as 4 x 2 accumulators of
 // 32 x 32, so the eight products of a 16-wide contraction step need six fragments (1.3 LDS bytes per flop less
 // than the kernels above, and eight independent accumulator chains).  The contraction runs in steps of 64
-// elements: a step's weight rows (256 x 128 B) and hidden rows (256 x 128 B) are 64 KiB of LDS, two stages, filled
-// by direct-to-LDS loads one step ahead, one barrier per step (32 products per wavefront).  A 128-byte tile row
-// holds eight 16-byte chunks; chunk c of row r sits at position c ^ ((r >> 1) & 7), so the sixteen consecutive rows
+// elements: a step's weight rows (256 x 128 B) and hidden rows (256 x 128 B) are 64 KiB of LDS, two stages.  A 128-byte
+// tile row holds eight 16-byte chunks; chunk c of row r sits at position c ^ ((r >> 1) & 7), so the sixteen consecutive rows
 // that a 16-byte fragment read serves in one cycle fall on sixteen different bank groups.  The weights reach a
-// compute unit from L2 (the row groups of one vocabulary tile run side by side on one XCD), the hidden rows from
+// compute unit from L2 (workgroups of one vocabulary tile run side by side on one XCD), the hidden rows from
 // L2 and the memory-side cache.  C^T[vocab, node] as above: a node is an accumulator column, so a wavefront's
 // maximum over its 128 vocabulary rows needs one exchange between the lane halves and is exactly one per-tile
 // partial of the layout the finishing kernel (and the epilogue) reads.
+// What bounds it is the matrix cores at the clock they hold under load: 4096 rows, D = 4096, V = 32000 take 834 us =
+// 1.29 PFLOP/s, the rate of a plain library product of that shape here.  With all loads, then all fragment reads, then all
+// products of a step behind its barrier it was 893 us (the wavefronts of a SIMD issued addresses and waited for LDS together),
+// and 2048 x 64000 x 2048 467 us (now 443).
 // ----------------------------------------------------------------------------------------------------------------
 constexpr int LHG_VT = 256, LHG_RT = 256;    // vocabulary rows, node rows per workgroup
 constexpr int LHG_KC = 64;                   // contraction elements per step
@@ -477,6 +480,7 @@ constexpr int LHG_ROWB = LHG_KC * 2;         // 128 B
 constexpr int LHG_W_BYTES = LHG_VT * LHG_ROWB;            // 32 KiB
 constexpr int LHG_STAGE = LHG_W_BYTES + LHG_RT * LHG_ROWB;  // 64 KiB
 constexpr int LHG_NS = 2;
+constexpr int LHG_PT = 4, LHG_PG = 8;        // tiles x row groups that an XCD works on at a time
 constexpr int LHG_MIN_ROWS = 257;   // measured: from 257 rows on this tiling beats the 128-row groups (288 rows: 129 vs 143 us)
 
 __global__ void __launch_bounds__(512, 2) lm_head_argmax_gemm_kernel(LhParams p) {
@@ -485,9 +489,17 @@ __global__ void __launch_bounds__(512, 2) lm_head_argmax_gemm_kernel(LhParams p)
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c32 = lane & 31, hh = lane >> 5;
     const int tiles256 = (p.tiles + 1) >> 1;
-    const int rest = blockIdx.x >> 3;
-    const int group = rest % p.groups;
-    const int tile = (rest / p.groups) * 8 + (blockIdx.x & 7);   // 256-row vocabulary tile
+    // XCD x = id % 8 takes the vocabulary tiles x, x + 8, ...  Its 32 compute units work on panels of LHG_PT tiles x LHG_PG
+    // row groups: 4 + 8 operand tiles are fetched for 32 products of tiles (all groups of one tile side by side: 2 + 16).
+    const int own = (tiles256 + 7) >> 3;                       // tiles of an XCD
+    int j = blockIdx.x >> 3;
+    const int panel = j / (LHG_PT * p.groups);
+    const int pt = min(LHG_PT, own - panel * LHG_PT);          // the last panel may be narrower
+    j -= panel * LHG_PT * p.groups;
+    const int gp = j / (pt * LHG_PG);
+    j -= gp * pt * LHG_PG;
+    const int group = gp * LHG_PG + j / pt;
+    const int tile = (panel * LHG_PT + j % pt) * 8 + (blockIdx.x & 7);   // 256-row vocabulary tile
     if (tile >= tiles256) return;  // uniform over the workgroup
     const int v0 = tile * LHG_VT;
     const int r0 = group * LHG_RT;
@@ -523,16 +535,15 @@ __global__ void __launch_bounds__(512, 2) lm_head_argmax_gemm_kernel(LhParams p)
         hbase[u] = p.hidden + (size_t)rfirst * row_bytes;
         hvoff[u] = (uint32_t)((size_t)(rrow - rfirst) * row_bytes) + lane_chunk * 16;
     }
-    auto issue = [&](int st) {
+    auto issue_one = [&](int st, int u) {   // load u of 8: four of the weight rows, four of the hidden rows
         const uint32_t dst = smem_addr + (uint32_t)(st % LHG_NS) * LHG_STAGE + (uint32_t)wave * 1024;
         const size_t koff = (size_t)st * LHG_ROWB;   // row-major: the next 128 B of every row
         const size_t woff = p.packed ? (size_t)(st >> 1) * LH_W_BYTES + (size_t)(st & 1) * LHG_ROWB : koff;
-#pragma unroll
-        for (int u = 0; u < 4; u++) lh_async_load16<false>(wbase[u] + woff, wvoff[u], dst + u * 8192);
-#pragma unroll
-        for (int u = 0; u < 4; u++) lh_async_load16<false>(hbase[u] + koff, hvoff[u], dst + LHG_W_BYTES + u * 8192);
+        if (u < 4) lh_async_load16<false>(wbase[u] + woff, wvoff[u], dst + u * 8192);
+        else lh_async_load16<false>(hbase[u - 4] + koff, hvoff[u - 4], dst + LHG_W_BYTES + (u - 4) * 8192);
     };
-    issue(0);
+#pragma unroll
+    for (int u = 0; u < 8; u++) issue_one(0, u);
 
     // Fragments: A = weight rows of vocabulary block vb (4 per wavefront), B = hidden rows of row block rb (2);
     // the lane holds row c32 and the 8 contraction values at chunk 2 * kk + hh of the 64-element step.
@@ -548,27 +559,54 @@ __global__ void __launch_bounds__(512, 2) lm_head_argmax_gemm_kernel(LhParams p)
 #pragma unroll
             for (int i = 0; i < 16; i++) acc[vb][rb][i] = 0.f;
 
-    for (int st = 0; st < steps; st++) {
-        lh_wait_vmcnt<0>();              // this wavefront's part of step st has landed
-        __builtin_amdgcn_s_barrier();    // step st is in LDS for everyone; the stage of step st - 1 is free
-        asm volatile("" ::: "memory");
-        if (st + 1 < steps) issue(st + 1);
+    // The fragments of a 16-wide contraction step are read one step ahead into the other of two register sets, and the
+    // barrier stands before the last of a stage's four: by then every fragment of the stage is in registers, so the products
+    // behind the barrier run while the next stage's first fragments are read and the stage just freed is filled again.
+    // Reads and load issue are placed one by one between the products, where they cost no issue slot of the matrix core.
+    struct Frags {
+        lh_bf16x8 a[4], b[2];
+    };
+    Frags f0, f1;
+    auto read_one = [&](Frags &f, int st, int kk, int x) {
         const uint8_t *stage = lh_smem + (st % LHG_NS) * LHG_STAGE;
+        const int col = ((2 * kk + hh) ^ sw) << 4;
+        if (x < 2) f.b[x] = *reinterpret_cast<const lh_bf16x8 *>(stage + b_row + x * (32 * LHG_ROWB) + col);
+        else f.a[x - 2] = *reinterpret_cast<const lh_bf16x8 *>(stage + a_row + (x - 2) * (32 * LHG_ROWB) + col);
+    };
+    // eight products of `cur`; between them the six reads of `next` (step nkk of stage nst) and, with `load`, stage ist
+    auto phase = [&](const Frags &cur, Frags &next, bool read, int nst, int nkk, bool load, int ist) {
 #pragma unroll
-        for (int kk = 0; kk < 4; kk++) {
-            const int col = ((2 * kk + hh) ^ sw) << 4;
-            lh_bf16x8 a[4], b[2];
-#pragma unroll
-            for (int vb = 0; vb < 4; vb++) a[vb] = *reinterpret_cast<const lh_bf16x8 *>(stage + a_row + vb * (32 * LHG_ROWB) + col);
-#pragma unroll
-            for (int rb = 0; rb < 2; rb++) b[rb] = *reinterpret_cast<const lh_bf16x8 *>(stage + b_row + rb * (32 * LHG_ROWB) + col);
-#pragma unroll
-            for (int vb = 0; vb < 4; vb++)
-#pragma unroll
-                for (int rb = 0; rb < 2; rb++)
-                    acc[vb][rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[vb], b[rb], acc[vb][rb], 0, 0, 0);
+        for (int x = 0; x < 8; x++) {
+            const int vb = x >> 1, rb = x & 1;
+            acc[vb][rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cur.a[vb], cur.b[rb], acc[vb][rb], 0, 0, 0);
+            if (read && x < 6) read_one(next, nst, nkk, x);
+            if (load) issue_one(ist, x);
+            __builtin_amdgcn_sched_barrier(0);
         }
-    }
+    };
+    lh_wait_vmcnt<0>();
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int u = 0; u < 8; u++) issue_one(1, u);   // D is a multiple of 128: at least two steps
+#pragma unroll
+    for (int x = 0; x < 6; x++) read_one(f0, 0, 0, x);
+    auto step = [&](int st, bool more, bool load) {
+        phase(f0, f1, true, st, 1, false, 0);
+        phase(f1, f0, true, st, 2, false, 0);
+        phase(f0, f1, true, st, 3, false, 0);
+        if (more) {
+            lh_wait_vmcnt<0>();                   // this wavefront's part of stage st + 1 has landed
+            __builtin_amdgcn_s_waitcnt(0xc07f);   // and its reads of stage st are done
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+        }
+        phase(f1, f0, more, st + 1, 0, load, st + 2);
+    };
+    int st = 0;
+    for (; st < steps - 2; st++) step(st, true, true);
+    step(st, true, false);
+    step(st + 1, false, false);
 
     // Epilogue: per node column the maximum over the wavefront's 128 vocabulary rows, ascending (block vb, then
     // element i of lane half hh = row 8 * (i / 4) + 4 * hh + i % 4), then over the two lane halves: one per-tile
