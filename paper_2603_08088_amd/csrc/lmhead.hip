@@ -457,7 +457,7 @@ __global__ void __launch_bounds__(512, 1) lm_head_argmax_wide_kernel(LhParams p)
 }
 
 // ----------------------------------------------------------------------------------------------------------------
-// More than 256 node rows (a batch of trees): the product is no longer a weight stream but a dense
+// Many node rows (a batch of trees; the rule is at lh_use_gemm): the product is no longer a weight stream but a dense
 // contraction bound by the matrix cores, and the tiling is a GEMM's.  A workgroup takes 256 vocabulary rows x 256
 // node rows; wavefront w of 8 owns 128 vocabulary rows (w % 2) x 64 node rows (w / 2) as 4 x 2 accumulators of
 // 32 x 32, so the eight products of a 16-wide contraction step need six fragments (1.3 LDS bytes per flop less
@@ -481,7 +481,15 @@ constexpr int LHG_W_BYTES = LHG_VT * LHG_ROWB;            // 32 KiB
 constexpr int LHG_STAGE = LHG_W_BYTES + LHG_RT * LHG_ROWB;  // 64 KiB
 constexpr int LHG_NS = 2;
 constexpr int LHG_PT = 4, LHG_PG = 8;        // tiles x row groups that an XCD works on at a time
-constexpr int LHG_MIN_ROWS = 257;   // measured: from 257 rows on this tiling beats the 128-row groups (288 rows: 129 vs 143 us)
+// This tiling or the 128-row groups: each runs one workgroup per compute unit, so its time is its rounds over the 256 of
+// them, and a round here is four times the products in about twice the time (D = 4096: 97 ... 120 us, against 46 ... 58).
+// 256 rows: V = 64000 83 us against 115 (1 and 4 rounds), V = 32000 120 against 105 (1 and 2); 300 rows, V = 32000 121 against 137
+// (1 and 3); 480 rows, V = 8000 76 against 46 (1 and 1); 1404 rows, D = 1536, V = 1133 35.5 against 21.9 (1 and 1).
+static bool lh_use_gemm(long rows, long tiles) {
+    const long wide = (tiles * ((rows + LHW_RT - 1) / LHW_RT) + 255) / 256;
+    const long gemm = ((tiles + 1) / 2 * ((rows + LHG_RT - 1) / LHG_RT) + 255) / 256;
+    return rows > LHW_RT && (2 * gemm < wide || rows > 65535L * LHW_RT);  // and where the other's groups exceed its grid
+}
 
 __global__ void __launch_bounds__(512, 2) lm_head_argmax_gemm_kernel(LhParams p) {
     const uint32_t smem_addr = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)lh_smem;
@@ -733,12 +741,11 @@ extern "C" int32_t etv_lm_head_argmax(const void *hidden, const void *weight, in
     if ((size_t)D * 2 * 8 >= (1ull << 32)) return ETV_ERR_UNSUPPORTED;
     if (B == 0) return ETV_OK;
     const long rows_total = (long)B * T_max;
+    const long tiles = ((long)V + LH_VT - 1) / LH_VT;
+    const bool gemm = lh_use_gemm(rows_total, tiles);
     const bool wide = rows_total > LH_RT;   // more than 64 rows: 128 per workgroup
-    // from a few hundred rows on the product is bound by the matrix cores: GEMM tiling, 256 x 256 per workgroup
-    const bool gemm = rows_total >= LHG_MIN_ROWS;
     const long rt = gemm ? LHG_RT : (wide ? LHW_RT : LH_RT);
     const long groups = (rows_total + rt - 1) / rt;
-    const long tiles = ((long)V + LH_VT - 1) / LH_VT;
     if (groups > 65535 || rows_total > 0x7fffffffL) return ETV_ERR_UNSUPPORTED;
     if (!workspace || workspace_bytes < etv_lm_head_argmax_workspace_bytes(B, T_max, V))
         return ETV_ERR_WORKSPACE_TOO_SMALL;

@@ -101,6 +101,20 @@ def test_random_row_counts_and_vocabularies_on_the_gemm_path():
         _check(h, w, n)
 
 
+@pytest.mark.parametrize("B,T,D,V", [(32, 125, 128, 2177), (31, 129, 384, 2304), (10, 100, 128, 8225), (3, 100, 256, 21889), (1, 257, 128, 22017),
+                                      (17, 241, 128, 2200)])
+def test_gemm_tiling_where_it_saves_rounds(B, T, D, V):
+    """The GEMM tiling runs where it needs less than half the rounds of workgroups: vocabularies that end inside the first and
+    the second half of a 256-row tile, last row groups of 1 ... 256 rows, several panels of tiles and groups per XCD."""
+    tiles, rows = (V + 127) // 128, B * T
+    rounds = [-(-t * -(-rows // r) // 256) for t, r in ((tiles, 128), ((tiles + 1) // 2, 256))]
+    assert 2 * rounds[1] < rounds[0]
+    rng = np.random.default_rng(3070 + V)
+    h = _bf16(rng.standard_normal((B, T, D)))
+    w = _bf16(rng.standard_normal((V, D)) / np.sqrt(D))
+    _check(h, w, [T] + [int(rng.integers(0, T + 1)) for _ in range(B - 1)])
+
+
 def test_exact_ties_on_the_gemm_path_take_the_lowest_index():
     rng = np.random.default_rng(3110)
     B, T, D, V = 5, 128, 128, 900
