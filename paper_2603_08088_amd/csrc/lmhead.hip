@@ -645,7 +645,8 @@ __global__ void __launch_bounds__(512, 2) lm_head_argmax_gemm_kernel(LhParams p)
     }
 }
 
-// One wavefront per node row: reduce the per-tile partials (lowest index among equals); padded rows give -1.
+// One wavefront per node row: reduce the per-tile partials (lowest index among equals); padded rows give -1.  Latency is all
+// there is to it: one trip to memory behind the kernel arguments.
 __global__ void __launch_bounds__(256) lm_head_finish_kernel(const float *__restrict__ pval,
                                                             const int32_t *__restrict__ pidx, int tiles,
                                                             const int32_t *__restrict__ n_nodes, int rows_total,
@@ -654,19 +655,23 @@ __global__ void __launch_bounds__(256) lm_head_finish_kernel(const float *__rest
     const int r = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (r >= rows_total) return;
     const int b = r / T_max, k = r - b * T_max;
-    if (k >= clampi(n_nodes[b], 0, T_max)) {
-        if (lane == 0) {
-            argmax[r] = -1;
-            if (maxval) maxval[r] = -INFINITY;
-        }
-        return;
-    }
+    // Padded rows have partials too: they are read with the node count still on its way, and dropped.
+    const int n = clampi(n_nodes[b], 0, T_max);
     float bv = -INFINITY;
     int bi = 0x7fffffff;
-    for (int t = lane; t < tiles; t += 64) {
-        const float v = pval[(size_t)r * tiles + t];
-        const int i = pidx[(size_t)r * tiles + t];
-        if (v > bv || (v == bv && i < bi)) { bv = v; bi = i; }
+    // four partials per lane and trip to memory (V = 32000: all 250 in one); past the end the last one again
+    for (int t0 = lane; t0 < tiles; t0 += 256) {
+        float v[4];
+        int i[4];
+#pragma unroll
+        for (int u = 0; u < 4; u++) {
+            const size_t at = (size_t)r * tiles + min(t0 + 64 * u, tiles - 1);
+            v[u] = pval[at];
+            i[u] = pidx[at];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; u++)
+            if (v[u] > bv || (v[u] == bv && i[u] < bi)) { bv = v[u]; bi = i[u]; }
     }
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) {
@@ -675,8 +680,8 @@ __global__ void __launch_bounds__(256) lm_head_finish_kernel(const float *__rest
         if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
     }
     if (lane == 0) {
-        argmax[r] = bi;
-        if (maxval) maxval[r] = bv;
+        argmax[r] = k < n ? bi : -1;
+        if (maxval) maxval[r] = k < n ? bv : -INFINITY;
     }
 }
 
