@@ -39,7 +39,7 @@ struct AttnParams {
     //   part_o [B * nsplit][Hq][T_max][d]; split_tab[b] = (first slot, splits in use) for the combine kernel
     int balanced;
     int2 *split_tab;
-    uint32_t inv_g, inv_hkv, inv_nsplit;  // key-block kernel: floor(2^32 / G) and so on, for fast_div
+    uint32_t inv_g, inv_hkv, inv_nsplit, inv_pairs;  // floor(2^32 / G) and so on, for fast_div
 };
 
 constexpr float kLn2 = 0.6931471805599453f;
@@ -62,6 +62,20 @@ __device__ __forceinline__ size_t prefix_row_offset(const AttnParams &p, int b, 
 __device__ __forceinline__ size_t tree_row_offset(const AttnParams &p, int b, int kvh, int j) {
     return (((size_t)b * p.T_max + j) * p.Hkv + kvh) * (size_t)p.d;
 }
+
+// x / d and x % d with inv = floor(2^32 / d): the estimate is at most one too small for any 32-bit x.  (The compiler's
+// general division is some forty dependent instructions, each 3.5 ns of a lone wavefront's start-up.)
+__device__ __forceinline__ uint32_t fast_div(uint32_t x, uint32_t d, uint32_t inv, uint32_t &rem) {
+    uint32_t q = __umulhi(x, inv);
+    rem = x - q * d;
+    if (rem >= d) {
+        q++;
+        rem -= d;
+    }
+    return q;
+}
+
+static uint32_t fast_div_inv(int d) { return d == 1 ? 0xffffffffu : (uint32_t)((1ull << 32) / (uint32_t)d); }
 
 __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll
@@ -1220,20 +1234,6 @@ __device__ __forceinline__ void wait_lds_reads() {
     asm volatile("" ::: "memory");
 }
 
-// x / d and x % d with inv = floor(2^32 / d): the estimate is at most one too small for any 32-bit x.  (The compiler's
-// general division is some forty dependent instructions, each 3.5 ns of a lone wavefront's start-up.)
-__device__ __forceinline__ uint32_t fast_div(uint32_t x, uint32_t d, uint32_t inv, uint32_t &rem) {
-    uint32_t q = __umulhi(x, inv);
-    rem = x - q * d;
-    if (rem >= d) {
-        q++;
-        rem -= d;
-    }
-    return q;
-}
-
-static uint32_t fast_div_inv(int d) { return d == 1 ? 0xffffffffu : (uint32_t)((1ull << 32) / (uint32_t)d); }
-
 template <int D, bool PAGED>
 __global__ void __launch_bounds__(KB_NW * 64, D == 64 ? 4 : 2) attn_blocks_kernel(AttnParams p) {
     using G_ = KbGeo<D>;
@@ -1530,9 +1530,13 @@ __global__ void __launch_bounds__(F32_NW * 64, 2) attn_f32_kernel(AttnParams p) 
     const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // 1-D grid: id = ((unit / 8) * chunks + chunk) * 8 + unit % 8, unit = slot * Hkv + KV head, slot = (sequence, split)
-    const int rest = blockIdx.x >> 3, rg = rest % p.pairs;
-    const long unit = (long)(rest / p.pairs) * 8 + (blockIdx.x & 7);
-    const int slot = (int)(unit / p.Hkv), kvh = (int)(unit % p.Hkv);
+    asm volatile("" ::"s"(p.q), "s"(p.k_cache), "s"(p.v_cache), "s"(p.kt), "s"(p.vt), "s"(p.block_table), "s"(p.prefix_len),
+                 "s"(p.n_nodes), "s"(p.bitmask), "s"(p.B), "s"(p.T_max), "s"(p.Hq), "s"(p.Hkv), "s"(p.G), "s"(p.block_size),
+                 "s"(p.max_blocks), "s"(p.P_cap), "s"(p.P_max), "s"(p.words), "s"(p.chunk), "s"(p.nsplit), "s"(p.pairs));
+    uint32_t rg_, rem;
+    const uint32_t unit8 = fast_div(blockIdx.x >> 3, p.pairs, p.inv_pairs, rg_);
+    const int rg = (int)rg_;
+    const int slot = (int)fast_div(unit8 * 8 + (blockIdx.x & 7), p.Hkv, p.inv_hkv, rem), kvh = (int)rem;
     if (slot >= p.B * p.nsplit) return;  // uniform over the workgroup
     SplitShare share{};
     if (p.balanced) {
@@ -1540,8 +1544,9 @@ __global__ void __launch_bounds__(F32_NW * 64, 2) attn_f32_kernel(AttnParams p) 
         if (!share.live) return;  // uniform over the workgroup
         if (share.j == 0 && kvh == 0 && rg == 0 && threadIdx.x == 0) p.split_tab[share.b] = make_int2(share.start, share.nvalid);
     }
-    const int b = p.balanced ? share.b : slot / p.nsplit;
-    const int s = p.balanced ? share.j : slot % p.nsplit;
+    const int slot_b = (int)fast_div(slot, p.nsplit, p.inv_nsplit, rem);
+    const int b = uni(p.balanced ? share.b : slot_b);
+    const int s = uni(p.balanced ? share.j : (int)rem);
     const int chunk = p.balanced ? share.tps * KT : p.chunk;
     const int n = clampi(p.balanced ? share.n_raw : p.n_nodes[b], 0, p.T_max);
     const int P = clampi(p.balanced ? share.P_raw : p.prefix_len[b], 0, p.P_max);
@@ -1549,8 +1554,8 @@ __global__ void __launch_bounds__(F32_NW * 64, 2) attn_f32_kernel(AttnParams p) 
     if (s >= nvalid) return;  // uniform over the workgroup
     const bool direct = (p.nsplit == 1);
 
-    const int r = rg * F32_ROWS + c;  // the lane's packed query row: node kq, head h
-    const int kq = r / p.G, h = kvh * p.G + (r - kq * p.G);
+    // the lane's packed query row: node kq, head h
+    const int kq = (int)fast_div(rg * F32_ROWS + c, p.G, p.inv_g, rem), h = kvh * p.G + (int)rem;
     const bool rv = kq < n;
     const int k0 = s * chunk, k1 = min(P, k0 + chunk);
     const bool active = rg * F32_ROWS < n * p.G;  // does the chunk hold a valid row?
@@ -1728,7 +1733,7 @@ __global__ void __launch_bounds__(F32_NW * 64, 2) attn_f32_kernel(AttnParams p) 
     }
     __syncthreads();
     const int row = threadIdx.x >> 4, piece = threadIdx.x & 15;  // a row's 16 threads own columns 64 v + 4 * piece .. + 3
-    const int r2 = rg * F32_ROWS + row, kq2 = r2 / p.G, h2 = kvh * p.G + (r2 - kq2 * p.G);
+    const int kq2 = (int)fast_div(rg * F32_ROWS + row, p.G, p.inv_g, rem), h2 = kvh * p.G + (int)rem;
     if (kq2 >= p.T_max) return;
     const bool rv2 = kq2 < n;
     if (!rv2 && !direct) return;
@@ -2052,6 +2057,8 @@ static int32_t attention_run(const etv_attn_desc *h, const void *q, const void *
     p.block_size = h->block_size; p.max_blocks = h->max_blocks; p.P_cap = h->P_cap; p.P_max = h->P_max;
     p.words = (h->T_max + 63) / 64;
     p.chunk = pl.chunk; p.nsplit = pl.nsplit; p.pairs = pl.pairs; p.wgp = pl.wgp;
+    p.inv_g = fast_div_inv(p.G); p.inv_hkv = fast_div_inv(p.Hkv); p.inv_nsplit = fast_div_inv(p.nsplit);
+    if (p.pairs > 0) p.inv_pairs = fast_div_inv(p.pairs);
     const float scale = (h->scale == 0.f) ? 1.0f / sqrtf((float)h->d) : h->scale;
     p.scale_log2 = scale * 1.4426950408889634f;
     if (pl.nsplit > 1) {
@@ -2066,9 +2073,6 @@ static int32_t attention_run(const etv_attn_desc *h, const void *q, const void *
     int32_t rc;
     if (pl.blocks) {
         const dim3 grid(8, pl.pairs, ((unsigned)h->B * pl.nsplit * h->Hkv + 7) / 8);
-        p.inv_g = fast_div_inv(p.G);
-        p.inv_hkv = fast_div_inv(p.Hkv);
-        p.inv_nsplit = fast_div_inv(p.nsplit);
         if (h->d == 128) rc = h->block_size > 0 ? launch_blocks<128, true>(p, grid, st) : launch_blocks<128, false>(p, grid, st);
         else rc = h->block_size > 0 ? launch_blocks<64, true>(p, grid, st) : launch_blocks<64, false>(p, grid, st);
     } else if (pl.mfma) {
