@@ -420,10 +420,9 @@ __global__ void __launch_bounds__(256) attn_combine_kernel(AttnParams p) {
 // Both products keep the query index on the accumulator column, so the softmax statistics and the
 // rescale of O never cross lanes.
 //
-// d = 64 runs the same loop on tiles of half the bytes, with two bf16 parts per probability (Geo::NP): half the
-// products per score but the same softmax, so the vector ALU bounds it from T = 32 up.  B = 4 sequences of 900 ... 1500
-// keys, T = 48, 32/8 heads: 20 us (1040 us on the one-row-per-wavefront VALU kernel, which re-read every key row from
-// L2 for each of the G * T query rows); B = 32, P = 4096: T = 8 52 us, T = 32 81 us, T = 128 242 us.
+// d = 64 runs the same loop on tiles of half the bytes, with three bf16 parts per probability (Geo::NP): twice the
+// products per score, and a softmax that splits its weights, so the vector ALU bounds it from T = 32 up.  32/8 heads, B = 32,
+// P = 4096: T = 32 90 us, T = 128 276 us (two parts, 16 bits of the weights: 76 and 230); B = 1, P = 32768, T = 128 80 us (68).
 // ----------------------------------------------------------------------------------------------
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
@@ -446,9 +445,9 @@ struct Geo {
     static constexpr int CPR = ROW_BYTES / 16;            // 16-byte chunks of a row: 16 or 8
     static constexpr int KK = D / 16;                     // 16-wide contraction steps of Q . K
     static constexpr int DB = D / 32;                     // 32-wide output column blocks
-    // bf16 parts of a probability in the PV product.  At d = 64 the products are half as many per score, and a second
-    // part (the remainder of the first) keeps the error of the result that of its own rounding to bf16.
-    static constexpr int NP = D == 64 ? 2 : 1;
+    // bf16 parts of a probability in the PV product.  At d = 64 a probability enters it with all its 24 bits: three
+    // parts of eight, whose products with a bf16 V are exact in fp32.
+    static constexpr int NP = D == 64 ? 3 : 1;
 };
 
 __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
@@ -457,12 +456,15 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
     return __builtin_bit_cast(uint32_t, r);
 }
 
-// Two fp32 values as bf16 pairs hi + lo: hi their upper halves, lo the remainders (exact) rounded to bf16, so that
-// hi + lo carries 16 significant bits.
-__device__ __forceinline__ void split_bf16x2(float a, float b, uint32_t &hi, uint32_t &lo) {
-    const uint32_t ua = __float_as_uint(a), ub = __float_as_uint(b);
-    hi = __builtin_amdgcn_perm(ub, ua, 0x07060302u);
-    lo = pack_bf16x2(a - __uint_as_float(ua & 0xffff0000u), b - __uint_as_float(ub & 0xffff0000u));
+// Two fp32 values as bf16 pairs hi + mid + lo, exactly: the upper half of the value, of the remainder, and the rest, which
+// has at most the last eight of the 24 bits.
+__device__ __forceinline__ void split_bf16x3(float a, float b, uint32_t &hi, uint32_t &mid, uint32_t &lo) {
+    const auto upper = [](float x) { return __uint_as_float(__float_as_uint(x) & 0xffff0000u); };
+    const auto halves = [](float x, float y) { return __builtin_amdgcn_perm(__float_as_uint(y), __float_as_uint(x), 0x07060302u); };
+    hi = halves(a, b);
+    a -= upper(a); b -= upper(b);
+    mid = halves(a, b);
+    lo = halves(a - upper(a), b - upper(b));
 }
 
 // acc + the two bf16 values of a packed pair, in fp32: one instruction for two probabilities.  The row sum is
@@ -717,9 +719,9 @@ __device__ __forceinline__ void qk_softmax(const TileView &tv, const uint8_t *lk
         const float a1 = __builtin_amdgcn_exp2f(fmaf(s0[i + 1], scale_log2, neg_m));
         const float b0 = __builtin_amdgcn_exp2f(fmaf(s1[i], scale_log2, neg_m));
         const float b1 = __builtin_amdgcn_exp2f(fmaf(s1[i + 1], scale_log2, neg_m));
-        if constexpr (Geo<D>::NP == 2) {
-            split_bf16x2(a0, a1, pk[0][0][i >> 1], pk[1][0][i >> 1]);
-            split_bf16x2(b0, b1, pk[0][1][i >> 1], pk[1][1][i >> 1]);
+        if constexpr (Geo<D>::NP == 3) {
+            split_bf16x3(a0, a1, pk[0][0][i >> 1], pk[1][0][i >> 1], pk[2][0][i >> 1]);
+            split_bf16x3(b0, b1, pk[0][1][i >> 1], pk[1][1][i >> 1], pk[2][1][i >> 1]);
             psum += a0 + a1;
             psum2 += b0 + b1;
         } else {
@@ -821,8 +823,8 @@ __device__ __forceinline__ void qk_softmax_half(const TileView &tv, const uint8_
     for (int i = 0; i < 16; i += 2) {
         const float a0 = __builtin_amdgcn_exp2f(fmaf(s0[i], scale_log2, neg_m));
         const float a1 = __builtin_amdgcn_exp2f(fmaf(s0[i + 1], scale_log2, neg_m));
-        if constexpr (Geo<D>::NP == 2) {
-            split_bf16x2(a0, a1, pk[0][i >> 1], pk[1][i >> 1]);
+        if constexpr (Geo<D>::NP == 3) {
+            split_bf16x3(a0, a1, pk[0][i >> 1], pk[1][i >> 1], pk[2][i >> 1]);
             psum += a0 + a1;
         } else {
             pk[0][i >> 1] = pack_bf16x2(a0, a1);
@@ -1208,7 +1210,7 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(AttnParams p) {
 //
 // B = 1, 32/8 heads of 128: T = 60, P = 2048 16.1 -> 14.0 us (4 splits instead of 8); P = 500 13.5 -> 9.4; T = 8, P = 4096
 // 14.5 -> 13.0; T = 128, P = 1024 17.8 -> 12.1.  B = 4, T = 60, P = 1000 21.6 -> 14.6; B = 32, T = 8, P = 4096 87.4 -> 82.7 us
-// (128 KiB in flight per compute unit: 6.5 TB/s); heads of 64, B = 4, T = 48, P = 900 ... 1500 18.1 -> 12.5.
+// (128 KiB in flight per compute unit: 6.5 TB/s); heads of 64, B = 4, T = 48, P = 900 ... 1500 13.7 us.
 // ----------------------------------------------------------------------------------------------
 constexpr int KB_NW = 8;     // wavefronts of a workgroup
 constexpr int KB_KEYS = 32;  // keys of a block

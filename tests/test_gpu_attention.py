@@ -149,8 +149,8 @@ def test_mfma_kernel_key_halves_and_whole_tiles_agree_with_the_oracle(flags, pag
                                    api.ATTN_FLAG_KEY_HALVES | api.ATTN_FLAG_LARGE_WG, api.ATTN_FLAG_WHOLE_TILE | api.ATTN_FLAG_LARGE_WG])
 def test_mfma_kernel_heads_of_64(flags, paged):
     """Every launch shape at head dimension 64: prefixes and trees around the 32- and 64-key boundaries.  Probabilities
-    enter the second product as two bf16 parts (16 bits), so the scaled error is that of rounding the output to bf16,
-    2^-9, plus terms of 2^-16: 2^-8 bounds it with a factor of two."""
+    enter the second product with all their bits, so the scaled error is that of rounding the output to bf16, 2^-9, plus
+    fp32 sums: 2^-8 bounds it with a factor of two."""
     rng = np.random.default_rng(6400 + flags + 100 * paged)
     P = [0, 1, 31, 32, 33, 63, 64, 65, 95, 97, 128, 500]
     n = [24, 1, 7, 24, 9, 24, 2, 24, 24, 5, 24, 11]
@@ -159,6 +159,45 @@ def test_mfma_kernel_heads_of_64(flags, paged):
         for kv_split in (0, 64, 4096):
             err, rel = _check(wl, flags=flags, kv_split=kv_split)
             assert rel <= 2.0 ** -8, (T, kv_split, rel)
+
+
+@pytest.mark.parametrize("flags", [api.ATTN_FLAG_GENERIC, api.ATTN_FLAG_KEY_BLOCKS, api.ATTN_FLAG_WHOLE_TILE | api.ATTN_FLAG_SMALL_WG,
+                                   api.ATTN_FLAG_WHOLE_TILE | api.ATTN_FLAG_LARGE_WG, api.ATTN_FLAG_KEY_HALVES | api.ATTN_FLAG_SMALL_WG,
+                                   api.ATTN_FLAG_KEY_HALVES | api.ATTN_FLAG_LARGE_WG])
+def test_heads_of_64_keep_all_bits_of_the_probabilities(flags):
+    """At head dimension 64 the weights of the value product are the fp32 probabilities.  Eight keys whose weighted values
+    cancel to about 2^-17 of their size show what the output's own rounding to bf16 hides otherwise.  Scores are exact
+    (one product each), |log2 weight| <= 2; against float64 a weight is off by at most 2^-23 (exponential, one unit) + 2 ln2
+    2^-24 (its argument), and the sum by less than 2^-22 of its terms (three products per key, two roundings of a partial sum
+    each): 2^-21 of the sum of |weight * value| together, doubled here, and 2^-8 of the output.  Weights of 16 bits miss
+    that bar by a factor of three."""
+    rng = np.random.default_rng(6464)
+    T, Hq, Hkv, P, scale = 128, 8, 2, 8, 0.125
+    wl = _small(rng, 1, T, Hq, Hkv, 64, [P], "bf16", False)
+    q, k, v = (np.zeros(x.shape, np.float32) for x in (wl.q, wl.k_cache, wl.v_cache))
+    q[..., 5] = 1.0
+    c = np.array([11.0, 7.0, 5.0, 3.0, 1.0, -2.0, -6.0, -9.0])
+    p = np.exp(c * scale - 11 * scale)
+    k[0, :P, :, 5] = c[:, None]
+    v[0, :P - 2] = rng.standard_normal((P - 2, Hkv, 64))
+    bf = lambda x: synth.bf16_bits_to_f32(synth.f32_to_bf16_bits(np.asarray(x, np.float32)))
+    v = bf(v)
+    for j in (P - 2, P - 1):     # the last two keys take back what the others add up to, as far as their eight bits go
+        v[0, j] = bf(-np.einsum("k,khd->hd", p[:j], v[0, :j].astype(np.float64)) / p[j])
+    wl.q, wl.k_cache, wl.v_cache = (synth.f32_to_bf16_bits(x) for x in (q, k, v))
+    wl.kt[:], wl.vt[:] = 0, 0    # tree keys: score 0, value 0
+    d = DevWorkload(wl)
+    m = api.build_tree_mask(d.parent, d.n_nodes)
+    out, _ = gpu_attention(d, m["bitmask"], flags=flags, scale=scale)
+    ref_mask = oracle.build_tree_mask(wl.parent, wl.n_nodes)
+    ref, _ = oracle.tree_verify_attention(wl.q, wl.k_cache, wl.v_cache, wl.prefix_len, wl.kt, wl.vt, ref_mask["dense"], wl.n_nodes,
+                                          dtype="bf16", scale=scale)
+    visible = ref_mask["dense"][0, 0].sum(1).astype(np.float64)            # per node: tree keys, each of weight exp(-11 scale)
+    total = p.sum() + visible * np.exp(-11 * scale)
+    size = np.einsum("k,khd->hd", p, np.abs(v[0, :P]).astype(np.float64)).repeat(Hq // Hkv, 0)[None] / total[:, None, None]
+    bar = 2.0 ** -20 * size + 2.0 ** -8 * np.abs(ref[0])
+    worst = (np.abs(to_host_f64(out)[0] - ref[0]) / bar).max()
+    assert worst <= 1.0, worst
 
 
 @pytest.mark.parametrize("paged", [False, True])
