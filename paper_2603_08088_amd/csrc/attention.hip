@@ -1811,6 +1811,11 @@ static size_t split_workspace(const etv_attn_desc *h, int ns) {
     return (size_t)h->B * h->Hq * h->T_max * ns * ((size_t)h->d + 2) * sizeof(float) + 1024;
 }
 
+// Splits that this file chooses by itself stay within the array of etv_tree_verify_attention_static, whose callers cannot
+// bring a workspace: fp32 and heads of 64 at any size, and the key-block kernel wherever the tile kernel's did.  (Tile kernel
+// at d = 128: a batch of many rows over a long prefix may be split beyond the array, as it always was.)
+static bool beyond_array(const etv_attn_desc *h, int ns) { return ns > 1 && split_workspace(h, ns) > ETV_ATTN_STATIC_WORKSPACE_BYTES; }
+
 // The next split count worth a look: with tps tiles per split now, the smallest count whose splits are shorter (the counts
 // between differ only in empty splits).  Some 2 * sqrt(tiles) candidates instead of all of them, on every call.
 static int next_split_count(int tiles, int tps) { return tps > 1 ? (tiles + tps - 2) / (tps - 1) : tiles + 1; }
@@ -1839,6 +1844,7 @@ static Plan make_plan(const etv_attn_desc *h) {
         double best = 1e30;
         for (int ns = forced_tps ? (tiles + forced_tps - 1) / forced_tps : 1, tps; ns <= tiles; ns = forced_tps ? tiles + 1 : next_split_count(tiles, tps)) {
             tps = forced_tps ? forced_tps : (tiles + ns - 1) / ns;
+            if (!forced_tps && beyond_array(h, ns)) break;
             const double per_wave = ceil((tps * 4.0 + (h->T_max + 15) / 16) / F32_NW);
             const double full = ceil((double)(units * ns) / 256.0);
             const double est = per_wave * (full * busy > chain ? full * busy : chain) + (ns > 1 ? 4.0 + ns * (part_us + 0.1) : 0.0);
@@ -1882,6 +1888,7 @@ static Plan make_plan(const etv_attn_desc *h) {
             const int forced_tps = h->kv_split > 0 ? min(tiles, (h->kv_split + KT - 1) / KT) : 0;
             for (int ns = forced_tps ? (tiles + forced_tps - 1) / forced_tps : 1, tps; ns <= tiles; ns = forced_tps ? tiles + 1 : next_split_count(tiles, tps)) {
                 tps = forced_tps ? forced_tps : (tiles + ns - 1) / ns;
+                if (!forced_tps && h->d == 64 && beyond_array(h, ns)) break;
                 const long wgs = units * ns;
                 const bool alone = (nw == 4 && wgs <= 256);
                 const double slots = nw == 8 ? 256.0 : 512.0;
@@ -1923,8 +1930,7 @@ static Plan make_plan(const etv_attn_desc *h) {
             const long wgs = units * ns;
             if (wgs > slots && !(blocks_only && (ns == 1 || forced_tps))) break;
             if (((long)B * ns * h->Hkv + 7) / 8 > 65535 || pl.pairs > 65535) break;  // grid dimensions
-            // splits of its own choice fit the library's array wherever the other kernel's did
-            if (!forced_tps && ns > 1 && split_workspace(h, ns) > ETV_ATTN_STATIC_WORKSPACE_BYTES) break;
+            if (!forced_tps && beyond_array(h, ns)) break;
             const int most = (2 * tps + tree_blocks + KB_NW - 1) / KB_NW, usual = (2 * tps + KB_NW - 1) / KB_NW;
             const double steps = ns > 1 ? 0.5 * (most + usual) : most;  // only the last split takes the tree
             const double t_step = d64 ? (wgs > 256 ? 2.0 : 1.1) : (pl.pairs == 1 ? 2.15 : 1.6);

@@ -110,3 +110,17 @@ def test_binding_refuses_what_is_not_a_device_tensor_or_a_descriptor():
     with pytest.raises(ctypes.ArgumentError):    # another struct
         api.tree_verify_attention(x, x, x, x, x, x, x, x, P_max=1, desc=api.CommitDesc(), out=x, lse=x, workspace=x)
     assert call.empty_i32(x, 3, 4).shape == (3, 4) and call.empty_i32(x, 2).dtype == torch.int32
+
+
+def test_unforced_fp32_and_heads_of_64_plans_fit_the_fixed_array():
+    """etv_tree_verify_attention_static cannot fall back on another workspace: a split that the library chooses by itself at
+    fp32 or heads of 64 stays within its array, at every size, so that no unforced call is refused.  (Host only: the plan.)"""
+    cases = [(64, api.BF16, 17, 60, 64, 8, 8192), (128, api.F32, 12, 60, 64, 8, 16384), (64, api.BF16, 8, 160, 64, 8, 4096),
+             (128, api.F32, 24, 60, 28, 4, 16384)]
+    cases += [(d, dt, B, T, Hq, Hkv, P) for d, dt in ((64, api.BF16), (64, api.F32), (128, api.F32)) for B in (1, 3, 17, 40, 65, 129)
+              for T in (1, 16, 60, 129, 256) for Hq, Hkv in ((4, 4), (32, 8), (64, 8), (28, 4), (257, 257)) for P in (0, 500, 8192, 100000)]
+    for d, dt, B, T, Hq, Hkv, P in cases:
+        dsc = api.AttnDesc(B=B, T_max=T, Hq=Hq, Hkv=Hkv, d=d, dtype=dt, P_cap=P, P_max=P)
+        need = api.tree_verify_attention_workspace_bytes(dsc)
+        assert need <= api.ATTN_STATIC_WORKSPACE_BYTES, (d, dt, B, T, Hq, Hkv, P, need)
+        assert api.tree_verify_attention_plan(dsc)["n_splits"] >= 1

@@ -13,10 +13,10 @@ from helpers import random_tree
 pytestmark = pytest.mark.gpu
 
 
-def _workload(seed, B, T, P, n_nodes, paged):
+def _workload(seed, B, T, P, n_nodes, paged, d=128, dtype="bf16"):
     rng = np.random.default_rng(seed)
     parents = [random_tree(rng, n_nodes[b]) for b in range(B)]
-    return synth.assemble("static_ws", rng, parents, P, Hq=8, Hkv=2, d=128, dtype="bf16", V=512, W=T, paged=paged,
+    return synth.assemble("static_ws", rng, parents, P, Hq=8, Hkv=2, d=d, dtype=dtype, V=512, W=T, paged=paged,
                           T_max=T, with_logits=False, spare_blocks=3)
 
 
@@ -49,6 +49,15 @@ def test_static_workspace_call_equals_the_workspace_call_twice_in_a_row():
     # and the library-chosen split of the first shape again
     need3, out3, lse3, ref_out3, ref_lse3 = _both(big, 0)
     assert torch.equal(out3, ref_out3) and torch.equal(lse3, ref_lse3)
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("f32", 64), ("f32", 128)])
+def test_static_workspace_call_equals_the_workspace_call_fp32_and_heads_of_64(dtype, d):
+    wl = _workload(4104, 3, 60, [2048, 700, 1], [60, 33, 1], True, d, dtype)
+    for kv_split in (64, 0):
+        need, out, lse, ref_out, ref_lse = _both(wl, kv_split)
+        assert need <= api.ATTN_STATIC_WORKSPACE_BYTES and (need > 256 or not kv_split)
+        assert torch.equal(out, ref_out) and torch.equal(lse, ref_lse)
 
 
 def test_static_workspace_call_refuses_shapes_beyond_its_array():
