@@ -628,6 +628,11 @@ struct TileView {
 // touch) becomes rare after the first tiles.
 constexpr float kLazy = 8.0f;
 
+// Can a row reach the exponentials of a tile without a finite score so far?  Where keys are masked, and at d = 64 also where
+// products overflow to -inf (such keys weigh nothing).
+template <int D, bool MASKED>
+constexpr bool kMayBeEmpty = MASKED || D == 64;
+
 // V^T fragments of 32 keys (key block kb) of the V tile at lv.
 template <int D>
 __device__ __forceinline__ void load_v_frags(const TileView &tv, const uint8_t *lv, int kb, bf16x8 (&vf)[2][Geo<D>::DB]) {
@@ -710,7 +715,7 @@ __device__ __forceinline__ void qk_softmax(const TileView &tv, const uint8_t *lk
 #pragma unroll
             for (int i = 0; i < 16; i++) oacc[db][i] *= alpha;
     }
-    const float neg_m = (MASKED && m_run == -INFINITY) ? 0.f : -m_run;
+    const float neg_m = (kMayBeEmpty<D, MASKED> && m_run == -INFINITY) ? 0.f : -m_run;
     float psum = 0.f, psum2 = 0.f;  // two chains
     uint32_t pk[Geo<D>::NP][2][8];
 #pragma unroll
@@ -816,7 +821,7 @@ __device__ __forceinline__ void qk_softmax_half(const TileView &tv, const uint8_
 #pragma unroll
             for (int i = 0; i < 16; i++) oacc[db][i] *= alpha;
     }
-    const float neg_m = (MASKED && m_run == -INFINITY) ? 0.f : -m_run;
+    const float neg_m = (kMayBeEmpty<D, MASKED> && m_run == -INFINITY) ? 0.f : -m_run;
     float psum = 0.f;
     uint32_t pk[Geo<D>::NP][8];
 #pragma unroll
@@ -1661,7 +1666,7 @@ __global__ void __launch_bounds__(F32_NW * 64, 2) attn_f32_kernel(AttnParams p) 
 #pragma unroll
                 for (int e = 0; e < 4; e++) o[v][e] *= alpha;
         }
-        const float ref = (masked && m_run == -INFINITY) ? 0.f : m_run;
+        const float ref = m_run == -INFINITY ? 0.f : m_run;  // no finite score so far: masked keys, or products that overflow
         float pr[4];
 #pragma unroll
         for (int i = 0; i < 4; i++) pr[i] = __builtin_amdgcn_exp2f(sc[i] - ref);

@@ -238,6 +238,26 @@ def test_row_maximum_uses_the_finished_scores(d, flags):
         _check(wl, flags=flags, kv_split=4096)
 
 
+# every kernel shape of bf16, and the one of fp32
+SHAPES = {"bf16": [0, api.ATTN_FLAG_KEY_BLOCKS, api.ATTN_FLAG_WHOLE_TILE | api.ATTN_FLAG_SMALL_WG, api.ATTN_FLAG_WHOLE_TILE | api.ATTN_FLAG_LARGE_WG,
+                   api.ATTN_FLAG_KEY_HALVES | api.ATTN_FLAG_SMALL_WG, api.ATTN_FLAG_KEY_HALVES | api.ATTN_FLAG_LARGE_WG], "f32": [0]}
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("f32", 64), ("f32", 128)])
+def test_tiles_whose_scores_overflow_to_minus_infinity_weigh_nothing(dtype, d):
+    """Products beyond the fp32 range: the keys of the first tiles score -inf for every row, and a row sees nothing finite
+    until later.  Such keys weigh nothing, as in the float64 oracle; tolerances as everywhere."""
+    rng = np.random.default_rng(8400 + d)
+    wl = _small(rng, 2, 70, 8, 2, d, [230, 150], dtype, False, n_nodes=[70, 33])
+    enc = synth.f32_to_bf16_bits if dtype == "bf16" else (lambda x: np.asarray(x, np.float32))
+    wl.q[..., 3] = enc(np.float32([1e38]))[0]
+    wl.k_cache[..., 3], wl.kt[..., 3] = 0, 0
+    wl.k_cache[:, :140, :, 3] = enc(np.float32([-1e38]))[0]
+    for flags in SHAPES[dtype] + [api.ATTN_FLAG_GENERIC]:
+        for kv_split in (0, 64, 4096):
+            _check(wl, flags=flags, kv_split=kv_split)
+
+
 def test_key_halves_merge_is_deterministic():
     """The merge of the two key halves has a fixed order: two launches on the same inputs give the same bits."""
     rng = np.random.default_rng(1800)
