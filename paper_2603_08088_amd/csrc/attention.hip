@@ -1658,7 +1658,7 @@ __global__ void __launch_bounds__(F32_NW * 64, 2) attn_f32_kernel(AttnParams p) 
         const bool lift = tmax > m_run + kLazy;
         if (__any(lift)) {
             const float m_new = lift ? tmax : m_run;
-            const float alpha = lift ? __builtin_amdgcn_exp2f(m_run - m_new) : 1.f;
+            const float alpha = lift ? exp2f(m_run - m_new) : 1.f;
             m_run = m_new;
             l_run *= alpha;
 #pragma unroll
@@ -1667,9 +1667,9 @@ __global__ void __launch_bounds__(F32_NW * 64, 2) attn_f32_kernel(AttnParams p) 
                 for (int e = 0; e < 4; e++) o[v][e] *= alpha;
         }
         const float ref = m_run == -INFINITY ? 0.f : m_run;  // no finite score so far: masked keys, or products that overflow
-        float pr[4];
+        float pr[4];  // exp2f, here and below: weights below the normal range stay (the bare instruction makes them zero)
 #pragma unroll
-        for (int i = 0; i < 4; i++) pr[i] = __builtin_amdgcn_exp2f(sc[i] - ref);
+        for (int i = 0; i < 4; i++) pr[i] = exp2f(sc[i] - ref);
         l_run += (pr[0] + pr[1]) + (pr[2] + pr[3]);
 #pragma unroll
         for (int i = 0; i < 4; i++)
@@ -1749,7 +1749,7 @@ __global__ void __launch_bounds__(F32_NW * 64, 2) attn_f32_kernel(AttnParams p) 
     for (int x = 0; x < F32_NW; x++) M = fmaxf(M, s_m[x][row]);
 #pragma unroll
     for (int x = 0; x < F32_NW; x++) {
-        w[x] = s_m[x][row] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(s_m[x][row] - M);
+        w[x] = s_m[x][row] == -INFINITY ? 0.f : exp2f(s_m[x][row] - M);
         L = fmaf(w[x], s_l[x][row], L);
     }
     const size_t pr = part_row(p, slot, h2, kq2);

@@ -258,6 +258,35 @@ def test_tiles_whose_scores_overflow_to_minus_infinity_weigh_nothing(dtype, d):
             _check(wl, flags=flags, kv_split=kv_split)
 
 
+@pytest.mark.parametrize("d", [64, 128])
+def test_fp32_weights_below_the_normal_range_stay(d):
+    """A key 126.2 ... 130.5 log2 units under its row's maximum weighs 2^-126.2 ... 2^-130.5: below the normal range, where fp32
+    keeps 18 to 22 bits, an error of at most 2^-19 (2e-6) of the weight.  With a value of 2^126 that key is all the output
+    there is.  At the front of the prefix, behind the maximum and in another split."""
+    rng = np.random.default_rng(8500 + d)
+    P, scale = 200, 0.0625
+    for low, high in ((0, 100), (100, 0), (3, 199), (199, 3)):
+        wl = _small(rng, 1, 17, 4, 2, d, [P], "f32", False)
+        wl.q[:], wl.k_cache[:], wl.v_cache[:], wl.kt[:], wl.vt[:] = 0, 0, 0, 0, 0
+        wl.q[..., 1] = 1.0
+        wl.k_cache[..., 1], wl.kt[..., 1] = -1e6, -1e6               # every other key weighs nothing
+        wl.k_cache[:, high, :, 1] = 0.0
+        gap = 126.2 + 4.3 * rng.random((1, 2)).astype(np.float32)
+        wl.k_cache[:, low, :, 1] = -gap * np.log(2.0) / scale
+        wl.v_cache[:, low] = 2.0 ** 126 * rng.uniform(0.5, 1.0, (1, 2, d))
+        dv = DevWorkload(wl)
+        m = api.build_tree_mask(dv.parent, dv.n_nodes)
+        dense = oracle.build_tree_mask(wl.parent, wl.n_nodes)["dense"]
+        ref, _ = oracle.tree_verify_attention(wl.q, wl.k_cache, wl.v_cache, wl.prefix_len, wl.kt, wl.vt, dense, wl.n_nodes,
+                                              dtype="f32", scale=scale)
+        assert np.abs(ref).min() > 0.01
+        for flags, kv_split in ((0, 0), (0, 64), (0, 4096), (api.ATTN_FLAG_GENERIC, 0)):
+            out, _ = gpu_attention(dv, m["bitmask"], flags=flags, kv_split=kv_split, scale=scale)
+            rel = (np.abs(to_host_f64(out) - ref) / np.abs(ref)).max()
+            # the argument (126 ... 131, fp32) is off by 2^-17 at most: 2^-17.5 of the weight; the score itself by as much
+            assert rel <= 2.0 ** -16, (low, high, flags, kv_split, rel)
+
+
 def test_key_halves_merge_is_deterministic():
     """The merge of the two key halves has a fixed order: two launches on the same inputs give the same bits."""
     rng = np.random.default_rng(1800)
