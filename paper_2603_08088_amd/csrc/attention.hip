@@ -193,6 +193,30 @@ __device__ __forceinline__ float dot_row(const float *sq, const T *row) {
     return acc;
 }
 
+// Values that are not finite, on the matrix-core kernels of fp32 and of heads of 64.  A key that a row does not see must not
+// reach it whatever its value, but 0 * inf and 0 * NaN in a product are NaN.  So where a tile with masked keys holds such a
+// value (rare, found with a few integer instructions per tile), the product runs with zeros in its place, and after the last
+// tile the wavefront goes through its masked keys once more for the columns that each of its rows has to add +inf, -inf or,
+// for NaN, both to.  (In a tile without masked keys every row sees every key.)
+// One group of keys base .. base + count - 1 of the tree or the prefix; `vis`: those that the lane's row sees.
+template <typename T, int D>
+__device__ __forceinline__ void find_nonfinite(const AttnParams &p, int b, int kvh, int P, bool tree, int base, int count, uint64_t vis,
+                                               uint64_t (&up)[D / 64], uint64_t (&down)[D / 64]) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll 1
+    for (int j = 0; j < count; j++) {
+        const T *row = tree && p.vt ? static_cast<const T *>(p.vt) + tree_row_offset(p, b, kvh, base + j)
+                                    : static_cast<const T *>(p.v_cache) + prefix_row_offset(p, b, kvh, (tree ? P : 0) + base + j);
+#pragma unroll
+        for (int c = 0; c < D / 64; c++) {
+            const float x = load_elem<T>(row, lane + 64 * c);
+            const bool bad = !(fabsf(x) < INFINITY);
+            const uint64_t u = __ballot(bad && x != -INFINITY), d = __ballot(bad && x != INFINITY);
+            if ((vis >> j) & 1ull) { up[c] |= u; down[c] |= d; }
+        }
+    }
+}
+
 // ----------------------------------------------------------------------------------------------
 // Generic kernel: grid (T_max, Hq, B * nsplit), one wavefront per (query row, head, split).
 // QK: lane = key (row dot product against q held in LDS); PV: lane = head-dim column, the weight of
@@ -651,6 +675,38 @@ __device__ __forceinline__ void load_v_frags(const TileView &tv, const uint8_t *
     }
 }
 
+// Heads of 64, masked keys: values that are not finite out of the fragments of 32 keys; true if there were any.
+__device__ __forceinline__ bool take_out_nonfinite(bf16x8 (&vf)[2][2]) {
+    const auto ill = [](uint32_t w) { return (w & 0x7f807f80u) + 0x00800080u; };  // bit 15 of a half: all ones in the exponent
+    uint32_t any = 0;
+#pragma unroll
+    for (int x = 0; x < 4; x++) {
+        const uint4 w = __builtin_bit_cast(uint4, vf[x >> 1][x & 1]);
+        any |= (ill(w.x) | ill(w.y)) | (ill(w.z) | ill(w.w));
+    }
+    if (__builtin_expect(!__any((any & 0x80008000u) != 0), 1)) return false;
+    const auto keep = [&](uint32_t w) { return w & ~(((ill(w) >> 15) & 0x00010001u) * 0xffffu); };
+#pragma unroll
+    for (int x = 0; x < 4; x++) {
+        uint4 w = __builtin_bit_cast(uint4, vf[x >> 1][x & 1]);
+        w = uint4{keep(w.x), keep(w.y), keep(w.z), keep(w.w)};
+        vf[x >> 1][x & 1] = __builtin_bit_cast(bf16x8, w);
+    }
+    return true;
+}
+
+// What find_nonfinite found for the lane's row, added to its outputs (columns 32 db + 8 (i / 4) + 4 hh + i % 4).
+__device__ __forceinline__ void add_nonfinite(f32x16 (&oacc)[2], uint64_t up, uint64_t down, int hh) {
+    up >>= 4 * hh; down >>= 4 * hh;
+#pragma unroll
+    for (int db = 0; db < 2; db++)
+#pragma unroll
+        for (int i = 0; i < 16; i++) {
+            const int bit = 32 * db + 8 * (i >> 2) + (i & 3);
+            oacc[db][i] += ((up >> bit) & 1ull ? INFINITY : 0.f) + ((down >> bit) & 1ull ? -INFINITY : 0.f);
+        }
+}
+
 // The B operands of a PV product over 32 keys from the packed probabilities of a lane.
 __device__ __forceinline__ void pack_frags(const uint32_t (&pk)[8], bf16x8 (&pf)[2]) {
     const uint4 l = {pk[0], pk[1], pk[2], pk[3]}, h = {pk[4], pk[5], pk[6], pk[7]};
@@ -743,10 +799,11 @@ __device__ __forceinline__ void qk_softmax(const TileView &tv, const uint8_t *lk
     l_run += psum + psum2;
 }
 
-// Second half: O^T += V^T P^T over the 64 keys of the V tile at lv; D / 32 independent accumulator chains.
+// Second half: O^T += V^T P^T over the 64 keys of the V tile at lv; D / 32 independent accumulator chains.  `ill` is set
+// where a tile with masked keys holds values that are not finite.
 template <int D>
 __device__ __forceinline__ void pv_accumulate(const TileView &tv, const uint8_t *lv, const bf16x8 (&pf)[Geo<D>::NP][2][2],
-                                              f32x16 (&oacc)[Geo<D>::DB]) {
+                                              f32x16 (&oacc)[Geo<D>::DB], bool masked, bool &ill) {
     constexpr int DB = Geo<D>::DB;
     bf16x8 vf[2][DB];
     load_v_frags<D>(tv, lv, 0, vf);
@@ -758,6 +815,8 @@ __device__ __forceinline__ void pv_accumulate(const TileView &tv, const uint8_t 
 #pragma unroll
             for (int db = 0; db < DB; db++) va[st][db] = vf[st][db];
         if (kb == 0) load_v_frags<D>(tv, lv, 1, vf);  // the second half's fragments fly during the first half's products
+        if constexpr (D == 64)
+            if (masked && take_out_nonfinite(va)) ill = true;
 #pragma unroll
         for (int st = 0; st < 2; st++)
 #pragma unroll
@@ -843,9 +902,11 @@ __device__ __forceinline__ void qk_softmax_half(const TileView &tv, const uint8_
 
 template <int D>
 __device__ __forceinline__ void pv_accumulate_half(const TileView &tv, const uint8_t *lv, int kb, const bf16x8 (&pf)[Geo<D>::NP][2],
-                                                   f32x16 (&oacc)[Geo<D>::DB]) {
+                                                   f32x16 (&oacc)[Geo<D>::DB], bool masked, bool &ill) {
     bf16x8 vf[2][Geo<D>::DB];
     load_v_frags<D>(tv, lv, kb, vf);
+    if constexpr (D == 64)
+        if (masked && take_out_nonfinite(vf)) ill = true;
 #pragma unroll
     for (int st = 0; st < 2; st++)
 #pragma unroll
@@ -1085,10 +1146,11 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(AttnParams p) {
             else qk_softmax<D, false>(tv, lk, qreg, oacc, m_run, l_run, p.scale_log2, ~0ull, pf);
         }
     };
-    auto part_pv = [&](int t) {
+    bool ill = false;
+    auto part_pv = [&](int t, bool masked) {
         const uint8_t *lv = smem + (t % NS) * STAGE_BYTES + TILE_BYTES;
-        if (KH) pv_accumulate_half<D>(tv, lv, kb, pfh, oacc);
-        else pv_accumulate<D>(tv, lv, pf, oacc);
+        if (KH) pv_accumulate_half<D>(tv, lv, kb, pfh, oacc, masked, ill);
+        else pv_accumulate<D>(tv, lv, pf, oacc, masked, ill);
     };
     int ti = 0;
     if (!kShifted || wave < 4) {
@@ -1097,29 +1159,41 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(AttnParams p) {
             ring_step(ti);
             if (!wactive) continue;
             part_qk(ti, false);
-            part_pv(ti);
+            part_pv(ti, false);
         }
         for (; ti < nt; ti++) {     // ragged last prefix tile and tree tiles
             ring_step(ti);
             if (!wactive) continue;
             part_qk(ti, true);
-            part_pv(ti);
+            part_pv(ti, true);
         }
     } else {
         // one phase behind: PV(t-1), QK(t), softmax(t) within ring step t; the last PV after the loop
         for (; ti < nfull; ti++) {
             ring_step(ti);
             if (!wactive) continue;
-            if (ti > 0) part_pv(ti - 1);
+            if (ti > 0) part_pv(ti - 1, false);
             part_qk(ti, false);
         }
         for (; ti < nt; ti++) {
             ring_step(ti);
             if (!wactive) continue;
-            if (ti > 0) part_pv(ti - 1);
+            if (ti > 0) part_pv(ti - 1, ti > nfull);
             part_qk(ti, true);
         }
-        if (nt > 0 && wactive) part_pv(nt - 1);
+        if (nt > 0 && wactive) part_pv(nt - 1, nt > nfull);
+    }
+    if constexpr (D == 64) {
+        if (ill) {
+            uint64_t up[1] = {0}, down[1] = {0};
+            for (int t = nfull; t < nt; t++) {
+                const bool tree = t >= npt;
+                const int base = tree ? (t - npt) * KT : k0 + t * KT, count = min(KT, (tree ? n : k1) - base);
+                const uint64_t own = KH ? 0xffffffffull << (32 * kb) : ~0ull;  // the keys that this wavefront takes
+                find_nonfinite<uint16_t, D>(p, b, kvh, P, tree, base, count, rv ? tile_vis(t) & own : 0, up, down);
+            }
+            add_nonfinite(oacc, up[0], down[0], hh);
+        }
     }
 
     if (KH) {
@@ -1384,6 +1458,11 @@ __global__ void __launch_bounds__(KB_NW * 64, D == 64 ? 4 : 2) attn_blocks_kerne
     for (int db = 0; db < DB; db++)
 #pragma unroll
         for (int i = 0; i < 16; i++) oacc[db][i] = 0.f;
+    auto block_vis = [&](int x) -> uint32_t {  // keys of block x >= nfull that the lane's row sees
+        if (x >= npb) return *reinterpret_cast<const uint32_t *>(smem + G_::BITS_AT + ((x - npb) >> 1) * 256 + c32 * 8 + ((x - npb) & 1) * 4);
+        return (1u << (k1 - k0 - x * KB_KEYS)) - 1u;  // ragged last prefix block: 1..31 keys
+    };
+    bool ill = false;
     if (t < nt) {
         bf16x8 qreg[KK];
         const uint8_t *lq = smem + G_::Q_AT + c32 * ROW_BYTES;
@@ -1400,9 +1479,7 @@ __global__ void __launch_bounds__(KB_NW * 64, D == 64 ? 4 : 2) attn_blocks_kerne
             asm volatile("" ::: "memory");
             bf16x8 pf[Geo<D>::NP][2];
             // one copy of the code for masked and unmasked blocks: a launch this short pays for every instruction it fetches
-            uint32_t vis = ~0u;
-            if (t >= npb) vis = *reinterpret_cast<const uint32_t *>(smem + G_::BITS_AT + ((t - npb) >> 1) * 256 + c32 * 8 + ((t - npb) & 1) * 4);
-            else if (t >= nfull) vis = (1u << (k1 - k0 - t * KB_KEYS)) - 1u;  // ragged last prefix block: 1..31 keys
+            const uint32_t vis = t >= nfull ? block_vis(t) : ~0u;
             qk_softmax_half<D, true>(tv, lk, 0, qreg, oacc, m_run, l_run, p.scale_log2, vis, pf, t >= nfull);
             wait_lds_reads();
             size_t b0 = 0, b1 = 0;
@@ -1416,10 +1493,22 @@ __global__ void __launch_bounds__(KB_NW * 64, D == 64 ? 4 : 2) attn_blocks_kerne
             if (tn < nt) wait_vmcnt<U>();  // V of block t (K of the next one may still be on its way)
             else wait_vmcnt<0>();
             asm volatile("" ::: "memory");
-            pv_accumulate_half<D>(tv, lv, 0, pf, oacc);
+            pv_accumulate_half<D>(tv, lv, 0, pf, oacc, t >= nfull, ill);
             wait_lds_reads();
             if (tn < nfull) issue_full(vc, vbuf, true, b0, b1);
             else if (tn < nt) issue_edge(tn, vc, p.vt, vbuf, true);
+        }
+    }
+
+    if constexpr (D == 64) {
+        if (ill) {
+            uint64_t up[1] = {0}, down[1] = {0};
+            for (int x = nfull + ((wave - nfull) & (KB_NW - 1)); x < nt; x += KB_NW) {  // the masked ones of the wavefront's blocks
+                const bool tree = x >= npb;
+                const int base = tree ? (x - npb) * KB_KEYS : k0 + x * KB_KEYS, count = min(KB_KEYS, (tree ? n : k1) - base);
+                find_nonfinite<uint16_t, D>(p, b, kvh, P, tree, base, count, block_vis(x), up, down);
+            }
+            add_nonfinite(oacc, up[0], down[0], hh);
         }
     }
 
@@ -1636,7 +1725,8 @@ __global__ void __launch_bounds__(F32_NW * 64, 2) attn_f32_kernel(AttnParams p) 
 
     // Q . K of the tile in buffer `buf`, online softmax, P . V with the V rows already requested.  vis: keys that the
     // lane's row sees.
-    auto tile = [&](int buf, const f32x4 (&vf)[4][VB], uint32_t vis, bool masked) {
+    bool ill = false;
+    auto tile = [&](int buf, f32x4 (&vf)[4][VB], uint32_t vis, bool masked) {
         const uint8_t *krow = kbuf + buf * TILE + c * ROWB;
         f32x4 kf[KJ], s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;  // two chains
 #pragma unroll
@@ -1671,6 +1761,24 @@ __global__ void __launch_bounds__(F32_NW * 64, 2) attn_f32_kernel(AttnParams p) 
 #pragma unroll
         for (int i = 0; i < 4; i++) pr[i] = exp2f(sc[i] - ref);
         l_run += (pr[0] + pr[1]) + (pr[2] + pr[3]);
+        if (masked) {
+            uint32_t top = 0;
+#pragma unroll
+            for (int i = 0; i < 4; i++)
+#pragma unroll
+                for (int v = 0; v < VB; v++)
+#pragma unroll
+                    for (int e = 0; e < 4; e++) top = max(top, __float_as_uint(vf[i][v][e]) & 0x7fffffffu);
+            if (__builtin_expect(__any(top >= 0x7f800000u), 0)) {
+                ill = true;
+#pragma unroll
+                for (int i = 0; i < 4; i++)
+#pragma unroll
+                    for (int v = 0; v < VB; v++)
+#pragma unroll
+                        for (int e = 0; e < 4; e++) vf[i][v][e] = fabsf(vf[i][v][e]) < INFINITY ? vf[i][v][e] : 0.f;
+            }
+        }
 #pragma unroll
         for (int i = 0; i < 4; i++)
 #pragma unroll
@@ -1678,6 +1786,11 @@ __global__ void __launch_bounds__(F32_NW * 64, 2) attn_f32_kernel(AttnParams p) 
 #pragma unroll
                 for (int e = 0; e < 4; e++)
                     o[v][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[i][v][e], pr[i], o[v][e], 0, 0, 0);
+    };
+    auto tile_vis = [&](int x) -> uint32_t {  // keys of tile x >= nfull that the lane's row sees
+        if (x < npt) return (1u << (k1 - k0 - x * 16)) - 1u;  // ragged last prefix tile: 1..15 keys
+        const int j0 = (x - npt) * 16;
+        return rv ? (uint32_t)(mrow[j0 >> 6] >> (j0 & 63)) & 0xffffu : 0u;
     };
     // A K tile is in LDS when its turn comes: the first one is waited for at the top, a later one is older than the V rows
     // that the previous products have used.  The next K tile is requested before this tile's V rows for that reason.
@@ -1711,14 +1824,24 @@ __global__ void __launch_bounds__(F32_NW * 64, 2) attn_f32_kernel(AttnParams p) 
 #pragma unroll
             for (int v = 0; v < VB; v++) vf[i][v] = *reinterpret_cast<const f32x4 *>(row + 256 * v);
         }
-        uint32_t vis;
-        if (t >= npt) {
-            const int j0 = (t - npt) * 16;
-            vis = rv ? (uint32_t)(mrow[j0 >> 6] >> (j0 & 63)) & 0xffffu : 0u;
-        } else {
-            vis = (1u << (k1 - k0 - t * 16)) - 1u;  // ragged last prefix tile: 1..15 keys
+        tile(buf, vf, tile_vis(t), true);
+    }
+    if (ill) {
+        uint64_t up[VB] = {}, down[VB] = {};
+        for (int x = nfull + ((wave - nfull) & (F32_NW - 1)); x < nt; x += F32_NW) {  // the masked ones of the wavefront's tiles
+            const bool tree = x >= npt;
+            const int base = tree ? (x - npt) * 16 : k0 + x * 16, count = min(16, (tree ? n : k1) - base);
+            find_nonfinite<float, D>(p, b, kvh, P, tree, base, count, tile_vis(x), up, down);
         }
-        tile(buf, vf, vis, true);
+#pragma unroll
+        for (int v = 0; v < VB; v++)
+#pragma unroll
+            for (int e = 0; e < 4; e++)
+#pragma unroll
+                for (int i = 0; i < 4; i++) {  // column 64 v + 16 g + 4 i + e
+                    const int bit = 16 * g + 4 * i + e;
+                    o[v][e][i] += ((up[v] >> bit) & 1ull ? INFINITY : 0.f) + ((down[v] >> bit) & 1ull ? -INFINITY : 0.f);
+                }
     }
 
     // ---- merge the four wavefronts

@@ -287,6 +287,88 @@ def test_fp32_weights_below_the_normal_range_stay(d):
             assert rel <= 2.0 ** -16, (low, high, flags, kv_split, rel)
 
 
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("f32", 64), ("f32", 128)])
+def test_values_that_are_not_finite_reach_only_the_rows_that_see_them(dtype, d, paged):
+    """Infinities and NaN in the K and V rows of some tree nodes (a draft branch that overflowed): a node that has none of them
+    among its ancestors gets the very result it gets without them, and one that has gets what the float64 oracle gives,
+    infinities by sign and NaN."""
+    rng = np.random.default_rng(8600 + d + paged)
+    T, Hq, Hkv = 100, 8, 2
+    wl = _small(rng, 2, T, Hq, Hkv, d, [85, 64], dtype, paged, n_nodes=[100, 37])
+    clean = DevWorkload(wl)
+    bits = {"bf16": (0x7f80, 0xff80, 0x7fc0), "f32": (0x7f800000, 0xff800000, 0x7fc00000)}[dtype]
+    as_bits = (lambda x: x) if dtype == "bf16" else (lambda x: x.view(np.uint32))
+    ill = ((0, 99, 2, 0), (0, 60, 5, 1), (0, 61, 5, 0), (0, 70, d - 1, 2), (0, 33, 40, 0), (1, 36, 0, 2), (1, 20, 7, 1))
+    for b, node, col, kind in ill:       # node 99 and node 36 are the last ones, whose rows stand in for those behind them
+        as_bits(wl.vt)[b, node, :, col] = bits[kind]
+    as_bits(wl.kt)[0, 70, :, 3] = bits[2]
+    d2 = DevWorkload(wl)
+    m = api.build_tree_mask(clean.parent, clean.n_nodes)
+    dense = oracle.build_tree_mask(wl.parent, wl.n_nodes)["dense"]
+    with np.errstate(invalid="ignore"):
+        ref, _ = oracle.tree_verify_attention(wl.q, wl.k_cache, wl.v_cache, wl.prefix_len, wl.kt, wl.vt, dense, wl.n_nodes, dtype=dtype,
+                                              block_table=wl.block_table)
+    for flags in SHAPES[dtype] + [api.ATTN_FLAG_GENERIC]:
+        for kv_split in (0, 64):
+            out0, lse0 = gpu_attention(clean, m["bitmask"], flags=flags, kv_split=kv_split)
+            out1, lse1 = gpu_attention(d2, m["bitmask"], flags=flags, kv_split=kv_split)
+            torch.cuda.synchronize()
+            g = to_host_f64(out1)
+            for b, n in enumerate((100, 37)):
+                sees = np.array([[dense[b, 0, k, x] for bb, x, _, _ in ill if bb == b] for k in range(n)]).any(1)
+                assert 0 < sees.sum() < n
+                rows = torch.from_numpy(np.flatnonzero(~sees)).cuda()
+                assert torch.equal(out0[b, rows], out1[b, rows]) and torch.equal(lse0[b][:, rows], lse1[b][:, rows]), (flags, kv_split, b)
+                for k in np.flatnonzero(sees):
+                    if b == 0 and dense[0, 0, k, 70]:       # the NaN key: everything the row holds
+                        assert np.isnan(g[b, k]).all()
+                        continue
+                    for kind in (np.isnan, np.isposinf, np.isneginf):
+                        assert np.array_equal(kind(g[b, k]), kind(ref[b, k])), (flags, kv_split, b, k)
+
+
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("f32", 64), ("f32", 128)])
+def test_values_that_are_not_finite_reach_only_the_rows_that_see_them(dtype, d, paged):
+    """Infinities and NaN in the K and V rows of some tree nodes (a draft branch that overflowed): a node that has none of them
+    among its ancestors gets the very result it gets without them, and one that has gets what the float64 oracle gives,
+    infinities by sign and NaN."""
+    rng = np.random.default_rng(8600 + d + paged)
+    T, Hq, Hkv = 100, 8, 2
+    wl = _small(rng, 2, T, Hq, Hkv, d, [85, 64], dtype, paged, n_nodes=[100, 37])
+    clean = DevWorkload(wl)
+    bits = {"bf16": (0x7f80, 0xff80, 0x7fc0), "f32": (0x7f800000, 0xff800000, 0x7fc00000)}[dtype]
+    as_bits = (lambda x: x) if dtype == "bf16" else (lambda x: x.view(np.uint32))
+    ill = ((0, 99, 2, 0), (0, 60, 5, 1), (0, 61, 5, 0), (0, 70, d - 1, 2), (0, 33, 40, 0), (1, 36, 0, 2), (1, 20, 7, 1))
+    for b, node, col, kind in ill:       # node 99 and node 36 are the last ones, whose rows stand in for those behind them
+        as_bits(wl.vt)[b, node, :, col] = bits[kind]
+    as_bits(wl.kt)[0, 70, :, 3] = bits[2]
+    d2 = DevWorkload(wl)
+    m = api.build_tree_mask(clean.parent, clean.n_nodes)
+    dense = oracle.build_tree_mask(wl.parent, wl.n_nodes)["dense"]
+    with np.errstate(invalid="ignore"):
+        ref, _ = oracle.tree_verify_attention(wl.q, wl.k_cache, wl.v_cache, wl.prefix_len, wl.kt, wl.vt, dense, wl.n_nodes, dtype=dtype,
+                                              block_table=wl.block_table)
+    for flags in SHAPES[dtype] + [api.ATTN_FLAG_GENERIC]:
+        for kv_split in (0, 64):
+            out0, lse0 = gpu_attention(clean, m["bitmask"], flags=flags, kv_split=kv_split)
+            out1, lse1 = gpu_attention(d2, m["bitmask"], flags=flags, kv_split=kv_split)
+            torch.cuda.synchronize()
+            g = to_host_f64(out1)
+            for b, n in enumerate((100, 37)):
+                sees = np.array([[dense[b, 0, k, x] for bb, x, _, _ in ill if bb == b] for k in range(n)]).any(1)
+                assert 0 < sees.sum() < n
+                rows = torch.from_numpy(np.flatnonzero(~sees)).cuda()
+                assert torch.equal(out0[b, rows], out1[b, rows]) and torch.equal(lse0[b][:, rows], lse1[b][:, rows]), (flags, kv_split, b)
+                for k in np.flatnonzero(sees):
+                    if b == 0 and dense[0, 0, k, 70]:       # the NaN key: everything the row holds
+                        assert np.isnan(g[b, k]).all()
+                        continue
+                    for kind in (np.isnan, np.isposinf, np.isneginf):
+                        assert np.array_equal(kind(g[b, k]), kind(ref[b, k])), (flags, kv_split, b, k)
+
+
 def test_key_halves_merge_is_deterministic():
     """The merge of the two key halves has a fixed order: two launches on the same inputs give the same bits."""
     rng = np.random.default_rng(1800)
