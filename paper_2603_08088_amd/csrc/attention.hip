@@ -34,6 +34,7 @@ struct AttnParams {
     int pairs;   // mfma kernel: 32-row chunks of the packed query rows of a KV head
     int wgp;     // mfma kernel: workgroups per (b, kv head, split) = ceil(pairs / 4)
     float scale_log2;
+    uint32_t q_sign;  // mfma kernel: sign bits to flip in a pair of Q values, so that scale_log2 is never negative there
     // mfma kernel, batches of 2 .. 64 sequences with splits: the B * nsplit split slots are shared out among the
     // sequences by their lengths (on the device, where the lengths are), slot-major partials
     //   part_o [B * nsplit][Hq][T_max][d]; split_tab[b] = (first slot, splits in use) for the combine kernel
@@ -498,6 +499,15 @@ __device__ __forceinline__ float pair_sum(uint32_t packed, float acc) {
                                            acc, false);
 }
 
+template <int N>
+__device__ __forceinline__ void flip_signs(bf16x8 (&x)[N], uint32_t sign) {
+#pragma unroll
+    for (int i = 0; i < N; i++) {
+        const uint4 w = __builtin_bit_cast(uint4, x[i]);
+        x[i] = __builtin_bit_cast(bf16x8, uint4{w.x ^ sign, w.y ^ sign, w.z ^ sign, w.w ^ sign});
+    }
+}
+
 // 16 bytes per lane from global memory straight into LDS at (lds_addr + 16 * lane); asynchronous.
 __device__ __forceinline__ void async_load16(const void *gptr, uint32_t lds_addr) {
     // lds_addr is the same in every lane; readfirstlane says so to the compiler whatever it concluded about the loop
@@ -958,7 +968,7 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(AttnParams p) {
     static_assert(PD >= 1 && PD <= 3, "ring depth");
     asm volatile("" ::"s"(p.q), "s"(p.k_cache), "s"(p.v_cache), "s"(p.kt), "s"(p.vt), "s"(p.block_table),
                  "s"(p.prefix_len), "s"(p.n_nodes), "s"(p.bitmask), "s"(p.T_max), "s"(p.Hq), "s"(p.G),
-                 "s"(p.max_blocks), "s"(p.P_cap), "s"(p.P_max), "s"(p.words), "s"(p.chunk), "s"(p.pairs));
+                 "s"(p.max_blocks), "s"(p.P_cap), "s"(p.P_max), "s"(p.words), "s"(p.chunk), "s"(p.pairs), "s"(p.q_sign));
     int n_raw, P_raw;
     if (p.balanced) {
         n_raw = share.n_raw; P_raw = share.P_raw;
@@ -1088,6 +1098,7 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(AttnParams p) {
         if (rv) v = *reinterpret_cast<const uint4 *>(qp + (((size_t)b * p.T_max + kq) * p.Hq + h) * D + 16 * kk + 8 * hh);
         qreg[kk] = __builtin_bit_cast(bf16x8, v);
     }
+    if (p.q_sign) flip_signs(qreg, p.q_sign);
 
     f32x16 oacc[DB];
     float m_run = -INFINITY, l_run = 0.f;
@@ -1458,9 +1469,11 @@ __global__ void __launch_bounds__(KB_NW * 64, D == 64 ? 4 : 2) attn_blocks_kerne
     for (int db = 0; db < DB; db++)
 #pragma unroll
         for (int i = 0; i < 16; i++) oacc[db][i] = 0.f;
-    auto block_vis = [&](int x) -> uint32_t {  // keys of block x >= nfull that the lane's row sees
-        if (x >= npb) return *reinterpret_cast<const uint32_t *>(smem + G_::BITS_AT + ((x - npb) >> 1) * 256 + c32 * 8 + ((x - npb) & 1) * 4);
-        return (1u << (k1 - k0 - x * KB_KEYS)) - 1u;  // ragged last prefix block: 1..31 keys
+    auto block_vis = [&](int x) {  // keys of block x that the lane's row sees
+        uint32_t vis = ~0u;
+        if (x >= npb) vis = *reinterpret_cast<const uint32_t *>(smem + G_::BITS_AT + ((x - npb) >> 1) * 256 + c32 * 8 + ((x - npb) & 1) * 4);
+        else if (x >= nfull) vis = (1u << (k1 - k0 - x * KB_KEYS)) - 1u;  // ragged last prefix block: 1..31 keys
+        return vis;
     };
     bool ill = false;
     if (t < nt) {
@@ -1479,7 +1492,7 @@ __global__ void __launch_bounds__(KB_NW * 64, D == 64 ? 4 : 2) attn_blocks_kerne
             asm volatile("" ::: "memory");
             bf16x8 pf[Geo<D>::NP][2];
             // one copy of the code for masked and unmasked blocks: a launch this short pays for every instruction it fetches
-            const uint32_t vis = t >= nfull ? block_vis(t) : ~0u;
+            const uint32_t vis = block_vis(t);
             qk_softmax_half<D, true>(tv, lk, 0, qreg, oacc, m_run, l_run, p.scale_log2, vis, pf, t >= nfull);
             wait_lds_reads();
             size_t b0 = 0, b1 = 0;
@@ -2001,7 +2014,8 @@ static Plan make_plan(const etv_attn_desc *h) {
     pl.pairs = ((h->Hq / h->Hkv) * h->T_max + 31) / 32;  // 32-row chunks of the G * T_max packed rows of a KV head
     const double part_us = 2.0 * B * h->Hq * h->T_max * (h->d + 2.0) * 4.0 / 3.0e6;
     double best = 1e30, best_lat = 0.0;
-    const bool blocks_only = (h->flags & ETV_ATTN_FLAG_KEY_BLOCKS) != 0;
+    // negative scales are the tile kernel's: turning Q round costs a launch of 14 us 0.1 us, and only there it disappears
+    const bool tiles_only = h->scale < 0.f, blocks_only = (h->flags & ETV_ATTN_FLAG_KEY_BLOCKS) != 0 && !tiles_only;
     for (int nw = 4; nw <= 8 && !blocks_only; nw += 4) {
         for (int kh = 0; kh <= 1; kh++) {
             const int cw = kh ? nw / 2 : nw;  // chunks per workgroup
@@ -2035,7 +2049,7 @@ static Plan make_plan(const etv_attn_desc *h) {
         }
     }
     constexpr int kShapeFlags = ETV_ATTN_FLAG_SMALL_WG | ETV_ATTN_FLAG_LARGE_WG | ETV_ATTN_FLAG_WHOLE_TILE | ETV_ATTN_FLAG_KEY_HALVES;
-    if (blocks_only || !(h->flags & kShapeFlags)) {
+    if (blocks_only || !(tiles_only || (h->flags & kShapeFlags))) {
         // Key-block kernel against the pick so far, for launches that fit the chip at once (one workgroup per compute unit, two
         // at d = 64): a further round pays start-up and merge again, and the other kernel is then always ahead.  Microseconds,
         // fitted to 128 workloads (B = 1 ... 32, T = 1 ... 250, P = 48 ... 30310, both head sizes; for 38 of them every split
@@ -2197,6 +2211,10 @@ static int32_t attention_run(const etv_attn_desc *h, const void *q, const void *
     if (p.pairs > 0) p.inv_pairs = fast_div_inv(p.pairs);
     const float scale = (h->scale == 0.f) ? 1.0f / sqrtf((float)h->d) : h->scale;
     p.scale_log2 = scale * 1.4426950408889634f;
+    if (pl.mfma && p.scale_log2 < 0.f) {  // a row's maximum is taken before it is scaled
+        p.scale_log2 = -p.scale_log2;
+        p.q_sign = 0x80008000u;
+    }
     if (pl.nsplit > 1) {
         size_t rows = (size_t)h->B * h->Hq * h->T_max * pl.nsplit;
         p.part_o = static_cast<float *>(workspace);

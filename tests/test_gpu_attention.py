@@ -369,6 +369,30 @@ def test_values_that_are_not_finite_reach_only_the_rows_that_see_them(dtype, d, 
                         assert np.array_equal(kind(g[b, k]), kind(ref[b, k])), (flags, kv_split, b, k)
 
 
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("bf16", 128), ("f32", 64), ("f32", 128)])
+def test_negative_scales(dtype, d):
+    """A negative scale turns the order of the scores round: the reference of a row is its smallest product.  Scores spread
+    over some 500 log2 units, so that any other reference overflows; tolerances as everywhere."""
+    rng = np.random.default_rng(8700 + d)
+    wl = _small(rng, 2, 70, 8, 2, d, [230, 150], dtype, True, n_nodes=[70, 33], q_scale=4.0)
+    dv = DevWorkload(wl)
+    m = api.build_tree_mask(dv.parent, dv.n_nodes)
+    dense = oracle.build_tree_mask(wl.parent, wl.n_nodes)["dense"]
+    for scale in (-1.0, -0.125):
+        ref, ref_lse = oracle.tree_verify_attention(wl.q, wl.k_cache, wl.v_cache, wl.prefix_len, wl.kt, wl.vt, dense, wl.n_nodes, dtype=dtype,
+                                                    block_table=wl.block_table, scale=scale)
+        for flags in SHAPES[dtype] + [api.ATTN_FLAG_GENERIC]:
+            for kv_split in (0, 64):
+                out, lse = gpu_attention(dv, m["bitmask"], flags=flags, kv_split=kv_split, scale=scale)
+                err, rel, _ = attention_errors(out, ref, wl.n_nodes)
+                # fp32: a score of up to 250 is a sum of d products, each addition off by up to 2^-24 of it, which is the relative error
+                # of a weight: at most d * 250 * 2^-24 (2e-3 at d = 128; rounding errors cancel for the most part)
+                assert rel <= (d * 250 * 2.0 ** -24 if dtype == "f32" else REL_TOL[dtype]), (flags, kv_split, scale, rel)
+                g = to_host_f64(lse)
+                for b, n in enumerate((70, 33)):
+                    assert np.abs(g[b, :, :n] - ref_lse[b, :, :n]).max() <= (d * 250 * 2.0 ** -24 if dtype == "f32" else 2e-2)
+
+
 def test_key_halves_merge_is_deterministic():
     """The merge of the two key halves has a fixed order: two launches on the same inputs give the same bits."""
     rng = np.random.default_rng(1800)
