@@ -2,7 +2,8 @@
 // marshalling a dozen tensors through Python (three attribute calls per tensor, a stream object, ctypes conversions) took
 // 9 us per attention call: longer than the kernel.  Here one template turns the arguments into those of the C prototype in
 // eagletv.h: a pointer parameter takes a device-resident contiguous tensor or None, a descriptor any object with the buffer
-// of that struct, an integer an int; the trailing stream is the current one.  The GIL is released around the call.
+// of that struct, an integer an int or what has __index__ (numpy's integers, tensors of one); the trailing stream is the
+// current one.  The GIL is released around the call.
 #include <Python.h>
 
 #include <ATen/ATen.h>
@@ -26,11 +27,13 @@ constexpr bool is_desc = std::is_same_v<T, const etv_attn_desc *> || std::is_sam
 template <class T>
 T arg(PyObject *o) {
     if constexpr (std::is_integral_v<T>) {
-        if (!PyLong_Check(o)) {
+        if (!PyIndex_Check(o)) {
             PyErr_Format(PyExc_TypeError, "int expected instead of %s", Py_TYPE(o)->tp_name);
             throw Refused{};
         }
-        return static_cast<T>(PyLong_AsUnsignedLongLongMask(o));
+        const unsigned long long v = PyLong_AsUnsignedLongLongMask(o);  // takes ints and what has __index__
+        if (v == ~0ull && PyErr_Occurred()) throw Refused{};
+        return static_cast<T>(v);
     } else if constexpr (is_desc<T>) {
         // the caller's reference keeps the object, and with it the memory of a ctypes structure, for the whole call
         Py_buffer view;

@@ -112,6 +112,24 @@ def test_binding_refuses_what_is_not_a_device_tensor_or_a_descriptor():
     assert call.empty_i32(x, 3, 4).shape == (3, 4) and call.empty_i32(x, 2).dtype == torch.int32
 
 
+def test_binding_takes_every_integer_that_ctypes_takes():
+    """Sizes come as ints, numpy integers or tensors of one element; what has no __index__ is refused.  Arguments are taken
+    from left to right: the host tensor at the end is the one refused where the sizes before it are good."""
+    import numpy as np
+    import pytest
+    import torch
+    call, x = api._native(), torch.zeros(8)
+    for size in (8, True, np.int64(8), np.int32(8), np.uint8(8), torch.tensor(8), torch.tensor([8], dtype=torch.int32)):
+        ctypes.c_int32.from_param(size)
+        with pytest.raises(AssertionError):
+            call.pack_lm_head(None, size, 128, x)
+    for other in (8.0, np.float32(8), None, "8", torch.tensor(0.5), torch.tensor([0, 0])):
+        with pytest.raises(TypeError):
+            ctypes.c_int32.from_param(other)
+        with pytest.raises(TypeError):
+            call.pack_lm_head(None, other, 128, x)
+
+
 def test_unforced_fp32_and_heads_of_64_plans_fit_the_fixed_array():
     """etv_tree_verify_attention_static cannot fall back on another workspace: a split that the library chooses by itself at
     fp32 or heads of 64 stays within its array, at every size, so that no unforced call is refused.  (Host only: the plan.)"""
