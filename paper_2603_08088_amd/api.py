@@ -235,7 +235,9 @@ def tree_verify_attention(q, k_cache, v_cache, prefix_len, kt, vt, bitmask, n_no
                           out=None, lse=None, want_lse: bool = True, workspace=None, desc: Optional[AttnDesc] = None):
     """q [B,T,Hq,d]; kt/vt [B,T,Hkv,d]; cache contiguous [B,P_cap,Hkv,d] or paged [nb,Hkv,16,d] + block_table.
     Returns (out [B,T,Hq,d] in q's dtype, lse float32 [B,Hq,T] or None)."""
-    dsc = desc or attn_desc(q, kt, k_cache, block_table, P_max, scale, kv_split, flags)
+    dsc = _attn_desc_only(desc or attn_desc(q, kt, k_cache, block_table, P_max, scale, kv_split, flags))
+    if q.dim() != 4:
+        raise ValueError("q is [B, T, Hq, d]")
     if out is None:
         out = torch.empty_like(q)
     if lse is None and want_lse:
@@ -244,7 +246,7 @@ def tree_verify_attention(q, k_cache, v_cache, prefix_len, kt, vt, bitmask, n_no
     if workspace is None:
         workspace = torch.empty((max(256, tree_verify_attention_workspace_bytes(dsc)),), dtype=torch.uint8,
                                 device=q.device)
-    rc = _native().tree_verify_attention(_attn_desc_only(dsc), q, k_cache, v_cache, block_table, prefix_len, kt, vt, bitmask,
+    rc = _native().tree_verify_attention(dsc, q, k_cache, v_cache, block_table, prefix_len, kt, vt, bitmask,
                                          n_nodes, out, lse, workspace, workspace.numel())
     _check("etv_tree_verify_attention", rc)
     return out, lse
@@ -388,7 +390,9 @@ def verify_epilogue(logits, tokens, retrieve, n_nodes, kt, vt, k_cache, v_cache,
     safe, pvalid = get(go, "safe", (B, L, W)), get(go, "pvalid", (B, L, W), torch.uint8)
     gathered, row_bytes = None, 0
     if src is not None:
-        row_bytes = src.element_size() * (src.numel() // max(1, src.shape[0] * src.shape[1]))
+        if src.shape[0] == 0 or src.shape[1] == 0:
+            raise IndexError("src has no row")
+        row_bytes = src.element_size() * (src.numel() // (src.shape[0] * src.shape[1]))
         gathered = get(go, "gathered", (B, L, W) + tuple(src.shape[2:]), src.dtype)
     g, ln, best = get(po, "argmax", (B, T)), get(po, "len", (B, L)), get(po, "best", (B,))
     A, acc, bonus = get(po, "accept_len", (B,)), get(po, "acc_nodes", (B, W)), get(po, "bonus", (B,))

@@ -130,6 +130,18 @@ def test_binding_takes_every_integer_that_ctypes_takes():
             call.pack_lm_head(None, other, 128, x)
 
 
+def test_calls_refuse_queries_of_another_rank_and_rows_that_are_not_there():
+    import pytest
+    import torch
+    x, ws = torch.zeros((2, 3, 8), dtype=torch.bfloat16), torch.zeros(256, dtype=torch.uint8)
+    with pytest.raises(ValueError):      # a descriptor of its own does not make up for a q that is not [B, T, Hq, d]
+        api.tree_verify_attention(x, x, x, x, x, x, x, x, P_max=1, desc=api.AttnDesc(), out=x, want_lse=False, workspace=ws)
+    tok, ret = torch.zeros((0, 3), dtype=torch.int32), torch.zeros((0, 2, 4), dtype=torch.int32)
+    kt, kc = torch.zeros((1, 0, 3, 2, 64)), torch.zeros((1, 0, 8, 2, 64))
+    with pytest.raises(IndexError):      # no first row to take the row's size from
+        api.verify_epilogue(None, tok, ret, tok, kt, kt, kc, kc, tok, tok, src=tok[..., None], post_out={"argmax": tok})
+
+
 def test_unforced_fp32_and_heads_of_64_plans_fit_the_fixed_array():
     """etv_tree_verify_attention_static cannot fall back on another workspace: a split that the library chooses by itself at
     fp32 or heads of 64 stays within its array, at every size, so that no unforced call is refused.  (Host only: the plan.)"""
