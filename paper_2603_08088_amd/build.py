@@ -1,7 +1,9 @@
 """Build libeagletv.so (hipcc, gfx950) and its Python binding in-tree.  Run as ``python -m paper_2603_08088_amd.build``."""
 from __future__ import annotations
 
+import importlib.util
 import os
+import shutil
 import subprocess
 import sys
 import sysconfig
@@ -25,12 +27,29 @@ def _hipcc(sources, target, verbose, extra=()):
 
 
 def _host_binding(verbose):
+    """The Python binding.  It needs torch, its headers, Python's and a C++ compiler; the C library is complete without it."""
+    cxx = os.environ.get("CXX", "g++").split()
+    py_include, missing = sysconfig.get_paths()["include"], []
+    if shutil.which(cxx[0]) is None:
+        missing.append(cxx[0])
+    if not os.path.exists(os.path.join(py_include, "Python.h")):
+        missing.append("Python.h")
+    spec = importlib.util.find_spec("torch")
+    torch_dir = os.path.dirname(spec.origin) if spec else None
+    if torch_dir is None or not os.path.exists(os.path.join(torch_dir, "include", "ATen", "ATen.h")):
+        missing.append("torch")
+    if missing:
+        if os.path.exists(BINDING):
+            os.remove(BINDING)   # one of another library must not stay
+        print(f"{os.path.basename(BINDING)}, which Python calls need, is not built: no {', '.join(missing)}", flush=True)
+        return
     import torch
     from torch.utils import cpp_extension
-    torch_lib = os.path.join(os.path.dirname(torch.__file__), "lib")
-    rocm = os.path.dirname(os.path.dirname(HIPCC))
-    includes = [os.path.join(ROOT, "include"), sysconfig.get_paths()["include"], os.path.join(rocm, "include")] + cpp_extension.include_paths()
-    _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+    torch_lib = os.path.join(torch_dir, "lib")
+    # HIP's headers: beside the compiler, which HIPCC may name by its path or as a command
+    rocm = os.path.dirname(os.path.dirname(os.path.realpath(shutil.which(HIPCC) or HIPCC)))
+    includes = [os.path.join(ROOT, "include"), py_include, os.path.join(rocm, "include")] + cpp_extension.include_paths()
+    _run(cxx + ["-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"] + [f"-I{d}" for d in includes] +
          [os.path.join(CSRC, "binding.cpp"), "-o", BINDING, f"-L{HERE}", f"-L{torch_lib}", "-l:libeagletv.so", "-lc10", "-lc10_hip", "-ltorch_cpu",
           "-ltorch_python", "-Wl,-rpath,$ORIGIN"], verbose)
