@@ -103,6 +103,12 @@ def test_mfma_kernel_tree_sizes(T):
     _check(wl, kv_split=64)       # one tile per split
     _check(wl, kv_split=4096)     # single split: direct epilogue
     ref = _check(wl, flags=api.ATTN_FLAG_GENERIC)   # same inputs through the fp32-VALU kernel
+    # calls this small plan the key-block kernel: the tile kernel at its own choice of splits and with the direct epilogue
+    for flags in (api.ATTN_FLAG_SMALL_WG, api.ATTN_FLAG_LARGE_WG):
+        for kv_split in (0, 4096):
+            _check(wl, flags=flags, kv_split=kv_split)
+            d = api.AttnDesc(B=2, T_max=T, Hq=8, Hkv=2, d=128, dtype=api.BF16, P_cap=400, P_max=300, kv_split=kv_split, flags=flags)
+            assert api.tree_verify_attention_plan(d)["ring_stages"] > 0
 
 
 @pytest.mark.parametrize("paged", [False, True])
@@ -393,6 +399,48 @@ def test_negative_scales(dtype, d):
                     assert np.abs(g[b, :, :n] - ref_lse[b, :, :n]).max() <= (d * 250 * 2.0 ** -24 if dtype == "f32" else 2e-2)
 
 
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("bf16", 128), ("f32", 64), ("f32", 128)])
+def test_in_place_tree_rows_on_every_kernel(dtype, d, paged):
+    """Tree rows in the cache itself behind the prefix (no tree buffer) give the bits that the separate buffer gives, on every
+    kernel: prefixes that end inside a block and inside a tile, padded sequences, splits."""
+    rng = np.random.default_rng(8800 + d + paged)
+    T = 70
+    parents = [random_tree(rng, T) for _ in range(5)]
+    wl = synth.assemble("tail", rng, parents, [600, 77, 64, 1, 129], Hq=8, Hkv=2, d=d, dtype=dtype, V=512, W=T, paged=paged, T_max=T,
+                        with_logits=False, spare_blocks=3, tail_room=T)
+    wl.n_nodes[1], wl.n_nodes[4] = 17, 65
+    for b in range(5):
+        for j in range(int(wl.n_nodes[b])):
+            pos = int(wl.prefix_len[b]) + j
+            at = (wl.block_table[b, pos // synth.BLOCK], slice(None), pos % synth.BLOCK) if paged else (b, pos)
+            wl.k_cache[at], wl.v_cache[at] = wl.kt[b, j], wl.vt[b, j]
+    dv = DevWorkload(wl)
+    m = api.build_tree_mask(dv.parent, dv.n_nodes)
+    for flags in SHAPES[dtype] + [api.ATTN_FLAG_GENERIC]:
+        for kv_split in (0, 64, 4096):
+            sep, lse_sep = gpu_attention(dv, m["bitmask"], flags=flags, kv_split=kv_split)
+            tail, lse_tail = api.tree_verify_attention(dv.q, dv.k_cache, dv.v_cache, dv.prefix_len, None, None, m["bitmask"], dv.n_nodes,
+                                                       P_max=dv.P_max, block_table=dv.block_table, flags=flags, kv_split=kv_split)
+            torch.cuda.synchronize()
+            assert torch.equal(sep, tail) and torch.equal(lse_sep, lse_tail), (flags, kv_split)
+    _check(wl)      # and the separate buffer is compared with the oracle
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("bf16", 128), ("f32", 64), ("f32", 128)])
+def test_combine_of_many_splits(dtype, d):
+    """More splits than one wavefront reads at once: up to 1024 query rows four wavefronts share a row's splits (17 and more), one
+    round and two rounds of them; beyond that one wavefront takes them in batches.  Splits that the shorter sequence lacks."""
+    rng = np.random.default_rng(8900 + d)
+    for P, T, n in (([1100, 700], 9, [9, 4]), ([1030], 1, [1]), ([7000], 5, [5]), ([1500, 1100], 70, [70, 33])):
+        wl = _small(rng, len(P), T, 8, 2, d, P, dtype, True, n_nodes=n, q_scale=2.0)
+        for flags in (0, api.ATTN_FLAG_UNIFORM_SPLITS):
+            _check(wl, kv_split=64, flags=flags)
+            dsc = api.AttnDesc(B=len(P), T_max=T, Hq=8, Hkv=2, d=d, dtype=api.F32 if dtype == "f32" else api.BF16, block_size=16,
+                               max_blocks=1000, num_blocks=1000, P_max=max(P), kv_split=64, flags=flags)
+            assert api.tree_verify_attention_plan(dsc)["n_splits"] >= 17
+
+
 def test_key_halves_merge_is_deterministic():
     """The merge of the two key halves has a fixed order: two launches on the same inputs give the same bits."""
     rng = np.random.default_rng(1800)
@@ -459,6 +507,8 @@ def test_splits_shared_out_by_length_agree_with_the_oracle(paged, B, T, kv_split
     assert uniform["balanced_splits"] == 0 and uniform["n_splits"] == plan["n_splits"]
     _check(wl, kv_split=kv_split)
     _check(wl, kv_split=kv_split, flags=api.ATTN_FLAG_UNIFORM_SPLITS)
+    for flags in (api.ATTN_FLAG_KEY_BLOCKS, api.ATTN_FLAG_LARGE_WG, api.ATTN_FLAG_SMALL_WG):   # on either kernel, whichever was picked
+        _check(wl, kv_split=kv_split, flags=flags)
 
 
 def test_no_leak_from_hidden_tree_rows_padding_and_stale_cache_bf16():
@@ -466,7 +516,7 @@ def test_no_leak_from_hidden_tree_rows_padding_and_stale_cache_bf16():
     wl = _small(rng, 1, 48, 8, 2, 128, [100], "bf16", False, n_nodes=[37])
     d = DevWorkload(wl)
     m = api.build_tree_mask(d.parent, d.n_nodes)
-    out0, lse0 = gpu_attention(d, m["bitmask"])
+    clean = [gpu_attention(d, m["bitmask"], flags=flags) for flags in SHAPES["bf16"]]
     dense = oracle.build_tree_mask(wl.parent, wl.n_nodes)["dense"][0, 0]
     k = 30
     hidden = [j for j in range(48) if not dense[k, j]]
@@ -475,10 +525,11 @@ def test_no_leak_from_hidden_tree_rows_padding_and_stale_cache_bf16():
     wl.k_cache[0, 100:] = big; wl.v_cache[0, 100:] = big
     wl.q[0, 37:] = big
     d2 = DevWorkload(wl)
-    out1, lse1 = gpu_attention(d2, m["bitmask"])
-    torch.cuda.synchronize()
-    assert torch.equal(out0[0, k], out1[0, k]) and torch.equal(lse0[0, :, k], lse1[0, :, k])
-    assert torch.all(out1[0, 37:] == 0)
+    for flags, (out0, lse0) in zip(SHAPES["bf16"], clean):
+        out1, lse1 = gpu_attention(d2, m["bitmask"], flags=flags)
+        torch.cuda.synchronize()
+        assert torch.equal(out0[0, k], out1[0, k]) and torch.equal(lse0[0, :, k], lse1[0, :, k]), flags
+        assert torch.all(out1[0, 37:] == 0)
 
 
 def test_unsupported_and_invalid_arguments_are_rejected():

@@ -84,17 +84,24 @@ def test_random_row_counts_and_vocabularies_on_the_wide_path():
         _check(h, w, n)
 
 
-def test_random_row_counts_and_vocabularies_on_the_gemm_path():
-    """Beyond 256 node rows the head runs as a GEMM tiling (256 vocabulary rows x 256 node rows per workgroup): row
-    counts that end inside the first, second, third or fourth 64-row block of the last row group, padded sequences,
-    vocabularies that end inside the first or the second 128-row half of a 256-row tile, one and several tiles,
-    contraction lengths of one to three packed steps."""
+def _gemm_runs(B, T, V):
+    """The head's choice: the GEMM tiling (256 vocabulary rows x 256 node rows per workgroup) where it needs less than half the
+    rounds of 256 workgroups that the 128-row groups need."""
+    tiles, rows = (V + 127) // 128, B * T
+    wide, gemm = (-(-t * -(-rows // r) // 256) for t, r in ((tiles, 128), ((tiles + 1) // 2, 256)))
+    return rows > 128 and 2 * gemm < wide
+
+
+def test_random_row_counts_and_vocabularies_beyond_256_rows():
+    """More than 256 node rows over a small vocabulary, which stay on the 128-row groups: row counts that end inside the
+    first, second, third or fourth 32-row block of the last group, padded sequences, vocabularies that end inside the first
+    or the second half of a tile, one and several tiles, contraction lengths of one to three packed steps."""
     rng = np.random.default_rng(3060)
     shapes = [(4, 128, 128, 513), (3, 200, 256, 300), (9, 100, 128, 129), (32, 33, 384, 1000), (2, 256, 128, 256),
               (5, 103, 256, 127), (8, 65, 128, 770), (1, 600, 128, 1), (6, 97, 384, 385), (1, 257, 128, 300),
               (8, 60, 256, 641), (3, 111, 128, 64)]
     for (B, T, D, V) in shapes:
-        assert B * T > 256
+        assert B * T > 256 and not _gemm_runs(B, T, V)
         h = _bf16(rng.standard_normal((B, T, D)))
         w = _bf16(rng.standard_normal((V, D)) / np.sqrt(D))
         n = [T] + [int(rng.integers(0, T + 1)) for _ in range(B - 1)]
@@ -106,31 +113,31 @@ def test_random_row_counts_and_vocabularies_on_the_gemm_path():
 def test_gemm_tiling_where_it_saves_rounds(B, T, D, V):
     """The GEMM tiling runs where it needs less than half the rounds of workgroups: vocabularies that end inside the first and
     the second half of a 256-row tile, last row groups of 1 ... 256 rows, several panels of tiles and groups per XCD."""
-    tiles, rows = (V + 127) // 128, B * T
-    rounds = [-(-t * -(-rows // r) // 256) for t, r in ((tiles, 128), ((tiles + 1) // 2, 256))]
-    assert 2 * rounds[1] < rounds[0]
+    assert _gemm_runs(B, T, V)
     rng = np.random.default_rng(3070 + V)
     h = _bf16(rng.standard_normal((B, T, D)))
     w = _bf16(rng.standard_normal((V, D)) / np.sqrt(D))
     _check(h, w, [T] + [int(rng.integers(0, T + 1)) for _ in range(B - 1)])
 
 
-def test_exact_ties_on_the_gemm_path_take_the_lowest_index():
+@pytest.mark.parametrize("B,T,V,gemm", [(5, 128, 900, False), (32, 125, 2177, True)])
+def test_exact_ties_beyond_256_rows_take_the_lowest_index(B, T, V, gemm):
     rng = np.random.default_rng(3110)
-    B, T, D, V = 5, 128, 128, 900
+    D = 128
+    assert _gemm_runs(B, T, V) == gemm
     hb = _bf16(rng.standard_normal((B, T, D)))
     wb = _bf16(rng.standard_normal((V, D)) / np.sqrt(D))
     hf = synth.bf16_bits_to_f32(hb)
     # node (2, 77): a clear winner duplicated in another 256-row tile, in the other 128-row half of its tile, in
     # another 32-row block of its half and in the last (partial) tile
     win = _bf16(8.0 * hf[2, 77] / float(hf[2, 77] @ hf[2, 77]))
-    for v in (300, 37, 310, 420, 899):
+    for v in (300, 37, 310, 420, 899, V - 1):
         wb[v] = win
-    ref, g = _check(hb, wb, [T] * B)
-    assert g[2, 77] == 37 and ref["argmax"][2, 77] == 37
-    wb[37] = _bf16(rng.standard_normal(D) / np.sqrt(D))
-    ref, g = _check(hb, wb, [T] * B)
-    assert g[2, 77] == 300
+    for gone, lowest in (((), 37), ((37,), 300), ((300, 310), 420)):
+        for v in gone:
+            wb[v] = _bf16(rng.standard_normal(D) / np.sqrt(D))
+        ref, g = _check(hb, wb, [T] * B)
+        assert g[2, 77] == lowest and ref["argmax"][2, 77] == lowest
 
 
 def test_unsupported_width_is_rejected():
@@ -238,10 +245,11 @@ def test_head_to_commit_without_logits():
 
 
 @pytest.mark.parametrize("T", [12, 13, 70])
-@pytest.mark.parametrize("V", [2048, 2049, 8200])
+@pytest.mark.parametrize("V", [2048, 2049, 8200, 32768, 32769, 70000])
 def test_partials_of_the_head_are_finished_inline_or_by_a_launch(T, V):
     """The choice per node out of the head's per-tile maxima, on both sides of the rule that picks where they are reduced
-    (nodes per tree, partials per node): hand-made partials with ties, against numpy and the oracle's acceptance."""
+    (nodes per tree, partials per node) and of the 256 partials that a wavefront reads per trip to memory: hand-made partials
+    with ties, against numpy and the oracle's acceptance."""
     from helpers import logits_from_argmax, random_tree
     rng = np.random.default_rng(100 * T + V)
     B, tiles = 3, (V + 127) // 128
@@ -260,6 +268,34 @@ def test_partials_of_the_head_are_finished_inline_or_by_a_launch(T, V):
     kt, vt, kc, vc = (to_dev(x)[None].clone() for x in (wl.kt, wl.vt, wl.k_cache, wl.v_cache))
     _, q, _ = api.verify_epilogue(None, tok, ret, dn, kt, vt, kc, vc, to_dev(wl.prefix_len), to_dev(wl.capacity),
                                   workspace=ws, head_V=V)
+    torch.cuda.synchronize()
+    for key in rp:
+        assert np.array_equal(bits_of(p[key]), rp[key]) and np.array_equal(bits_of(q[key]), rp[key]), key
+
+
+@pytest.mark.parametrize("T", [12, 13])
+@pytest.mark.parametrize("V", [65536, 65541, 70000])
+def test_partials_of_the_logits_are_finished_inline_or_by_a_launch(T, V):
+    """Vocabularies around 16 chunks of the logit scan: beyond them the choice per node is finished by a launch of its own from 13
+    nodes on.  Ties within a chunk and across chunks; against the oracle."""
+    rng = np.random.default_rng(T + V)
+    B, n = 2, [T, T - 4]
+    from helpers import random_tree
+    wl = synth.assemble("logits", rng, [random_tree(rng, x) for x in n], [40] * B, Hq=2, Hkv=2, d=64, dtype="bf16", V=V, W=T, paged=False,
+                        T_max=T, with_logits=False)
+    lg = rng.integers(0, 4, size=(B, T, V)).astype(np.float32)         # ties everywhere
+    for b in range(B):
+        for k in range(T):
+            lg[b, k, rng.integers(0, V, size=3)] = 9.0                 # three of the largest, in any chunks
+        for p in wl.retrieve[b]:                                       # and the children's tokens now and then, so that paths are accepted
+            for x, y in zip(p[:-1], p[1:]):
+                if 0 <= x and 0 <= y and rng.random() < 0.5:
+                    lg[b, x, wl.tokens[b, y]] = 10.0
+    rp = oracle.evaluate_posterior(lg, wl.tokens, wl.retrieve, wl.n_nodes)
+    tok, ret, dn, dl = to_dev(wl.tokens), to_dev(wl.retrieve), to_dev(wl.n_nodes), to_dev(lg)
+    p = api.evaluate_posterior(dl, tok, ret, dn)
+    kt, vt, kc, vc = (to_dev(x)[None].clone() for x in (wl.kt, wl.vt, wl.k_cache, wl.v_cache))
+    _, q, _ = api.verify_epilogue(dl, tok, ret, dn, kt, vt, kc, vc, to_dev(wl.prefix_len), to_dev(wl.capacity))
     torch.cuda.synchronize()
     for key in rp:
         assert np.array_equal(bits_of(p[key]), rp[key]) and np.array_equal(bits_of(q[key]), rp[key]), key
