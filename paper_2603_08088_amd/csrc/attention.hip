@@ -2252,7 +2252,10 @@ static int32_t attention_run(const etv_attn_desc *h, const void *q, const void *
     }
     if (rc != ETV_OK || pl.nsplit == 1) return rc;
     const long crows = (long)h->B * h->T_max * h->Hq;
-    const bool shared = pl.nsplit > 16 && crows <= 1024;      // more splits than one batch of a wavefront
+    // More splits than one batch of a wavefront.  Splits shared out by length leave a sequence about half of nsplit (two equal
+    // sequences of 17 tiles: 9 each), so there the line is 32: B = 2, T = 7 / 16, 8/2 / 32/8 heads, 20 ... 32 splits 12.9 ... 13.4 /
+    // 17.2 ... 18.5 us, shared 13.4 ... 13.6 / 18.7 ... 19.9; 33 splits 14.4 / 19.6, shared 12.8 / 19.2.
+    const bool shared = pl.nsplit > (pl.balanced ? 32 : 16) && crows <= 1024;
     const bool two = !shared && h->d == 128 && crows <= 512;  // very few rows: two wavefronts per row
     const bool wide = pl.nsplit > 8;                          // many splits: sixteen per batch of loads
     const int rows_per_wg = shared ? 1 : (two ? 2 : 4);
