@@ -326,7 +326,8 @@ __global__ void __launch_bounds__(64) attn_generic_kernel(AttnParams p) {
 // SHARED: the four wavefronts of a workgroup take every fourth split of one row and merge through LDS, for launches whose
 // splits would otherwise be several batches in series.  32 rows, 43 splits: 9.0 -> 4.7 us; 16 rows, 107 splits: 18.2 -> 7.4;
 // with many rows the batches of different rows overlap anyway (1920 rows, 32 splits: 9.0, shared 11.2), and up to 16 splits
-// one wavefront's single batch is as fast.
+// one wavefront's single batch is as fast or faster: a row whose sequence has no more is left to the first wavefront (whole
+// call, B = 2, T = 16, 32/8 heads, 24 equal splits launched and some 12 used 18.0 us, shared 20.1; one sequence with 24 10.7, 12.1).
 template <typename T, int D, int WPR, int U, bool SHARED>
 __global__ void __launch_bounds__(256) attn_combine_kernel(AttnParams p) {
     constexpr int E = D / (64 * WPR);
@@ -355,16 +356,19 @@ __global__ void __launch_bounds__(256) attn_combine_kernel(AttnParams p) {
     }
     const size_t pr0 = part_row(p, p.balanced ? share.x : b * p.nsplit, h, k);
     const size_t sstride = (size_t)p.Hq * p.T_max;  // rows between consecutive splits
-    constexpr int STEP = SHARED ? 4 : 1;
+    // (splits shared out by length: a sequence may have far fewer than nsplit)
+    const bool many = SHARED && nvalid > U;
+    if (SHARED && !many && wv > 0) return;  // uniform over the workgroup, as below
+    const int step = many ? 4 : 1;
     float M = -INFINITY, L = 0.f, acc[E];
 #pragma unroll
     for (int e = 0; e < E; e++) acc[e] = 0.f;
-    for (int s0 = SHARED ? wv : 0; s0 < nvalid; s0 += U * STEP) {
+    for (int s0 = many ? wv : 0; s0 < nvalid; s0 += U * step) {
         float ms[U], ls[U], os[U][E];
 #pragma unroll
         for (int u = 0; u < U; u++) {
-            const bool ok = s0 + u * STEP < nvalid;
-            const size_t r = pr0 + (size_t)(ok ? s0 + u * STEP : 0) * sstride;
+            const bool ok = s0 + u * step < nvalid;
+            const size_t r = pr0 + (size_t)(ok ? s0 + u * step : 0) * sstride;
             ms[u] = ok ? p.part_m[r] : -INFINITY;
             ls[u] = ok ? p.part_l[r] : 0.f;
 #pragma unroll
@@ -389,7 +393,7 @@ __global__ void __launch_bounds__(256) attn_combine_kernel(AttnParams p) {
             }
         }
     }
-    if (SHARED) {
+    if (many) {
         __shared__ float s_m[4], s_l[4], s_acc[4][D];
         if (lane == 0) { s_m[wv] = M; s_l[wv] = L; }
 #pragma unroll
@@ -2252,10 +2256,7 @@ static int32_t attention_run(const etv_attn_desc *h, const void *q, const void *
     }
     if (rc != ETV_OK || pl.nsplit == 1) return rc;
     const long crows = (long)h->B * h->T_max * h->Hq;
-    // More splits than one batch of a wavefront.  Splits shared out by length leave a sequence about half of nsplit (two equal
-    // sequences of 17 tiles: 9 each), so there the line is 32: B = 2, T = 7 / 16, 8/2 / 32/8 heads, 20 ... 32 splits 12.9 ... 13.4 /
-    // 17.2 ... 18.5 us, shared 13.4 ... 13.6 / 18.7 ... 19.9; 33 splits 14.4 / 19.6, shared 12.8 / 19.2.
-    const bool shared = pl.nsplit > (pl.balanced ? 32 : 16) && crows <= 1024;
+    const bool shared = pl.nsplit > 16 && crows <= 1024;      // more splits than one batch of a wavefront
     const bool two = !shared && h->d == 128 && crows <= 512;  // very few rows: two wavefronts per row
     const bool wide = pl.nsplit > 8;                          // many splits: sixteen per batch of loads
     const int rows_per_wg = shared ? 1 : (two ? 2 : 4);

@@ -429,9 +429,9 @@ def test_in_place_tree_rows_on_every_kernel(dtype, d, paged):
 
 @pytest.mark.parametrize("dtype,d", [("bf16", 64), ("bf16", 128), ("f32", 64), ("f32", 128)])
 def test_combine_of_many_splits(dtype, d):
-    """More splits than one wavefront reads at once: up to 1024 query rows four wavefronts share a row's splits (from 17 on, from 33
-    where the splits follow the lengths), one round and two rounds of them; beyond that one wavefront takes them in batches.
-    Splits that the shorter sequence lacks."""
+    """More splits than one wavefront reads at once: up to 1024 query rows four wavefronts share a row's splits, one round
+    and two rounds of them, unless its sequence has no more than 16; beyond that one wavefront takes them in batches.  Splits
+    that the shorter sequence lacks."""
     rng = np.random.default_rng(8900 + d)
     for P, T, n in (([1100, 700], 9, [9, 4]), ([2200, 1800, 40], 9, [9, 4, 2]), ([1030], 1, [1]), ([7000], 5, [5]), ([1500, 1100], 70, [70, 33])):
         wl = _small(rng, len(P), T, 8, 2, d, P, dtype, True, n_nodes=n, q_scale=2.0)
