@@ -159,7 +159,7 @@ typedef struct etv_attn_desc {
     int32_t num_blocks; /* paged: blocks in the pool (not read by attention) */
     int32_t P_cap;      /* contiguous: rows allocated per sequence */
     int32_t P_max;      /* host-known upper bound of prefix_len[b]; sizes the launch */
-    float scale;        /* 0 => 1/sqrt(d); may be negative */
+    float scale;        /* 0 => 1/sqrt(d); negative: bf16 runs on the kernel that ETV_ATTN_FLAG_GENERIC asks for */
     int32_t kv_split;   /* keys per work unit (multiple of 64); 0 => chosen by the library */
     int32_t flags;      /* ETV_ATTN_FLAG_* */
 } etv_attn_desc;
@@ -173,7 +173,7 @@ typedef struct etv_attn_desc {
 #define ETV_ATTN_FLAG_UNIFORM_SPLITS 32 /* one split size for the whole batch, also where the splits could follow the
                                            sequences' lengths (tuning) */
 
-#define ETV_ATTN_FLAG_KEY_BLOCKS 64 /* bf16, scale not negative: every wavefront takes 32-key blocks of its own (tuning) */
+#define ETV_ATTN_FLAG_KEY_BLOCKS 64 /* bf16: every wavefront takes 32-key blocks of its own (tuning) */
 
 ETV_API size_t etv_tree_verify_attention_workspace_bytes(const etv_attn_desc *h_desc);
 

@@ -9,7 +9,7 @@
 //                        its own instead of a tile shared by the workgroup.
 //   * attn_f32_kernel    fp32: both products on v_mfma_f32_16x16x4_f32, no barrier in the tile loop.
 //   * attn_generic_kernel  any supported dtype / head dim, fp32 VALU arithmetic, one wavefront per query
-//                        row; runs only where ETV_ATTN_FLAG_GENERIC asks for it, as an independent check.
+//                        row; bf16 with a negative scale, and where ETV_ATTN_FLAG_GENERIC asks for it, as an independent check.
 // and attn_combine_kernel merges the splits by log-sum-exp.  With a single split the partial kernels write
 // the final output themselves.
 //
@@ -34,7 +34,6 @@ struct AttnParams {
     int pairs;   // mfma kernel: 32-row chunks of the packed query rows of a KV head
     int wgp;     // mfma kernel: workgroups per (b, kv head, split) = ceil(pairs / 4)
     float scale_log2;
-    uint32_t q_sign;  // mfma kernel: sign bits to flip in a pair of Q values, so that scale_log2 is never negative there
     // mfma kernel, batches of 2 .. 64 sequences with splits: the B * nsplit split slots are shared out among the
     // sequences by their lengths (on the device, where the lengths are), slot-major partials
     //   part_o [B * nsplit][Hq][T_max][d]; split_tab[b] = (first slot, splits in use) for the combine kernel
@@ -503,15 +502,6 @@ __device__ __forceinline__ float pair_sum(uint32_t packed, float acc) {
                                            acc, false);
 }
 
-template <int N>
-__device__ __forceinline__ void flip_signs(bf16x8 (&x)[N], uint32_t sign) {
-#pragma unroll
-    for (int i = 0; i < N; i++) {
-        const uint4 w = __builtin_bit_cast(uint4, x[i]);
-        x[i] = __builtin_bit_cast(bf16x8, uint4{w.x ^ sign, w.y ^ sign, w.z ^ sign, w.w ^ sign});
-    }
-}
-
 // 16 bytes per lane from global memory straight into LDS at (lds_addr + 16 * lane); asynchronous.
 __device__ __forceinline__ void async_load16(const void *gptr, uint32_t lds_addr) {
     // lds_addr is the same in every lane; readfirstlane says so to the compiler whatever it concluded about the loop
@@ -972,7 +962,7 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(AttnParams p) {
     static_assert(PD >= 1 && PD <= 3, "ring depth");
     asm volatile("" ::"s"(p.q), "s"(p.k_cache), "s"(p.v_cache), "s"(p.kt), "s"(p.vt), "s"(p.block_table),
                  "s"(p.prefix_len), "s"(p.n_nodes), "s"(p.bitmask), "s"(p.T_max), "s"(p.Hq), "s"(p.G),
-                 "s"(p.max_blocks), "s"(p.P_cap), "s"(p.P_max), "s"(p.words), "s"(p.chunk), "s"(p.pairs), "s"(p.q_sign));
+                 "s"(p.max_blocks), "s"(p.P_cap), "s"(p.P_max), "s"(p.words), "s"(p.chunk), "s"(p.pairs));
     int n_raw, P_raw;
     if (p.balanced) {
         n_raw = share.n_raw; P_raw = share.P_raw;
@@ -1102,7 +1092,6 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(AttnParams p) {
         if (rv) v = *reinterpret_cast<const uint4 *>(qp + (((size_t)b * p.T_max + kq) * p.Hq + h) * D + 16 * kk + 8 * hh);
         qreg[kk] = __builtin_bit_cast(bf16x8, v);
     }
-    if (p.q_sign) flip_signs(qreg, p.q_sign);
 
     f32x16 oacc[DB];
     float m_run = -INFINITY, l_run = 0.f;
@@ -1972,7 +1961,10 @@ static Plan make_plan(const etv_attn_desc *h) {
     // d is 64 or 128.  The row groups of all KV heads share a grid dimension of at most 65535; thousands of heads with the
     // largest trees that go beyond it stay on the kernel with a workgroup per row.
     const long rows = (long)(h->Hq / h->Hkv) * h->T_max;
-    const bool generic = (h->flags & ETV_ATTN_FLAG_GENERIC) != 0;
+    // The bf16 kernels take a row's maximum before they scale it, which a negative scale turns into its minimum; such calls go to
+    // the kernel that scales first.  (Turning the signs of Q round in them instead costs every short launch: B = 22, T = 7,
+    // 32/32 heads, P = 95 16.7 -> 17.6 us.)
+    const bool generic = (h->flags & ETV_ATTN_FLAG_GENERIC) != 0 || (h->dtype == ETV_BF16 && h->scale < 0.f);
     pl.mfma = h->dtype == ETV_BF16 && !generic && (h->d == 128 || h->Hkv * ((rows + 63) / 64) <= 65535);
     pl.f32 = h->dtype == ETV_F32 && !generic;
     if (pl.f32) {
@@ -2018,8 +2010,7 @@ static Plan make_plan(const etv_attn_desc *h) {
     pl.pairs = ((h->Hq / h->Hkv) * h->T_max + 31) / 32;  // 32-row chunks of the G * T_max packed rows of a KV head
     const double part_us = 2.0 * B * h->Hq * h->T_max * (h->d + 2.0) * 4.0 / 3.0e6;
     double best = 1e30, best_lat = 0.0;
-    // negative scales are the tile kernel's: turning Q round costs a launch of 14 us 0.1 us, and only there it disappears
-    const bool tiles_only = h->scale < 0.f, blocks_only = (h->flags & ETV_ATTN_FLAG_KEY_BLOCKS) != 0 && !tiles_only;
+    const bool blocks_only = (h->flags & ETV_ATTN_FLAG_KEY_BLOCKS) != 0;
     for (int nw = 4; nw <= 8 && !blocks_only; nw += 4) {
         for (int kh = 0; kh <= 1; kh++) {
             const int cw = kh ? nw / 2 : nw;  // chunks per workgroup
@@ -2053,7 +2044,7 @@ static Plan make_plan(const etv_attn_desc *h) {
         }
     }
     constexpr int kShapeFlags = ETV_ATTN_FLAG_SMALL_WG | ETV_ATTN_FLAG_LARGE_WG | ETV_ATTN_FLAG_WHOLE_TILE | ETV_ATTN_FLAG_KEY_HALVES;
-    if (blocks_only || !(tiles_only || (h->flags & kShapeFlags))) {
+    if (blocks_only || !(h->flags & kShapeFlags)) {
         // Key-block kernel against the pick so far, for launches that fit the chip at once (one workgroup per compute unit, two
         // at d = 64): a further round pays start-up and merge again, and the other kernel is then always ahead.  Microseconds,
         // fitted to 128 workloads (B = 1 ... 32, T = 1 ... 250, P = 48 ... 30310, both head sizes; for 38 of them every split
@@ -2215,10 +2206,6 @@ static int32_t attention_run(const etv_attn_desc *h, const void *q, const void *
     if (p.pairs > 0) p.inv_pairs = fast_div_inv(p.pairs);
     const float scale = (h->scale == 0.f) ? 1.0f / sqrtf((float)h->d) : h->scale;
     p.scale_log2 = scale * 1.4426950408889634f;
-    if (pl.mfma && p.scale_log2 < 0.f) {  // a row's maximum is taken before it is scaled
-        p.scale_log2 = -p.scale_log2;
-        p.q_sign = 0x80008000u;
-    }
     if (pl.nsplit > 1) {
         size_t rows = (size_t)h->B * h->Hq * h->T_max * pl.nsplit;
         p.part_o = static_cast<float *>(workspace);

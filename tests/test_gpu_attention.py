@@ -378,7 +378,8 @@ def test_values_that_are_not_finite_reach_only_the_rows_that_see_them(dtype, d, 
 @pytest.mark.parametrize("dtype,d", [("bf16", 64), ("bf16", 128), ("f32", 64), ("f32", 128)])
 def test_negative_scales(dtype, d):
     """A negative scale turns the order of the scores round: the reference of a row is its smallest product.  Scores spread
-    over some 500 log2 units, so that any other reference overflows; tolerances as everywhere."""
+    over some 500 log2 units, so that any other reference overflows; tolerances as everywhere.  (bf16 goes to the one-row
+    kernel, whatever shape the flags ask for.)"""
     rng = np.random.default_rng(8700 + d)
     wl = _small(rng, 2, 70, 8, 2, d, [230, 150], dtype, True, n_nodes=[70, 33], q_scale=4.0)
     dv = DevWorkload(wl)
