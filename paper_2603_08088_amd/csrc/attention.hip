@@ -2010,6 +2010,8 @@ static Plan make_plan(const etv_attn_desc *h) {
     pl.pairs = ((h->Hq / h->Hkv) * h->T_max + 31) / 32;  // 32-row chunks of the G * T_max packed rows of a KV head
     const double part_us = 2.0 * B * h->Hq * h->T_max * (h->d + 2.0) * 4.0 / 3.0e6;
     double best = 1e30, best_lat = 0.0;
+    // a batch with splits: the slots go to the sequences by length (lane i of a wavefront plans sequence i)
+    const bool shared_out = B >= 2 && B <= 64 && !(h->flags & ETV_ATTN_FLAG_UNIFORM_SPLITS);
     const bool blocks_only = (h->flags & ETV_ATTN_FLAG_KEY_BLOCKS) != 0;
     for (int nw = 4; nw <= 8 && !blocks_only; nw += 4) {
         for (int kh = 0; kh <= 1; kh++) {
@@ -2047,40 +2049,41 @@ static Plan make_plan(const etv_attn_desc *h) {
     if (blocks_only || !(h->flags & kShapeFlags)) {
         // Key-block kernel against the pick so far, for launches that fit the chip at once (one workgroup per compute unit, two
         // at d = 64): a further round pays start-up and merge again, and the other kernel is then always ahead.  Microseconds,
-        // fitted to 128 workloads (B = 1 ... 32, T = 1 ... 250, P = 48 ... 30310, both head sizes; for 38 of them every split
-        // count of both kernels): the pick is within 0.5 % of the best measured shape on average, and 14 % ahead of what the
-        // other kernel gives.  A wavefront's block is 1.6 (2.15 where a single chunk waits for HBM and not for its neighbours'
-        // lines in L2; d = 64 1.1, and 1.8 times that with two workgroups on a compute unit); the memory side is the K/V bytes
-        // once at 6.9 TB/s and once more per further chunk at 42 TB/s.
+        // fitted to 488 workloads (B = 1 ... 32, T = 1 ... 256, P = 64 ... 30000, both head sizes; profiles/attention_plan_picks.csv):
+        // what the choice costs against the best measured shape, and twice over against the tile kernel's own pick.  A
+        // wavefront's block is 2.0 (2.33 where a single chunk waits for HBM and not for its neighbours' lines in L2; d = 64 1.4,
+        // and 2.3 times that with two workgroups on a compute unit); the memory side is the K/V bytes once at 6.9 TB/s and once
+        // more per further chunk at 46 TB/s.  The pick so far counts as 3 % faster than its estimate: what a wrong one costs.
         const bool d64 = h->d == 64;
-        const double kv_bytes = 4.0 * B * h->P_max * (double)h->Hkv * h->d, part2_us = part_us * 0.72;
+        const double kv_bytes = 4.0 * B * h->P_max * (double)h->Hkv * h->d, part2_us = part_us * 0.67;
         if (best < 1e30) {
-            const double lat = 0.8 * best_lat * (d64 ? 0.76 : 1.0) + 5.6, mem = 7.8 + kv_bytes / 6.2e6;
-            best = (lat > mem ? lat : mem) + (pl.nsplit > 1 ? 3.3 + pl.nsplit * part2_us : 0.0);
+            const double lat = 0.78 * best_lat * (d64 ? 0.68 : 1.0) + 6.6, mem = 7.15 + kv_bytes / 5.7e6;
+            best = 0.97 * ((lat > mem ? lat : mem) + (pl.nsplit > 1 ? 3.3 + pl.nsplit * part2_us : 0.0));
         }
         const long units = (long)B * h->Hkv * pl.pairs, slots = d64 ? 512 : 256;
-        const double mem = 4.9 + kv_bytes / 6.9e6 + (pl.pairs - 1) * kv_bytes / 42.0e6, mem25 = mem * mem * sqrt(mem);
+        const double mem = 4.75 + kv_bytes / 6.9e6 + (pl.pairs - 1) * kv_bytes / 46.0e6, mem25 = mem * mem * sqrt(mem);
         const int tree_blocks = (h->T_max + KB_KEYS - 1) / KB_KEYS;
         const int forced_tps = h->kv_split > 0 ? min(tiles, (h->kv_split + KT - 1) / KT) : 0;
         for (int ns = forced_tps ? (tiles + forced_tps - 1) / forced_tps : 1, tps; ns <= tiles; ns = forced_tps ? tiles + 1 : next_split_count(tiles, tps)) {
             tps = forced_tps ? forced_tps : (tiles + ns - 1) / ns;
             const long wgs = units * ns;
-            if (wgs > slots && !(blocks_only && (ns == 1 || forced_tps))) break;
+            // the chunks of a (split, KV head, sequence) stay on one XCD: the fullest of the eight has to hold all of its own at once
+            const long fullest = ((long)B * ns * h->Hkv + 7) / 8 * pl.pairs;
+            if (fullest > slots / 8 && !(blocks_only && (ns == 1 || forced_tps))) break;
             if (((long)B * ns * h->Hkv + 7) / 8 > 65535 || pl.pairs > 65535) break;  // grid dimensions
             if (!forced_tps && beyond_array(h, ns)) break;
             const int most = (2 * tps + tree_blocks + KB_NW - 1) / KB_NW, usual = (2 * tps + KB_NW - 1) / KB_NW;
             const double steps = ns > 1 ? 0.5 * (most + usual) : most;  // only the last split takes the tree
-            const double t_step = d64 ? (wgs > 256 ? 2.0 : 1.1) : (pl.pairs == 1 ? 2.15 : 1.6);
-            const double lat = steps * t_step + (d64 ? 2.5 : 3.4);
-            const double est = pow(lat * lat * sqrt(lat) + mem25, 0.4) + (ns > 1 ? 3.3 + ns * part2_us : 0.0);
+            const double t_step = d64 ? (wgs > 256 ? 3.2 : 1.4) : (pl.pairs == 1 ? 2.33 : 2.0);
+            const double lat = steps * t_step + (d64 ? 2.4 : 3.3);
+            const double est = pow(lat * lat * sqrt(lat) + mem25, 0.4) + (ns > 1 ? 3.05 + ns * part2_us + (shared_out ? 1.2 : 0.0) : 0.0);
             if (est < best) {
                 best = est;
                 pl.blocks = true; pl.nw = KB_NW; pl.kh = false; pl.wgp = pl.pairs; pl.chunk = tps * KT; pl.nsplit = ns; pl.ns = 0;
             }
         }
     }
-    // a batch with splits: the slots go to the sequences by length (lane i of a wavefront plans sequence i)
-    pl.balanced = pl.nsplit > 1 && B >= 2 && B <= 64 && !(h->flags & ETV_ATTN_FLAG_UNIFORM_SPLITS);
+    pl.balanced = pl.nsplit > 1 && shared_out;
     if (best == 1e30) {  // kv_split larger than the prefix: a single split
         pl.nw = (pl.pairs > 4 && !(h->flags & ETV_ATTN_FLAG_SMALL_WG)) ? 8 : 4;
         pl.kh = false;

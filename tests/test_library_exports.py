@@ -154,3 +154,20 @@ def test_unforced_fp32_and_heads_of_64_plans_fit_the_fixed_array():
         need = api.tree_verify_attention_workspace_bytes(dsc)
         assert need <= api.ATTN_STATIC_WORKSPACE_BYTES, (d, dt, B, T, Hq, Hkv, P, need)
         assert api.tree_verify_attention_plan(dsc)["n_splits"] >= 1
+
+
+def test_key_block_launches_fit_every_xcd():
+    """The key-block kernel runs where a launch fits the chip at once.  The chunks of one (split, KV head, sequence) stay on one of
+    the eight XCDs, so the fullest XCD, not the sum, has to fit its 32 compute units (two workgroups on each at heads of 64)."""
+    import random
+    rng = random.Random(3)
+    shapes = [(10, 96, 8, 2, 128, 230), (6, 107, 4, 2, 128, 2667)]
+    shapes += [(rng.randint(1, 32), rng.randint(1, 256), *rng.choice([(8, 2), (4, 2), (32, 8), (32, 32), (16, 4)]), rng.choice([64, 128]),
+                rng.choice([60, 230, 700, 2667, 9000])) for _ in range(600)]
+    taken = 0
+    for B, T, Hq, Hkv, d, P in shapes:
+        plan = api.tree_verify_attention_plan(api.AttnDesc(B=B, T_max=T, Hq=Hq, Hkv=Hkv, d=d, dtype=api.BF16, P_cap=P, P_max=P))
+        if plan["ring_stages"] == 0:
+            taken += 1
+            assert -(-B * plan["n_splits"] * Hkv // 8) * plan["row_groups"] <= (64 if d == 64 else 32), (B, T, Hq, Hkv, d, P, plan)
+    assert taken > 100
