@@ -16,6 +16,7 @@
 // Scores are kept in "scaled log2 units" t = (q.k) * scale * log2(e) so that exp is a bare v_exp_f32.
 #include "etv_common.h"
 #include <atomic>
+#include <type_traits>
 
 namespace etv {
 
@@ -358,40 +359,44 @@ __global__ void __launch_bounds__(256) attn_combine_kernel(AttnParams p) {
     // (splits shared out by length: a sequence may have far fewer than nsplit)
     const bool many = SHARED && nvalid > U;
     if (SHARED && !many && wv > 0) return;  // uniform over the workgroup, as below
-    const int step = many ? 4 : 1;
     float M = -INFINITY, L = 0.f, acc[E];
 #pragma unroll
     for (int e = 0; e < E; e++) acc[e] = 0.f;
-    for (int s0 = many ? wv : 0; s0 < nvalid; s0 += U * step) {
-        float ms[U], ls[U], os[U][E];
+    auto take = [&](auto every, int first) {  // splits first, first + every, ...
+        constexpr int step = decltype(every)::value;
+        for (int s0 = first; s0 < nvalid; s0 += U * step) {
+            float ms[U], ls[U], os[U][E];
 #pragma unroll
-        for (int u = 0; u < U; u++) {
-            const bool ok = s0 + u * step < nvalid;
-            const size_t r = pr0 + (size_t)(ok ? s0 + u * step : 0) * sstride;
-            ms[u] = ok ? p.part_m[r] : -INFINITY;
-            ls[u] = ok ? p.part_l[r] : 0.f;
+            for (int u = 0; u < U; u++) {
+                const bool ok = s0 + u * step < nvalid;
+                const size_t r = pr0 + (size_t)(ok ? s0 + u * step : 0) * sstride;
+                ms[u] = ok ? p.part_m[r] : -INFINITY;
+                ls[u] = ok ? p.part_l[r] : 0.f;
 #pragma unroll
-            for (int e = 0; e < E; e++) os[u][e] = ok ? p.part_o[r * D + (size_t)lane * E + e] : 0.f;
-        }
-        float Mb = M;
+                for (int e = 0; e < E; e++) os[u][e] = ok ? p.part_o[r * D + (size_t)lane * E + e] : 0.f;
+            }
+            float Mb = M;
 #pragma unroll
-        for (int u = 0; u < U; u++) Mb = fmaxf(Mb, ms[u]);
-        if (Mb == -INFINITY) continue;  // nothing visible in this batch or before
-        const float keep = exp2f(M - Mb);  // 0 while M is still -inf
-        L *= keep;
+            for (int u = 0; u < U; u++) Mb = fmaxf(Mb, ms[u]);
+            if (Mb == -INFINITY) continue;  // nothing visible in this batch or before
+            const float keep = exp2f(M - Mb);  // 0 while M is still -inf
+            L *= keep;
 #pragma unroll
-        for (int e = 0; e < E; e++) acc[e] *= keep;
-        M = Mb;
+            for (int e = 0; e < E; e++) acc[e] *= keep;
+            M = Mb;
 #pragma unroll
-        for (int u = 0; u < U; u++) {
-            if (ms[u] != -INFINITY) {  // absent or empty split: its l/O may be uninitialised memory
-                const float w = exp2f(ms[u] - M);
-                L = fmaf(w, ls[u], L);
+            for (int u = 0; u < U; u++) {
+                if (ms[u] != -INFINITY) {  // absent or empty split: its l/O may be uninitialised memory
+                    const float w = exp2f(ms[u] - M);
+                    L = fmaf(w, ls[u], L);
 #pragma unroll
-                for (int e = 0; e < E; e++) acc[e] = fmaf(w, os[u][e], acc[e]);
+                    for (int e = 0; e < E; e++) acc[e] = fmaf(w, os[u][e], acc[e]);
+                }
             }
         }
-    }
+    };
+    if (many) take(std::integral_constant<int, 4>{}, wv);
+    else take(std::integral_constant<int, 1>{}, 0);
     if (many) {
         __shared__ float s_m[4], s_l[4], s_acc[4][D];
         if (lane == 0) { s_m[wv] = M; s_l[wv] = L; }
