@@ -348,8 +348,9 @@ ETV_API size_t etv_lm_head_packed_bytes(int32_t V, int32_t D);
 ETV_API int32_t etv_pack_lm_head(const void *weight, int32_t V, int32_t D, void *packed, void *stream);
 
 /* ---------------------------------------------------------------------------
- * verify_epilogue -- everything after the teacher forward in one launch (two when
- * the logits have to be scanned first): the safe gather (Section 3.2 "Dummy-root
+ * verify_epilogue -- everything after the teacher forward in one launch (one more
+ * when the logits have to be scanned first, and one more where more than 16 partials
+ * per node of more than 12 nodes are left to reduce): the safe gather (Section 3.2 "Dummy-root
  * indexing"), greedy acceptance (Sections 2.3 and 5.1) and the commit of the
  * accepted rows for all layers (Section 3.1 "Commit by path indices and
  * prefix-sharing fast reorder"), with the accepted length and nodes never leaving

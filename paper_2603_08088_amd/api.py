@@ -371,7 +371,7 @@ def verify_epilogue(logits, tokens, retrieve, n_nodes, kt, vt, k_cache, v_cache,
                     gather_out: Optional[Dict[str, torch.Tensor]] = None,
                     post_out: Optional[Dict[str, torch.Tensor]] = None,
                     commit_out: Optional[Dict[str, torch.Tensor]] = None, head_V: int = 0):
-    """safe_gather_paths + evaluate_posterior + commit_accepted_kv in three launches; same tensors and results.
+    """safe_gather_paths + evaluate_posterior + commit_accepted_kv in one to three launches; same tensors and results.
     With logits=None, post_out["argmax"] is an input, or, with head_V > 0, `workspace` is the one
     lm_head_argmax(..., finish=False) returned.  Returns (gather dict, posterior dict, commit dict)."""
     if logits is None:

@@ -13,7 +13,8 @@
 // and attn_combine_kernel merges the splits by log-sum-exp.  With a single split the partial kernels write
 // the final output themselves.
 //
-// Scores are kept in "scaled log2 units" t = (q.k) * scale * log2(e) so that exp is a bare v_exp_f32.
+// Scores are kept in "scaled log2 units" t = (q.k) * scale * log2(e) so that exp is a bare v_exp_f32
+// (bf16 kernels; fp32 keeps results below the normal range).
 #include "etv_common.h"
 #include <atomic>
 #include <type_traits>
@@ -1298,7 +1299,7 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(AttnParams p) {
 //
 // B = 1, 32/8 heads of 128: T = 60, P = 2048 16.1 -> 14.0 us (4 splits instead of 8); P = 500 13.5 -> 9.4; T = 8, P = 4096
 // 14.5 -> 13.0; T = 128, P = 1024 17.8 -> 12.1.  B = 4, T = 60, P = 1000 21.6 -> 14.6; B = 32, T = 8, P = 4096 87.4 -> 82.7 us
-// (128 KiB in flight per compute unit: 6.5 TB/s); heads of 64, B = 4, T = 48, P = 900 ... 1500 13.7 us.
+// (128 KiB in flight per compute unit: 6.5 TB/s); heads of 64, B = 4, T = 48, P = 900 ... 1500 13.4 us.
 // ----------------------------------------------------------------------------------------------
 constexpr int KB_NW = 8;     // wavefronts of a workgroup
 constexpr int KB_KEYS = 32;  // keys of a block
@@ -1615,8 +1616,8 @@ __global__ void __launch_bounds__(KB_NW * 64, D == 64 ? 4 : 2) attn_blocks_kerne
 // so a query row is a lane column in both, and only the row maximum crosses lanes (c, g) -> (c, g').
 //
 // B = 2, T = 33, 16/4 heads of 128, P = 771 / 1003: 18 us (262 us with one wavefront per query row on the vector ALU,
-// which re-read every key row for each of the G * T rows); B = 1, T = 15, 4/4 heads of 64, P = 128: 6.6 us against
-// 19.7 and a combine launch of 4.0; B = 16, T = 128, P = 2048, 32/8 heads of 128: 646 us, 109 TFLOP/s (the library's fp32
+// which re-read every key row for each of the G * T rows); B = 1, T = 15, 4/4 heads of 64, P = 128: 6.7 us against
+// 19.7 and a combine launch of 4.0; B = 16, T = 128, P = 2048, 32/8 heads of 128: 659 us, 107 TFLOP/s (the library's fp32
 // matrix product reaches 144 ... 154 on this machine).
 // ----------------------------------------------------------------------------------------------
 typedef __attribute__((ext_vector_type(4))) float f32x4;
