@@ -91,8 +91,9 @@ def test_generic_kernel_shapes(dtype, d, paged):
     for (Hq, Hkv, T, P, n) in [(4, 4, 15, [128, 0, 77], [15, 9, 1]), (8, 2, 70, [200, 33], [70, 64]),
                                 (4, 2, 128, [130], [128]), (4, 2, 200, [70], [193])]:
         wl = _small(rng, len(P), T, Hq, Hkv, d, P, dtype, paged, n_nodes=n)
-        _check(wl)
-        _check(wl, kv_split=64)
+        for flags in (0, api.ATTN_FLAG_GENERIC):     # the kernel that runs by itself, and the one-row kernel
+            _check(wl, flags=flags)
+            _check(wl, kv_split=64, flags=flags)
 
 
 @pytest.mark.parametrize("T", [1, 8, 16, 31, 32, 33, 60, 64, 65, 96, 127, 128, 129, 160, 192, 193, 255, 256])
@@ -474,7 +475,8 @@ def test_long_prefix_and_many_sequences():
     rng = np.random.default_rng(1950)
     wl = _small(rng, 1, 24, 8, 2, 128, [40000], "bf16", True, q_scale=4.0)
     _check(wl)
-    _check(wl, kv_split=40000)      # one split of 625 tiles
+    for flags in (api.ATTN_FLAG_SMALL_WG, api.ATTN_FLAG_KEY_BLOCKS):
+        _check(wl, kv_split=40000, flags=flags)      # one split of 625 tiles
     B = 200
     P = [int(x) for x in rng.integers(0, 70, size=B)]
     n = [int(x) for x in rng.integers(0, 13, size=B)]
