@@ -119,8 +119,9 @@ def test_mfma_kernel_grouping_ragged_and_edge_prefixes(paged, G, Hkv):
     P = [0, 1, 63, 64, 65, 500]
     n = [40, 1, 40, 17, 40, 33]
     wl = _small(rng, len(P), 40, G * Hkv, Hkv, 128, P, "bf16", paged, n_nodes=n)
-    _check(wl)
-    _check(wl, kv_split=128)
+    for flags in (0, api.ATTN_FLAG_SMALL_WG, api.ATTN_FLAG_LARGE_WG):   # the library's pick, and the tile kernel in both sizes
+        _check(wl, flags=flags)
+        _check(wl, kv_split=128, flags=flags)
     wl4 = _small(rng, 2, 40, G * Hkv, Hkv, 128, [257, 31], "bf16", paged, q_scale=4.0)   # peaked softmax
     _check(wl4)
     _check(wl4, kv_split=64)
