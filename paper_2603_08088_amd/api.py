@@ -31,6 +31,7 @@ ATTN_FLAG_KEY_HALVES = 8
 ATTN_FLAG_LARGE_WG = 16
 ATTN_FLAG_UNIFORM_SPLITS = 32
 ATTN_FLAG_KEY_BLOCKS = 64
+ATTN_FLAG_WIDE = 128
 MAX_TREE, ATTN_MAX_TREE = 256, 256
 ATTN_STATIC_WORKSPACE_BYTES = 64 << 20
 

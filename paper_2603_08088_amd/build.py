@@ -3,6 +3,7 @@ from __future__ import annotations
 
 import importlib.util
 import os
+import runpy
 import shutil
 import subprocess
 import sys
@@ -11,6 +12,7 @@ import sysconfig
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
+GENERATED = os.path.join(CSRC, "_build")   # what the scripts of csrc write for the compiler
 LIB = os.path.join(HERE, "libeagletv.so")
 PROBE_LIB = os.path.join(HERE, "libeagletv_probe.so")   # measurement aids (include/eagletv_probe.h), separate on purpose
 BINDING = os.path.join(HERE, "_binding.so")   # the calls of the library as a Python module (csrc/binding.cpp), host code only
@@ -18,7 +20,7 @@ SOURCES = ["api.hip", "mask.hip", "attention.hip", "posterior.hip", "commit.hip"
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-         "-I", os.path.join(ROOT, "include"), "-I", CSRC]
+         "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-I", GENERATED]
 
 
 def _hipcc(sources, target, verbose, extra=()):
@@ -66,7 +68,15 @@ def _run(cmd, verbose):
         print(out)
 
 
+def _generate():
+    os.makedirs(GENERATED, exist_ok=True)
+    text = runpy.run_path(os.path.join(CSRC, "attn_wide_loop.py"))["header"]()
+    with open(os.path.join(GENERATED, "attn_wide_loop.h"), "w") as f:
+        f.write(text)
+
+
 def build(verbose: bool = False, extra=()) -> str:
+    _generate()
     _hipcc(SOURCES, LIB, verbose, extra)
     _hipcc(["probe.hip"], PROBE_LIB, verbose)
     _host_binding(verbose)

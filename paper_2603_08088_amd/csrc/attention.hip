@@ -16,6 +16,7 @@
 // Scores are kept in "scaled log2 units" t = (q.k) * scale * log2(e) so that exp is a bare v_exp_f32
 // (bf16 kernels; fp32 keeps results below the normal range).
 #include "etv_common.h"
+#include "attn_wide_loop.h"
 #include <atomic>
 #include <type_traits>
 
@@ -112,6 +113,9 @@ struct SplitShare {
     bool live;
 };
 __device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ uint64_t uni64(uint64_t v) {
+    return (uint64_t)(uint32_t)uni((int)(uint32_t)v) | (uint64_t)(uint32_t)uni((int)(uint32_t)(v >> 32)) << 32;
+}
 __device__ inline SplitShare balanced_share(const AttnParams &p, int x, int lane) {
     const bool has = lane < p.B;
     const int P_raw = has ? p.prefix_len[lane] : 0, n_raw = has ? p.n_nodes[lane] : 0;
@@ -519,6 +523,11 @@ template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
     __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | (0x7 << 4) | (0xF << 8));
 }
+// every LDS access this wavefront has issued is done (the buffer it read may be filled again)
+__device__ __forceinline__ void wait_lds_reads() {
+    __builtin_amdgcn_s_waitcnt(0xc07f);
+    asm volatile("" ::: "memory");
+}
 // max / sum of a value with its partner in the other half of the wavefront (lane ^ 32) without touching
 // LDS: v_permlane32_swap exchanges the upper 32 lanes of one register with the lower 32 of another.  (A
 // ds_bpermute shuffle here would make the wavefront wait for its pending V-fragment LDS reads as well.)
@@ -610,17 +619,18 @@ __device__ __forceinline__ void issue_full_tile(const TileLoader<D, NW> &ld, int
 }
 
 // ragged last prefix tile or tree tile: rows past the end re-read the last valid row (masked later)
-template <int D, int NW, int NS>
-__device__ __forceinline__ void issue_edge_tile(const TileLoader<D, NW> &ld, int ti) {
+template <int D, int NW>
+__device__ __forceinline__ void issue_edge_tile(const TileLoader<D, NW> &ld, int ti, int place) {
     constexpr int U = TileLoader<D, NW>::U, NI = TileLoader<D, NW>::NI;
     constexpr int ROW_BYTES = Geo<D>::ROW_BYTES, RPU = Geo<D>::RPU;
     const bool tree = ti >= ld.npt;
     const int base = tree ? (ti - ld.npt) * KT : ld.k0 + ti * KT;
     const int last = (tree ? ld.n : ld.k1) - 1;
-    const uint32_t stage = ld.smem_addr + (uint32_t)(ti % NS) * Geo<D>::STAGE_BYTES;
+    const uint32_t stage = ld.smem_addr + (uint32_t)place * Geo<D>::STAGE_BYTES;
     const bool own = tree && !ld.tail;  // rows of the step's own tree buffer
     const uint8_t *ksrc = own ? ld.kt : ld.kc;
     const uint8_t *vsrc = own ? ld.vt : ld.vc;
+    size_t offs[U];
 #pragma unroll
     for (int u = 0; u < U; u++) {
         const int j = ld.wave + NI * u;
@@ -643,9 +653,13 @@ __device__ __forceinline__ void issue_edge_tile(const TileLoader<D, NW> &ld, int
         } else {
             off = ld.seq_off + (size_t)key * ld.row_stride;
         }
-        async_load16(ksrc + off + ld.kcol, stage + j * 1024);
-        async_load16(vsrc + off + ld.vcol, stage + Geo<D>::TILE_BYTES + j * 1024);
+        offs[u] = off;
     }
+    // all of K, then all of V (attn_wide_kernel counts on the order)
+#pragma unroll
+    for (int u = 0; u < U; u++) async_load16(ksrc + offs[u] + ld.kcol, stage + (ld.wave + NI * u) * 1024);
+#pragma unroll
+    for (int u = 0; u < U; u++) async_load16(vsrc + offs[u] + ld.vcol, stage + Geo<D>::TILE_BYTES + (ld.wave + NI * u) * 1024);
 }
 
 // LDS view of one staged tile plus the per-lane fragment offsets (bytes) that do not depend on the tile.
@@ -1076,7 +1090,7 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(AttnParams p) {
             if (stream_kv) issue_full_tile<D, NW, NS, PAGED, true>(ld, t, blk_pro[t]);
             else issue_full_tile<D, NW, NS, PAGED, false>(ld, t, blk_pro[t]);
         } else {
-            issue_edge_tile<D, NW, NS>(ld, t);
+            issue_edge_tile<D, NW>(ld, t, t % NS);
         }
     }
 
@@ -1134,7 +1148,7 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(AttnParams p) {
             if (stream_kv) issue_full_tile<D, NW, NS, PAGED, true>(ld, tn, blk);
             else issue_full_tile<D, NW, NS, PAGED, false>(ld, tn, blk);
         }
-        else if (issuer && tn < nt) issue_edge_tile<D, NW, NS>(ld, tn);
+        else if (issuer && tn < nt) issue_edge_tile<D, NW>(ld, tn, tn % NS);
     };
     auto tile_vis = [&](int ti) -> uint64_t {
         if (ti < npt) return (1ull << (k1 - k0 - nfull * KT)) - 1ull;  // ragged last prefix tile: 1..63 keys
@@ -1279,6 +1293,369 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(AttnParams p) {
 }
 
 // ----------------------------------------------------------------------------------------------
+// Wide kernel (bf16, d = 128): trees of many rows over long splits.
+//
+// Work unit: (split, KV head x group of 256 rows, sequence), one workgroup of four wavefronts, one per SIMD; wavefront w owns the
+// 32-row chunks w and w + 4, so that a fragment of K or V is read from LDS once for 64 rows, and one chunk's softmax runs between
+// the matrix instructions of the other.  Swizzles and register layouts are those of attn_mfma_kernel, four ring places of 32 KiB
+// and three tiles in flight.  The loop over the tiles is written by attn_wide_loop.py.
+//
+// A tile of the loop takes 2574 cycles, of which the 64 + 16 matrix instructions are 2176.  What bounds it is the power: the clock is
+// 1.48 GHz with everything in the loop, 1.67 without the tile loads, 1.78 with the matrix instructions alone, and a tile takes 1.73,
+// 1.55 and 1.23 us.  B = 32, T = 128, P = 4096, 32/8 heads: 296 -> 258 us (two rounds of workgroups; of a round's 128 about 15
+// are start-up, the first references and the output); T = 64 158 -> 136; B = 1, T = 128, P = 32768 86 -> 79.  Against
+// the eight wavefronts of attn_mfma_kernel a round costs 4 us more and a tile a quarter less.
+// ----------------------------------------------------------------------------------------------
+typedef __attribute__((ext_vector_type(32))) float f32x32;
+typedef __attribute__((ext_vector_type(8))) uint32_t u32x8;
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+
+struct WideGeo {
+    static constexpr int NW = 4, CW = 8, NS = 4, AHEAD = 3;  // wavefronts, chunks, ring places, tiles asked for before the loop
+    static constexpr int MASKED = 3;                         // tiles with masked keys that the loop takes
+    static constexpr int RING = NS * Geo<128>::STAGE_BYTES;
+    static constexpr int Q_AT = 3 * Geo<128>::STAGE_BYTES;   // Q until the loop has read it: 16 KiB a wavefront
+    static constexpr int OUT_AT = RING;                      // outputs on their way to memory: 8 KiB a wavefront
+    static constexpr int LDS = RING + NW * 8192;             // all 160 KiB of a compute unit
+};
+
+template <bool PAGED, bool NT, bool MANY>
+__global__ void __launch_bounds__(256, 1) attn_wide_kernel(AttnParams p) {
+    constexpr int D = 128, AHEAD = WideGeo::AHEAD;
+    constexpr int ROW_BYTES = Geo<D>::ROW_BYTES, TILE_BYTES = Geo<D>::TILE_BYTES, STAGE_BYTES = Geo<D>::STAGE_BYTES;
+    constexpr int KK = Geo<D>::KK, DB = Geo<D>::DB;
+    uint8_t *const smem = attn_smem;
+    const uint32_t smem_addr = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)attn_smem;
+
+    // grid, shares of a ragged batch and the rotation of the split index: as in attn_mfma_kernel
+    const int wg = blockIdx.y / p.Hkv, kvh = blockIdx.y % p.Hkv;
+    const int tid = threadIdx.x, lane = tid & 63;
+    SplitShare share{};
+    if (p.balanced) {
+        share = balanced_share(p, (int)blockIdx.x, lane);
+        if (!share.live) return;  // uniform over the workgroup
+        if (share.j == 0 && blockIdx.y == 0 && tid == 0) p.split_tab[share.b] = make_int2(share.start, share.nvalid);
+    }
+    const int b = uni(p.balanced ? share.b : (int)blockIdx.z);
+    const int s = uni(p.balanced ? share.j : (int)((blockIdx.x + blockIdx.z) % p.nsplit));
+    const int chunk = uni(p.balanced ? share.tps * KT : p.chunk);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    asm volatile("" ::"s"(p.q), "s"(p.k_cache), "s"(p.v_cache), "s"(p.kt), "s"(p.vt), "s"(p.block_table),
+                 "s"(p.prefix_len), "s"(p.n_nodes), "s"(p.bitmask), "s"(p.T_max), "s"(p.Hq), "s"(p.G),
+                 "s"(p.max_blocks), "s"(p.P_cap), "s"(p.P_max), "s"(p.words), "s"(p.chunk), "s"(p.pairs));
+    const int k0 = uni(s * chunk);
+    const const_i32_ptr bt = (const_i32_ptr)(uintptr_t)(PAGED ? p.block_table + (size_t)b * p.max_blocks : nullptr);
+    // One trip for the sizes, the wavefront's blocks of the first full tiles (read before it is known whether the prefix reaches
+    // that far, used only if it does) and the ancestor bits of the lane's two rows.
+    const int lb0 = (k0 >> 4) + wave;
+    const bool spec = PAGED && (k0 >> 4) + 4 * AHEAD <= p.max_blocks;
+    int blk0 = 0, blk1 = 0, blk2 = 0;
+    if (spec) {
+        blk0 = bt[lb0];
+        blk1 = bt[lb0 + 4];
+        blk2 = bt[lb0 + 8];
+    }
+    const int n_raw = p.balanced ? share.n_raw : ((const_i32_ptr)(uintptr_t)p.n_nodes)[b];
+    const int P_raw = p.balanced ? share.P_raw : ((const_i32_ptr)(uintptr_t)p.prefix_len)[b];
+    // The 64 packed rows r = k * G + g (node k, head g of the group) of the wavefront's two chunks, lane i working out row i.
+    struct Row { int kq; uint32_t at; bool in_launch; };  // at: byte offset of the row in its sequence's part of Q and of the output (below
+                                                          // 2^32: at most 256 nodes of 65536 heads)
+    auto own_row = [&](int l) -> Row {
+        const int pair = wg * WideGeo::CW + wave + WideGeo::NW * (l >> 5);
+        uint32_t g;
+        const int kq = (int)fast_div((uint32_t)(pair * 32 + (l & 31)), p.G, p.inv_g, g);
+        return {kq, (uint32_t)(kq * p.Hq + kvh * p.G + (int)g) * ROW_BYTES, pair < p.pairs && kq < p.T_max};
+    };
+    // of chunk 0 and chunk 1 the row of column lane % 32
+    auto both_chunks = [&](uint32_t v, uint32_t (&of)[2]) {
+        auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+        of[0] = r[0]; of[1] = r[1];
+    };
+    const Row row = own_row(lane);
+    uint32_t kq_of[2];
+    both_chunks(row.in_launch ? (uint32_t)row.kq : 0xffffffffu, kq_of);  // no row there: no node
+    uint64_t bits0[2] = {0, 0}, bits1[2] = {0, 0}, bits2[2] = {0, 0}, bits3[2] = {0, 0};
+#pragma unroll
+    for (int x = 0; x < 2; x++) {
+        if (kq_of[x] != 0xffffffffu) {
+            const uint64_t *mrow = p.bitmask + ((size_t)b * p.T_max + kq_of[x]) * p.words;
+            bits0[x] = mrow[0];
+            if (p.words > 1) bits1[x] = mrow[1];
+            if (p.words > 2) bits2[x] = mrow[2];
+            if (p.words > 3) bits3[x] = mrow[3];
+        }
+    }
+    asm volatile("" ::"s"(n_raw), "s"(P_raw), "s"(blk0), "s"(blk1), "s"(blk2), "v"(bits0[0]), "v"(bits0[1]), "v"(bits1[0]),
+                 "v"(bits1[1]), "v"(bits2[0]), "v"(bits2[1]), "v"(bits3[0]), "v"(bits3[1]));
+    const int n = uni(clampi(n_raw, 0, p.T_max)), P = uni(clampi(P_raw, 0, p.P_max));
+    const int nvalid = uni(p.balanced ? share.nvalid : seq_nsplit(p, P));
+    if (s >= nvalid) return;  // uniform over the workgroup
+    const bool direct = (p.nsplit == 1);
+
+    const int k1 = min(P, k0 + chunk);
+    const int nfull = (k1 > k0) ? (k1 - k0) / KT : 0;
+    const int npt = (k1 > k0) ? (k1 - k0 + KT - 1) / KT : 0;
+    const int ntt = (s == nvalid - 1) ? (n + KT - 1) / KT : 0;
+    const int edges = npt - nfull + ntt;  // tiles with masked keys: edge e is tile nfull + e of the split
+
+    const bool tail = (p.kt == nullptr);
+    const size_t row_stride = (size_t)p.Hkv * ROW_BYTES, blk_stride = row_stride * 16;  // both below 2^32
+    const size_t head_at = PAGED ? (size_t)kvh * 16 * ROW_BYTES : ((size_t)b * p.P_cap * p.Hkv + kvh) * ROW_BYTES;
+    const uint8_t *const kf = static_cast<const uint8_t *>(p.k_cache) + head_at, *const vf = static_cast<const uint8_t *>(p.v_cache) + head_at;
+    const size_t tree_at = ((size_t)b * p.T_max * p.Hkv + kvh) * ROW_BYTES;
+    // the lane, anew: what is worked out from it for use ahead of and behind the loop is not kept in registers during it
+    auto again = [&]() -> int {
+        int l = lane;
+        asm volatile("" : "+v"(l));
+        return l;
+    };
+    auto fragment_view = [&](int l) -> TileView {
+        const int g16 = l >> 4, i16 = l & 15, vrow = 4 * (l >> 5) + (i16 >> 2);
+        return {(l & 31) * ROW_BYTES, kswz_of_row<D>(l & 31), vrow, vswz_of_row<D>(vrow), 2 * (g16 & 1) + ((i16 & 3) >> 1), 8 * (i16 & 1), l >> 5};
+    };
+    // A wavefront brings rows 16 w .. 16 w + 15 of a tile (of a full one: one cache block), four rows a load.  The lane's source
+    // columns under the swizzles: load j holds rows 4 j + lane / 16 of the 16.
+    struct Columns { uint32_t k[4], v[2]; };
+    auto columns = [&](int l) -> Columns {
+        Columns c;
+#pragma unroll
+        for (int j = 0; j < 4; j++) c.k[j] = (uint32_t)(((l & 15) ^ kswz_of_row<D>(4 * j + (l >> 4))) * 16);
+#pragma unroll
+        for (int j = 0; j < 2; j++) c.v[j] = (uint32_t)(((l & 15) ^ vswz_of_row<D>(4 * j + (l >> 4))) * 16);
+        return c;
+    };
+    u32x4 koff, voff;  // full tiles: the lane's pieces relative to the block
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+        const Columns c = columns(lane);
+        const uint32_t at = (uint32_t)(4 * j + (lane >> 4)) * (PAGED ? (uint32_t)ROW_BYTES : (uint32_t)row_stride);
+        koff[j] = at + c.k[j];
+        voff[j] = at + c.v[j & 1];
+    }
+    const uint32_t lds_wave = smem_addr + (uint32_t)wave * 4096;
+    auto full_offset = [&](int t, int id) -> size_t {
+        return PAGED ? (size_t)(uint32_t)uni(id) * (size_t)(uint32_t)blk_stride
+                     : (size_t)(uint32_t)(k0 + t * KT + 16 * wave) * (size_t)(uint32_t)row_stride;
+    };
+    // The loads of a tile: all of K, then all of V (the loop counts on the order).
+    auto issue_full = [&](size_t off, int place) {
+        const uint32_t dst = lds_wave + (uint32_t)place * STAGE_BYTES;
+#pragma unroll
+        for (int j = 0; j < 4; j++) async_load16_s<NT>(kf + off, koff[j], dst + j * 1024);
+#pragma unroll
+        for (int j = 0; j < 4; j++) async_load16_s<NT>(vf + off, voff[j], dst + TILE_BYTES + j * 1024);
+    };
+    // Edge e: rows past the end repeat the last one.
+    auto issue_edge = [&](int e, int place) {
+        const uint32_t dst = lds_wave + (uint32_t)place * STAGE_BYTES;
+        const int w = nfull + e - npt;  // tree tile, or -1: the ragged end of the prefix
+        const int l = again(), r0 = 16 * wave + (l >> 4);
+        const Columns col = columns(l);
+        uint32_t at[4];
+        if (w >= 0 && !tail) {  // the step's own tree buffer
+            const uint8_t *const kt = static_cast<const uint8_t *>(p.kt) + tree_at, *const vt = static_cast<const uint8_t *>(p.vt) + tree_at;
+#pragma unroll
+            for (int j = 0; j < 4; j++) at[j] = (uint32_t)min(w * KT + r0 + 4 * j, n - 1) * (uint32_t)row_stride;
+#pragma unroll
+            for (int j = 0; j < 4; j++) async_load16_s<false>(kt, at[j] + col.k[j], dst + j * 1024);
+#pragma unroll
+            for (int j = 0; j < 4; j++) async_load16_s<false>(vt, at[j] + col.v[j & 1], dst + TILE_BYTES + j * 1024);
+            return;
+        }
+        // cache positions pos0 .. last; an in-place branch cache has node j at position P + j
+        const int pos0 = w >= 0 ? P + w * KT : k0 + nfull * KT, last = w >= 0 ? P + n - 1 : k1 - 1;
+        if (!PAGED) {
+            const size_t off = (size_t)(uint32_t)pos0 * (size_t)(uint32_t)row_stride;
+#pragma unroll
+            for (int j = 0; j < 4; j++) at[j] = (uint32_t)min(r0 + 4 * j, last - pos0) * (uint32_t)row_stride;
+#pragma unroll
+            for (int j = 0; j < 4; j++) async_load16_s<false>(kf + off, at[j] + col.k[j], dst + j * 1024);
+#pragma unroll
+            for (int j = 0; j < 4; j++) async_load16_s<false>(vf + off, at[j] + col.v[j & 1], dst + TILE_BYTES + j * 1024);
+            return;
+        }
+        // 16 positions in a row lie in two blocks at most
+        const int i0 = uni(min(pos0 + 16 * wave, last) >> 4), i1 = uni(min(i0 + 1, last >> 4));
+        const int id0 = bt[i0], id1 = bt[i1];
+        const size_t b0 = (size_t)(uint32_t)uni(id0) * blk_stride, b1 = (size_t)(uint32_t)uni(id1) * blk_stride;
+        size_t off[4];
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+            const int pos = min(pos0 + r0 + 4 * j, last);
+            off[j] = ((pos >> 4) == i0 ? b0 : b1) + (uint32_t)(pos & 15) * ROW_BYTES;
+        }
+#pragma unroll
+        for (int j = 0; j < 4; j++) async_load16(kf + off[j] + col.k[j], dst + j * 1024);
+#pragma unroll
+        for (int j = 0; j < 4; j++) async_load16(vf + off[j] + col.v[j & 1], dst + TILE_BYTES + j * 1024);
+    };
+    // keys of edge e that the lane's row of chunk x sees; a row that is not there sees all, so that its sums stay finite
+    auto edge_vis = [&](int x, int e) -> uint64_t {
+        const int w = nfull + e - npt;
+        const uint64_t lo = (w & 1) ? bits1[x] : bits0[x], hi = (w & 1) ? bits3[x] : bits2[x];
+        const uint64_t vis = w < 0 ? (1ull << (k1 - k0 - nfull * KT)) - 1ull : ((w & 2) ? hi : lo);
+        return kq_of[x] < (uint32_t)n ? vis : ~0ull;
+    };
+    // Q, 1 KiB a load, laid out like K rows, to the ring's last place and the space behind it; rows that are not there repeat
+    // node 0's.
+    {
+        const uint8_t *const qseq = reinterpret_cast<const uint8_t *>(uni64((uint64_t)(uintptr_t)p.q + (size_t)b * p.T_max * p.Hq * ROW_BYTES));
+        const uint32_t from = row.in_launch && row.kq < n ? row.at : (uint32_t)(kvh * p.G) * ROW_BYTES;
+        const Columns c = columns(lane);
+        uint32_t at[16];
+#pragma unroll
+        for (int u = 0; u < 16; u++) at[u] = (uint32_t)__builtin_amdgcn_ds_bpermute(4 * (4 * u + (lane >> 4)), (int)from);
+#pragma unroll
+        for (int u = 0; u < 16; u++)
+            async_load16_s<false>(qseq, at[u] + c.k[u & 3], smem_addr + WideGeo::Q_AT + (uint32_t)wave * 16384 + u * 1024);
+    }
+
+    f32x32 oa0, oa1, ob0, ob1;  // zeroed by the first pass of the loop, beside its first products
+    float na = INFINITY, nb = INFINITY, la = 0.f, lb = 0.f;  // minus the references (-inf so far), sums
+    // The order of work: a full tile, whose maximum is the rows' first reference (over the few nodes that a row sees of the tree
+    // it would be farther from the largest score, and the largest probability is exact only where it is 1), the tiles with masked
+    // keys, the other full tiles.  The loop wants masked tiles among its first three: with a ragged end of the prefix ahead of two
+    // tree tiles that one leads, and trees of more than 128 nodes take a pass for the first three tiles (it does not touch Q's place).
+    const bool lead_full = nfull > 0 && !(edges == 3 && npt > nfull);
+    // (MANY: trees of more than 128 nodes.  Without a second pass the outputs stay in accumulation registers on the way.)
+    int e_done = 0, f_done = 0;
+    bool again_pass = edges + nfull > 0;
+#pragma unroll 1
+    while (again_pass) {
+        const uint32_t done = uni(e_done + f_done);
+        // chunk `wave` of the group and chunk `wave` + 4 (a small group is spread over the SIMDs): how many of them hold rows?
+        const uint32_t chunks = uni((int)((wg * WideGeo::CW + wave) * 32 < n * p.G) + (int)((wg * WideGeo::CW + wave + WideGeo::NW) * 32 < n * p.G));
+        const int lead = lead_full && f_done == 0 ? 1 : 0, e_left = edges - e_done;
+        const bool more = MANY && e_left > 3 - lead;  // not the last pass
+        const int ne = more ? (lead ? 2 : e_left - 3) : e_left, masked = lead + ne, nt = masked + (more ? 0 : nfull - f_done - lead);
+#pragma unroll 1
+        for (int c = 0; c < AHEAD; c++) {
+            if (c >= lead && c < masked) {
+                issue_edge(e_done + c - lead, c);
+            } else if (c < nt) {
+                const int t = f_done + (c < lead ? 0 : c - ne);  // 0, 1, 2
+                int id = t == 0 ? blk0 : (t == 1 ? blk1 : blk2);
+                if (PAGED && !spec) id = bt[lb0 + 4 * t];
+                issue_full(full_offset(t, id), c);
+            }
+        }
+        const TileView tv = fragment_view(again());
+        u32x4 vis[3];  // visible keys of the masked tiles: chunk A's two key blocks, chunk B's
+#pragma unroll
+        for (int e = 0; e < 3; e++)
+#pragma unroll
+            for (int x = 0; x < 2; x++) {
+                const uint64_t v = e >= lead && e < masked ? edge_vis(x, e_done + e - lead) : ~0ull;
+                vis[e][2 * x] = (uint32_t)v >> (4 * tv.hh);  // bits of the other half of the wavefront do not matter
+                vis[e][2 * x + 1] = (uint32_t)(v >> 32) >> (4 * tv.hh);
+            }
+        u32x8 kaddr;
+        u32x4 vaddr;
+#pragma unroll
+        for (int kk = 0; kk < KK; kk++) kaddr[kk] = smem_addr + tv.krow + (((2 * kk + tv.hh) ^ tv.ksw) << 4);
+#pragma unroll
+        for (int db = 0; db < DB; db++) vaddr[db] = smem_addr + tv.vrow * ROW_BYTES + tv.vsub + (((4 * db + tv.vchunk) ^ tv.vsw) << 4);
+        uint32_t left = uni(nt), n_masked = uni(masked), idx = uni(f_done + AHEAD - ne);  // idx: the loop's fourth tile among the full ones
+        uint64_t off = PAGED ? 0 : uni64(full_offset((int)idx, 0));
+        const uint32_t last_full = uni(nfull - 1);
+        const uint64_t ids = uni64((uint64_t)(uintptr_t)bt + (PAGED ? 4 * (uint64_t)lb0 : 0));
+        const uint64_t kbase = uni64((uint64_t)(uintptr_t)kf), vbase = uni64((uint64_t)(uintptr_t)vf);
+        const uint32_t stride = uni(PAGED ? (int)blk_stride : (int)(KT * row_stride));
+        const uint32_t lds_wave_s = uni(lds_wave), q_off = uni(WideGeo::Q_AT + wave * 16384);
+#define ETV_WIDE(LOOP) \
+        asm volatile(LOOP : "+{a[0:31]}"(oa0), "+{a[32:63]}"(oa1), "+{a[64:95]}"(ob0), "+{a[96:127]}"(ob1), \
+                     "+{v[208:215]}"(kaddr), "+{v[216:219]}"(vaddr), "+{v228}"(na), "+{v229}"(nb), "+{v230}"(la), "+{v231}"(lb), \
+                     "+{v[242:245]}"(vis[0]), "+{v[246:249]}"(vis[1]), "+{v[250:253]}"(vis[2]), "+{s40}"(left), "+{s68}"(n_masked), \
+                     "+{s[48:49]}"(off), "+{s59}"(idx) \
+                     : "{v[220:223]}"(koff), "{v[224:227]}"(voff), "{s53}"(last_full), "{s69}"(done), "{s70}"(chunks), "{s[54:55]}"(ids), "{s[60:61]}"(kbase), "{s[62:63]}"(vbase), \
+                       "{s64}"(stride), "{s65}"(lds_wave_s), "{s66}"(p.scale_log2), "{s67}"(q_off) \
+                     : ETV_WIDE_CLOBBERS)
+        if constexpr (PAGED && NT) ETV_WIDE(ETV_WIDE_LOOP_PAGED_NT);
+        else if constexpr (PAGED) ETV_WIDE(ETV_WIDE_LOOP_PAGED);
+        else if constexpr (NT) ETV_WIDE(ETV_WIDE_LOOP_FLAT_NT);
+        else ETV_WIDE(ETV_WIDE_LOOP_FLAT);
+#undef ETV_WIDE
+        e_done += ne;
+        f_done += nt - ne;
+        again_pass = more;
+        if (more) __builtin_amdgcn_s_barrier();  // nobody reads the places any more
+    }
+
+    wait_vmcnt<0>();  // nothing on its way to LDS is left behind (a sequence without keys: Q)
+    // ---- outputs, through the wavefront's own 8 KiB of LDS so that whole rows (of a group: neighbours) go out together:
+    // 32 rows of 16 pieces of 16 bytes, piece c of row r at c ^ (r % 16)
+    uint8_t *const oseq = static_cast<uint8_t *>(p.out) + (size_t)b * p.T_max * p.Hq * ROW_BYTES;
+    uint8_t *const stage = smem + WideGeo::OUT_AT + wave * 8192;
+    const int l2 = again(), col = l2 & 31, half = l2 >> 5, piece = l2 & 15, sub = l2 >> 4;
+    const Row row2 = own_row(l2);
+    uint32_t kq2[2], at2[2];
+    both_chunks(row2.in_launch ? (uint32_t)row2.kq : 0xffffffffu, kq2);
+    both_chunks(row2.at, at2);
+    const uint32_t own = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)stage + col * 256 + ((col & 15) << 4);
+    auto put = [&](int c) -> uint8_t * {  // piece c of the lane's row
+        return (uint8_t *)(__attribute__((address_space(3))) uint8_t *)(uintptr_t)(own ^ (c << 4));
+    };
+    auto send = [&](int x, uint32_t from, auto &&dst) {  // dst(v): where the 16 pieces of a row go whose lane has v = from
+        wait_lds_reads();  // the pieces are in LDS
+#pragma unroll
+        for (int i = 0; i < 8; i++) {
+            const int r_in = 4 * i + sub;
+            const uint32_t at = (uint32_t)__builtin_amdgcn_ds_bpermute(4 * (32 * x + r_in), (int)from);
+            const uint4 v = *reinterpret_cast<const uint4 *>(stage + r_in * 256 + ((piece ^ (r_in & 15)) << 4));
+            if (at != 0xffffffffu) *reinterpret_cast<uint4 *>(dst(at) + piece * 16) = v;
+        }
+        wait_lds_reads();  // the place may be written again
+    };
+#pragma unroll
+    for (int x = 0; x < 2; x++) {
+        if (wg * WideGeo::CW + wave + WideGeo::NW * x >= p.pairs) break;  // uniform over the wavefront
+        const f32x32 &o0 = x ? ob0 : oa0, &o1 = x ? ob1 : oa1;
+        const float m_run = -(x ? nb : na);
+        const bool in_launch = kq2[x] != 0xffffffffu, valid = kq2[x] < (uint32_t)n;
+        const size_t lrow = ((size_t)b * p.Hq + (at2[x] / ROW_BYTES - kq2[x] * p.Hq)) * p.T_max + kq2[x];
+        const float l_tot = half_swap_sum(x ? lb : la);
+        auto o = [&](int i) { return i < 32 ? o0[i & 31] : o1[i & 31]; };
+        if (direct) {
+            const float inv = 1.f / l_tot;
+            const bool whole = __all(valid);  // else padded rows: zeros
+#pragma unroll
+            for (int db = 0; db < DB; db++)
+#pragma unroll
+                for (int ig = 0; ig < 4; ig++) {
+                    const int at = 16 * db + 4 * ig;
+                    uint2 w = {pack_bf16x2(o(at) * inv, o(at + 1) * inv), pack_bf16x2(o(at + 2) * inv, o(at + 3) * inv)};
+                    if (!whole) w = valid ? w : uint2{0u, 0u};
+                    *reinterpret_cast<uint2 *>(put(4 * db + ig) + 8 * half) = w;
+                }
+            send(x, row2.in_launch ? row2.at : 0xffffffffu, [&](uint32_t at) { return oseq + at; });
+            if (p.lse && half == 0 && in_launch) p.lse[lrow] = valid ? (m_run + __builtin_amdgcn_logf(l_tot)) * kLn2 : -INFINITY;
+        } else {
+            // rows of the slot's partials: head, then node
+            const size_t slot_row = part_row(p, p.balanced ? (int)blockIdx.x : b * p.nsplit + s, 0, 0);
+            float *const part = p.part_o + slot_row * D;
+            const uint32_t prow = (row2.at / ROW_BYTES - row2.kq * p.Hq) * p.T_max + row2.kq;
+#pragma unroll
+            for (int hf = 0; hf < 2; hf++) {  // half a row of fp32 each time
+#pragma unroll
+                for (int y = 0; y < 2; y++)
+#pragma unroll
+                    for (int ig = 0; ig < 4; ig++) {
+                        const int at = 16 * (2 * hf + y) + 4 * ig;
+                        *reinterpret_cast<float4 *>(put(8 * y + 2 * ig + half)) = float4{o(at), o(at + 1), o(at + 2), o(at + 3)};
+                    }
+                send(x, row2.in_launch && row2.kq < n ? prow : 0xffffffffu,
+                     [&](uint32_t at) { return reinterpret_cast<uint8_t *>(part + (size_t)at * D + 64 * hf); });
+            }
+            if (half == 0 && valid) {
+                const size_t pr = slot_row + (at2[x] / ROW_BYTES - kq2[x] * p.Hq) * p.T_max + kq2[x];
+                p.part_m[pr] = m_run;
+                p.part_l[pr] = l_tot;
+            }
+        }
+    }
+}
+
+// ----------------------------------------------------------------------------------------------
 // Key-block kernel (bf16, d = 128 or 64): launches that are short of work.
 //
 // Work unit: (split, KV head, sequence) x 32-row chunk of the KV head's packed query rows, one workgroup of eight
@@ -1318,11 +1695,6 @@ struct KbGeo {
 __device__ __forceinline__ void async_load4(const void *gptr, uint32_t lds_addr) {
     asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off\n" ::"v"(gptr),
                  "s"(__builtin_amdgcn_readfirstlane(lds_addr)) : "memory");
-}
-// every LDS read this wavefront has issued is done (the buffer it read may be filled again)
-__device__ __forceinline__ void wait_lds_reads() {
-    __builtin_amdgcn_s_waitcnt(0xc07f);
-    asm volatile("" ::: "memory");
 }
 
 template <int D, bool PAGED>
@@ -1920,6 +2292,7 @@ struct Plan {
     bool mfma, kh;  // mfma: attn_mfma_kernel
     bool f32;       // attn_f32_kernel
     bool blocks;    // attn_blocks_kernel
+    bool wide;      // attn_wide_kernel (nw counts its 32-row chunks, two to a wavefront)
     int nw, ns, pairs, wgp, chunk, nsplit;
     bool balanced;  // split slots shared out among the sequences by their lengths, on the device
 };
@@ -1959,6 +2332,60 @@ static bool beyond_array(const etv_attn_desc *h, int ns) { return ns > 1 && spli
 // The next split count worth a look: with tps tiles per split now, the smallest count whose splits are shorter (the counts
 // between differ only in empty splits).  Some 2 * sqrt(tiles) candidates instead of all of them, on every call.
 static int next_split_count(int tiles, int tps) { return tps > 1 ? (tiles + tps - 2) / (tps - 1) : tiles + 1; }
+
+// Launch shape of a bf16 call with heads of 128 on the tile kernels.  Microseconds, fitted to 2900 timings of 170 workloads (B = 1 ... 32,
+// T = 6 ... 256, P = 60 ... 32768, every shape at up to twelve split counts): a round of workgroups costs its tiles and a start-up;
+// a tile costs the more, the more of the chip's wavefronts have rows (the clock follows the power); K/V bytes on top, and splits as
+// before.  The pick is within 1.0 % of the best measured shape on average (before: 7 %) and at most 1.7 % behind the pick of the
+// earlier rule, 6 % ahead of it on average.  The wide kernel passes the eight wavefronts of the tile kernel from about 12 tiles a split on: 2 tiles 1.06,
+// 10 tiles 0.98, 20 tiles 0.92, 65 tiles 0.80 of its time.
+struct TileShape {
+    int nw, kh, wide;                        // chunks of a workgroup: nw, with key halves nw / 2
+    double alone, least, full, start;        // a tile alone on a compute unit (nw = 4), with few, with all wavefronts busy; a round
+};
+constexpr TileShape kTileShapes[] = {{8, 0, 1, 0.0, 1.05, 1.22, 7.8}, {8, 0, 0, 0.0, 1.31, 1.81, 4.0}, {8, 1, 0, 0.0, 0.82, 1.06, 4.55},
+                                     {4, 0, 0, 1.27, 1.61, 1.95, 3.15}, {4, 1, 0, 0.77, 1.12, 1.30, 2.95}};
+
+static bool shape_allowed(const etv_attn_desc *h, int pairs, int nw, int kh) {
+    if (kh && (h->flags & ETV_ATTN_FLAG_WHOLE_TILE)) return false;
+    if (!kh && (h->flags & ETV_ATTN_FLAG_KEY_HALVES)) return false;
+    // larger workgroups only for more chunks than the smaller ones hold
+    if (nw == 8 && (pairs <= (kh ? 2 : 4) || (h->flags & ETV_ATTN_FLAG_SMALL_WG))) return false;
+    if (nw == 4 && (h->flags & ETV_ATTN_FLAG_LARGE_WG) && pairs > (kh ? 2 : 4)) return false;
+    return true;
+}
+
+static void pick_tile_shape(const etv_attn_desc *h, Plan &pl) {
+    const int tiles = max(1, (h->P_max + KT - 1) / KT), B = max(1, h->B);
+    const int forced_tps = h->kv_split > 0 ? min(tiles, (h->kv_split + KT - 1) / KT) : 0;
+    const double part_us = 2.0 * B * h->Hq * h->T_max * (h->d + 2.0) * 4.0 / 3.0e6;
+    const double fixed = 4.7 + 4.0 * B * h->P_max * (double)h->Hkv * h->d / 33.5e6;
+    const int tree_tiles = (h->T_max + KT - 1) / KT;
+    double best = 1e30;
+    for (const TileShape &sh : kTileShapes) {
+        if (!shape_allowed(h, pl.pairs, sh.nw, sh.kh)) continue;
+        if (!sh.wide && (h->flags & ETV_ATTN_FLAG_WIDE) && pl.pairs > 4) continue;
+        const int cw = sh.kh ? sh.nw / 2 : sh.nw, wgp = (pl.pairs + cw - 1) / cw;
+        const long units = (long)B * h->Hkv * wgp;
+        const double held = (double)pl.pairs / (wgp * cw);  // part of a workgroup's chunks that have rows
+        for (int ns = forced_tps ? (tiles + forced_tps - 1) / forced_tps : 1, tps; ns <= tiles; ns = forced_tps ? tiles + 1 : next_split_count(tiles, tps)) {
+            tps = forced_tps ? forced_tps : (tiles + ns - 1) / ns;
+            if (!forced_tps && beyond_array(h, ns)) break;
+            const long wgs = units * ns;
+            const bool alone = sh.nw == 4 && wgs <= 256;
+            const double slots = sh.nw == 4 && !alone ? 512.0 : 256.0;
+            const double busy = sh.full * held * (wgs < slots ? wgs / slots : 1.0);
+            const double tile = alone ? sh.alone : (busy > sh.least ? busy : sh.least);
+            const double est = ceil(wgs / slots) * ((tps + tree_tiles * (ns > 1 ? 0.67 : 1.0)) * tile + sh.start) + fixed +
+                               (ns > 1 ? 3.2 + ns * part_us * 0.51 : 0.0);
+            if (est < best) {
+                best = est;
+                pl.nw = sh.nw; pl.kh = sh.kh; pl.wide = sh.wide; pl.wgp = wgp; pl.chunk = tps * KT; pl.nsplit = ns;
+                pl.ns = sh.nw == 8 || alone ? 4 : 2;  // ring places
+            }
+        }
+    }
+}
 
 static Plan make_plan(const etv_attn_desc *h) {
     Plan pl{};
@@ -2022,11 +2449,7 @@ static Plan make_plan(const etv_attn_desc *h) {
     for (int nw = 4; nw <= 8 && !blocks_only; nw += 4) {
         for (int kh = 0; kh <= 1; kh++) {
             const int cw = kh ? nw / 2 : nw;  // chunks per workgroup
-            // key halves pay when a workgroup would otherwise have idle wavefronts
-            if (kh && (h->flags & ETV_ATTN_FLAG_WHOLE_TILE)) continue;
-            if (!kh && (h->flags & ETV_ATTN_FLAG_KEY_HALVES)) continue;
-            if (nw == 8 && (pl.pairs <= (kh ? 2 : 4) || (h->flags & ETV_ATTN_FLAG_SMALL_WG))) continue;
-            if (nw == 4 && (h->flags & ETV_ATTN_FLAG_LARGE_WG) && pl.pairs > (kh ? 2 : 4)) continue;
+            if (!shape_allowed(h, pl.pairs, nw, kh)) continue;
             const int wgp = (pl.pairs + cw - 1) / cw;
             const long units = (long)B * h->Hkv * wgp;
             // candidates: every distinct number of splits, or the one split size the caller asks for
@@ -2051,7 +2474,8 @@ static Plan make_plan(const etv_attn_desc *h) {
             }
         }
     }
-    constexpr int kShapeFlags = ETV_ATTN_FLAG_SMALL_WG | ETV_ATTN_FLAG_LARGE_WG | ETV_ATTN_FLAG_WHOLE_TILE | ETV_ATTN_FLAG_KEY_HALVES;
+    constexpr int kShapeFlags = ETV_ATTN_FLAG_SMALL_WG | ETV_ATTN_FLAG_LARGE_WG | ETV_ATTN_FLAG_WHOLE_TILE | ETV_ATTN_FLAG_KEY_HALVES |
+                                ETV_ATTN_FLAG_WIDE;
     if (blocks_only || !(h->flags & kShapeFlags)) {
         // Key-block kernel against the pick so far, for launches that fit the chip at once (one workgroup per compute unit, two
         // at d = 64): a further round pays start-up and merge again, and the other kernel is then always ahead.  Microseconds,
@@ -2089,10 +2513,11 @@ static Plan make_plan(const etv_attn_desc *h) {
             }
         }
     }
+    if (h->d == 128 && !pl.blocks) pick_tile_shape(h, pl);
     pl.balanced = pl.nsplit > 1 && shared_out;
     if (best == 1e30) {  // kv_split larger than the prefix: a single split
         pl.nw = (pl.pairs > 4 && !(h->flags & ETV_ATTN_FLAG_SMALL_WG)) ? 8 : 4;
-        pl.kh = false;
+        pl.kh = false; pl.wide = false;
         pl.wgp = (pl.pairs + pl.nw - 1) / pl.nw;
         pl.chunk = tiles * KT; pl.nsplit = 1; pl.ns = pl.nw == 8 ? 4 : 2;
     }
@@ -2111,6 +2536,18 @@ static int32_t launch_mfma(const AttnParams &p, dim3 grid, hipStream_t st) {
     return check_launch();
 }
 
+template <bool PAGED, bool NT, bool MANY>
+static int32_t launch_wide(const AttnParams &p, dim3 grid, hipStream_t st) {
+    constexpr size_t lds = WideGeo::LDS;
+    static const bool lds_ok = [] {
+        return hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_wide_kernel<PAGED, NT, MANY>),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) == hipSuccess;
+    }();
+    if (!lds_ok) return ETV_ERR_HIP;
+    hipLaunchKernelGGL((attn_wide_kernel<PAGED, NT, MANY>), grid, dim3(256), lds, st, p);
+    return check_launch();
+}
+
 template <int D, bool PAGED>
 static int32_t launch_blocks(const AttnParams &p, dim3 grid, hipStream_t st) {
     static const bool lds_ok = [] {
@@ -2126,6 +2563,19 @@ static int32_t launch_blocks(const AttnParams &p, dim3 grid, hipStream_t st) {
 // 4 wavefronts: two workgroups per compute unit with 2 stages each, or 4 stages when the grid is small
 template <int D>
 static int32_t launch_mfma_shape(const Plan &pl, bool paged, const AttnParams &p, dim3 grid, hipStream_t st) {
+    if constexpr (D == 128)
+        if (pl.wide) {
+            switch ((paged ? 4 : 0) + (p.wgp == 1 ? 2 : 0) + (p.T_max > 128 ? 1 : 0)) {
+            case 0: return launch_wide<false, false, false>(p, grid, st);
+            case 1: return launch_wide<false, false, true>(p, grid, st);
+            case 2: return launch_wide<false, true, false>(p, grid, st);
+            case 3: return launch_wide<false, true, true>(p, grid, st);
+            case 4: return launch_wide<true, false, false>(p, grid, st);
+            case 5: return launch_wide<true, false, true>(p, grid, st);
+            case 6: return launch_wide<true, true, false>(p, grid, st);
+            default: return launch_wide<true, true, true>(p, grid, st);
+            }
+        }
     const int shape = (pl.nw == 8 ? 0 : (pl.ns == 4 ? 1 : 2)) * 4 + (paged ? 2 : 0) + (pl.kh ? 1 : 0);
     switch (shape) {
     case 0: return launch_mfma<D, 8, 4, false, false>(p, grid, st);
@@ -2200,7 +2650,7 @@ static int32_t attention_run(const etv_attn_desc *h, const void *q, const void *
     if ((long)h->B * pl.nsplit > 65535 && !pl.mfma && !pl.f32) return ETV_ERR_UNSUPPORTED;
     if (pl.f32 && f32_blocks(h, pl) > 0x7fffffffL) return ETV_ERR_UNSUPPORTED;
     if (pl.nsplit > 1) {
-        if (!workspace || workspace_bytes < etv_tree_verify_attention_workspace_bytes(h))
+        if (!workspace || workspace_bytes < split_workspace(h, pl.nsplit))
             return ETV_ERR_WORKSPACE_TOO_SMALL;
     }
     AttnParams p{};

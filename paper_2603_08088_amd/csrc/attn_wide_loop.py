@@ -1,0 +1,481 @@
+"""Writes the tile loop of attn_wide_kernel (attention.hip) as one asm statement per variant: attn_wide_loop.h.
+
+Why not HIP: the loop keeps 430 registers live in fixed places and interleaves three streams (matrix instructions, softmax,
+LDS reads) at the grain of one instruction.  The compiler moves the scores through accumulation registers and issues the
+fragment reads three or four products ahead of their use, whatever scheduling directives say.
+
+One wavefront per SIMD, two 32-row chunks A and B.  A section is 32 matrix instructions of one chunk and, between them, the
+softmax of the other:
+
+    section A(t):  PV(A, t), QK(A, t + 1)   beside   softmax(B, t)        reads K(t + 1) from LDS for its own second half
+    section B(t):  PV(B, t), QK(B, t + 1)   beside   softmax(A, t + 1)    reads V(t + 1) from LDS for section A(t + 1)
+
+so a fragment is read once for 64 query rows, 16 ... 32 matrix instructions ahead of its first use.  The barrier that hands
+over tiles stands at the head of section B(t): V(t + 1) and K(t + 2) have arrived, and every wavefront is done with V(t) and
+K(t + 1), whose places are refilled with V(t + 4) and K(t + 5).
+
+The first tiles of a split (up to three: the tree, a ragged end of the prefix) have masked keys: their scores' places in the
+softmax go through the row's visibility bits.
+
+The softmax takes no maximum: probabilities are 2^(score - reference), and their sum over the lane's keys, which is needed
+anyway, tells whether the reference is too low (a sum above 2^20, or not a number).  Only then the row's maximum is taken, O
+and l are rescaled and the probabilities computed again (`lift`).
+
+Registers.  v0 ... v31 stay with the compiler.  Score of key 32 kb + 8 (i / 4) + 4 (lane / 32) + i % 4 at S + 16 kb + i.
+"""
+SA, SB = 32, 64            # scores: 2 key blocks x 16
+PA, PB = 96, 112           # probabilities, bf16 pairs: [key block][8]
+VF = 128                   # V^T fragments: 16 x 4, in the order of the value product
+TMP, PAIRS = 192, 6        # 6 pairs of temporaries
+X = 204                    # 4 temporaries of lift and of the masked softmax
+KADDR, VADDR = 208, 216    # LDS addresses of the fragments: 8 and 4
+KOFF, VOFF = 220, 224      # byte offsets of a lane's 16-byte pieces from the base of a 16-key block: 4 and 4
+NMA, NMB, LA, LB = 228, 229, 230, 231    # minus the reference, sum of the probabilities
+SUM = 232                  # a tile's sums, in two chains; each is there four times
+MASK = 242                 # visible keys, [tile][chunk][key block]: bit 8 (i / 4) + i % 4 for score i
+ONES = 254                 # four bf16 ones
+OA, OB, QA, QB, KF = 0, 64, 128, 160, 192    # accumulation registers: outputs, query fragments, K fragments (16 x 4)
+
+# scalar registers of the loop
+S_LEFT, S_STAGE, S_NEXT, S_DELTA, S_LIMIT, S_NINF = 40, 41, 42, 43, 44, 45
+S_ID3, S_ID4, S_OFF, S_BASE, S_ID, S_LAST, S_BT, S_LIFT, S_TMP, S_IDX = 46, 47, 48, 50, 52, 53, 54, 56, 58, 59
+S_KP, S_VP, S_STRIDE, S_LDS, S_SCALE, S_Q, S_MASKED, S_DONE, S_CHUNKS = 60, 62, 64, 65, 66, 67, 68, 69, 70
+
+TILE, STAGE, RING = 16384, 32768, 131072
+
+
+class Out:
+    def __init__(self):
+        self.lines = []
+
+    def __call__(self, *ops):
+        for op in ops:
+            self.lines.append(op)
+
+
+def v(r, n=1):
+    return f"v{r}" if n == 1 else f"v[{r}:{r + n - 1}]"
+
+
+def a(r, n=1):
+    return f"a{r}" if n == 1 else f"a[{r}:{r + n - 1}]"
+
+
+def s(r, n=1):
+    return f"s{r}" if n == 1 else f"s[{r}:{r + n - 1}]"
+
+
+class Chunk:
+    def __init__(self, name):
+        first = name == "A"
+        self.name = name
+        self.S, self.P, self.O, self.Q = (SA, PA, OA, QA) if first else (SB, PB, OB, QB)
+        self.nm, self.l = (NMA, LA) if first else (NMB, LB)
+        self.mask = MASK + (0 if first else 2)
+
+
+A, B = Chunk("A"), Chunk("B")
+
+
+# ---------------------------------------------------------------------------------------------------------------
+# the three streams
+# ---------------------------------------------------------------------------------------------------------------
+def qk_products(c):
+    """16 products; product i needs K fragment i = 2 kk + kb."""
+    r = []
+    for kk in range(8):
+        for kb in range(2):
+            d = v(c.S + 16 * kb, 16)
+            r.append((f"v_mfma_f32_32x32x16_bf16 {d}, {a(KF + 4 * (2 * kk + kb), 4)}, {a(c.Q + 4 * kk, 4)}, {'0' if kk == 0 else d}",
+                      (("K", 2 * kk + kb), ("Q" + c.name, kk))))
+    return r
+
+
+def pv_products(c):
+    """16 products; product i needs V fragment i = (2 kb + st) * 4 + db."""
+    r = []
+    for ks in range(4):
+        for db in range(4):
+            o = a(c.O + 16 * db, 16)
+            r.append((f"v_mfma_f32_32x32x16_bf16 {o}, {v(VF + 4 * (4 * ks + db), 4)}, {v(c.P + 4 * ks, 4)}, {o}", (("V", 4 * ks + db),)))
+    return r
+
+
+def k_reads():
+    return [(f"ds_read_b128 {a(KF + 4 * (2 * kk + kb), 4)}, {v(KADDR + kk)} offset:{8192 * kb}", ("K", 2 * kk + kb))
+            for kk in range(8) for kb in range(2)]
+
+
+def v_reads():
+    r = []
+    for ks in range(4):
+        for db in range(4):
+            f = 4 * ks + db
+            for half in range(2):
+                r.append((f"ds_read_b64_tr_b16 {v(VF + 4 * f + 2 * half, 2)}, {v(VADDR + db)} offset:{TILE + 4096 * ks + 2048 * half}", ("V", f)))
+    return r
+
+
+def mask_bit(i):
+    return 8 * (i >> 2) + (i & 3)
+
+
+def softmax(c, masked=False):
+    """P = 2^(S * scale - reference) as bf16 pairs and the sum over them: a list of instructions, two or more apart where one
+    needs the other (a transcendental result may be read by the second instruction behind it at the earliest, a matrix
+    instruction may read what is two behind).
+
+    The sum is over the rounded probabilities, the weights of the value product (over the unrounded ones the error against
+    float64 grows by 0.5 %).  v_mfma_f32_4x4x4_16b_bf16 with ones adds up the four of two registers lane by lane; in groups of four,
+    since a change between the two sizes of matrix instructions costs a dozen cycles.  A tile of the loop takes 2574 cycles with it
+    (one by one 2614), with v_dot2_f32_bf16 3046 (groups of 16: 2693), with the pairs taken apart for v_add_f32 2697."""
+    fma, hide, exp, cvt, add, group = [], [], [], [], [], []
+    for i in range(16):
+        s0, t0 = c.S + 2 * i, TMP + 2 * (i % PAIRS)
+        fma.append([f"v_fma_f32 {v(t0 + x)}, {v(s0 + x)}, {s(S_SCALE)}, {v(c.nm)}" for x in range(2)])
+        if masked:
+            m0 = X + 2 * (i % 2)
+            fma[-1] += [f"v_bfe_i32 {v(m0 + x)}, {v(c.mask + i // 8)}, {mask_bit(2 * (i % 8) + x)}, 1" for x in range(2)]
+            hide.append([f"v_bfi_b32 {v(t0 + x)}, {v(m0 + x)}, {v(t0 + x)}, {s(S_NINF)}" for x in range(2)])
+        exp.append([f"v_exp_f32 {v(t0 + x)}, {v(t0 + x)}" for x in range(2)])
+        cvt.append([f"v_cvt_pk_bf16_f32 {v(c.P + i)}, {v(t0)}, {v(t0 + 1)}"])
+        if i % 2:
+            total = v(SUM + 4 * (i // 2 % 2), 4)
+            group.append(f"v_mfma_f32_4x4x4_16b_bf16 {total}, {v(ONES, 2)}, {v(c.P + i - 1, 2)}, {total if i > 3 else 0}")
+        add.append([])
+        if i % 8 == 7:
+            group.insert(2, "s_nop 0")    # two wait states between those of a chain
+            add[-1], group = group, []
+    stages = (fma, hide, exp, cvt, add) if masked else (fma, exp, cvt, add)
+    r = []
+    for i in range(16 + len(stages) - 1):
+        for lag, ops in enumerate(stages):
+            if 0 <= i - lag < 16:
+                r += ops[i - lag]
+        if i == 16 + len(stages) - 2:
+            r.insert(len(r) - 5, "s_nop 1")
+    return r
+
+
+def check(o, c, label, masked=False):
+    """The tile's sum; out of line to `lift` where the reference is too low."""
+    o("s_nop 4", f"v_add_f32 {v(SUM)}, {v(SUM)}, {v(SUM + 4)}", f"v_cmp_nle_f32 vcc, {v(SUM)}, {s(S_LIMIT)}",
+      f"s_cbranch_vccnz .Llift_{label}%=", f".Llifted_{label}%=:", f"v_add_f32 {v(c.l)}, {v(c.l)}, {v(SUM)}")
+    if masked:   # on to the next tile's bits; behind the masked tiles all keys are visible
+        o(*[f"v_mov_b32 {v(c.mask + 4 * x + y)}, {v(c.mask + 4 * x + 4 + y) if x < 2 else '-1'}" for x in range(3) for y in range(2)])
+    LIFTS.append((c, label, masked))
+
+
+LIFTS = []
+
+
+def lift(o, c, label, masked):
+    """vcc: lanes whose sum failed.  A row is in the lanes l and l + 32; the rows that did not fail keep their reference and are
+    computed again to the same values."""
+    o(f".Llift_{label}%=:", "s_nop 15", f"s_or_b32 {s(S_LIFT)}, vcc_lo, vcc_hi", f"s_mov_b32 {s(S_LIFT + 1)}, {s(S_LIFT)}")
+    if masked:
+        for i in range(0, 32, 2):
+            o(*[f"v_bfe_i32 {v(TMP + x)}, {v(c.mask + i // 16)}, {mask_bit(i % 16 + x)}, 1" for x in range(2)])
+            o(*[f"v_bfi_b32 {v(TMP + x)}, {v(TMP + x)}, {v(c.S + i + x)}, {s(S_NINF)}" for x in range(2)])
+            o(f"v_maximum3_f32 {v(X)}, {v(X) if i else v(TMP)}, {v(TMP)}, {v(TMP + 1)}")
+    else:
+        o(f"v_maximum3_f32 {v(X)}, {v(c.S)}, {v(c.S + 1)}, {v(c.S + 2)}")
+        for i in range(3, 31, 2):
+            o(f"v_maximum3_f32 {v(X)}, {v(X)}, {v(c.S + i)}, {v(c.S + i + 1)}")
+        o(f"v_max_f32 {v(X)}, {v(X)}, {v(c.S + 31)}")
+    o(f"v_mov_b32 {v(X + 1)}, {v(X)}", "s_nop 1",
+      f"v_permlane32_swap_b32 {v(X)}, {v(X + 1)}", "s_nop 1", f"v_max_f32 {v(X)}, {v(X)}, {v(X + 1)}",
+      f"v_mul_f32 {v(X)}, {s(S_SCALE)}, {v(X)}",
+      f"v_cndmask_b32_e64 {v(X)}, {v(c.nm)}, -{v(X)}, {s(S_LIFT, 2)}",        # minus the new reference
+      f"v_sub_f32 {v(X + 1)}, {v(X)}, {v(c.nm)}", f"v_exp_f32 {v(X + 1)}, {v(X + 1)}", f"v_mov_b32 {v(c.nm)}, {v(X)}",
+      f"v_cmp_neq_f32 vcc, 0, {v(c.l)}",
+      f"v_cndmask_b32_e64 {v(X + 1)}, 1.0, {v(X + 1)}, {s(S_LIFT, 2)}", f"s_cbranch_vccz .Lempty_{label}%=",   # nothing to rescale yet
+      f"v_mul_f32 {v(c.l)}, {v(c.l)}, {v(X + 1)}")
+    for g in range(0, 64, 8):
+        o(*[f"v_accvgpr_read_b32 {v(TMP + i)}, {a(c.O + g + i)}" for i in range(8)])
+        o(*[f"v_mul_f32 {v(TMP + i)}, {v(TMP + i)}, {v(X + 1)}" for i in range(8)])
+        o(*[f"v_accvgpr_write_b32 {a(c.O + g + i)}, {v(TMP + i)}" for i in range(8)])
+    o(f".Lempty_{label}%=:")
+    o(*softmax(c, masked))
+    o("s_nop 4", f"v_add_f32 {v(SUM)}, {v(SUM)}, {v(SUM + 4)}", f"s_branch .Llifted_{label}%=")
+
+
+# ---------------------------------------------------------------------------------------------------------------
+# tile loads: wavefront w brings the 16 keys 16 w ... of a tile, four loads of four rows for K and for V
+# ---------------------------------------------------------------------------------------------------------------
+def loads(what, place, nt):
+    """Instructions, in order, for K or V of the tile at S_OFF; `place`: the ring place, a scalar register or a number."""
+    base, voff, at = (S_KP, KOFF, 0) if what == "K" else (S_VP, VOFF, TILE)
+    r = [f"s_add_u32 {s(S_BASE)}, {s(base)}, {s(S_OFF)}", f"s_addc_u32 {s(S_BASE + 1)}, {s(base + 1)}, {s(S_OFF + 1)}",
+         f"s_add_u32 {s(S_TMP)}, {s(S_LDS)}, {place}"]
+    for j in range(4):
+        r.append(f"s_add_u32 m0, {s(S_TMP)}, {at + 1024 * j}")
+        r.append("s_nop 0")
+        r.append(f"global_load_lds_dwordx4 {v(voff + j)}, {s(S_BASE, 2)}{' nt' if nt else ''}")
+    return r
+
+
+def next_offset(paged, ident=S_ID):
+    """S_OFF: byte offset of the wavefront's 16 keys of the next tile, from a block id (paged) or by counting on (contiguous)."""
+    if paged:
+        return [f"s_mul_i32 {s(S_OFF)}, {s(ident)}, {s(S_STRIDE)}", f"s_mul_hi_u32 {s(S_OFF + 1)}, {s(ident)}, {s(S_STRIDE)}"]
+    return [f"s_add_u32 {s(S_OFF)}, {s(S_OFF)}, {s(S_STRIDE)}", f"s_addc_u32 {s(S_OFF + 1)}, {s(S_OFF + 1)}, 0"]
+
+
+def fetch_id(dst, paged):
+    """Block id of tile S_IDX, which then counts on; behind the last tile the last one's."""
+    if not paged:
+        return []
+    return [f"s_min_u32 {s(S_TMP)}, {s(S_IDX)}, {s(S_LAST)}", f"s_lshl_b32 {s(S_TMP)}, {s(S_TMP)}, 4",
+            f"s_load_dword {s(dst)}, {s(S_BT, 2)}, {s(S_TMP)}", f"s_add_u32 {s(S_IDX)}, {s(S_IDX)}, 1"]
+
+
+# ---------------------------------------------------------------------------------------------------------------
+# sections
+# ---------------------------------------------------------------------------------------------------------------
+class Reads:
+    """LDS reads in flight, oldest first: how far the counter may stand when a fragment is needed."""
+
+    def __init__(self):
+        self.queue = []
+
+    def issue(self, tag):
+        self.queue.append(tag)
+
+    def wait_for(self, o, tag):
+        if tag not in self.queue:
+            return
+        last = len(self.queue) - 1 - self.queue[::-1].index(tag)
+        newer = len(self.queue) - 1 - last
+        o(f"s_waitcnt lgkmcnt({min(15, newer)})")
+        del self.queue[:max(last + 1, len(self.queue) - 15)]
+
+
+def section(o, products, valu, reads, flying, extra=(), valu_from=3, valu_to=None):
+    """Matrix instructions with the other streams between them.  reads: (slot, instruction, tag); extra: (slot, instruction)."""
+    n = len(products)
+    valu_to = n if valu_to is None else valu_to
+    done = 0
+    for i, (text, need) in enumerate(products):
+        for tag in need:
+            flying.wait_for(o, tag)
+        o(text)
+        for slot, ins, tag in reads:
+            if slot == i:
+                o(ins)
+                flying.issue(tag)
+        for slot, ins in extra:
+            if slot == i:
+                o(ins)
+        if i >= valu_from:
+            upto = len(valu) if i >= valu_to - 1 else (len(valu) * (i + 1 - valu_from)) // (valu_to - valu_from)
+            o(*valu[done:upto])
+            done = upto
+    o(*valu[done:])
+
+
+def spread(ops, first, per_slot=1.0):
+    return [(int(first + i / per_slot), op) for i, op in enumerate(ops)]
+
+
+def section_a(o, flying, nm, masked=False):
+    """PV(A, t), QK(A, t + 1) | softmax(B, t); K(t + 1) is read in the first half."""
+    reads = [(i, ins, tag) for i, (ins, tag) in enumerate(k_reads())]
+    move = [f"v_add_u32 {v(VADDR + x)}, {s(S_DELTA)}, {v(VADDR + x)}" for x in range(4)]
+    section(o, pv_products(A) + qk_products(A), softmax(B, masked), reads, flying, spread(move, 20))
+    check(o, B, f"B{nm}", masked)
+
+
+def hand_over(o, nm, paged, nt, steady):
+    """The head of section B(t): wait for V(t + 1) and K(t + 2), barrier, ask for V(t + 4) and K(t + 5).  steady: both of these
+    exist; the scalar instructions that remain to be issued are returned."""
+    if steady:
+        o("s_waitcnt vmcnt(16) lgkmcnt(0)")
+    else:   # towards the last tile: fewer loads are behind the ones that are needed
+        o("s_waitcnt lgkmcnt(0)", f"s_cmp_gt_u32 {s(S_LEFT)}, 4", f"s_cbranch_scc1 .Lw16_{nm}%=", f"s_cmp_eq_u32 {s(S_LEFT)}, 4",
+          f"s_cbranch_scc1 .Lw12_{nm}%=", f"s_cmp_eq_u32 {s(S_LEFT)}, 3", f"s_cbranch_scc1 .Lw4_{nm}%=", "s_waitcnt vmcnt(0)",
+          f"s_branch .Lw_{nm}%=", f".Lw4_{nm}%=:", "s_waitcnt vmcnt(4)", f"s_branch .Lw_{nm}%=", f".Lw12_{nm}%=:", "s_waitcnt vmcnt(12)",
+          f"s_branch .Lw_{nm}%=", f".Lw16_{nm}%=:", "s_waitcnt vmcnt(16)", f".Lw_{nm}%=:")
+    o("s_barrier")
+    ask_v, ask_k = loads("V", s(S_STAGE), nt), next_offset(paged) + loads("K", s(S_NEXT), nt) + fetch_id(S_ID, paged)
+    scalar = []
+    if steady:
+        scalar += ask_v + ask_k
+    else:
+        o(f"s_cmp_lt_u32 {s(S_LEFT)}, 5", f"s_cbranch_scc1 .Lnone_{nm}%=", *ask_v)
+        o(f"s_cmp_lt_u32 {s(S_LEFT)}, 6", f"s_cbranch_scc1 .Lnone_{nm}%=", *ask_k)
+        o(f".Lnone_{nm}%=:")
+    # ring places of the next iteration
+    return scalar + [f"s_mov_b32 {s(S_STAGE)}, {s(S_NEXT)}", f"s_add_u32 {s(S_NEXT)}, {s(S_NEXT)}, {STAGE}",
+                     f"s_and_b32 {s(S_NEXT)}, {s(S_NEXT)}, {RING - 1}", f"s_sub_i32 {s(S_DELTA)}, {s(S_NEXT)}, {s(S_STAGE)}",
+                     f"s_sub_u32 {s(S_LEFT)}, {s(S_LEFT)}, 1"]
+
+
+def section_b(o, flying, nm, paged, nt, steady, masked=False):
+    """PV(B, t), QK(B, t + 1) | softmax(A, t + 1); V(t + 1) is read as its fragments' last uses go by."""
+    scalar = hand_over(o, nm, paged, nt, steady)
+    flying.queue.clear()
+    extra = spread(scalar, 0, 2.0)
+    last = max([slot for slot, _ in extra])
+    extra += spread([f"v_add_u32 {v(KADDR + x)}, {s(S_DELTA)}, {v(KADDR + x)}" for x in range(8)], max(last + 1, 20))
+    reads = [(max(i // 2 + 1, i), ins, tag) for i, (ins, tag) in enumerate(v_reads())]
+    section(o, pv_products(B) + qk_products(B), softmax(A, masked), reads, flying, extra)
+    check(o, A, f"A{nm}", masked)
+
+
+def after_v_reads():
+    """The LDS reads in flight where section A(t) begins: those of V(t)."""
+    flying = Reads()
+    for _, tag in v_reads():
+        flying.issue(tag)
+    return flying
+
+
+def more_tiles(o, nm, paged, nt):
+    """Nobody reads Q or K(0) any more: places for K(3), V(3) and K(4)."""
+    o("s_waitcnt lgkmcnt(0)", "s_barrier", f"s_cmp_lt_u32 {s(S_LEFT)}, 4", f"s_cbranch_scc1 .Lp2{nm}%=")
+    o(*(next_offset(True, S_ID3) if paged else []), *loads("K", 3 * STAGE, nt), *loads("V", 3 * STAGE, nt))
+    o(f"s_cmp_lt_u32 {s(S_LEFT)}, 5", f"s_cbranch_scc1 .Lp2{nm}%=", *next_offset(paged, S_ID4), *loads("K", s(S_STAGE), nt), f".Lp2{nm}%=:")
+
+
+def second_tile(o, nm):
+    """K(1) has arrived."""
+    o(f"s_cmp_lt_u32 {s(S_LEFT)}, 5", f"s_cbranch_scc1 .Lp3{nm}%=", "s_waitcnt vmcnt(24)", f"s_branch .Lp4{nm}%=", f".Lp3{nm}%=:",
+      "s_waitcnt vmcnt(0)", f".Lp4{nm}%=:", "s_barrier")
+
+
+def one_chunk(o, paged, nt):
+    """A wavefront with chunk A only: nothing to run its softmax beside, and time to spare, so one form of the loop for masked and
+    unmasked tiles.  Or with no chunk: it brings its share of the tiles."""
+    fly = Reads()
+    o(".Lnot_both%=:", f"s_cmp_eq_u32 {s(S_CHUNKS)}, 0", "s_cbranch_scc1 .Lno_chunk%=")
+    o(*[f"v_add_u32 {v(TMP + kk)}, {s(S_Q)}, {v(KADDR + kk)}" for kk in range(8)])
+    keys = k_reads()
+    for kk in range(8):
+        o(f"ds_read_b128 {a(QA + 4 * kk, 4)}, {v(TMP + kk)}")
+        fly.issue(("QA", kk))
+        for ins, tag in keys[2 * kk:2 * kk + 2]:
+            o(ins)
+            fly.issue(tag)
+    o(f"s_cmp_lg_u32 {s(S_DONE)}, 0", "s_cbranch_scc1 .Lnext_pass1%=", *[f"v_accvgpr_write_b32 {a(OA + i)}, 0" for i in range(64)], ".Lnext_pass1%=:")
+    section(o, qk_products(A), [], [], fly)
+    more_tiles(o, "o", paged, nt)
+    o(*[ins for ins, _ in v_reads()], *softmax(A, True))
+    check(o, A, "Ao", True)
+    o(f"s_cmp_lt_u32 {s(S_LEFT)}, 2", "s_cbranch_scc1 .Llast1%=")
+    second_tile(o, "o")
+    o(*[f"v_add_u32 {v(KADDR + x)}, {s(S_DELTA)}, {v(KADDR + x)}" for x in range(8)], ".Lone%=:")
+    flying = after_v_reads()
+    section(o, pv_products(A) + qk_products(A), [], [(i, ins, tag) for i, (ins, tag) in enumerate(k_reads())], flying)
+    o(*[f"v_add_u32 {v(VADDR + x)}, {s(S_DELTA)}, {v(VADDR + x)}" for x in range(4)])
+    o(*hand_over(o, "o", paged, nt, False))
+    o(*[f"v_add_u32 {v(KADDR + x)}, {s(S_DELTA)}, {v(KADDR + x)}" for x in range(8)])
+    o(*[ins for ins, _ in v_reads()], *softmax(A, True))
+    check(o, A, "Al", True)
+    o(f"s_cmp_gt_u32 {s(S_LEFT)}, 1", "s_cbranch_scc1 .Lone%=", ".Llast1%=:")
+    section(o, pv_products(A), [], [], after_v_reads())
+    o("s_branch .Lend%=")
+
+    o(".Lno_chunk%=:")
+    more_tiles(o, "n", paged, nt)
+    o(f"s_cmp_lt_u32 {s(S_LEFT)}, 2", "s_cbranch_scc1 .Lend%=")
+    second_tile(o, "n")
+    o(".Lnone%=:")
+    o(*hand_over(o, "n", paged, nt, False))
+    o(f"s_cmp_gt_u32 {s(S_LEFT)}, 1", "s_cbranch_scc1 .Lnone%=", "s_branch .Lend%=")
+
+
+def program(paged, nt):
+    """Tiles 0, 1, 2 are on their way to ring places 0, 1, 2 (of each all of K, then all of V), Q to place 3 and the 32 KiB behind it.  S_LEFT tiles in
+    all, of which the first S_MASKED (at most 3) have masked keys.  S_CHUNKS: those of the wavefront that hold rows."""
+    o = Out()
+    LIFTS.clear()
+    fly = Reads()
+    o(f"s_mov_b32 {s(S_LIMIT)}, 0x49800000", f"s_mov_b32 {s(S_NINF)}, 0xff800000",       # 2^20, -inf
+      f"v_mov_b32 {v(ONES)}, 0x3f803f80", f"v_mov_b32 {v(ONES + 1)}, 0x3f803f80",
+      f"s_mov_b32 {s(S_STAGE)}, 0", f"s_mov_b32 {s(S_NEXT)}, {STAGE}", f"s_mov_b32 {s(S_DELTA)}, {STAGE}")
+    if paged:
+        o(f"s_cmp_lt_u32 {s(S_LEFT)}, 4", "s_cbranch_scc1 .Lfew%=", *fetch_id(S_ID3, True), *fetch_id(S_ID4, True), *fetch_id(S_ID, True), ".Lfew%=:")
+    # Q and tile 0 have arrived
+    o(f"s_cmp_lt_u32 {s(S_LEFT)}, 3", "s_cbranch_scc1 .Lp0%=", "s_waitcnt vmcnt(16)", "s_branch .Lp1%=", ".Lp0%=:", "s_waitcnt vmcnt(0)", ".Lp1%=:",
+      "s_waitcnt lgkmcnt(0)", "s_barrier")
+    o(f"s_cmp_lt_u32 {s(S_CHUNKS)}, 2", "s_cbranch_scc1 .Lnot_both%=")
+    o(*[f"v_add_u32 {v(TMP + kk)}, {s(S_Q)}, {v(KADDR + kk)}" for kk in range(8)])
+    keys = k_reads()
+    for kk in range(8):
+        o(f"ds_read_b128 {a(QA + 4 * kk, 4)}, {v(TMP + kk)}")
+        fly.issue(("QA", kk))
+        for ins, tag in keys[2 * kk:2 * kk + 2]:
+            o(ins)
+            fly.issue(tag)
+    o(*[f"ds_read_b128 {a(QB + 4 * kk, 4)}, {v(TMP + kk)} offset:8192" for kk in range(8)])
+    for kk in range(8):
+        fly.issue(("QB", kk))
+    zero = [f"v_accvgpr_write_b32 {a(OA + i)}, 0" for i in range(128)]
+    flying, fly2 = Reads(), Reads()
+    flying.queue, fly2.queue = list(fly.queue), list(fly.queue)
+    o(f"s_cmp_lg_u32 {s(S_DONE)}, 0", "s_cbranch_scc1 .Lnext_pass%=")
+    section(o, qk_products(A), zero, [], flying, valu_from=0)
+    o("s_branch .Lp5%=", ".Lnext_pass%=:")
+    section(o, qk_products(A), [], [], fly2)
+    o(".Lp5%=:")
+    fly.queue.clear()
+    more_tiles(o, "", paged, nt)
+    reads = [(i // 2, ins, tag) for i, (ins, tag) in enumerate(v_reads())]
+    section(o, qk_products(B), softmax(A, True), reads, fly)
+    check(o, A, "Ap", True)
+    o(f"s_cmp_lt_u32 {s(S_LEFT)}, 2", "s_cbranch_scc1 .Ltail%=")
+    second_tile(o, "")
+    o(*[f"v_add_u32 {v(KADDR + x)}, {s(S_DELTA)}, {v(KADDR + x)}" for x in range(8)])
+
+    o(".Lmasked%=:", f"s_cmp_eq_u32 {s(S_MASKED)}, 0", "s_cbranch_scc1 .Lplain%=")
+    flying = after_v_reads()
+    section_a(o, flying, "e", True)
+    section_b(o, flying, "e", paged, nt, False, True)
+    o(f"s_sub_u32 {s(S_MASKED)}, {s(S_MASKED)}, 1", f"s_cmp_gt_u32 {s(S_LEFT)}, 1", "s_cbranch_scc1 .Lmasked%=", "s_branch .Ltail%=")
+
+    o(".Lplain%=:", f"s_cmp_lt_u32 {s(S_LEFT)}, 6", "s_cbranch_scc1 .Ldrain%=")
+    flying = after_v_reads()
+    o(".p2align 6", ".Lloop%=:")
+    section_a(o, flying, "m")
+    section_b(o, flying, "m", paged, nt, True)
+    o(f"s_cmp_gt_u32 {s(S_LEFT)}, 5", "s_cbranch_scc1 .Lloop%=")
+    o(".Ldrain%=:")
+    flying = after_v_reads()
+    o(".Ldrain_loop%=:")
+    section_a(o, flying, "d")
+    section_b(o, flying, "d", paged, nt, False)
+    o(f"s_cmp_gt_u32 {s(S_LEFT)}, 1", "s_cbranch_scc1 .Ldrain_loop%=")
+
+    o(".Ltail%=:", f"s_cmp_gt_u32 {s(S_MASKED)}, 0", "s_cbranch_scc1 .Ltail_masked%=")
+    for masked in (False, True):
+        flying = after_v_reads()
+        section(o, pv_products(A), softmax(B, masked), [], flying)
+        check(o, B, f"Bt{int(masked)}", masked)
+        section(o, pv_products(B), [], [], flying)
+        o("s_branch .Lend%=", *([] if masked else [".Ltail_masked%=:"]))
+    one_chunk(o, paged, nt)
+    for c, label, masked in LIFTS:
+        lift(o, c, label, masked)
+    o(".Lend%=:", "s_waitcnt lgkmcnt(0)", "s_nop 15")   # no scalar load may arrive after the loop, in a register used otherwise
+    return o.lines
+
+
+def clobbers():
+    owned = set(range(KOFF, KOFF + 8)) | set(range(KADDR, KADDR + 12)) | {NMA, NMB, LA, LB}
+    names = [f"v{r}" for r in [*range(32, SUM + 8), ONES, ONES + 1] if r not in owned]
+    names += [f"a{r}" for r in range(QA, KF + 64)]
+    names += [f"s{r}" for r in range(S_STAGE, S_KP) if r not in (S_OFF, S_OFF + 1, S_BT, S_BT + 1, S_IDX, S_LAST)]
+    return names + ["vcc", "scc", "memory"]   # m0: as everywhere, set before each use
+
+
+def header():
+    out = ["// Written by attn_wide_loop.py: the tile loop of attn_wide_kernel.  Not to be edited.", "#pragma once", ""]
+    out.append("#define ETV_WIDE_CLOBBERS " + ", ".join(f'"{c}"' for c in clobbers()))
+    for paged in (0, 1):
+        for nt in (0, 1):
+            out.append(f"#define ETV_WIDE_LOOP_{'PAGED' if paged else 'FLAT'}{'_NT' if nt else ''} \\")
+            lines = program(bool(paged), bool(nt))
+            out += [f'    "{l}\\n\\t" \\' for l in lines[:-1]] + [f'    "{lines[-1]}\\n"']
+    return "\n".join(out) + "\n"
+

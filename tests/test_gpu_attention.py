@@ -627,3 +627,48 @@ def test_key_block_kernel_edges(d, paged):
                 err, rel = _check(wl, flags=flag, kv_split=kv_split)
                 assert d == 128 or rel <= 2.0 ** -8, (T, kv_split, rel)
             _check(wl, kv_split=64, flags=flag | api.ATTN_FLAG_UNIFORM_SPLITS)
+
+
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("T,Hq,Hkv", [(33, 16, 4), (64, 8, 2), (65, 8, 2), (70, 7, 1), (97, 8, 2), (150, 2, 1), (192, 4, 2), (256, 4, 2)])
+def test_wide_kernel_edges(T, Hq, Hkv, paged):
+    """Two chunks per wavefront: splits of 0 ... 14 full tiles (fewer than the ring, its start, its last five), no to five tiles
+    with masked keys ahead of them (trees of every mask word, prefixes that end inside a tile), groups whose last wavefronts hold
+    one chunk or none, sequences whose few nodes leave whole chunks without rows; scores so far apart that the references move
+    again and again (Q x 24).  The bars are those of every bf16 case."""
+    flag = api.ATTN_FLAG_WIDE
+    rng = np.random.default_rng(9100 + T + paged)
+    P = [0, 1, 63, 64, 65, 129, 256, 321, 449, 640, 900] if T < 100 else [0, 64, 200, 449]
+    n = [T, 1, T - 1, T // 2, 9, T, T, T // 3, T, 2, T] if T < 100 else [T, T - 1, T // 2, T]
+    for q_scale in (1.0, 24.0):
+        wl = _small(rng, len(P), T, Hq, Hkv, 128, P, "bf16", paged, n_nodes=n, q_scale=q_scale)
+        for kv_split in (0, 64, 192, 448, 4096):
+            _check(wl, flags=flag, kv_split=kv_split)
+        _check(wl, flags=flag | api.ATTN_FLAG_UNIFORM_SPLITS, kv_split=128)
+    d = api.AttnDesc(B=len(P), T_max=T, Hq=Hq, Hkv=Hkv, d=128, dtype=api.BF16, P_cap=1200, P_max=900, flags=flag)
+    assert api.tree_verify_attention_plan(d)["wavefronts"] == 8 and api.tree_verify_attention_plan(d)["ring_stages"] == 4
+
+
+@pytest.mark.parametrize("paged", [False, True])
+def test_wide_kernel_in_place_tree_rows(paged):
+    """Tree rows in the cache behind the prefix, at positions that start anywhere in a block: the bits of the separate buffer."""
+    rng = np.random.default_rng(9300 + paged)
+    T = 150
+    parents = [random_tree(rng, T) for _ in range(4)]
+    wl = synth.assemble("tail", rng, parents, [600, 77, 64, 129], Hq=8, Hkv=2, d=128, dtype="bf16", V=512, W=T, paged=paged, T_max=T,
+                        with_logits=False, spare_blocks=3, tail_room=T)
+    wl.n_nodes[1], wl.n_nodes[3] = 17, 65
+    for b in range(4):
+        for j in range(int(wl.n_nodes[b])):
+            pos = int(wl.prefix_len[b]) + j
+            at = (wl.block_table[b, pos // synth.BLOCK], slice(None), pos % synth.BLOCK) if paged else (b, pos)
+            wl.k_cache[at], wl.v_cache[at] = wl.kt[b, j], wl.vt[b, j]
+    dv = DevWorkload(wl)
+    m = api.build_tree_mask(dv.parent, dv.n_nodes)
+    for kv_split in (0, 128, 4096):
+        sep, lse_sep = gpu_attention(dv, m["bitmask"], flags=api.ATTN_FLAG_WIDE, kv_split=kv_split)
+        tail, lse_tail = api.tree_verify_attention(dv.q, dv.k_cache, dv.v_cache, dv.prefix_len, None, None, m["bitmask"], dv.n_nodes,
+                                                   P_max=dv.P_max, block_table=dv.block_table, flags=api.ATTN_FLAG_WIDE, kv_split=kv_split)
+        torch.cuda.synchronize()
+        assert torch.equal(sep, tail) and torch.equal(lse_sep, lse_tail), kv_split
+    _check(wl, flags=api.ATTN_FLAG_WIDE)
