@@ -33,6 +33,7 @@ namespace etv {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 lh_bf16x8;
 typedef __attribute__((ext_vector_type(16))) float lh_f32x16;
+typedef __attribute__((ext_vector_type(4))) float lh_f32x4;
 
 constexpr int LH_VT = 128;   // vocabulary rows per workgroup
 constexpr int LH_RT = 64;    // node rows per workgroup (2 chunks of 32)
@@ -459,9 +460,9 @@ __global__ void __launch_bounds__(512, 1) lm_head_argmax_wide_kernel(LhParams p)
 // ----------------------------------------------------------------------------------------------------------------
 // Many node rows (a batch of trees; the rule is at lh_use_gemm): the product is no longer a weight stream but a dense
 // contraction bound by the matrix cores, and the tiling is a GEMM's.  A workgroup takes 256 vocabulary rows x 256
-// node rows; wavefront w of 8 owns 128 vocabulary rows (w % 2) x 64 node rows (w / 2) as 4 x 2 accumulators of
-// 32 x 32, so the eight products of a 16-wide contraction step need six fragments (1.3 LDS bytes per flop less
-// than the kernels above, and eight independent accumulator chains).  The contraction runs in steps of 64
+// node rows; wavefront w of 8 owns 128 vocabulary rows (w % 2) x 64 node rows (w / 2) as 8 x 4 accumulators of
+// 16 x 16, so the 32 products of a 32-wide contraction step need twelve fragments (1.3 LDS bytes per flop less
+// than the kernels above).  The contraction runs in steps of 64
 // elements: a step's weight rows (256 x 128 B) and hidden rows (256 x 128 B) are 64 KiB of LDS, two stages.  A 128-byte
 // tile row holds eight 16-byte chunks; chunk c of row r sits at position c ^ ((r >> 1) & 7), so the sixteen consecutive rows
 // that a 16-byte fragment read serves in one cycle fall on sixteen different bank groups.  The weights reach a
@@ -469,10 +470,11 @@ __global__ void __launch_bounds__(512, 1) lm_head_argmax_wide_kernel(LhParams p)
 // L2 and the memory-side cache.  C^T[vocab, node] as above: a node is an accumulator column, so a wavefront's
 // maximum over its 128 vocabulary rows needs one exchange between the lane halves and is exactly one per-tile
 // partial of the layout the finishing kernel (and the epilogue) reads.
-// What bounds it is the matrix cores at the clock they hold under load: 4096 rows, D = 4096, V = 32000 take 834 us =
-// 1.29 PFLOP/s, the rate of a plain library product of that shape here.  With all loads, then all fragment reads, then all
-// products of a step behind its barrier it was 893 us (the wavefronts of a SIMD issued addresses and waited for LDS together),
-// and 2048 x 64000 x 2048 467 us (now 443).
+// What bounds it is the power of the matrix cores: the clock falls until the chip is at its limit.  v_mfma_f32_16x16x32_bf16
+// moves less accumulator data per product than 32x32x16 and so runs at a higher clock: alone, on random operands, 1.63 against
+// 1.52 PFLOP/s, here 770 against 824 us for 4096 rows, D = 4096, V = 32000 (1.39 PFLOP/s; a plain library product of that shape
+// 1.29), and 432 against 443 us for 2048 x 64000 x 2048.  With all loads, then all fragment reads, then all products of a step behind
+// its barrier it was 893 us (the wavefronts of a SIMD issued addresses and waited for LDS together).
 // ----------------------------------------------------------------------------------------------------------------
 constexpr int LHG_VT = 256, LHG_RT = 256;    // vocabulary rows, node rows per workgroup
 constexpr int LHG_KC = 64;                   // contraction elements per step
@@ -495,7 +497,6 @@ __global__ void __launch_bounds__(512, 2) lm_head_argmax_gemm_kernel(LhParams p)
     const uint32_t smem_addr = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)lh_smem;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int c32 = lane & 31, hh = lane >> 5;
     const int tiles256 = (p.tiles + 1) >> 1;
     // XCD x = id % 8 takes the vocabulary tiles x, x + 8, ...  Its 32 compute units work on panels of LHG_PT tiles x LHG_PG
     // row groups: 4 + 8 operand tiles are fetched for 32 products of tiles (all groups of one tile side by side: 2 + 16).
@@ -553,43 +554,44 @@ __global__ void __launch_bounds__(512, 2) lm_head_argmax_gemm_kernel(LhParams p)
 #pragma unroll
     for (int u = 0; u < 8; u++) issue_one(0, u);
 
-    // Fragments: A = weight rows of vocabulary block vb (4 per wavefront), B = hidden rows of row block rb (2);
-    // the lane holds row c32 and the 8 contraction values at chunk 2 * kk + hh of the 64-element step.
+    // Fragments: A = weight rows of vocabulary block vb (8 per wavefront), B = hidden rows of row block rb (4); the lane holds
+    // row lane % 16 and the 8 contraction values at chunk 4 * kk + lane / 16 of the 64-element step.
     const int wv = wave & 1, wr = wave >> 1;
-    const int sw = (c32 >> 1) & 7;   // (row >> 1) & 7: block bases are multiples of 32 rows
-    const uint32_t a_row = (uint32_t)((128 * wv + c32) * LHG_ROWB);
-    const uint32_t b_row = (uint32_t)(LHG_W_BYTES + (64 * wr + c32) * LHG_ROWB);
-    lh_f32x16 acc[4][2];
+    const int c16 = lane & 15, g = lane >> 4;
+    const int sw = (c16 >> 1) & 7;   // (row >> 1) & 7: block bases are multiples of 16 rows
+    const uint32_t a_row = (uint32_t)((128 * wv + c16) * LHG_ROWB);
+    const uint32_t b_row = (uint32_t)(LHG_W_BYTES + (64 * wr + c16) * LHG_ROWB);
+    lh_f32x4 acc[8][4];
 #pragma unroll
-    for (int vb = 0; vb < 4; vb++)
+    for (int vb = 0; vb < 8; vb++)
 #pragma unroll
-        for (int rb = 0; rb < 2; rb++)
+        for (int rb = 0; rb < 4; rb++)
 #pragma unroll
-            for (int i = 0; i < 16; i++) acc[vb][rb][i] = 0.f;
+            for (int i = 0; i < 4; i++) acc[vb][rb][i] = 0.f;
 
-    // The fragments of a 16-wide contraction step are read one step ahead into the other of two register sets, and the
-    // barrier stands before the last of a stage's four: by then every fragment of the stage is in registers, so the products
-    // behind the barrier run while the next stage's first fragments are read and the stage just freed is filled again.
-    // Reads and load issue are placed one by one between the products, where they cost no issue slot of the matrix core.
+    // The fragments of a 32-wide contraction step are read one step ahead into the other of two register sets, and the
+    // barrier stands between a stage's two: by then every fragment of the stage is in registers, so the products behind the
+    // barrier run while the next stage's first fragments are read and the stage just freed is filled again.  Reads and load
+    // issue are placed one by one between the products, where they cost no issue slot of the matrix core.
     struct Frags {
-        lh_bf16x8 a[4], b[2];
+        lh_bf16x8 a[8], b[4];
     };
     Frags f0, f1;
     auto read_one = [&](Frags &f, int st, int kk, int x) {
         const uint8_t *stage = lh_smem + (st % LHG_NS) * LHG_STAGE;
-        const int col = ((2 * kk + hh) ^ sw) << 4;
-        if (x < 2) f.b[x] = *reinterpret_cast<const lh_bf16x8 *>(stage + b_row + x * (32 * LHG_ROWB) + col);
-        else f.a[x - 2] = *reinterpret_cast<const lh_bf16x8 *>(stage + a_row + (x - 2) * (32 * LHG_ROWB) + col);
+        const int col = ((4 * kk + g) ^ sw) << 4;
+        if (x < 4) f.b[x] = *reinterpret_cast<const lh_bf16x8 *>(stage + b_row + x * (16 * LHG_ROWB) + col);
+        else f.a[x - 4] = *reinterpret_cast<const lh_bf16x8 *>(stage + a_row + (x - 4) * (16 * LHG_ROWB) + col);
     };
-    // eight products of `cur`; between them the six reads of `next` (step nkk of stage nst) and, with `load`, stage ist
+    // 32 products of `cur`; between them the twelve reads of `next` (step nkk of stage nst) and, with `load`, stage ist
     auto phase = [&](const Frags &cur, Frags &next, bool read, int nst, int nkk, bool load, int ist) {
 #pragma unroll
-        for (int x = 0; x < 8; x++) {
-            const int vb = x >> 1, rb = x & 1;
-            acc[vb][rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cur.a[vb], cur.b[rb], acc[vb][rb], 0, 0, 0);
-            if (read && x < 6) read_one(next, nst, nkk, x);
-            if (load) issue_one(ist, x);
-            __builtin_amdgcn_sched_barrier(0);
+        for (int x = 0; x < 32; x++) {
+            const int vb = x >> 2, rb = vb & 1 ? 3 - (x & 3) : x & 3;  // neighbours share an operand
+            acc[vb][rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cur.a[vb], cur.b[rb], acc[vb][rb], 0, 0, 0);
+            if (read && x % 2 == 0 && x < 24) read_one(next, nst, nkk, x / 2);
+            if (load && x % 4 == 1) issue_one(ist, x / 4);
+            if (x % 2 == 1) __builtin_amdgcn_sched_barrier(0);
         }
     };
     lh_wait_vmcnt<0>();
@@ -598,11 +600,9 @@ __global__ void __launch_bounds__(512, 2) lm_head_argmax_gemm_kernel(LhParams p)
 #pragma unroll
     for (int u = 0; u < 8; u++) issue_one(1, u);   // D is a multiple of 128: at least two steps
 #pragma unroll
-    for (int x = 0; x < 6; x++) read_one(f0, 0, 0, x);
+    for (int x = 0; x < 12; x++) read_one(f0, 0, 0, x);
     auto step = [&](int st, bool more, bool load) {
         phase(f0, f1, true, st, 1, false, 0);
-        phase(f1, f0, true, st, 2, false, 0);
-        phase(f0, f1, true, st, 3, false, 0);
         if (more) {
             lh_wait_vmcnt<0>();                   // this wavefront's part of stage st + 1 has landed
             __builtin_amdgcn_s_waitcnt(0xc07f);   // and its reads of stage st are done
@@ -617,27 +617,30 @@ __global__ void __launch_bounds__(512, 2) lm_head_argmax_gemm_kernel(LhParams p)
     step(st + 1, false, false);
 
     // Epilogue: per node column the maximum over the wavefront's 128 vocabulary rows, ascending (block vb, then
-    // element i of lane half hh = row 8 * (i / 4) + 4 * hh + i % 4), then over the two lane halves: one per-tile
-    // partial.  Lowest index wins among equals.
+    // element i = row 4 * (lane / 16) + i), then over the four lanes of the column: one per-tile partial.  Lowest index wins
+    // among equals.
     const int t128 = 2 * tile + wv;
     if (t128 >= p.tiles) return;
 #pragma unroll
-    for (int rb = 0; rb < 2; rb++) {
+    for (int rb = 0; rb < 4; rb++) {
         float bv = -INFINITY;
         int bi = 0x7fffffff;
 #pragma unroll
-        for (int vb = 0; vb < 4; vb++)
+        for (int vb = 0; vb < 8; vb++)
 #pragma unroll
-            for (int i = 0; i < 16; i++) {
-                const int v = v0 + 128 * wv + 32 * vb + 8 * (i >> 2) + 4 * hh + (i & 3);
+            for (int i = 0; i < 4; i++) {
+                const int v = v0 + 128 * wv + 16 * vb + 4 * g + i;
                 const float x = (v < p.V) ? acc[vb][rb][i] : -INFINITY;
                 if (x > bv || (bi == 0x7fffffff && v < p.V)) { bv = x; bi = v; }
             }
-        const float ov = __shfl_xor(bv, 32);
-        const int oi = __shfl_xor(bi, 32);
-        if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
-        const int row = r0 + 64 * wr + 32 * rb + c32;
-        if (hh == 0 && row < p.rows_total) {
+#pragma unroll
+        for (int off = 16; off < 64; off *= 2) {
+            const float ov = __shfl_xor(bv, off);
+            const int oi = __shfl_xor(bi, off);
+            if (ov > bv || (ov == bv && oi < bi)) { bv = ov; bi = oi; }
+        }
+        const int row = r0 + 64 * wr + 16 * rb + c16;
+        if (g == 0 && row < p.rows_total) {
             const size_t o = (size_t)row * p.tiles + t128;
             p.pval[o] = bv;
             p.pidx[o] = bi;
