@@ -545,6 +545,11 @@ __device__ __forceinline__ float half_swap_sum(float v) {
     auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
+// sum with the partner in the other half of its 32 lanes (lane ^ 16)
+__device__ __forceinline__ float quarter_swap_sum(float v) {
+    auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
 // chunk-position swizzles (measured on gfx950: 16-byte reads reach the full 256 B/clk only with a 4-bit
 // row term; the 8-byte transpose reads are fastest with the 3-bit term below).  Rows of 128 B (d = 64) lie two to a
 // 256-byte line of the banks: the K term uses the row pair, and the V term moves rows 2, 3 of four to the other half.
@@ -1307,8 +1312,9 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(AttnParams p) {
 // the eight wavefronts of attn_mfma_kernel a round costs 4 us more and a tile a quarter less.
 // ----------------------------------------------------------------------------------------------
 typedef __attribute__((ext_vector_type(32))) float f32x32;
-typedef __attribute__((ext_vector_type(8))) uint32_t u32x8;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 struct WideGeo {
     static constexpr int NW = 4, CW = 8, NS = 4, AHEAD = 3;  // wavefronts, chunks, ring places, tiles asked for before the loop
@@ -1366,27 +1372,31 @@ __global__ void __launch_bounds__(256, 1) attn_wide_kernel(AttnParams p) {
         const int kq = (int)fast_div((uint32_t)(pair * 32 + (l & 31)), p.G, p.inv_g, g);
         return {kq, (uint32_t)(kq * p.Hq + kvh * p.G + (int)g) * ROW_BYTES, pair < p.pairs && kq < p.T_max};
     };
-    // of chunk 0 and chunk 1 the row of column lane % 32
-    auto both_chunks = [&](uint32_t v, uint32_t (&of)[2]) {
-        auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-        of[0] = r[0]; of[1] = r[1];
+    // The lane's own four rows: of chunk x the rows lane % 16 (y = 0) and 16 + lane % 16 (y = 1).
+    auto own_four = [&](int l, uint32_t v, uint32_t (&of)[2][2]) {
+#pragma unroll
+        for (int x = 0; x < 2; x++)
+#pragma unroll
+            for (int y = 0; y < 2; y++) of[x][y] = (uint32_t)__builtin_amdgcn_ds_bpermute(4 * (32 * x + 16 * y + (l & 15)), (int)v);
     };
     const Row row = own_row(lane);
-    uint32_t kq_of[2];
-    both_chunks(row.in_launch ? (uint32_t)row.kq : 0xffffffffu, kq_of);  // no row there: no node
-    uint64_t bits0[2] = {0, 0}, bits1[2] = {0, 0}, bits2[2] = {0, 0}, bits3[2] = {0, 0};
+    uint32_t kq_of[2][2];
+    own_four(lane, row.in_launch ? (uint32_t)row.kq : 0xffffffffu, kq_of);  // no row there: no node
+    // ancestor bits of these rows, the first two words (with MANY: read where they are needed)
+    uint64_t bits0[2][2] = {{0, 0}, {0, 0}}, bits1[2][2] = {{0, 0}, {0, 0}};
+    if constexpr (!MANY) {
 #pragma unroll
-    for (int x = 0; x < 2; x++) {
-        if (kq_of[x] != 0xffffffffu) {
-            const uint64_t *mrow = p.bitmask + ((size_t)b * p.T_max + kq_of[x]) * p.words;
-            bits0[x] = mrow[0];
-            if (p.words > 1) bits1[x] = mrow[1];
-            if (p.words > 2) bits2[x] = mrow[2];
-            if (p.words > 3) bits3[x] = mrow[3];
-        }
+        for (int x = 0; x < 2; x++)
+#pragma unroll
+            for (int y = 0; y < 2; y++)
+                if (kq_of[x][y] != 0xffffffffu) {
+                    const uint64_t *mrow = p.bitmask + ((size_t)b * p.T_max + kq_of[x][y]) * p.words;
+                    bits0[x][y] = mrow[0];
+                    if (p.words > 1) bits1[x][y] = mrow[1];
+                }
     }
-    asm volatile("" ::"s"(n_raw), "s"(P_raw), "s"(blk0), "s"(blk1), "s"(blk2), "v"(bits0[0]), "v"(bits0[1]), "v"(bits1[0]),
-                 "v"(bits1[1]), "v"(bits2[0]), "v"(bits2[1]), "v"(bits3[0]), "v"(bits3[1]));
+    asm volatile("" ::"s"(n_raw), "s"(P_raw), "s"(blk0), "s"(blk1), "s"(blk2), "v"(bits0[0][0]), "v"(bits0[0][1]),
+                 "v"(bits0[1][0]), "v"(bits0[1][1]), "v"(bits1[0][0]), "v"(bits1[0][1]), "v"(bits1[1][0]), "v"(bits1[1][1]));
     const int n = uni(clampi(n_raw, 0, p.T_max)), P = uni(clampi(P_raw, 0, p.P_max));
     const int nvalid = uni(p.balanced ? share.nvalid : seq_nsplit(p, P));
     if (s >= nvalid) return;  // uniform over the workgroup
@@ -1408,10 +1418,6 @@ __global__ void __launch_bounds__(256, 1) attn_wide_kernel(AttnParams p) {
         int l = lane;
         asm volatile("" : "+v"(l));
         return l;
-    };
-    auto fragment_view = [&](int l) -> TileView {
-        const int g16 = l >> 4, i16 = l & 15, vrow = 4 * (l >> 5) + (i16 >> 2);
-        return {(l & 31) * ROW_BYTES, kswz_of_row<D>(l & 31), vrow, vswz_of_row<D>(vrow), 2 * (g16 & 1) + ((i16 & 3) >> 1), 8 * (i16 & 1), l >> 5};
     };
     // A wavefront brings rows 16 w .. 16 w + 15 of a tile (of a full one: one cache block), four rows a load.  The lane's source
     // columns under the swizzles: load j holds rows 4 j + lane / 16 of the 16.
@@ -1489,13 +1495,24 @@ __global__ void __launch_bounds__(256, 1) attn_wide_kernel(AttnParams p) {
 #pragma unroll
         for (int j = 0; j < 4; j++) async_load16(vf + off[j] + col.v[j & 1], dst + TILE_BYTES + j * 1024);
     };
-    // keys of edge e that the lane's row of chunk x sees; a row that is not there sees all, so that its sums stay finite
-    auto edge_vis = [&](int x, int e) -> uint64_t {
+    // keys of edge e that a row of the lane sees, those of its part of the wavefront: bit 4 kb + i for key 16 kb + 4 (lane / 16) + i;
+    // a row that is not there sees all, so that its sums stay finite
+    auto edge_vis = [&](int x, int y, int e, int l) -> uint32_t {
         const int w = nfull + e - npt;
-        const uint64_t lo = (w & 1) ? bits1[x] : bits0[x], hi = (w & 1) ? bits3[x] : bits2[x];
-        const uint64_t vis = w < 0 ? (1ull << (k1 - k0 - nfull * KT)) - 1ull : ((w & 2) ? hi : lo);
-        return kq_of[x] < (uint32_t)n ? vis : ~0ull;
+        uint64_t vis = (1ull << (k1 - k0 - nfull * KT)) - 1ull;
+        if (w >= 0) {
+            if constexpr (MANY) {
+                vis = 0;
+                if (kq_of[x][y] != 0xffffffffu) vis = p.bitmask[((size_t)b * p.T_max + kq_of[x][y]) * p.words + w];
+            } else {
+                vis = (w & 1) ? bits1[x][y] : bits0[x][y];
+            }
+        }
+        if (kq_of[x][y] >= (uint32_t)n) return 0xffffu;
+        const uint32_t lo = (uint32_t)vis >> (4 * (l >> 4)), hi = (uint32_t)(vis >> 32) >> (4 * (l >> 4));
+        return (lo & 15u) | ((lo >> 12) & 0xf0u) | ((hi & 15u) << 8) | ((hi >> 4) & 0xf000u);
     };
+
     // Q, 1 KiB a load, laid out like K rows, to the ring's last place and the space behind it; rows that are not there repeat
     // node 0's.
     {
@@ -1511,7 +1528,7 @@ __global__ void __launch_bounds__(256, 1) attn_wide_kernel(AttnParams p) {
     }
 
     f32x32 oa0, oa1, ob0, ob1;  // zeroed by the first pass of the loop, beside its first products
-    float na = INFINITY, nb = INFINITY, la = 0.f, lb = 0.f;  // minus the references (-inf so far), sums
+    f32x4 nm = {INFINITY, INFINITY, INFINITY, INFINITY}, sum = {0.f, 0.f, 0.f, 0.f};  // minus the references (-inf so far), sums
     // The order of work: a full tile, whose maximum is the rows' first reference (over the few nodes that a row sees of the tree
     // it would be farther from the largest score, and the largest probability is exact only where it is 1), the tiles with masked
     // keys, the other full tiles.  The loop wants masked tiles among its first three: with a ragged end of the prefix ahead of two
@@ -1528,6 +1545,15 @@ __global__ void __launch_bounds__(256, 1) attn_wide_kernel(AttnParams p) {
         const int lead = lead_full && f_done == 0 ? 1 : 0, e_left = edges - e_done;
         const bool more = MANY && e_left > 3 - lead;  // not the last pass
         const int ne = more ? (lead ? 2 : e_left - 3) : e_left, masked = lead + ne, nt = masked + (more ? 0 : nfull - f_done - lead);
+        const int l = again();
+        u32x2 vis[3];  // visible keys of the first three tiles for chunk A and chunk B, two rows of 16 bits each
+#pragma unroll
+        for (int e = 0; e < 3; e++)
+#pragma unroll
+            for (int x = 0; x < 2; x++) {
+                vis[e][x] = 0xffffffffu;
+                if (e >= lead && e < masked) vis[e][x] = edge_vis(x, 0, e_done + e - lead, l) | edge_vis(x, 1, e_done + e - lead, l) << 16;
+            }
 #pragma unroll 1
         for (int c = 0; c < AHEAD; c++) {
             if (c >= lead && c < masked) {
@@ -1539,22 +1565,13 @@ __global__ void __launch_bounds__(256, 1) attn_wide_kernel(AttnParams p) {
                 issue_full(full_offset(t, id), c);
             }
         }
-        const TileView tv = fragment_view(again());
-        u32x4 vis[3];  // visible keys of the masked tiles: chunk A's two key blocks, chunk B's
+        const int l16 = l & 15, g = l >> 4, vrow = 4 * g + (l16 >> 2);
+        u32x4 kaddr, vaddr;
 #pragma unroll
-        for (int e = 0; e < 3; e++)
+        for (int ds = 0; ds < 4; ds++) kaddr[ds] = smem_addr + l16 * ROW_BYTES + (((4 * ds + g) ^ kswz_of_row<D>(l16)) << 4);
 #pragma unroll
-            for (int x = 0; x < 2; x++) {
-                const uint64_t v = e >= lead && e < masked ? edge_vis(x, e_done + e - lead) : ~0ull;
-                vis[e][2 * x] = (uint32_t)v >> (4 * tv.hh);  // bits of the other half of the wavefront do not matter
-                vis[e][2 * x + 1] = (uint32_t)(v >> 32) >> (4 * tv.hh);
-            }
-        u32x8 kaddr;
-        u32x4 vaddr;
-#pragma unroll
-        for (int kk = 0; kk < KK; kk++) kaddr[kk] = smem_addr + tv.krow + (((2 * kk + tv.hh) ^ tv.ksw) << 4);
-#pragma unroll
-        for (int db = 0; db < DB; db++) vaddr[db] = smem_addr + tv.vrow * ROW_BYTES + tv.vsub + (((4 * db + tv.vchunk) ^ tv.vsw) << 4);
+        for (int db = 0; db < 4; db++)
+            vaddr[db] = smem_addr + vrow * ROW_BYTES + 8 * (l16 & 1) + (((2 * db + ((l16 & 3) >> 1)) ^ vswz_of_row<D>(vrow)) << 4);
         uint32_t left = uni(nt), n_masked = uni(masked), idx = uni(f_done + AHEAD - ne);  // idx: the loop's fourth tile among the full ones
         uint64_t off = PAGED ? 0 : uni64(full_offset((int)idx, 0));
         const uint32_t last_full = uni(nfull - 1);
@@ -1564,10 +1581,10 @@ __global__ void __launch_bounds__(256, 1) attn_wide_kernel(AttnParams p) {
         const uint32_t lds_wave_s = uni(lds_wave), q_off = uni(WideGeo::Q_AT + wave * 16384);
 #define ETV_WIDE(LOOP) \
         asm volatile(LOOP : "+{a[0:31]}"(oa0), "+{a[32:63]}"(oa1), "+{a[64:95]}"(ob0), "+{a[96:127]}"(ob1), \
-                     "+{v[208:215]}"(kaddr), "+{v[216:219]}"(vaddr), "+{v228}"(na), "+{v229}"(nb), "+{v230}"(la), "+{v231}"(lb), \
-                     "+{v[242:245]}"(vis[0]), "+{v[246:249]}"(vis[1]), "+{v[250:253]}"(vis[2]), "+{s40}"(left), "+{s68}"(n_masked), \
+                     "+{v[208:211]}"(kaddr), "+{v[212:215]}"(vaddr), "+{v[224:227]}"(nm), "+{v[228:231]}"(sum), \
+                     "+{v[240:241]}"(vis[0]), "+{v[242:243]}"(vis[1]), "+{v[244:245]}"(vis[2]), "+{s40}"(left), "+{s68}"(n_masked), \
                      "+{s[48:49]}"(off), "+{s59}"(idx) \
-                     : "{v[220:223]}"(koff), "{v[224:227]}"(voff), "{s53}"(last_full), "{s69}"(done), "{s70}"(chunks), "{s[54:55]}"(ids), "{s[60:61]}"(kbase), "{s[62:63]}"(vbase), \
+                     : "{v[216:219]}"(koff), "{v[220:223]}"(voff), "{s53}"(last_full), "{s69}"(done), "{s70}"(chunks), "{s[54:55]}"(ids), "{s[60:61]}"(kbase), "{s[62:63]}"(vbase), \
                        "{s64}"(stride), "{s65}"(lds_wave_s), "{s66}"(p.scale_log2), "{s67}"(q_off) \
                      : ETV_WIDE_CLOBBERS)
         if constexpr (PAGED && NT) ETV_WIDE(ETV_WIDE_LOOP_PAGED_NT);
@@ -1586,14 +1603,15 @@ __global__ void __launch_bounds__(256, 1) attn_wide_kernel(AttnParams p) {
     // 32 rows of 16 pieces of 16 bytes, piece c of row r at c ^ (r % 16)
     uint8_t *const oseq = static_cast<uint8_t *>(p.out) + (size_t)b * p.T_max * p.Hq * ROW_BYTES;
     uint8_t *const stage = smem + WideGeo::OUT_AT + wave * 8192;
-    const int l2 = again(), col = l2 & 31, half = l2 >> 5, piece = l2 & 15, sub = l2 >> 4;
+    const int l2 = again(), piece = l2 & 15, sub = l2 >> 4;
     const Row row2 = own_row(l2);
-    uint32_t kq2[2], at2[2];
-    both_chunks(row2.in_launch ? (uint32_t)row2.kq : 0xffffffffu, kq2);
-    both_chunks(row2.at, at2);
-    const uint32_t own = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)stage + col * 256 + ((col & 15) << 4);
-    auto put = [&](int c) -> uint8_t * {  // piece c of the lane's row
-        return (uint8_t *)(__attribute__((address_space(3))) uint8_t *)(uintptr_t)(own ^ (c << 4));
+    uint32_t kq2[2][2], at2[2][2];
+    own_four(l2, row2.in_launch ? (uint32_t)row2.kq : 0xffffffffu, kq2);
+    own_four(l2, row2.at, at2);
+    // piece c of the lane's row y (rows lane % 16 and 16 + lane % 16: the same swizzle)
+    const uint32_t own = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)stage + piece * 256 + (piece << 4);
+    auto put = [&](int y, int c) -> uint8_t * {
+        return (uint8_t *)(__attribute__((address_space(3))) uint8_t *)(uintptr_t)((own ^ (c << 4)) + y * 4096);
     };
     auto send = [&](int x, uint32_t from, auto &&dst) {  // dst(v): where the 16 pieces of a row go whose lane has v = from
         wait_lds_reads();  // the pieces are in LDS
@@ -1610,25 +1628,35 @@ __global__ void __launch_bounds__(256, 1) attn_wide_kernel(AttnParams p) {
     for (int x = 0; x < 2; x++) {
         if (wg * WideGeo::CW + wave + WideGeo::NW * x >= p.pairs) break;  // uniform over the wavefront
         const f32x32 &o0 = x ? ob0 : oa0, &o1 = x ? ob1 : oa1;
-        const float m_run = -(x ? nb : na);
-        const bool in_launch = kq2[x] != 0xffffffffu, valid = kq2[x] < (uint32_t)n;
-        const size_t lrow = ((size_t)b * p.Hq + (at2[x] / ROW_BYTES - kq2[x] * p.Hq)) * p.T_max + kq2[x];
-        const float l_tot = half_swap_sum(x ? lb : la);
-        auto o = [&](int i) { return i < 32 ? o0[i & 31] : o1[i & 31]; };
+        auto o = [&](int i) { return i < 32 ? o0[i & 31] : o1[i & 31]; };  // 4 (2 db + y) + i: column 16 db + 4 (lane / 16) + i of row y
+        float l_tot[2];
+        bool valid[2];
+#pragma unroll
+        for (int y = 0; y < 2; y++) {
+            valid[y] = kq2[x][y] < (uint32_t)n;
+            l_tot[y] = quarter_swap_sum(half_swap_sum(sum[2 * x + y]));
+        }
+        auto head = [&](int y) { return at2[x][y] / ROW_BYTES - kq2[x][y] * p.Hq; };
         if (direct) {
-            const float inv = 1.f / l_tot;
-            const bool whole = __all(valid);  // else padded rows: zeros
+            const bool whole = __all(valid[0] && valid[1]);  // else padded rows: zeros
 #pragma unroll
-            for (int db = 0; db < DB; db++)
+            for (int y = 0; y < 2; y++) {
+                const float inv = 1.f / l_tot[y];
 #pragma unroll
-                for (int ig = 0; ig < 4; ig++) {
-                    const int at = 16 * db + 4 * ig;
+                for (int db = 0; db < 8; db++) {
+                    const int at = 4 * (2 * db + y);
                     uint2 w = {pack_bf16x2(o(at) * inv, o(at + 1) * inv), pack_bf16x2(o(at + 2) * inv, o(at + 3) * inv)};
-                    if (!whole) w = valid ? w : uint2{0u, 0u};
-                    *reinterpret_cast<uint2 *>(put(4 * db + ig) + 8 * half) = w;
+                    if (!whole) w = valid[y] ? w : uint2{0u, 0u};
+                    *reinterpret_cast<uint2 *>(put(y, 2 * db + (sub >> 1)) + 8 * (sub & 1)) = w;
                 }
+            }
             send(x, row2.in_launch ? row2.at : 0xffffffffu, [&](uint32_t at) { return oseq + at; });
-            if (p.lse && half == 0 && in_launch) p.lse[lrow] = valid ? (m_run + __builtin_amdgcn_logf(l_tot)) * kLn2 : -INFINITY;
+            if (p.lse && sub == 0)
+#pragma unroll
+                for (int y = 0; y < 2; y++)
+                    if (kq2[x][y] != 0xffffffffu)
+                        p.lse[((size_t)b * p.Hq + head(y)) * p.T_max + kq2[x][y]] =
+                            valid[y] ? (-nm[2 * x + y] + __builtin_amdgcn_logf(l_tot[y])) * kLn2 : -INFINITY;
         } else {
             // rows of the slot's partials: head, then node
             const size_t slot_row = part_row(p, p.balanced ? (int)blockIdx.x : b * p.nsplit + s, 0, 0);
@@ -1639,18 +1667,21 @@ __global__ void __launch_bounds__(256, 1) attn_wide_kernel(AttnParams p) {
 #pragma unroll
                 for (int y = 0; y < 2; y++)
 #pragma unroll
-                    for (int ig = 0; ig < 4; ig++) {
-                        const int at = 16 * (2 * hf + y) + 4 * ig;
-                        *reinterpret_cast<float4 *>(put(8 * y + 2 * ig + half)) = float4{o(at), o(at + 1), o(at + 2), o(at + 3)};
+                    for (int d4 = 0; d4 < 4; d4++) {
+                        const int at = 4 * (2 * (4 * hf + d4) + y);
+                        *reinterpret_cast<float4 *>(put(y, 4 * d4 + sub)) = float4{o(at), o(at + 1), o(at + 2), o(at + 3)};
                     }
                 send(x, row2.in_launch && row2.kq < n ? prow : 0xffffffffu,
                      [&](uint32_t at) { return reinterpret_cast<uint8_t *>(part + (size_t)at * D + 64 * hf); });
             }
-            if (half == 0 && valid) {
-                const size_t pr = slot_row + (at2[x] / ROW_BYTES - kq2[x] * p.Hq) * p.T_max + kq2[x];
-                p.part_m[pr] = m_run;
-                p.part_l[pr] = l_tot;
-            }
+            if (sub == 0)
+#pragma unroll
+                for (int y = 0; y < 2; y++)
+                    if (valid[y]) {
+                        const size_t pr = slot_row + head(y) * p.T_max + kq2[x][y];
+                        p.part_m[pr] = -nm[2 * x + y];
+                        p.part_l[pr] = l_tot[y];
+                    }
         }
     }
 }
@@ -1992,7 +2023,6 @@ __global__ void __launch_bounds__(KB_NW * 64, D == 64 ? 4 : 2) attn_blocks_kerne
 // 19.7 and a combine launch of 4.0; B = 16, T = 128, P = 2048, 32/8 heads of 128: 659 us, 107 TFLOP/s (the library's fp32
 // matrix product reaches 144 ... 154 on this machine).
 // ----------------------------------------------------------------------------------------------
-typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 __device__ __forceinline__ float quad_max(float v) {  // over the lanes c, c + 16, c + 32, c + 48
     auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);

@@ -4,13 +4,13 @@ Why not HIP: the loop keeps 430 registers live in fixed places and interleaves t
 LDS reads) at the grain of one instruction.  The compiler moves the scores through accumulation registers and issues the
 fragment reads three or four products ahead of their use, whatever scheduling directives say.
 
-One wavefront per SIMD, two 32-row chunks A and B.  A section is 32 matrix instructions of one chunk and, between them, the
+One wavefront per SIMD, two 32-row chunks A and B.  A section is 64 matrix instructions of one chunk and, between them, the
 softmax of the other:
 
     section A(t):  PV(A, t), QK(A, t + 1)   beside   softmax(B, t)        reads K(t + 1) from LDS for its own second half
     section B(t):  PV(B, t), QK(B, t + 1)   beside   softmax(A, t + 1)    reads V(t + 1) from LDS for section A(t + 1)
 
-so a fragment is read once for 64 query rows, 16 ... 32 matrix instructions ahead of its first use.  The barrier that hands
+so a fragment is read once for 64 query rows, 32 ... 64 matrix instructions ahead of its first use.  The barrier that hands
 over tiles stands at the head of section B(t): V(t + 1) and K(t + 2) have arrived, and every wavefront is done with V(t) and
 K(t + 1), whose places are refilled with V(t + 4) and K(t + 5).
 
@@ -21,20 +21,28 @@ The softmax takes no maximum: probabilities are 2^(score - reference), and their
 anyway, tells whether the reference is too low (a sum above 2^20, or not a number).  Only then the row's maximum is taken, O
 and l are rescaled and the probabilities computed again (`lift`).
 
-Registers.  v0 ... v31 stay with the compiler.  Score of key 32 kb + 8 (i / 4) + 4 (lane / 32) + i % 4 at S + 16 kb + i.
+The matrix instructions are 16x16x32: they move less accumulator data per product than 32x32x16, and the launch is limited by the
+power.  64-lane layouts, l = lane % 16, g = lane / 16: A / B operand row | column l, contraction values 8 g ... 8 g + 7; accumulator
+column l, rows 4 g + i.  A chunk's 32 query rows are two column blocks cb, so a lane has the rows l and 16 + l.
+
+    S^T[key, q]: A = K[16 kb + l][32 ds + 8 g + j], B = Q[16 cb + l][the same]   score of key 16 kb + 4 g + i at S + 4 (2 kb + cb) + i
+    O^T[d, q]:   contraction value j of g is key 32 ks + 4 g + j, and 12 more for j >= 4: B = the probabilities of the blocks kb = 2 ks
+                 and 2 ks + 1 as they are, A = V^T by two transposing reads of four keys each; O + 4 (2 db + cb) + i, d = 16 db + 4 g + i
+
+Registers: v0 ... v31 stay with the compiler.
 """
-SA, SB = 32, 64            # scores: 2 key blocks x 16
-PA, PB = 96, 112           # probabilities, bf16 pairs: [key block][8]
-VF = 128                   # V^T fragments: 16 x 4, in the order of the value product
+SA, SB = 32, 64            # scores
+PA, PB = 96, 112           # probabilities, bf16 pairs: P + 4 (2 ks + cb) + 0 ... 3
+VF = 128                   # V^T fragments: 16 x 4, 8 ks + db
 TMP, PAIRS = 192, 6        # 6 pairs of temporaries
 X = 204                    # 4 temporaries of lift and of the masked softmax
-KADDR, VADDR = 208, 216    # LDS addresses of the fragments: 8 and 4
-KOFF, VOFF = 220, 224      # byte offsets of a lane's 16-byte pieces from the base of a 16-key block: 4 and 4
-NMA, NMB, LA, LB = 228, 229, 230, 231    # minus the reference, sum of the probabilities
-SUM = 232                  # a tile's sums, in two chains; each is there four times
-MASK = 242                 # visible keys, [tile][chunk][key block]: bit 8 (i / 4) + i % 4 for score i
-ONES = 254                 # four bf16 ones
-OA, OB, QA, QB, KF = 0, 64, 128, 160, 192    # accumulation registers: outputs, query fragments, K fragments (16 x 4)
+KADDR, VADDR = 208, 212    # LDS addresses of the fragments: by ds and by db % 4
+KOFF, VOFF = 216, 220      # byte offsets of a lane's 16-byte pieces from the base of a 16-key block: 4 and 4
+NM, L = 224, 228           # minus the references, sums of the probabilities: A's two column blocks, B's
+SUM = 232                  # a tile's sums of the two column blocks; each is there four times
+MASK = 240                 # visible keys, [tile][chunk]: bit 16 cb + 4 kb + i
+ONES = 246                 # four bf16 ones
+OA, OB, QA, QB, KF = 0, 64, 128, 160, 192    # accumulation registers: outputs, query fragments (2 ds + cb), K fragments (4 ds + kb)
 
 # scalar registers of the loop
 S_LEFT, S_STAGE, S_NEXT, S_DELTA, S_LIMIT, S_NINF = 40, 41, 42, 43, 44, 45
@@ -70,8 +78,7 @@ class Chunk:
         first = name == "A"
         self.name = name
         self.S, self.P, self.O, self.Q = (SA, PA, OA, QA) if first else (SB, PB, OB, QB)
-        self.nm, self.l = (NMA, LA) if first else (NMB, LB)
-        self.mask = MASK + (0 if first else 2)
+        self.nm, self.l, self.mask = (NM, L, MASK) if first else (NM + 2, L + 2, MASK + 1)
 
 
 A, B = Chunk("A"), Chunk("B")
@@ -80,44 +87,56 @@ A, B = Chunk("A"), Chunk("B")
 # ---------------------------------------------------------------------------------------------------------------
 # the three streams
 # ---------------------------------------------------------------------------------------------------------------
+def snake(outer):
+    """The two column blocks for each of the outer blocks; neighbours share an operand."""
+    return [(x, cb) for n, x in enumerate(outer) for cb in ((0, 1) if n % 2 == 0 else (1, 0))]
+
+
 def qk_products(c):
-    """16 products; product i needs K fragment i = 2 kk + kb."""
     r = []
-    for kk in range(8):
-        for kb in range(2):
-            d = v(c.S + 16 * kb, 16)
-            r.append((f"v_mfma_f32_32x32x16_bf16 {d}, {a(KF + 4 * (2 * kk + kb), 4)}, {a(c.Q + 4 * kk, 4)}, {'0' if kk == 0 else d}",
-                      (("K", 2 * kk + kb), ("Q" + c.name, kk))))
+    for ds in range(4):
+        for kb, cb in snake(range(4)):
+            d = v(c.S + 4 * (2 * kb + cb), 4)
+            r.append((f"v_mfma_f32_16x16x32_bf16 {d}, {a(KF + 4 * (4 * ds + kb), 4)}, {a(c.Q + 4 * (2 * ds + cb), 4)}, {'0' if ds == 0 else d}",
+                      (("K", 4 * ds + kb), ("Q" + c.name, 2 * ds + cb))))
     return r
 
 
 def pv_products(c):
-    """16 products; product i needs V fragment i = (2 kb + st) * 4 + db."""
     r = []
-    for ks in range(4):
-        for db in range(4):
-            o = a(c.O + 16 * db, 16)
-            r.append((f"v_mfma_f32_32x32x16_bf16 {o}, {v(VF + 4 * (4 * ks + db), 4)}, {v(c.P + 4 * ks, 4)}, {o}", (("V", 4 * ks + db),)))
+    for ks in range(2):
+        for db, cb in snake(range(8)):
+            o = a(c.O + 4 * (2 * db + cb), 4)
+            r.append((f"v_mfma_f32_16x16x32_bf16 {o}, {v(VF + 4 * (8 * ks + db), 4)}, {v(c.P + 4 * (2 * ks + cb), 4)}, {o}", (("V", 8 * ks + db),)))
     return r
 
 
 def k_reads():
-    return [(f"ds_read_b128 {a(KF + 4 * (2 * kk + kb), 4)}, {v(KADDR + kk)} offset:{8192 * kb}", ("K", 2 * kk + kb))
-            for kk in range(8) for kb in range(2)]
+    return [(f"ds_read_b128 {a(KF + 4 * (4 * ds + kb), 4)}, {v(KADDR + ds)} offset:{4096 * kb}", ("K", 4 * ds + kb))
+            for ds in range(4) for kb in range(4)]
+
+
+def q_reads(c, at):
+    """From the addresses TMP ...; `at`: the chunk's place."""
+    return [(f"ds_read_b128 {a(c.Q + 4 * (2 * ds + cb), 4)}, {v(TMP + ds)} offset:{at + 4096 * cb}", ("Q" + c.name, 2 * ds + cb))
+            for ds in range(4) for cb in range(2)]
 
 
 def v_reads():
     r = []
-    for ks in range(4):
-        for db in range(4):
-            f = 4 * ks + db
+    for ks in range(2):
+        for db in range(8):
+            f = 8 * ks + db
             for half in range(2):
-                r.append((f"ds_read_b64_tr_b16 {v(VF + 4 * f + 2 * half, 2)}, {v(VADDR + db)} offset:{TILE + 4096 * ks + 2048 * half}", ("V", f)))
+                r.append((f"ds_read_b64_tr_b16 {v(VF + 4 * f + 2 * half, 2)}, {v(VADDR + db % 4)} offset:{TILE + 8192 * ks + 4096 * half + 128 * (db // 4)}", ("V", f)))
     return r
 
 
-def mask_bit(i):
-    return 8 * (i >> 2) + (i & 3)
+def scores(c, i):
+    """The registers and mask bits of the scores that become pair i of P."""
+    ks, cb, r = i // 8, i // 4 % 2, i % 4
+    kb, e = 2 * ks + r // 2, 2 * (r % 2)
+    return c.S + 4 * (2 * kb + cb) + e, 16 * cb + 4 * kb + e, cb
 
 
 def softmax(c, masked=False):
@@ -127,25 +146,27 @@ def softmax(c, masked=False):
 
     The sum is over the rounded probabilities, the weights of the value product (over the unrounded ones the error against
     float64 grows by 0.5 %).  v_mfma_f32_4x4x4_16b_bf16 with ones adds up the four of two registers lane by lane; in groups of four,
-    since a change between the two sizes of matrix instructions costs a dozen cycles.  A tile of the loop takes 2574 cycles with it
-    (one by one 2614), with v_dot2_f32_bf16 3046 (groups of 16: 2693), with the pairs taken apart for v_add_f32 2697."""
-    fma, hide, exp, cvt, add, group = [], [], [], [], [], []
+    since a change between the two sizes of matrix instructions costs a dozen cycles.  Between 32x32x16 instructions a tile of the
+    loop took 2574 cycles with it (one by one 2614), with v_dot2_f32_bf16 3046 (groups of 16: 2693), with the pairs taken apart for
+    v_add_f32 2697."""
+    fma, hide, exp, cvt, add = [], [], [], [], []
     for i in range(16):
-        s0, t0 = c.S + 2 * i, TMP + 2 * (i % PAIRS)
-        fma.append([f"v_fma_f32 {v(t0 + x)}, {v(s0 + x)}, {s(S_SCALE)}, {v(c.nm)}" for x in range(2)])
+        (s0, bit, cb), t0 = scores(c, i), TMP + 2 * (i % PAIRS)
+        fma.append([f"v_fma_f32 {v(t0 + x)}, {v(s0 + x)}, {s(S_SCALE)}, {v(c.nm + cb)}" for x in range(2)])
         if masked:
             m0 = X + 2 * (i % 2)
-            fma[-1] += [f"v_bfe_i32 {v(m0 + x)}, {v(c.mask + i // 8)}, {mask_bit(2 * (i % 8) + x)}, 1" for x in range(2)]
+            fma[-1] += [f"v_bfe_i32 {v(m0 + x)}, {v(c.mask)}, {bit + x}, 1" for x in range(2)]
             hide.append([f"v_bfi_b32 {v(t0 + x)}, {v(m0 + x)}, {v(t0 + x)}, {s(S_NINF)}" for x in range(2)])
         exp.append([f"v_exp_f32 {v(t0 + x)}, {v(t0 + x)}" for x in range(2)])
         cvt.append([f"v_cvt_pk_bf16_f32 {v(c.P + i)}, {v(t0)}, {v(t0 + 1)}"])
-        if i % 2:
-            total = v(SUM + 4 * (i // 2 % 2), 4)
-            group.append(f"v_mfma_f32_4x4x4_16b_bf16 {total}, {v(ONES, 2)}, {v(c.P + i - 1, 2)}, {total if i > 3 else 0}")
         add.append([])
         if i % 8 == 7:
-            group.insert(2, "s_nop 0")    # two wait states between those of a chain
-            add[-1], group = group, []
+            for half in range(2):
+                for x in range(2):
+                    total = v(SUM + 4 * x, 4)
+                    add[-1].append(f"v_mfma_f32_4x4x4_16b_bf16 {total}, {v(ONES, 2)}, {v(c.P + i - 7 + 4 * x + 2 * half, 2)}, {total if i > 7 or half else 0}")
+                if half == 0:
+                    add[-1].append("s_nop 0")    # two wait states between those of a chain
     stages = (fma, hide, exp, cvt, add) if masked else (fma, exp, cvt, add)
     r = []
     for i in range(16 + len(stages) - 1):
@@ -158,11 +179,11 @@ def softmax(c, masked=False):
 
 
 def check(o, c, label, masked=False):
-    """The tile's sum; out of line to `lift` where the reference is too low."""
-    o("s_nop 4", f"v_add_f32 {v(SUM)}, {v(SUM)}, {v(SUM + 4)}", f"v_cmp_nle_f32 vcc, {v(SUM)}, {s(S_LIMIT)}",
-      f"s_cbranch_vccnz .Llift_{label}%=", f".Llifted_{label}%=:", f"v_add_f32 {v(c.l)}, {v(c.l)}, {v(SUM)}")
+    """The tile's sums; out of line to `lift` where a reference is too low."""
+    o("s_nop 4", f"v_add_f32 {v(X)}, {v(SUM)}, {v(SUM + 4)}", f"v_cmp_nle_f32 vcc, {v(X)}, {s(S_LIMIT)}",
+      f"s_cbranch_vccnz .Llift_{label}%=", f".Llifted_{label}%=:", *[f"v_add_f32 {v(c.l + x)}, {v(c.l + x)}, {v(SUM + 4 * x)}" for x in range(2)])
     if masked:   # on to the next tile's bits; behind the masked tiles all keys are visible
-        o(*[f"v_mov_b32 {v(c.mask + 4 * x + y)}, {v(c.mask + 4 * x + 4 + y) if x < 2 else '-1'}" for x in range(3) for y in range(2)])
+        o(*[f"v_mov_b32 {v(c.mask + 2 * x)}, {v(c.mask + 2 * x + 2) if x < 2 else '-1'}" for x in range(3)])
     LIFTS.append((c, label, masked))
 
 
@@ -170,34 +191,41 @@ LIFTS = []
 
 
 def lift(o, c, label, masked):
-    """vcc: lanes whose sum failed.  A row is in the lanes l and l + 32; the rows that did not fail keep their reference and are
-    computed again to the same values."""
-    o(f".Llift_{label}%=:", "s_nop 15", f"s_or_b32 {s(S_LIFT)}, vcc_lo, vcc_hi", f"s_mov_b32 {s(S_LIFT + 1)}, {s(S_LIFT)}")
-    if masked:
-        for i in range(0, 32, 2):
-            o(*[f"v_bfe_i32 {v(TMP + x)}, {v(c.mask + i // 16)}, {mask_bit(i % 16 + x)}, 1" for x in range(2)])
-            o(*[f"v_bfi_b32 {v(TMP + x)}, {v(TMP + x)}, {v(c.S + i + x)}, {s(S_NINF)}" for x in range(2)])
-            o(f"v_maximum3_f32 {v(X)}, {v(X) if i else v(TMP)}, {v(TMP)}, {v(TMP + 1)}")
-    else:
-        o(f"v_maximum3_f32 {v(X)}, {v(c.S)}, {v(c.S + 1)}, {v(c.S + 2)}")
-        for i in range(3, 31, 2):
-            o(f"v_maximum3_f32 {v(X)}, {v(X)}, {v(c.S + i)}, {v(c.S + i + 1)}")
-        o(f"v_max_f32 {v(X)}, {v(X)}, {v(c.S + 31)}")
-    o(f"v_mov_b32 {v(X + 1)}, {v(X)}", "s_nop 1",
-      f"v_permlane32_swap_b32 {v(X)}, {v(X + 1)}", "s_nop 1", f"v_max_f32 {v(X)}, {v(X)}, {v(X + 1)}",
-      f"v_mul_f32 {v(X)}, {s(S_SCALE)}, {v(X)}",
-      f"v_cndmask_b32_e64 {v(X)}, {v(c.nm)}, -{v(X)}, {s(S_LIFT, 2)}",        # minus the new reference
-      f"v_sub_f32 {v(X + 1)}, {v(X)}, {v(c.nm)}", f"v_exp_f32 {v(X + 1)}, {v(X + 1)}", f"v_mov_b32 {v(c.nm)}, {v(X)}",
-      f"v_cmp_neq_f32 vcc, 0, {v(c.l)}",
-      f"v_cndmask_b32_e64 {v(X + 1)}, 1.0, {v(X + 1)}, {s(S_LIFT, 2)}", f"s_cbranch_vccz .Lempty_{label}%=",   # nothing to rescale yet
-      f"v_mul_f32 {v(c.l)}, {v(c.l)}, {v(X + 1)}")
-    for g in range(0, 64, 8):
-        o(*[f"v_accvgpr_read_b32 {v(TMP + i)}, {a(c.O + g + i)}" for i in range(8)])
-        o(*[f"v_mul_f32 {v(TMP + i)}, {v(TMP + i)}, {v(X + 1)}" for i in range(8)])
-        o(*[f"v_accvgpr_write_b32 {a(c.O + g + i)}, {v(TMP + i)}" for i in range(8)])
-    o(f".Lempty_{label}%=:")
+    """A row is in the lanes l, l + 16, l + 32, l + 48; one whose sum is above the limit in any of them moves its reference to the
+    largest score of the tile.  The rows that do not are computed again to the same values."""
+    o(f".Llift_{label}%=:", "s_nop 15")
+    for cb in range(2):
+        o(f"v_cmp_nle_f32 vcc, {v(SUM + 4 * cb)}, {s(S_LIMIT)}", f"s_or_b32 {s(S_LIFT)}, vcc_lo, vcc_hi", f"s_lshr_b32 {s(S_TMP)}, {s(S_LIFT)}, 16",
+          f"s_or_b32 {s(S_LIFT)}, {s(S_LIFT)}, {s(S_TMP)}", f"s_and_b32 {s(S_LIFT)}, {s(S_LIFT)}, 0xffff", f"s_lshl_b32 {s(S_TMP)}, {s(S_LIFT)}, 16",
+          f"s_or_b32 {s(S_LIFT)}, {s(S_LIFT)}, {s(S_TMP)}", f"s_mov_b32 {s(S_LIFT + 1)}, {s(S_LIFT)}")
+        first = True
+        for i in range(16):
+            s0, bit, own = scores(c, i)
+            if own != cb:
+                continue
+            at = s0
+            if masked:
+                o(*[f"v_bfe_i32 {v(TMP + x)}, {v(c.mask)}, {bit + x}, 1" for x in range(2)])
+                o(*[f"v_bfi_b32 {v(TMP + x)}, {v(TMP + x)}, {v(s0 + x)}, {s(S_NINF)}" for x in range(2)])
+                at = TMP
+            o(f"v_maximum3_f32 {v(X)}, {v(at) if first else v(X)}, {v(at)}, {v(at + 1)}")
+            first = False
+        for swap in ("32", "16"):
+            o(f"v_mov_b32 {v(X + 1)}, {v(X)}", "s_nop 1", f"v_permlane{swap}_swap_b32 {v(X)}, {v(X + 1)}", "s_nop 1", f"v_max_f32 {v(X)}, {v(X)}, {v(X + 1)}")
+        o(f"v_mul_f32 {v(X)}, {s(S_SCALE)}, {v(X)}",
+          f"v_cndmask_b32_e64 {v(X)}, {v(c.nm + cb)}, -{v(X)}, {s(S_LIFT, 2)}",        # minus the new reference
+          f"v_sub_f32 {v(X + 1)}, {v(X)}, {v(c.nm + cb)}", f"v_exp_f32 {v(X + 1)}, {v(X + 1)}", f"v_mov_b32 {v(c.nm + cb)}, {v(X)}",
+          f"v_cmp_neq_f32 vcc, 0, {v(c.l + cb)}",
+          f"v_cndmask_b32_e64 {v(X + 1)}, 1.0, {v(X + 1)}, {s(S_LIFT, 2)}", f"s_cbranch_vccz .Lempty_{label}{cb}%=",   # nothing to rescale yet
+          f"v_mul_f32 {v(c.l + cb)}, {v(c.l + cb)}, {v(X + 1)}")
+        for db in range(0, 8, 2):
+            o_regs = [c.O + 4 * (2 * (db + x) + cb) + i for x in range(2) for i in range(4)]
+            o(*[f"v_accvgpr_read_b32 {v(TMP + i)}, {a(r)}" for i, r in enumerate(o_regs)])
+            o(*[f"v_mul_f32 {v(TMP + i)}, {v(TMP + i)}, {v(X + 1)}" for i in range(8)])
+            o(*[f"v_accvgpr_write_b32 {a(r)}, {v(TMP + i)}" for i, r in enumerate(o_regs)])
+        o(f".Lempty_{label}{cb}%=:")
     o(*softmax(c, masked))
-    o("s_nop 4", f"v_add_f32 {v(SUM)}, {v(SUM)}, {v(SUM + 4)}", f"s_branch .Llifted_{label}%=")
+    o("s_nop 4", f"s_branch .Llifted_{label}%=")
 
 
 # ---------------------------------------------------------------------------------------------------------------
@@ -251,7 +279,7 @@ class Reads:
         del self.queue[:max(last + 1, len(self.queue) - 15)]
 
 
-def section(o, products, valu, reads, flying, extra=(), valu_from=3, valu_to=None):
+def section(o, products, valu, reads, flying, extra=(), valu_from=8, valu_to=None):
     """Matrix instructions with the other streams between them.  reads: (slot, instruction, tag); extra: (slot, instruction)."""
     n = len(products)
     valu_to = n if valu_to is None else valu_to
@@ -280,9 +308,9 @@ def spread(ops, first, per_slot=1.0):
 
 def section_a(o, flying, nm, masked=False):
     """PV(A, t), QK(A, t + 1) | softmax(B, t); K(t + 1) is read in the first half."""
-    reads = [(i, ins, tag) for i, (ins, tag) in enumerate(k_reads())]
+    reads = [(2 * i, ins, tag) for i, (ins, tag) in enumerate(k_reads())]
     move = [f"v_add_u32 {v(VADDR + x)}, {s(S_DELTA)}, {v(VADDR + x)}" for x in range(4)]
-    section(o, pv_products(A) + qk_products(A), softmax(B, masked), reads, flying, spread(move, 20))
+    section(o, pv_products(A) + qk_products(A), softmax(B, masked), reads, flying, spread(move, 40, 0.5))
     check(o, B, f"B{nm}", masked)
 
 
@@ -315,10 +343,10 @@ def section_b(o, flying, nm, paged, nt, steady, masked=False):
     """PV(B, t), QK(B, t + 1) | softmax(A, t + 1); V(t + 1) is read as its fragments' last uses go by."""
     scalar = hand_over(o, nm, paged, nt, steady)
     flying.queue.clear()
-    extra = spread(scalar, 0, 2.0)
+    extra = spread(scalar, 0, 1.0)
     last = max([slot for slot, _ in extra])
-    extra += spread([f"v_add_u32 {v(KADDR + x)}, {s(S_DELTA)}, {v(KADDR + x)}" for x in range(8)], max(last + 1, 20))
-    reads = [(max(i // 2 + 1, i), ins, tag) for i, (ins, tag) in enumerate(v_reads())]
+    extra += spread([f"v_add_u32 {v(KADDR + x)}, {s(S_DELTA)}, {v(KADDR + x)}" for x in range(4)], max(last + 1, 40), 0.5)
+    reads = [(2 * i + 1, ins, tag) for i, (ins, tag) in enumerate(v_reads())]
     section(o, pv_products(B) + qk_products(B), softmax(A, masked), reads, flying, extra)
     check(o, A, f"A{nm}", masked)
 
@@ -344,19 +372,21 @@ def second_tile(o, nm):
       "s_waitcnt vmcnt(0)", f".Lp4{nm}%=:", "s_barrier")
 
 
+def first_reads():
+    """Q of chunk A and K(0), by ds."""
+    queries, keys = q_reads(A, 0), k_reads()
+    return [r for ds in range(4) for r in queries[2 * ds:2 * ds + 2] + keys[4 * ds:4 * ds + 4]]
+
+
 def one_chunk(o, paged, nt):
     """A wavefront with chunk A only: nothing to run its softmax beside, and time to spare, so one form of the loop for masked and
     unmasked tiles.  Or with no chunk: it brings its share of the tiles."""
     fly = Reads()
     o(".Lnot_both%=:", f"s_cmp_eq_u32 {s(S_CHUNKS)}, 0", "s_cbranch_scc1 .Lno_chunk%=")
-    o(*[f"v_add_u32 {v(TMP + kk)}, {s(S_Q)}, {v(KADDR + kk)}" for kk in range(8)])
-    keys = k_reads()
-    for kk in range(8):
-        o(f"ds_read_b128 {a(QA + 4 * kk, 4)}, {v(TMP + kk)}")
-        fly.issue(("QA", kk))
-        for ins, tag in keys[2 * kk:2 * kk + 2]:
-            o(ins)
-            fly.issue(tag)
+    o(*[f"v_add_u32 {v(TMP + ds)}, {s(S_Q)}, {v(KADDR + ds)}" for ds in range(4)])
+    for ins, tag in first_reads():
+        o(ins)
+        fly.issue(tag)
     o(f"s_cmp_lg_u32 {s(S_DONE)}, 0", "s_cbranch_scc1 .Lnext_pass1%=", *[f"v_accvgpr_write_b32 {a(OA + i)}, 0" for i in range(64)], ".Lnext_pass1%=:")
     section(o, qk_products(A), [], [], fly)
     more_tiles(o, "o", paged, nt)
@@ -364,12 +394,12 @@ def one_chunk(o, paged, nt):
     check(o, A, "Ao", True)
     o(f"s_cmp_lt_u32 {s(S_LEFT)}, 2", "s_cbranch_scc1 .Llast1%=")
     second_tile(o, "o")
-    o(*[f"v_add_u32 {v(KADDR + x)}, {s(S_DELTA)}, {v(KADDR + x)}" for x in range(8)], ".Lone%=:")
+    o(*[f"v_add_u32 {v(KADDR + x)}, {s(S_DELTA)}, {v(KADDR + x)}" for x in range(4)], ".Lone%=:")
     flying = after_v_reads()
-    section(o, pv_products(A) + qk_products(A), [], [(i, ins, tag) for i, (ins, tag) in enumerate(k_reads())], flying)
+    section(o, pv_products(A) + qk_products(A), [], [(2 * i, ins, tag) for i, (ins, tag) in enumerate(k_reads())], flying)
     o(*[f"v_add_u32 {v(VADDR + x)}, {s(S_DELTA)}, {v(VADDR + x)}" for x in range(4)])
     o(*hand_over(o, "o", paged, nt, False))
-    o(*[f"v_add_u32 {v(KADDR + x)}, {s(S_DELTA)}, {v(KADDR + x)}" for x in range(8)])
+    o(*[f"v_add_u32 {v(KADDR + x)}, {s(S_DELTA)}, {v(KADDR + x)}" for x in range(4)])
     o(*[ins for ins, _ in v_reads()], *softmax(A, True))
     check(o, A, "Al", True)
     o(f"s_cmp_gt_u32 {s(S_LEFT)}, 1", "s_cbranch_scc1 .Lone%=", ".Llast1%=:")
@@ -400,17 +430,10 @@ def program(paged, nt):
     o(f"s_cmp_lt_u32 {s(S_LEFT)}, 3", "s_cbranch_scc1 .Lp0%=", "s_waitcnt vmcnt(16)", "s_branch .Lp1%=", ".Lp0%=:", "s_waitcnt vmcnt(0)", ".Lp1%=:",
       "s_waitcnt lgkmcnt(0)", "s_barrier")
     o(f"s_cmp_lt_u32 {s(S_CHUNKS)}, 2", "s_cbranch_scc1 .Lnot_both%=")
-    o(*[f"v_add_u32 {v(TMP + kk)}, {s(S_Q)}, {v(KADDR + kk)}" for kk in range(8)])
-    keys = k_reads()
-    for kk in range(8):
-        o(f"ds_read_b128 {a(QA + 4 * kk, 4)}, {v(TMP + kk)}")
-        fly.issue(("QA", kk))
-        for ins, tag in keys[2 * kk:2 * kk + 2]:
-            o(ins)
-            fly.issue(tag)
-    o(*[f"ds_read_b128 {a(QB + 4 * kk, 4)}, {v(TMP + kk)} offset:8192" for kk in range(8)])
-    for kk in range(8):
-        fly.issue(("QB", kk))
+    o(*[f"v_add_u32 {v(TMP + ds)}, {s(S_Q)}, {v(KADDR + ds)}" for ds in range(4)])
+    for ins, tag in first_reads() + q_reads(B, 8192):
+        o(ins)
+        fly.issue(tag)
     zero = [f"v_accvgpr_write_b32 {a(OA + i)}, 0" for i in range(128)]
     flying, fly2 = Reads(), Reads()
     flying.queue, fly2.queue = list(fly.queue), list(fly.queue)
@@ -421,12 +444,11 @@ def program(paged, nt):
     o(".Lp5%=:")
     fly.queue.clear()
     more_tiles(o, "", paged, nt)
-    reads = [(i // 2, ins, tag) for i, (ins, tag) in enumerate(v_reads())]
-    section(o, qk_products(B), softmax(A, True), reads, fly)
+    section(o, qk_products(B), softmax(A, True), [(i, ins, tag) for i, (ins, tag) in enumerate(v_reads())], fly)
     check(o, A, "Ap", True)
     o(f"s_cmp_lt_u32 {s(S_LEFT)}, 2", "s_cbranch_scc1 .Ltail%=")
     second_tile(o, "")
-    o(*[f"v_add_u32 {v(KADDR + x)}, {s(S_DELTA)}, {v(KADDR + x)}" for x in range(8)])
+    o(*[f"v_add_u32 {v(KADDR + x)}, {s(S_DELTA)}, {v(KADDR + x)}" for x in range(4)])
 
     o(".Lmasked%=:", f"s_cmp_eq_u32 {s(S_MASKED)}, 0", "s_cbranch_scc1 .Lplain%=")
     flying = after_v_reads()
@@ -462,7 +484,7 @@ def program(paged, nt):
 
 
 def clobbers():
-    owned = set(range(KOFF, KOFF + 8)) | set(range(KADDR, KADDR + 12)) | {NMA, NMB, LA, LB}
+    owned = set(range(KADDR, L + 4))
     names = [f"v{r}" for r in [*range(32, SUM + 8), ONES, ONES + 1] if r not in owned]
     names += [f"a{r}" for r in range(QA, KF + 64)]
     names += [f"s{r}" for r in range(S_STAGE, S_KP) if r not in (S_OFF, S_OFF + 1, S_BT, S_BT + 1, S_IDX, S_LAST)]
