@@ -174,8 +174,7 @@ typedef struct etv_attn_desc {
                                            sequences' lengths (tuning) */
 
 #define ETV_ATTN_FLAG_KEY_BLOCKS 64 /* bf16: every wavefront takes 32-key blocks of its own (tuning) */
-#define ETV_ATTN_FLAG_WIDE 128 /* bf16, heads of 128: every wavefront takes two 32-row chunks wherever the tree has more than
-                                  four (tuning) */
+#define ETV_ATTN_FLAG_WIDE 128 /* bf16, heads of 128: workgroups of eight 32-row chunks, two to a wavefront (tuning) */
 
 ETV_API size_t etv_tree_verify_attention_workspace_bytes(const etv_attn_desc *h_desc);
 

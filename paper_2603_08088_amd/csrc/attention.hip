@@ -2393,8 +2393,7 @@ static void pick_tile_shape(const etv_attn_desc *h, Plan &pl) {
     const int tree_tiles = (h->T_max + KT - 1) / KT;
     double best = 1e30;
     for (const TileShape &sh : kTileShapes) {
-        if (!shape_allowed(h, pl.pairs, sh.nw, sh.kh)) continue;
-        if (!sh.wide && (h->flags & ETV_ATTN_FLAG_WIDE) && pl.pairs > 4) continue;
+        if (h->flags & ETV_ATTN_FLAG_WIDE ? !sh.wide : !shape_allowed(h, pl.pairs, sh.nw, sh.kh)) continue;
         const int cw = sh.kh ? sh.nw / 2 : sh.nw, wgp = (pl.pairs + cw - 1) / cw;
         const long units = (long)B * h->Hkv * wgp;
         const double held = (double)pl.pairs / (wgp * cw);  // part of a workgroup's chunks that have rows

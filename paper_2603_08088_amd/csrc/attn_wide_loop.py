@@ -82,6 +82,8 @@ class Chunk:
 
 
 A, B = Chunk("A"), Chunk("B")
+A2 = Chunk("A")            # chunk A with its probabilities where B's would be
+A2.P = PB
 
 
 # ---------------------------------------------------------------------------------------------------------------
@@ -284,9 +286,11 @@ def section(o, products, valu, reads, flying, extra=(), valu_from=8, valu_to=Non
     n = len(products)
     valu_to = n if valu_to is None else valu_to
     done = 0
-    for i, (text, need) in enumerate(products):
-        for tag in need:
-            flying.wait_for(o, tag)
+    for i, (text, _) in enumerate(products):
+        if i % 4 == 0:   # for four products at a time
+            for _, need in products[i:i + 4]:
+                for tag in need:
+                    flying.wait_for(o, tag)
         o(text)
         for slot, ins, tag in reads:
             if slot == i:
@@ -379,8 +383,12 @@ def first_reads():
 
 
 def one_chunk(o, paged, nt):
-    """A wavefront with chunk A only: nothing to run its softmax beside, and time to spare, so one form of the loop for masked and
-    unmasked tiles.  Or with no chunk: it brings its share of the tiles."""
+    """A wavefront with chunk A only: its softmax runs beside its own value product, the probabilities of every other tile in the place
+    of chunk B's.
+
+        QK(A, t + 1), V(t) read | barrier | PV(A, t) beside softmax(A, t + 1), K(t + 2) read
+
+    Or with no chunk: it brings its share of the tiles."""
     fly = Reads()
     o(".Lnot_both%=:", f"s_cmp_eq_u32 {s(S_CHUNKS)}, 0", "s_cbranch_scc1 .Lno_chunk%=")
     o(*[f"v_add_u32 {v(TMP + ds)}, {s(S_Q)}, {v(KADDR + ds)}" for ds in range(4)])
@@ -390,21 +398,38 @@ def one_chunk(o, paged, nt):
     o(f"s_cmp_lg_u32 {s(S_DONE)}, 0", "s_cbranch_scc1 .Lnext_pass1%=", *[f"v_accvgpr_write_b32 {a(OA + i)}, 0" for i in range(64)], ".Lnext_pass1%=:")
     section(o, qk_products(A), [], [], fly)
     more_tiles(o, "o", paged, nt)
-    o(*[ins for ins, _ in v_reads()], *softmax(A, True))
+    o(*softmax(A, True))
     check(o, A, "Ao", True)
-    o(f"s_cmp_lt_u32 {s(S_LEFT)}, 2", "s_cbranch_scc1 .Llast1%=")
+    o(f"s_cmp_lt_u32 {s(S_LEFT)}, 2", "s_cbranch_scc1 .Llast_A%=")
     second_tile(o, "o")
-    o(*[f"v_add_u32 {v(KADDR + x)}, {s(S_DELTA)}, {v(KADDR + x)}" for x in range(4)], ".Lone%=:")
-    flying = after_v_reads()
-    section(o, pv_products(A) + qk_products(A), [], [(2 * i, ins, tag) for i, (ins, tag) in enumerate(k_reads())], flying)
-    o(*[f"v_add_u32 {v(VADDR + x)}, {s(S_DELTA)}, {v(VADDR + x)}" for x in range(4)])
-    o(*hand_over(o, "o", paged, nt, False))
-    o(*[f"v_add_u32 {v(KADDR + x)}, {s(S_DELTA)}, {v(KADDR + x)}" for x in range(4)])
-    o(*[ins for ins, _ in v_reads()], *softmax(A, True))
-    check(o, A, "Al", True)
-    o(f"s_cmp_gt_u32 {s(S_LEFT)}, 1", "s_cbranch_scc1 .Lone%=", ".Llast1%=:")
-    section(o, pv_products(A), [], [], after_v_reads())
-    o("s_branch .Lend%=")
+    o(*[f"v_add_u32 {v(KADDR + x)}, {s(S_DELTA)}, {v(KADDR + x)}" for x in range(4)], *[ins for ins, _ in k_reads()])
+
+    def one_tile(now, then, nm, masked):
+        flying = Reads()
+        for _, tag in k_reads():
+            flying.issue(tag)
+        section(o, qk_products(then), [], [(i, ins, tag) for i, (ins, tag) in enumerate(v_reads())], flying)
+        o(*[f"v_add_u32 {v(VADDR + x)}, {s(S_DELTA)}, {v(VADDR + x)}" for x in range(4)])
+        o(*hand_over(o, nm, paged, nt, False))
+        o(*[f"v_add_u32 {v(KADDR + x)}, {s(S_DELTA)}, {v(KADDR + x)}" for x in range(4)])
+        # (behind the last tile the reads find an older one, and nothing uses them)
+        section(o, pv_products(now), softmax(then, masked), [(2 * i, ins, tag) for i, (ins, tag) in enumerate(k_reads())], Reads())
+        check(o, then, nm, masked)
+
+    # the masked tiles, then the others, two tiles a turn
+    for masked in (True, False):
+        x = "m" if masked else "p"
+        o(f".Lone_{x}%=:")
+        for now, then, nm in ((A, A2, "A"), (A2, A, "B")):
+            one_tile(now, then, f"1{nm}{x}", masked)
+            o(f"s_cmp_lt_u32 {s(S_LEFT)}, 2", f"s_cbranch_scc1 .Llast_{'B' if nm == 'A' else 'A'}%=")
+        if masked:
+            o(f"s_sub_u32 {s(S_MASKED)}, {s(S_MASKED)}, 2", f"s_cmp_gt_i32 {s(S_MASKED)}, 0")
+        o(f"s_cbranch_scc1 .Lone_m%=" if masked else "s_branch .Lone_p%=")
+    for c, nm in ((A, "A"), (A2, "B")):
+        o(f".Llast_{nm}%=:", *[ins for ins, _ in v_reads()])
+        section(o, pv_products(c), [], [], after_v_reads())
+        o("s_branch .Lend%=")
 
     o(".Lno_chunk%=:")
     more_tiles(o, "n", paged, nt)
