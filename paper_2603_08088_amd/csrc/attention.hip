@@ -2363,18 +2363,22 @@ static bool beyond_array(const etv_attn_desc *h, int ns) { return ns > 1 && spli
 // between differ only in empty splits).  Some 2 * sqrt(tiles) candidates instead of all of them, on every call.
 static int next_split_count(int tiles, int tps) { return tps > 1 ? (tiles + tps - 2) / (tps - 1) : tiles + 1; }
 
-// Launch shape of a bf16 call with heads of 128 on the tile kernels.  Microseconds, fitted to 2900 timings of 170 workloads (B = 1 ... 32,
+// Launch shape of a bf16 call with heads of 128 on the tile kernels.  Microseconds, fitted to 4500 timings of 270 workloads (B = 1 ... 32,
 // T = 6 ... 256, P = 60 ... 32768, every shape at up to twelve split counts): a round of workgroups costs its tiles and a start-up;
 // a tile costs the more, the more of the chip's wavefronts have rows (the clock follows the power); K/V bytes on top, and splits as
-// before.  The pick is within 1.0 % of the best measured shape on average (before: 7 %) and at most 1.7 % behind the pick of the
-// earlier rule, 6 % ahead of it on average.  The wide kernel passes the eight wavefronts of the tile kernel from about 12 tiles a split on: 2 tiles 1.06,
-// 10 tiles 0.98, 20 tiles 0.92, 65 tiles 0.80 of its time.
+// before.  The pick is within 1.0 % of the best measured shape on average (with the constants from before the wide kernel: 7 %)
+// and at most 3.5 % behind the pick of those, 5.4 % ahead of it on average.  The wide kernel passes the eight wavefronts of the
+// tile kernel from about 12 tiles a split on: 2 tiles 1.06, 10 tiles 0.98, 20 tiles 0.92, 65 tiles 0.80 of its time.  With three
+// or four chunks each of its wavefronts has one; it gains over long splits (B = 32, T = 32, P = 4096: 93.6 us, the tile kernel
+// 105.6; B = 8, T = 113, 32/32 heads, P = 8735: 176 and 201), loses over short ones (B = 16, T = 76, 32/32 heads, P = 124: 24.8
+// and 20.0), and with two chunks, half of its wavefronts idle, it is rarely ahead (B = 25, T = 35, 32/32 heads, P = 1653: 142
+// and 123), so it starts at three.
 struct TileShape {
-    int nw, kh, wide;                        // chunks of a workgroup: nw, with key halves nw / 2
+    int nw, kh, wide, chunks;                // wavefronts; key halves; wide; chunks of a workgroup (wide: 4 if it needs no more)
     double alone, least, full, start;        // a tile alone on a compute unit (nw = 4), with few, with all wavefronts busy; a round
 };
-constexpr TileShape kTileShapes[] = {{8, 0, 1, 0.0, 1.05, 1.22, 7.8}, {8, 0, 0, 0.0, 1.31, 1.81, 4.0}, {8, 1, 0, 0.0, 0.82, 1.06, 4.55},
-                                     {4, 0, 0, 1.27, 1.61, 1.95, 3.15}, {4, 1, 0, 0.77, 1.12, 1.30, 2.95}};
+constexpr TileShape kTileShapes[] = {{8, 0, 1, 8, 0.0, 1.05, 1.15, 7.72}, {8, 0, 1, 4, 0.0, 0.71, 0.75, 4.71}, {8, 0, 0, 8, 0.0, 1.26, 1.68, 3.81},
+                                     {8, 1, 0, 4, 0.0, 0.78, 1.00, 4.06}, {4, 0, 0, 4, 1.15, 1.66, 1.86, 2.62}, {4, 1, 0, 2, 0.63, 0.92, 1.24, 3.45}};
 
 static bool shape_allowed(const etv_attn_desc *h, int pairs, int nw, int kh) {
     if (kh && (h->flags & ETV_ATTN_FLAG_WHOLE_TILE)) return false;
@@ -2385,16 +2389,23 @@ static bool shape_allowed(const etv_attn_desc *h, int pairs, int nw, int kh) {
     return true;
 }
 
+static bool tile_shape_allowed(const etv_attn_desc *h, int pairs, const TileShape &sh) {
+    if (sh.wide && (pairs <= 4) != (sh.chunks == 4)) return false;
+    if (h->flags & ETV_ATTN_FLAG_WIDE) return sh.wide;
+    if (sh.wide && sh.chunks == 4) return pairs > 2 && !(h->flags & (ETV_ATTN_FLAG_KEY_HALVES | ETV_ATTN_FLAG_SMALL_WG));
+    return shape_allowed(h, pairs, sh.nw, sh.kh);
+}
+
 static void pick_tile_shape(const etv_attn_desc *h, Plan &pl) {
     const int tiles = max(1, (h->P_max + KT - 1) / KT), B = max(1, h->B);
     const int forced_tps = h->kv_split > 0 ? min(tiles, (h->kv_split + KT - 1) / KT) : 0;
     const double part_us = 2.0 * B * h->Hq * h->T_max * (h->d + 2.0) * 4.0 / 3.0e6;
-    const double fixed = 4.7 + 4.0 * B * h->P_max * (double)h->Hkv * h->d / 33.5e6;
+    const double fixed = 4.66 + 4.0 * B * h->P_max * (double)h->Hkv * h->d / 25.0e6;
     const int tree_tiles = (h->T_max + KT - 1) / KT;
     double best = 1e30;
     for (const TileShape &sh : kTileShapes) {
-        if (h->flags & ETV_ATTN_FLAG_WIDE ? !sh.wide : !shape_allowed(h, pl.pairs, sh.nw, sh.kh)) continue;
-        const int cw = sh.kh ? sh.nw / 2 : sh.nw, wgp = (pl.pairs + cw - 1) / cw;
+        if (!tile_shape_allowed(h, pl.pairs, sh)) continue;
+        const int cw = sh.chunks, wgp = (pl.pairs + cw - 1) / cw;
         const long units = (long)B * h->Hkv * wgp;
         const double held = (double)pl.pairs / (wgp * cw);  // part of a workgroup's chunks that have rows
         for (int ns = forced_tps ? (tiles + forced_tps - 1) / forced_tps : 1, tps; ns <= tiles; ns = forced_tps ? tiles + 1 : next_split_count(tiles, tps)) {
@@ -2405,8 +2416,8 @@ static void pick_tile_shape(const etv_attn_desc *h, Plan &pl) {
             const double slots = sh.nw == 4 && !alone ? 512.0 : 256.0;
             const double busy = sh.full * held * (wgs < slots ? wgs / slots : 1.0);
             const double tile = alone ? sh.alone : (busy > sh.least ? busy : sh.least);
-            const double est = ceil(wgs / slots) * ((tps + tree_tiles * (ns > 1 ? 0.67 : 1.0)) * tile + sh.start) + fixed +
-                               (ns > 1 ? 3.2 + ns * part_us * 0.51 : 0.0);
+            const double est = ceil(wgs / slots) * ((tps + tree_tiles * (ns > 1 ? 0.6 : 1.0)) * tile + sh.start) + fixed +
+                               (ns > 1 ? 2.25 + ns * part_us * 0.6 : 0.0);
             if (est < best) {
                 best = est;
                 pl.nw = sh.nw; pl.kh = sh.kh; pl.wide = sh.wide; pl.wgp = wgp; pl.chunk = tps * KT; pl.nsplit = ns;
