@@ -471,7 +471,7 @@ def main():
     roof["frac"] = roof["achieved"] / roof["peak"]
     roof["traffic"] = traffic_on_file(a.workload)
     roof["plan"] = api.tree_verify_attention_plan(st.desc)
-    roof.update({"kernel": "tree_verify_attention (one layer; attn_mfma_kernel, plus attn_combine_kernel when the keys are split)",
+    roof.update({"kernel": "tree_verify_attention (one layer; attn_wide_kernel, attn_mfma_kernel or attn_blocks_kernel by size, plus attn_combine_kernel when the keys are split)",
                  "avg_launch_us": att_us, "median_launch_us": att_stats["median_us"], "min_launch_us": att_stats["min_us"],
                  "launches_timed": n_samples * a.layers, "algorithmic_bytes": by, "algorithmic_flops": fl,
                  "hbm_gbs": by / (att_us * 1e-6) / 1e9, "mfma_tflops": fl / (att_us * 1e-6) / 1e12,
@@ -649,7 +649,7 @@ def compact(line):
     m = roof.get("measured_mfma_tflops")
     if m:
         roof["measured_mfma_tflops"] = {k: m[k] for k in ("first_launch", "sustained", "attention_products")}
-    roof["kernel"] = "tree_verify_attention (attn_mfma_kernel)"
+    roof["kernel"] = "tree_verify_attention (attn_wide / mfma / blocks_kernel by size)"
     out["roofline"] = r4(roof)
     cpu = line["cpu_baseline"]
     if cpu:

@@ -174,7 +174,7 @@ typedef struct etv_attn_desc {
                                            sequences' lengths (tuning) */
 
 #define ETV_ATTN_FLAG_KEY_BLOCKS 64 /* bf16: every wavefront takes 32-key blocks of its own (tuning) */
-#define ETV_ATTN_FLAG_WIDE 128 /* bf16, heads of 128: workgroups of eight 32-row chunks, two to a wavefront (tuning) */
+#define ETV_ATTN_FLAG_WIDE 128 /* bf16, heads of 128: four wavefronts with up to two 32-row chunks each (tuning) */
 
 ETV_API size_t etv_tree_verify_attention_workspace_bytes(const etv_attn_desc *h_desc);
 
@@ -185,7 +185,7 @@ ETV_API size_t etv_tree_verify_attention_workspace_bytes(const etv_attn_desc *h_
  * and this call shows the outcome, so that a poor pick on another shape or machine can be seen and corrected. */
 typedef struct etv_attn_plan {
     int32_t mfma;        /* 1: the bf16 matrix-core kernels; 0: a kernel with fp32 products */
-    int32_t wavefronts;  /* per workgroup: 4 or 8 (fp32: 4; 1 for the VALU kernel); one that takes two 32-row chunks counts twice */
+    int32_t wavefronts;  /* per workgroup: 4 or 8 (fp32: 4; 1 for the VALU kernel); those that can take two 32-row chunks count twice */
     int32_t key_halves;  /* 1: two wavefronts per 32-row chunk, each with 32 of a tile's 64 keys */
     int32_t ring_stages; /* K/V tiles of LDS ring; 0: every wavefront takes 32-key blocks of its own, no ring */
     int32_t row_groups;  /* workgroups per (split, KV head, sequence); 0 for the VALU kernel */

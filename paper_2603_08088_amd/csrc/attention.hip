@@ -1,10 +1,12 @@
 // tree_verify_attention: tree-masked attention of the draft-tree query rows against the committed
 // prefix cache plus the tree's own K/V (Section 3.3, "Execution view" and "Tree attention mask").
 //
-// Four kernels compute the per-split partial (m, l, O):
+// Five kernels compute the per-split partial (m, l, O):
 //   * attn_mfma_kernel   bf16: K/V tiles staged through LDS, QK^T and PV on
 //                        v_mfma_f32_32x32x16_bf16, online softmax in registers, the ancestor mask applied
 //                        as a per-row bitmask only on the tree tile.
+//   * attn_wide_kernel   bf16, d = 128, many rows over long splits: the same work unit with 64 rows a wavefront, the tile loop
+//                        in assembly (attn_wide_loop.py), v_mfma_f32_16x16x32_bf16.
 //   * attn_blocks_kernel bf16, launches that are short of work: the same products, every wavefront with 32-key blocks of
 //                        its own instead of a tile shared by the workgroup.
 //   * attn_f32_kernel    fp32: both products on v_mfma_f32_16x16x4_f32, no barrier in the tile loop.
@@ -34,8 +36,8 @@ struct AttnParams {
     int nsplit;  // splits the launch provides; sequence b uses max(1, ceil(P_b / chunk)) of them
     // partial results, split-major so that one workgroup writes one contiguous region:
     //   part_o [B][nsplit][Hq][T_max][d], part_m / part_l [B][nsplit][Hq][T_max]
-    int pairs;   // mfma kernel: 32-row chunks of the packed query rows of a KV head
-    int wgp;     // mfma kernel: workgroups per (b, kv head, split) = ceil(pairs / 4)
+    int pairs;   // mfma kernels: 32-row chunks of the packed query rows of a KV head
+    int wgp;     // mfma kernels: workgroups per (b, kv head, split)
     float scale_log2;
     // mfma kernel, batches of 2 .. 64 sequences with splits: the B * nsplit split slots are shared out among the
     // sequences by their lengths (on the device, where the lengths are), slot-major partials
@@ -1305,11 +1307,12 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(AttnParams p) {
 // the matrix instructions of the other.  Swizzles and register layouts are those of attn_mfma_kernel, four ring places of 32 KiB
 // and three tiles in flight.  The loop over the tiles is written by attn_wide_loop.py.
 //
-// A tile of the loop takes 2574 cycles, of which the 64 + 16 matrix instructions are 2176.  What bounds it is the power: the clock is
-// 1.48 GHz with everything in the loop, 1.67 without the tile loads, 1.78 with the matrix instructions alone, and a tile takes 1.73,
-// 1.55 and 1.23 us.  B = 32, T = 128, P = 4096, 32/8 heads: 296 -> 258 us (two rounds of workgroups; of a round's 128 about 15
-// are start-up, the first references and the output); T = 64 158 -> 136; B = 1, T = 128, P = 32768 86 -> 79.  Against
-// the eight wavefronts of attn_mfma_kernel a round costs 4 us more and a tile a quarter less.
+// What bounds a tile is the power.  With 32x32x16 matrix instructions it took 2574 cycles, 2176 of them matrix instructions, and the
+// clock was 1.48 GHz with everything in the loop, 1.67 without the tile loads, 1.78 with the matrix instructions alone: 1.73, 1.55
+// and 1.23 us.  The 16x16x32 instructions that it has now cost the same cycles and less power.  B = 32, P = 4096, 32/8 heads: T = 128
+// 288 us on the tile kernel, 255 here with 32x32x16, 249 now (two rounds of workgroups; of a round's 124 us about 13 are start-up, the
+// first references and the output); T = 32, one chunk a wavefront, 100.6 -> 92.4.  B = 1, T = 128, P = 32768 with its combine: 83.5 ->
+// 76.0.  Against the eight wavefronts of attn_mfma_kernel a round costs 4 us more and a tile a quarter less.
 // ----------------------------------------------------------------------------------------------
 typedef __attribute__((ext_vector_type(32))) float f32x32;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
@@ -2319,10 +2322,10 @@ __global__ void __launch_bounds__(F32_NW * 64, 2) attn_f32_kernel(AttnParams p) 
 // host side
 // ----------------------------------------------------------------------------------------------
 struct Plan {
-    bool mfma, kh;  // mfma: attn_mfma_kernel
+    bool mfma, kh;  // mfma: the bf16 kernels on matrix instructions
     bool f32;       // attn_f32_kernel
     bool blocks;    // attn_blocks_kernel
-    bool wide;      // attn_wide_kernel (nw counts its 32-row chunks, two to a wavefront)
+    bool wide;      // attn_wide_kernel (nw is 8: the chunks that its four wavefronts can take)
     int nw, ns, pairs, wgp, chunk, nsplit;
     bool balanced;  // split slots shared out among the sequences by their lengths, on the device
 };
