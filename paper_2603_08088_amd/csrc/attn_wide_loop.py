@@ -281,28 +281,43 @@ class Reads:
         del self.queue[:max(last + 1, len(self.queue) - 15)]
 
 
-def section(o, products, valu, reads, flying, extra=(), valu_from=8, valu_to=None):
-    """Matrix instructions with the other streams between them.  reads: (slot, instruction, tag); extra: (slot, instruction)."""
+def slots(op):
+    """Issue slots (4 cycles) of an instruction between matrix instructions."""
+    return 2 if op.startswith("v_exp") else 0 if op.startswith("v_mfma") else int(op.split()[1]) + 1 if op.startswith("s_nop") else 1
+
+
+def section(o, products, valu, reads, flying, extra=(), valu_from=2):
+    """Matrix instructions with the other streams between them.  reads: (slot, instruction, tag); extra: (slot, instruction).
+
+    A lone wavefront issues one instruction in four cycles, two of them in the shadow of a 16x16x32 product (64 products alone
+    1048 cycles, with one or two v_fma_f32 behind each 1056 and 1061, with three 1317; two products and then four v_fma_f32: 1332; v_exp_f32
+    counts twice).  There is more to issue than that, so what counts is that no product goes without its two: the vector stream
+    follows the pace of all streams together, and fills up where the others leave a slot."""
     n = len(products)
-    valu_to = n if valu_to is None else valu_to
-    done = 0
+    beside = [[] for _ in range(n)]
+    for slot, ins, tag in reads:
+        beside[slot].append((ins, tag))
+    for slot, ins in extra:
+        beside[slot].append((ins, None))
+    total = sum(slots(ins) for ops in beside for ins, _ in ops) + sum(slots(op) for op in valu)
+    pace, issued, done = max(2.0, total / n), 0, 0
     for i, (text, _) in enumerate(products):
         if i % 4 == 0:   # for four products at a time
             for _, need in products[i:i + 4]:
                 for tag in need:
                     flying.wait_for(o, tag)
         o(text)
-        for slot, ins, tag in reads:
-            if slot == i:
-                o(ins)
+        here = 0
+        for ins, tag in beside[i]:
+            o(ins)
+            here += slots(ins)
+            if tag:
                 flying.issue(tag)
-        for slot, ins in extra:
-            if slot == i:
-                o(ins)
-        if i >= valu_from:
-            upto = len(valu) if i >= valu_to - 1 else (len(valu) * (i + 1 - valu_from)) // (valu_to - valu_from)
-            o(*valu[done:upto])
-            done = upto
+        while i >= valu_from and done < len(valu) and (here < 2 or issued + here + slots(valu[done]) <= pace * (i + 1)):
+            o(valu[done])
+            here += slots(valu[done])
+            done += 1
+        issued += here
     o(*valu[done:])
 
 
@@ -332,7 +347,7 @@ def hand_over(o, nm, paged, nt, steady):
     ask_v, ask_k = loads("V", s(S_STAGE), nt), next_offset(paged) + loads("K", s(S_NEXT), nt) + fetch_id(S_ID, paged)
     scalar = []
     if steady:
-        scalar += ask_v + ask_k
+        scalar += [op for op in ask_v + ask_k if op != "s_nop 0"]   # (a matrix instruction comes between)
     else:
         o(f"s_cmp_lt_u32 {s(S_LEFT)}, 5", f"s_cbranch_scc1 .Lnone_{nm}%=", *ask_v)
         o(f"s_cmp_lt_u32 {s(S_LEFT)}, 6", f"s_cbranch_scc1 .Lnone_{nm}%=", *ask_k)
