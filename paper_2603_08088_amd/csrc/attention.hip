@@ -1309,10 +1309,11 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(AttnParams p) {
 //
 // What bounds a tile is the power.  With 32x32x16 matrix instructions it took 2574 cycles, 2176 of them matrix instructions, and the
 // clock was 1.48 GHz with everything in the loop, 1.67 without the tile loads, 1.78 with the matrix instructions alone: 1.73, 1.55
-// and 1.23 us.  The 16x16x32 instructions that it has now cost the same cycles and less power.  B = 32, P = 4096, 32/8 heads: T = 128
-// 288 us on the tile kernel, 255 here with 32x32x16, 249 now (two rounds of workgroups; of a round's 124 us about 13 are start-up, the
-// first references and the output); T = 32, one chunk a wavefront, 100.6 -> 92.4.  B = 1, T = 128, P = 32768 with its combine: 83.5 ->
-// 76.0.  Against the eight wavefronts of attn_mfma_kernel a round costs 4 us more and a tile a quarter less.
+// and 1.23 us.  The 16x16x32 instructions that it has now cost the same cycles and less power, but leave fewer issue slots beside
+// them (2 against 3 for the same product), so the streams are paced by slots.  B = 32, P = 4096, 32/8 heads: T = 128 288-293 us on the
+// tile kernel, 255 here with 32x32x16, 249 with 16x16x32, 243-247 paced (two rounds of workgroups; of a round's 122 us about 13 are
+// start-up, the first references and the output); T = 32, one chunk a wavefront, 100.6 -> 91.3-93.  B = 1, T = 128, P = 32768 with its
+// combine: 83.5 -> 73.8-75.4.  Against the eight wavefronts of attn_mfma_kernel a round costs 4 us more and a tile a quarter less.
 // ----------------------------------------------------------------------------------------------
 typedef __attribute__((ext_vector_type(32))) float f32x32;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
