@@ -1518,8 +1518,9 @@ __global__ void __launch_bounds__(256, 1) attn_wide_kernel(AttnParams p) {
     };
 
     // Q, 1 KiB a load, laid out like K rows, to the ring's last place and the space behind it; rows that are not there repeat
-    // node 0's.
-    {
+    // node 0's.  A sequence without keys reads none: it has no pass of the loop, whose barriers keep a wavefront's Q apart from the
+    // outputs that others stage in the same LDS.
+    if (edges + nfull > 0) {
         const uint8_t *const qseq = reinterpret_cast<const uint8_t *>(uni64((uint64_t)(uintptr_t)p.q + (size_t)b * p.T_max * p.Hq * ROW_BYTES));
         const uint32_t from = row.in_launch && row.kq < n ? row.at : (uint32_t)(kvh * p.G) * ROW_BYTES;
         const Columns c = columns(lane);
@@ -1602,7 +1603,7 @@ __global__ void __launch_bounds__(256, 1) attn_wide_kernel(AttnParams p) {
         if (more) __builtin_amdgcn_s_barrier();  // nobody reads the places any more
     }
 
-    wait_vmcnt<0>();  // nothing on its way to LDS is left behind (a sequence without keys: Q)
+    wait_vmcnt<0>();  // nothing on its way to LDS is left behind
     // ---- outputs, through the wavefront's own 8 KiB of LDS so that whole rows (of a group: neighbours) go out together:
     // 32 rows of 16 pieces of 16 bytes, piece c of row r at c ^ (r % 16)
     uint8_t *const oseq = static_cast<uint8_t *>(p.out) + (size_t)b * p.T_max * p.Hq * ROW_BYTES;

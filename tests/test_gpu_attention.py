@@ -672,3 +672,23 @@ def test_wide_kernel_in_place_tree_rows(paged):
         torch.cuda.synchronize()
         assert torch.equal(sep, tail) and torch.equal(lse_sep, lse_tail), kv_split
     _check(wl, flags=api.ATTN_FLAG_WIDE)
+
+
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("T", [64, 128, 200])
+def test_wide_kernel_sequences_without_keys(T, paged):
+    """Idle slots of a batch: sequences without nodes and without a prefix beside ordinary ones, sequences without nodes only, a
+    single split (outputs go out directly).  Every row that is not there is zero and -inf, whatever Q, out and lse held before."""
+    rng = np.random.default_rng(9400 + T + paged)
+    P, n = [130, 0, 0, 64, 0, 300, 0, 0], [T, 0, 0, 0, T, 1, 0, 3]
+    wl = _small(rng, len(P), T, 8, 2, 128, P, "bf16", paged, n_nodes=n)
+    assert np.all((np.abs(synth.bf16_bits_to_f32(wl.q[1])) > 0).any(-1))
+    d = DevWorkload(wl)
+    m = api.build_tree_mask(d.parent, d.n_nodes)
+    out, lse = torch.full_like(d.q, 7.5), torch.full((len(P), 8, T), 7.5, device="cuda")
+    gpu_attention(d, m["bitmask"], flags=api.ATTN_FLAG_WIDE, kv_split=4096, out=out, lse=lse)
+    torch.cuda.synchronize()
+    for b in range(len(P)):
+        assert torch.all(out[b, n[b]:] == 0) and torch.all(torch.isneginf(lse[b, :, n[b]:])), b
+    for kv_split in (0, 64, 4096):
+        _check(wl, flags=api.ATTN_FLAG_WIDE, kv_split=kv_split)
