@@ -48,6 +48,7 @@ OA, OB, QA, QB, KF = 0, 64, 128, 160, 192    # accumulation registers: outputs, 
 S_LEFT, S_STAGE, S_NEXT, S_DELTA, S_LIMIT, S_NINF = 40, 41, 42, 43, 44, 45
 S_ID3, S_ID4, S_OFF, S_BASE, S_ID, S_LAST, S_BT, S_LIFT, S_TMP, S_IDX = 46, 47, 48, 50, 52, 53, 54, 56, 58, 59
 S_KP, S_VP, S_STRIDE, S_LDS, S_SCALE, S_Q, S_MASKED, S_DONE, S_CHUNKS = 60, 62, 64, 65, 66, 67, 68, 69, 70
+S_EMPTY = 72               # lanes whose rows of a column block have no finite score yet: two pairs
 
 TILE, STAGE, RING = 16384, 32768, 131072
 
@@ -194,7 +195,9 @@ LIFTS = []
 
 def lift(o, c, label, masked):
     """A row is in the lanes l, l + 16, l + 32, l + 48; one whose sum is above the limit in any of them moves its reference to the
-    largest score of the tile.  The rows that do not are computed again to the same values."""
+    largest score of the tile.  The rows that do not are computed again to the same values.  Where that score is -inf too (products
+    that overflow) the keys weigh nothing: the tile is computed against zero, and the reference stays where it was before the
+    first finite score."""
     o(f".Llift_{label}%=:", "s_nop 15")
     for cb in range(2):
         o(f"v_cmp_nle_f32 vcc, {v(SUM + 4 * cb)}, {s(S_LIMIT)}", f"s_or_b32 {s(S_LIFT)}, vcc_lo, vcc_hi", f"s_lshr_b32 {s(S_TMP)}, {s(S_LIFT)}, 16",
@@ -216,6 +219,8 @@ def lift(o, c, label, masked):
             o(f"v_mov_b32 {v(X + 1)}, {v(X)}", "s_nop 1", f"v_permlane{swap}_swap_b32 {v(X)}, {v(X + 1)}", "s_nop 1", f"v_max_f32 {v(X)}, {v(X)}, {v(X + 1)}")
         o(f"v_mul_f32 {v(X)}, {s(S_SCALE)}, {v(X)}",
           f"v_cndmask_b32_e64 {v(X)}, {v(c.nm + cb)}, -{v(X)}, {s(S_LIFT, 2)}",        # minus the new reference
+          f"v_cmp_eq_f32_e64 {s(S_EMPTY + 2 * cb, 2)}, {v(X)}, -{s(S_NINF)}", "s_nop 1",
+          f"v_cndmask_b32_e64 {v(X)}, {v(X)}, 0, {s(S_EMPTY + 2 * cb, 2)}",
           f"v_sub_f32 {v(X + 1)}, {v(X)}, {v(c.nm + cb)}", f"v_exp_f32 {v(X + 1)}, {v(X + 1)}", f"v_mov_b32 {v(c.nm + cb)}, {v(X)}",
           f"v_cmp_neq_f32 vcc, 0, {v(c.l + cb)}",
           f"v_cndmask_b32_e64 {v(X + 1)}, 1.0, {v(X + 1)}, {s(S_LIFT, 2)}", f"s_cbranch_vccz .Lempty_{label}{cb}%=",   # nothing to rescale yet
@@ -227,6 +232,7 @@ def lift(o, c, label, masked):
             o(*[f"v_accvgpr_write_b32 {a(r)}, {v(TMP + i)}" for i, r in enumerate(o_regs)])
         o(f".Lempty_{label}{cb}%=:")
     o(*softmax(c, masked))
+    o(f"v_mov_b32 {v(X)}, 0x7f800000", *[f"v_cndmask_b32_e64 {v(c.nm + cb)}, {v(c.nm + cb)}, {v(X)}, {s(S_EMPTY + 2 * cb, 2)}" for cb in range(2)])
     o("s_nop 4", f"s_branch .Llifted_{label}%=")
 
 
@@ -528,6 +534,7 @@ def clobbers():
     names = [f"v{r}" for r in [*range(32, SUM + 8), ONES, ONES + 1] if r not in owned]
     names += [f"a{r}" for r in range(QA, KF + 64)]
     names += [f"s{r}" for r in range(S_STAGE, S_KP) if r not in (S_OFF, S_OFF + 1, S_BT, S_BT + 1, S_IDX, S_LAST)]
+    names += [f"s{r}" for r in range(S_EMPTY, S_EMPTY + 4)]
     return names + ["vcc", "scc", "memory"]   # m0: as everywhere, set before each use
 
 

@@ -692,3 +692,22 @@ def test_wide_kernel_sequences_without_keys(T, paged):
         assert torch.all(out[b, n[b]:] == 0) and torch.all(torch.isneginf(lse[b, :, n[b]:])), b
     for kv_split in (0, 64, 4096):
         _check(wl, flags=api.ATTN_FLAG_WIDE, kv_split=kv_split)
+
+
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("flags", SHAPES["bf16"] + [api.ATTN_FLAG_WIDE])
+def test_masked_tiles_whose_scores_overflow_come_first(flags, paged):
+    """A prefix that ends inside a tile, its last keys (one, two, or the whole short prefix) scoring -inf for every row: products
+    beyond the fp32 range.  On the wide kernel such a tile comes first where a split has no full tile, or two tree tiles.  These keys
+    weigh nothing, as in the float64 oracle; tolerances as everywhere."""
+    rng = np.random.default_rng(9500 + flags + paged)
+    P = [257, 20, 130, 20]
+    wl = _small(rng, 4, 100, 8, 2, 128, P, "bf16", paged, n_nodes=[100, 100, 70, 9])
+    big = synth.f32_to_bf16_bits(np.float32([1e38, -1e38]))
+    wl.q[..., 3], wl.kt[..., 3], wl.k_cache[..., 3] = big[0], 0, 0
+    for b, lo in ((0, 256), (1, 0), (2, 128), (3, 0)):
+        for pos in range(lo, P[b]):
+            at = (wl.block_table[b, pos // synth.BLOCK], slice(None), pos % synth.BLOCK) if paged else (b, pos)
+            wl.k_cache[at][..., 3] = big[1]
+    for kv_split in (0, 64, 4096):
+        _check(wl, flags=flags, kv_split=kv_split)
