@@ -18,7 +18,7 @@ The first tiles of a split (up to three: the tree, a ragged end of the prefix) h
 softmax go through the row's visibility bits.
 
 The softmax takes no maximum: probabilities are 2^(score - reference), and their sum over the lane's keys, which is needed
-anyway, tells whether the reference is too low (a sum above 2^20, or not a number).  Only then the row's maximum is taken, O
+anyway, tells whether the reference is too low (a sum above 2^8, or not a number).  Only then the row's maximum is taken, O
 and l are rescaled and the probabilities computed again (`lift`).
 
 The matrix instructions are 16x16x32: they move less accumulator data per product than 32x32x16, and the launch is limited by the
@@ -48,7 +48,7 @@ OA, OB, QA, QB, KF = 0, 64, 128, 160, 192    # accumulation registers: outputs, 
 S_LEFT, S_STAGE, S_NEXT, S_DELTA, S_LIMIT, S_NINF = 40, 41, 42, 43, 44, 45
 S_ID3, S_ID4, S_OFF, S_BASE, S_ID, S_LAST, S_BT, S_LIFT, S_TMP, S_IDX = 46, 47, 48, 50, 52, 53, 54, 56, 58, 59
 S_KP, S_VP, S_STRIDE, S_LDS, S_SCALE, S_Q, S_MASKED, S_DONE, S_CHUNKS = 60, 62, 64, 65, 66, 67, 68, 69, 70
-S_EMPTY = 72               # lanes whose rows of a column block have no finite score yet: two pairs
+S_EMPTY = 72               # lanes whose rows have no finite score yet
 
 TILE, STAGE, RING = 16384, 32768, 131072
 
@@ -195,32 +195,35 @@ LIFTS = []
 
 def lift(o, c, label, masked):
     """A row is in the lanes l, l + 16, l + 32, l + 48; one whose sum is above the limit in any of them moves its reference to the
-    largest score of the tile.  The rows that do not are computed again to the same values.  Where that score is -inf too (products
-    that overflow) the keys weigh nothing: the tile is computed against zero, and the reference stays where it was before the
-    first finite score."""
+    largest score of the tile.  The rows of its column block that do not are computed again to the same values; a column block
+    without such a row is left alone.  Where that score is -inf too (products that overflow) the keys weigh nothing: the tile is
+    computed against zero, and the reference stays where it was before the first finite score.
+
+    The limit is the tile kernel's: it moves a reference that a score passes by 2^8, whose weight is then 1 and exact in bf16.  Every row that
+    it would move moves here.  With a limit of 2^20 the error against float64 grew by up to 4 % (Q x 4; lse by 40 %).
+
+    The matrix cores wait meanwhile.  B = 32, T = 128, P = 4096 in us, Q x 1, 3, 6, 12: tile kernel 293, 299, 304, 307; here 247, 269, 303-308,
+    315-319; with both column blocks computed whichever row moved 246, 286, 329, 350."""
     o(f".Llift_{label}%=:", "s_nop 15")
     for cb in range(2):
-        o(f"v_cmp_nle_f32 vcc, {v(SUM + 4 * cb)}, {s(S_LIMIT)}", f"s_or_b32 {s(S_LIFT)}, vcc_lo, vcc_hi", f"s_lshr_b32 {s(S_TMP)}, {s(S_LIFT)}, 16",
+        pairs = [i for i in range(16) if scores(c, i)[2] == cb]
+        o(f"v_cmp_nle_f32 vcc, {v(SUM + 4 * cb)}, {s(S_LIMIT)}", f"s_cbranch_vccz .Lkeep_{label}{cb}%=",
+          f"s_or_b32 {s(S_LIFT)}, vcc_lo, vcc_hi", f"s_lshr_b32 {s(S_TMP)}, {s(S_LIFT)}, 16",
           f"s_or_b32 {s(S_LIFT)}, {s(S_LIFT)}, {s(S_TMP)}", f"s_and_b32 {s(S_LIFT)}, {s(S_LIFT)}, 0xffff", f"s_lshl_b32 {s(S_TMP)}, {s(S_LIFT)}, 16",
           f"s_or_b32 {s(S_LIFT)}, {s(S_LIFT)}, {s(S_TMP)}", f"s_mov_b32 {s(S_LIFT + 1)}, {s(S_LIFT)}")
-        first = True
-        for i in range(16):
-            s0, bit, own = scores(c, i)
-            if own != cb:
-                continue
-            at = s0
+        for n, i in enumerate(pairs):
+            at, bit, _ = scores(c, i)
             if masked:
                 o(*[f"v_bfe_i32 {v(TMP + x)}, {v(c.mask)}, {bit + x}, 1" for x in range(2)])
-                o(*[f"v_bfi_b32 {v(TMP + x)}, {v(TMP + x)}, {v(s0 + x)}, {s(S_NINF)}" for x in range(2)])
+                o(*[f"v_bfi_b32 {v(TMP + x)}, {v(TMP + x)}, {v(at + x)}, {s(S_NINF)}" for x in range(2)])
                 at = TMP
-            o(f"v_maximum3_f32 {v(X)}, {v(at) if first else v(X)}, {v(at)}, {v(at + 1)}")
-            first = False
+            o(f"v_maximum3_f32 {v(X)}, {v(X if n else at)}, {v(at)}, {v(at + 1)}")
         for swap in ("32", "16"):
             o(f"v_mov_b32 {v(X + 1)}, {v(X)}", "s_nop 1", f"v_permlane{swap}_swap_b32 {v(X)}, {v(X + 1)}", "s_nop 1", f"v_max_f32 {v(X)}, {v(X)}, {v(X + 1)}")
         o(f"v_mul_f32 {v(X)}, {s(S_SCALE)}, {v(X)}",
           f"v_cndmask_b32_e64 {v(X)}, {v(c.nm + cb)}, -{v(X)}, {s(S_LIFT, 2)}",        # minus the new reference
-          f"v_cmp_eq_f32_e64 {s(S_EMPTY + 2 * cb, 2)}, {v(X)}, -{s(S_NINF)}", "s_nop 1",
-          f"v_cndmask_b32_e64 {v(X)}, {v(X)}, 0, {s(S_EMPTY + 2 * cb, 2)}",
+          f"v_cmp_eq_f32_e64 {s(S_EMPTY, 2)}, {v(X)}, -{s(S_NINF)}", "s_nop 1",
+          f"v_cndmask_b32_e64 {v(X)}, {v(X)}, 0, {s(S_EMPTY, 2)}",
           f"v_sub_f32 {v(X + 1)}, {v(X)}, {v(c.nm + cb)}", f"v_exp_f32 {v(X + 1)}, {v(X + 1)}", f"v_mov_b32 {v(c.nm + cb)}, {v(X)}",
           f"v_cmp_neq_f32 vcc, 0, {v(c.l + cb)}",
           f"v_cndmask_b32_e64 {v(X + 1)}, 1.0, {v(X + 1)}, {s(S_LIFT, 2)}", f"s_cbranch_vccz .Lempty_{label}{cb}%=",   # nothing to rescale yet
@@ -231,8 +234,21 @@ def lift(o, c, label, masked):
             o(*[f"v_mul_f32 {v(TMP + i)}, {v(TMP + i)}, {v(X + 1)}" for i in range(8)])
             o(*[f"v_accvgpr_write_b32 {a(r)}, {v(TMP + i)}" for i, r in enumerate(o_regs)])
         o(f".Lempty_{label}{cb}%=:")
-    o(*softmax(c, masked))
-    o(f"v_mov_b32 {v(X)}, 0x7f800000", *[f"v_cndmask_b32_e64 {v(c.nm + cb)}, {v(c.nm + cb)}, {v(X)}, {s(S_EMPTY + 2 * cb, 2)}" for cb in range(2)])
+        # `softmax` of the column block, four pairs of P at a time
+        for ks in range(2):
+            four = pairs[4 * ks:4 * ks + 4]
+            total = v(SUM + 4 * cb, 4)
+            o(*[f"v_fma_f32 {v(TMP + 2 * n + x)}, {v(scores(c, i)[0] + x)}, {s(S_SCALE)}, {v(c.nm + cb)}" for n, i in enumerate(four) for x in range(2)])
+            if masked:
+                for n, i in enumerate(four):
+                    o(*[f"v_bfe_i32 {v(X + x)}, {v(c.mask)}, {scores(c, i)[1] + x}, 1" for x in range(2)])
+                    o(*[f"v_bfi_b32 {v(TMP + 2 * n + x)}, {v(X + x)}, {v(TMP + 2 * n + x)}, {s(S_NINF)}" for x in range(2)])
+            o(*[f"v_exp_f32 {v(TMP + n)}, {v(TMP + n)}" for n in range(8)])
+            o(*[f"v_cvt_pk_bf16_f32 {v(c.P + i)}, {v(TMP + 2 * n)}, {v(TMP + 2 * n + 1)}" for n, i in enumerate(four)])
+            for half in range(2):
+                o("s_nop 2", f"v_mfma_f32_4x4x4_16b_bf16 {total}, {v(ONES, 2)}, {v(c.P + four[2 * half], 2)}, {total if ks or half else 0}")
+        o(f"v_mov_b32 {v(X)}, 0x7f800000", f"v_cndmask_b32_e64 {v(c.nm + cb)}, {v(c.nm + cb)}, {v(X)}, {s(S_EMPTY, 2)}")
+        o(f".Lkeep_{label}{cb}%=:")
     o("s_nop 4", f"s_branch .Llifted_{label}%=")
 
 
@@ -467,7 +483,7 @@ def program(paged, nt):
     o = Out()
     LIFTS.clear()
     fly = Reads()
-    o(f"s_mov_b32 {s(S_LIMIT)}, 0x49800000", f"s_mov_b32 {s(S_NINF)}, 0xff800000",       # 2^20, -inf
+    o(f"s_mov_b32 {s(S_LIMIT)}, 0x43800000", f"s_mov_b32 {s(S_NINF)}, 0xff800000",       # 2^8, -inf
       f"v_mov_b32 {v(ONES)}, 0x3f803f80", f"v_mov_b32 {v(ONES + 1)}, 0x3f803f80",
       f"s_mov_b32 {s(S_STAGE)}, 0", f"s_mov_b32 {s(S_NEXT)}, {STAGE}", f"s_mov_b32 {s(S_DELTA)}, {STAGE}")
     if paged:
@@ -534,7 +550,7 @@ def clobbers():
     names = [f"v{r}" for r in [*range(32, SUM + 8), ONES, ONES + 1] if r not in owned]
     names += [f"a{r}" for r in range(QA, KF + 64)]
     names += [f"s{r}" for r in range(S_STAGE, S_KP) if r not in (S_OFF, S_OFF + 1, S_BT, S_BT + 1, S_IDX, S_LAST)]
-    names += [f"s{r}" for r in range(S_EMPTY, S_EMPTY + 4)]
+    names += [f"s{r}" for r in range(S_EMPTY, S_EMPTY + 2)]
     return names + ["vcc", "scc", "memory"]   # m0: as everywhere, set before each use
 
 

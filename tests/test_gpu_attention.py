@@ -711,3 +711,27 @@ def test_masked_tiles_whose_scores_overflow_come_first(flags, paged):
             wl.k_cache[at][..., 3] = big[1]
     for kv_split in (0, 64, 4096):
         _check(wl, flags=flags, kv_split=kv_split)
+
+
+@pytest.mark.parametrize("flags", [api.ATTN_FLAG_WIDE] + SHAPES["bf16"])
+def test_a_key_far_above_the_first_reference_weighs_exactly_one(flags):
+    """A key 9 to 18 log2 units above all that its row has met, the rest far below: the reference moves there, so that its weight is 1
+    and the sum of the weights exact.  What is left of the error is fp32: a product of two bf16 values, its scaling and a logarithm, each
+    off by at most 2^-23 of some 20 log2 units, and the weight of key 0, at most 2^-9, rounded by 2^-9 of it: 2^-17, four times that
+    allowed.  A weight rounded to bf16 is off by up to 2^-9."""
+    rng = np.random.default_rng(9600 + flags)
+    T, P, scale = 128, 300, 0.4
+    wl = _small(rng, 1, T, 8, 2, 128, [P], "bf16", False)
+    bf = synth.f32_to_bf16_bits
+    wl.q[:], wl.k_cache[:], wl.kt[:] = 0, 0, 0
+    wl.q[..., 5] = bf(rng.uniform(1.0, 2.0, wl.q.shape[:-1]).astype(np.float32))
+    wl.k_cache[..., 5], wl.kt[..., 5] = bf(np.float32([-128.0]))[0], bf(np.float32([-128.0]))[0]
+    wl.k_cache[:, 0, :, 5] = 0
+    wl.k_cache[:, 100, :, 5] = bf(np.float32([16.0]))[0]
+    d = DevWorkload(wl)
+    m = api.build_tree_mask(d.parent, d.n_nodes)
+    dense = oracle.build_tree_mask(wl.parent, wl.n_nodes)["dense"]
+    _, ref = oracle.tree_verify_attention(wl.q, wl.k_cache, wl.v_cache, wl.prefix_len, wl.kt, wl.vt, dense, wl.n_nodes, dtype="bf16", scale=scale)
+    _, lse = gpu_attention(d, m["bitmask"], flags=flags, kv_split=4096, scale=scale)
+    err = np.abs(to_host_f64(lse) - ref).max()
+    assert err <= 2.0 ** -15, err
