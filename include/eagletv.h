@@ -199,6 +199,16 @@ typedef struct etv_attn_plan {
 
 ETV_API int32_t etv_tree_verify_attention_plan(const etv_attn_desc *h_desc, etv_attn_plan *out);
 
+/* Which kernel that launch shape belongs to (host only): an ETV_ATTN_KERNEL_*, or a negative status.  The tile kernel
+ * with eight wavefronts and the wide kernel have the same figures in etv_attn_plan. */
+#define ETV_ATTN_KERNEL_GENERIC 0    /* a workgroup per query row, fp32 VALU */
+#define ETV_ATTN_KERNEL_F32 1        /* fp32 matrix cores */
+#define ETV_ATTN_KERNEL_TILE 2       /* bf16: K/V tiles shared by four or eight wavefronts */
+#define ETV_ATTN_KERNEL_WIDE 3       /* bf16, heads of 128: up to two 32-row chunks a wavefront (ETV_ATTN_FLAG_WIDE) */
+#define ETV_ATTN_KERNEL_KEY_BLOCKS 4 /* bf16: 32-key blocks of a wavefront's own (ETV_ATTN_FLAG_KEY_BLOCKS) */
+
+ETV_API int32_t etv_tree_verify_attention_kernel(const etv_attn_desc *h_desc);
+
 ETV_API int32_t etv_tree_verify_attention(const etv_attn_desc *h_desc, const void *q, const void *k_cache,
                                   const void *v_cache, const int32_t *block_table, const int32_t *prefix_len,
                                   const void *kt, const void *vt, const uint64_t *bitmask, const int32_t *n_nodes,

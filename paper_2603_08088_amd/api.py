@@ -32,13 +32,14 @@ ATTN_FLAG_LARGE_WG = 16
 ATTN_FLAG_UNIFORM_SPLITS = 32
 ATTN_FLAG_KEY_BLOCKS = 64
 ATTN_FLAG_WIDE = 128
+ATTN_KERNELS = ("generic", "f32", "tile", "wide", "key_blocks")   # by ETV_ATTN_KERNEL_*
 MAX_TREE, ATTN_MAX_TREE = 256, 256
 ATTN_STATIC_WORKSPACE_BYTES = 64 << 20
 
 EXPORTS = ("etv_status_string", "etv_version", "etv_last_hip_error", "etv_build_tree_mask",
            "etv_tensorize_tree",
-           "etv_tree_verify_attention_workspace_bytes", "etv_tree_verify_attention_plan", "etv_tree_verify_attention",
-           "etv_tree_verify_attention_static", "etv_safe_gather_paths",
+           "etv_tree_verify_attention_workspace_bytes", "etv_tree_verify_attention_plan", "etv_tree_verify_attention_kernel",
+           "etv_tree_verify_attention", "etv_tree_verify_attention_static", "etv_safe_gather_paths",
            "etv_evaluate_posterior_workspace_bytes", "etv_evaluate_posterior", "etv_commit_accepted_kv",
            "etv_verify_epilogue", "etv_lm_head_argmax_workspace_bytes", "etv_lm_head_argmax",
            "etv_lm_head_packed_bytes", "etv_pack_lm_head", "etv_replicate_branches", "etv_commit_path_indices")
@@ -94,6 +95,8 @@ def lib():
         l.etv_tree_verify_attention_workspace_bytes.argtypes = [C.POINTER(AttnDesc)]
         l.etv_tree_verify_attention_plan.restype = i32
         l.etv_tree_verify_attention_plan.argtypes = [C.POINTER(AttnDesc), C.POINTER(AttnPlan)]
+        l.etv_tree_verify_attention_kernel.restype = i32
+        l.etv_tree_verify_attention_kernel.argtypes = [C.POINTER(AttnDesc)]
         l.etv_tree_verify_attention.restype = i32
         l.etv_tree_verify_attention.argtypes = [C.POINTER(AttnDesc)] + [vp] * 12 + [sz, vp]
         l.etv_tree_verify_attention_static.restype = i32
@@ -229,6 +232,13 @@ def tree_verify_attention_plan(dsc: AttnDesc) -> Dict[str, int]:
     pl = AttnPlan()
     _check("etv_tree_verify_attention_plan", lib().etv_tree_verify_attention_plan(C.byref(dsc), C.byref(pl)))
     return {n: int(getattr(pl, n)) for n, _ in AttnPlan._fields_ if n != "reserved"}
+
+
+def tree_verify_attention_kernel(dsc: AttnDesc) -> str:
+    """Which of ATTN_KERNELS the library picks for this descriptor (host only)."""
+    rc = lib().etv_tree_verify_attention_kernel(C.byref(dsc))
+    _check("etv_tree_verify_attention_kernel", min(rc, 0))
+    return ATTN_KERNELS[rc]
 
 
 def tree_verify_attention(q, k_cache, v_cache, prefix_len, kt, vt, bitmask, n_nodes, *, P_max: int,

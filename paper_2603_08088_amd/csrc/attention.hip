@@ -2656,6 +2656,13 @@ extern "C" int32_t etv_tree_verify_attention_plan(const etv_attn_desc *h, etv_at
     return ETV_OK;
 }
 
+extern "C" int32_t etv_tree_verify_attention_kernel(const etv_attn_desc *h) {
+    if (!h || !etv::supported(h) || h->Hq % h->Hkv != 0) return ETV_ERR_INVALID_ARG;
+    const etv::Plan pl = etv::make_plan(h);
+    if (!pl.mfma) return pl.f32 ? ETV_ATTN_KERNEL_F32 : ETV_ATTN_KERNEL_GENERIC;
+    return pl.blocks ? ETV_ATTN_KERNEL_KEY_BLOCKS : (pl.wide ? ETV_ATTN_KERNEL_WIDE : ETV_ATTN_KERNEL_TILE);
+}
+
 extern "C" size_t etv_tree_verify_attention_workspace_bytes(const etv_attn_desc *h) {
     if (!h || !etv::supported(h) || h->B == 0) return 0;
     etv::Plan pl = etv::make_plan(h);

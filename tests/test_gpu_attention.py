@@ -44,8 +44,10 @@ def _error_report():
             json.dump(_WORST, f, indent=1, sort_keys=True)
 
 
-def _check(wl, *, kv_split=0, flags=0, check_lse=True, rows=None):
+def _check(wl, *, kv_split=0, flags=0, check_lse=True, rows=None, kernel=None):
     d = DevWorkload(wl)
+    if kernel:      # the one that the case is about
+        assert api.tree_verify_attention_kernel(api.attn_desc(d.q, d.kt, d.k_cache, d.block_table, d.P_max, kv_split=kv_split, flags=flags)) == kernel
     m = api.build_tree_mask(d.parent, d.n_nodes)
     out, lse = gpu_attention(d, m["bitmask"], kv_split=kv_split, flags=flags)
     torch.cuda.synchronize()
@@ -226,9 +228,8 @@ def test_fp32_kernel_tile_and_chunk_edges(d, paged):
             _check(wl, flags=api.ATTN_FLAG_GENERIC)
 
 
-@pytest.mark.parametrize("flags", [api.ATTN_FLAG_WHOLE_TILE | api.ATTN_FLAG_LARGE_WG, api.ATTN_FLAG_WHOLE_TILE | api.ATTN_FLAG_SMALL_WG,
-                                   api.ATTN_FLAG_KEY_HALVES | api.ATTN_FLAG_LARGE_WG])
-@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("d,flags", [(d, flags) for flags in (api.ATTN_FLAG_WHOLE_TILE | api.ATTN_FLAG_LARGE_WG, api.ATTN_FLAG_WHOLE_TILE | api.ATTN_FLAG_SMALL_WG,
+                                                              api.ATTN_FLAG_KEY_HALVES | api.ATTN_FLAG_LARGE_WG) for d in (64, 128)] + [(128, api.ATTN_FLAG_WIDE)])
 def test_row_maximum_uses_the_finished_scores(d, flags):
     """The reference of a row's softmax must come from the scores after the last matrix instruction.  Keys 0 and 32 of the
     first tile (read first by the maximum) get scores of hundreds of log2 units that sit entirely in the last 16
@@ -248,7 +249,7 @@ def test_row_maximum_uses_the_finished_scores(d, flags):
 
 # every kernel shape of bf16, and the one of fp32
 SHAPES = {"bf16": [0, api.ATTN_FLAG_KEY_BLOCKS, api.ATTN_FLAG_WHOLE_TILE | api.ATTN_FLAG_SMALL_WG, api.ATTN_FLAG_WHOLE_TILE | api.ATTN_FLAG_LARGE_WG,
-                   api.ATTN_FLAG_KEY_HALVES | api.ATTN_FLAG_SMALL_WG, api.ATTN_FLAG_KEY_HALVES | api.ATTN_FLAG_LARGE_WG], "f32": [0]}
+                   api.ATTN_FLAG_KEY_HALVES | api.ATTN_FLAG_SMALL_WG, api.ATTN_FLAG_KEY_HALVES | api.ATTN_FLAG_LARGE_WG, api.ATTN_FLAG_WIDE], "f32": [0]}
 
 
 @pytest.mark.parametrize("dtype,d", [("bf16", 64), ("f32", 64), ("f32", 128)])
@@ -634,17 +635,17 @@ def test_key_block_kernel_edges(d, paged):
 def test_wide_kernel_edges(T, Hq, Hkv, paged):
     """Two chunks per wavefront: splits of 0 ... 14 full tiles (fewer than the ring, its start, its last five), no to five tiles
     with masked keys ahead of them (trees of every mask word, prefixes that end inside a tile), groups whose last wavefronts hold
-    one chunk or none, sequences whose few nodes leave whole chunks without rows; scores so far apart that the references move
+    one chunk or none, sequences whose few nodes leave whole chunks without rows, or that have none; scores so far apart that the references move
     again and again (Q x 24).  The bars are those of every bf16 case."""
     flag = api.ATTN_FLAG_WIDE
     rng = np.random.default_rng(9100 + T + paged)
-    P = [0, 1, 63, 64, 65, 129, 256, 321, 449, 640, 900] if T < 100 else [0, 64, 200, 449]
-    n = [T, 1, T - 1, T // 2, 9, T, T, T // 3, T, 2, T] if T < 100 else [T, T - 1, T // 2, T]
+    P = [0, 1, 63, 64, 65, 129, 256, 321, 449, 640, 900, 0, 321] if T < 100 else [0, 64, 200, 449, 0, 130]
+    n = [T, 1, T - 1, T // 2, 9, T, T, T // 3, T, 2, T, 0, 0] if T < 100 else [T, T - 1, T // 2, T, 0, 0]
     for q_scale in (1.0, 24.0):
         wl = _small(rng, len(P), T, Hq, Hkv, 128, P, "bf16", paged, n_nodes=n, q_scale=q_scale)
         for kv_split in (0, 64, 192, 448, 4096):
-            _check(wl, flags=flag, kv_split=kv_split)
-        _check(wl, flags=flag | api.ATTN_FLAG_UNIFORM_SPLITS, kv_split=128)
+            _check(wl, flags=flag, kv_split=kv_split, kernel="wide")
+        _check(wl, flags=flag | api.ATTN_FLAG_UNIFORM_SPLITS, kv_split=128, kernel="wide")
     d = api.AttnDesc(B=len(P), T_max=T, Hq=Hq, Hkv=Hkv, d=128, dtype=api.BF16, P_cap=1200, P_max=900, flags=flag)
     assert api.tree_verify_attention_plan(d)["wavefronts"] == 8 and api.tree_verify_attention_plan(d)["ring_stages"] == 4
 
@@ -671,7 +672,7 @@ def test_wide_kernel_in_place_tree_rows(paged):
                                                    P_max=dv.P_max, block_table=dv.block_table, flags=api.ATTN_FLAG_WIDE, kv_split=kv_split)
         torch.cuda.synchronize()
         assert torch.equal(sep, tail) and torch.equal(lse_sep, lse_tail), kv_split
-    _check(wl, flags=api.ATTN_FLAG_WIDE)
+    _check(wl, flags=api.ATTN_FLAG_WIDE, kernel="wide")
 
 
 @pytest.mark.parametrize("paged", [False, True])
@@ -691,11 +692,11 @@ def test_wide_kernel_sequences_without_keys(T, paged):
     for b in range(len(P)):
         assert torch.all(out[b, n[b]:] == 0) and torch.all(torch.isneginf(lse[b, :, n[b]:])), b
     for kv_split in (0, 64, 4096):
-        _check(wl, flags=api.ATTN_FLAG_WIDE, kv_split=kv_split)
+        _check(wl, flags=api.ATTN_FLAG_WIDE, kv_split=kv_split, kernel="wide")
 
 
 @pytest.mark.parametrize("paged", [False, True])
-@pytest.mark.parametrize("flags", SHAPES["bf16"] + [api.ATTN_FLAG_WIDE])
+@pytest.mark.parametrize("flags", SHAPES["bf16"])
 def test_masked_tiles_whose_scores_overflow_come_first(flags, paged):
     """A prefix that ends inside a tile, its last keys (one, two, or the whole short prefix) scoring -inf for every row: products
     beyond the fp32 range.  On the wide kernel such a tile comes first where a split has no full tile, or two tree tiles.  These keys
@@ -713,7 +714,7 @@ def test_masked_tiles_whose_scores_overflow_come_first(flags, paged):
         _check(wl, flags=flags, kv_split=kv_split)
 
 
-@pytest.mark.parametrize("flags", [api.ATTN_FLAG_WIDE] + SHAPES["bf16"])
+@pytest.mark.parametrize("flags", SHAPES["bf16"])
 def test_a_key_far_above_the_first_reference_weighs_exactly_one(flags):
     """A key 9 to 18 log2 units above all that its row has met, the rest far below: the reference moves there, so that its weight is 1
     and the sum of the weights exact.  What is left of the error is fp32: a product of two bf16 values, its scaling and a logarithm, each

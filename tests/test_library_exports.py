@@ -85,6 +85,27 @@ def test_launch_plan_is_reported_and_follows_the_tuning_flags():
     assert api.tree_verify_attention_plan(f32)["mfma"] == 0
 
 
+def test_the_kernel_of_a_plan_is_reported():
+    """Host only: each kernel by a call that takes it on its own, and by the flag that asks for it."""
+    import pytest
+
+    def kernel(flags=0, **kw):
+        c = dict(dict(B=32, T_max=128, Hq=32, Hkv=8, d=128, dtype=api.BF16, P_cap=4096, P_max=4096, flags=flags), **kw)
+        return api.tree_verify_attention_kernel(api.AttnDesc(**c))
+    assert kernel() == "wide"                                           # many rows, long splits
+    assert kernel(B=1, T_max=60, P_max=2048) == "key_blocks"            # a launch that fits the chip at once
+    assert kernel(T_max=16) == "tile"
+    assert kernel(dtype=api.F32, d=64) == kernel(dtype=api.F32) == "f32"
+    assert kernel(scale=-1.0) == kernel(flags=api.ATTN_FLAG_GENERIC) == kernel(dtype=api.F32, flags=api.ATTN_FLAG_GENERIC) == "generic"
+    assert kernel(flags=api.ATTN_FLAG_KEY_BLOCKS) == kernel(d=64, flags=api.ATTN_FLAG_KEY_BLOCKS) == "key_blocks"
+    assert kernel(d=64) == "tile"
+    for T in (1, 33, 64, 65, 256):
+        for P in (0, 1, 900, 4096):
+            assert kernel(T_max=T, P_max=P, flags=api.ATTN_FLAG_WIDE) == "wide", (T, P)
+    with pytest.raises(api.EtvError):
+        kernel(Hq=9)
+
+
 def test_struct_layouts_match_the_header():
     assert ctypes.sizeof(api.AttnDesc) == 14 * 4
     assert ctypes.sizeof(api.AttnPlan) == 8 * 4 + 8
