@@ -174,7 +174,8 @@ typedef struct etv_attn_desc {
                                            sequences' lengths (tuning) */
 
 #define ETV_ATTN_FLAG_KEY_BLOCKS 64 /* bf16: every wavefront takes 32-key blocks of its own (tuning) */
-#define ETV_ATTN_FLAG_WIDE 128 /* bf16, heads of 128: four wavefronts with up to two 32-row chunks each (tuning) */
+#define ETV_ATTN_FLAG_WIDE 128 /* bf16, heads of 128: four wavefronts with up to two 32-row chunks each; goes before the four
+                                  flags of tile kernel shapes, any of which keeps the wide kernel out otherwise (tuning) */
 
 ETV_API size_t etv_tree_verify_attention_workspace_bytes(const etv_attn_desc *h_desc);
 

@@ -2394,11 +2394,12 @@ static bool shape_allowed(const etv_attn_desc *h, int pairs, int nw, int kh) {
     return true;
 }
 
+// Flags that ask for a shape of the tile kernel leave the wide one out, unless its own flag is there too.
 static bool tile_shape_allowed(const etv_attn_desc *h, int pairs, const TileShape &sh) {
-    if (sh.wide && (pairs <= 4) != (sh.chunks == 4)) return false;
-    if (h->flags & ETV_ATTN_FLAG_WIDE) return sh.wide;
-    if (sh.wide && sh.chunks == 4) return pairs > 2 && !(h->flags & (ETV_ATTN_FLAG_KEY_HALVES | ETV_ATTN_FLAG_SMALL_WG));
-    return shape_allowed(h, pairs, sh.nw, sh.kh);
+    if (h->flags & ETV_ATTN_FLAG_WIDE) return sh.wide && (pairs <= 4) == (sh.chunks == 4);
+    if (!sh.wide) return shape_allowed(h, pairs, sh.nw, sh.kh);
+    return pairs > 2 && (pairs <= 4) == (sh.chunks == 4) &&
+           !(h->flags & (ETV_ATTN_FLAG_SMALL_WG | ETV_ATTN_FLAG_LARGE_WG | ETV_ATTN_FLAG_WHOLE_TILE | ETV_ATTN_FLAG_KEY_HALVES));
 }
 
 static void pick_tile_shape(const etv_attn_desc *h, Plan &pl) {
