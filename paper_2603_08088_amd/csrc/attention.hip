@@ -2520,9 +2520,9 @@ static Plan make_plan(const etv_attn_desc *h) {
             }
         }
     }
-    constexpr int kShapeFlags = ETV_ATTN_FLAG_SMALL_WG | ETV_ATTN_FLAG_LARGE_WG | ETV_ATTN_FLAG_WHOLE_TILE | ETV_ATTN_FLAG_KEY_HALVES |
-                                ETV_ATTN_FLAG_WIDE;
-    if (blocks_only || !(h->flags & kShapeFlags)) {
+    const int shape_flags = ETV_ATTN_FLAG_SMALL_WG | ETV_ATTN_FLAG_LARGE_WG | ETV_ATTN_FLAG_WHOLE_TILE | ETV_ATTN_FLAG_KEY_HALVES |
+                            (h->d == 128 ? ETV_ATTN_FLAG_WIDE : 0);
+    if (blocks_only || !(h->flags & shape_flags)) {
         // Key-block kernel against the pick so far, for launches that fit the chip at once (one workgroup per compute unit, two
         // at d = 64): a further round pays start-up and merge again, and the other kernel is then always ahead.  Microseconds,
         // fitted to 488 workloads (B = 1 ... 32, T = 1 ... 256, P = 64 ... 30000, both head sizes; profiles/attention_plan_picks.csv):

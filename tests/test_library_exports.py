@@ -108,6 +108,11 @@ def test_the_kernel_of_a_plan_is_reported():
         for kw in (dict(), dict(T_max=32), dict(B=2, T_max=32, Hq=8, Hkv=2, P_max=300, kv_split=4096), dict(B=1, P_max=32768), dict(T_max=8)):
             assert kernel(flags=flags, **kw) == "tile", (flags, kw)
             assert kernel(flags=flags | api.ATTN_FLAG_WIDE, **kw) == "wide", (flags, kw)
+    # heads of 64 and fp32 have no wide kernel, and its flag changes nothing for them
+    for kw in (dict(d=64), dict(d=64, B=1, T_max=60, P_max=2048), dict(d=64, B=4, T_max=48, P_max=1500), dict(dtype=api.F32)):
+        c = dict(dict(B=32, T_max=128, Hq=32, Hkv=8, d=128, dtype=api.BF16, P_cap=4096, P_max=4096), **kw)
+        plain, wide = api.AttnDesc(**c), api.AttnDesc(**c, flags=api.ATTN_FLAG_WIDE)
+        assert api.tree_verify_attention_plan(plain) == api.tree_verify_attention_plan(wide)
     with pytest.raises(api.EtvError):
         kernel(Hq=9)
 
