@@ -2385,6 +2385,11 @@ struct TileShape {
 constexpr TileShape kTileShapes[] = {{8, 0, 1, 8, 0.0, 1.05, 1.15, 7.72}, {8, 0, 1, 4, 0.0, 0.71, 0.75, 4.71}, {8, 0, 0, 8, 0.0, 1.26, 1.68, 3.81},
                                      {8, 1, 0, 4, 0.0, 0.78, 1.00, 4.06}, {4, 0, 0, 4, 1.15, 1.66, 1.86, 2.62}, {4, 1, 0, 2, 0.63, 0.92, 1.24, 3.45}};
 
+// Trees of more than 128 nodes: the wide kernel's pass for the first masked tiles, a round.  Without it the model took the wide kernel for
+// short prefixes (B = 23, T = 199, 32/32 heads, P = 377: 99 us, tile kernel 81): of 300 draws with T = 129 ... 256 35 were more
+// than 3 % slower than before there was a wide kernel (by up to 15 %) and 66 faster, now 16 and 67.
+constexpr double kWideSecondPass = 5.0;
+
 static bool shape_allowed(const etv_attn_desc *h, int pairs, int nw, int kh) {
     if (kh && (h->flags & ETV_ATTN_FLAG_WHOLE_TILE)) return false;
     if (!kh && (h->flags & ETV_ATTN_FLAG_KEY_HALVES)) return false;
@@ -2422,7 +2427,8 @@ static void pick_tile_shape(const etv_attn_desc *h, Plan &pl) {
             const double slots = sh.nw == 4 && !alone ? 512.0 : 256.0;
             const double busy = sh.full * held * (wgs < slots ? wgs / slots : 1.0);
             const double tile = alone ? sh.alone : (busy > sh.least ? busy : sh.least);
-            const double est = ceil(wgs / slots) * ((tps + tree_tiles * (ns > 1 ? 0.6 : 1.0)) * tile + sh.start) + fixed +
+            const double start = sh.start + (sh.wide && h->T_max > 128 ? kWideSecondPass : 0.0);
+            const double est = ceil(wgs / slots) * ((tps + tree_tiles * (ns > 1 ? 0.6 : 1.0)) * tile + start) + fixed +
                                (ns > 1 ? 2.25 + ns * part_us * 0.6 : 0.0);
             if (est < best) {
                 best = est;

@@ -102,6 +102,9 @@ def test_the_kernel_of_a_plan_is_reported():
     for T in (1, 33, 64, 65, 256):
         for P in (0, 1, 900, 4096):
             assert kernel(T_max=T, P_max=P, flags=api.ATTN_FLAG_WIDE) == "wide", (T, P)
+    # more than 128 nodes cost the wide kernel a second pass: over short splits the tile kernel is faster (99 and 81 us, 52 and 41)
+    assert kernel(B=23, T_max=199, Hq=32, Hkv=32, P_max=377) == "tile" and kernel(B=12, T_max=169, P_max=428) == "tile"
+    assert kernel(T_max=256) == "wide"
     # a flag for a shape of the tile kernel names that kernel, and the wide one's goes before it
     for flags in (api.ATTN_FLAG_SMALL_WG, api.ATTN_FLAG_LARGE_WG, api.ATTN_FLAG_WHOLE_TILE, api.ATTN_FLAG_KEY_HALVES,
                   api.ATTN_FLAG_LARGE_WG | api.ATTN_FLAG_WHOLE_TILE, api.ATTN_FLAG_LARGE_WG | api.ATTN_FLAG_KEY_HALVES):
