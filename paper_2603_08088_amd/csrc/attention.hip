@@ -2407,7 +2407,8 @@ static bool tile_shape_allowed(const etv_attn_desc *h, int pairs, const TileShap
            !(h->flags & (ETV_ATTN_FLAG_SMALL_WG | ETV_ATTN_FLAG_LARGE_WG | ETV_ATTN_FLAG_WHOLE_TILE | ETV_ATTN_FLAG_KEY_HALVES));
 }
 
-static void pick_tile_shape(const etv_attn_desc *h, Plan &pl) {
+// false: the flags leave no shape
+static bool pick_tile_shape(const etv_attn_desc *h, Plan &pl) {
     const int tiles = max(1, (h->P_max + KT - 1) / KT), B = max(1, h->B);
     const int forced_tps = h->kv_split > 0 ? min(tiles, (h->kv_split + KT - 1) / KT) : 0;
     const double part_us = 2.0 * B * h->Hq * h->T_max * (h->d + 2.0) * 4.0 / 3.0e6;
@@ -2437,6 +2438,7 @@ static void pick_tile_shape(const etv_attn_desc *h, Plan &pl) {
             }
         }
     }
+    return best < 1e30;
 }
 
 static Plan make_plan(const etv_attn_desc *h) {
@@ -2498,7 +2500,13 @@ static Plan make_plan(const etv_attn_desc *h) {
     // a batch with splits: the slots go to the sequences by length (lane i of a wavefront plans sequence i)
     const bool shared_out = B >= 2 && B <= 64 && !(h->flags & ETV_ATTN_FLAG_UNIFORM_SPLITS);
     const bool blocks_only = (h->flags & ETV_ATTN_FLAG_KEY_BLOCKS) != 0;
-    for (int nw = 4; nw <= 8 && !blocks_only; nw += 4) {
+    const int shape_flags = ETV_ATTN_FLAG_SMALL_WG | ETV_ATTN_FLAG_LARGE_WG | ETV_ATTN_FLAG_WHOLE_TILE | ETV_ATTN_FLAG_KEY_HALVES |
+                            (h->d == 128 ? ETV_ATTN_FLAG_WIDE : 0);
+    const long block_slots = h->d == 64 ? 512 : 256;  // workgroups of the key-block kernel that run at once
+    const bool maybe_blocks = blocks_only || (!(h->flags & shape_flags) && ((long)B * h->Hkv + 7) / 8 * pl.pairs <= block_slots / 8);
+    // The tile kernel's shape at d = 64.  At d = 128 pick_tile_shape has the last word; there this is only the price against which the
+    // key-block kernel is weighed, and is left out where that one is no candidate.
+    for (int nw = 4; nw <= 8 && !blocks_only && (h->d == 64 || maybe_blocks); nw += 4) {
         for (int kh = 0; kh <= 1; kh++) {
             const int cw = kh ? nw / 2 : nw;  // chunks per workgroup
             if (!shape_allowed(h, pl.pairs, nw, kh)) continue;
@@ -2526,9 +2534,7 @@ static Plan make_plan(const etv_attn_desc *h) {
             }
         }
     }
-    const int shape_flags = ETV_ATTN_FLAG_SMALL_WG | ETV_ATTN_FLAG_LARGE_WG | ETV_ATTN_FLAG_WHOLE_TILE | ETV_ATTN_FLAG_KEY_HALVES |
-                            (h->d == 128 ? ETV_ATTN_FLAG_WIDE : 0);
-    if (blocks_only || !(h->flags & shape_flags)) {
+    if (maybe_blocks) {
         // Key-block kernel against the pick so far, for launches that fit the chip at once (one workgroup per compute unit, two
         // at d = 64): a further round pays start-up and merge again, and the other kernel is then always ahead.  Microseconds,
         // fitted to 488 workloads (B = 1 ... 32, T = 1 ... 256, P = 64 ... 30000, both head sizes; profiles/attention_plan_picks.csv):
@@ -2542,7 +2548,7 @@ static Plan make_plan(const etv_attn_desc *h) {
             const double lat = 0.78 * best_lat * (d64 ? 0.68 : 1.0) + 6.6, mem = 7.15 + kv_bytes / 5.7e6;
             best = 0.97 * ((lat > mem ? lat : mem) + (pl.nsplit > 1 ? 3.3 + pl.nsplit * part2_us : 0.0));
         }
-        const long units = (long)B * h->Hkv * pl.pairs, slots = d64 ? 512 : 256;
+        const long units = (long)B * h->Hkv * pl.pairs;
         const double mem = 4.75 + kv_bytes / 6.9e6 + (pl.pairs - 1) * kv_bytes / 46.0e6, mem25 = mem * mem * sqrt(mem);
         const int tree_blocks = (h->T_max + KB_KEYS - 1) / KB_KEYS;
         const int forced_tps = h->kv_split > 0 ? min(tiles, (h->kv_split + KT - 1) / KT) : 0;
@@ -2551,7 +2557,7 @@ static Plan make_plan(const etv_attn_desc *h) {
             const long wgs = units * ns;
             // the chunks of a (split, KV head, sequence) stay on one XCD: the fullest of the eight has to hold all of its own at once
             const long fullest = ((long)B * ns * h->Hkv + 7) / 8 * pl.pairs;
-            if (fullest > slots / 8 && !(blocks_only && (ns == 1 || forced_tps))) break;
+            if (fullest > block_slots / 8 && !(blocks_only && (ns == 1 || forced_tps))) break;
             if (((long)B * ns * h->Hkv + 7) / 8 > 65535 || pl.pairs > 65535) break;  // grid dimensions
             if (!forced_tps && beyond_array(h, ns)) break;
             const int most = (2 * tps + tree_blocks + KB_NW - 1) / KB_NW, usual = (2 * tps + KB_NW - 1) / KB_NW;
@@ -2565,9 +2571,10 @@ static Plan make_plan(const etv_attn_desc *h) {
             }
         }
     }
-    if (h->d == 128 && !pl.blocks) pick_tile_shape(h, pl);
+    bool picked = best < 1e30;
+    if (h->d == 128 && !pl.blocks) picked = pick_tile_shape(h, pl) && !blocks_only;
     pl.balanced = pl.nsplit > 1 && shared_out;
-    if (best == 1e30) {  // kv_split larger than the prefix: a single split
+    if (!picked) {  // flags that leave no shape (whole tiles and key halves, a launch too large for key blocks): a single split
         pl.nw = (pl.pairs > 4 && !(h->flags & ETV_ATTN_FLAG_SMALL_WG)) ? 8 : 4;
         pl.kh = false; pl.wide = false;
         pl.wgp = (pl.pairs + pl.nw - 1) / pl.nw;

@@ -107,7 +107,8 @@ def test_the_kernel_of_a_plan_is_reported():
     assert kernel(T_max=256) == "wide"
     # a flag for a shape of the tile kernel names that kernel, and the wide one's goes before it
     for flags in (api.ATTN_FLAG_SMALL_WG, api.ATTN_FLAG_LARGE_WG, api.ATTN_FLAG_WHOLE_TILE, api.ATTN_FLAG_KEY_HALVES,
-                  api.ATTN_FLAG_LARGE_WG | api.ATTN_FLAG_WHOLE_TILE, api.ATTN_FLAG_LARGE_WG | api.ATTN_FLAG_KEY_HALVES):
+                  api.ATTN_FLAG_LARGE_WG | api.ATTN_FLAG_WHOLE_TILE, api.ATTN_FLAG_LARGE_WG | api.ATTN_FLAG_KEY_HALVES,
+                  api.ATTN_FLAG_WHOLE_TILE | api.ATTN_FLAG_KEY_HALVES):
         for kw in (dict(), dict(T_max=32), dict(B=2, T_max=32, Hq=8, Hkv=2, P_max=300, kv_split=4096), dict(B=1, P_max=32768), dict(T_max=8)):
             assert kernel(flags=flags, **kw) == "tile", (flags, kw)
             assert kernel(flags=flags | api.ATTN_FLAG_WIDE, **kw) == "wide", (flags, kw)
