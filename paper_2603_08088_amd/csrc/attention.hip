@@ -1322,7 +1322,7 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 struct WideGeo {
     static constexpr int NW = 4, CW = 8, NS = 4, AHEAD = 3;  // wavefronts, chunks, ring places, tiles asked for before the loop
-    static constexpr int MASKED = 3;                         // tiles with masked keys that the loop takes
+    static constexpr int MASKED = 3;                         // tiles with masked keys that the loop takes (its asm names three masks)
     static constexpr int RING = NS * Geo<128>::STAGE_BYTES;
     static constexpr int Q_AT = 3 * Geo<128>::STAGE_BYTES;   // Q until the loop has read it: 16 KiB a wavefront
     static constexpr int OUT_AT = RING;                      // outputs on their way to memory: 8 KiB a wavefront
@@ -1331,9 +1331,8 @@ struct WideGeo {
 
 template <bool PAGED, bool NT, bool MANY>
 __global__ void __launch_bounds__(256, 1) attn_wide_kernel(AttnParams p) {
-    constexpr int D = 128, AHEAD = WideGeo::AHEAD;
+    constexpr int D = 128, AHEAD = WideGeo::AHEAD, MASKED = WideGeo::MASKED;
     constexpr int ROW_BYTES = Geo<D>::ROW_BYTES, TILE_BYTES = Geo<D>::TILE_BYTES, STAGE_BYTES = Geo<D>::STAGE_BYTES;
-    constexpr int KK = Geo<D>::KK, DB = Geo<D>::DB;
     uint8_t *const smem = attn_smem;
     const uint32_t smem_addr = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)attn_smem;
 
@@ -1538,7 +1537,7 @@ __global__ void __launch_bounds__(256, 1) attn_wide_kernel(AttnParams p) {
     // it would be farther from the largest score, and the largest probability is exact only where it is 1), the tiles with masked
     // keys, the other full tiles.  The loop wants masked tiles among its first three: with a ragged end of the prefix ahead of two
     // tree tiles that one leads, and trees of more than 128 nodes take a pass for the first three tiles (it does not touch Q's place).
-    const bool lead_full = nfull > 0 && !(edges == 3 && npt > nfull);
+    const bool lead_full = nfull > 0 && !(edges == MASKED && npt > nfull);
     // (MANY: trees of more than 128 nodes.  Without a second pass the outputs stay in accumulation registers on the way.)
     int e_done = 0, f_done = 0;
     bool again_pass = edges + nfull > 0;
@@ -1548,12 +1547,12 @@ __global__ void __launch_bounds__(256, 1) attn_wide_kernel(AttnParams p) {
         // chunk `wave` of the group and chunk `wave` + 4 (a small group is spread over the SIMDs): how many of them hold rows?
         const uint32_t chunks = uni((int)((wg * WideGeo::CW + wave) * 32 < n * p.G) + (int)((wg * WideGeo::CW + wave + WideGeo::NW) * 32 < n * p.G));
         const int lead = lead_full && f_done == 0 ? 1 : 0, e_left = edges - e_done;
-        const bool more = MANY && e_left > 3 - lead;  // not the last pass
-        const int ne = more ? (lead ? 2 : e_left - 3) : e_left, masked = lead + ne, nt = masked + (more ? 0 : nfull - f_done - lead);
+        const bool more = MANY && e_left > MASKED - lead;  // not the last pass
+        const int ne = more ? (lead ? MASKED - 1 : e_left - MASKED) : e_left, masked = lead + ne, nt = masked + (more ? 0 : nfull - f_done - lead);
         const int l = again();
-        u32x2 vis[3];  // visible keys of the first three tiles for chunk A and chunk B, two rows of 16 bits each
+        u32x2 vis[MASKED];  // visible keys of the first tiles for chunk A and chunk B, two rows of 16 bits each
 #pragma unroll
-        for (int e = 0; e < 3; e++)
+        for (int e = 0; e < MASKED; e++)
 #pragma unroll
             for (int x = 0; x < 2; x++) {
                 vis[e][x] = 0xffffffffu;
