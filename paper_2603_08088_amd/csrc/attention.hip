@@ -1310,10 +1310,11 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(AttnParams p) {
 // What bounds a tile is the power.  With 32x32x16 matrix instructions it took 2574 cycles, 2176 of them matrix instructions, and the
 // clock was 1.48 GHz with everything in the loop, 1.67 without the tile loads, 1.78 with the matrix instructions alone: 1.73, 1.55
 // and 1.23 us.  The 16x16x32 instructions that it has now cost the same cycles and less power, but leave fewer issue slots beside
-// them (2 against 3 for the same product), so the streams are paced by slots.  B = 32, P = 4096, 32/8 heads: T = 128 288-293 us on the
-// tile kernel, 255 here with 32x32x16, 249 with 16x16x32, 243-247 paced (two rounds of workgroups; of a round's 122 us about 13 are
-// start-up, the first references and the output); T = 32, one chunk a wavefront, 100.6 -> 91.3-93.  B = 1, T = 128, P = 32768 with its
-// combine: 83.5 -> 73.8-75.4.  Against the eight wavefronts of attn_mfma_kernel a round costs 4 us more and a tile a quarter less.
+// them (2 against 3 for the same product), so the streams are paced by slots.  B = 32, P = 4096, 32/8 heads: T = 128 288-295 us on the
+// tile kernel, 255 here with 32x32x16, 249 with 16x16x32, 242-251 paced (two rounds of workgroups; of a round's 122 us about 13 are
+// start-up, the first references and the output); T = 32, one chunk a wavefront, 100.6-103.2 -> 91.4-95.5.  B = 1, T = 128, P = 32768 with
+// its combine: 83.5-84.7 -> 74.0-78.1.  Against the eight wavefronts of attn_mfma_kernel a round costs 4 us more and a tile a quarter less.
+// Peaked scores: every row that moves its reference stops the matrix cores (`lift` in attn_wide_loop.py has the figures).
 // ----------------------------------------------------------------------------------------------
 typedef __attribute__((ext_vector_type(32))) float f32x32;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
@@ -2337,7 +2338,8 @@ static bool supported(const etv_attn_desc *h) {
     return true;
 }
 
-// Launch shape.  Cost model in microseconds, fitted on MI355X: workgroups run in rounds of the slots the chip
+// Launch shape at d = 64, and at d = 128 the price of the tile kernel in the choice against key blocks (what then runs there is
+// pick_tile_shape's).  Cost model in microseconds, fitted on MI355X: workgroups run in rounds of the slots the chip
 // offers; a round costs its tiles plus tree tiles and ramp-up; every extra split writes and re-reads one
 // (m, l, O) set per query row and needs the combine launch.  A tile costs about 2.8 us for an 8-wavefront
 // workgroup (two wavefronts per SIMD), the same for two 4-wavefront workgroups sharing a compute unit, and
@@ -2359,24 +2361,22 @@ static size_t split_workspace(const etv_attn_desc *h, int ns) {
 }
 
 // Splits that this file chooses by itself stay within the array of etv_tree_verify_attention_static, whose callers cannot
-// bring a workspace: fp32 and heads of 64 at any size, and the key-block kernel wherever the tile kernel's did.  (Tile kernel
-// at d = 128: a batch of many rows over a long prefix may be split beyond the array, as it always was.)
+// bring a workspace, on every matrix-core kernel and at any size.
 static bool beyond_array(const etv_attn_desc *h, int ns) { return ns > 1 && split_workspace(h, ns) > ETV_ATTN_STATIC_WORKSPACE_BYTES; }
 
 // The next split count worth a look: with tps tiles per split now, the smallest count whose splits are shorter (the counts
 // between differ only in empty splits).  Some 2 * sqrt(tiles) candidates instead of all of them, on every call.
 static int next_split_count(int tiles, int tps) { return tps > 1 ? (tiles + tps - 2) / (tps - 1) : tiles + 1; }
 
-// Launch shape of a bf16 call with heads of 128 on the tile kernels.  Microseconds, fitted to 4500 timings of 270 workloads (B = 1 ... 32,
-// T = 6 ... 256, P = 60 ... 32768, every shape at up to twelve split counts): a round of workgroups costs its tiles and a start-up;
-// a tile costs the more, the more of the chip's wavefronts have rows (the clock follows the power); K/V bytes on top, and splits as
-// before.  The pick is within 1.0 % of the best measured shape on average (with the constants from before the wide kernel: 7 %)
-// and at most 3.5 % behind the pick of those, 5.4 % ahead of it on average.  The wide kernel passes the eight wavefronts of the
-// tile kernel from about 12 tiles a split on: 2 tiles 1.06, 10 tiles 0.98, 20 tiles 0.92, 65 tiles 0.80 of its time.  With three
-// or four chunks each of its wavefronts has one; it gains over long splits (B = 32, T = 32, P = 4096: 93.6 us, the tile kernel
-// 105.6; B = 8, T = 113, 32/32 heads, P = 8735: 176 and 201), loses over short ones (B = 16, T = 76, 32/32 heads, P = 124: 24.8
-// and 20.0), and with two chunks, half of its wavefronts idle, it is rarely ahead (B = 25, T = 35, 32/32 heads, P = 1653: 142
-// and 123), so it starts at three.
+// Launch shape of a bf16 call with heads of 128 on the tile and wide kernels.  Microseconds: a round of workgroups costs its tiles and a
+// start-up; a tile costs the more, the more of the chip's wavefronts have rows (the clock follows the power); K/V bytes on top, and splits
+// as before.  On 500 drawn workloads with every shape at up to five split counts (profiles/attention_tile_shapes.csv) the pick is 1.5 % behind
+// the best measured shape on average and 8 % at the 95th percentile, and no other constants pick better.  The wide kernel passes the
+// eight wavefronts of the tile kernel from about 14 tiles a split on: 1-2 tiles 1.12, 9-11 tiles 1.02, 16-39 tiles 0.96, 64 and more 0.88 of its
+// time.  With three or four chunks each of its wavefronts has one; it gains over long splits (B = 32, T = 32, P = 4096: 93.6 us, the tile
+// kernel 105.6; B = 8, T = 113, 32/32 heads, P = 8735: 176 and 201), loses over short ones (B = 16, T = 76, 32/32 heads, P = 124: 24.8 and 20.0),
+// and with two chunks, half of its wavefronts idle, it is rarely ahead (B = 25, T = 35, 32/32 heads, P = 1653: 142 and 123), so it starts
+// at three.
 struct TileShape {
     int nw, kh, wide, chunks;                // wavefronts; key halves; wide; chunks of a workgroup (wide: 4 if it needs no more)
     double alone, least, full, start;        // a tile alone on a compute unit (nw = 4), with few, with all wavefronts busy; a round
@@ -2536,8 +2536,9 @@ static Plan make_plan(const etv_attn_desc *h) {
     if (maybe_blocks) {
         // Key-block kernel against the pick so far, for launches that fit the chip at once (one workgroup per compute unit, two
         // at d = 64): a further round pays start-up and merge again, and the other kernel is then always ahead.  Microseconds,
-        // fitted to 488 workloads (B = 1 ... 32, T = 1 ... 256, P = 64 ... 30000, both head sizes; profiles/attention_plan_picks.csv):
-        // what the choice costs against the best measured shape, and twice over against the tile kernel's own pick.  A
+        // fitted to 488 workloads (B = 1 ... 32, T = 1 ... 256, P = 64 ... 30000, both head sizes) by what the choice costs against the
+        // best measured shape, and twice over against the tile kernel's own pick; with the wide kernel beside the tile kernel it costs
+        // 1.15 % against the better of the two (1682 draws; profiles/attention_plan_picks.md).  A
         // wavefront's block is 2.0 (2.33 where a single chunk waits for HBM and not for its neighbours' lines in L2; d = 64 1.4,
         // and 2.3 times that with two workgroups on a compute unit); the memory side is the K/V bytes once at 6.9 TB/s and once
         // more per further chunk at 46 TB/s.  The pick so far counts as 3 % faster than its estimate: what a wrong one costs.

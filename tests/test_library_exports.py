@@ -179,11 +179,11 @@ def test_calls_refuse_queries_of_another_rank_and_rows_that_are_not_there():
 
 
 def test_unforced_fp32_and_heads_of_64_plans_fit_the_fixed_array():
-    """etv_tree_verify_attention_static cannot fall back on another workspace: a split that the library chooses by itself at
-    fp32 or heads of 64 stays within its array, at every size, so that no unforced call is refused.  (Host only: the plan.)"""
+    """etv_tree_verify_attention_static cannot fall back on another workspace: a split that the library chooses by itself (fp32, heads
+    of 64, and heads of 128) stays within its array, at every size, so that no unforced call is refused.  (Host only: the plan.)"""
     cases = [(64, api.BF16, 17, 60, 64, 8, 8192), (128, api.F32, 12, 60, 64, 8, 16384), (64, api.BF16, 8, 160, 64, 8, 4096),
              (128, api.F32, 24, 60, 28, 4, 16384)]
-    cases += [(d, dt, B, T, Hq, Hkv, P) for d, dt in ((64, api.BF16), (64, api.F32), (128, api.F32)) for B in (1, 3, 17, 40, 65, 129)
+    cases += [(d, dt, B, T, Hq, Hkv, P) for d, dt in ((64, api.BF16), (64, api.F32), (128, api.F32), (128, api.BF16)) for B in (1, 3, 17, 40, 65, 129)
               for T in (1, 16, 60, 129, 256) for Hq, Hkv in ((4, 4), (32, 8), (64, 8), (28, 4), (257, 257)) for P in (0, 500, 8192, 100000)]
     for d, dt, B, T, Hq, Hkv, P in cases:
         dsc = api.AttnDesc(B=B, T_max=T, Hq=Hq, Hkv=Hkv, d=d, dtype=dt, P_cap=P, P_max=P)
