@@ -202,9 +202,10 @@ def lift(o, c, label, masked):
     The limit is the tile kernel's: it moves a reference that a score passes by 2^8, whose weight is then 1 and exact in bf16.  Every row that
     it would move moves here.  With a limit of 2^20 the error against float64 grew by up to 4 % (Q x 4; lse by 40 %).
 
-    The matrix cores wait meanwhile.  B = 32, T = 128, P = 4096 in us, Q x 1, 3, 6, 12: tile kernel 293, 299, 304, 307; here 247, 269, 303-308,
-    315-319; with both column blocks computed whichever row moved 246, 286, 329, 350."""
-    o(f".Llift_{label}%=:", "s_nop 15")
+    The matrix cores wait meanwhile.  B = 32, T = 128, P = 4096 in us, Q x 1, 3, 6, 12: tile kernel 295, 302, 308, 308; here 248, 269, 306,
+    316; with both column blocks computed whichever row moved 246, 286, 329, 350."""
+    # (O of a lone chunk is being written by the products just issued: more than 40 instructions pass before it is read here)
+    o(f".Llift_{label}%=:")
     for cb in range(2):
         pairs = [i for i in range(16) if scores(c, i)[2] == cb]
         o(f"v_cmp_nle_f32 vcc, {v(SUM + 4 * cb)}, {s(S_LIMIT)}", f"s_cbranch_vccz .Lkeep_{label}{cb}%=",
