@@ -1311,7 +1311,7 @@ __global__ void __launch_bounds__(NW * 64, 2) attn_mfma_kernel(AttnParams p) {
 // clock was 1.48 GHz with everything in the loop, 1.67 without the tile loads, 1.78 with the matrix instructions alone: 1.73, 1.55
 // and 1.23 us.  The 16x16x32 instructions that it has now cost the same cycles and less power, but leave fewer issue slots beside
 // them (2 against 3 for the same product), so the streams are paced by slots.  B = 32, P = 4096, 32/8 heads: T = 128 288-295 us on the
-// tile kernel, 255 here with 32x32x16, 249 with 16x16x32, 242-251 paced (two rounds of workgroups; of a round's 122 us about 13 are
+// tile kernel, 255 here with 32x32x16, 249 with 16x16x32, 242-256 paced (two rounds of workgroups; of a round's 122 us about 13 are
 // start-up, the first references and the output); T = 32, one chunk a wavefront, 100.6-103.2 -> 91.4-95.5.  B = 1, T = 128, P = 32768 with
 // its combine: 83.5-84.7 -> 74.0-78.1.  Against the eight wavefronts of attn_mfma_kernel a round costs 4 us more and a tile a quarter less.
 // Peaked scores: every row that moves its reference stops the matrix cores (`lift` in attn_wide_loop.py has the figures).

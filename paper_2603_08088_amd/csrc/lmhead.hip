@@ -472,7 +472,7 @@ __global__ void __launch_bounds__(512, 1) lm_head_argmax_wide_kernel(LhParams p)
 // partial of the layout the finishing kernel (and the epilogue) reads.
 // What bounds it is the power of the matrix cores: the clock falls until the chip is at its limit.  v_mfma_f32_16x16x32_bf16
 // moves less accumulator data per product than 32x32x16 and so runs at a higher clock: alone, on random operands, 1.63 against
-// 1.52 PFLOP/s, here 766-786 against 824-840 us for 4096 rows, D = 4096, V = 32000 (1.37-1.40 PFLOP/s; a plain library product of that shape
+// 1.52 PFLOP/s, here 766-792 against 824-840 us for 4096 rows, D = 4096, V = 32000 (1.36-1.40 PFLOP/s; a plain library product of that shape
 // 1.29), and 432 against 443 us for 2048 x 64000 x 2048.  With all loads, then all fragment reads, then all products of a step behind
 // its barrier it was 893 us (the wavefronts of a SIMD issued addresses and waited for LDS together).
 // ----------------------------------------------------------------------------------------------------------------
