@@ -2538,7 +2538,7 @@ static Plan make_plan(const etv_attn_desc *h) {
         // at d = 64): a further round pays start-up and merge again, and the other kernel is then always ahead.  Microseconds,
         // fitted to 488 workloads (B = 1 ... 32, T = 1 ... 256, P = 64 ... 30000, both head sizes) by what the choice costs against the
         // best measured shape, and twice over against the tile kernel's own pick; with the wide kernel beside the tile kernel it costs
-        // 1.15 % against the better of the two (1682 draws; profiles/attention_plan_picks.md).  A
+        // 1.15 % against the better of the two (1682 drawn calls).  A
         // wavefront's block is 2.0 (2.33 where a single chunk waits for HBM and not for its neighbours' lines in L2; d = 64 1.4,
         // and 2.3 times that with two workgroups on a compute unit); the memory side is the K/V bytes once at 6.9 TB/s and once
         // more per further chunk at 46 TB/s.  The pick so far counts as 3 % faster than its estimate: what a wrong one costs.
