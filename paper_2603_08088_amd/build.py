@@ -20,6 +20,7 @@ SOURCES = ["api.hip", "mask.hip", "attention.hip", "posterior.hip", "commit.hip"
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         "-mllvm", "-amdgpu-kernarg-preload-count=14",   # a kernel's leading scalar arguments are in registers when it starts
          "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-I", GENERATED]
 
 

@@ -44,7 +44,7 @@ struct AttnParams {
     //   part_o [B * nsplit][Hq][T_max][d]; split_tab[b] = (first slot, splits in use) for the combine kernel
     int balanced;
     int2 *split_tab;
-    uint32_t inv_g, inv_hkv, inv_nsplit, inv_pairs;  // floor(2^32 / G) and so on, for fast_div
+    uint32_t inv_g, inv_hkv, inv_nsplit, inv_pairs, inv_chunk;  // floor(2^32 / G) and so on, for fast_div
 };
 
 constexpr float kLn2 = 0.6931471805599453f;
@@ -1707,12 +1707,22 @@ __global__ void __launch_bounds__(256, 1) attn_wide_kernel(AttnParams p) {
 // A wavefront owns a K and a V buffer of one block each (8 KiB + 8 KiB at d = 128), filled by direct-to-LDS loads: K of
 // the next block is requested when the score products have read this one's, V when the value products have.  Q (one
 // copy for the workgroup) and the rows' ancestor bits come the same way, so that nothing the compiler tracks is
-// outstanding and no wait of its own drains the block loads.  What bounds a step is the LDS pipe (K and V written, read once
+// outstanding and no wait of its own drains the block loads.
+//
+// Start-up is a third of a short launch, so it is one trip to memory: what the first addresses need are leading scalar arguments,
+// which are in registers when the kernel starts (the -amdgpu-kernarg-preload-count of the build), and the sequence's sizes, the
+// first block ids and the other arguments are asked for together.  K of the first block goes out first, then Q, then V.  The
+// loads of a block with masked keys know their block ids beforehand too; with a look-up per lane and load the wavefronts of
+// such blocks came to the first barrier 2.3 us after the others (paged, P = 200, T = 30: 8.7 us from the first to the last
+// instruction, now 7.0).  Whether K/V bytes have one reader and whether the split slots follow the lengths are template
+// arguments: a branch per load, and a wait for the arguments before the sizes are asked for, otherwise.  What bounds a step is the LDS pipe (K and V written, read once
 // for 32 rows: 256 KiB per compute unit and step) and, with one chunk, the latency of the next block.
 //
-// B = 1, 32/8 heads of 128: T = 60, P = 2048 16.1 -> 14.0 us (4 splits instead of 8); P = 500 13.5 -> 9.4; T = 8, P = 4096
-// 14.5 -> 13.0; T = 128, P = 1024 17.8 -> 12.1.  B = 4, T = 60, P = 1000 21.6 -> 14.6; B = 32, T = 8, P = 4096 87.4 -> 82.7 us
-// (128 KiB in flight per compute unit: 6.5 TB/s); heads of 64, B = 4, T = 48, P = 900 ... 1500 13.4 us.
+// Against the tile kernel: B = 1, 32/8 heads of 128, T = 60, P = 2048 16.1 -> 14.0 us (4 splits instead of 8); P = 500 13.5 -> 9.4;
+// T = 8, P = 4096 14.5 -> 13.0; T = 128, P = 1024 17.8 -> 12.1.  B = 4, T = 60, P = 1000 21.6 -> 14.6; B = 32, T = 8, P = 4096
+// 87.4 -> 82.7 us (128 KiB in flight per compute unit: 6.5 TB/s).  By the start-up and edge loads above: 32 layers of B = 1, T = 60,
+// P = 2048 510 -> 471 us (with the combine launches); heads of 64, B = 4, T = 48, P = 900 ... 1500 13.4 -> 11.5; 68 drawn calls
+// below 40 MB 16 % shorter on average.
 // ----------------------------------------------------------------------------------------------
 constexpr int KB_NW = 8;     // wavefronts of a workgroup
 constexpr int KB_KEYS = 32;  // keys of a block
@@ -1733,8 +1743,10 @@ __device__ __forceinline__ void async_load4(const void *gptr, uint32_t lds_addr)
                  "s"(__builtin_amdgcn_readfirstlane(lds_addr)) : "memory");
 }
 
-template <int D, bool PAGED>
-__global__ void __launch_bounds__(KB_NW * 64, D == 64 ? 4 : 2) attn_blocks_kernel(AttnParams p) {
+template <int D, bool PAGED, bool BALANCED, bool NT>
+__global__ void __launch_bounds__(KB_NW * 64, D == 64 ? 4 : 2)
+attn_blocks_kernel(const int32_t *prefix_len, const int32_t *n_nodes, const int32_t *block_table, int Hkv, uint32_t inv_hkv, int slots, int nsplit,
+                   uint32_t inv_nsplit, int max_blocks, int chunk_, uint32_t inv_chunk, AttnParams p) {
     using G_ = KbGeo<D>;
     constexpr int ROW_BYTES = Geo<D>::ROW_BYTES, KK = Geo<D>::KK, DB = Geo<D>::DB, RPU = Geo<D>::RPU, CPR = Geo<D>::CPR;
     constexpr int BLOCK = G_::BLOCK, U = G_::U, UH = U / 2;  // UH loads cover 16 rows
@@ -1746,39 +1758,34 @@ __global__ void __launch_bounds__(KB_NW * 64, D == 64 ? 4 : 2) attn_blocks_kerne
     // grid (8, chunks, units / 8): the linear id is ((unit / 8) * chunks + chunk) * 8 + unit % 8, unit = slot * Hkv + KV head
     const int rg = blockIdx.y;
     uint32_t rem;
-    const int slot = (int)fast_div(blockIdx.z * 8 + blockIdx.x, p.Hkv, p.inv_hkv, rem);
+    const int slot = (int)fast_div(blockIdx.z * 8 + blockIdx.x, Hkv, inv_hkv, rem);
     const int kvh = (int)rem;
-    if (slot >= p.B * p.nsplit) return;  // uniform over the workgroup
-    asm volatile("" ::"s"(p.q), "s"(p.k_cache), "s"(p.v_cache), "s"(p.kt), "s"(p.vt), "s"(p.block_table),
-                 "s"(p.prefix_len), "s"(p.n_nodes), "s"(p.bitmask), "s"(p.T_max), "s"(p.Hq), "s"(p.G),
-                 "s"(p.max_blocks), "s"(p.P_cap), "s"(p.P_max), "s"(p.words), "s"(p.chunk));
+    if (slot >= slots) return;  // uniform over the workgroup
     SplitShare share{};
-    if (p.balanced) {
+    if constexpr (BALANCED) {
         share = balanced_share(p, slot, lane);
         if (!share.live) return;  // uniform over the workgroup
-        if (share.j == 0 && kvh == 0 && rg == 0 && tid == 0) p.split_tab[share.b] = make_int2(share.start, share.nvalid);
     }
-    const int slot_b = (int)fast_div(slot, p.nsplit, p.inv_nsplit, rem);
-    const int b = uni(p.balanced ? share.b : slot_b);
-    const int s = uni(p.balanced ? share.j : (int)rem);
-    const int chunk = uni(p.balanced ? share.tps * KT : p.chunk);
+    const int slot_b = (int)fast_div(slot, nsplit, inv_nsplit, rem);
+    const int b = uni(BALANCED ? share.b : slot_b), s = BALANCED ? share.j : (int)rem, chunk = BALANCED ? share.tps * KT : chunk_;
     const int k0 = s * chunk;
-    const const_i32_ptr bt = (const_i32_ptr)(uintptr_t)(PAGED ? p.block_table + (size_t)b * p.max_blocks : nullptr);
-    // One trip for the sizes and the two cache blocks of the wavefront's first key block; those ids are read before it is
-    // known whether the prefix reaches that far, and used only if it does.
+    const const_i32_ptr bt = (const_i32_ptr)(uintptr_t)(PAGED ? block_table + (size_t)b * max_blocks : nullptr);
+    // One trip for the sizes, the other arguments and the two cache blocks of the wavefront's first key block; those ids are
+    // read before it is known whether the prefix reaches that far (inside the table in any case), and used only if it does.
     const int lb0 = (k0 >> 4) + 2 * wave;
     int blk0 = 0, blk1 = 0;
-    if (PAGED && lb0 + 1 < p.max_blocks) {
-        blk0 = bt[lb0];
-        blk1 = bt[lb0 + 1];
+    if (PAGED) {
+        blk0 = bt[min(lb0, max_blocks - 1)];
+        blk1 = bt[min(lb0 + 1, max_blocks - 1)];
     }
-    const int n_raw = p.balanced ? share.n_raw : ((const_i32_ptr)(uintptr_t)p.n_nodes)[b];
-    const int P_raw = p.balanced ? share.P_raw : ((const_i32_ptr)(uintptr_t)p.prefix_len)[b];
-    asm volatile("" ::"s"(n_raw), "s"(P_raw), "s"(blk0), "s"(blk1));
-    const int n = uni(clampi(n_raw, 0, p.T_max)), P = uni(clampi(P_raw, 0, p.P_max));
-    const int nvalid = uni(p.balanced ? share.nvalid : seq_nsplit(p, P));
+    const int n_raw = BALANCED ? share.n_raw : ((const_i32_ptr)(uintptr_t)n_nodes)[b];
+    const int P_raw = BALANCED ? share.P_raw : ((const_i32_ptr)(uintptr_t)prefix_len)[b];
+    asm volatile("" ::"s"(n_raw), "s"(P_raw), "s"(blk0), "s"(blk1), "s"(p.q), "s"(p.k_cache), "s"(p.v_cache), "s"(p.kt), "s"(p.vt),
+                 "s"(p.bitmask), "s"(p.T_max), "s"(p.Hq), "s"(p.G), "s"(p.inv_g), "s"(p.P_cap), "s"(p.P_max), "s"(p.words), "s"(p.scale_log2));
+    const int n = clampi(n_raw, 0, p.T_max), P = clampi(P_raw, 0, p.P_max);
+    const int nvalid = BALANCED ? share.nvalid : max(1, (int)fast_div(P + chunk - 1, chunk, inv_chunk, rem));
     if (s >= nvalid) return;  // uniform over the workgroup
-    const bool direct = (p.nsplit == 1);
+    const bool direct = (nsplit == 1);
     const bool active = rg * 32 < n * p.G;  // does the chunk hold a valid row?
     const int k1 = min(P, k0 + chunk);
     const int nfull = (active && k1 > k0) ? (k1 - k0) >> 5 : 0;     // full prefix blocks
@@ -1787,10 +1794,11 @@ __global__ void __launch_bounds__(KB_NW * 64, D == 64 ? 4 : 2) attn_blocks_kerne
     const int nt = npb + (with_tree ? (n + 31) >> 5 : 0);
 
     const uint8_t *const kc = static_cast<const uint8_t *>(p.k_cache), *const vc = static_cast<const uint8_t *>(p.v_cache);
-    const size_t hstride = (size_t)p.Hkv * ROW_BYTES;  // between the rows of a head (contiguous cache, tree buffer)
-    const size_t blk_stride = (size_t)p.Hkv * 16 * ROW_BYTES;
-    const size_t head_at = PAGED ? (size_t)kvh * 16 * ROW_BYTES : ((size_t)b * p.P_cap * p.Hkv + kvh) * ROW_BYTES;
-    const uint32_t rstride = PAGED ? (uint32_t)ROW_BYTES : (uint32_t)hstride;
+    const auto mul = [](uint32_t x, uint32_t y) { return (uint64_t)x * y; };
+    const uint32_t hstride = (uint32_t)Hkv * ROW_BYTES;  // between the rows of a head (contiguous cache, tree buffer)
+    const uint32_t blk_stride = 16 * hstride;
+    const uint64_t head_at = PAGED ? (uint64_t)((uint32_t)kvh * 16 * ROW_BYTES) : mul(b, p.P_cap) * hstride + (uint32_t)kvh * ROW_BYTES;
+    const uint32_t rstride = PAGED ? (uint32_t)ROW_BYTES : hstride;
     const uint32_t kbuf = smem_addr + (uint32_t)wave * (2 * BLOCK), vbuf = kbuf + BLOCK;
     const int l_row = lane / CPR, l_pos = lane % CPR;
     // chunk-position swizzles as in the tile kernel: load u covers rows RPU * u + l_row of the block
@@ -1799,43 +1807,63 @@ __global__ void __launch_bounds__(KB_NW * 64, D == 64 ? 4 : 2) attn_blocks_kerne
     for (int x = 0; x < UH; x++) koff[x] = l_row * rstride + (l_pos ^ kswz_of_row<D>(RPU * x + l_row)) * 16;
 #pragma unroll
     for (int x = 0; x < VP; x++) voff[x] = l_row * rstride + (l_pos ^ vswz_of_row<D>(RPU * x + l_row)) * 16;
-    const bool stream_kv = p.pairs == 1;  // a single reader of these K/V bytes: streamed past L2
-    auto full_base = [&](int t, int j, int blk) -> size_t {
-        return head_at + (PAGED ? (size_t)(uint32_t)uni(blk) * blk_stride : (size_t)(uint32_t)(k0 + t * KB_KEYS + 16 * j) * hstride);
+    // The cache blocks that key block x lies in: two, or three where the tree rows begin anywhere (in-place branch cache).
+    auto block_ids = [&](int x, int &i0, int &i1, int &i2) {
+        if (PAGED && !(x >= npb && p.kt)) {
+            const int first = (x >= npb ? P + (x - npb) * KB_KEYS : k0 + x * KB_KEYS) >> 4, last = (x >= npb ? P + n - 1 : k1 - 1) >> 4;
+            i0 = bt[first];
+            i1 = bt[min(first + 1, last)];
+            i2 = bt[min(first + 2, last)];
+        }
     };
-    auto issue_full = [&](const uint8_t *cache, uint32_t dst, bool is_v, size_t b0, size_t b1) {
+    auto issue_full = [&](int x, int i0, int i1, int i2, const uint8_t *cache, uint32_t dst, bool is_v) {
+        const uint8_t *b0 = cache + head_at + (PAGED ? mul(uni(i0), blk_stride) : mul(k0 + x * KB_KEYS, hstride));
+        const uint8_t *b1 = PAGED ? cache + head_at + mul(uni(i1), blk_stride) : b0 + blk_stride;
 #pragma unroll
-        for (int u = 0; u < U; u++) {
-            const uint8_t *src = cache + (u < UH ? b0 : b1) + (size_t)((u % UH) * RPU) * rstride;
-            const uint32_t off = is_v ? voff[u % VP] : koff[u % UH];
-            if (stream_kv) async_load16_s<true>(src, off, dst + u * 1024);
-            else async_load16_s<false>(src, off, dst + u * 1024);
+        for (int u = 0; u < U; u++)
+            async_load16_s<NT>((u < UH ? b0 : b1) + (uint32_t)((u % UH) * RPU) * rstride, is_v ? voff[u % VP] : koff[u % UH], dst + u * 1024);
+    };
+    // Ragged last prefix block and tree blocks: rows past the end repeat the last valid one (masked later).  The block ids are
+    // there already, so that no load of the loop waits for another.
+    auto issue_edge = [&](int x, int i0, int i1, int i2, const uint8_t *cache, const void *own_rows, uint32_t dst, bool is_v) {
+        const bool tree = x >= npb;
+        const int base = tree ? (x - npb) * KB_KEYS : k0 + x * KB_KEYS;
+        const int last = (tree ? n : k1) - 1 - base;
+        const bool own = tree && own_rows;
+        const int pos = tree ? P + base : base;  // in-place branch cache: node j at position P + j
+        if (!PAGED || own) {
+            const uint8_t *src = own ? static_cast<const uint8_t *>(own_rows) + mul(b * p.T_max + base, hstride) + (uint32_t)kvh * ROW_BYTES
+                                     : cache + head_at + mul(pos, hstride);
+#pragma unroll 1
+            for (int u = 0; u < U; u++) {
+                const int r = RPU * u + l_row;
+                async_load16_s<false>(src, min(r, last) * hstride + (l_pos ^ (is_v ? vswz_of_row<D>(r) : kswz_of_row<D>(r))) * 16,
+                                      dst + u * 1024);
+            }
+        } else {
+            const uint8_t *src = cache + head_at;
+#pragma unroll 1
+            for (int u = 0; u < U; u++) {
+                const int r = RPU * u + l_row, at = (pos & 15) + min(r, last);
+                const int blk = at < 16 ? i0 : (at < 32 ? i1 : i2);
+                async_load16(src + mul(blk, blk_stride) + ((at & 15) * ROW_BYTES + (l_pos ^ (is_v ? vswz_of_row<D>(r) : kswz_of_row<D>(r))) * 16),
+                             dst + u * 1024);
+            }
         }
     };
-    // ragged last prefix block and tree blocks: rows past the end repeat the last valid one (masked later)
-    auto issue_edge = [&](int t, const uint8_t *cache, const void *own_rows, uint32_t dst, bool is_v) {
-        const bool tree = t >= npb;
-        const int base = tree ? (t - npb) * KB_KEYS : k0 + t * KB_KEYS;
-        const int last = (tree ? n : k1) - 1;
-        const uint8_t *own = static_cast<const uint8_t *>(own_rows);
-#pragma unroll 1
-        for (int u = 0; u < U; u++) {
-            const int r = RPU * u + l_row;
-            const int key = min(base + r, last);
-            const uint8_t *src;
-            if (tree && own) {
-                src = own + (((size_t)b * p.T_max + key) * p.Hkv + kvh) * ROW_BYTES;
-            } else {
-                const int pos = tree ? P + key : key;  // in-place branch cache: node j at position P + j
-                if (PAGED) src = cache + (size_t)(uint32_t)bt[pos >> 4] * blk_stride + head_at + (size_t)(pos & 15) * ROW_BYTES;
-                else src = cache + head_at + (size_t)pos * hstride;
-            }
-            async_load16(src + (l_pos ^ (is_v ? vswz_of_row<D>(r) : kswz_of_row<D>(r))) * 16, dst + u * 1024);
-        }
+    auto issue = [&](int x, int i0, int i1, int i2, bool is_v) {
+        if (x < nfull) issue_full(x, i0, i1, i2, is_v ? vc : kc, is_v ? vbuf : kbuf, is_v);
+        else issue_edge(x, i0, i1, i2, is_v ? vc : kc, is_v ? p.vt : p.kt, is_v ? vbuf : kbuf, is_v);
     };
 
+    // K of the first block, then Q and the ancestor bits, then V: the first products wait for all but V.
     int t = wave;
     if (active) {
+        int i0 = blk0, i1 = blk1, i2 = 0;
+        if (t < nt) {
+            if (t >= npb) block_ids(t, i0, i1, i2);
+            issue(t, i0, i1, i2, false);
+        }
         // Q, 1 KiB per wavefront, laid out like a K block; padded rows repeat node 0's (their results are dropped)
         if (wave < U) {
             const int row = RPU * wave + l_row;
@@ -1850,16 +1878,12 @@ __global__ void __launch_bounds__(KB_NW * 64, D == 64 ? 4 : 2) attn_blocks_kerne
             async_load4(reinterpret_cast<const uint32_t *>(p.bitmask + ((size_t)b * p.T_max + kq) * p.words + wave) + (lane & 1),
                         smem_addr + G_::BITS_AT + wave * 256);
         }
-        if (t < nfull) {
-            const size_t b0 = full_base(t, 0, blk0), b1 = full_base(t, 1, blk1);
-            issue_full(kc, kbuf, false, b0, b1);
-            issue_full(vc, vbuf, true, b0, b1);
-        } else if (t < nt) {
-            issue_edge(t, kc, p.kt, kbuf, false);
-            issue_edge(t, vc, p.vt, vbuf, true);
+        if (t < nt) {
+            issue(t, i0, i1, i2, true);
+            wait_vmcnt<U>();
+        } else {
+            wait_vmcnt<0>();
         }
-        if (t < nt) wait_vmcnt<2 * U>();
-        else wait_vmcnt<0>();
     }
     __builtin_amdgcn_s_barrier();  // Q and the ancestor bits are in LDS
     asm volatile("" ::: "memory");
@@ -1890,11 +1914,8 @@ __global__ void __launch_bounds__(KB_NW * 64, D == 64 ? 4 : 2) attn_blocks_kerne
         for (int kk = 0; kk < KK; kk++) qreg[kk] = *reinterpret_cast<const bf16x8 *>(lq + (((2 * kk + hh) ^ tv.ksw) << 4));
         for (; t < nt; t += KB_NW) {
             const int tn = t + KB_NW;
-            int nb0 = 0, nb1 = 0;  // the next block's ids fly during this one's products
-            if (PAGED && tn < nfull) {
-                nb0 = bt[(k0 >> 4) + 2 * tn];
-                nb1 = bt[(k0 >> 4) + 2 * tn + 1];
-            }
+            int i0 = 0, i1 = 0, i2 = 0;
+            if (tn < nt) block_ids(tn, i0, i1, i2);  // they fly during this block's products
             wait_vmcnt<U>();  // K of block t (V may still be on its way)
             asm volatile("" ::: "memory");
             bf16x8 pf[Geo<D>::NP][2];
@@ -1902,21 +1923,16 @@ __global__ void __launch_bounds__(KB_NW * 64, D == 64 ? 4 : 2) attn_blocks_kerne
             const uint32_t vis = block_vis(t);
             qk_softmax_half<D, true>(tv, lk, 0, qreg, oacc, m_run, l_run, p.scale_log2, vis, pf, t >= nfull);
             wait_lds_reads();
-            size_t b0 = 0, b1 = 0;
-            if (tn < nfull) {
-                b0 = full_base(tn, 0, nb0);
-                b1 = full_base(tn, 1, nb1);
-                issue_full(kc, kbuf, false, b0, b1);
-            } else if (tn < nt) {
-                issue_edge(tn, kc, p.kt, kbuf, false);
+            if (tn < nt) {
+                issue(tn, i0, i1, i2, false);
+                wait_vmcnt<U>();  // V of block t (K of the next one may still be on its way)
+            } else {
+                wait_vmcnt<0>();
             }
-            if (tn < nt) wait_vmcnt<U>();  // V of block t (K of the next one may still be on its way)
-            else wait_vmcnt<0>();
             asm volatile("" ::: "memory");
             pv_accumulate_half<D>(tv, lv, 0, pf, oacc, t >= nfull, ill);
             wait_lds_reads();
-            if (tn < nfull) issue_full(vc, vbuf, true, b0, b1);
-            else if (tn < nt) issue_edge(tn, vc, p.vt, vbuf, true);
+            if (tn < nt) issue(tn, i0, i1, i2, true);
         }
     }
 
@@ -1948,6 +1964,7 @@ __global__ void __launch_bounds__(KB_NW * 64, D == 64 ? 4 : 2) attn_blocks_kerne
         if (hh == 0) ml[wave * 32 + c32] = float2{m_run, l_tot};
     }
     __syncthreads();
+    if (BALANCED && share.j == 0 && kvh == 0 && rg == 0 && tid == 0) p.split_tab[b] = make_int2(share.start, share.nvalid);
     const int row = tid >> 4, piece = tid & 15;  // a row's 16 threads own pieces `piece` and (d = 128) piece + 16
     const int kq2 = (int)fast_div(rg * 32 + row, p.G, p.inv_g, rem), h2 = kvh * p.G + (int)rem;
     if (kq2 >= p.T_max) return;
@@ -2607,15 +2624,30 @@ static int32_t launch_wide(const AttnParams &p, dim3 grid, hipStream_t st) {
     return check_launch();
 }
 
-template <int D, bool PAGED>
+template <int D, bool PAGED, bool BALANCED, bool NT>
 static int32_t launch_blocks(const AttnParams &p, dim3 grid, hipStream_t st) {
     static const bool lds_ok = [] {
-        return hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_blocks_kernel<D, PAGED>),
+        return hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_blocks_kernel<D, PAGED, BALANCED, NT>),
                                    hipFuncAttributeMaxDynamicSharedMemorySize, KbGeo<D>::LDS) == hipSuccess;
     }();
     if (!lds_ok) return ETV_ERR_HIP;
-    hipLaunchKernelGGL((attn_blocks_kernel<D, PAGED>), grid, dim3(KB_NW * 64), KbGeo<D>::LDS, st, p);
+    hipLaunchKernelGGL((attn_blocks_kernel<D, PAGED, BALANCED, NT>), grid, dim3(KB_NW * 64), KbGeo<D>::LDS, st, p.prefix_len, p.n_nodes,
+                       p.block_table, p.Hkv, p.inv_hkv, p.B * p.nsplit, p.nsplit, p.inv_nsplit, p.max_blocks, p.chunk, p.inv_chunk, p);
     return check_launch();
+}
+template <int D>
+static int32_t launch_blocks_form(bool paged, const AttnParams &p, dim3 grid, hipStream_t st) {
+    // a single reader of its K/V bytes streams them past L2
+    switch ((paged ? 4 : 0) + (p.balanced ? 2 : 0) + (p.pairs == 1 ? 1 : 0)) {
+    case 0: return launch_blocks<D, false, false, false>(p, grid, st);
+    case 1: return launch_blocks<D, false, false, true>(p, grid, st);
+    case 2: return launch_blocks<D, false, true, false>(p, grid, st);
+    case 3: return launch_blocks<D, false, true, true>(p, grid, st);
+    case 4: return launch_blocks<D, true, false, false>(p, grid, st);
+    case 5: return launch_blocks<D, true, false, true>(p, grid, st);
+    case 6: return launch_blocks<D, true, true, false>(p, grid, st);
+    default: return launch_blocks<D, true, true, true>(p, grid, st);
+    }
 }
 
 // 8 wavefronts: one workgroup per compute unit with a 4-stage ring (128 KiB of LDS at d = 128);
@@ -2727,7 +2759,7 @@ static int32_t attention_run(const etv_attn_desc *h, const void *q, const void *
     p.block_size = h->block_size; p.max_blocks = h->max_blocks; p.P_cap = h->P_cap; p.P_max = h->P_max;
     p.words = (h->T_max + 63) / 64;
     p.chunk = pl.chunk; p.nsplit = pl.nsplit; p.pairs = pl.pairs; p.wgp = pl.wgp;
-    p.inv_g = fast_div_inv(p.G); p.inv_hkv = fast_div_inv(p.Hkv); p.inv_nsplit = fast_div_inv(p.nsplit);
+    p.inv_g = fast_div_inv(p.G); p.inv_hkv = fast_div_inv(p.Hkv); p.inv_nsplit = fast_div_inv(p.nsplit); p.inv_chunk = fast_div_inv(p.chunk);
     if (p.pairs > 0) p.inv_pairs = fast_div_inv(p.pairs);
     const float scale = (h->scale == 0.f) ? 1.0f / sqrtf((float)h->d) : h->scale;
     p.scale_log2 = scale * 1.4426950408889634f;
@@ -2743,8 +2775,7 @@ static int32_t attention_run(const etv_attn_desc *h, const void *q, const void *
     int32_t rc;
     if (pl.blocks) {
         const dim3 grid(8, pl.pairs, ((unsigned)h->B * pl.nsplit * h->Hkv + 7) / 8);
-        if (h->d == 128) rc = h->block_size > 0 ? launch_blocks<128, true>(p, grid, st) : launch_blocks<128, false>(p, grid, st);
-        else rc = h->block_size > 0 ? launch_blocks<64, true>(p, grid, st) : launch_blocks<64, false>(p, grid, st);
+        rc = h->d == 128 ? launch_blocks_form<128>(h->block_size > 0, p, grid, st) : launch_blocks_form<64>(h->block_size > 0, p, grid, st);
     } else if (pl.mfma) {
         const dim3 grid = pl.balanced ? dim3(pl.nsplit * h->B, h->Hkv * pl.wgp, 1) : dim3(pl.nsplit, h->Hkv * pl.wgp, h->B);
         rc = h->d == 128 ? launch_mfma_shape<128>(pl, h->block_size > 0, p, grid, st)

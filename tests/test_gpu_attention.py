@@ -631,6 +631,36 @@ def test_key_block_kernel_edges(d, paged):
 
 
 @pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("d", [64, 128])
+def test_key_block_kernel_tree_rows_at_every_place_of_a_block(d, paged):
+    """Tree rows in the cache behind prefixes of 80 ... 96 keys: a 32-key block of the tree lies in two or three cache blocks, and the
+    last of them is the table's last entry.  The bits of the separate buffer."""
+    rng = np.random.default_rng(5300 + d + paged)
+    T, P = 40, list(range(80, 97))
+    n = [40, 32, 33, 1, 17, 16, 39] + [T] * 10
+    parents = [random_tree(rng, T) for _ in P]
+    wl = synth.assemble("tail", rng, parents, P, Hq=4, Hkv=2, d=d, dtype="bf16", V=512, W=T, paged=paged, T_max=T, with_logits=False,
+                        spare_blocks=3, tail_room=T)
+    wl.n_nodes[:] = n
+    for b in range(len(P)):
+        for j in range(n[b]):
+            pos = P[b] + j
+            at = (wl.block_table[b, pos // synth.BLOCK], slice(None), pos % synth.BLOCK) if paged else (b, pos)
+            wl.k_cache[at], wl.v_cache[at] = wl.kt[b, j], wl.vt[b, j]
+    if paged:
+        wl.block_table = np.ascontiguousarray(wl.block_table[:, :(max(P) + T + synth.BLOCK - 1) // synth.BLOCK])
+    dv = DevWorkload(wl)
+    m = api.build_tree_mask(dv.parent, dv.n_nodes)
+    for kv_split in (64, 4096):
+        sep, lse_sep = gpu_attention(dv, m["bitmask"], flags=api.ATTN_FLAG_KEY_BLOCKS, kv_split=kv_split)
+        tail, lse_tail = api.tree_verify_attention(dv.q, dv.k_cache, dv.v_cache, dv.prefix_len, None, None, m["bitmask"], dv.n_nodes,
+                                                   P_max=dv.P_max, block_table=dv.block_table, flags=api.ATTN_FLAG_KEY_BLOCKS, kv_split=kv_split)
+        torch.cuda.synchronize()
+        assert torch.equal(sep, tail) and torch.equal(lse_sep, lse_tail), kv_split
+    _check(wl, flags=api.ATTN_FLAG_KEY_BLOCKS, kernel="key_blocks")
+
+
+@pytest.mark.parametrize("paged", [False, True])
 @pytest.mark.parametrize("T,Hq,Hkv", [(33, 16, 4), (64, 8, 2), (65, 8, 2), (70, 7, 1), (97, 8, 2), (150, 2, 1), (192, 4, 2), (256, 4, 2)])
 def test_wide_kernel_edges(T, Hq, Hkv, paged):
     """Two chunks per wavefront: splits of 0 ... 14 full tiles (fewer than the ring, its start, its last five), no to five tiles
