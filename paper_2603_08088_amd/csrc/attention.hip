@@ -48,6 +48,9 @@ struct AttnParams {
 };
 
 constexpr float kLn2 = 0.6931471805599453f;
+typedef __attribute__((ext_vector_type(2))) float f32x2;
+// memory that no kernel writes while it is read: uniform addresses go through scalar loads
+typedef __attribute__((address_space(4))) const int32_t *const_i32_ptr;
 
 __device__ __forceinline__ int seq_prefix_len(const AttnParams &p, int b) { return clampi(p.prefix_len[b], 0, p.P_max); }
 __device__ __forceinline__ int seq_nsplit(const AttnParams &p, int P) { return max(1, (P + p.chunk - 1) / p.chunk); }
@@ -331,81 +334,125 @@ __global__ void __launch_bounds__(64) attn_generic_kernel(AttnParams p) {
 }
 
 // ----------------------------------------------------------------------------------------------
-// Combine: grid (T_max, Hq, B), D threads.  out = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s.
+// Combine: grid (row groups of a sequence, B).  out = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s.
 // ----------------------------------------------------------------------------------------------
 // WPR wavefronts per query row (b, k, h), 4 / WPR rows per workgroup; a lane owns D / (64 * WPR) consecutive output
-// elements (two wavefronts per row for small launches, where the latency of a row's chain is what counts).  Two
-// trips to memory: the sequence's sizes, then the row's first U splits (only splits that exist are read; all loads of
-// a batch are in flight together).  Further batches of U splits, for launches with more splits than that, update a
-// running (M, L, acc) that is rescaled when a later batch raises the maximum.
+// elements (two wavefronts per row for small launches, where the latency of a row's chain is what counts).  U splits are a
+// batch, whose loads are in flight together; further batches, for launches with more splits than that, update a
+// running (M, L, acc) that is rescaled when a later batch raises the maximum.  Lane i of every sixteen works out the weight of
+// split i % U, so a batch costs one exponential and a few lane moves instead of U exponentials in every lane.
+// What bounds it is latency: what the first addresses need are leading scalar arguments, as in the key-block kernel, and where
+// every sequence owns the same slots (!BALANCED) the first batch is asked for together with the sizes (the slots exist whatever the
+// lengths are, and what an absent one holds is not used).  Before, the arguments, two 64-bit divisions, the sizes and the
+// partials came one after the other: 32 layers of B = 1, T = 60, P = 2048 with four splits 470.7 -> 433.0 us, 63 drawn calls with
+// splits 6 % shorter on average, one sequence with 108 splits 16.6 -> 14.3.
 // SHARED: the four wavefronts of a workgroup take every fourth split of one row and merge through LDS, for launches whose
 // splits would otherwise be several batches in series.  32 rows, 43 splits: 9.0 -> 4.7 us; 16 rows, 107 splits: 18.2 -> 7.4;
 // with many rows the batches of different rows overlap anyway (1920 rows, 32 splits: 9.0, shared 11.2), and up to 16 splits
 // one wavefront's single batch is as fast or faster: a row whose sequence has no more is left to the first wavefront (whole
 // call, B = 2, T = 16, 32/8 heads, 24 equal splits launched and some 12 used 18.0 us, shared 20.1; one sequence with 24 10.7, 12.1).
-template <typename T, int D, int WPR, int U, bool SHARED>
-__global__ void __launch_bounds__(256) attn_combine_kernel(AttnParams p) {
+template <typename T, int D, int WPR, int U, bool SHARED, bool BALANCED>
+__global__ void __launch_bounds__(256)
+attn_combine_kernel(const int32_t *sizes, const int32_t *n_nodes, const float *part_o, const float *part_m, const float *part_l, int Hq,
+                    uint32_t inv_hq, int T_max, int nsplit, AttnParams p) {
     constexpr int E = D / (64 * WPR);
     static_assert(E >= 1 && (!SHARED || WPR == 1), "at least one element per lane");
-    const int wv = threadIdx.x >> 6;
-    const long row = SHARED ? (long)blockIdx.x : (long)blockIdx.x * (4 / WPR) + wv / WPR;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int row = SHARED ? (int)blockIdx.x : (int)blockIdx.x * (4 / WPR) + wv / WPR;  // of the sequence
     const int lane = (wv % WPR) * 64 + (threadIdx.x & 63);  // position within the row, in units of E elements
-    const long rows_total = (long)p.B * p.T_max * p.Hq;
-    if (row >= rows_total) return;
-    const int h = (int)(row % p.Hq);
-    const long bk = row / p.Hq;
-    const int k = (int)(bk % p.T_max), b = (int)(bk / p.T_max);
-    const int n_raw = p.n_nodes[b], P_raw = p.prefix_len[b];  // all before any is used: one trip
-    int2 share = {0, 0};
-    if (p.balanced) share = p.split_tab[b];
+    if (row >= Hq * T_max) return;
+    uint32_t h_;
+    const int k = (int)fast_div(row, Hq, inv_hq, h_), h = (int)h_, b = blockIdx.y;
+    const uint32_t sstride = (uint32_t)Hq * T_max;  // rows between consecutive splits
     T *out = static_cast<T *>(p.out);
-    const size_t orow = (((size_t)b * p.T_max + k) * p.Hq + h) * D + (size_t)lane * E;
-    const size_t lrow = ((size_t)b * p.Hq + h) * p.T_max + k;
-    const int nvalid = p.balanced ? share.y : seq_nsplit(p, clampi(P_raw, 0, p.P_max));
-    if (k >= clampi(n_raw, 0, p.T_max)) {
+    const size_t orow = (((size_t)b * T_max + k) * Hq + h) * D + (size_t)lane * E;
+    const size_t lrow = ((size_t)b * Hq + h) * T_max + k;
+    // A batch: splits first, first + step, ... of `count`.  Lane i of every sixteen holds the statistics of split i % U of the batch (one
+    // load each, one exponential for all), and every lane its elements of all of them.
+    typedef std::conditional_t<E == 2, f32x2, float> elems;
+    const int u_own = threadIdx.x & (U - 1);
+    float m_own, l_own;
+    elems os[U];
+    auto fetch = [&](size_t pr0, int first, int step, int count) {
+        const int own = first + u_own * step;
+        const size_t r_own = pr0 + (size_t)(uint32_t)(own < count ? own : 0) * sstride;
+        m_own = part_m[r_own];
+        l_own = part_l[r_own];
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const int x = first + u * step;
+            os[u] = *reinterpret_cast<const elems *>(part_o + (pr0 + (size_t)(uint32_t)(x < count ? x : 0) * sstride) * D + (size_t)lane * E);
+        }
+    };
+    const size_t pr_fixed = ((size_t)((uint32_t)b * nsplit) * Hq + h) * T_max + k;
+    const int n_raw = ((const_i32_ptr)(uintptr_t)n_nodes)[b];
+    int first_slot = 0, nvalid, P_raw = 0;
+    if constexpr (BALANCED) {
+        first_slot = ((const_i32_ptr)(uintptr_t)sizes)[2 * b];
+        nvalid = ((const_i32_ptr)(uintptr_t)sizes)[2 * b + 1];
+    } else {
+        P_raw = ((const_i32_ptr)(uintptr_t)sizes)[b];
+        if constexpr (!SHARED) {
+            fetch(pr_fixed, 0, 1, nsplit);
+            // all of them here and now, with the arguments: one trip
+            if constexpr (U == 8)
+                asm volatile("" ::"s"(n_raw), "s"(P_raw), "s"(p.P_max), "s"(p.chunk), "s"(p.inv_chunk), "s"(p.out), "s"(p.lse), "v"(m_own), "v"(l_own),
+                             "v"(os[0]), "v"(os[1]), "v"(os[2]), "v"(os[3]), "v"(os[4]), "v"(os[5]), "v"(os[6]), "v"(os[7]));
+            else
+                asm volatile("" ::"s"(n_raw), "s"(P_raw), "s"(p.P_max), "s"(p.chunk), "s"(p.inv_chunk), "s"(p.out), "s"(p.lse), "v"(m_own), "v"(l_own),
+                             "v"(os[0]), "v"(os[1]), "v"(os[2]), "v"(os[3]), "v"(os[4]), "v"(os[5]), "v"(os[6]), "v"(os[7]), "v"(os[U - 8]),
+                             "v"(os[U - 7]), "v"(os[U - 6]), "v"(os[U - 5]), "v"(os[U - 4]), "v"(os[U - 3]), "v"(os[U - 2]), "v"(os[U - 1]));
+        }
+        uint32_t rem;
+        nvalid = max(1, (int)fast_div(clampi(P_raw, 0, p.P_max) + p.chunk - 1, p.chunk, p.inv_chunk, rem));
+    }
+    if (k >= clampi(n_raw, 0, T_max)) {
         if (SHARED && wv > 0) return;  // uniform over the workgroup: no barrier is left behind
 #pragma unroll
         for (int e = 0; e < E; e++) store_elem<T>(out, orow + e, 0.f);
         if (p.lse && lane == 0) p.lse[lrow] = -INFINITY;
         return;
     }
-    const size_t pr0 = part_row(p, p.balanced ? share.x : b * p.nsplit, h, k);
-    const size_t sstride = (size_t)p.Hq * p.T_max;  // rows between consecutive splits
+    const size_t pr0 = BALANCED ? ((size_t)(uint32_t)first_slot * Hq + h) * T_max + k : pr_fixed;
     // (splits shared out by length: a sequence may have far fewer than nsplit)
     const bool many = SHARED && nvalid > U;
     if (SHARED && !many && wv > 0) return;  // uniform over the workgroup, as below
     float M = -INFINITY, L = 0.f, acc[E];
 #pragma unroll
     for (int e = 0; e < E; e++) acc[e] = 0.f;
+    auto over = [](float v, auto f) {  // over the U lanes of a batch, in every lane
+        const auto turn = [](float x, auto ctrl) {
+            return __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), decltype(ctrl)::value, 0xf, 0xf, false));
+        };
+        if (U == 16) v = f(v, turn(v, std::integral_constant<int, 0x128>{}));  // 8, 4, 2, 1 lanes round the sixteen
+        v = f(v, turn(v, std::integral_constant<int, 0x124>{}));
+        v = f(v, turn(v, std::integral_constant<int, 0x122>{}));
+        return f(v, turn(v, std::integral_constant<int, 0x121>{}));
+    };
     auto take = [&](auto every, int first) {  // splits first, first + every, ...
         constexpr int step = decltype(every)::value;
         for (int s0 = first; s0 < nvalid; s0 += U * step) {
-            float ms[U], ls[U], os[U][E];
-#pragma unroll
-            for (int u = 0; u < U; u++) {
-                const bool ok = s0 + u * step < nvalid;
-                const size_t r = pr0 + (size_t)(ok ? s0 + u * step : 0) * sstride;
-                ms[u] = ok ? p.part_m[r] : -INFINITY;
-                ls[u] = ok ? p.part_l[r] : 0.f;
-#pragma unroll
-                for (int e = 0; e < E; e++) os[u][e] = ok ? p.part_o[r * D + (size_t)lane * E + e] : 0.f;
-            }
-            float Mb = M;
-#pragma unroll
-            for (int u = 0; u < U; u++) Mb = fmaxf(Mb, ms[u]);
+            if (BALANCED || SHARED || s0 > 0) fetch(pr0, s0, step, nvalid);
+            if (s0 + u_own * step >= nvalid) m_own = -INFINITY;
+            const float Mb = fmaxf(M, over(m_own, [](float x, float y) { return fmaxf(x, y); }));
             if (Mb == -INFINITY) continue;  // nothing visible in this batch or before
             const float keep = exp2f(M - Mb);  // 0 while M is still -inf
-            L *= keep;
+            M = Mb;
+            const bool there = m_own != -INFINITY;  // absent or empty split: its l and O may be uninitialised memory
+            const float w = there ? exp2f(m_own - M) : 0.f;
+            const uint32_t present = (uint32_t)__ballot(there);
+            L = fmaf(L, keep, over(there ? w * l_own : 0.f, [](float x, float y) { return x + y; }));
 #pragma unroll
             for (int e = 0; e < E; e++) acc[e] *= keep;
-            M = Mb;
 #pragma unroll
             for (int u = 0; u < U; u++) {
-                if (ms[u] != -INFINITY) {  // absent or empty split: its l/O may be uninitialised memory
-                    const float w = exp2f(ms[u] - M);
-                    L = fmaf(w, ls[u], L);
-#pragma unroll
-                    for (int e = 0; e < E; e++) acc[e] = fmaf(w, os[u][e], acc[e]);
+                const float wu = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w), u));
+                const uint32_t mask = 0u - ((present >> u) & 1u);
+                if constexpr (E == 2) {
+                    acc[0] = fmaf(wu, __uint_as_float(__float_as_uint(os[u][0]) & mask), acc[0]);
+                    acc[1] = fmaf(wu, __uint_as_float(__float_as_uint(os[u][1]) & mask), acc[1]);
+                } else {
+                    acc[0] = fmaf(wu, __uint_as_float(__float_as_uint(os[u]) & mask), acc[0]);
                 }
             }
         }
@@ -431,8 +478,12 @@ __global__ void __launch_bounds__(256) attn_combine_kernel(AttnParams p) {
             for (int e = 0; e < E; e++) acc[e] = fmaf(w, s_acc[x][lane * E + e], acc[e]);
         }
     }
+    if constexpr (E == 2 && sizeof(T) == 2) {
+        *reinterpret_cast<uint32_t *>(out + orow) = (uint32_t)float_to_bf16_bits(acc[0] / L) | (uint32_t)float_to_bf16_bits(acc[1] / L) << 16;
+    } else {
 #pragma unroll
-    for (int e = 0; e < E; e++) store_elem<T>(out, orow + e, acc[e] / L);
+        for (int e = 0; e < E; e++) store_elem<T>(out, orow + e, acc[e] / L);
+    }
     if (p.lse && lane == 0) p.lse[lrow] = (M + log2f(L)) * kLn2;
 }
 
@@ -477,9 +528,7 @@ typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) short s16x4;
-typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-typedef __attribute__((address_space(4))) const int32_t *const_i32_ptr;
 
 constexpr int KT = 64;  // keys per tile
 
@@ -2658,6 +2707,25 @@ static int32_t launch_blocks_form(bool paged, const AttnParams &p, dim3 grid, hi
     }
 }
 
+template <typename T, int D, int WPR, int U, bool SHARED>
+static void launch_combine_form(const AttnParams &p, dim3 grid, hipStream_t st) {
+    const uint32_t inv_hq = fast_div_inv(p.Hq);
+    if (p.balanced)
+        hipLaunchKernelGGL((attn_combine_kernel<T, D, WPR, U, SHARED, true>), grid, dim3(256), 0, st, reinterpret_cast<const int32_t *>(p.split_tab),
+                           p.n_nodes, p.part_o, p.part_m, p.part_l, p.Hq, inv_hq, p.T_max, p.nsplit, p);
+    else
+        hipLaunchKernelGGL((attn_combine_kernel<T, D, WPR, U, SHARED, false>), grid, dim3(256), 0, st, p.prefix_len, p.n_nodes, p.part_o, p.part_m,
+                           p.part_l, p.Hq, inv_hq, p.T_max, p.nsplit, p);
+}
+template <typename T, int D, int WPR>
+static void launch_combine(const AttnParams &p, bool shared, hipStream_t st) {
+    const unsigned rows = (unsigned)p.T_max * p.Hq, per_wg = shared ? 1 : 4 / WPR;
+    const dim3 grid((rows + per_wg - 1) / per_wg, p.B);
+    if (shared) launch_combine_form<T, D, 1, 16, true>(p, grid, st);
+    else if (p.nsplit > 8) launch_combine_form<T, D, WPR, 16, false>(p, grid, st);  // many splits: sixteen per batch of loads
+    else launch_combine_form<T, D, WPR, 8, false>(p, grid, st);
+}
+
 // 8 wavefronts: one workgroup per compute unit with a 4-stage ring (128 KiB of LDS at d = 128);
 // 4 wavefronts: two workgroups per compute unit with 2 stages each, or 4 stages when the grid is small
 template <int D>
@@ -2809,22 +2877,12 @@ static int32_t attention_run(const etv_attn_desc *h, const void *q, const void *
     const long crows = (long)h->B * h->T_max * h->Hq;
     const bool shared = pl.nsplit > 16 && crows <= 1024;      // more splits than one batch of a wavefront
     const bool two = !shared && h->d == 128 && crows <= 512;  // very few rows: two wavefronts per row
-    const bool wide = pl.nsplit > 8;                          // many splits: sixteen per batch of loads
-    const int rows_per_wg = shared ? 1 : (two ? 2 : 4);
-    dim3 cgrid((unsigned)((crows + rows_per_wg - 1) / rows_per_wg));
-#define ETV_COMBINE(TY, DD, WPR) \
-    do { \
-        if (shared) hipLaunchKernelGGL((attn_combine_kernel<TY, DD, 1, 16, true>), cgrid, dim3(256), 0, st, p); \
-        else if (wide) hipLaunchKernelGGL((attn_combine_kernel<TY, DD, WPR, 16, false>), cgrid, dim3(256), 0, st, p); \
-        else hipLaunchKernelGGL((attn_combine_kernel<TY, DD, WPR, 8, false>), cgrid, dim3(256), 0, st, p); \
-    } while (0)
-    if (h->dtype == ETV_F32 && h->d == 64) ETV_COMBINE(float, 64, 1);
-    else if (h->dtype == ETV_F32 && two) ETV_COMBINE(float, 128, 2);
-    else if (h->dtype == ETV_F32) ETV_COMBINE(float, 128, 1);
-    else if (h->d == 64) ETV_COMBINE(uint16_t, 64, 1);
-    else if (two) ETV_COMBINE(uint16_t, 128, 2);
-    else ETV_COMBINE(uint16_t, 128, 1);
-#undef ETV_COMBINE
+    if (h->dtype == ETV_F32 && h->d == 64) launch_combine<float, 64, 1>(p, shared, st);
+    else if (h->dtype == ETV_F32 && two) launch_combine<float, 128, 2>(p, shared, st);
+    else if (h->dtype == ETV_F32) launch_combine<float, 128, 1>(p, shared, st);
+    else if (h->d == 64) launch_combine<uint16_t, 64, 1>(p, shared, st);
+    else if (two) launch_combine<uint16_t, 128, 2>(p, shared, st);
+    else launch_combine<uint16_t, 128, 1>(p, shared, st);
     return check_launch();
 }
 }  // namespace etv
