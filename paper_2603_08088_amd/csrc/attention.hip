@@ -44,7 +44,7 @@ struct AttnParams {
     //   part_o [B * nsplit][Hq][T_max][d]; split_tab[b] = (first slot, splits in use) for the combine kernel
     int balanced;
     int2 *split_tab;
-    uint32_t inv_g, inv_hkv, inv_nsplit, inv_pairs, inv_chunk;  // floor(2^32 / G) and so on, for fast_div
+    uint32_t inv_g, inv_hkv, inv_nsplit, inv_chunk;  // floor(2^32 / G) and so on, for fast_div
 };
 
 constexpr float kLn2 = 0.6931471805599453f;
@@ -2082,13 +2082,18 @@ attn_blocks_kernel(const int32_t *prefix_len, const int32_t *n_nodes, const int3
 //
 // Work unit: (split, KV head, sequence) x 16-row chunk of the KV head's packed query rows, one workgroup of four
 // wavefronts that take the 16-key tiles of the split in turn and merge their (m, l, O) through LDS at the end.  No tile
-// is shared inside a workgroup, so the loop has no barrier.  V goes from memory straight into the registers that the
-// matrix instructions read (16 lanes fetch 256 consecutive bytes of a row).  The K operand wants a different row in each
-// of 16 neighbouring lanes, which the vector memory path serves at a quarter of its rate: K tiles take the way through LDS, two buffers per
-// wavefront, filled by direct-to-LDS loads one tile ahead (a lone wavefront's tile 1.35 us, against 1.55 with K in registers,
-// of which the matrix instructions are 0.86).
-// The chunks of one (split, KV head, sequence) re-read its K/V; they get ids that differ by 8, so they run side by side
-// on one XCD and find it in that XCD's L2.
+// is shared inside a workgroup, so the loop has no barrier.  A wavefront owns a K and a V buffer of one tile each, filled by
+// direct-to-LDS loads: K of the next tile is requested when the score products' operand is in registers, V when the value products'
+// is, so that each has most of a tile to arrive.  (The K operand wants a different row in each of 16 neighbouring lanes, which the
+// vector memory path serves at a quarter of its rate; Q, the same way, is fetched once for the workgroup.)  As on the key-block
+// kernel the start-up is one trip to memory for the sizes, the first block ids and the arguments, and nothing in the loop waits for
+// a look-up.
+// The chunks of one (split, KV head, sequence) re-read its K/V; their ids differ by 8, so they run side by side
+// on one XCD and find it in that XCD's L2.  Where there is one chunk, the loads stream past L2.
+// What bounds it: a tile is 64 matrix instructions, 0.86 us at d = 128 (0.43 at 64); two wavefronts of a SIMD take 1.05 us a tile
+// each, a lone one 1.47, so the plan fills two workgroups per compute unit.  The same loads spread between the matrix
+// instructions left V and K half the time to arrive (1.77 us a tile of a lone wavefront); eight wavefronts a workgroup in place of
+// two workgroups were 2 ... 4 % faster in launches that leave the chip idle and 7 % slower in large ones.
 //
 // 64-lane layouts of the 16x16x4 instruction: A / B operand lane = (row | col l % 16, contraction index l / 16),
 // accumulator lane = (col l % 16, rows 4 * (l / 16) + i).  With c = l % 16, g = l / 16:
@@ -2097,10 +2102,11 @@ attn_blocks_kernel(const int32_t *prefix_len, const int32_t *n_nodes, const int3
 //                one 16-byte load: accumulator (v, e) holds columns d = 64 v + 4 * row + e
 // so a query row is a lane column in both, and only the row maximum crosses lanes (c, g) -> (c, g').
 //
-// B = 2, T = 33, 16/4 heads of 128, P = 771 / 1003: 18 us (262 us with one wavefront per query row on the vector ALU,
-// which re-read every key row for each of the G * T rows); B = 1, T = 15, 4/4 heads of 64, P = 128: 6.7 us against
-// 19.7 and a combine launch of 4.0; B = 16, T = 128, P = 2048, 32/8 heads of 128: 659 us, 107 TFLOP/s (the library's fp32
-// matrix product reaches 144 ... 154 on this machine).
+// Against V straight to registers, K one tile ahead in LDS, and three trips to memory before the first load: B = 2, T = 33, 16/4
+// heads of 128, P = 771 / 1003 18.8 -> 16.6 us (graph of calls); B = 1, T = 8, 8/8 heads, P = 300 10.2 -> 7.7; T = 1, 8/2 heads, P =
+// 16384 17.9 -> 15.4; B = 12, T = 20, 32/32 heads of 64, P = 150 14.4 -> 12.7; B = 2, T = 200, 16/4 heads, P = 300 31.7 -> 27.8;
+// B = 16, T = 128, P = 2048, 32/8 heads of 128 657 -> 643, 110 TFLOP/s (the library's fp32 matrix product reaches 144 ... 154 on
+// this machine).
 // ----------------------------------------------------------------------------------------------
 
 __device__ __forceinline__ float quad_max(float v) {  // over the lanes c, c + 16, c + 32, c + 48
@@ -2111,219 +2117,258 @@ __device__ __forceinline__ float quad_max(float v) {  // over the lanes c, c + 1
 }
 
 constexpr int F32_NW = 4;    // wavefronts of a workgroup
+constexpr int F32_GRID_Y = 32768;  // units / 8 of the grid's second dimension; the third has the rest
 constexpr int F32_ROWS = 16; // query rows of a chunk = keys of a tile
 
 template <int D>
-__global__ void __launch_bounds__(F32_NW * 64, 2) attn_f32_kernel(AttnParams p) {
-    constexpr int KJ = D / 16, VB = D / 64, ROWB = 4 * D;
-    const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // 1-D grid: id = ((unit / 8) * chunks + chunk) * 8 + unit % 8, unit = slot * Hkv + KV head, slot = (sequence, split)
-    asm volatile("" ::"s"(p.q), "s"(p.k_cache), "s"(p.v_cache), "s"(p.kt), "s"(p.vt), "s"(p.block_table), "s"(p.prefix_len),
-                 "s"(p.n_nodes), "s"(p.bitmask), "s"(p.B), "s"(p.T_max), "s"(p.Hq), "s"(p.Hkv), "s"(p.G), "s"(p.block_size),
-                 "s"(p.max_blocks), "s"(p.P_cap), "s"(p.P_max), "s"(p.words), "s"(p.chunk), "s"(p.nsplit), "s"(p.pairs));
-    uint32_t rg_, rem;
-    const uint32_t unit8 = fast_div(blockIdx.x >> 3, p.pairs, p.inv_pairs, rg_);
-    const int rg = (int)rg_;
-    const int slot = (int)fast_div(unit8 * 8 + (blockIdx.x & 7), p.Hkv, p.inv_hkv, rem), kvh = (int)rem;
-    if (slot >= p.B * p.nsplit) return;  // uniform over the workgroup
+struct F32Geo {
+    static constexpr int NW = F32_NW;
+    static constexpr int ROWB = 4 * D, TILE = F32_ROWS * ROWB;  // bytes of a K (V, Q, output) row and of 16 of them: 8 or 4 KiB
+    static constexpr int CPR = ROWB / 16, RPL = 64 / CPR;       // 16-byte pieces of a row, rows of a 1 KiB load
+    static constexpr int LOADS = TILE / 1024;                   // 1 KiB loads of a tile: 8 or 4
+    static constexpr int Q_AT = NW * 2 * TILE;                  // LDS: wavefront buffers, Q, ancestor bits, (m, l)
+    static constexpr int BITS_AT = Q_AT + TILE;                 // 4 words x 32 x 8 B (16 rows, twice)
+    static constexpr int ML_AT = BITS_AT + 4 * 256;
+    static constexpr int LDS = ML_AT + NW * F32_ROWS * 8;
+};
+
+template <int D, bool PAGED, bool BALANCED, bool NT>
+__global__ void __launch_bounds__(F32_NW * 64, 2)
+attn_f32_kernel(const int32_t *prefix_len, const int32_t *n_nodes, const int32_t *block_table, int Hkv, uint32_t inv_hkv, int slots, int nsplit,
+                uint32_t inv_nsplit, int max_blocks, int chunk_, uint32_t inv_chunk, AttnParams p) {
+    using G_ = F32Geo<D>;
+    constexpr int NW = F32_NW, KJ = D / 16, VB = D / 64, ROWB = G_::ROWB, TILE = G_::TILE, CPR = G_::CPR, RPL = G_::RPL, LOADS = G_::LOADS;
+    uint8_t *const smem = attn_smem;
+    const uint32_t smem_addr = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)attn_smem;
+    const int tid = threadIdx.x, lane = tid & 63, c = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // grid (8 * chunks, units / 8, its rest): the linear id is ((unit / 8) * chunks + chunk) * 8 + unit % 8, unit = slot * Hkv + KV head
+    const int rg = blockIdx.x >> 3;
+    uint32_t rem;
+    const int slot = (int)fast_div((blockIdx.z * F32_GRID_Y + blockIdx.y) * 8 + (blockIdx.x & 7), Hkv, inv_hkv, rem);
+    const int kvh = (int)rem;
+    if ((uint32_t)slot >= (uint32_t)slots) return;  // uniform over the workgroup
     SplitShare share{};
-    if (p.balanced) {
+    if constexpr (BALANCED) {
         share = balanced_share(p, slot, lane);
         if (!share.live) return;  // uniform over the workgroup
-        if (share.j == 0 && kvh == 0 && rg == 0 && threadIdx.x == 0) p.split_tab[share.b] = make_int2(share.start, share.nvalid);
     }
-    const int slot_b = (int)fast_div(slot, p.nsplit, p.inv_nsplit, rem);
-    const int b = uni(p.balanced ? share.b : slot_b);
-    const int s = uni(p.balanced ? share.j : (int)rem);
-    const int chunk = p.balanced ? share.tps * KT : p.chunk;
-    const int n = clampi(p.balanced ? share.n_raw : p.n_nodes[b], 0, p.T_max);
-    const int P = clampi(p.balanced ? share.P_raw : p.prefix_len[b], 0, p.P_max);
-    const int nvalid = p.balanced ? share.nvalid : seq_nsplit(p, P);
+    const int slot_b = (int)fast_div(slot, nsplit, inv_nsplit, rem);
+    const int b = uni(BALANCED ? share.b : slot_b), s = BALANCED ? share.j : (int)rem, chunk = BALANCED ? share.tps * KT : chunk_;
+    const int k0 = s * chunk;
+    const const_i32_ptr bt = (const_i32_ptr)(uintptr_t)(PAGED ? block_table + (size_t)b * max_blocks : nullptr);
+    // One trip for the sizes, the other arguments and the cache block of the wavefront's first tile, which is read before it is known
+    // whether the prefix reaches that far (inside the table in any case), and used only if it does.
+    int blk0 = 0;
+    if (PAGED) blk0 = bt[min((k0 >> 4) + wave, max_blocks - 1)];
+    const int n_raw = BALANCED ? share.n_raw : ((const_i32_ptr)(uintptr_t)n_nodes)[b];
+    const int P_raw = BALANCED ? share.P_raw : ((const_i32_ptr)(uintptr_t)prefix_len)[b];
+    asm volatile("" ::"s"(n_raw), "s"(P_raw), "s"(blk0), "s"(p.q), "s"(p.k_cache), "s"(p.v_cache), "s"(p.kt), "s"(p.vt), "s"(p.bitmask),
+                 "s"(p.T_max), "s"(p.Hq), "s"(p.G), "s"(p.inv_g), "s"(p.P_cap), "s"(p.P_max), "s"(p.words), "s"(p.scale_log2));
+    const int n = clampi(n_raw, 0, p.T_max), P = clampi(P_raw, 0, p.P_max);
+    const int nvalid = BALANCED ? share.nvalid : max(1, (int)fast_div(P + chunk - 1, chunk, inv_chunk, rem));
     if (s >= nvalid) return;  // uniform over the workgroup
-    const bool direct = (p.nsplit == 1);
-
-    // the lane's packed query row: node kq, head h
-    const int kq = (int)fast_div(rg * F32_ROWS + c, p.G, p.inv_g, rem), h = kvh * p.G + (int)rem;
-    const bool rv = kq < n;
-    const int k0 = s * chunk, k1 = min(P, k0 + chunk);
+    const bool direct = (nsplit == 1);
     const bool active = rg * F32_ROWS < n * p.G;  // does the chunk hold a valid row?
+    const int k1 = min(P, k0 + chunk);
     const int nfull = (active && k1 > k0) ? (k1 - k0) >> 4 : 0;     // full prefix tiles
     const int npt = (active && k1 > k0) ? (k1 - k0 + 15) >> 4 : 0;  // prefix tiles incl. a ragged last one
-    const int nt = npt + ((active && s == nvalid - 1) ? (n + 15) >> 4 : 0);
+    const bool with_tree = active && s == nvalid - 1;
+    const int nt = npt + (with_tree ? (n + 15) >> 4 : 0);
 
-    const uint8_t *kc = static_cast<const uint8_t *>(p.k_cache), *vc = static_cast<const uint8_t *>(p.v_cache);
-    const uint8_t *kt = static_cast<const uint8_t *>(p.kt), *vt = static_cast<const uint8_t *>(p.vt);
-    const const_i32_ptr bt = (const_i32_ptr)(uintptr_t)(p.block_size ? p.block_table + (size_t)b * p.max_blocks : nullptr);
-    const size_t hstride = (size_t)p.Hkv * ROWB;  // between the rows of a head (contiguous cache, tree buffer)
-
-    // K tiles go into LDS buffer `buf` of the wavefront.  A 1 KiB load covers RPL rows; chunk x (16 bytes) of row r is kept
-    // at position x ^ r, which spreads the reads of 16 rows at one chunk over all banks.
-    constexpr int CPR = ROWB / 16, RPL = 64 / CPR, LOADS = 16 / RPL, TILE = 16 * ROWB;
-    __shared__ __attribute__((aligned(1024))) uint8_t smem[F32_NW * 2 * TILE];
-    uint8_t *const kbuf = smem + wave * (2 * TILE);
-    const uint32_t kbuf_addr = (uint32_t)__builtin_amdgcn_readfirstlane(
-        (int)(uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)kbuf);
-    const int lr = lane / CPR, lp = lane % CPR;
-
-    // Full prefix tiles: a scalar base (block or row) plus per-lane offsets that are the same for every tile.
-    const uint32_t rstride = (uint32_t)(bt ? (size_t)ROWB : hstride);
-    uint32_t koff[LOADS], voff[4];
+    const uint8_t *const kc = static_cast<const uint8_t *>(p.k_cache), *const vc = static_cast<const uint8_t *>(p.v_cache);
+    const auto mul = [](uint32_t x, uint32_t y) { return (uint64_t)x * y; };
+    const uint32_t hstride = (uint32_t)Hkv * ROWB;  // between the rows of a head (contiguous cache, tree buffer)
+    const uint32_t blk_stride = 16 * hstride;
+    const uint64_t head_at = PAGED ? (uint64_t)((uint32_t)kvh * 16 * ROWB) : mul(b, p.P_cap) * hstride + (uint32_t)kvh * ROWB;
+    const uint32_t rstride = PAGED ? (uint32_t)ROWB : hstride;
+    // A 1 KiB load covers RPL rows, 64 / RPL lanes each.  16-byte piece x of row r of K (and of Q) is kept at position x ^ r, which
+    // spreads the reads of 16 rows at one piece over all banks; V is read in whole rows and lies as it comes.
+    const uint32_t kbuf = smem_addr + (uint32_t)wave * (2 * TILE), vbuf = kbuf + TILE;
+    const int l_row = lane / CPR, l_pos = lane % CPR;
+    uint32_t koff[LOADS];
 #pragma unroll
-    for (int u = 0; u < LOADS; u++) koff[u] = (RPL * u + lr) * rstride + ((lp ^ (RPL * u + lr)) * 16);
-#pragma unroll
-    for (int i = 0; i < 4; i++) voff[i] = (4 * g + i) * rstride + 16 * c;
-    auto full_off = [&](int t) -> size_t {
-        const int base = k0 + t * 16;
-        return bt ? ((size_t)bt[base >> 4] * p.Hkv + kvh) * (size_t)(16 * ROWB)
-                  : (((size_t)b * p.P_cap + base) * p.Hkv + kvh) * (size_t)ROWB;
+    for (int u = 0; u < LOADS; u++) koff[u] = l_row * rstride + (l_pos ^ (RPL * u + l_row)) * 16;
+    const uint32_t voff = l_row * rstride + l_pos * 16;
+    // The cache blocks that tile x lies in: one, or two where the tree rows begin anywhere (in-place branch cache).
+    auto block_ids = [&](int x, int &i0, int &i1) {
+        if (PAGED) {
+            const int first = x >= npt ? (P + (x - npt) * F32_ROWS) >> 4 : (k0 >> 4) + x;
+            i0 = bt[min(first, max_blocks - 1)];
+            i1 = bt[min(first + 1, max_blocks - 1)];
+        }
     };
-    auto full_k = [&](size_t off, int buf) {
+    auto issue_full = [&](int x, int i0, const uint8_t *cache, uint32_t dst, bool is_v) {
+        const uint8_t *src = cache + head_at + (PAGED ? mul(uni(i0), blk_stride) : mul(k0 + x * F32_ROWS, hstride));
 #pragma unroll
-        for (int u = 0; u < LOADS; u++) async_load16_s<false>(kc + off, koff[u], kbuf_addr + buf * TILE + u * 1024);
+        for (int u = 0; u < LOADS; u++) async_load16_s<NT>(src + (uint32_t)(RPL * u) * rstride, is_v ? voff : koff[u], dst + u * 1024);
     };
     // Ragged last prefix tile and tree tiles: rows past the end repeat the last valid one (masked later).
-    auto edge_row = [&](int t, int j, const uint8_t *cache, const uint8_t *own) -> const uint8_t * {
-        const bool tree = t >= npt;
-        const int base = tree ? (t - npt) * 16 : k0 + t * 16;
-        const int key = min(base + j, (tree ? n : k1) - 1);
-        if (tree && own) return own + (((size_t)b * p.T_max + key) * p.Hkv + kvh) * (size_t)ROWB;
-        const int pos = tree ? P + key : key;  // in-place branch cache: node j at position P + j
-        if (bt) return cache + (((size_t)bt[pos >> 4] * p.Hkv + kvh) * 16 + (pos & 15)) * (size_t)ROWB;
-        return cache + (((size_t)b * p.P_cap + pos) * p.Hkv + kvh) * (size_t)ROWB;
-    };
-    auto edge_k = [&](int t, int buf) {
+    auto issue_edge = [&](int x, int i0, int i1, const uint8_t *cache, const void *own_rows, uint32_t dst, bool is_v) {
+        const bool tree = x >= npt;
+        const int base = tree ? (x - npt) * F32_ROWS : k0 + x * F32_ROWS;
+        const int last = (tree ? n : k1) - 1 - base;
+        const bool own = tree && own_rows;
+        const int pos = tree ? P + base : base;  // in-place branch cache: node j at position P + j
+        if (!PAGED || own) {
+            const uint8_t *src = own ? static_cast<const uint8_t *>(own_rows) + mul(b * p.T_max + base, hstride) + (uint32_t)kvh * ROWB
+                                     : cache + head_at + mul(pos, hstride);
 #pragma unroll
-        for (int u = 0; u < LOADS; u++)
-            async_load16(edge_row(t, RPL * u + lr, kc, kt) + ((lp ^ (RPL * u + lr)) * 16), kbuf_addr + buf * TILE + u * 1024);
+            for (int u = 0; u < LOADS; u++) {
+                const int r = RPL * u + l_row;
+                async_load16_s<false>(src, min(r, last) * hstride + (is_v ? l_pos : l_pos ^ r) * 16, dst + u * 1024);
+            }
+        } else {
+            const uint8_t *src = cache + head_at;
+#pragma unroll
+            for (int u = 0; u < LOADS; u++) {
+                const int r = RPL * u + l_row, at = (pos & 15) + min(r, last);
+                async_load16(src + mul(at < 16 ? i0 : i1, blk_stride) + ((at & 15) * ROWB + (is_v ? l_pos : l_pos ^ r) * 16), dst + u * 1024);
+            }
+        }
+    };
+    auto issue = [&](int x, int i0, int i1, bool is_v) {
+        if (x < nfull) issue_full(x, i0, is_v ? vc : kc, is_v ? vbuf : kbuf, is_v);
+        else issue_edge(x, i0, i1, is_v ? vc : kc, is_v ? p.vt : p.kt, is_v ? vbuf : kbuf, is_v);
     };
 
+    // K of the first tile, then Q and the ancestor bits, then V: the first products wait for all but V.
+    int t = wave, i0 = blk0, i1 = 0;
+    if (active) {
+        if (t < nt) {
+            if (t >= npt) block_ids(t, i0, i1);
+            issue(t, i0, i1, false);
+        }
+        // Q, laid out like a K tile; padded rows repeat node 0's (their results are dropped)
+#pragma unroll
+        for (int u = wave; u < LOADS; u += NW) {
+            const int row = RPL * u + l_row;
+            int kq = (int)fast_div(rg * F32_ROWS + row, p.G, p.inv_g, rem), h = kvh * p.G + (int)rem;
+            if (kq >= n) { kq = 0; h = kvh * p.G; }
+            async_load16(static_cast<const uint8_t *>(p.q) + (((size_t)b * p.T_max + kq) * p.Hq + h) * ROWB + (l_pos ^ row) * 16,
+                         smem_addr + G_::Q_AT + u * 1024);
+        }
+        if (with_tree && wave < p.words) {  // word `wave` of the ancestor bits of the 16 rows
+            int kq = (int)fast_div(rg * F32_ROWS + ((lane >> 1) & 15), p.G, p.inv_g, rem);
+            if (kq >= n) kq = 0;
+            async_load4(reinterpret_cast<const uint32_t *>(p.bitmask + ((size_t)b * p.T_max + kq) * p.words + wave) + (lane & 1),
+                        smem_addr + G_::BITS_AT + wave * 256);
+        }
+        if (t < nt) {
+            issue(t, i0, i1, true);
+            if (t + NW < nt) block_ids(t + NW, i0, i1);
+            wait_vmcnt<LOADS>();
+        } else {
+            wait_vmcnt<0>();
+        }
+    }
+    __builtin_amdgcn_s_barrier();  // Q and the ancestor bits are in LDS
+    asm volatile("" ::: "memory");
+
+    const uint8_t *const lk = smem + wave * (2 * TILE), *const lv = lk + TILE;
     f32x4 qf[KJ], o[VB][4];
     float m_run = -INFINITY, l_run = 0.f;
-    size_t cur = 0;
-    if (wave < nfull) {
-        cur = full_off(wave);
-        full_k(cur, 0);
-    } else if (wave < nt) {
-        edge_k(wave, 0);
-    }
-    const float *qrow = static_cast<const float *>(p.q) + (((size_t)b * p.T_max + kq) * p.Hq + h) * D + 4 * g;
-#pragma unroll
-    for (int j = 0; j < KJ; j++) qf[j] = rv ? *reinterpret_cast<const f32x4 *>(qrow + 16 * j) : f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int v = 0; v < VB; v++)
 #pragma unroll
         for (int e = 0; e < 4; e++) o[v][e] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const uint64_t *mrow = p.bitmask + ((size_t)b * p.T_max + (rv ? kq : 0)) * p.words;
-
-    // Q . K of the tile in buffer `buf`, online softmax, P . V with the V rows already requested.  vis: keys that the
-    // lane's row sees.
+    auto tile_vis = [&](int x) -> uint32_t {  // keys of tile x that the lane's row sees
+        if (x < nfull) return 0xffffu;
+        if (x < npt) return (1u << (k1 - k0 - x * F32_ROWS)) - 1u;  // ragged last prefix tile: 1..15 keys
+        const int w = x - npt;
+        return *reinterpret_cast<const uint16_t *>(smem + G_::BITS_AT + (w >> 2) * 256 + c * 8 + (w & 3) * 2);
+    };
     bool ill = false;
-    auto tile = [&](int buf, f32x4 (&vf)[4][VB], uint32_t vis, bool masked) {
-        const uint8_t *krow = kbuf + buf * TILE + c * ROWB;
-        f32x4 kf[KJ], s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;  // two chains
+    if (t < nt) {
+        const uint8_t *const lq = smem + G_::Q_AT + c * ROWB;
 #pragma unroll
-        for (int j = 0; j < KJ; j++) kf[j] = *reinterpret_cast<const f32x4 *>(krow + (((4 * j + g) ^ c) * 16));
+        for (int j = 0; j < KJ; j++) qf[j] = *reinterpret_cast<const f32x4 *>(lq + (((4 * j + g) ^ c) * 16));
+        const uint8_t *const krow = lk + c * ROWB;
+        const uint8_t *const vrow = lv + 4 * g * ROWB + c * 16;
+#pragma unroll 1
+        for (; t < nt; t += NW) {
+            const int tn = t + NW;
+            const bool masked = t >= nfull;
+            wait_vmcnt<LOADS>();  // K of tile t (V may still be on its way)
+            asm volatile("" ::: "memory");
+            f32x4 kf[KJ], s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0;  // two chains
 #pragma unroll
-        for (int j = 0; j < KJ; j += 2)
+            for (int j = 0; j < KJ; j++) kf[j] = *reinterpret_cast<const f32x4 *>(krow + (((4 * j + g) ^ c) * 16));
+            const uint32_t vis = tile_vis(t);
+            wait_lds_reads();
+            if (tn < nt) issue(tn, i0, i1, false);
 #pragma unroll
-            for (int e = 0; e < 4; e++) {
-                s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[j][e], qf[j][e], s0, 0, 0, 0);
-                s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[j + 1][e], qf[j + 1][e], s1, 0, 0, 0);
-            }
-        float sc[4];
+            for (int j = 0; j < KJ; j += 2)
 #pragma unroll
-        for (int i = 0; i < 4; i++) {
-            sc[i] = (s0[i] + s1[i]) * p.scale_log2;
-            if (masked) sc[i] = ((vis >> (4 * g + i)) & 1u) ? sc[i] : -INFINITY;
-        }
-        const float tmax = quad_max(fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3])));
-        const bool lift = tmax > m_run + kLazy;
-        if (__any(lift)) {
-            const float m_new = lift ? tmax : m_run;
-            const float alpha = lift ? exp2f(m_run - m_new) : 1.f;
-            m_run = m_new;
-            l_run *= alpha;
+                for (int e = 0; e < 4; e++) {
+                    s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[j][e], qf[j][e], s0, 0, 0, 0);
+                    s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[j + 1][e], qf[j + 1][e], s1, 0, 0, 0);
+                }
+            float sc[4];
 #pragma unroll
-            for (int v = 0; v < VB; v++)
-#pragma unroll
-                for (int e = 0; e < 4; e++) o[v][e] *= alpha;
-        }
-        const float ref = m_run == -INFINITY ? 0.f : m_run;  // no finite score so far: masked keys, or products that overflow
-        float pr[4];  // exp2f, here and below: weights below the normal range stay (the bare instruction makes them zero)
-#pragma unroll
-        for (int i = 0; i < 4; i++) pr[i] = exp2f(sc[i] - ref);
-        l_run += (pr[0] + pr[1]) + (pr[2] + pr[3]);
-        if (masked) {
-            uint32_t top = 0;
-#pragma unroll
-            for (int i = 0; i < 4; i++)
+            for (int i = 0; i < 4; i++) sc[i] = ((vis >> (4 * g + i)) & 1u) ? (s0[i] + s1[i]) * p.scale_log2 : -INFINITY;
+            const float tmax = quad_max(fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3])));
+            const bool lift = tmax > m_run + kLazy;
+            if (__any(lift)) {
+                const float m_new = lift ? tmax : m_run;
+                const float alpha = lift ? exp2f(m_run - m_new) : 1.f;
+                m_run = m_new;
+                l_run *= alpha;
 #pragma unroll
                 for (int v = 0; v < VB; v++)
 #pragma unroll
-                    for (int e = 0; e < 4; e++) top = max(top, __float_as_uint(vf[i][v][e]) & 0x7fffffffu);
-            if (__builtin_expect(__any(top >= 0x7f800000u), 0)) {
-                ill = true;
+                    for (int e = 0; e < 4; e++) o[v][e] *= alpha;
+            }
+            const float ref = m_run == -INFINITY ? 0.f : m_run;  // no finite score so far: masked keys, or products that overflow
+            float pr[4];  // exp2f, here and below: weights below the normal range stay (the bare instruction makes them zero)
+#pragma unroll
+            for (int i = 0; i < 4; i++) pr[i] = exp2f(sc[i] - ref);
+            l_run += (pr[0] + pr[1]) + (pr[2] + pr[3]);
+            if (tn < nt) wait_vmcnt<LOADS>();  // V of tile t (K of the next one may still be on its way)
+            else wait_vmcnt<0>();
+            asm volatile("" ::: "memory");
+            f32x4 vf[4][VB];
+#pragma unroll
+            for (int i = 0; i < 4; i++)
+#pragma unroll
+                for (int v = 0; v < VB; v++) vf[i][v] = *reinterpret_cast<const f32x4 *>(vrow + i * ROWB + 256 * v);
+            wait_lds_reads();
+            if (tn < nt) {
+                issue(tn, i0, i1, true);
+                if (tn + NW < nt) block_ids(tn + NW, i0, i1);  // they fly during a whole tile
+            }
+            if (masked) {
+                uint32_t top = 0;
 #pragma unroll
                 for (int i = 0; i < 4; i++)
 #pragma unroll
                     for (int v = 0; v < VB; v++)
 #pragma unroll
-                        for (int e = 0; e < 4; e++) vf[i][v][e] = fabsf(vf[i][v][e]) < INFINITY ? vf[i][v][e] : 0.f;
+                        for (int e = 0; e < 4; e++) top = max(top, __float_as_uint(vf[i][v][e]) & 0x7fffffffu);
+                if (__builtin_expect(__any(top >= 0x7f800000u), 0)) {
+                    ill = true;
+#pragma unroll
+                    for (int i = 0; i < 4; i++)
+#pragma unroll
+                        for (int v = 0; v < VB; v++)
+#pragma unroll
+                            for (int e = 0; e < 4; e++) vf[i][v][e] = fabsf(vf[i][v][e]) < INFINITY ? vf[i][v][e] : 0.f;
+                }
             }
+#pragma unroll
+            for (int i = 0; i < 4; i++)
+#pragma unroll
+                for (int v = 0; v < VB; v++)
+#pragma unroll
+                    for (int e = 0; e < 4; e++)
+                        o[v][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[i][v][e], pr[i], o[v][e], 0, 0, 0);
         }
-#pragma unroll
-        for (int i = 0; i < 4; i++)
-#pragma unroll
-            for (int v = 0; v < VB; v++)
-#pragma unroll
-                for (int e = 0; e < 4; e++)
-                    o[v][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[i][v][e], pr[i], o[v][e], 0, 0, 0);
-    };
-    auto tile_vis = [&](int x) -> uint32_t {  // keys of tile x >= nfull that the lane's row sees
-        if (x < npt) return (1u << (k1 - k0 - x * 16)) - 1u;  // ragged last prefix tile: 1..15 keys
-        const int j0 = (x - npt) * 16;
-        return rv ? (uint32_t)(mrow[j0 >> 6] >> (j0 & 63)) & 0xffffu : 0u;
-    };
-    // A K tile is in LDS when its turn comes: the first one is waited for at the top, a later one is older than the V rows
-    // that the previous products have used.  The next K tile is requested before this tile's V rows for that reason.
-    int t = wave, buf = 0;
-    for (; t < nfull; t += F32_NW, buf ^= 1) {
-        wait_vmcnt<0>();
-        asm volatile("" ::: "memory");
-        const uint8_t *vb = vc + cur;
-        const int tn = t + F32_NW;
-        if (tn < nfull) {
-            cur = full_off(tn);
-            full_k(cur, buf ^ 1);
-        } else if (tn < nt) {
-            edge_k(tn, buf ^ 1);
-        }
-        f32x4 vf[4][VB];
-#pragma unroll
-        for (int i = 0; i < 4; i++)
-#pragma unroll
-            for (int v = 0; v < VB; v++) vf[i][v] = *reinterpret_cast<const f32x4 *>(vb + voff[i] + 256 * v);
-        tile(buf, vf, 0xffffu, false);
-    }
-    for (; t < nt; t += F32_NW, buf ^= 1) {
-        wait_vmcnt<0>();
-        asm volatile("" ::: "memory");
-        if (t + F32_NW < nt) edge_k(t + F32_NW, buf ^ 1);
-        f32x4 vf[4][VB];
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-            const uint8_t *row = edge_row(t, 4 * g + i, vc, vt) + 16 * c;
-#pragma unroll
-            for (int v = 0; v < VB; v++) vf[i][v] = *reinterpret_cast<const f32x4 *>(row + 256 * v);
-        }
-        tile(buf, vf, tile_vis(t), true);
     }
     if (ill) {
         uint64_t up[VB] = {}, down[VB] = {};
-        for (int x = nfull + ((wave - nfull) & (F32_NW - 1)); x < nt; x += F32_NW) {  // the masked ones of the wavefront's tiles
+        for (int x = nfull + ((wave - nfull) & (NW - 1)); x < nt; x += NW) {  // the masked ones of the wavefront's tiles
             const bool tree = x >= npt;
-            const int base = tree ? (x - npt) * 16 : k0 + x * 16, count = min(16, (tree ? n : k1) - base);
+            const int base = tree ? (x - npt) * F32_ROWS : k0 + x * F32_ROWS, count = min(F32_ROWS, (tree ? n : k1) - base);
             find_nonfinite<float, D>(p, b, kvh, P, tree, base, count, tile_vis(x), up, down);
         }
 #pragma unroll
@@ -2337,56 +2382,66 @@ __global__ void __launch_bounds__(F32_NW * 64, 2) attn_f32_kernel(AttnParams p) 
                 }
     }
 
-    // ---- merge the four wavefronts
-    static_assert(F32_NW * F32_ROWS * (D + 6) * 4 <= F32_NW * 2 * TILE, "the merge fits the K buffers");
-    __syncthreads();  // every wavefront has read its last K tile
-    float (*s_o)[F32_ROWS][D + 4] = reinterpret_cast<float (*)[F32_ROWS][D + 4]>(smem);
-    float (*s_m)[F32_ROWS] = reinterpret_cast<float (*)[F32_ROWS]>(smem + sizeof(float) * F32_NW * F32_ROWS * (D + 4));
-    float (*s_l)[F32_ROWS] = s_m + F32_NW;
-    l_run += __shfl_xor(l_run, 16);
-    l_run += __shfl_xor(l_run, 32);
+    // ---- merge the wavefronts: each leaves O in its own K buffer (same size and swizzle)
+    float2 *const ml = reinterpret_cast<float2 *>(smem + G_::ML_AT);
+    const int live = min(NW, nt);
+    if (wave < live) {
+        const float l_tot = quarter_swap_sum(half_swap_sum(l_run));
+        uint8_t *const dst = smem + wave * (2 * TILE) + c * ROWB;
 #pragma unroll
-    for (int v = 0; v < VB; v++)
+        for (int v = 0; v < VB; v++)
 #pragma unroll
-        for (int i = 0; i < 4; i++)
-            *reinterpret_cast<f32x4 *>(&s_o[wave][c][64 * v + 16 * g + 4 * i]) = f32x4{o[v][0][i], o[v][1][i], o[v][2][i], o[v][3][i]};
-    if (g == 0) {
-        s_m[wave][c] = m_run;
-        s_l[wave][c] = l_run;
+            for (int i = 0; i < 4; i++)
+                *reinterpret_cast<f32x4 *>(dst + (((16 * v + 4 * g + i) ^ c) * 16)) = f32x4{o[v][0][i], o[v][1][i], o[v][2][i], o[v][3][i]};
+        if (g == 0) ml[wave * F32_ROWS + c] = float2{m_run, l_tot};
     }
     __syncthreads();
-    const int row = threadIdx.x >> 4, piece = threadIdx.x & 15;  // a row's 16 threads own columns 64 v + 4 * piece .. + 3
+    if (BALANCED && share.j == 0 && kvh == 0 && rg == 0 && tid == 0) p.split_tab[b] = make_int2(share.start, share.nvalid);
+    constexpr int TPR = NW * 64 / F32_ROWS < CPR ? NW * 64 / F32_ROWS : CPR;  // threads of a row: pieces `piece`, `piece` + TPR, ...
+    const int row = tid / TPR, piece = tid % TPR;
+    if (row >= F32_ROWS) return;
     const int kq2 = (int)fast_div(rg * F32_ROWS + row, p.G, p.inv_g, rem), h2 = kvh * p.G + (int)rem;
     if (kq2 >= p.T_max) return;
-    const bool rv2 = kq2 < n;
-    if (!rv2 && !direct) return;
-    float M = -INFINITY, L = 0.f, w[F32_NW];
+    const bool rv = kq2 < n;
+    if (!rv && !direct) return;
+    // all reads of the statistics in one trip, then all reads of the outputs (those of absent wavefronts are skipped)
+    float2 st[NW];
+    float M = -INFINITY, L = 0.f;
 #pragma unroll
-    for (int x = 0; x < F32_NW; x++) M = fmaxf(M, s_m[x][row]);
+    for (int x = 0; x < NW; x++) st[x] = ml[x * F32_ROWS + row];
 #pragma unroll
-    for (int x = 0; x < F32_NW; x++) {
-        w[x] = s_m[x][row] == -INFINITY ? 0.f : exp2f(s_m[x][row] - M);
-        L = fmaf(w[x], s_l[x][row], L);
+    for (int x = 0; x < NW; x++) {
+        if (x >= live) st[x] = float2{-INFINITY, 0.f};
+        M = fmaxf(M, st[x].x);
+    }
+    f32x4 acc[CPR / TPR];
+#pragma unroll
+    for (int v = 0; v < CPR / TPR; v++) acc[v] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int x = 0; x < NW; x++) {
+        if (x >= live) break;  // uniform
+        const float w = st[x].x == -INFINITY ? 0.f : exp2f(st[x].x - M);
+        L = fmaf(w, st[x].y, L);
+        const uint8_t *src = smem + x * (2 * TILE) + row * ROWB;
+#pragma unroll
+        for (int v = 0; v < CPR / TPR; v++) {
+            const f32x4 ox = *reinterpret_cast<const f32x4 *>(src + (((piece + TPR * v) ^ row) * 16));
+#pragma unroll
+            for (int e = 0; e < 4; e++) acc[v][e] = fmaf(w, ox[e], acc[v][e]);
+        }
     }
     const size_t pr = part_row(p, slot, h2, kq2);
     float *dst = direct ? static_cast<float *>(p.out) + (((size_t)b * p.T_max + kq2) * p.Hq + h2) * D : p.part_o + pr * D;
-    const float inv = direct ? (rv2 ? 1.f / L : 0.f) : 1.f;
+    const float inv = direct ? 1.f / L : 1.f;
 #pragma unroll
-    for (int v = 0; v < VB; v++) {
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int v = 0; v < CPR / TPR; v++) {
 #pragma unroll
-        for (int x = 0; x < F32_NW; x++) {
-            const f32x4 ox = *reinterpret_cast<const f32x4 *>(&s_o[x][row][64 * v + 4 * piece]);
-#pragma unroll
-            for (int e = 0; e < 4; e++) acc[e] = fmaf(w[x], ox[e], acc[e]);
-        }
-#pragma unroll
-        for (int e = 0; e < 4; e++) acc[e] = rv2 ? acc[e] * inv : 0.f;
-        *reinterpret_cast<f32x4 *>(dst + 64 * v + 4 * piece) = acc;
+        for (int e = 0; e < 4; e++) acc[v][e] = rv ? acc[v][e] * inv : 0.f;
+        *reinterpret_cast<f32x4 *>(dst + 4 * (piece + TPR * v)) = acc[v];
     }
     if (piece == 0) {
         if (direct) {
-            if (p.lse) p.lse[((size_t)b * p.Hq + h2) * p.T_max + kq2] = rv2 ? (M + log2f(L)) * kLn2 : -INFINITY;
+            if (p.lse) p.lse[((size_t)b * p.Hq + h2) * p.T_max + kq2] = rv ? (M + log2f(L)) * kLn2 : -INFINITY;
         } else {
             p.part_m[pr] = M;
             p.part_l[pr] = L;
@@ -2531,10 +2586,10 @@ static Plan make_plan(const etv_attn_desc *h) {
         // A workgroup puts one wavefront on each SIMD of a compute unit and the matrix cores bound the launch: its time is
         // the tiles of a wavefront times the workgroups of the fullest compute unit, and not less than a tile's latency
         // chain allows; every split adds partials and a combine step, the first one the combine launch.  Measured per tile:
-        // 1.1 us at d = 128 (0.6 at d = 64) times the wavefronts of a SIMD, 1.35 us (0.8) for a lone one, of which
-        // 0.86 (0.43) are matrix instructions; 16384 keys, T = 1: 24 us with 43 splits, 36 with 128.
+        // 1.05 us at d = 128 (0.6 at d = 64) times the wavefronts of a SIMD, 1.47 us (0.95) for a lone one, of which
+        // 0.86 (0.43) are matrix instructions.
         pl.pairs = (int)((rows + F32_ROWS - 1) / F32_ROWS);
-        const double busy = h->d == 128 ? 1.1 : 0.6, chain = h->d == 128 ? 1.35 : 0.8;
+        const double busy = h->d == 128 ? 1.05 : 0.6, chain = h->d == 128 ? 1.47 : 0.95;
         const double part_us = 2.0 * B * h->Hq * h->T_max * (h->d + 2.0) * 4.0 / 3.0e6;
         const long units = (long)B * h->Hkv * pl.pairs;
         const int forced_tps = h->kv_split > 0 ? min(tiles, (h->kv_split + KT - 1) / KT) : 0;
@@ -2707,6 +2762,32 @@ static int32_t launch_blocks_form(bool paged, const AttnParams &p, dim3 grid, hi
     }
 }
 
+template <int D, bool PAGED, bool BALANCED, bool NT>
+static int32_t launch_f32(const AttnParams &p, dim3 grid, hipStream_t st) {
+    static const bool lds_ok = [] {
+        return hipFuncSetAttribute(reinterpret_cast<const void *>(&attn_f32_kernel<D, PAGED, BALANCED, NT>),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, F32Geo<D>::LDS) == hipSuccess;
+    }();
+    if (!lds_ok) return ETV_ERR_HIP;
+    hipLaunchKernelGGL((attn_f32_kernel<D, PAGED, BALANCED, NT>), grid, dim3(F32_NW * 64), F32Geo<D>::LDS, st, p.prefix_len, p.n_nodes,
+                       p.block_table, p.Hkv, p.inv_hkv, p.B * p.nsplit, p.nsplit, p.inv_nsplit, p.max_blocks, p.chunk, p.inv_chunk, p);
+    return check_launch();
+}
+template <int D>
+static int32_t launch_f32_form(bool paged, const AttnParams &p, dim3 grid, hipStream_t st) {
+    // a single reader of its K/V bytes streams them past L2
+    switch ((paged ? 4 : 0) + (p.balanced ? 2 : 0) + (p.pairs == 1 ? 1 : 0)) {
+    case 0: return launch_f32<D, false, false, false>(p, grid, st);
+    case 1: return launch_f32<D, false, false, true>(p, grid, st);
+    case 2: return launch_f32<D, false, true, false>(p, grid, st);
+    case 3: return launch_f32<D, false, true, true>(p, grid, st);
+    case 4: return launch_f32<D, true, false, false>(p, grid, st);
+    case 5: return launch_f32<D, true, false, true>(p, grid, st);
+    case 6: return launch_f32<D, true, true, false>(p, grid, st);
+    default: return launch_f32<D, true, true, true>(p, grid, st);
+    }
+}
+
 template <typename T, int D, int WPR, int U, bool SHARED>
 static void launch_combine_form(const AttnParams &p, dim3 grid, hipStream_t st) {
     const uint32_t inv_hq = fast_div_inv(p.Hq);
@@ -2836,7 +2917,6 @@ static int32_t attention_run(const etv_attn_desc *h, const void *q, const void *
     p.words = (h->T_max + 63) / 64;
     p.chunk = pl.chunk; p.nsplit = pl.nsplit; p.pairs = pl.pairs; p.wgp = pl.wgp;
     p.inv_g = fast_div_inv(p.G); p.inv_hkv = fast_div_inv(p.Hkv); p.inv_nsplit = fast_div_inv(p.nsplit); p.inv_chunk = fast_div_inv(p.chunk);
-    if (p.pairs > 0) p.inv_pairs = fast_div_inv(p.pairs);
     const float scale = (h->scale == 0.f) ? 1.0f / sqrtf((float)h->d) : h->scale;
     p.scale_log2 = scale * 1.4426950408889634f;
     if (pl.nsplit > 1) {
@@ -2857,10 +2937,9 @@ static int32_t attention_run(const etv_attn_desc *h, const void *q, const void *
         rc = h->d == 128 ? launch_mfma_shape<128>(pl, h->block_size > 0, p, grid, st)
                          : launch_mfma_shape<64>(pl, h->block_size > 0, p, grid, st);
     } else if (pl.f32) {
-        const dim3 grid((unsigned)f32_blocks(h, pl));
-        if (h->d == 64) hipLaunchKernelGGL((attn_f32_kernel<64>), grid, dim3(F32_NW * 64), 0, st, p);
-        else hipLaunchKernelGGL((attn_f32_kernel<128>), grid, dim3(F32_NW * 64), 0, st, p);
-        rc = check_launch();
+        const unsigned units8 = (unsigned)(((long)h->B * pl.nsplit * h->Hkv + 7) / 8);
+        const dim3 grid(8 * (unsigned)pl.pairs, min(units8, (unsigned)F32_GRID_Y), (units8 + F32_GRID_Y - 1) / F32_GRID_Y);
+        rc = h->d == 128 ? launch_f32_form<128>(h->block_size > 0, p, grid, st) : launch_f32_form<64>(h->block_size > 0, p, grid, st);
     } else {
         dim3 grid(h->T_max, h->Hq, h->B * pl.nsplit);
         if (h->dtype == ETV_F32 && h->d == 64)

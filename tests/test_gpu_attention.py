@@ -228,6 +228,51 @@ def test_fp32_kernel_tile_and_chunk_edges(d, paged):
             _check(wl, flags=api.ATTN_FLAG_GENERIC)
 
 
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("d", [64, 128])
+def test_fp32_kernel_tree_rows_at_every_place_of_a_block(d, paged):
+    """Tree rows in the cache behind prefixes of 80 ... 96 keys: a 16-key tile of the tree lies in one or two cache blocks, and the last
+    of them is the table's last entry; one 16-row chunk per KV head (loads that stream) and several.  The bits of the separate buffer."""
+    rng = np.random.default_rng(3300 + d + paged)
+    T, P = 40, list(range(80, 97))
+    n = [40, 32, 33, 1, 17, 16, 39] + [T] * 10
+    parents = [random_tree(rng, T) for _ in P]
+    for Hq, T_few in ((4, T), (2, 16)):
+        wl = synth.assemble("tail", rng, parents, P, Hq=Hq, Hkv=2, d=d, dtype="f32", V=512, W=T, paged=paged, T_max=T, with_logits=False,
+                            spare_blocks=3, tail_room=T)
+        wl.n_nodes[:] = [min(x, T_few) for x in n]
+        for b in range(len(P)):
+            for j in range(n[b]):
+                pos = P[b] + j
+                at = (wl.block_table[b, pos // synth.BLOCK], slice(None), pos % synth.BLOCK) if paged else (b, pos)
+                wl.k_cache[at], wl.v_cache[at] = wl.kt[b, j], wl.vt[b, j]
+        if paged:
+            wl.block_table = np.ascontiguousarray(wl.block_table[:, :(max(P) + T + synth.BLOCK - 1) // synth.BLOCK])
+        dv = DevWorkload(wl)
+        m = api.build_tree_mask(dv.parent, dv.n_nodes)
+        for kv_split in (64, 4096):
+            sep, lse_sep = gpu_attention(dv, m["bitmask"], kv_split=kv_split)
+            tail, lse_tail = api.tree_verify_attention(dv.q, dv.k_cache, dv.v_cache, dv.prefix_len, None, None, m["bitmask"], dv.n_nodes,
+                                                       P_max=dv.P_max, block_table=dv.block_table, kv_split=kv_split)
+            torch.cuda.synchronize()
+            assert torch.equal(sep, tail) and torch.equal(lse_sep, lse_tail), kv_split
+        _check(wl)
+
+
+def test_fp32_kernel_grid_beyond_its_second_dimension():
+    """More than 32768 * 8 (sequence, KV head) units: the grid's third dimension.  One node over one prefix key, which torch can say
+    in float64: 1e-5 as for every fp32 case."""
+    B, H, d = 1030, 256, 64
+    gen = torch.Generator(device="cuda").manual_seed(3400)
+    q, kt, vt, kc, vc = (torch.randn((B, 1, H, d), generator=gen, device="cuda") for _ in range(5))
+    one = torch.ones(B, dtype=torch.int32, device="cuda")
+    bits = torch.ones((B, 1, 1), dtype=torch.int64, device="cuda")
+    out, _ = api.tree_verify_attention(q, kc, vc, one, kt, vt, bits, one, P_max=1)
+    s = torch.stack([(q.double() * k.double()).sum(-1) for k in (kc, kt)]) / d ** 0.5
+    w = torch.softmax(s, 0)[..., None]
+    assert (out.double() - w[0] * vc.double() - w[1] * vt.double()).abs().max() <= 1e-5
+
+
 @pytest.mark.parametrize("d,flags", [(d, flags) for flags in (api.ATTN_FLAG_WHOLE_TILE | api.ATTN_FLAG_LARGE_WG, api.ATTN_FLAG_WHOLE_TILE | api.ATTN_FLAG_SMALL_WG,
                                                               api.ATTN_FLAG_KEY_HALVES | api.ATTN_FLAG_LARGE_WG) for d in (64, 128)] + [(128, api.ATTN_FLAG_WIDE)])
 def test_row_maximum_uses_the_finished_scores(d, flags):
