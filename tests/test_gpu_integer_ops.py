@@ -66,6 +66,25 @@ def test_tensorize_random_trees(T):
     _tensorize_case(par, n, P, 1, 1)
 
 
+@pytest.mark.parametrize("T", [16, 17, 18, 33, 66, 130])
+def test_tensorize_deep_leaves_and_a_dense_mask_anywhere(T):
+    """Chains around the sixteen nodes a thread keeps of its own, and the dense mask at every alignment."""
+    rng = np.random.default_rng(2500 + T)
+    short = synth.tree_chain(17) if T > 17 else synth.tree_chain(T)
+    par = np.zeros((3, T), dtype=np.int32)
+    par[0], par[1, :len(short)], par[2] = synth.tree_chain(T), short, random_tree(rng, T)
+    n, P = np.asarray([T, len(short), T], np.int32), np.asarray([0, 7, 100], np.int32)
+    for W in (T, 17, 5):
+        _tensorize_case(par, n, P, T, W)
+    ref = oracle.build_tree_mask(par, n)["dense"].reshape(-1)
+    for off in range(4):
+        flat = torch.full((3 * T * T + 8,), 9, dtype=torch.uint8, device=DEV)
+        out = dict(dense=flat[off:off + 3 * T * T].view(3, 1, T, T))
+        api.build_tree_mask(to_dev(par), to_dev(n), out=out)
+        got = bits_of(flat)
+        assert np.array_equal(got[off:off + 3 * T * T], ref) and np.all(got[:off] == 9) and np.all(got[off + 3 * T * T:] == 9)
+
+
 def test_tensorize_shapes_of_the_workloads_invalid_trees_and_worked_example():
     ex = golden("worked_example.json")
     ref = _tensorize_case(np.asarray([ex["parent"]], dtype=np.int32), [7], [100], 4, 4)
