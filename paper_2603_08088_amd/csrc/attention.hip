@@ -71,20 +71,6 @@ __device__ __forceinline__ size_t tree_row_offset(const AttnParams &p, int b, in
     return (((size_t)b * p.T_max + j) * p.Hkv + kvh) * (size_t)p.d;
 }
 
-// x / d and x % d with inv = floor(2^32 / d), or one less: the estimate is at most one too small for any 32-bit x.  (The compiler's
-// general division is some forty dependent instructions, each 3.5 ns of a lone wavefront's start-up.)
-__device__ __forceinline__ uint32_t fast_div(uint32_t x, uint32_t d, uint32_t inv, uint32_t &rem) {
-    uint32_t q = __umulhi(x, inv);
-    rem = x - q * d;
-    if (rem >= d) {
-        q++;
-        rem -= d;
-    }
-    return q;
-}
-
-static uint32_t fast_div_inv(int d) { return d == 1 ? 0xffffffffu : (uint32_t)((1ull << 32) / (uint32_t)d); }
-
 __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) v = fmaxf(v, __shfl_xor(v, off));
@@ -95,22 +81,6 @@ __device__ __forceinline__ float wave_sum(float v) {
     for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
     return v;
 }
-
-// Inclusive sums / maxima (of values that are not negative) over the lanes before and with each, by lane moves of the vector unit:
-// six dependent instructions, where a shuffle through LDS costs some 100 cycles a step.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ int lane_move(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xf, false); }
-template <class F>
-__device__ __forceinline__ int wave_scan(int v, F f) {
-    v = f(v, lane_move<0x111, 0xf>(v));  // the neighbours 1, 2, 4, 8 lanes down within the 16 of a row
-    v = f(v, lane_move<0x112, 0xf>(v));
-    v = f(v, lane_move<0x114, 0xf>(v));
-    v = f(v, lane_move<0x118, 0xf>(v));
-    v = f(v, lane_move<0x142, 0xa>(v));  // the last lane of row 0 / 2 to row 1 / 3
-    return f(v, lane_move<0x143, 0xc>(v));  // lane 31 to rows 2 and 3
-}
-__device__ __forceinline__ int wave_scan_sum(int v) { return wave_scan(v, [](int a, int b) { return a + b; }); }
-__device__ __forceinline__ int wave_scan_max(int v) { return wave_scan(v, [](int a, int b) { return max(a, b); }); }
 
 // Balanced splits.  With one split size for the whole batch a ragged batch leaves the split slots of its short
 // sequences empty while the workgroups of its longest sequence decide the launch time.  Here the launch's

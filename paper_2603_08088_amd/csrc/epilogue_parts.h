@@ -47,23 +47,55 @@ __device__ __forceinline__ MaxIdx better(MaxIdx a, MaxIdx b) {
 
 constexpr int kChunk = 4096;  // floats of one logit row scanned by one workgroup (16 KiB)
 
+// A path table of at most this many entries is copied to LDS (16 KiB) before it is walked.
+constexpr int kPathEntries = 4096;
+
 // Acceptance for sequence b by one workgroup of 256 threads (thread t): finish the argmax from the per-chunk
 // partials (or, with pval == nullptr, take argmax[] as given), walk every path with guarded compares, reduce to the best path (longest, lowest index on ties),
 // write argmax / len / best / accept_len / acc_nodes / bonus (unless write_out is false: a workgroup that only
 // needs the result for itself).  Leaves the accepted length in *s_A and the accepted node row (W entries) in
-// s_acc (both in LDS, valid after the call for every thread).
+// s_acc (both in LDS, valid after the call for every thread).  n_raw: the node count as given.
 // Section 2.3 / 5.1: greedy acceptance of the longest root-to-leaf prefix.
+//
+// Latency is all there is to it.  Up to eight partials of a node, its token and the path table are asked for together with the
+// node count (what lies behind the last node is read and dropped), without a branch, behind which the compiler would wait;
+// ahead(): what else the caller wants on its way by then.  The walk, whose every step depends on the one before, stays in LDS.
+template <class F>
 __device__ __forceinline__ void posterior_for_sequence(
     int b, int t, const float *__restrict__ pval, const int32_t *__restrict__ pidx, int chunks,
-    const int32_t *__restrict__ tokens, const int32_t *__restrict__ retrieve, int n, int T_max, int L_max, int W,
+    const int32_t *__restrict__ tokens, const int32_t *__restrict__ retrieve, int n_raw, int T_max, int L_max, int W,
     int dummy, int32_t *__restrict__ argmax, int32_t *__restrict__ len, int32_t *__restrict__ best,
     int32_t *__restrict__ accept_len, int32_t *__restrict__ acc_nodes, int32_t *__restrict__ bonus, int32_t *s_A,
-    int32_t *s_acc, bool write_out = true) {
+    int32_t *s_acc, bool write_out, F &&ahead) {
     __shared__ int32_t s_g[ETV_MAX_TREE];
     __shared__ int32_t s_tok[ETV_MAX_TREE];
-    __shared__ int32_t s_len[256];
-    __shared__ int32_t s_path[256];
-    if (pval && chunks > 16) {
+    __shared__ int32_t s_len[4];
+    __shared__ int32_t s_path[4];
+    __shared__ int32_t s_table[kPathEntries];
+    static_assert(ETV_MAX_TREE <= 256, "one node per thread");
+    constexpr int E = 4, C = 8;  // loads in flight: path entries (E * 256 cover most tables), chunks of a node
+    const bool few = pval && chunks <= 16;
+    const int32_t *const table = retrieve + (size_t)b * L_max * W;
+    const bool staged = (long)L_max * W <= kPathEntries;
+    const int entries = staged ? L_max * W : 0;
+    const uint32_t row = (uint32_t)b * (uint32_t)T_max + (uint32_t)min(t, T_max - 1);  // B is below 2^16
+    // the choice per node: its partials, or as given (etv_lm_head_argmax), or (many partials) worked out below
+    const float *const pv = few ? pval : reinterpret_cast<const float *>(tokens);
+    const int32_t *const pi = few ? pidx : (pval ? tokens : argmax);
+    const uint32_t at = few ? row * (uint32_t)chunks : row;
+    MaxIdx x[C];
+#pragma unroll
+    for (int u = 0; u < C; u++) {
+        const int c = few ? min(u, chunks - 1) : 0;  // past the end the last one again, which changes nothing
+        x[u] = {(pv + c)[at], (pi + c)[at]};
+    }
+    const int32_t tok = tokens[row];
+    int32_t ent[E];
+#pragma unroll
+    for (int e = 0; e < E; e++) ent[e] = table[(uint32_t)(staged ? min(t + 256 * e, entries - 1) : 0)];
+    ahead();
+    const int n = clampi(n_raw, 0, T_max);
+    if (pval && !few) {
         // many partials per node (the per-tile maxima of the fused head) and few nodes: one wavefront per node, lanes
         // stride over the partials, shuffle reduce
         const int lane = t & 63;
@@ -71,84 +103,107 @@ __device__ __forceinline__ void posterior_for_sequence(
             MaxIdx m = {-INFINITY, 0x7fffffff};
             if (node < n) {
                 const size_t o = ((size_t)b * T_max + node) * chunks;
-                for (int c = lane; c < chunks; c += 64) m = better(m, MaxIdx{pval[o + c], pidx[o + c]});
+                for (int c0 = lane; c0 < chunks; c0 += 64 * E) {
+                    MaxIdx y[E];
+#pragma unroll
+                    for (int u = 0; u < E; u++) {
+                        const int c = min(c0 + 64 * u, chunks - 1);  // past the end the last one again
+                        y[u] = {pval[o + c], pidx[o + c]};
+                    }
+#pragma unroll
+                    for (int u = 0; u < E; u++) m = better(m, y[u]);
+                }
 #pragma unroll
                 for (int off = 32; off >= 1; off >>= 1) m = better(m, MaxIdx{__shfl_xor(m.v, off), __shfl_xor(m.i, off)});
             }
             if (lane == 0) {
                 const int32_t g = node < n ? m.i : -1;
                 s_g[node] = g;
-                s_tok[node] = tokens[(size_t)b * T_max + node];
                 if (write_out) argmax[(size_t)b * T_max + node] = g;
             }
         }
     } else {
-        for (int node = t; node < T_max; node += 256) {
-            int32_t g = -1;
-            if (node < n) {
-                if (pval) {
-                    size_t o = ((size_t)b * T_max + node) * chunks;
-                    MaxIdx m = {pval[o], pidx[o]};
-                    for (int c = 1; c < chunks; c++) m = better(m, MaxIdx{pval[o + c], pidx[o + c]});
-                    g = m.i;
-                } else {  // the caller already has the teacher's choice per node (etv_lm_head_argmax)
-                    g = argmax[(size_t)b * T_max + node];
-                }
-            }
-            s_g[node] = g;
-            s_tok[node] = tokens[(size_t)b * T_max + node];
-            if (pval && write_out) argmax[(size_t)b * T_max + node] = g;
+        MaxIdx m = x[0];
+#pragma unroll
+        for (int u = 1; u < C; u++) m = better(m, x[u]);
+        if (few)
+            for (int c = C; c < chunks; c++) m = better(m, MaxIdx{(pv + c)[at], (pi + c)[at]});
+        const int32_t g = t < n ? m.i : -1;
+        if (t < T_max) {
+            s_g[t] = g;
+            if (few && write_out) argmax[row] = g;
         }
+    }
+    if (t < T_max) s_tok[t] = tok;
+    if (staged) {
+#pragma unroll
+        for (int e = 0; e < E; e++)
+            if (t + 256 * e < entries) s_table[t + 256 * e] = ent[e];
+        for (int e = t + 256 * E; e < entries; e += 256) s_table[e] = table[e];
     }
     __syncthreads();
     int my_len = -1, my_path = 0x7fffffff;
-    for (int p = t; p < L_max; p += 256) {
-        const int32_t *path = retrieve + ((size_t)b * L_max + p) * W;
-        int cnt = 0;
-        int32_t a = path[0];
-        for (int i = 0; i + 1 < W; i++) {
-            int32_t c = path[i + 1];
-            bool va = (a >= 0 && a < n), vc = (c >= 0 && c < n);
-            int32_t sa = safe_index(a, T_max, dummy), sc = safe_index(c, T_max, dummy);
-            if (!(va && vc && s_tok[sc] == s_g[sa])) break;
-            cnt++;
-            a = c;
-        }
-        if (write_out) len[(size_t)b * L_max + p] = cnt;
-        if (cnt > my_len) {  // ascending p per thread: strict '>' keeps the lowest path
-            my_len = cnt;
-            my_path = p;
-        }
-    }
-    s_len[t] = my_len;
-    s_path[t] = my_path;
-    __syncthreads();
-    for (int off = 128; off >= 1; off >>= 1) {
-        if (t < off) {
-            int l2 = s_len[t + off], p2 = s_path[t + off];
-            if (l2 > s_len[t] || (l2 == s_len[t] && p2 < s_path[t])) {
-                s_len[t] = l2;
-                s_path[t] = p2;
+    const auto walk = [&](const int32_t *paths) {
+        for (int p = t; p < L_max; p += 256) {
+            const int32_t *path = paths + (size_t)p * W;
+            int cnt = 0;
+            int32_t a = path[0];
+            for (int i = 0; i + 1 < W; i++) {
+                int32_t c = path[i + 1];
+                bool va = (a >= 0 && a < n), vc = (c >= 0 && c < n);
+                int32_t sa = safe_index(a, T_max, dummy), sc = safe_index(c, T_max, dummy);
+                if (!(va && vc && s_tok[sc] == s_g[sa])) break;
+                cnt++;
+                a = c;
+            }
+            if (write_out) len[(size_t)b * L_max + p] = cnt;
+            if (cnt > my_len) {  // ascending p per thread: strict '>' keeps the lowest path
+                my_len = cnt;
+                my_path = p;
             }
         }
-        __syncthreads();
+    };
+    if (staged) walk(s_table);
+    else walk(table);
+    // the longest, and of these the lowest: of the wavefront, then of the four
+    const auto last = [](int v) { return __builtin_amdgcn_readlane(v, 63); };
+    const auto best_of = [&](int &l, int &p) {
+        const int top = last(wave_scan_max(l + 1)) - 1;
+        p = 0x7fffffff - last(wave_scan_max(l == top ? 0x7fffffff - p : 0));
+        l = top;
+    };
+    best_of(my_len, my_path);
+    if ((t & 63) == 0) {
+        s_len[t >> 6] = my_len;
+        s_path[t >> 6] = my_path;
     }
-    const int A = s_len[0], bp = s_path[0];
-    const int32_t *path = retrieve + ((size_t)b * L_max + bp) * W;
-    for (int i = t; i < W; i += 256) {
-        const int32_t nd = (i <= A) ? safe_index(path[i], T_max, dummy) : dummy;
-        if (write_out) acc_nodes[(size_t)b * W + i] = nd;
-        if (s_acc) s_acc[i] = nd;
-    }
-    if (t == 0) {
-        if (write_out) {
-            best[b] = bp;
-            accept_len[b] = A;
-            int32_t last = safe_index(path[A], T_max, dummy);
-            bonus[b] = s_g[last];
+    __syncthreads();
+    int A = s_len[0], bp = s_path[0];
+#pragma unroll
+    for (int w = 1; w < 4; w++)
+        if (s_len[w] > A || (s_len[w] == A && s_path[w] < bp)) {
+            A = s_len[w];
+            bp = s_path[w];
         }
-        if (s_A) *s_A = A;
-    }
+    const auto take = [&](const int32_t *paths) {
+        const int32_t *path = paths + (size_t)bp * W;
+        for (int i = t; i < W; i += 256) {
+            const int32_t nd = (i <= A) ? safe_index(path[i], T_max, dummy) : dummy;
+            if (write_out) acc_nodes[(size_t)b * W + i] = nd;
+            if (s_acc) s_acc[i] = nd;
+        }
+        if (t == 0) {
+            if (write_out) {
+                best[b] = bp;
+                accept_len[b] = A;
+                int32_t last_node = safe_index(path[A], T_max, dummy);
+                bonus[b] = s_g[last_node];
+            }
+            if (s_A) *s_A = A;
+        }
+    };
+    if (staged) take(s_table);
+    else take(table);
     __syncthreads();
 }
 
@@ -203,17 +258,33 @@ __device__ __forceinline__ void commit_plan_for_sequence(const etv_commit_desc &
     *prefix_len_out_b = st ? P : P + A + 1;
 }
 
-// The same plan computed by a whole workgroup (thread t of nthreads, all of them call it): one position per thread
-// instead of one thread walking all of them, because every position costs a dependent trip to the block table and
-// a single thread pays those one after the other.  The checks are those of commit_plan_for_sequence in an order
+// The logical block of position P + t, one position per thread, and what the table says about it: asked for as soon as P is known,
+// long before the accepted length is.  inv_bs: of fast_div for the block size.
+struct PlannedBlock {
+    bool in_table;
+    int32_t id, at;  // physical block, position within it
+};
+__device__ __forceinline__ PlannedBlock planned_block(const etv_commit_desc &dsc, uint32_t inv_bs, int b, const int32_t *__restrict__ block_table,
+                                                      const int32_t *__restrict__ other, int P, int t) {
+    const bool paged = dsc.block_size > 0;
+    uint32_t at;
+    const uint32_t lb = fast_div((uint32_t)max(P, 0) + (uint32_t)t, (uint32_t)max(dsc.block_size, 1), inv_bs, at);
+    const uint32_t end = (uint32_t)max(dsc.max_blocks, 1);
+    // a contiguous cache has no table: any word that may be read, without a branch
+    const int32_t id = (paged ? block_table + (size_t)b * dsc.max_blocks : other)[paged ? min(lb, end - 1) : 0];
+    return {lb < end, id, (int32_t)at};
+}
+
+// The same plan computed by a whole workgroup of 256 threads (thread t, all of them call it; W and the node count are at most 256): one
+// position per thread instead of one thread walking all of them.  The checks are those of commit_plan_for_sequence in an order
 // that does not matter: a position whose logical block lies behind the table row sets CAPACITY and skips the block
 // check, exactly the positions the sequential walk never reaches.  s_status: one word of LDS; the results are in
-// slot_row / *status_b / *prefix_len_out_b after the call's last barrier.
-__device__ __forceinline__ void commit_plan_cooperative(const etv_commit_desc &dsc, int b,
-                                                        const int32_t *__restrict__ block_table, int P, int cap, int n,
+// slot_row / *status_b / *prefix_len_out_b after the call's last barrier, and in row_at where the appended rows are in the cache:
+// head hh of position i at (row_at[i] + hh * (block size, or 1 in a contiguous cache)) * the bytes of a head.
+__device__ __forceinline__ void commit_plan_cooperative(const etv_commit_desc &dsc, int b, PlannedBlock blk, int P, int cap, int n,
                                                         const int32_t *acc_row, int A, int32_t *prefix_len_out_b,
-                                                        int32_t *slot_row, int32_t *status_b, bool in_place, int t,
-                                                        int nthreads, int32_t *s_status) {
+                                                        int32_t *slot_row, uint64_t *row_at, int32_t *status_b, bool in_place, int t,
+                                                        int32_t *s_status) {
     const int W = dsc.W;
     const bool bad_len = (A < 0 || A > W - 1);
     int32_t pre = bad_len ? ETV_COMMIT_BAD_LEN : 0;
@@ -225,22 +296,17 @@ __device__ __forceinline__ void commit_plan_cooperative(const etv_commit_desc &d
     __syncthreads();
     if (!bad_len) {
         int32_t mine = 0;
-        for (int i = t; i <= A; i += nthreads) {
-            const int32_t nd = acc_row[i];
+        if (t <= A) {
+            const int32_t nd = acc_row[t];
             if (nd < 0 || nd >= n) mine |= ETV_COMMIT_BAD_NODE;
-            if (in_place && i > 0 && nd <= acc_row[i - 1]) mine |= ETV_COMMIT_BAD_NODE;
+            if (in_place && t > 0 && nd <= acc_row[t - 1]) mine |= ETV_COMMIT_BAD_NODE;
         }
         const int reach = in_place ? max(n, A + 1) : A + 1;
         if (!(pre & ETV_COMMIT_CAPACITY)) {
             if (dsc.block_size > 0) {
-                for (int i = t; i < reach; i += nthreads) {
-                    const int lb = (P + i) / dsc.block_size;
-                    if (lb >= dsc.max_blocks) {
-                        mine |= ETV_COMMIT_CAPACITY;
-                    } else {
-                        const int blk = block_table[(size_t)b * dsc.max_blocks + lb];
-                        if (blk < 0 || blk >= dsc.num_blocks) mine |= ETV_COMMIT_BAD_BLOCK;
-                    }
+                if (t < reach) {
+                    if (!blk.in_table) mine |= ETV_COMMIT_CAPACITY;
+                    else if (blk.id < 0 || blk.id >= dsc.num_blocks) mine |= ETV_COMMIT_BAD_BLOCK;
                 }
             } else if (t == 0 && (long)P + reach > (long)dsc.P_cap) {
                 mine |= ETV_COMMIT_CAPACITY;
@@ -250,15 +316,10 @@ __device__ __forceinline__ void commit_plan_cooperative(const etv_commit_desc &d
     }
     __syncthreads();
     const int32_t st = *s_status;
-    for (int i = t; i < W; i += nthreads) {
-        int32_t slot = -1;
-        if (!st && i <= A) {
-            const int pos = P + i;
-            slot = dsc.block_size > 0 ? block_table[(size_t)b * dsc.max_blocks + pos / dsc.block_size] * dsc.block_size +
-                                            pos % dsc.block_size
-                                      : pos;
-        }
-        slot_row[i] = slot;
+    const bool paged = dsc.block_size > 0;
+    if (t < W) {
+        slot_row[t] = st || t > A ? -1 : (paged ? blk.id * dsc.block_size + blk.at : P + t);
+        row_at[t] = paged ? (uint64_t)(uint32_t)blk.id * dsc.Hkv * dsc.block_size + blk.at : ((uint64_t)b * dsc.P_cap + P + t) * dsc.Hkv;
     }
     if (t == 0) {
         *status_b = st;
@@ -293,6 +354,33 @@ __device__ __forceinline__ void commit_copy_unit(const etv_commit_desc &dsc, int
     const uint8_t *src = (is_v ? vt : kt) + src_off + (size_t)uu * 16;
     uint8_t *dst = (is_v ? v_cache : k_cache) + layer_off + cache_unit_offset(dsc, b, slot, hh, part);
     *reinterpret_cast<uint4 *>(dst) = *reinterpret_cast<const uint4 *>(src);
+}
+
+// The accepted rows 0 .. A of one layer by the threads t, t + nthreads, ...: a thread keeps its 16-byte column of the [K row | V row] pair
+// and moves it for all rows, eight loads in flight.  acc / row_at: in LDS, of the plan.  inv_units: of fast_div for the 16-byte units of a head.
+__device__ __forceinline__ void commit_copy_layer(const etv_commit_desc &dsc, uint32_t inv_units, int b, int l, int A, const int32_t *acc,
+                                                  const uint64_t *row_at, const uint8_t *__restrict__ kt, const uint8_t *__restrict__ vt,
+                                                  uint8_t *__restrict__ k_cache, uint8_t *__restrict__ v_cache, int t, int nthreads) {
+    constexpr int R = 8;
+    const uint32_t head_bytes = (uint32_t)dsc.d * (uint32_t)dsc.elem_bytes, units_per_head = head_bytes / 16, units = units_per_head * (uint32_t)dsc.Hkv;
+    const size_t src_off = ((size_t)l * dsc.B + b) * dsc.T_max * (size_t)units * 16;
+    const size_t layer_off = (size_t)l * (size_t)dsc.cache_layer_stride * dsc.elem_bytes;
+    for (uint32_t u = (uint32_t)t; u < 2 * units; u += (uint32_t)nthreads) {
+        const bool is_v = u >= units;
+        const uint32_t uu = is_v ? u - units : u;
+        uint32_t part;
+        const uint32_t hh = fast_div(uu, units_per_head, inv_units, part);
+        const uint8_t *const src = (is_v ? vt : kt) + src_off + (size_t)uu * 16;
+        uint8_t *const dst = (is_v ? v_cache : k_cache) + layer_off + (size_t)(hh * (uint32_t)max(dsc.block_size, 1)) * head_bytes + part * 16;
+        for (int i0 = 0; i0 <= A; i0 += R) {
+            uint4 val[R];
+#pragma unroll
+            for (int j = 0; j < R; j++) val[j] = *reinterpret_cast<const uint4 *>(src + (size_t)acc[min(i0 + j, A)] * ((size_t)units * 16));
+#pragma unroll
+            for (int j = 0; j < R; j++)
+                if (i0 + j <= A) *reinterpret_cast<uint4 *>(dst + row_at[i0 + j] * head_bytes) = val[j];
+        }
+    }
 }
 
 // In-place branch cache, one layer of one sequence by the threads t, t + nthreads, ...: the accepted rows move

@@ -31,4 +31,34 @@ __device__ __forceinline__ uint16_t float_to_bf16_bits(float f) {
 
 __device__ __forceinline__ int clampi(int x, int lo, int hi) { return x < lo ? lo : (x > hi ? hi : x); }
 
+// x / d and x % d with inv = floor(2^32 / d), or one less: the estimate is at most one too small for any 32-bit x.  (The compiler's
+// general division is some forty dependent instructions, each 3.5 ns of a lone wavefront's start-up.)
+__device__ __forceinline__ uint32_t fast_div(uint32_t x, uint32_t d, uint32_t inv, uint32_t &rem) {
+    uint32_t q = __umulhi(x, inv);
+    rem = x - q * d;
+    if (rem >= d) {
+        q++;
+        rem -= d;
+    }
+    return q;
+}
+
+static uint32_t fast_div_inv(int d) { return d == 1 ? 0xffffffffu : (uint32_t)((1ull << 32) / (uint32_t)d); }
+
+// Inclusive sums / maxima (of values that are not negative) over the lanes before and with each, by lane moves of the vector unit:
+// six dependent instructions, where a shuffle through LDS costs some 100 cycles a step.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int lane_move(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xf, false); }
+template <class F>
+__device__ __forceinline__ int wave_scan(int v, F f) {
+    v = f(v, lane_move<0x111, 0xf>(v));  // the neighbours 1, 2, 4, 8 lanes down within the 16 of a row
+    v = f(v, lane_move<0x112, 0xf>(v));
+    v = f(v, lane_move<0x114, 0xf>(v));
+    v = f(v, lane_move<0x118, 0xf>(v));
+    v = f(v, lane_move<0x142, 0xa>(v));  // the last lane of row 0 / 2 to row 1 / 3
+    return f(v, lane_move<0x143, 0xc>(v));  // lane 31 to rows 2 and 3
+}
+__device__ __forceinline__ int wave_scan_sum(int v) { return wave_scan(v, [](int a, int b) { return a + b; }); }
+__device__ __forceinline__ int wave_scan_max(int v) { return wave_scan(v, [](int a, int b) { return max(a, b); }); }
+
 }  // namespace etv

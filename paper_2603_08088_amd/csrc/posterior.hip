@@ -81,8 +81,8 @@ __global__ void __launch_bounds__(256) posterior_paths_kernel(
     int32_t *__restrict__ best, int32_t *__restrict__ accept_len, int32_t *__restrict__ acc_nodes,
     int32_t *__restrict__ bonus) {
     const int b = blockIdx.x;
-    posterior_for_sequence(b, threadIdx.x, pval, pidx, chunks, tokens, retrieve, clampi(n_nodes[b], 0, T_max), T_max,
-                           L_max, W, dummy, argmax, len, best, accept_len, acc_nodes, bonus, nullptr, nullptr);
+    posterior_for_sequence(b, threadIdx.x, pval, pidx, chunks, tokens, retrieve, n_nodes[b], T_max, L_max,
+                           W, dummy, argmax, len, best, accept_len, acc_nodes, bonus, nullptr, nullptr, true, [] {});
 }
 
 // Fused epilogue: gather, acceptance and commit in ONE launch.
@@ -92,40 +92,62 @@ __global__ void __launch_bounds__(256) posterior_paths_kernel(
 // accepted K/V rows of its own layers (g, g + G, ...).  Recomputing the small acceptance G times costs less than
 // any way of handing its result to other workgroups of the same launch (a flag in memory would cost each waiter
 // a device-scope round trip and the launch a scratch word that has to start at zero), and no workgroup ever
-// waits for another.  Workgroups B*G ..: the safe gather, four path entries each (it depends on the path table
-// only, so it runs beside the acceptance instead of before it).
+// waits for another.  Workgroups B*G ..: the safe gather (it depends on the path table only, so it runs beside the acceptance
+// instead of before it), per workgroup four path entries with a row each, or 256 where a row is a few words at most.
+//
+// What bounds it are the trips to memory in series: sizes, partials, tokens and paths; block ids; the rows.  With the launch that
+// finds the partials, in graphs, V = 32000: B = 1, T = 60, 32 layers 9.3 -> 8.3 us; B = 8, T = 60, 4 layers, from the head's partials
+// 10.1 -> 8.7; B = 32, T = 128, 2 layers 86.0 -> 81.6 (74 of it logits).
 __global__ void __launch_bounds__(256) verify_epilogue_kernel(
-    etv_commit_desc dsc, int G, const float *__restrict__ pval, const int32_t *__restrict__ pidx, int chunks,
-    const int32_t *__restrict__ tokens, const int32_t *__restrict__ retrieve, const int32_t *__restrict__ n_nodes,
+    const int32_t *__restrict__ n_nodes, const int32_t *__restrict__ prefix_len, const int32_t *__restrict__ capacity,
+    const int32_t *__restrict__ tokens, const int32_t *__restrict__ retrieve, const float *__restrict__ pval,
+    const int32_t *__restrict__ pidx, etv_commit_desc dsc, int G, uint32_t inv_g, uint32_t inv_bs, uint32_t inv_units, int chunks,
     int L_max, int dummy, const uint8_t *__restrict__ src, size_t row_bytes, int32_t *__restrict__ safe,
     uint8_t *__restrict__ pvalid, uint8_t *__restrict__ gathered, int32_t *__restrict__ argmax,
     int32_t *__restrict__ len, int32_t *__restrict__ best, int32_t *__restrict__ accept_len,
     int32_t *__restrict__ acc_nodes, int32_t *__restrict__ bonus, const uint8_t *__restrict__ kt,
     const uint8_t *__restrict__ vt, uint8_t *__restrict__ k_cache, uint8_t *__restrict__ v_cache,
-    const int32_t *__restrict__ block_table, const int32_t *__restrict__ prefix_len,
-    const int32_t *__restrict__ capacity, int32_t *__restrict__ prefix_len_out, int32_t *__restrict__ slot_map,
-    int32_t *__restrict__ status, int in_place) {
+    const int32_t *__restrict__ block_table, int32_t *__restrict__ prefix_len_out, int32_t *__restrict__ slot_map,
+    int32_t *__restrict__ status, int in_place, int per_thread) {
     __shared__ int32_t s_A, s_st, s_plo, s_coop;
     __shared__ int32_t s_acc[ETV_MAX_TREE];
     __shared__ int32_t s_slot[ETV_MAX_TREE];
+    __shared__ uint64_t s_at[ETV_MAX_TREE];
     const int t = threadIdx.x;
     const int T_max = dsc.T_max, W = dsc.W;
     if ((long)blockIdx.x >= (long)dsc.B * G) {  // uniform over the workgroup
-        const long per_seq = (long)L_max * W;
-        const long e = ((long)blockIdx.x - (long)dsc.B * G) * 4 + (t >> 6);
-        if (e >= per_seq * dsc.B) return;
-        const int b = (int)(e / per_seq);
-        gather_entry(e, b, t & 63, retrieve, clampi(n_nodes[b], 0, T_max), T_max, dummy, src, row_bytes, safe, pvalid,
-                     gathered);
+        const long per_seq = (long)L_max * W, total = per_seq * dsc.B;
+        const long wg = (long)blockIdx.x - (long)dsc.B * G;
+        const long e = per_thread ? wg * 256 + t : wg * 4 + (t >> 6);
+        if (e >= total) return;
+        const int b = total <= 0x7fffffffL ? (int)((uint32_t)e / (uint32_t)per_seq) : (int)(e / per_seq);
+        if (!per_thread) {
+            gather_entry(e, b, t & 63, retrieve, clampi(n_nodes[b], 0, T_max), T_max, dummy, src, row_bytes, safe, pvalid, gathered);
+            return;
+        }
+        const int32_t idx = retrieve[e], n_raw = n_nodes[b], s = safe_index(idx, T_max, dummy);
+        if (src && gathered) {
+            const uint32_t words = (uint32_t)row_bytes >> 2;
+            const uint32_t *from = reinterpret_cast<const uint32_t *>(src) + ((size_t)b * T_max + s) * words;
+            uint32_t *to = reinterpret_cast<uint32_t *>(gathered) + (size_t)e * words;
+            for (uint32_t o = 0; o < words; o++) to[o] = from[o];
+        }
+        if (safe) safe[e] = s;
+        if (pvalid) pvalid[e] = (uint8_t)(idx >= 0 && idx < clampi(n_raw, 0, T_max));
         return;
     }
-    const int b = blockIdx.x / G, g = blockIdx.x % G;
-    const int n = clampi(n_nodes[b], 0, T_max);
+    // the arguments in one trip
+    asm volatile("" ::"s"(G), "s"(inv_g), "s"(inv_bs), "s"(inv_units), "s"(chunks), "s"(L_max), "s"(dummy), "s"(argmax), "s"(len), "s"(best),
+                 "s"(accept_len), "s"(acc_nodes), "s"(bonus), "s"(kt), "s"(vt), "s"(k_cache), "s"(v_cache), "s"(block_table), "s"(slot_map));
+    uint32_t g_;
+    const int b = (int)fast_div(blockIdx.x, (uint32_t)G, inv_g, g_), g = (int)g_;
+    const int n_raw = n_nodes[b], cap = capacity[b];
     const int P = prefix_len[b];  // read before group 0 can have written anything (prefix_len_out is another buffer)
-    posterior_for_sequence(b, t, pval, pidx, chunks, tokens, retrieve, n, T_max, L_max, W, dummy, argmax, len, best,
-                           accept_len, acc_nodes, bonus, &s_A, s_acc, g == 0);
-    commit_plan_cooperative(dsc, b, block_table, P, capacity[b], n, s_acc, s_A, &s_plo, s_slot, &s_st, in_place != 0, t, 256,
-                            &s_coop);
+    PlannedBlock blk;
+    posterior_for_sequence(b, t, pval, pidx, chunks, tokens, retrieve, n_raw, T_max, L_max, W, dummy, argmax, len, best,
+                           accept_len, acc_nodes, bonus, &s_A, s_acc, g == 0,
+                           [&] { blk = planned_block(dsc, inv_bs, b, block_table, tokens, P, t); });
+    commit_plan_cooperative(dsc, b, blk, P, cap, clampi(n_raw, 0, T_max), s_acc, s_A, &s_plo, s_slot, s_at, &s_st, in_place != 0, t, &s_coop);
     if (g == 0) {
         for (int i = t; i < W; i += 256) slot_map[(size_t)b * W + i] = s_slot[i];
         if (t == 0) {
@@ -135,17 +157,9 @@ __global__ void __launch_bounds__(256) verify_epilogue_kernel(
     }
     if (s_st) return;  // refused: the sequence stays untouched
     const int A = s_A;
-    if (in_place) {
-        for (int l = g; l < dsc.n_layers; l += G)
-            commit_compact_layer(dsc, b, l, P, A, s_acc, s_slot, block_table, k_cache, v_cache, t, 256);
-    } else {
-        const int units2 = 2 * (int)((size_t)dsc.d * dsc.elem_bytes / 16) * dsc.Hkv;
-        const int total = (A + 1) * units2;
-        for (int l = g; l < dsc.n_layers; l += G)
-            for (int idx = t; idx < total; idx += 256) {
-                const int i = idx / units2;
-                commit_copy_unit(dsc, b, l, s_acc[i], s_slot[i], idx - i * units2, kt, vt, k_cache, v_cache);
-            }
+    for (int l = g; l < dsc.n_layers; l += G) {
+        if (in_place) commit_compact_layer(dsc, b, l, P, A, s_acc, s_slot, block_table, k_cache, v_cache, t, 256);
+        else commit_copy_layer(dsc, inv_units, b, l, A, s_acc, s_at, kt, vt, k_cache, v_cache, t, 256);
     }
 }
 
@@ -277,16 +291,20 @@ extern "C" int32_t etv_verify_epilogue(const etv_commit_desc *h, const float *lo
     }
     rc = etv::finish_partials_first(pval, pidx, chunks, n_nodes, B, T_max, argmax, s);
     if (rc != ETV_OK) return rc;
-    const long gather_blocks = (safe || pvalid || gathered) ? ((long)B * L_max * h->W + 3) / 4 : 0;
+    const long gather_entries = (safe || pvalid || gathered) ? (long)B * L_max * h->W : 0;
     // layer groups per sequence: enough workgroups to spread the row copies over the chip, at most one per layer
     const int G = std::max(1, std::min((int)h->n_layers, 512 / B));
-    if (gather_blocks + (long)B * G > 0x7fffffffL) return ETV_ERR_UNSUPPORTED;
-    hipLaunchKernelGGL(etv::verify_epilogue_kernel, dim3((unsigned)((long)B * G + gather_blocks)), dim3(256), 0, s, *h, G,
-                       pval, pidx, chunks, tokens, retrieve, n_nodes, (int)L_max, (int)dummy,
+    if ((gather_entries + 3) / 4 + (long)B * G > 0x7fffffffL) return ETV_ERR_UNSUPPORTED;
+    // a thread per entry where a row is up to four aligned words (tokens): 8 x 60 paths of 7 entries are 14 workgroups then, not 840
+    const bool per_thread = !src || ((row_bytes & 3) == 0 && row_bytes <= 16 && (((uintptr_t)src | (uintptr_t)gathered) & 3) == 0);
+    const long gather_blocks = per_thread ? (gather_entries + 255) / 256 : (gather_entries + 3) / 4;
+    hipLaunchKernelGGL(etv::verify_epilogue_kernel, dim3((unsigned)((long)B * G + gather_blocks)), dim3(256), 0, s, n_nodes,
+                       prefix_len, capacity, tokens, retrieve, pval, pidx, *h, G, etv::fast_div_inv(G), etv::fast_div_inv(std::max(h->block_size, 1)),
+                       etv::fast_div_inv((int)((size_t)h->d * h->elem_bytes / 16)), chunks, (int)L_max, (int)dummy,
                        static_cast<const uint8_t *>(src), row_bytes, safe, pvalid, static_cast<uint8_t *>(gathered),
                        argmax, len, best, accept_len, acc_nodes, bonus, static_cast<const uint8_t *>(kt),
                        static_cast<const uint8_t *>(vt), static_cast<uint8_t *>(k_cache),
-                       static_cast<uint8_t *>(v_cache), block_table, prefix_len, capacity, prefix_len_out, slot_map,
-                       status, in_place ? 1 : 0);
+                       static_cast<uint8_t *>(v_cache), block_table, prefix_len_out, slot_map,
+                       status, in_place ? 1 : 0, per_thread ? 1 : 0);
     return etv::check_launch();
 }

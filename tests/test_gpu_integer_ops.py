@@ -303,7 +303,7 @@ def test_probe_library_runs_and_rejects_bad_arguments():
         probe.mfma_bf16_live_probe(0, sink)
 
 
-def _epilogue_case(wl, L=2, dummy=0, spoil=None):
+def _epilogue_case(wl, L=2, dummy=0, spoil=None, src=None):
     """The fused epilogue against the oracle's gather, acceptance and commit (and so against the separate calls)."""
     rng = np.random.default_rng(77)
     kt = np.stack([wl.kt] + [synth._values(rng, wl.kt.shape, wl.dtype) for _ in range(L - 1)])
@@ -314,6 +314,8 @@ def _epilogue_case(wl, L=2, dummy=0, spoil=None):
     if spoil is not None:
         capacity[spoil] = wl.prefix_len[spoil]          # no room: that sequence must be left untouched
     tok3 = wl.tokens.reshape(wl.B, wl.T_max, 1)
+    if src is not None:
+        tok3 = src
     rg = oracle.safe_gather_paths(wl.retrieve, wl.n_nodes, wl.T_max, dummy, tok3)
     rp = oracle.evaluate_posterior(wl.logits, wl.tokens, wl.retrieve, wl.n_nodes, dummy)
     okc, ovc = kc.copy(), vc.copy()
@@ -322,8 +324,7 @@ def _epilogue_case(wl, L=2, dummy=0, spoil=None):
     d = DevWorkload(wl)
     dkc, dvc = to_dev(kc), to_dev(vc)
     g, p, c = api.verify_epilogue(d.logits, d.tokens, d.retrieve, d.n_nodes, to_dev(kt), to_dev(vt), dkc, dvc,
-                                  d.prefix_len, to_dev(capacity), block_table=d.block_table, dummy=dummy,
-                                  src=d.tokens.reshape(wl.B, wl.T_max, 1))
+                                  d.prefix_len, to_dev(capacity), block_table=d.block_table, dummy=dummy, src=to_dev(tok3))
     torch.cuda.synchronize()
     for key in ("safe", "pvalid", "gathered"):
         assert np.array_equal(bits_of(g[key]), rg[key]), key
@@ -345,6 +346,16 @@ def test_fused_epilogue_matches_gather_acceptance_and_commit():
     assert rc["status"][2] != 0 and np.all(np.delete(rc["status"], 2) == 0)
     assert len(set(rp["accept_len"].tolist())) > 1
     _epilogue_case(synth.config5(16, 4, B=6, P=200), dummy=3)               # padding-heavy path table, dummy != 0
+
+
+@pytest.mark.parametrize("V,T,W,row", [(4096, 15, 5, 1), (32768, 33, 9, 4), (32772, 60, 6, 5), (65536, 12, 4, 2), (65540, 13, 4, 3),
+                                       (300, 210, 20, 4), (300, 256, 16, 1)])
+def test_fused_epilogue_at_the_edges_of_its_forms(V, T, W, row):
+    """1, 8, 9, 16 and 17 partials a node; path tables that LDS holds and one that it does not; gathered rows of one to five words."""
+    rng = np.random.default_rng(V + T)
+    parents = [synth.tree_star(T) if T > 200 else synth.tree_bfs(rng, T, W - 1, 4), synth.tree_bfs(rng, T - 3, W - 1, 4)]
+    wl = synth.assemble("forms", rng, parents, [37, 16], Hq=2, Hkv=2, d=64, dtype="f32", V=V, W=W, paged=T != 33, T_max=T, spare_blocks=3)
+    _epilogue_case(wl, L=3, src=rng.integers(0, 1 << 30, size=(2, T, row)).astype(np.int32))
 
 
 @pytest.mark.parametrize("paged", [False, True])
