@@ -153,6 +153,10 @@ def _dtype_code(t: torch.Tensor) -> int:
     raise EtvError("dtype", -2)
 
 
+def _i32(shape, dev) -> torch.Tensor:
+    return torch.empty(shape, dtype=torch.int32, device=dev)
+
+
 # ------------------------------------------------------------------------------------------------
 def build_tree_mask(parent: torch.Tensor, n_nodes: torch.Tensor, *, want_dense: bool = True,
                     want_depth: bool = True, out: Optional[Dict[str, torch.Tensor]] = None):
@@ -180,18 +184,23 @@ def tensorize_tree(parent: torch.Tensor, n_nodes: torch.Tensor, prefix_len: torc
     """parent int32 [B,T_max], n_nodes, prefix_len int32 [B] -> the outputs of build_tree_mask plus position_ids
     int32 [B,T_max], retrieve int32 [B,L_max,W] (root-to-leaf paths, -1 padded) and n_paths int32 [B]."""
     B, T = parent.shape
-    dev = parent.device
-    words = (T + 63) // 64
-    o = out or {}
-    i32 = dict(dtype=torch.int32, device=dev)
-
-    def get(name, shape, dtype=torch.int32):
-        t = o.get(name)
-        return t if t is not None else torch.empty(shape, dtype=dtype, device=dev)
-    bitmask = get("bitmask", (B, T, words), torch.int64)
-    dense = o.get("dense") if out else (torch.empty((B, 1, T, T), dtype=torch.uint8, device=dev) if want_dense else None)
-    depth, pos = get("depth", (B, T)), get("position_ids", (B, T))
-    retrieve, n_paths, status = get("retrieve", (B, L_max, W)), get("n_paths", (B,)), get("status", (B,))
+    dev, get = parent.device, (out or {}).get
+    bitmask, dense, depth, pos = get("bitmask"), get("dense"), get("depth"), get("position_ids")
+    retrieve, n_paths, status = get("retrieve"), get("n_paths"), get("status")
+    if bitmask is None:
+        bitmask = torch.empty((B, T, (T + 63) // 64), dtype=torch.int64, device=dev)
+    if not out and want_dense:
+        dense = torch.empty((B, 1, T, T), dtype=torch.uint8, device=dev)
+    if depth is None:
+        depth = _i32((B, T), dev)
+    if pos is None:
+        pos = _i32((B, T), dev)
+    if retrieve is None:
+        retrieve = _i32((B, L_max, W), dev)
+    if n_paths is None:
+        n_paths = _i32((B,), dev)
+    if status is None:
+        status = _i32((B,), dev)
     rc = _native().tensorize_tree(parent, n_nodes, prefix_len, B, T, L_max, W, bitmask, dense, depth, pos, retrieve, n_paths,
                                    status)
     _check("etv_tensorize_tree", rc)
@@ -362,7 +371,11 @@ def lm_head_argmax(hidden, weight, n_nodes, *, V: Optional[int] = None, want_max
     return dict(argmax=g, maxval=mx) if finish else dict(workspace=workspace)
 
 
-def _commit_desc(kt, k_cache, block_table, W: int, B: Optional[int] = None, T_max: Optional[int] = None) -> CommitDesc:
+def _commit_desc(kt, k_cache, block_table, W: int, B: Optional[int] = None, T_max: Optional[int] = None):
+    """The memory of a CommitDesc, from the binding where the shapes are in order."""
+    dsc = _native().commit_desc(kt, k_cache, block_table, W)
+    if dsc is not None:
+        return dsc
     if kt is not None:
         Lyr, B, T, Hkv, d = kt.shape
     else:   # in-place branch cache: shapes from the cache, B and T_max from the caller
@@ -390,24 +403,43 @@ def verify_epilogue(logits, tokens, retrieve, n_nodes, kt, vt, k_cache, v_cache,
         assert workspace is not None if V else (post_out is not None and post_out.get("argmax") is not None)
     else:
         B, T, V = logits.shape
+    # Written out: one call of a step of some 20 us, and a closure, a shape and a look-up per output took a third of it.
     _, L, W = retrieve.shape
     dev = tokens.device
-    i32 = dict(dtype=torch.int32, device=dev)
-    go, po, co = gather_out or {}, post_out or {}, commit_out or {}
-
-    def get(d, name, shape, dtype=torch.int32):
-        t = d.get(name)
-        return t if t is not None else torch.empty(shape, dtype=dtype, device=dev)
-    safe, pvalid = get(go, "safe", (B, L, W)), get(go, "pvalid", (B, L, W), torch.uint8)
-    gathered, row_bytes = None, 0
+    go, po, co = (gather_out or {}).get, (post_out or {}).get, (commit_out or {}).get
+    safe, pvalid, gathered, row_bytes = go("safe"), go("pvalid"), None, 0
+    if safe is None:
+        safe = _i32((B, L, W), dev)
+    if pvalid is None:
+        pvalid = torch.empty((B, L, W), dtype=torch.uint8, device=dev)
     if src is not None:
-        if src.shape[0] == 0 or src.shape[1] == 0:
+        rows = src.shape
+        if rows[0] == 0 or rows[1] == 0:
             raise IndexError("src has no row")
-        row_bytes = src.element_size() * (src.numel() // (src.shape[0] * src.shape[1]))
-        gathered = get(go, "gathered", (B, L, W) + tuple(src.shape[2:]), src.dtype)
-    g, ln, best = get(po, "argmax", (B, T)), get(po, "len", (B, L)), get(po, "best", (B,))
-    A, acc, bonus = get(po, "accept_len", (B,)), get(po, "acc_nodes", (B, W)), get(po, "bonus", (B,))
-    plo, slot, status = get(co, "prefix_len_out", (B,)), get(co, "slot_map", (B, W)), get(co, "status", (B,))
+        row_bytes = src.element_size() * (src.numel() // (rows[0] * rows[1]))
+        gathered = go("gathered")
+        if gathered is None:
+            gathered = torch.empty((B, L, W) + tuple(rows[2:]), dtype=src.dtype, device=dev)
+    g, ln, best, A, acc, bonus = po("argmax"), po("len"), po("best"), po("accept_len"), po("acc_nodes"), po("bonus")
+    if g is None:
+        g = _i32((B, T), dev)
+    if ln is None:
+        ln = _i32((B, L), dev)
+    if best is None:
+        best = _i32((B,), dev)
+    if A is None:
+        A = _i32((B,), dev)
+    if acc is None:
+        acc = _i32((B, W), dev)
+    if bonus is None:
+        bonus = _i32((B,), dev)
+    plo, slot, status = co("prefix_len_out"), co("slot_map"), co("status")
+    if plo is None:
+        plo = _i32((B,), dev)
+    if slot is None:
+        slot = _i32((B, W), dev)
+    if status is None:
+        status = _i32((B,), dev)
     if workspace is None and logits is not None:
         workspace = torch.empty((max(256, evaluate_posterior_workspace_bytes(B, T, V)),), dtype=torch.uint8, device=dev)
     dsc = _commit_desc(kt, k_cache, block_table, W, B, T)

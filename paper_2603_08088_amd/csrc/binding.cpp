@@ -104,11 +104,44 @@ PyObject *empty_i32(PyObject *, PyObject *const *args, Py_ssize_t n) {
     END_HANDLE_TH_ERRORS
 }
 
+// commit_desc(kt, k_cache, block_table or None, W): the descriptor's bytes, from the shapes; None where they are not those of a step's tree
+// rows and caches (kt None among them), which the Python caller then names
+PyObject *commit_desc(PyObject *, PyObject *const *args, Py_ssize_t n) {
+    HANDLE_TH_ERRORS
+    if (n != 4) return PyErr_Format(PyExc_TypeError, "4 arguments expected, got %zd", n);
+    const bool paged = args[2] != Py_None;
+    if (!THPVariable_Check(args[0]) || !THPVariable_Check(args[1]) || (paged && !THPVariable_Check(args[2])) || !PyLong_Check(args[3])) Py_RETURN_NONE;
+    const at::Tensor &kt = THPVariable_Unpack(args[0]), &cache = THPVariable_Unpack(args[1]);
+    if (kt.dim() != 5 || cache.dim() != 5 || kt.size(0) != cache.size(0)) Py_RETURN_NONE;
+    etv_commit_desc d{};
+    const auto i32 = [](int64_t v) { return static_cast<int32_t>(v); };
+    d.n_layers = i32(kt.size(0));
+    d.B = i32(kt.size(1));
+    d.T_max = i32(kt.size(2));
+    d.Hkv = i32(kt.size(3));
+    d.d = i32(kt.size(4));
+    d.elem_bytes = i32(cache.element_size());
+    d.W = static_cast<int32_t>(PyLong_AsUnsignedLongLongMask(args[3]));
+    if (paged) {
+        const at::Tensor &table = THPVariable_Unpack(args[2]);
+        if (table.dim() < 2) Py_RETURN_NONE;
+        d.block_size = i32(cache.size(3));
+        d.max_blocks = i32(table.size(1));
+        d.num_blocks = i32(cache.size(1));
+    } else {
+        d.P_cap = i32(cache.size(2));
+    }
+    d.cache_layer_stride = d.n_layers > 1 ? cache.stride(0) : cache.numel();
+    return PyBytes_FromStringAndSize(reinterpret_cast<const char *>(&d), sizeof d);
+    END_HANDLE_TH_ERRORS
+}
+
 #define ETV_METHOD(name) {#name, (PyCFunction)(void (*)(void))call<&etv_##name>, METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {ETV_METHOD(build_tree_mask), ETV_METHOD(tensorize_tree), ETV_METHOD(tree_verify_attention),
                          ETV_METHOD(tree_verify_attention_static), ETV_METHOD(safe_gather_paths), ETV_METHOD(evaluate_posterior),
                          ETV_METHOD(commit_accepted_kv), ETV_METHOD(verify_epilogue), ETV_METHOD(lm_head_argmax),
                          ETV_METHOD(pack_lm_head), ETV_METHOD(replicate_branches), ETV_METHOD(commit_path_indices),
+                         {"commit_desc", (PyCFunction)(void (*)(void))commit_desc, METH_FASTCALL, nullptr},
                          {"empty_i32", (PyCFunction)(void (*)(void))empty_i32, METH_FASTCALL, nullptr},
                          {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_binding", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
