@@ -61,4 +61,20 @@ __device__ __forceinline__ int wave_scan(int v, F f) {
 __device__ __forceinline__ int wave_scan_sum(int v) { return wave_scan(v, [](int a, int b) { return a + b; }); }
 __device__ __forceinline__ int wave_scan_max(int v) { return wave_scan(v, [](int a, int b) { return max(a, b); }); }
 
+// The best over the wavefront, f(x, x) being x (a maximum, a minimum): lanes whose neighbour is outside a row combine with themselves.
+template <class T, class F>
+__device__ __forceinline__ T wave_best(T v, F f) {
+    static_assert(sizeof(T) == 4, "one register");
+#define ETV_STEP(ctrl, rows) \
+    v = f(v, __builtin_bit_cast(T, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, v), __builtin_bit_cast(int, v), ctrl, rows, 0xf, false)))
+    ETV_STEP(0x111, 0xf);
+    ETV_STEP(0x112, 0xf);
+    ETV_STEP(0x114, 0xf);
+    ETV_STEP(0x118, 0xf);
+    ETV_STEP(0x142, 0xa);
+    ETV_STEP(0x143, 0xc);
+#undef ETV_STEP
+    return __builtin_bit_cast(T, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
+}
+
 }  // namespace etv
