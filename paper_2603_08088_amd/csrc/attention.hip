@@ -99,18 +99,18 @@ __device__ __forceinline__ uint64_t uni64(uint64_t v) {
 // It stands before a workgroup's first load, so it is written for latency: lane moves of the vector unit instead of shuffles through
 // LDS, uniform divisions only, and the owner's shares alone are worked out.  fp32, B = 2, T = 33, P = 771 / 1003 18.4 -> 17.0 us; bf16
 // calls whose splits follow the lengths 0.3 ... 0.8 us (B = 3, T = 4, P = 2816: 15.0 -> 14.4).
-__device__ inline SplitShare balanced_share(const AttnParams &p, int x, int lane) {
-    const int at = min(lane, p.B - 1);
-    const bool has = lane < p.B;
-    const int P_raw = p.prefix_len[at], n_raw = p.n_nodes[at];
+__device__ inline SplitShare balanced_share(const AttnParams &p, const int32_t *prefix_len, const int32_t *n_nodes, int B, int x, int lane) {
+    const int at = min(lane, B - 1);
+    const bool has = lane < B;
+    const int P_raw = prefix_len[at], n_raw = n_nodes[at];
     const int P = clampi(P_raw, 0, p.P_max), n = clampi(n_raw, 0, p.T_max);
     const int pt = has ? (P + 63) >> 6 : 0;
     const int tt = pt + (has ? (n + 63) >> 6 : 0);
-    const int S = p.B * p.nsplit;
+    const int S = B * p.nsplit;
     const auto last = [](int v) { return __builtin_amdgcn_readlane(v, 63); };
     const int total = last(wave_scan_sum(tt));
     int hi = max(1, last(wave_scan_max(tt)));                                              // one slot per sequence always fits
-    if (S > p.B) hi = min(hi, max(1, (int)((uint32_t)(total + (S - p.B) - 1) / (uint32_t)(S - p.B))));  // sum (tiles_b / L + 1) <= S
+    if (S > B) hi = min(hi, max(1, (int)((uint32_t)(total + (S - B) - 1) / (uint32_t)(S - B))));  // sum (tiles_b / L + 1) <= S
     int lo = min(hi, max(1, (int)((uint32_t)(total + S - 1) / (uint32_t)S)));
     const auto slots_of = [&](int L) {  // of the lane's sequence, L tiles to a slot
         uint32_t rem;
@@ -137,6 +137,9 @@ __device__ inline SplitShare balanced_share(const AttnParams &p, int x, int lane
     r.n_raw = of_owner(n_raw);
     r.live = owner >= 0 && r.j < r.nvalid;
     return r;
+}
+__device__ __forceinline__ SplitShare balanced_share(const AttnParams &p, int x, int lane) {
+    return balanced_share(p, p.prefix_len, p.n_nodes, p.B, x, lane);
 }
 
 template <typename T>
@@ -1357,51 +1360,65 @@ struct WideGeo {
     static constexpr int LDS = RING + NW * 8192;             // all 160 KiB of a compute unit
 };
 
+// form: nodes of a tree (16 bits), splits shared out by length (1), a single split (1), sequences if shared out (8)
+static uint32_t wide_form(const AttnParams &p) {
+    return (uint32_t)p.T_max | (p.balanced ? 1u : 0u) << 16 | (p.nsplit == 1 ? 1u : 0u) << 17 | (p.balanced ? (uint32_t)p.B : 0u) << 18;
+}
+
 template <bool PAGED, bool NT, bool MANY>
-__global__ void __launch_bounds__(256, 1) attn_wide_kernel(AttnParams p) {
+__global__ void __launch_bounds__(256, 1)
+attn_wide_kernel(const int32_t *prefix_len, const int32_t *n_nodes, const uint64_t *bitmask, const int32_t *block_table, uint32_t Hkv,
+                 uint32_t inv_hkv, uint32_t G, uint32_t inv_g, int max_blocks, uint32_t form, AttnParams p) {
     constexpr int D = 128, AHEAD = WideGeo::AHEAD, MASKED = WideGeo::MASKED;
     constexpr int ROW_BYTES = Geo<D>::ROW_BYTES, TILE_BYTES = Geo<D>::TILE_BYTES, STAGE_BYTES = Geo<D>::STAGE_BYTES;
     uint8_t *const smem = attn_smem;
     const uint32_t smem_addr = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)attn_smem;
 
     // grid, shares of a ragged batch and the rotation of the split index: as in attn_mfma_kernel
-    const int wg = blockIdx.y / p.Hkv, kvh = blockIdx.y % p.Hkv;
+    const int T_max = (int)(form & 0xffffu);
+    const bool balanced = (form >> 16 & 1u) != 0, single = (form >> 17 & 1u) != 0;
+    uint32_t rem;
+    const int wg = (int)fast_div(blockIdx.y, Hkv, inv_hkv, rem), kvh = (int)rem;
     const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     SplitShare share{};
-    if (p.balanced) {
-        share = balanced_share(p, (int)blockIdx.x, lane);
+    int s_ = 0, chunk_ = 0;
+    if (balanced) {
+        share = balanced_share(p, prefix_len, n_nodes, (int)(form >> 18), (int)blockIdx.x, lane);
         if (!share.live) return;  // uniform over the workgroup
         if (share.j == 0 && blockIdx.y == 0 && tid == 0) p.split_tab[share.b] = make_int2(share.start, share.nvalid);
+        s_ = share.j;
+        chunk_ = share.tps * KT;
+    } else if (!single) {
+        asm volatile("" ::"s"(p.nsplit), "s"(p.inv_nsplit), "s"(p.chunk));  // nobody else waits for these
+        fast_div(blockIdx.x + blockIdx.z, (uint32_t)p.nsplit, p.inv_nsplit, rem);
+        s_ = (int)rem;
+        chunk_ = p.chunk;
     }
-    const int b = uni(p.balanced ? share.b : (int)blockIdx.z);
-    const int s = uni(p.balanced ? share.j : (int)((blockIdx.x + blockIdx.z) % p.nsplit));
-    const int chunk = uni(p.balanced ? share.tps * KT : p.chunk);
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    asm volatile("" ::"s"(p.q), "s"(p.k_cache), "s"(p.v_cache), "s"(p.kt), "s"(p.vt), "s"(p.block_table),
-                 "s"(p.prefix_len), "s"(p.n_nodes), "s"(p.bitmask), "s"(p.T_max), "s"(p.Hq), "s"(p.G),
-                 "s"(p.max_blocks), "s"(p.P_cap), "s"(p.P_max), "s"(p.words), "s"(p.chunk), "s"(p.pairs));
-    const int k0 = uni(s * chunk);
-    const const_i32_ptr bt = (const_i32_ptr)(uintptr_t)(PAGED ? p.block_table + (size_t)b * p.max_blocks : nullptr);
-    // One trip for the sizes, the wavefront's blocks of the first full tiles (read before it is known whether the prefix reaches
-    // that far, used only if it does) and the ancestor bits of the lane's two rows.
+    const int b = uni(balanced ? share.b : (int)blockIdx.z), s = uni(s_);
+    const int k0 = uni(s * chunk_);
+    const const_i32_ptr bt = (const_i32_ptr)(uintptr_t)(PAGED ? block_table + (size_t)b * max_blocks : nullptr);
+    // One trip for the other arguments, the sizes, the wavefront's blocks of the first full tiles (read before it is known whether the
+    // prefix reaches that far, used only if it does) and the ancestor bits of the lane's four rows.
     const int lb0 = (k0 >> 4) + wave;
-    const bool spec = PAGED && (k0 >> 4) + 4 * AHEAD <= p.max_blocks;
+    const bool spec = PAGED && (k0 >> 4) + 4 * AHEAD <= max_blocks;
     int blk0 = 0, blk1 = 0, blk2 = 0;
     if (spec) {
         blk0 = bt[lb0];
         blk1 = bt[lb0 + 4];
         blk2 = bt[lb0 + 8];
     }
-    const int n_raw = p.balanced ? share.n_raw : ((const_i32_ptr)(uintptr_t)p.n_nodes)[b];
-    const int P_raw = p.balanced ? share.P_raw : ((const_i32_ptr)(uintptr_t)p.prefix_len)[b];
+    const int n_raw = balanced ? share.n_raw : ((const_i32_ptr)(uintptr_t)n_nodes)[b];
+    const int P_raw = balanced ? share.P_raw : ((const_i32_ptr)(uintptr_t)prefix_len)[b];
     // The 64 packed rows r = k * G + g (node k, head g of the group) of the wavefront's two chunks, lane i working out row i.
     struct Row { int kq; uint32_t at; bool in_launch; };  // at: byte offset of the row in its sequence's part of Q and of the output (below
                                                           // 2^32: at most 256 nodes of 65536 heads)
+    const int pairs = (int)((G * (uint32_t)T_max + 31) >> 5);  // 32-row chunks of a KV head
     auto own_row = [&](int l) -> Row {
         const int pair = wg * WideGeo::CW + wave + WideGeo::NW * (l >> 5);
         uint32_t g;
-        const int kq = (int)fast_div((uint32_t)(pair * 32 + (l & 31)), p.G, p.inv_g, g);
-        return {kq, (uint32_t)(kq * p.Hq + kvh * p.G + (int)g) * ROW_BYTES, pair < p.pairs && kq < p.T_max};
+        const int kq = (int)fast_div((uint32_t)(pair * 32 + (l & 31)), G, inv_g, g);
+        return {kq, ((uint32_t)kq * Hkv * G + (uint32_t)kvh * G + g) * ROW_BYTES, pair < pairs && kq < T_max};
     };
     // The lane's own four rows: of chunk x the rows lane % 16 (y = 0) and 16 + lane % 16 (y = 1).
     auto own_four = [&](int l, uint32_t v, uint32_t (&of)[2][2]) {
@@ -1413,25 +1430,30 @@ __global__ void __launch_bounds__(256, 1) attn_wide_kernel(AttnParams p) {
     const Row row = own_row(lane);
     uint32_t kq_of[2][2];
     own_four(lane, row.in_launch ? (uint32_t)row.kq : 0xffffffffu, kq_of);  // no row there: no node
-    // ancestor bits of these rows, the first two words (with MANY: read where they are needed)
+    // ancestor bits of these rows, the first two words (with MANY: read where they are needed); of rows that are not there node 0's
     uint64_t bits0[2][2] = {{0, 0}, {0, 0}}, bits1[2][2] = {{0, 0}, {0, 0}};
+    const uint32_t words = (uint32_t)(T_max + 63) >> 6;
     if constexpr (!MANY) {
+        const uint64_t *const mask = bitmask + (size_t)b * T_max * words;
+        const uint32_t second = words > 1 ? 1 : 0;
 #pragma unroll
         for (int x = 0; x < 2; x++)
 #pragma unroll
-            for (int y = 0; y < 2; y++)
-                if (kq_of[x][y] != 0xffffffffu) {
-                    const uint64_t *mrow = p.bitmask + ((size_t)b * p.T_max + kq_of[x][y]) * p.words;
-                    bits0[x][y] = mrow[0];
-                    if (p.words > 1) bits1[x][y] = mrow[1];
-                }
+            for (int y = 0; y < 2; y++) {
+                const uint32_t at = (kq_of[x][y] == 0xffffffffu ? 0u : kq_of[x][y]) * words;
+                bits0[x][y] = mask[at];
+                bits1[x][y] = mask[at + second];
+            }
     }
-    asm volatile("" ::"s"(n_raw), "s"(P_raw), "s"(blk0), "s"(blk1), "s"(blk2), "v"(bits0[0][0]), "v"(bits0[0][1]),
-                 "v"(bits0[1][0]), "v"(bits0[1][1]), "v"(bits1[0][0]), "v"(bits1[0][1]), "v"(bits1[1][0]), "v"(bits1[1][1]));
-    const int n = uni(clampi(n_raw, 0, p.T_max)), P = uni(clampi(P_raw, 0, p.P_max));
-    const int nvalid = uni(p.balanced ? share.nvalid : seq_nsplit(p, P));
+    asm volatile("" ::"s"(n_raw), "s"(P_raw), "s"(blk0), "s"(blk1), "s"(blk2), "s"(p.q), "s"(p.k_cache), "s"(p.v_cache), "s"(p.kt), "s"(p.vt),
+                 "s"(p.P_cap), "s"(p.P_max), "s"(p.chunk), "s"(p.inv_chunk), "s"(p.scale_log2));
+    asm volatile("" ::"v"(bits0[0][0]), "v"(bits0[0][1]), "v"(bits0[1][0]), "v"(bits0[1][1]), "v"(bits1[0][0]), "v"(bits1[0][1]),
+                 "v"(bits1[1][0]), "v"(bits1[1][1]));
+    const int n = uni(clampi(n_raw, 0, T_max)), P = uni(clampi(P_raw, 0, p.P_max));
+    const int chunk = uni(single ? p.chunk : chunk_);
+    const int nvalid = uni(balanced ? share.nvalid : single ? 1 : max(1, (int)fast_div((uint32_t)(P + chunk - 1), (uint32_t)chunk, p.inv_chunk, rem)));
     if (s >= nvalid) return;  // uniform over the workgroup
-    const bool direct = (p.nsplit == 1);
+    const bool direct = single;
 
     const int k1 = min(P, k0 + chunk);
     const int nfull = (k1 > k0) ? (k1 - k0) / KT : 0;
@@ -1440,10 +1462,10 @@ __global__ void __launch_bounds__(256, 1) attn_wide_kernel(AttnParams p) {
     const int edges = npt - nfull + ntt;  // tiles with masked keys: edge e is tile nfull + e of the split
 
     const bool tail = (p.kt == nullptr);
-    const size_t row_stride = (size_t)p.Hkv * ROW_BYTES, blk_stride = row_stride * 16;  // both below 2^32
-    const size_t head_at = PAGED ? (size_t)kvh * 16 * ROW_BYTES : ((size_t)b * p.P_cap * p.Hkv + kvh) * ROW_BYTES;
+    const size_t row_stride = (size_t)Hkv * ROW_BYTES, blk_stride = row_stride * 16;  // both below 2^32
+    const size_t head_at = PAGED ? (size_t)kvh * 16 * ROW_BYTES : ((size_t)b * p.P_cap * Hkv + kvh) * ROW_BYTES;
     const uint8_t *const kf = static_cast<const uint8_t *>(p.k_cache) + head_at, *const vf = static_cast<const uint8_t *>(p.v_cache) + head_at;
-    const size_t tree_at = ((size_t)b * p.T_max * p.Hkv + kvh) * ROW_BYTES;
+    const size_t tree_at = ((size_t)b * T_max * Hkv + kvh) * ROW_BYTES;
     // the lane, anew: what is worked out from it for use ahead of and behind the loop is not kept in registers during it
     auto again = [&]() -> int {
         int l = lane;
@@ -1534,7 +1556,7 @@ __global__ void __launch_bounds__(256, 1) attn_wide_kernel(AttnParams p) {
         if (w >= 0) {
             if constexpr (MANY) {
                 vis = 0;
-                if (kq_of[x][y] != 0xffffffffu) vis = p.bitmask[((size_t)b * p.T_max + kq_of[x][y]) * p.words + w];
+                if (kq_of[x][y] != 0xffffffffu) vis = bitmask[((size_t)b * T_max + kq_of[x][y]) * words + w];
             } else {
                 vis = (w & 1) ? bits1[x][y] : bits0[x][y];
             }
@@ -1548,8 +1570,8 @@ __global__ void __launch_bounds__(256, 1) attn_wide_kernel(AttnParams p) {
     // node 0's.  A sequence without keys reads none: it has no pass of the loop, whose barriers keep a wavefront's Q apart from the
     // outputs that others stage in the same LDS.
     if (edges + nfull > 0) {
-        const uint8_t *const qseq = reinterpret_cast<const uint8_t *>(uni64((uint64_t)(uintptr_t)p.q + (size_t)b * p.T_max * p.Hq * ROW_BYTES));
-        const uint32_t from = row.in_launch && row.kq < n ? row.at : (uint32_t)(kvh * p.G) * ROW_BYTES;
+        const uint8_t *const qseq = reinterpret_cast<const uint8_t *>(uni64((uint64_t)(uintptr_t)p.q + (size_t)b * T_max * (int)(Hkv * G) * ROW_BYTES));
+        const uint32_t from = row.in_launch && row.kq < n ? row.at : (uint32_t)(kvh * (int)G) * ROW_BYTES;
         const Columns c = columns(lane);
         uint32_t at[16];
 #pragma unroll
@@ -1573,7 +1595,7 @@ __global__ void __launch_bounds__(256, 1) attn_wide_kernel(AttnParams p) {
     while (again_pass) {
         const uint32_t done = uni(e_done + f_done);
         // chunk `wave` of the group and chunk `wave` + 4 (a small group is spread over the SIMDs): how many of them hold rows?
-        const uint32_t chunks = uni((int)((wg * WideGeo::CW + wave) * 32 < n * p.G) + (int)((wg * WideGeo::CW + wave + WideGeo::NW) * 32 < n * p.G));
+        const uint32_t chunks = uni((int)((wg * WideGeo::CW + wave) * 32 < n * (int)G) + (int)((wg * WideGeo::CW + wave + WideGeo::NW) * 32 < n * (int)G));
         const int lead = lead_full && f_done == 0 ? 1 : 0, e_left = edges - e_done;
         const bool more = MANY && e_left > MASKED - lead;  // not the last pass
         const int ne = more ? (lead ? MASKED - 1 : e_left - MASKED) : e_left, masked = lead + ne, nt = masked + (more ? 0 : nfull - f_done - lead);
@@ -1633,7 +1655,7 @@ __global__ void __launch_bounds__(256, 1) attn_wide_kernel(AttnParams p) {
     wait_vmcnt<0>();  // nothing on its way to LDS is left behind
     // ---- outputs, through the wavefront's own 8 KiB of LDS so that whole rows (of a group: neighbours) go out together:
     // 32 rows of 16 pieces of 16 bytes, piece c of row r at c ^ (r % 16)
-    uint8_t *const oseq = static_cast<uint8_t *>(p.out) + (size_t)b * p.T_max * p.Hq * ROW_BYTES;
+    uint8_t *const oseq = static_cast<uint8_t *>(p.out) + (size_t)b * T_max * (int)(Hkv * G) * ROW_BYTES;
     uint8_t *const stage = smem + WideGeo::OUT_AT + wave * 8192;
     const int l2 = again(), piece = l2 & 15, sub = l2 >> 4;
     const Row row2 = own_row(l2);
@@ -1658,7 +1680,7 @@ __global__ void __launch_bounds__(256, 1) attn_wide_kernel(AttnParams p) {
     };
 #pragma unroll
     for (int x = 0; x < 2; x++) {
-        if (wg * WideGeo::CW + wave + WideGeo::NW * x >= p.pairs) break;  // uniform over the wavefront
+        if (wg * WideGeo::CW + wave + WideGeo::NW * x >= pairs) break;  // uniform over the wavefront
         const f32x32 &o0 = x ? ob0 : oa0, &o1 = x ? ob1 : oa1;
         auto o = [&](int i) { return i < 32 ? o0[i & 31] : o1[i & 31]; };  // 4 (2 db + y) + i: column 16 db + 4 (lane / 16) + i of row y
         float l_tot[2];
@@ -1668,7 +1690,7 @@ __global__ void __launch_bounds__(256, 1) attn_wide_kernel(AttnParams p) {
             valid[y] = kq2[x][y] < (uint32_t)n;
             l_tot[y] = quarter_swap_sum(half_swap_sum(sum[2 * x + y]));
         }
-        auto head = [&](int y) { return at2[x][y] / ROW_BYTES - kq2[x][y] * p.Hq; };
+        auto head = [&](int y) { return at2[x][y] / ROW_BYTES - kq2[x][y] * (int)(Hkv * G); };
         if (direct) {
             const bool whole = __all(valid[0] && valid[1]);  // else padded rows: zeros
 #pragma unroll
@@ -1687,13 +1709,13 @@ __global__ void __launch_bounds__(256, 1) attn_wide_kernel(AttnParams p) {
 #pragma unroll
                 for (int y = 0; y < 2; y++)
                     if (kq2[x][y] != 0xffffffffu)
-                        p.lse[((size_t)b * p.Hq + head(y)) * p.T_max + kq2[x][y]] =
+                        p.lse[((size_t)b * (int)(Hkv * G) + head(y)) * T_max + kq2[x][y]] =
                             valid[y] ? (-nm[2 * x + y] + __builtin_amdgcn_logf(l_tot[y])) * kLn2 : -INFINITY;
         } else {
             // rows of the slot's partials: head, then node
-            const size_t slot_row = part_row(p, p.balanced ? (int)blockIdx.x : b * p.nsplit + s, 0, 0);
+            const size_t slot_row = part_row(p, balanced ? (int)blockIdx.x : b * p.nsplit + s, 0, 0);
             float *const part = p.part_o + slot_row * D;
-            const uint32_t prow = (row2.at / ROW_BYTES - row2.kq * p.Hq) * p.T_max + row2.kq;
+            const uint32_t prow = (row2.at / ROW_BYTES - row2.kq * (int)(Hkv * G)) * T_max + row2.kq;
 #pragma unroll
             for (int hf = 0; hf < 2; hf++) {  // half a row of fp32 each time
 #pragma unroll
@@ -1710,7 +1732,7 @@ __global__ void __launch_bounds__(256, 1) attn_wide_kernel(AttnParams p) {
 #pragma unroll
                 for (int y = 0; y < 2; y++)
                     if (valid[y]) {
-                        const size_t pr = slot_row + head(y) * p.T_max + kq2[x][y];
+                        const size_t pr = slot_row + head(y) * T_max + kq2[x][y];
                         p.part_m[pr] = -nm[2 * x + y];
                         p.part_l[pr] = l_tot[y];
                     }
@@ -2702,7 +2724,8 @@ static int32_t launch_wide(const AttnParams &p, dim3 grid, hipStream_t st) {
                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) == hipSuccess;
     }();
     if (!lds_ok) return ETV_ERR_HIP;
-    hipLaunchKernelGGL((attn_wide_kernel<PAGED, NT, MANY>), grid, dim3(256), lds, st, p);
+    hipLaunchKernelGGL((attn_wide_kernel<PAGED, NT, MANY>), grid, dim3(256), lds, st, p.prefix_len, p.n_nodes, p.bitmask, p.block_table,
+                       (uint32_t)p.Hkv, p.inv_hkv, (uint32_t)p.G, p.inv_g, p.max_blocks, wide_form(p), p);
     return check_launch();
 }
 
