@@ -893,10 +893,14 @@ __device__ __forceinline__ void pv_accumulate(const TileView &tv, const uint8_t 
 // per-tile dependency chain of a wavefront, which is what bounds the rate when a workgroup has fewer chunks
 // than wavefronts.  vis32: visibility bits of the wavefront's 32 keys; apply: a uniform switch for callers that keep one
 // copy of the code for masked and unmasked blocks.
-template <int D, bool MASKED>
+struct Nothing {
+    __device__ void operator()() const {}
+};
+// between(): runs once K is in registers, beside the score products
+template <int D, bool MASKED, class F = Nothing>
 __device__ __forceinline__ void qk_softmax_half(const TileView &tv, const uint8_t *lk, int kb, const bf16x8 (&qreg)[Geo<D>::KK],
                                                 f32x16 (&oacc)[Geo<D>::DB], float &m_run, float &l_run, float scale_log2,
-                                                uint32_t vis32, bf16x8 (&pf)[Geo<D>::NP][2], bool apply = true) {
+                                                uint32_t vis32, bf16x8 (&pf)[Geo<D>::NP][2], bool apply = true, F &&between = F{}) {
     constexpr int ROW_BYTES = Geo<D>::ROW_BYTES, KK = Geo<D>::KK;
     // two accumulator chains over the even / odd 16-wide d steps, summed afterwards
     f32x16 s0, s1;
@@ -914,6 +918,7 @@ __device__ __forceinline__ void qk_softmax_half(const TileView &tv, const uint8_
             s1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[kk + 1], qreg[kk + 1], s1, 0, 0, 0);
         }
     }
+    between();
 #pragma unroll
     for (int i = 0; i < 16; i++) s0[i] += s1[i];
     if (MASKED && apply) {
@@ -1970,14 +1975,12 @@ attn_blocks_kernel(const int32_t *prefix_len, const int32_t *n_nodes, const int3
             bf16x8 pf[Geo<D>::NP][2];
             // one copy of the code for masked and unmasked blocks: a launch this short pays for every instruction it fetches
             const uint32_t vis = block_vis(t);
-            qk_softmax_half<D, true>(tv, lk, 0, qreg, oacc, m_run, l_run, p.scale_log2, vis, pf, t >= nfull);
-            wait_lds_reads();
-            if (tn < nt) {
-                issue(tn, i0, i1, i2, false);
-                wait_vmcnt<U>();  // V of block t (K of the next one may still be on its way)
-            } else {
-                wait_vmcnt<0>();
-            }
+            qk_softmax_half<D, true>(tv, lk, 0, qreg, oacc, m_run, l_run, p.scale_log2, vis, pf, t >= nfull, [&] {
+                wait_lds_reads();
+                if (tn < nt) issue(tn, i0, i1, i2, false);
+            });
+            if (tn < nt) wait_vmcnt<U>();  // V of block t (K of the next one may still be on its way)
+            else wait_vmcnt<0>();
             asm volatile("" ::: "memory");
             pv_accumulate_half<D>(tv, lv, 0, pf, oacc, t >= nfull, ill);
             wait_lds_reads();
