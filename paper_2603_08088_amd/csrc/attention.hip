@@ -912,6 +912,8 @@ __device__ __forceinline__ void qk_softmax_half(const TileView &tv, const uint8_
 #pragma unroll
         for (int kk = 0; kk < KK; kk++)
             ka[kk] = *reinterpret_cast<const bf16x8 *>(kr + (((2 * kk + tv.hh) ^ tv.ksw) << 4));
+        if constexpr (D == 128 && !std::is_same_v<F, Nothing>)  // all in flight: with two registers in turn every product waits for a read
+            asm volatile("" ::"v"(ka[0]), "v"(ka[1]), "v"(ka[2]), "v"(ka[3]), "v"(ka[4]), "v"(ka[5]), "v"(ka[6]), "v"(ka[7]));
 #pragma unroll
         for (int kk = 0; kk < KK; kk += 2) {
             s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[kk], qreg[kk], s0, 0, 0, 0);
@@ -966,11 +968,13 @@ __device__ __forceinline__ void qk_softmax_half(const TileView &tv, const uint8_
     l_run += psum;
 }
 
-template <int D>
+template <int D, bool AT_ONCE = false>
 __device__ __forceinline__ void pv_accumulate_half(const TileView &tv, const uint8_t *lv, int kb, const bf16x8 (&pf)[Geo<D>::NP][2],
                                                    f32x16 (&oacc)[Geo<D>::DB], bool masked, bool &ill) {
     bf16x8 vf[2][Geo<D>::DB];
     load_v_frags<D>(tv, lv, kb, vf);
+    if constexpr (D == 128 && AT_ONCE)
+        asm volatile("" ::"v"(vf[0][0]), "v"(vf[0][1]), "v"(vf[0][2]), "v"(vf[0][3]), "v"(vf[1][0]), "v"(vf[1][1]), "v"(vf[1][2]), "v"(vf[1][3]));
     if constexpr (D == 64)
         if (masked && take_out_nonfinite(vf)) ill = true;
 #pragma unroll
@@ -1777,6 +1781,11 @@ attn_wide_kernel(const int32_t *prefix_len, const int32_t *n_nodes, const uint64
 // 87.4 -> 82.7 us (128 KiB in flight per compute unit: 6.5 TB/s).  By the start-up and edge loads above: 32 layers of B = 1, T = 60,
 // P = 2048 510 -> 471 us (with the combine launches); heads of 64, B = 4, T = 48, P = 900 ... 1500 13.4 -> 11.5; 68 drawn calls
 // below 40 MB 16 % shorter on average.
+// Behind the start-up a launch of two or three steps is a chain of instructions, one every 3.5 ns: the fragments of a product are all read
+// before the first of its instructions (the compiler takes them two by two and waits each time), zeros and LDS addresses are
+// ready before the sizes arrive, K of the next block is asked for beside the products of this one, and the merge reads all
+// eight outputs without a branch (wavefronts without a block leave zeros).  The 32 layers 430 -> 422 us, heads of 64 11.43 -> 11.27,
+// B = 32, T = 8, P = 4096 81.7 -> 81.3; the merge with a second copy for launches of fewer wavefronts was slower than before.
 // ----------------------------------------------------------------------------------------------
 constexpr int KB_NW = 8;     // wavefronts of a workgroup
 constexpr int KB_KEYS = 32;  // keys of a block
@@ -1834,6 +1843,20 @@ attn_blocks_kernel(const int32_t *prefix_len, const int32_t *n_nodes, const int3
     }
     const int n_raw = BALANCED ? share.n_raw : ((const_i32_ptr)(uintptr_t)n_nodes)[b];
     const int P_raw = BALANCED ? share.P_raw : ((const_i32_ptr)(uintptr_t)prefix_len)[b];
+    // Ready before the sizes are: the views of the wavefront's buffers, as in the tile kernel, and zeros.
+    const int g16 = lane >> 4, i16 = lane & 15;
+    const int vrow = 4 * hh + (i16 >> 2);
+    const TileView tv{c32 * ROW_BYTES, kswz_of_row<D>(c32), vrow, vswz_of_row<D>(vrow),
+                      2 * (g16 & 1) + ((i16 & 3) >> 1), 8 * (i16 & 1), hh};
+    const uint8_t *const lk = smem + wave * (2 * BLOCK), *const lv = lk + BLOCK;
+    f32x16 oacc[DB];
+    float m_run = -INFINITY, l_run = 0.f;
+#pragma unroll
+    for (int db = 0; db < DB; db++)
+#pragma unroll
+        for (int i = 0; i < 16; i++) oacc[db][i] = 0.f;
+#pragma unroll
+    for (int db = 0; db < DB; db++) asm volatile("" : "+v"(oacc[db]));
     asm volatile("" ::"s"(n_raw), "s"(P_raw), "s"(blk0), "s"(blk1), "s"(p.q), "s"(p.k_cache), "s"(p.v_cache), "s"(p.kt), "s"(p.vt),
                  "s"(p.bitmask), "s"(p.T_max), "s"(p.Hq), "s"(p.G), "s"(p.inv_g), "s"(p.P_cap), "s"(p.P_max), "s"(p.words), "s"(p.scale_log2));
     const int n = clampi(n_raw, 0, p.T_max), P = clampi(P_raw, 0, p.P_max);
@@ -1942,18 +1965,6 @@ attn_blocks_kernel(const int32_t *prefix_len, const int32_t *n_nodes, const int3
     __builtin_amdgcn_s_barrier();  // Q and the ancestor bits are in LDS
     asm volatile("" ::: "memory");
 
-    // the views of the wavefront's buffers, as in the tile kernel
-    const int g16 = lane >> 4, i16 = lane & 15;
-    const int vrow = 4 * hh + (i16 >> 2);
-    const TileView tv{c32 * ROW_BYTES, kswz_of_row<D>(c32), vrow, vswz_of_row<D>(vrow),
-                      2 * (g16 & 1) + ((i16 & 3) >> 1), 8 * (i16 & 1), hh};
-    const uint8_t *const lk = smem + wave * (2 * BLOCK), *const lv = lk + BLOCK;
-    f32x16 oacc[DB];
-    float m_run = -INFINITY, l_run = 0.f;
-#pragma unroll
-    for (int db = 0; db < DB; db++)
-#pragma unroll
-        for (int i = 0; i < 16; i++) oacc[db][i] = 0.f;
     auto block_vis = [&](int x) {  // keys of block x that the lane's row sees
         uint32_t vis = ~0u;
         if (x >= npb) vis = *reinterpret_cast<const uint32_t *>(smem + G_::BITS_AT + ((x - npb) >> 1) * 256 + c32 * 8 + ((x - npb) & 1) * 4);
@@ -1982,7 +1993,7 @@ attn_blocks_kernel(const int32_t *prefix_len, const int32_t *n_nodes, const int3
             if (tn < nt) wait_vmcnt<U>();  // V of block t (K of the next one may still be on its way)
             else wait_vmcnt<0>();
             asm volatile("" ::: "memory");
-            pv_accumulate_half<D>(tv, lv, 0, pf, oacc, t >= nfull, ill);
+            pv_accumulate_half<D, true>(tv, lv, 0, pf, oacc, t >= nfull, ill);
             wait_lds_reads();
             if (tn < nt) issue(tn, i0, i1, i2, true);
         }
@@ -2003,8 +2014,7 @@ attn_blocks_kernel(const int32_t *prefix_len, const int32_t *n_nodes, const int3
     // ---- merge the wavefronts: each leaves O in its own K/V buffers (same size), 16-byte piece c of row r at c ^ r
     constexpr int CH = D / 4;  // 16-byte pieces of an fp32 output row
     float2 *const ml = reinterpret_cast<float2 *>(smem + G_::ML_AT);
-    const int live = min(KB_NW, nt);
-    if (wave < live) {
+    {
         const float l_tot = half_swap_sum(l_run);
         float4 *dst = reinterpret_cast<float4 *>(smem + wave * (2 * BLOCK)) + c32 * CH;
 #pragma unroll
@@ -2022,31 +2032,33 @@ attn_blocks_kernel(const int32_t *prefix_len, const int32_t *n_nodes, const int3
     if (kq2 >= p.T_max) return;
     const bool rv = kq2 < n;
     if (!rv && !direct) return;
-    // all reads of the statistics in one trip, then all reads of the outputs (those of absent wavefronts are skipped)
+    // all reads of the statistics in one trip, then all reads of the outputs, without a branch: a wavefront without a block left zeros
     float2 e[KB_NW];
     float M = -INFINITY, L = 0.f;
 #pragma unroll
     for (int x = 0; x < KB_NW; x++) e[x] = ml[x * 32 + row];
 #pragma unroll
     for (int x = 0; x < KB_NW; x++) {
-        if (x >= live) e[x] = float2{-INFINITY, 0.f};
         M = fmaxf(M, e[x].x);
     }
     float4 acc[D / 64];
 #pragma unroll
     for (int v = 0; v < D / 64; v++) acc[v] = float4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int x = 0; x < KB_NW; x++) {
-        if (x >= live) break;  // uniform
+    const auto add = [&](int x, const float4 (&o)[D / 64]) {
         const float w = e[x].x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(e[x].x - M);
         L = fmaf(w, e[x].y, L);
-        const float4 *src = reinterpret_cast<const float4 *>(smem + x * (2 * BLOCK)) + row * CH;
 #pragma unroll
         for (int v = 0; v < D / 64; v++) {
-            const float4 o = src[(piece + 16 * v) ^ (row & (CH - 1))];
-            acc[v].x = fmaf(w, o.x, acc[v].x); acc[v].y = fmaf(w, o.y, acc[v].y);
-            acc[v].z = fmaf(w, o.z, acc[v].z); acc[v].w = fmaf(w, o.w, acc[v].w);
+            acc[v].x = fmaf(w, o[v].x, acc[v].x); acc[v].y = fmaf(w, o[v].y, acc[v].y);
+            acc[v].z = fmaf(w, o[v].z, acc[v].z); acc[v].w = fmaf(w, o[v].w, acc[v].w);
         }
+    };
+#pragma unroll
+    for (int x = 0; x < KB_NW; x++) {
+        float4 o[D / 64];
+#pragma unroll
+        for (int v = 0; v < D / 64; v++) o[v] = reinterpret_cast<const float4 *>(smem + x * (2 * BLOCK))[row * CH + ((piece + 16 * v) ^ (row & (CH - 1)))];
+        add(x, o);
     }
     if (direct) {
         uint16_t *orow = static_cast<uint16_t *>(p.out) + (((size_t)b * p.T_max + kq2) * p.Hq + h2) * D;
