@@ -98,6 +98,7 @@ __global__ void __launch_bounds__(256) posterior_paths_kernel(
 // What bounds it are the trips to memory in series: sizes, partials, tokens and paths; block ids; the rows.  With the launch that
 // finds the partials, in graphs, V = 32000: B = 1, T = 60, 32 layers 9.3 -> 8.3 us; B = 8, T = 60, 4 layers, from the head's partials
 // 10.1 -> 8.7; B = 32, T = 128, 2 layers 86.0 -> 81.6 (74 of it logits).
+template <bool FEW>
 __global__ void __launch_bounds__(256) verify_epilogue_kernel(
     const int32_t *__restrict__ n_nodes, const int32_t *__restrict__ prefix_len, const int32_t *__restrict__ capacity,
     const int32_t *__restrict__ tokens, const int32_t *__restrict__ retrieve, const float *__restrict__ pval,
@@ -159,7 +160,7 @@ __global__ void __launch_bounds__(256) verify_epilogue_kernel(
     const int A = s_A;
     for (int l = g; l < dsc.n_layers; l += G) {
         if (in_place) commit_compact_layer(dsc, b, l, P, A, s_acc, s_slot, block_table, k_cache, v_cache, t, 256);
-        else commit_copy_layer(dsc, inv_units, b, l, A, s_acc, s_at, kt, vt, k_cache, v_cache, t, 256);
+        else commit_copy_layer<FEW>(dsc, inv_units, b, l, A, s_acc, s_at, kt, vt, k_cache, v_cache, t);
     }
 }
 
@@ -298,7 +299,8 @@ extern "C" int32_t etv_verify_epilogue(const etv_commit_desc *h, const float *lo
     // a thread per entry where a row is up to four aligned words (tokens): 8 x 60 paths of 7 entries are 14 workgroups then, not 840
     const bool per_thread = !src || ((row_bytes & 3) == 0 && row_bytes <= 16 && (((uintptr_t)src | (uintptr_t)gathered) & 3) == 0);
     const long gather_blocks = per_thread ? (gather_entries + 255) / 256 : (gather_entries + 3) / 4;
-    hipLaunchKernelGGL(etv::verify_epilogue_kernel, dim3((unsigned)((long)B * G + gather_blocks)), dim3(256), 0, s, n_nodes,
+    const auto kernel = !in_place && etv::few_columns(*h) ? etv::verify_epilogue_kernel<true> : etv::verify_epilogue_kernel<false>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((long)B * G + gather_blocks)), dim3(256), 0, s, n_nodes,
                        prefix_len, capacity, tokens, retrieve, pval, pidx, *h, G, etv::fast_div_inv(G), etv::fast_div_inv(std::max(h->block_size, 1)),
                        etv::fast_div_inv((int)((size_t)h->d * h->elem_bytes / 16)), chunks, (int)L_max, (int)dummy,
                        static_cast<const uint8_t *>(src), row_bytes, safe, pvalid, static_cast<uint8_t *>(gathered),

@@ -496,6 +496,38 @@ def test_in_place_commit_of_a_deep_gapped_path_and_refusal_of_a_backward_path(pa
     assert np.array_equal(bits_of(dkc2), okc2) and np.array_equal(bits_of(dvc2), ovc2)
 
 
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("Hkv,d,dtype", [(1, 8, "bf16"), (1, 64, "bf16"), (3, 64, "bf16"), (3, 128, "f32"), (4, 128, "f32"), (5, 128, "f32")])
+def test_fused_epilogue_moves_the_rows_of_few_kv_heads(Hkv, d, dtype, paged):
+    """A [K row | V row] pair of 2, 16, 48, 192, 256 and 320 columns of 16 bytes: groups of threads that take the batches of eight rows
+    in turn, threads left over, and one group.  1 ... 40 accepted rows, at the edges of the batches."""
+    rng = np.random.default_rng(9400 + Hkv * d + paged)
+    T, L, accepted = 40, 2, [0, 1, 6, 7, 8, 15, 16, 39]
+    B = len(accepted)
+    wl = synth.assemble("few", rng, [synth.tree_chain(T)] * B, [int(x) for x in rng.integers(0, 50, size=B)], Hq=Hkv, Hkv=Hkv, d=d, dtype=dtype,
+                        V=300, W=T, paged=paged, T_max=T, spare_blocks=3, with_logits=False)
+    g = np.full((B, T), -1, dtype=np.int32)
+    for b, a in enumerate(accepted):
+        g[b, :a] = wl.tokens[b, 1:a + 1]                   # the choice at a node is its child's token, a times
+        g[b, a:] = 299 - wl.tokens[b, min(a + 1, T - 1)] // 299
+    kt, vt = (np.stack([synth._values(rng, wl.kt.shape, dtype) for _ in range(L)]) for _ in range(2))
+    kc, vc = (np.stack([synth._values(rng, wl.k_cache.shape, dtype) for _ in range(L)]) for _ in range(2))
+    rp = oracle.evaluate_posterior(synth_logits_from(g, 300), wl.tokens, wl.retrieve, wl.n_nodes)
+    assert rp["accept_len"].tolist() == accepted
+    okc, ovc = kc.copy(), vc.copy()
+    rc = oracle.commit_accepted_kv(kt, vt, okc, ovc, wl.prefix_len, wl.capacity, wl.n_nodes, rp["acc_nodes"], rp["accept_len"],
+                                   block_table=wl.block_table)
+    assert np.all(rc["status"] == 0)
+    w = DevWorkload(wl)
+    dkc, dvc = to_dev(kc), to_dev(vc)
+    _, _, c = api.verify_epilogue(None, w.tokens, w.retrieve, w.n_nodes, to_dev(kt), to_dev(vt), dkc, dvc, w.prefix_len, w.capacity,
+                                  block_table=w.block_table, post_out=dict(argmax=to_dev(g)))
+    torch.cuda.synchronize()
+    for key in rc:
+        assert np.array_equal(bits_of(c[key]), rc[key]), key
+    assert np.array_equal(bits_of(dkc), okc) and np.array_equal(bits_of(dvc), ovc)
+
+
 def synth_logits_from(g, V):
     """Logits whose row argmax is g (padding rows, g < 0: any)."""
     lg = np.zeros(g.shape + (V,), dtype=np.float32)
