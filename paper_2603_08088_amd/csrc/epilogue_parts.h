@@ -47,8 +47,10 @@ __device__ __forceinline__ MaxIdx better(MaxIdx a, MaxIdx b) {
 
 constexpr int kChunk = 4096;  // floats of one logit row scanned by one workgroup (16 KiB)
 
-// A path table of at most this many entries is copied to LDS (16 KiB) before it is walked.
-constexpr int kPathEntries = 4096;
+// A path table of at most this many entries is copied to LDS (4 KiB) before it is walked: what 256 threads have in flight at once.  A larger
+// one is read where the walk, which mostly ends after a few steps, needs it: evaluate_posterior in graphs, 64 paths of 61
+// entries 6.2 us, copied 7.4; 256 of 11 6.1, copied 6.6.
+constexpr int kPathEntries = 1024;
 
 // Acceptance for sequence b by one workgroup of 256 threads (thread t): finish the argmax from the per-chunk
 // partials (or, with pval == nullptr, take argmax[] as given), walk every path with guarded compares, reduce to the best path (longest, lowest index on ties),
@@ -73,7 +75,7 @@ __device__ __forceinline__ void posterior_for_sequence(
     __shared__ int32_t s_path[4];
     __shared__ int32_t s_table[kPathEntries];
     static_assert(ETV_MAX_TREE <= 256, "one node per thread");
-    constexpr int E = 4, C = 8;  // loads in flight: path entries (E * 256 cover most tables), chunks of a node
+    constexpr int E = kPathEntries / 256, C = 8;  // loads in flight: path entries, chunks of a node
     const bool few = pval && chunks <= 16;
     const int32_t *const table = retrieve + (size_t)b * L_max * W;
     const bool staged = (long)L_max * W <= kPathEntries;
@@ -139,7 +141,6 @@ __device__ __forceinline__ void posterior_for_sequence(
 #pragma unroll
         for (int e = 0; e < E; e++)
             if (t + 256 * e < entries) s_table[t + 256 * e] = ent[e];
-        for (int e = t + 256 * E; e < entries; e += 256) s_table[e] = table[e];
     }
     __syncthreads();
     int my_len = -1, my_path = 0x7fffffff;

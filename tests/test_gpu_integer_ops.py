@@ -349,9 +349,10 @@ def test_fused_epilogue_matches_gather_acceptance_and_commit():
 
 
 @pytest.mark.parametrize("V,T,W,row", [(4096, 15, 5, 1), (32768, 33, 9, 4), (32772, 60, 6, 5), (65536, 12, 4, 2), (65540, 13, 4, 3),
-                                       (300, 210, 20, 4), (300, 256, 16, 1)])
+                                       (300, 210, 20, 4), (300, 256, 16, 1), (300, 205, 5, 1), (300, 206, 5, 2)])
 def test_fused_epilogue_at_the_edges_of_its_forms(V, T, W, row):
-    """1, 8, 9, 16 and 17 partials a node; path tables that LDS holds and one that it does not; gathered rows of one to five words."""
+    """1, 8, 9, 16 and 17 partials a node; path tables that LDS holds (up to 1020 entries) and that it does not (1025 and more); gathered
+    rows of one to five words."""
     rng = np.random.default_rng(V + T)
     parents = [synth.tree_star(T) if T > 200 else synth.tree_bfs(rng, T, W - 1, 4), synth.tree_bfs(rng, T - 3, W - 1, 4)]
     wl = synth.assemble("forms", rng, parents, [37, 16], Hq=2, Hkv=2, d=64, dtype="f32", V=V, W=W, paged=T != 33, T_max=T, spare_blocks=3)
