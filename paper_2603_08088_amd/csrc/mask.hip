@@ -4,6 +4,8 @@
 // tensorize_tree: the same launch also writes position ids (Section 3.3 "Execution view": prefix
 // length + depth) and the table of root-to-leaf paths that the gather and the acceptance step
 // consume, so nothing about the tree is computed on the host.
+#include <algorithm>
+
 #include "etv_common.h"
 
 namespace etv {
@@ -22,7 +24,7 @@ constexpr int kMaskWords = ETV_MAX_TREE / 64;
 // One workgroup and no bandwidth: what bounds it are the trips to memory and LDS in series.  Sizes, parents and the prefix length
 // come in one trip (the parent of a row behind the last node is read and dropped), the chain is walked once, and beyond 32 nodes
 // 256 threads share the dense mask and the padding whatever the node count is.  The dense mask of a large tree is spread over
-// several workgroups (blockIdx.y), each of which works out the few KiB of rows for itself; the first writes everything else.  With paths, in graphs: B = 1,
+// several workgroups (blockIdx.y, in batches that leave room for them), each of which works out the few KiB of rows for itself; the first writes everything else.  With paths, in graphs: B = 1,
 // T = 60 4.7 -> 3.8 us; B = 32, T = 128 6.9 -> 4.8; B = 4, T = 250 30.5 -> 5.0 (16.2 without the further workgroups).
 __global__ void __launch_bounds__(ETV_MAX_TREE) build_tree_mask_kernel(
     const int32_t *__restrict__ parent, const int32_t *__restrict__ n_nodes, int T_max, int words,
@@ -176,10 +178,13 @@ __global__ void __launch_bounds__(ETV_MAX_TREE) build_tree_mask_kernel(
     }
 }
 
-// beyond 32 nodes the dense mask is more work than the nodes
-static int mask_threads(int T_max) { return T_max <= 32 ? 64 : ETV_MAX_TREE; }
-// four words a thread and workgroup: 1 workgroup up to 64 nodes, 4 at 128, 16 at 256
-static int mask_parts(int T_max, const void *dense) { return dense ? (T_max * T_max + 4095) / 4096 : 1; }
+// Work beside the nodes' own (the dense mask, the padding of the paths) is shared by 256 threads from 33 nodes on, and a dense mask of more
+// than 64 nodes by several workgroups, four words a thread: 4 at 128 nodes, 16 at 256.  Both only while the launch leaves compute
+// units idle, up to two workgroups of 256 threads for each or four with the parts: beyond that further ones repeat the chains for
+// nothing.  Dense masks, B = 2048, T = 128 10.2 us with a workgroup a tree, 16.7 with four, 9.6 by this rule; B = 256, T = 256 9.1, 11.8
+// (sixteen) and 7.0; neither mask nor paths, B = 4096, T = 40 4.4 us with 64 threads, 6.0 with 256, 4.6.
+static int mask_threads(int B, int T_max, bool more_work) { return more_work && T_max > 32 && B <= 512 ? ETV_MAX_TREE : (T_max + 63) / 64 * 64; }
+static int mask_parts(int B, int T_max, const void *dense) { return dense ? std::max(1, std::min((T_max * T_max + 4095) / 4096, 1024 / B)) : 1; }
 
 }  // namespace etv
 
@@ -190,9 +195,9 @@ extern "C" int32_t etv_build_tree_mask(const int32_t *parent, const int32_t *n_n
     if (T_max < 1) return ETV_ERR_INVALID_ARG;
     if (T_max > ETV_MAX_TREE) return ETV_ERR_UNSUPPORTED;
     if (B == 0) return ETV_OK;
-    int threads = etv::mask_threads(T_max);
+    int threads = etv::mask_threads(B, T_max, dense != nullptr);
     int words = (T_max + 63) / 64;
-    hipLaunchKernelGGL(etv::build_tree_mask_kernel, dim3(B, etv::mask_parts(T_max, dense)), dim3(threads), 0, etv::as_stream(stream), parent,
+    hipLaunchKernelGGL(etv::build_tree_mask_kernel, dim3(B, etv::mask_parts(B, T_max, dense)), dim3(threads), 0, etv::as_stream(stream), parent,
                        n_nodes, (int)T_max, words, (const int32_t *)nullptr, bitmask, dense, depth, status,
                        (int32_t *)nullptr, (int32_t *)nullptr, (int32_t *)nullptr, 0, 0);
     return etv::check_launch();
@@ -208,9 +213,9 @@ extern "C" int32_t etv_tensorize_tree(const int32_t *parent, const int32_t *n_no
     if (T_max > ETV_MAX_TREE) return ETV_ERR_UNSUPPORTED;
     if ((long)L_max * W > (1l << 24)) return ETV_ERR_UNSUPPORTED;
     if (B == 0) return ETV_OK;
-    int threads = etv::mask_threads(T_max);
+    int threads = etv::mask_threads(B, T_max, true);
     int words = (T_max + 63) / 64;
-    hipLaunchKernelGGL(etv::build_tree_mask_kernel, dim3(B, etv::mask_parts(T_max, dense)), dim3(threads), 0, etv::as_stream(stream), parent,
+    hipLaunchKernelGGL(etv::build_tree_mask_kernel, dim3(B, etv::mask_parts(B, T_max, dense)), dim3(threads), 0, etv::as_stream(stream), parent,
                        n_nodes, (int)T_max, words, prefix_len, bitmask, dense, depth, status, position_ids, retrieve,
                        n_paths, (int)L_max, (int)W);
     return etv::check_launch();

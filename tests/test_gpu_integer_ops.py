@@ -85,6 +85,17 @@ def test_tensorize_deep_leaves_and_a_dense_mask_anywhere(T):
         assert np.array_equal(got[off:off + 3 * T * T], ref) and np.all(got[:off] == 9) and np.all(got[off + 3 * T * T:] == 9)
 
 
+@pytest.mark.parametrize("B,T", [(64, 256), (65, 255), (300, 256), (512, 40), (513, 40), (513, 101), (257, 128), (1025, 128)])
+def test_tree_tensors_of_large_batches(B, T):
+    """Batches at which a tree has sixteen workgroups for its dense mask, fifteen, three, two and one, and 256 threads or one for each node."""
+    rng = np.random.default_rng(9600 + B + T)
+    some = [random_tree(rng, T) for _ in range(7)]
+    par = np.stack([some[b % 7] for b in range(B)]).astype(np.int32)
+    n = np.where(np.arange(B) % 3 == 0, T, rng.integers(0, T + 1, size=B)).astype(np.int32)
+    _mask_case(par, n)
+    _tensorize_case(par, n, np.arange(B, dtype=np.int32), T, 12)
+
+
 def test_tensorize_shapes_of_the_workloads_invalid_trees_and_worked_example():
     ex = golden("worked_example.json")
     ref = _tensorize_case(np.asarray([ex["parent"]], dtype=np.int32), [7], [100], 4, 4)
