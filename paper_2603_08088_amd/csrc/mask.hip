@@ -16,7 +16,7 @@ constexpr int kMaskWords = ETV_MAX_TREE / 64;
 // (D_max+1) x T ancestor table, each thread follows its own parent chain (bounded by the
 // node count) and ORs the visited rows into registers: the same relation, no table.
 //
-// Paths (retrieve != nullptr): a leaf is a valid node that no valid node names as its parent; leaves are
+// Paths (PATHS): a leaf is a valid node that no valid node names as its parent; leaves are
 // ranked in ascending row order with one ballot per wavefront; the thread of the leaf ranked r writes row r from
 // the last sixteen nodes of its chain, kept in registers as they were visited (deeper leaves walk once more, back to
 // front), then pads the row with -1; rows beyond the last leaf are filled by all threads together.
@@ -26,6 +26,8 @@ constexpr int kMaskWords = ETV_MAX_TREE / 64;
 // 256 threads share the dense mask and the padding whatever the node count is.  The dense mask of a large tree is spread over
 // several workgroups (blockIdx.y, in batches that leave room for them), each of which works out the few KiB of rows for itself; the first writes everything else.  With paths, in graphs: B = 1,
 // T = 60 4.7 -> 3.8 us; B = 32, T = 128 6.9 -> 4.8; B = 4, T = 250 30.5 -> 5.0 (16.2 without the further workgroups).
+// Without paths nothing of a chain is kept but its bits (PATHS): bit mask of B = 4096, T = 128 6.5 -> 5.9 us, of B = 32, T = 60 3.03 -> 2.88.
+template <bool PATHS>
 __global__ void __launch_bounds__(ETV_MAX_TREE) build_tree_mask_kernel(
     const int32_t *__restrict__ parent, const int32_t *__restrict__ n_nodes, int T_max, int words,
     const int32_t *__restrict__ prefix_len, uint64_t *__restrict__ bitmask, uint8_t *__restrict__ dense, int32_t *__restrict__ depth,
@@ -42,7 +44,7 @@ __global__ void __launch_bounds__(ETV_MAX_TREE) build_tree_mask_kernel(
     const int n_raw = n_nodes[b];
     const int P_raw = prefix_len ? prefix_len[b] : 0;
     if (k == 0) s_status = 0;
-    s_child[k] = 0;
+    if constexpr (PATHS) s_child[k] = 0;
     const int n = clampi(n_raw, 0, T_max);
     int32_t st = 0, ep = 0;
     if (k < n) {
@@ -69,8 +71,10 @@ __global__ void __launch_bounds__(ETV_MAX_TREE) build_tree_mask_kernel(
 #pragma unroll
             for (int w = 0; w < kMaskWords; w++)
                 if ((cur >> 6) == w) bits[w] |= 1ull << (cur & 63);
-            chain_hi = chain_hi << 8 | chain >> 56;
-            chain = chain << 8 | (uint32_t)cur;
+            if constexpr (PATHS) {
+                chain_hi = chain_hi << 8 | chain >> 56;
+                chain = chain << 8 | (uint32_t)cur;
+            }
             cur = s_ep[cur];
             steps++;
         }
@@ -87,7 +91,8 @@ __global__ void __launch_bounds__(ETV_MAX_TREE) build_tree_mask_kernel(
             ep = 0;  // s_ep keeps the cycle: no chain that reaches the root passes it
         }
     }
-    if (k >= 1 && k < n) s_child[ep] = 1;
+    if constexpr (PATHS)
+        if (k >= 1 && k < n) s_child[ep] = 1;
     if (st) atomicOr(&s_status, st);
     if (k < T_max) {
 #pragma unroll
@@ -99,7 +104,7 @@ __global__ void __launch_bounds__(ETV_MAX_TREE) build_tree_mask_kernel(
         if (position_ids && part == 0) position_ids[(size_t)b * T_max + k] = max(P_raw, 0) + dep;
     }
     __syncthreads();
-    if (retrieve && part == 0) {
+    if (PATHS && part == 0) {
         const bool leaf = k < n && !s_child[k];
         const unsigned long long lb = __ballot(leaf);
         const int wv = k >> 6;
@@ -181,8 +186,8 @@ __global__ void __launch_bounds__(ETV_MAX_TREE) build_tree_mask_kernel(
 // Work beside the nodes' own (the dense mask, the padding of the paths) is shared by 256 threads from 33 nodes on, and a dense mask of more
 // than 64 nodes by several workgroups, four words a thread: 4 at 128 nodes, 16 at 256.  Both only while the launch leaves compute
 // units idle, up to two workgroups of 256 threads for each or four with the parts: beyond that further ones repeat the chains for
-// nothing.  Dense masks, B = 2048, T = 128 10.2 us with a workgroup a tree, 16.7 with four, 9.6 by this rule; B = 256, T = 256 9.1, 11.8
-// (sixteen) and 7.0; neither mask nor paths, B = 4096, T = 40 4.4 us with 64 threads, 6.0 with 256, 4.6.
+// nothing.  Dense masks, B = 2048, T = 128 10.2 us with a workgroup a tree, 16.7 with four, 9.3 by this rule; B = 256, T = 256 9.1, 11.8
+// (sixteen) and 6.8; neither mask nor paths, B = 4096, T = 40 4.4 us with 64 threads, 6.0 with 256.
 static int mask_threads(int B, int T_max, bool more_work) { return more_work && T_max > 32 && B <= 512 ? ETV_MAX_TREE : (T_max + 63) / 64 * 64; }
 static int mask_parts(int B, int T_max, const void *dense) { return dense ? std::max(1, std::min((T_max * T_max + 4095) / 4096, 1024 / B)) : 1; }
 
@@ -197,7 +202,7 @@ extern "C" int32_t etv_build_tree_mask(const int32_t *parent, const int32_t *n_n
     if (B == 0) return ETV_OK;
     int threads = etv::mask_threads(B, T_max, dense != nullptr);
     int words = (T_max + 63) / 64;
-    hipLaunchKernelGGL(etv::build_tree_mask_kernel, dim3(B, etv::mask_parts(B, T_max, dense)), dim3(threads), 0, etv::as_stream(stream), parent,
+    hipLaunchKernelGGL(etv::build_tree_mask_kernel<false>, dim3(B, etv::mask_parts(B, T_max, dense)), dim3(threads), 0, etv::as_stream(stream), parent,
                        n_nodes, (int)T_max, words, (const int32_t *)nullptr, bitmask, dense, depth, status,
                        (int32_t *)nullptr, (int32_t *)nullptr, (int32_t *)nullptr, 0, 0);
     return etv::check_launch();
@@ -215,7 +220,7 @@ extern "C" int32_t etv_tensorize_tree(const int32_t *parent, const int32_t *n_no
     if (B == 0) return ETV_OK;
     int threads = etv::mask_threads(B, T_max, true);
     int words = (T_max + 63) / 64;
-    hipLaunchKernelGGL(etv::build_tree_mask_kernel, dim3(B, etv::mask_parts(B, T_max, dense)), dim3(threads), 0, etv::as_stream(stream), parent,
+    hipLaunchKernelGGL(etv::build_tree_mask_kernel<true>, dim3(B, etv::mask_parts(B, T_max, dense)), dim3(threads), 0, etv::as_stream(stream), parent,
                        n_nodes, (int)T_max, words, prefix_len, bitmask, dense, depth, status, position_ids, retrieve,
                        n_paths, (int)L_max, (int)W);
     return etv::check_launch();
