@@ -314,22 +314,27 @@ __global__ void __launch_bounds__(64) attn_generic_kernel(AttnParams p) {
 // batch, whose loads are in flight together; further batches, for launches with more splits than that, update a
 // running (M, L, acc) that is rescaled when a later batch raises the maximum.  Lane i of every sixteen works out the weight of
 // split i % U, so a batch costs one exponential and a few lane moves instead of U exponentials in every lane.
-// What bounds it is latency: what the first addresses need are leading scalar arguments, as in the key-block kernel, and where
-// every sequence owns the same slots (!BALANCED) the first batch is asked for together with the sizes (the slots exist whatever the
-// lengths are, and what an absent one holds is not used).  Before, the arguments, two 64-bit divisions, the sizes and the
-// partials came one after the other: 32 layers of B = 1, T = 60, P = 2048 with four splits 470.7 -> 433.0 us, 63 drawn calls with
-// splits 6 % shorter on average, one sequence with 108 splits 16.6 -> 14.3.
+// What bounds it is latency: what the first addresses need are leading scalar arguments, as in the key-block kernel.  Before, the
+// arguments, two 64-bit divisions, the sizes and the partials came one after the other: 32 layers of B = 1, T = 60, P = 2048 with four
+// splits 470.7 -> 433.0 us, 63 drawn calls with splits 6 % shorter on average, one sequence with 108 splits 16.6 -> 14.3.
+// AHEAD: the first batch is asked for together with the sizes (every sequence owns the same slots, which exist whatever the lengths are;
+// what an absent one or a padded row's holds is not used).  That saves a trip, 0.2 ... 0.4 us of a call, and reads partials that nobody
+// wrote where P_max is a bound well above the prefixes or rows are padded: up to kCombineAhead bytes the trip is worth
+// more (T = 128, 2 splits, P_max = 1500, P = 750 11.6 -> 11.3 us with all nodes, 12 and 12 with a quarter), beyond it the bytes are (B = 1,
+// 32/8 heads, whole call: T = 256, 3 splits, 64 nodes 39.8, ahead 41.2; T = 128, 15 splits, P_max = 32768, P = 2048 57.4 and 59.1, with 32
+// nodes 43.8 and 46.5; B = 66, T = 16, 6 splits, P_max = 4096, P = 512 18.4 and 19.5).
 // SHARED: the four wavefronts of a workgroup take every fourth split of one row and merge through LDS, for launches whose
 // splits would otherwise be several batches in series.  32 rows, 43 splits: 9.0 -> 4.7 us; 16 rows, 107 splits: 18.2 -> 7.4;
 // with many rows the batches of different rows overlap anyway (1920 rows, 32 splits: 9.0, shared 11.2), and up to 16 splits
 // one wavefront's single batch is as fast or faster: a row whose sequence has no more is left to the first wavefront (whole
 // call, B = 2, T = 16, 32/8 heads, 24 equal splits launched and some 12 used 18.0 us, shared 20.1; one sequence with 24 10.7, 12.1).
-template <typename T, int D, int WPR, int U, bool SHARED, bool BALANCED>
+template <typename T, int D, int WPR, int U, bool SHARED, bool BALANCED, bool AHEAD>
 __global__ void __launch_bounds__(256)
 attn_combine_kernel(const int32_t *sizes, const int32_t *n_nodes, const float *part_o, const float *part_m, const float *part_l, int Hq,
                     uint32_t inv_hq, int T_max, int nsplit, AttnParams p) {
     constexpr int E = D / (64 * WPR);
     static_assert(E >= 1 && (!SHARED || WPR == 1), "at least one element per lane");
+    static_assert(!AHEAD || (!SHARED && !BALANCED), "slots that are known without the sizes");
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int row = SHARED ? (int)blockIdx.x : (int)blockIdx.x * (4 / WPR) + wv / WPR;  // of the sequence
     const int lane = (wv % WPR) * 64 + (threadIdx.x & 63);  // position within the row, in units of E elements
@@ -365,7 +370,7 @@ attn_combine_kernel(const int32_t *sizes, const int32_t *n_nodes, const float *p
         nvalid = ((const_i32_ptr)(uintptr_t)sizes)[2 * b + 1];
     } else {
         P_raw = ((const_i32_ptr)(uintptr_t)sizes)[b];
-        if constexpr (!SHARED) {
+        if constexpr (AHEAD) {
             fetch(pr_fixed, 0, 1, nsplit);
             // all of them here and now, with the arguments: one trip
             if constexpr (U == 8)
@@ -405,7 +410,7 @@ attn_combine_kernel(const int32_t *sizes, const int32_t *n_nodes, const float *p
     auto take = [&](auto every, int first) {  // splits first, first + every, ...
         constexpr int step = decltype(every)::value;
         for (int s0 = first; s0 < nvalid; s0 += U * step) {
-            if (BALANCED || SHARED || s0 > 0) fetch(pr0, s0, step, nvalid);
+            if (!AHEAD || s0 > 0) fetch(pr0, s0, step, nvalid);
             if (s0 + u_own * step >= nvalid) m_own = -INFINITY;
             const float Mb = fmaxf(M, over(m_own, [](float x, float y) { return fmaxf(x, y); }));
             if (Mb == -INFINITY) continue;  // nothing visible in this batch or before
@@ -2796,15 +2801,16 @@ static int32_t launch_f32_form(bool paged, const AttnParams &p, dim3 grid, hipSt
     }
 }
 
+constexpr size_t kCombineAhead = 8u << 20;  // see AHEAD
+
 template <typename T, int D, int WPR, int U, bool SHARED>
 static void launch_combine_form(const AttnParams &p, dim3 grid, hipStream_t st) {
-    const uint32_t inv_hq = fast_div_inv(p.Hq);
-    if (p.balanced)
-        hipLaunchKernelGGL((attn_combine_kernel<T, D, WPR, U, SHARED, true>), grid, dim3(256), 0, st, reinterpret_cast<const int32_t *>(p.split_tab),
-                           p.n_nodes, p.part_o, p.part_m, p.part_l, p.Hq, inv_hq, p.T_max, p.nsplit, p);
-    else
-        hipLaunchKernelGGL((attn_combine_kernel<T, D, WPR, U, SHARED, false>), grid, dim3(256), 0, st, p.prefix_len, p.n_nodes, p.part_o, p.part_m,
-                           p.part_l, p.Hq, inv_hq, p.T_max, p.nsplit, p);
+    const bool ahead = !SHARED && !p.balanced && (size_t)p.B * p.Hq * p.T_max * min(p.nsplit, U) * D * sizeof(float) <= kCombineAhead;
+    const auto kernel = p.balanced ? attn_combine_kernel<T, D, WPR, U, SHARED, true, false>
+                                   : (ahead ? attn_combine_kernel<T, D, WPR, U, SHARED, false, !SHARED>
+                                            : attn_combine_kernel<T, D, WPR, U, SHARED, false, false>);
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, p.balanced ? reinterpret_cast<const int32_t *>(p.split_tab) : p.prefix_len, p.n_nodes,
+                       p.part_o, p.part_m, p.part_l, p.Hq, fast_div_inv(p.Hq), p.T_max, p.nsplit, p);
 }
 template <typename T, int D, int WPR>
 static void launch_combine(const AttnParams &p, bool shared, hipStream_t st) {

@@ -491,6 +491,32 @@ def test_combine_of_many_splits(dtype, d):
             assert api.tree_verify_attention_plan(dsc)["n_splits"] >= 17
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_combine_of_equal_splits_whose_partials_are_large(dtype):
+    """More than 8 MiB of partials in a first batch of splits, which is then read behind the sizes: 3 splits of heads of 128 (batches of
+    eight), and 9 and 17 of heads of 64 (batches of sixteen, one and two).  Slots that nobody writes and padded rows."""
+    rng = np.random.default_rng(8950)
+    for d, Hq, P_max, P, n in ((128, 32, 192, 60, 70), (128, 32, 192, 192, 256), (64, 32, 576, 130, 256), (64, 16, 1088, 1080, 200)):
+        wl = _small(rng, 1, 256, Hq, 8, d, [P], dtype, True, n_nodes=[n])
+        dv = DevWorkload(wl)
+        width = P_max // synth.BLOCK
+        table = to_dev(np.pad(wl.block_table, ((0, 0), (0, max(0, width - wl.block_table.shape[1])))))
+        m = api.build_tree_mask(dv.parent, dv.n_nodes)
+        desc = api.attn_desc(dv.q, dv.kt, dv.k_cache, table, P_max, kv_split=64)
+        plan = api.tree_verify_attention_plan(desc)
+        assert plan["n_splits"] == P_max // 64 and not plan["balanced_splits"]
+        assert min(plan["n_splits"], 8 if plan["n_splits"] <= 8 else 16) * 256 * Hq * d * 4 > 8 << 20
+        out, lse = api.tree_verify_attention(dv.q, dv.k_cache, dv.v_cache, dv.prefix_len, dv.kt, dv.vt, m["bitmask"], dv.n_nodes, P_max=P_max,
+                                             block_table=table, desc=desc)
+        torch.cuda.synchronize()
+        ref, ref_lse = oracle.tree_verify_attention(wl.q, wl.k_cache, wl.v_cache, wl.prefix_len, wl.kt, wl.vt,
+                                                    oracle.build_tree_mask(wl.parent, wl.n_nodes)["dense"], wl.n_nodes, dtype=dtype,
+                                                    block_table=wl.block_table)
+        err, rel, padded_zero = attention_errors(out, ref, wl.n_nodes)
+        assert padded_zero and err <= TOL[dtype] and rel <= REL_TOL[dtype], (d, P_max, err, rel)
+        assert np.all(np.isneginf(to_host_f64(lse)[0, :, n:])) and np.abs(to_host_f64(lse)[0, :, :n] - ref_lse[0, :, :n]).max() <= (1e-4 if dtype == "f32" else 2e-2)
+
+
 def test_key_halves_merge_is_deterministic():
     """The merge of the two key halves has a fixed order: two launches on the same inputs give the same bits."""
     rng = np.random.default_rng(1800)
