@@ -2102,8 +2102,12 @@ attn_blocks_kernel(const int32_t *prefix_len, const int32_t *n_nodes, const int3
 // a look-up.
 // The chunks of one (split, KV head, sequence) re-read its K/V; their ids differ by 8, so they run side by side
 // on one XCD and find it in that XCD's L2.  Where there is one chunk, the loads stream past L2.
-// What bounds it: a tile is 64 matrix instructions, 0.86 us at d = 128 (0.43 at 64); two wavefronts of a SIMD take 1.05 us a tile
-// each, a lone one 1.47, so the plan fills two workgroups per compute unit.  The same loads spread between the matrix
+// What bounds it: a tile is 64 matrix instructions, 0.86 us at d = 128 (0.43 at 64); two wavefronts of a SIMD take 1.0 us a tile
+// each, a lone one 1.3, so the plan fills two workgroups per compute unit.  The wavefronts of a SIMD only gain from each other while one
+// multiplies and the other does not: without a priority of the products some of the kernel's forms ran them in step, others not
+// (B = 4, T = 120, 8/2 heads of 128, P = 9397, two equal splits: paged 174 us, contiguous 189, paged with shares by length 191; now 170 ...
+// 171), and with V read behind the softmax a lone wavefront took 1.47 us (B = 2, T = 100, 8/8 heads, P = 12000 292 us, now 276).  The
+// same loads spread between the matrix
 // instructions left V and K half the time to arrive (1.77 us a tile of a lone wavefront); eight wavefronts a workgroup in place of
 // two workgroups were 2 ... 4 % faster in launches that leave the chip idle and 7 % slower in large ones.
 //
@@ -2117,7 +2121,7 @@ attn_blocks_kernel(const int32_t *prefix_len, const int32_t *n_nodes, const int3
 // Against V straight to registers, K one tile ahead in LDS, and three trips to memory before the first load: B = 2, T = 33, 16/4
 // heads of 128, P = 771 / 1003 18.8 -> 16.6 us (graph of calls); B = 1, T = 8, 8/8 heads, P = 300 10.2 -> 7.7; T = 1, 8/2 heads, P =
 // 16384 17.9 -> 15.4; B = 12, T = 20, 32/32 heads of 64, P = 150 14.4 -> 12.7; B = 2, T = 200, 16/4 heads, P = 300 31.7 -> 27.8;
-// B = 16, T = 128, P = 2048, 32/8 heads of 128 657 -> 643, 110 TFLOP/s (the library's fp32 matrix product reaches 144 ... 154 on
+// B = 16, T = 128, P = 2048, 32/8 heads of 128 657 -> 627, 113 TFLOP/s (the library's fp32 matrix product reaches 144 ... 154 on
 // this machine).
 // ----------------------------------------------------------------------------------------------
 
@@ -2309,6 +2313,7 @@ attn_f32_kernel(const int32_t *prefix_len, const int32_t *n_nodes, const int32_t
             const uint32_t vis = tile_vis(t);
             wait_lds_reads();
             if (tn < nt) issue(tn, i0, i1, false);
+            __builtin_amdgcn_s_setprio(1);  // products ahead of the other wavefront's softmax
 #pragma unroll
             for (int j = 0; j < KJ; j += 2)
 #pragma unroll
@@ -2316,6 +2321,16 @@ attn_f32_kernel(const int32_t *prefix_len, const int32_t *n_nodes, const int32_t
                     s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[j][e], qf[j][e], s0, 0, 0, 0);
                     s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[j + 1][e], qf[j + 1][e], s1, 0, 0, 0);
                 }
+            __builtin_amdgcn_s_setprio(0);
+            if (tn < nt) wait_vmcnt<LOADS>();  // V of tile t (K of the next one may still be on its way)
+            else wait_vmcnt<0>();
+            asm volatile("" ::: "memory");
+            f32x4 vf[4][VB];
+#pragma unroll
+            for (int i = 0; i < 4; i++)
+#pragma unroll
+                for (int v = 0; v < VB; v++) vf[i][v] = *reinterpret_cast<const f32x4 *>(vrow + i * ROWB + 256 * v);
+            __builtin_amdgcn_sched_barrier(0);  // these reads fly during the softmax, which ends at the next one
             float sc[4];
 #pragma unroll
             for (int i = 0; i < 4; i++) sc[i] = ((vis >> (4 * g + i)) & 1u) ? (s0[i] + s1[i]) * p.scale_log2 : -INFINITY;
@@ -2336,14 +2351,7 @@ attn_f32_kernel(const int32_t *prefix_len, const int32_t *n_nodes, const int32_t
 #pragma unroll
             for (int i = 0; i < 4; i++) pr[i] = exp2f(sc[i] - ref);
             l_run += (pr[0] + pr[1]) + (pr[2] + pr[3]);
-            if (tn < nt) wait_vmcnt<LOADS>();  // V of tile t (K of the next one may still be on its way)
-            else wait_vmcnt<0>();
-            asm volatile("" ::: "memory");
-            f32x4 vf[4][VB];
-#pragma unroll
-            for (int i = 0; i < 4; i++)
-#pragma unroll
-                for (int v = 0; v < VB; v++) vf[i][v] = *reinterpret_cast<const f32x4 *>(vrow + i * ROWB + 256 * v);
+            __builtin_amdgcn_sched_barrier(0);
             wait_lds_reads();
             if (tn < nt) {
                 issue(tn, i0, i1, true);
@@ -2367,6 +2375,7 @@ attn_f32_kernel(const int32_t *prefix_len, const int32_t *n_nodes, const int32_t
                             for (int e = 0; e < 4; e++) vf[i][v][e] = fabsf(vf[i][v][e]) < INFINITY ? vf[i][v][e] : 0.f;
                 }
             }
+            __builtin_amdgcn_s_setprio(1);
 #pragma unroll
             for (int i = 0; i < 4; i++)
 #pragma unroll
@@ -2374,6 +2383,7 @@ attn_f32_kernel(const int32_t *prefix_len, const int32_t *n_nodes, const int32_t
 #pragma unroll
                     for (int e = 0; e < 4; e++)
                         o[v][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[i][v][e], pr[i], o[v][e], 0, 0, 0);
+            __builtin_amdgcn_s_setprio(0);
         }
     }
     if (ill) {
