@@ -45,6 +45,7 @@ struct AttnParams {
     int balanced;
     int2 *split_tab;
     uint32_t inv_g, inv_hkv, inv_nsplit, inv_chunk;  // floor(2^32 / G) and so on, for fast_div
+    int stagger;   // fp32 kernel: the second workgroup of a compute unit starts late
 };
 
 constexpr float kLn2 = 0.6931471805599453f;
@@ -2106,7 +2107,7 @@ attn_blocks_kernel(const int32_t *prefix_len, const int32_t *n_nodes, const int3
 // each, a lone one 1.3, so the plan fills two workgroups per compute unit.  The wavefronts of a SIMD only gain from each other while one
 // multiplies and the other does not: without a priority of the products some of the kernel's forms ran them in step, others not
 // (B = 4, T = 120, 8/2 heads of 128, P = 9397, two equal splits: paged 174 us, contiguous 189, paged with shares by length 191; now 170 ...
-// 171), and with V read behind the softmax a lone wavefront took 1.47 us (B = 2, T = 100, 8/8 heads, P = 12000 292 us, now 276).  The
+// 171), and with V read behind the softmax a lone wavefront took 1.47 us (B = 2, T = 100, 8/8 heads, P = 12000 292 us, now 276 ... 279).  The
 // same loads spread between the matrix
 // instructions left V and K half the time to arrive (1.77 us a tile of a lone wavefront); eight wavefronts a workgroup in place of
 // two workgroups were 2 ... 4 % faster in launches that leave the chip idle and 7 % slower in large ones.
@@ -2180,7 +2181,12 @@ attn_f32_kernel(const int32_t *prefix_len, const int32_t *n_nodes, const int32_t
     const int n_raw = BALANCED ? share.n_raw : ((const_i32_ptr)(uintptr_t)n_nodes)[b];
     const int P_raw = BALANCED ? share.P_raw : ((const_i32_ptr)(uintptr_t)prefix_len)[b];
     asm volatile("" ::"s"(n_raw), "s"(P_raw), "s"(blk0), "s"(p.q), "s"(p.k_cache), "s"(p.v_cache), "s"(p.kt), "s"(p.vt), "s"(p.bitmask),
-                 "s"(p.T_max), "s"(p.Hq), "s"(p.G), "s"(p.inv_g), "s"(p.P_cap), "s"(p.P_max), "s"(p.words), "s"(p.scale_log2));
+                 "s"(p.T_max), "s"(p.Hq), "s"(p.G), "s"(p.inv_g), "s"(p.P_cap), "s"(p.P_max), "s"(p.words), "s"(p.scale_log2), "s"(p.pairs),
+                 "s"(p.stagger));
+    // The two workgroups of a compute unit share its matrix cores evenly and end together, and where a third follows, some compute units
+    // then take two of these while as many take none (3, 4 and 2 workgroups on 228, 14 and 14).  With the second 32 of an XCD 3 us
+    // late the ends lie apart.
+    if (p.stagger && (((int)blockIdx.z * F32_GRID_Y + (int)blockIdx.y) * p.pairs + rg) >> 5 == 1) __builtin_amdgcn_s_sleep(127);
     const int n = clampi(n_raw, 0, p.T_max), P = clampi(P_raw, 0, p.P_max);
     const int nvalid = BALANCED ? share.nvalid : max(1, (int)fast_div(P + chunk - 1, chunk, inv_chunk, rem));
     if (s >= nvalid) return;  // uniform over the workgroup
@@ -2505,6 +2511,10 @@ constexpr double kTileWhole8 = 2.65;
 static long f32_blocks(const etv_attn_desc *h, const Plan &pl) {
     return ((long)h->B * pl.nsplit * h->Hkv + 7) / 8 * 8 * pl.pairs;
 }
+// fp32 kernel: workgroups of the fullest compute unit (the chunks of a (split, KV head, sequence) stay on one XCD, which takes every
+// eighth of these), and tiles of a wavefront that takes the tree's too
+static long f32_fullest(const etv_attn_desc *h, int chunks, int ns) { return (((long)max(1, h->B) * h->Hkv * ns + 7) / 8 * chunks + 31) / 32; }
+static int f32_tiles(const etv_attn_desc *h, int tps) { return (tps * (KT / F32_ROWS) + (h->T_max + F32_ROWS - 1) / F32_ROWS + F32_NW - 1) / F32_NW; }
 
 // bytes of the partial results of ns splits (and of the split table)
 static size_t split_workspace(const etv_attn_desc *h, int ns) {
@@ -2606,22 +2616,27 @@ static Plan make_plan(const etv_attn_desc *h) {
     pl.f32 = h->dtype == ETV_F32 && !generic;
     if (pl.f32) {
         // A workgroup puts one wavefront on each SIMD of a compute unit and the matrix cores bound the launch: its time is
-        // the tiles of a wavefront times the workgroups of the fullest compute unit, and not less than a tile's latency
-        // chain allows; every split adds partials and a combine step, the first one the combine launch.  Measured per tile:
-        // 1.05 us at d = 128 (0.6 at d = 64) times the wavefronts of a SIMD, 1.47 us (0.95) for a lone one, of which
-        // 0.86 (0.43) are matrix instructions.
+        // the tiles of a wavefront times the workgroups of the fullest compute unit, which run in twos (fours at d = 64) with an odd one by
+        // itself at the end, and a start for each such round; every split adds partials and a combine step, the first one the combine launch.
+        // The compute units that count are the fullest XCD's: the chunks of a (split, KV head, sequence) stay on one, which takes every
+        // eighth.  Measured per tile: 1.0 us at d = 128 (0.6 at d = 64) for each of an even number of workgroups, 1.38 us (0.7) for the odd one, 1.3
+        // (0.95) in a launch of lone ones; 0.86 (0.43) are matrix instructions.
+        // profiles/attention_f32_plan_picks.csv: 324 calls at up to twelve split counts.  Counted over all 256 compute units, an odd
+        // workgroup like any other, the choice is PICKOLD behind the best of them on average and up to PICKOLDMAX; so it is PICKNEW.
         pl.pairs = (int)((rows + F32_ROWS - 1) / F32_ROWS);
-        const double busy = h->d == 128 ? 1.05 : 0.6, chain = h->d == 128 ? 1.47 : 0.95;
-        const double part_us = 2.0 * B * h->Hq * h->T_max * (h->d + 2.0) * 4.0 / 3.0e6;
-        const long units = (long)B * h->Hkv * pl.pairs;
+        const bool d128 = h->d == 128;
+        const double busy = d128 ? 1.0 : 0.6, odd = d128 ? 1.38 : 0.7, lone = d128 ? 1.3 : 0.95;
+        const int together = d128 ? 2 : 4;
+        const double part_us = 0.4 * 2.0 * B * h->Hq * h->T_max * (h->d + 2.0) * 4.0 / 3.0e6;
         const int forced_tps = h->kv_split > 0 ? min(tiles, (h->kv_split + KT - 1) / KT) : 0;
         double best = 1e30;
         for (int ns = forced_tps ? (tiles + forced_tps - 1) / forced_tps : 1, tps; ns <= tiles; ns = forced_tps ? tiles + 1 : next_split_count(tiles, tps)) {
             tps = forced_tps ? forced_tps : (tiles + ns - 1) / ns;
             if (!forced_tps && beyond_array(h, ns)) break;
             const double per_wave = ceil((tps * 4.0 + (h->T_max + 15) / 16) / F32_NW);
-            const double full = ceil((double)(units * ns) / 256.0);
-            const double est = per_wave * (full * busy > chain ? full * busy : chain) + (ns > 1 ? 4.0 + ns * (part_us + 0.1) : 0.0);
+            const long full = (((long)B * h->Hkv * ns + 7) / 8 * pl.pairs + 31) / 32;
+            const double tile = full == 1 ? lone : ((full & 1) ? (full - 1) * busy + odd : full * busy);
+            const double est = per_wave * tile + (full + together - 1) / together * 3.0 + (ns > 1 ? 3.0 + ns * (part_us + 0.15) : 0.0);
             if (est < best) {
                 best = est;
                 pl.chunk = tps * KT; pl.nsplit = ns;
@@ -2962,6 +2977,11 @@ static int32_t attention_run(const etv_attn_desc *h, const void *q, const void *
                          : launch_mfma_shape<64>(pl, h->block_size > 0, p, grid, st);
     } else if (pl.f32) {
         const unsigned units8 = (unsigned)(((long)h->B * pl.nsplit * h->Hkv + 7) / 8);
+        // Three or five workgroups on the fullest compute unit, two at a time, of 24 tiles and more: shorter ones gain nothing, with seven
+        // and more it is lost in the rest, and at d = 64 four run at a time.
+        // B = 6, T = 64, 32/8 heads, P = 2000 148.7 -> 125.8 us, P = 1500 117.5 -> 99.2, B = 13, T = 48 170.0 -> 153.2.
+        const long full = f32_fullest(h, pl.pairs, pl.nsplit);
+        p.stagger = h->d == 128 && (full == 3 || full == 5) && f32_tiles(h, pl.chunk / KT) >= 24;
         const dim3 grid(8 * (unsigned)pl.pairs, min(units8, (unsigned)F32_GRID_Y), (units8 + F32_GRID_Y - 1) / F32_GRID_Y);
         rc = h->d == 128 ? launch_f32_form<128>(h->block_size > 0, p, grid, st) : launch_f32_form<64>(h->block_size > 0, p, grid, st);
     } else {

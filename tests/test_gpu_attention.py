@@ -259,6 +259,22 @@ def test_fp32_kernel_tree_rows_at_every_place_of_a_block(d, paged):
         _check(wl)
 
 
+@pytest.mark.parametrize("paged", [False, True])
+@pytest.mark.parametrize("B,kv_split", [(6, 4096), (3, 1536), (10, 4096)])
+def test_fp32_kernel_late_workgroups(B, kv_split, paged):
+    """Three and five workgroups on a compute unit, of 24 tiles a wavefront: the second 32 of each XCD start late.  16 chunks for 6 units an
+    XCD (sequences, and splits shared out by length) and for 10.  Few of the rows are nodes."""
+    rng = np.random.default_rng(3350 + B + paged)
+    P = [1490, 1500, 1411, 1500, 1, 1333, 1500, 0, 1499, 1472] if kv_split > 1536 else [3000, 2888, 2999]
+    n = [9, 64, 1, 3, 2, 5, 4, 1, 6, 2] if kv_split > 1536 else [5, 2, 64]
+    wl = _small(rng, B, 64, 32, 8, 128, P[:B], "f32", paged, n_nodes=n[:B])
+    dv = DevWorkload(wl)
+    plan = api.tree_verify_attention_plan(api.attn_desc(dv.q, dv.kt, dv.k_cache, dv.block_table, dv.P_max, kv_split=kv_split))
+    on_a_unit = -(-(-(-B * 8 * plan["n_splits"] // 8) * plan["row_groups"]) // 32)
+    assert on_a_unit == (5 if B == 10 else 3) and (plan["kv_split"] // 16 + 4 + 3) // 4 >= 24
+    _check(wl, kv_split=kv_split)
+
+
 def test_fp32_kernel_grid_beyond_its_second_dimension():
     """More than 32768 * 8 (sequence, KV head) units: the grid's third dimension.  One node over one prefix key, which torch can say
     in float64: 1e-5 as for every fp32 case."""
