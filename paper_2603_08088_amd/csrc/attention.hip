@@ -2618,11 +2618,10 @@ static Plan make_plan(const etv_attn_desc *h) {
         // A workgroup puts one wavefront on each SIMD of a compute unit and the matrix cores bound the launch: its time is
         // the tiles of a wavefront times the workgroups of the fullest compute unit, which run in twos (fours at d = 64) with an odd one by
         // itself at the end, and a start for each such round; every split adds partials and a combine step, the first one the combine launch.
-        // The compute units that count are the fullest XCD's: the chunks of a (split, KV head, sequence) stay on one, which takes every
-        // eighth.  Measured per tile: 1.0 us at d = 128 (0.6 at d = 64) for each of an even number of workgroups, 1.38 us (0.7) for the odd one, 1.3
-        // (0.95) in a launch of lone ones; 0.86 (0.43) are matrix instructions.
-        // profiles/attention_f32_plan_picks.csv: 324 calls at up to twelve split counts.  Counted over all 256 compute units, an odd
-        // workgroup like any other, the choice is PICKOLD behind the best of them on average and up to PICKOLDMAX; so it is PICKNEW.
+        // Measured per tile: 1.0 us at d = 128 (0.6 at d = 64) for each of an even number of workgroups, 1.38 us (0.7) for the odd one, 1.3
+        // (0.95) in a launch of lone ones; 0.86 (0.43) are matrix instructions.  The rest is fitted to 324 calls at up to twelve split counts
+        // (profiles/attention_f32_plan_picks.csv): the choice is 1.7 % behind the best count on average, with workgroups counted over
+        // all 256 compute units and an odd one priced like any other it was 3.2 %, and up to 52 %.
         pl.pairs = (int)((rows + F32_ROWS - 1) / F32_ROWS);
         const bool d128 = h->d == 128;
         const double busy = d128 ? 1.0 : 0.6, odd = d128 ? 1.38 : 0.7, lone = d128 ? 1.3 : 0.95;
