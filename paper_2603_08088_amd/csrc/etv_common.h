@@ -31,8 +31,9 @@ __device__ __forceinline__ uint16_t float_to_bf16_bits(float f) {
 
 __device__ __forceinline__ int clampi(int x, int lo, int hi) { return x < lo ? lo : (x > hi ? hi : x); }
 
-// x / d and x % d with inv = floor(2^32 / d), or one less: the estimate is at most one too small for any 32-bit x.  (The compiler's
-// general division is some forty dependent instructions, each 3.5 ns of a lone wavefront's start-up.)
+// x / d and x % d for any 32-bit x, with inv = floor(2^32 / d) or floor((2^32 - 1) / d), which differ where d is a power of two: the
+// estimate is at most one too small.  (A smaller inv is not enough: d = 3, inv = 0x55555554, x = 0xffffffff is two too small.  The
+// compiler's general division is some forty dependent instructions, each 3.5 ns of a lone wavefront's start-up.)
 __device__ __forceinline__ uint32_t fast_div(uint32_t x, uint32_t d, uint32_t inv, uint32_t &rem) {
     uint32_t q = __umulhi(x, inv);
     rem = x - q * d;

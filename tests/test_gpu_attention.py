@@ -234,13 +234,13 @@ def test_fp32_kernel_tree_rows_at_every_place_of_a_block(d, paged):
     """Tree rows in the cache behind prefixes of 80 ... 96 keys: a 16-key tile of the tree lies in one or two cache blocks, and the last
     of them is the table's last entry; one 16-row chunk per KV head (loads that stream) and several.  The bits of the separate buffer."""
     rng = np.random.default_rng(3300 + d + paged)
-    T, P = 40, list(range(80, 97))
-    n = [40, 32, 33, 1, 17, 16, 39] + [T] * 10
-    parents = [random_tree(rng, T) for _ in P]
-    for Hq, T_few in ((4, T), (2, 16)):
+    P = list(range(80, 97))
+    for Hq, T, chunks in ((4, 40, 5), (2, 16, 1)):
+        n = [min(x, T) for x in [40, 32, 33, 1, 17, 16, 39] + [T] * 10]
+        parents = [random_tree(rng, T) for _ in P]
         wl = synth.assemble("tail", rng, parents, P, Hq=Hq, Hkv=2, d=d, dtype="f32", V=512, W=T, paged=paged, T_max=T, with_logits=False,
                             spare_blocks=3, tail_room=T)
-        wl.n_nodes[:] = [min(x, T_few) for x in n]
+        wl.n_nodes[:] = n
         for b in range(len(P)):
             for j in range(n[b]):
                 pos = P[b] + j
@@ -251,6 +251,8 @@ def test_fp32_kernel_tree_rows_at_every_place_of_a_block(d, paged):
         dv = DevWorkload(wl)
         m = api.build_tree_mask(dv.parent, dv.n_nodes)
         for kv_split in (64, 4096):
+            desc = api.attn_desc(dv.q, None, dv.k_cache, dv.block_table, dv.P_max, kv_split=kv_split)
+            assert api.tree_verify_attention_plan(desc)["row_groups"] == chunks
             sep, lse_sep = gpu_attention(dv, m["bitmask"], kv_split=kv_split)
             tail, lse_tail = api.tree_verify_attention(dv.q, dv.k_cache, dv.v_cache, dv.prefix_len, None, None, m["bitmask"], dv.n_nodes,
                                                        P_max=dv.P_max, block_table=dv.block_table, kv_split=kv_split)

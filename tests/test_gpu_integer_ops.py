@@ -359,10 +359,10 @@ def test_fused_epilogue_matches_gather_acceptance_and_commit():
     _epilogue_case(synth.config5(16, 4, B=6, P=200), dummy=3)               # padding-heavy path table, dummy != 0
 
 
-@pytest.mark.parametrize("V,T,W,row", [(4096, 15, 5, 1), (32768, 33, 9, 4), (32772, 60, 6, 5), (65536, 12, 4, 2), (65540, 13, 4, 3),
+@pytest.mark.parametrize("V,T,W,row", [(4096, 15, 5, 1), (32768, 33, 9, 4), (32772, 60, 6, 5), (65536, 12, 4, 2), (65540, 12, 4, 3), (65540, 13, 4, 3),
                                        (300, 210, 20, 4), (300, 256, 16, 1), (300, 205, 5, 1), (300, 206, 5, 2)])
 def test_fused_epilogue_at_the_edges_of_its_forms(V, T, W, row):
-    """1, 8, 9, 16 and 17 partials a node; path tables that LDS holds (up to 1020 entries) and that it does not (1025 and more); gathered
+    """1, 8, 9, 16 and 17 partials a node, of 12 nodes the 17 too inside the kernel, of 13 by the launch ahead of it; path tables that LDS holds (up to 1020 entries) and that it does not (1025 and more); gathered
     rows of one to five words."""
     rng = np.random.default_rng(V + T)
     parents = [synth.tree_star(T) if T > 200 else synth.tree_bfs(rng, T, W - 1, 4), synth.tree_bfs(rng, T - 3, W - 1, 4)]

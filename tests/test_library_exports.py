@@ -3,6 +3,10 @@ import ctypes
 import os
 import re
 
+import numpy as np
+import pytest
+import torch
+
 from paper_2603_08088_amd import api
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -87,7 +91,6 @@ def test_launch_plan_is_reported_and_follows_the_tuning_flags():
 
 def test_the_kernel_of_a_plan_is_reported():
     """Host only: each kernel by a call that takes it on its own, and by the flag that asks for it."""
-    import pytest
 
     def kernel(flags=0, **kw):
         c = dict(dict(B=32, T_max=128, Hq=32, Hkv=8, d=128, dtype=api.BF16, P_cap=4096, P_max=4096, flags=flags), **kw)
@@ -127,10 +130,29 @@ def test_struct_layouts_match_the_header():
     assert ctypes.sizeof(api.CommitDesc) == 12 * 4 + 8
 
 
+@pytest.mark.parametrize("layers", [1, 3])
+def test_commit_descriptor_of_the_binding_is_the_struct(layers):
+    """What the binding builds from the shapes, byte for byte: paged and contiguous caches, every second layer of a larger one, and what it
+    leaves to Python (rows in the cache, a width that is no int, other layers)."""
+    B, T, Hkv, d, W = 2, 12, 3, 64, 5
+    for dtype in (torch.bfloat16, torch.float32):
+        kt = torch.zeros((layers, B, T, Hkv, d), dtype=dtype)
+        paged, table = torch.zeros((2 * layers, 7, Hkv, 16, d), dtype=dtype), torch.zeros((B, 4), dtype=torch.int32)
+        flat = torch.zeros((2 * layers, B, 40, Hkv, d), dtype=dtype)
+        for step in (1, 2):
+            pc, fc = paged[:step * layers:step], flat[:step * layers:step]
+            sp, sf = (pc.stride(0), fc.stride(0)) if layers > 1 else (pc.numel(), fc.numel())
+            e = dtype.itemsize
+            for cache, bt, tail in ((pc, table, (16, 4, 7, 0, 0, sp)), (fc, None, (0, 0, 0, 40, 0, sf))):
+                want = bytes(api.CommitDesc(B, T, Hkv, d, e, layers, W, *tail))
+                assert api._native().commit_desc(kt, cache, bt, W) == want
+                assert bytes(api._commit_desc(kt, cache, bt, np.int64(W))) == want and bytes(api._commit_desc(None, cache, bt, W, B, T)) == want
+                assert api._native().commit_desc(None, cache, bt, W) is None and api._native().commit_desc(kt, cache, bt, np.int64(W)) is None
+    assert api._native().commit_desc(kt, torch.zeros((layers + 1, B, 40, Hkv, d)), None, W) is None
+
+
 def test_binding_refuses_what_is_not_a_device_tensor_or_a_descriptor():
     """The native call path checks its arguments before anything is launched; it needs no GPU to do so."""
-    import pytest
-    import torch
     x = torch.zeros(8, dtype=torch.int32)
     call = api._native()
     with pytest.raises(AssertionError):          # host memory
@@ -151,9 +173,6 @@ def test_binding_refuses_what_is_not_a_device_tensor_or_a_descriptor():
 def test_binding_takes_every_integer_that_ctypes_takes():
     """Sizes come as ints, numpy integers or tensors of one element; what has no __index__ is refused.  Arguments are taken
     from left to right: the host tensor at the end is the one refused where the sizes before it are good."""
-    import numpy as np
-    import pytest
-    import torch
     call, x = api._native(), torch.zeros(8)
     for size in (8, True, np.int64(8), np.int32(8), np.uint8(8), torch.tensor(8), torch.tensor([8], dtype=torch.int32)):
         ctypes.c_int32.from_param(size)
@@ -167,8 +186,6 @@ def test_binding_takes_every_integer_that_ctypes_takes():
 
 
 def test_calls_refuse_queries_of_another_rank_and_rows_that_are_not_there():
-    import pytest
-    import torch
     x, ws = torch.zeros((2, 3, 8), dtype=torch.bfloat16), torch.zeros(256, dtype=torch.uint8)
     with pytest.raises(ValueError):      # a descriptor of its own does not make up for a q that is not [B, T, Hq, d]
         api.tree_verify_attention(x, x, x, x, x, x, x, x, P_max=1, desc=api.AttnDesc(), out=x, want_lse=False, workspace=ws)
