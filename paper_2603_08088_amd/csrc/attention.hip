@@ -318,24 +318,25 @@ __global__ void __launch_bounds__(64) attn_generic_kernel(AttnParams p) {
 // What bounds it is latency: what the first addresses need are leading scalar arguments, as in the key-block kernel.  Before, the
 // arguments, two 64-bit divisions, the sizes and the partials came one after the other: 32 layers of B = 1, T = 60, P = 2048 with four
 // splits 470.7 -> 433.0 us, 63 drawn calls with splits 6 % shorter on average, one sequence with 108 splits 16.6 -> 14.3.
-// AHEAD: the first batch is asked for together with the sizes (every sequence owns the same slots, which exist whatever the lengths are;
-// what an absent one or a padded row's holds is not used).  That saves a trip, 0.2 ... 0.4 us of a call, and reads partials that nobody
-// wrote where P_max is a bound well above the prefixes or rows are padded: up to kCombineAhead bytes the trip is worth
-// more (T = 128, 2 splits, P_max = 1500, P = 750 11.6 -> 11.3 us with all nodes, 12 and 12 with a quarter), beyond it the bytes are (B = 1,
-// 32/8 heads, whole call: T = 256, 3 splits, 64 nodes 39.8, ahead 41.2; T = 128, 15 splits, P_max = 32768, P = 2048 57.4 and 59.1, with 32
-// nodes 43.8 and 46.5; B = 66, T = 16, 6 splits, P_max = 4096, P = 512 18.4 and 19.5).
+// AHEAD: so many splits of the first batch are asked for together with the sizes (every sequence owns the same slots, which exist
+// whatever the lengths are; what an absent one or a padded row's holds is not used), the others of the batch behind them.  That
+// hides a trip, and reads partials that nobody wrote where P_max is a bound well above the prefixes or rows are padded.  Up to kCombineAhead
+// bytes the whole batch is worth it, beyond that two splits of kCombineAheadTwo, and none where even these are more.  B = 1, 32/8 heads,
+// whole call, whole batch / nothing / by this rule: T = 128, P_max = 32768 (15 splits), P = 32768 68.5 / 69.7 / 68.8 us, P = 2048 59.1 / 57.3 /
+// 57.3, with 16 nodes 42.5 / 39.4 / 39.5; P_max = P = 6000 (6 splits) 29.4 / 30.1 / 29.5; T = 256, P_max = 6000 (3 splits), 32 nodes, P = 375
+// 19.0 / 17.7 / 17.6; B = 66, T = 16, 4/1 heads (6 splits), P_max = 4096, P = 512 19.2 / 18.4 / 18.1.
 // SHARED: the four wavefronts of a workgroup take every fourth split of one row and merge through LDS, for launches whose
 // splits would otherwise be several batches in series.  32 rows, 43 splits: 9.0 -> 4.7 us; 16 rows, 107 splits: 18.2 -> 7.4;
 // with many rows the batches of different rows overlap anyway (1920 rows, 32 splits: 9.0, shared 11.2), and up to 16 splits
 // one wavefront's single batch is as fast or faster: a row whose sequence has no more is left to the first wavefront (whole
 // call, B = 2, T = 16, 32/8 heads, 24 equal splits launched and some 12 used 18.0 us, shared 20.1; one sequence with 24 10.7, 12.1).
-template <typename T, int D, int WPR, int U, bool SHARED, bool BALANCED, bool AHEAD>
+template <typename T, int D, int WPR, int U, bool SHARED, bool BALANCED, int AHEAD>
 __global__ void __launch_bounds__(256)
 attn_combine_kernel(const int32_t *sizes, const int32_t *n_nodes, const float *part_o, const float *part_m, const float *part_l, int Hq,
                     uint32_t inv_hq, int T_max, int nsplit, AttnParams p) {
     constexpr int E = D / (64 * WPR);
     static_assert(E >= 1 && (!SHARED || WPR == 1), "at least one element per lane");
-    static_assert(!AHEAD || (!SHARED && !BALANCED), "slots that are known without the sizes");
+    static_assert(AHEAD == 0 || (!SHARED && !BALANCED && (AHEAD == 2 || AHEAD == U)), "slots that are known without the sizes");
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int row = SHARED ? (int)blockIdx.x : (int)blockIdx.x * (4 / WPR) + wv / WPR;  // of the sequence
     const int lane = (wv % WPR) * 64 + (threadIdx.x & 63);  // position within the row, in units of E elements
@@ -352,16 +353,25 @@ attn_combine_kernel(const int32_t *sizes, const int32_t *n_nodes, const float *p
     const int u_own = threadIdx.x & (U - 1);
     float m_own, l_own;
     elems os[U];
-    auto fetch = [&](size_t pr0, int first, int step, int count) {
+    auto fetch_part = [&](auto from, auto to, size_t pr0, int first, int step, int count) {  // elements of the batch's splits from ... to - 1
+#pragma unroll
+        for (int u = decltype(from)::value; u < decltype(to)::value; u++) {
+            const int x = first + u * step;
+            os[u] = *reinterpret_cast<const elems *>(part_o + (pr0 + (size_t)(uint32_t)(x < count ? x : 0) * sstride) * D + (size_t)lane * E);
+        }
+    };
+    auto fetch_own = [&](size_t pr0, int first, int step, int count) {
         const int own = first + u_own * step;
         const size_t r_own = pr0 + (size_t)(uint32_t)(own < count ? own : 0) * sstride;
         m_own = part_m[r_own];
         l_own = part_l[r_own];
-#pragma unroll
-        for (int u = 0; u < U; u++) {
-            const int x = first + u * step;
-            os[u] = *reinterpret_cast<const elems *>(part_o + (pr0 + (size_t)(uint32_t)(x < count ? x : 0) * sstride) * D + (size_t)lane * E);
-        }
+    };
+    constexpr std::integral_constant<int, 0> none;
+    constexpr std::integral_constant<int, AHEAD> ahead;
+    constexpr std::integral_constant<int, U> all;
+    auto fetch = [&](size_t pr0, int first, int step, int count) {
+        fetch_own(pr0, first, step, count);
+        fetch_part(none, all, pr0, first, step, count);
     };
     const size_t pr_fixed = ((size_t)((uint32_t)b * nsplit) * Hq + h) * T_max + k;
     const int n_raw = ((const_i32_ptr)(uintptr_t)n_nodes)[b];
@@ -371,7 +381,7 @@ attn_combine_kernel(const int32_t *sizes, const int32_t *n_nodes, const float *p
         nvalid = ((const_i32_ptr)(uintptr_t)sizes)[2 * b + 1];
     } else {
         P_raw = ((const_i32_ptr)(uintptr_t)sizes)[b];
-        if constexpr (AHEAD) {
+        if constexpr (AHEAD == U) {
             fetch(pr_fixed, 0, 1, nsplit);
             // all of them here and now, with the arguments: one trip
             if constexpr (U == 8)
@@ -381,6 +391,11 @@ attn_combine_kernel(const int32_t *sizes, const int32_t *n_nodes, const float *p
                 asm volatile("" ::"s"(n_raw), "s"(P_raw), "s"(p.P_max), "s"(p.chunk), "s"(p.inv_chunk), "s"(p.out), "s"(p.lse), "v"(m_own), "v"(l_own),
                              "v"(os[0]), "v"(os[1]), "v"(os[2]), "v"(os[3]), "v"(os[4]), "v"(os[5]), "v"(os[6]), "v"(os[7]), "v"(os[U - 8]),
                              "v"(os[U - 7]), "v"(os[U - 6]), "v"(os[U - 5]), "v"(os[U - 4]), "v"(os[U - 3]), "v"(os[U - 2]), "v"(os[U - 1]));
+        } else if constexpr (AHEAD > 0) {
+            fetch_own(pr_fixed, 0, 1, nsplit);
+            fetch_part(none, ahead, pr_fixed, 0, 1, nsplit);
+            __builtin_amdgcn_sched_barrier(0);
+            asm volatile("" ::"s"(n_raw), "s"(P_raw), "s"(p.P_max), "s"(p.chunk), "s"(p.inv_chunk), "s"(p.out), "s"(p.lse));
         }
         uint32_t rem;
         nvalid = max(1, (int)fast_div(clampi(P_raw, 0, p.P_max) + p.chunk - 1, p.chunk, p.inv_chunk, rem));
@@ -393,6 +408,7 @@ attn_combine_kernel(const int32_t *sizes, const int32_t *n_nodes, const float *p
         return;
     }
     const size_t pr0 = BALANCED ? ((size_t)(uint32_t)first_slot * Hq + h) * T_max + k : pr_fixed;
+    if constexpr (AHEAD > 0 && AHEAD < U) fetch_part(ahead, all, pr0, 0, 1, nvalid);
     // (splits shared out by length: a sequence may have far fewer than nsplit)
     const bool many = SHARED && nvalid > U;
     if (SHARED && !many && wv > 0) return;  // uniform over the workgroup, as below
@@ -411,7 +427,7 @@ attn_combine_kernel(const int32_t *sizes, const int32_t *n_nodes, const float *p
     auto take = [&](auto every, int first) {  // splits first, first + every, ...
         constexpr int step = decltype(every)::value;
         for (int s0 = first; s0 < nvalid; s0 += U * step) {
-            if (!AHEAD || s0 > 0) fetch(pr0, s0, step, nvalid);
+            if (AHEAD == 0 || s0 > 0) fetch(pr0, s0, step, nvalid);
             if (s0 + u_own * step >= nvalid) m_own = -INFINITY;
             const float Mb = fmaxf(M, over(m_own, [](float x, float y) { return fmaxf(x, y); }));
             if (Mb == -INFINITY) continue;  // nothing visible in this batch or before
@@ -2825,14 +2841,16 @@ static int32_t launch_f32_form(bool paged, const AttnParams &p, dim3 grid, hipSt
     }
 }
 
-constexpr size_t kCombineAhead = 8u << 20;  // see AHEAD
+constexpr size_t kCombineAhead = 8u << 20, kCombineAheadTwo = 5u << 20;  // see AHEAD
 
 template <typename T, int D, int WPR, int U, bool SHARED>
 static void launch_combine_form(const AttnParams &p, dim3 grid, hipStream_t st) {
-    const bool ahead = !SHARED && !p.balanced && (size_t)p.B * p.Hq * p.T_max * min(p.nsplit, U) * D * sizeof(float) <= kCombineAhead;
-    const auto kernel = p.balanced ? attn_combine_kernel<T, D, WPR, U, SHARED, true, false>
-                                   : (ahead ? attn_combine_kernel<T, D, WPR, U, SHARED, false, !SHARED>
-                                            : attn_combine_kernel<T, D, WPR, U, SHARED, false, false>);
+    const size_t split_bytes = (size_t)p.B * p.Hq * p.T_max * D * sizeof(float);
+    const bool fixed = !SHARED && !p.balanced;
+    const auto kernel = p.balanced ? attn_combine_kernel<T, D, WPR, U, SHARED, true, 0>
+                        : fixed && min(p.nsplit, U) * split_bytes <= kCombineAhead ? attn_combine_kernel<T, D, WPR, U, SHARED, false, SHARED ? 0 : U>
+                        : fixed && 2 * split_bytes <= kCombineAheadTwo ? attn_combine_kernel<T, D, WPR, U, SHARED, false, SHARED ? 0 : 2>
+                                                                       : attn_combine_kernel<T, D, WPR, U, SHARED, false, 0>;
     hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, p.balanced ? reinterpret_cast<const int32_t *>(p.split_tab) : p.prefix_len, p.n_nodes,
                        p.part_o, p.part_m, p.part_l, p.Hq, fast_div_inv(p.Hq), p.T_max, p.nsplit, p);
 }

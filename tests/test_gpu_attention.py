@@ -511,10 +511,12 @@ def test_combine_of_many_splits(dtype, d):
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_combine_of_equal_splits_whose_partials_are_large(dtype):
-    """More than 8 MiB of partials in a first batch of splits, which is then read behind the sizes: 3 splits of heads of 128 (batches of
-    eight), and 9 and 17 of heads of 64 (batches of sixteen, one and two).  Slots that nobody writes and padded rows."""
+    """More than 8 MiB of partials in a first batch of splits, which is then read behind the sizes, all of it or all but two splits: 3 and 5
+    splits of heads of 128 (batches of eight), and 9 and 17 of heads of 64 (batches of sixteen, one and two).  Slots that nobody writes
+    and padded rows."""
     rng = np.random.default_rng(8950)
-    for d, Hq, P_max, P, n in ((128, 32, 192, 60, 70), (128, 32, 192, 192, 256), (64, 32, 576, 130, 256), (64, 16, 1088, 1080, 200)):
+    for d, Hq, P_max, P, n in ((128, 32, 192, 60, 70), (128, 32, 192, 192, 256), (128, 16, 320, 100, 200), (128, 16, 320, 320, 256),
+                                (64, 64, 576, 130, 100), (64, 32, 576, 130, 256), (64, 16, 1088, 1080, 200)):
         wl = _small(rng, 1, 256, Hq, 8, d, [P], dtype, True, n_nodes=[n])
         dv = DevWorkload(wl)
         width = P_max // synth.BLOCK
