@@ -42,10 +42,10 @@ struct AttnParams {
     // mfma kernel, batches of 2 .. 64 sequences with splits: the B * nsplit split slots are shared out among the
     // sequences by their lengths (on the device, where the lengths are), slot-major partials
     //   part_o [B * nsplit][Hq][T_max][d]; split_tab[b] = (first slot, splits in use) for the combine kernel
+    int stagger;  // fp32 kernel: chunks of a KV head if the second workgroup of a compute unit starts late, else 0
     int balanced;
     int2 *split_tab;
     uint32_t inv_g, inv_hkv, inv_nsplit, inv_chunk;  // floor(2^32 / G) and so on, for fast_div
-    int stagger;   // fp32 kernel: the second workgroup of a compute unit starts late
 };
 
 constexpr float kLn2 = 0.6931471805599453f;
@@ -2197,12 +2197,11 @@ attn_f32_kernel(const int32_t *prefix_len, const int32_t *n_nodes, const int32_t
     const int n_raw = BALANCED ? share.n_raw : ((const_i32_ptr)(uintptr_t)n_nodes)[b];
     const int P_raw = BALANCED ? share.P_raw : ((const_i32_ptr)(uintptr_t)prefix_len)[b];
     asm volatile("" ::"s"(n_raw), "s"(P_raw), "s"(blk0), "s"(p.q), "s"(p.k_cache), "s"(p.v_cache), "s"(p.kt), "s"(p.vt), "s"(p.bitmask),
-                 "s"(p.T_max), "s"(p.Hq), "s"(p.G), "s"(p.inv_g), "s"(p.P_cap), "s"(p.P_max), "s"(p.words), "s"(p.scale_log2), "s"(p.pairs),
-                 "s"(p.stagger));
+                 "s"(p.T_max), "s"(p.Hq), "s"(p.G), "s"(p.inv_g), "s"(p.P_cap), "s"(p.P_max), "s"(p.words), "s"(p.scale_log2), "s"(p.stagger));
     // The two workgroups of a compute unit share its matrix cores evenly and end together, and where a third follows, some compute units
     // then take two of these while as many take none (3, 4 and 2 workgroups on 228, 14 and 14).  With the second 32 of an XCD 3 us
     // late the ends lie apart.
-    if (p.stagger && (((int)blockIdx.z * F32_GRID_Y + (int)blockIdx.y) * p.pairs + rg) >> 5 == 1) __builtin_amdgcn_s_sleep(127);
+    if (p.stagger && ((int)blockIdx.y * p.stagger + rg) >> 5 == 1) __builtin_amdgcn_s_sleep(127);
     const int n = clampi(n_raw, 0, p.T_max), P = clampi(P_raw, 0, p.P_max);
     const int nvalid = BALANCED ? share.nvalid : max(1, (int)fast_div(P + chunk - 1, chunk, inv_chunk, rem));
     if (s >= nvalid) return;  // uniform over the workgroup
@@ -2998,7 +2997,7 @@ static int32_t attention_run(const etv_attn_desc *h, const void *q, const void *
         // and more it is lost in the rest, and at d = 64 four run at a time.
         // B = 6, T = 64, 32/8 heads, P = 2000 148.7 -> 125.8 us, P = 1500 117.5 -> 99.2, B = 13, T = 48 170.0 -> 153.2.
         const long full = f32_fullest(h, pl.pairs, pl.nsplit);
-        p.stagger = h->d == 128 && (full == 3 || full == 5) && f32_tiles(h, pl.chunk / KT) >= 24;
+        p.stagger = h->d == 128 && (full == 3 || full == 5) && f32_tiles(h, pl.chunk / KT) >= 24 ? pl.pairs : 0;
         const dim3 grid(8 * (unsigned)pl.pairs, min(units8, (unsigned)F32_GRID_Y), (units8 + F32_GRID_Y - 1) / F32_GRID_Y);
         rc = h->d == 128 ? launch_f32_form<128>(h->block_size > 0, p, grid, st) : launch_f32_form<64>(h->block_size > 0, p, grid, st);
     } else {
