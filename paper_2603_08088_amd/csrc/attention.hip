@@ -1792,22 +1792,19 @@ attn_wide_kernel(const int32_t *prefix_len, const int32_t *n_nodes, const uint64
 // Start-up is a third of a short launch, so it is one trip to memory: what the first addresses need are leading scalar arguments,
 // which are in registers when the kernel starts (the -amdgpu-kernarg-preload-count of the build), and the sequence's sizes, the
 // first block ids and the other arguments are asked for together.  K of the first block goes out first, then Q, then V.  The
-// loads of a block with masked keys know their block ids beforehand too; with a look-up per lane and load the wavefronts of
-// such blocks came to the first barrier 2.3 us after the others (paged, P = 200, T = 30: 8.7 us from the first to the last
-// instruction, now 7.0).  Whether K/V bytes have one reader and whether the split slots follow the lengths are template
-// arguments: a branch per load, and a wait for the arguments before the sizes are asked for, otherwise.  What bounds a step is the LDS pipe (K and V written, read once
-// for 32 rows: 256 KiB per compute unit and step) and, with one chunk, the latency of the next block.
+// loads of a block with masked keys know their block ids beforehand too (a look-up per lane and load kept these wavefronts from the
+// first barrier for 2.3 us).  Whether K/V bytes have one reader and whether the split slots follow the lengths are template
+// arguments: a branch per load, and a wait for the arguments before the sizes are asked for, otherwise.
+// What bounds a step is the LDS pipe (K and V written, read once for 32 rows: 256 KiB per compute unit and step) and, with one chunk, the
+// latency of the next block.  Behind the start-up a launch of two or three steps is a chain of instructions, one every 3.5 ns: the
+// fragments of a product are all read before the first of its instructions (the compiler takes them two by two and waits each time), zeros
+// and LDS addresses are ready before the sizes arrive, K of the next block is asked for beside the products of this one, and the merge reads all
+// eight outputs without a branch (wavefronts without a block leave zeros), also where there are one or two blocks.
 //
-// Against the tile kernel: B = 1, 32/8 heads of 128, T = 60, P = 2048 16.1 -> 14.0 us (4 splits instead of 8); P = 500 13.5 -> 9.4;
-// T = 8, P = 4096 14.5 -> 13.0; T = 128, P = 1024 17.8 -> 12.1.  B = 4, T = 60, P = 1000 21.6 -> 14.6; B = 32, T = 8, P = 4096
-// 87.4 -> 82.7 us (128 KiB in flight per compute unit: 6.5 TB/s).  By the start-up and edge loads above: 32 layers of B = 1, T = 60,
-// P = 2048 510 -> 471 us (with the combine launches); heads of 64, B = 4, T = 48, P = 900 ... 1500 13.4 -> 11.5; 68 drawn calls
-// below 40 MB 16 % shorter on average.
-// Behind the start-up a launch of two or three steps is a chain of instructions, one every 3.5 ns: the fragments of a product are all read
-// before the first of its instructions (the compiler takes them two by two and waits each time), zeros and LDS addresses are
-// ready before the sizes arrive, K of the next block is asked for beside the products of this one, and the merge reads all
-// eight outputs without a branch (wavefronts without a block leave zeros).  The 32 layers 430 -> 422 us, heads of 64 11.43 -> 11.27,
-// B = 32, T = 8, P = 4096 81.7 -> 81.3; the merge with a second copy for launches of fewer wavefronts was slower than before.
+// Against the tile kernel: B = 1, 32/8 heads of 128, T = 60, P = 2048 16.1 -> 12.0 us (4 splits instead of 8); B = 32, T = 8,
+// P = 4096 87.4 -> 82 (128 KiB in flight per compute unit: 6.6 TB/s).  The start-up and the chain, against three trips and
+// fragments two by two: 32 layers of B = 1, T = 60, P = 2048 510 -> 421 us (with the combine launches); heads of 64, B = 4, T = 48,
+// P = 900 ... 1500 13.3 -> 11.25; B = 1, T = 4 ... 60, P = 0 ... 40 5.4 ... 6.0 -> 5.1 ... 5.5, P = 200 7.7 ... 9.5 -> 6.5 ... 7.4.
 // ----------------------------------------------------------------------------------------------
 constexpr int KB_NW = 8;     // wavefronts of a workgroup
 constexpr int KB_KEYS = 32;  // keys of a block

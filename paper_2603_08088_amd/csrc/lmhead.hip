@@ -651,7 +651,7 @@ __global__ void __launch_bounds__(512, 2) lm_head_argmax_gemm_kernel(LhParams p)
 // One wavefront per node row: reduce the per-tile partials (lowest index among equals); padded rows give -1.  Latency is all
 // there is to it: one trip to memory behind the kernel arguments, and lane moves of the vector unit instead of shuffles through LDS.
 // U partials per lane and trip: 1 up to 64 partials, where further loads of the same line only cost their issue (V = 1000, D = 1408,
-// head and finish: 0.2 of 12 us).  Head and finish of 60 rows, D = 4096, V = 32000: 45.4 -> 44.8 us by the lane moves.
+// head and finish: 0.2 of 12 us).  Head and finish of 60 rows, D = 4096, V = 32000: 45 ... 46 us, with shuffles too.
 template <int U>
 __global__ void __launch_bounds__(256) lm_head_finish_kernel(const float *__restrict__ pval,
                                                             const int32_t *__restrict__ pidx, const int32_t *__restrict__ n_nodes,
